@@ -92,7 +92,7 @@ struct revffn_ctx {
   // backward
   void *dRS, *dYp, *dYs, *dHs, *dGUs, *dUm_sh, *dHh, *dGU, *dXg, *dUm, *dn3, *g1;
   float *dw, *dzext, *rinv, *rinv3, *partial;
-  float *splitk_ws, *splitk_ws_r;   // split-k slices: weight-gradient side, router side (fold, then logits)
+  float* zraw;                      // router logits before the 1/rms scale [T, E1]
   bool fold_queued = false;         // the router fold of this call is already enqueued on helper stream 2
   // the workspace still holds every activation of this revffn_forward call (stored-activation backward)
   const void *fwd_x1 = nullptr, *fwd_x2 = nullptr, *fwd_y1 = nullptr;
@@ -108,12 +108,10 @@ struct revffn_ctx {
 
 namespace {
 
-const int BM_A = 64;    // m-tile height of the generic grouped GEMM
+const int BM_A = 32;    // m-tile height of the generic grouped GEMM
 const int BM_B = 128;   // m-tile heights of the MFMA grouped GEMM (list b is built 160 rows high instead where that
 const int BM_C = 256;   // holds a typical expert, see expert_rows_b)
 const int BM_B_MID = 160;
-// k-slices of the small fp32 GEMMs around the router (each would otherwise run on a handful of CUs)
-const int SPLIT_FOLD = 16, SPLIT_LOGITS = 16, SPLIT_DWR = 32;
 
 int check_cfg(const revffn_config* c) {
   if (!c) return REVFFN_ENULL;
@@ -216,11 +214,7 @@ size_t carve(revffn_ctx* c, char* base) {
   c->wr_ext = cv.take(E1p * d * es);
   c->dzb = cv.take(T * E1p * 2);
   c->dUm_r = cv.take(T * d * es);
-  {
-    size_t a = SPLIT_FOLD * E1 * h, b2 = SPLIT_LOGITS * T * E1, c3 = SPLIT_DWR * E1 * d;
-    c->splitk_ws_r = (float*)cv.take((a > b2 ? a : b2) * 4);
-    c->splitk_ws = (float*)cv.take(c3 * 4);
-  }
+  c->zraw = (float*)cv.take(T * E1 * 4);
   c->rinv = (float*)cv.take(2 * T * 4);
   c->rinv3 = (float*)cv.take(T * 4);
   size_t maxcols = d > E1 ? d : E1;
@@ -378,11 +372,11 @@ void p_rope(revffn_ctx* c, int dt, void* buf, const float* cs, int T, int S, int
   launch_rope(dt, buf, cs, T, S, H, dh, sign, s, buf2, skip);
   ps.done(KID_ROPE);
 }
-void p_router(revffn_ctx* c, int dt, const void* y1, i64 ld, const float* zparts, int n_parts, const float* b_router,
+void p_router(revffn_ctx* c, int dt, const void* y1, i64 ld, const float* zraw, const float* b_router,
               float* probs, int* idx, float* wts, float* gamma, int T, int h, int E, int k, int has_gate, int norm_topk,
               float eps, hipStream_t s) {
-  ProfScope ps(c, s, 0, (double)T * (h * esz(dt) + (double)n_parts * (E + has_gate) * 4 + E * 4 + k * 8 + has_gate * 4));
-  launch_router(dt, y1, ld, zparts, n_parts, b_router, probs, idx, wts, gamma, T, h, E, k, has_gate, norm_topk, eps, s);
+  ProfScope ps(c, s, 0, (double)T * (h * esz(dt) + (E + has_gate) * 4.0 + E * 4 + k * 8 + has_gate * 4));
+  launch_router(dt, y1, ld, zraw, b_router, probs, idx, wts, gamma, T, h, E, k, has_gate, norm_topk, eps, s);
   ps.done(KID_ROUTER);
 }
 void p_permute(revffn_ctx* c, const int* idx, int T, int k, int E, int* counts, int* offsets, int* row_map, int* inv_map,
@@ -620,8 +614,8 @@ void router_fold(revffn_ctx* c, const revffn_weights* w, hipStream_t s, float* d
     ps.done(KID_COPY_ROWS);
   }
   GemmArgs a = nn(c->wr_ext, d, w->pup_m, h, dst ? dst : c->wrp, h, E + (Is ? 1 : 0), h, d);
-  a.split_k = SPLIT_FOLD; a.splitk_ws = c->splitk_ws_r; a.col_scale = w->norm_m;
-  (void)run_gemm(c, a, dt, dt, 0, sr);
+  a.col_scale = w->norm_m;
+  (void)launch_gemm_generic(a, GemmTypes{dt, dt, 0, dt}, sr);
   if (!dst) c->fold_queued = true;
 }
 
@@ -653,12 +647,11 @@ int moe_acts(revffn_ctx* c, const revffn_weights* w, const void* y1, i64 ld, int
   else router_fold(c, w, s);              // (forks from s as well)
   c->fold_queued = false;
   {
-    GemmArgs z = nt(y1, ld, c->wrp, h, c->splitk_ws_r, E1, T, E1, h);
-    z.split_k = SPLIT_LOGITS; z.splitk_ws = c->splitk_ws_r; z.splitk_raw = 1;   // the router kernel adds the slices
+    GemmArgs z = nt(y1, ld, c->wrp, h, c->zraw, E1, T, E1, h);
     GemmTypes tz{c->sdt, 0, 0, dt};
     if (launch_gemm_generic(z, tz, sr)) return REVFFN_EUNSUPPORTED;
   }
-  p_router(c, c->sdt, y1, ld, c->splitk_ws_r, SPLIT_LOGITS, w->b_router, c->probs, c->idx, c->wts, c->gamma, T, h, E, k,
+  p_router(c, c->sdt, y1, ld, c->zraw, w->b_router, c->probs, c->idx, c->wts, c->gamma, T, h, E, k,
                 Is ? 1 : 0, f.norm_topk_prob, f.rms_eps, sr);
   TileLists tl{{c->tg_a, c->tg_b, c->tg_c}, {c->tm_a, c->tm_b, c->tm_c}, {c->tf_a, c->tf_b, c->tf_c},
                {c->max_tiles_a, c->max_tiles_b, c->max_tiles_c}, {BM_A, c->bm_b, BM_C}, c->tile_cnt};
@@ -795,12 +788,11 @@ int moe_merged(revffn_ctx* c, const revffn_weights* w, const revffn_merged* m, c
   hipStream_t sr = side(c, s, 2), s0 = side(c, s, 0);
   after(c, s, sr);
   {
-    GemmArgs z = nt(y1, ld, m->w_router, h, c->splitk_ws_r, E1, T, E1, h);
-    z.split_k = SPLIT_LOGITS; z.splitk_ws = c->splitk_ws_r; z.splitk_raw = 1;
+    GemmArgs z = nt(y1, ld, m->w_router, h, c->zraw, E1, T, E1, h);
     GemmTypes tz{c->sdt, 0, 0, dt};
     if (launch_gemm_generic(z, tz, sr)) return REVFFN_EUNSUPPORTED;
   }
-  p_router(c, c->sdt, y1, ld, c->splitk_ws_r, SPLIT_LOGITS, w->b_router, c->probs, c->idx, c->wts, c->gamma, T, h, E, k,
+  p_router(c, c->sdt, y1, ld, c->zraw, w->b_router, c->probs, c->idx, c->wts, c->gamma, T, h, E, k,
            Is ? 1 : 0, f.norm_topk_prob, f.rms_eps, sr);
   TileLists tl{{c->tg_a, c->tg_b, c->tg_c}, {c->tm_a, c->tm_b, c->tm_c}, {c->tf_a, c->tf_b, c->tf_c},
                {c->max_tiles_a, c->max_tiles_b, c->max_tiles_c}, {BM_A, c->bm_b, BM_C}, c->tile_cnt};
@@ -1021,9 +1013,8 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
   hipStream_t sc = side(c, s, 2);
   if (GF(w_router) || (Is && GF(ws_gate)) || (g && g->b_router)) after(c, s, sc);
   if (GF(w_router) || (Is && GF(ws_gate))) {
-    // [dW_r ; dw_shared_gate] = dzext^T . Um in one fp32-A split-k GEMM, then the rows go to their buffers
+    // [dW_r ; dw_shared_gate] = dzext^T . Um in one fp32-A GEMM, then the rows go to their buffers
     GemmArgs a = tn(c->dzext, E1, c->Um, d, c->dwr_tmp, d, E1, d, T);
-    a.split_k = SPLIT_DWR; a.splitk_ws = c->splitk_ws;
     GemmTypes t{0, dt, c->gdt, dt};
     if (launch_gemm_generic(a, t, sc)) return REVFFN_EUNSUPPORTED;
     if (GF(w_router)) p_copy_rows(c, c->gdt, c->dwr_tmp, d, GF(w_router), d, E, d, sc);

@@ -238,22 +238,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const bf16* A, cons
   wait_vmcnt<0>();                                   // the zero-filled loads past the last tile
 
   // ---- epilogue: lane holds column n = lane & 31 and rows (e>>2)*8 + (lane>>5)*4 + (e&3)
-  if (g.group_mode == 0 && g.split_k > 1) {
-    float* ws = g.splitk_ws + (i64)bz * g.M * g.N;
-#pragma unroll
-    for (int j = 0; j < TN; j++) {
-      const int n = n0 + wn + j * 32 + (lane & 31);
-      if (n >= g.N) continue;
-#pragma unroll
-      for (int i = 0; i < TE; i++)
-#pragma unroll
-        for (int e = 0; e < 16; e++) {
-          const int m = m0 + wm + i * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
-          if (m < m_end) ws[(i64)m * g.N + n] = acc[i][j][e];
-        }
-    }
-    return;
-  }
   if (g.act_half) {
     // gate/up GEMM with the SwiGLU epilogue: this wave's first 32-column block is gate columns, its second the up
     // columns of the same indices.  Both go to C (the backward pass needs them), and silu(gate) * up, from the
@@ -483,10 +467,6 @@ __global__ void __launch_bounds__(NW * 64) gemm_mfma_k(GemmArgs g) {
       k0 = g.offsets[grp];
       k_end = g.offsets[grp + 1];
       C += (i64)grp * g.c_group_stride;
-    } else if (g.split_k > 1) {                      // k slices of whole k-tiles; partial sums go to splitk_ws
-      int per = ((g.K + BK - 1) / BK + g.split_k - 1) / g.split_k * BK;
-      k0 = min(g.K, bz * per);
-      k_end = min(g.K, k0 + per);
     } else if (g.n_sub > 1 && bz > 0) {              // one of several problems of one shape launched together
       // (constant indices: the argument block stays in scalar registers)
       if (bz == 1) { A = (const bf16*)g.subA[0]; Bm = (const bf16*)g.subB[0]; C = (TC*)g.subC[0]; bias = g.subBias[0]; }
@@ -516,7 +496,7 @@ static void go(const GemmArgs& g0, hipStream_t s) {
   { static int off = -1; if (off < 0) { const char* e = getenv("REVFFN_NO_PACKED_STORES"); off = e ? atoi(e) : 0; } g.no_packed_stores = off; }
   g.tiles_n = g.act_half ? cdiv(g.act_half, BN / 2) : cdiv(g.N, BN);
   g.tiles_m = g.group_mode == 1 ? g.max_tiles : cdiv(g.M, BM);
-  const int zdim = g.group_mode == 2 ? g.n_groups : (g.group_mode == 0 && g.split_k > 1 ? g.split_k : (g.group_mode == 0 ? g.n_sub : 1));
+  const int zdim = g.group_mode == 2 ? g.n_groups : (g.group_mode == 0 ? g.n_sub : 1);
   if (g.tiles_n <= 0 || g.tiles_m <= 0 || zdim <= 0) return;
   dim3 grid(g.tiles_n, g.tiles_m, zdim);
   g.xcd_m = 0;
@@ -563,7 +543,7 @@ static void pick_tile(const GemmArgs& g, hipStream_t s) {
   // 1.72 times, one of 256x256 about 3.05 times as long as one of 128x128 (measured on this block's shapes at 1024 to
   // 8192 tokens: larger tiles do more work per loaded byte, but a last, partly filled round costs a whole tile's time).
   auto dense_choice = [&]() {
-    const int z = g.split_k > 1 ? g.split_k : g.n_sub;
+    const int z = g.n_sub;
     // (a launch that runs beside others on a helper stream fills only the CUs it needs: its cost is its tile count.
     // Not for a problem of fewer than 128 of the largest tiles: on a fraction of the CUs it takes several times as
     // long, and helper streams are chains too -- 32-tile weight gradients at the end of a call were the last thing
@@ -623,7 +603,7 @@ static void pick_tile(const GemmArgs& g, hipStream_t s) {
     return;                                            // (launch_gemm_mfma admits this mode for that layout only)
   }
   // below ~200 tiles of 128x128: 128x64 (two workgroups per CU)
-  const i64 t128 = (i64)cdiv(g.M, 128) * cdiv(g.N, 128) * (g.split_k > 1 ? g.split_k : g.n_sub);
+  const i64 t128 = (i64)cdiv(g.M, 128) * cdiv(g.N, 128) * g.n_sub;
   if (t128 < 200 && g.N >= 128) { go_128x64<AT, BT, TC>(g, s); return; }
   switch (dense_choice()) {
     case 4:
@@ -656,13 +636,12 @@ int launch_gemm_mfma(const GemmArgs& g, GemmTypes t, hipStream_t s) {
   if (g.group_mode == 1 && (g.a_trans || (g.tile_bm != 128 && g.tile_bm != 256 && !(g.tile_bm == 160 && !g.b_trans && g.tile_bn == 256)))) return 1;
   if (g.a_gather && g.a_trans) return 1;
   if (g.group_mode != 1 && g.M <= 0) return 1;
-  if (g.split_k > 1 && (g.group_mode != 0 || !g.splitk_ws)) return 1;
-  if (g.n_sub < 1 || g.n_sub > 3 || (g.n_sub > 1 && (g.group_mode != 0 || g.split_k > 1 || g.resid || g.tap || g.act_half))) return 1;
+  if (g.n_sub < 1 || g.n_sub > 3 || (g.n_sub > 1 && (g.group_mode != 0 || g.resid || g.tap || g.act_half))) return 1;
   for (int z = 1; z < g.n_sub; z++)
     if (!g.subA[z - 1] || !g.subB[z - 1] || !g.subC[z - 1] || !aligned16(g.subA[z - 1]) || !aligned16(g.subB[z - 1])) return 1;
-  if (g.col_scale && g.split_k <= 1) return 1;           // column scale lives in the split-k reduction only
+  if (g.col_scale) return 1;                             // (the generic kernel's epilogue only)
   if (g.act_half) {
-    if (g.a_trans || g.b_trans || g.group_mode == 2 || g.split_k > 1 || g.bias || g.resid || g.tap || !g.act_out) return 1;
+    if (g.a_trans || g.b_trans || g.group_mode == 2 || g.bias || g.resid || g.tap || !g.act_out) return 1;
     if (g.N != 2 * g.act_half) return 1;
   }
   // every operand must span less than 2 GiB from its base (32-bit buffer offsets)
@@ -679,6 +658,5 @@ int launch_gemm_mfma(const GemmArgs& g, GemmTypes t, hipStream_t s) {
   } else {
     if (f32out) pick_tile<true, true, float>(g, s); else pick_tile<true, true, bf16>(g, s);
   }
-  if (g.group_mode == 0 && g.split_k > 1) launch_splitk_reduce(g, t, s);
   return 0;
 }

@@ -38,16 +38,12 @@ struct GemmArgs {
   // and up columns and also writes act_out[m*ldact + c] = silu(gate) * up, computed from the rounded outputs exactly
   // as the separate SwiGLU kernel does from C.  Ignored by the generic kernel (the caller runs that kernel instead).
   void* act_out = nullptr; i64 ldact = 0; int act_half = 0;
-  // generic kernel only: the k range is cut into split_k slices whose fp32 partial tiles go to
-  // splitk_ws[slice][M][N]; a second kernel adds the slices in index order and applies the epilogue
-  int split_k = 1; float* splitk_ws = nullptr;
-  int splitk_raw = 0;                    // generic kernel: leave the slices in splitk_ws, the consumer adds them
-  const void* col_scale = nullptr;
+  const void* col_scale = nullptr;       // generic kernel only
   // group_mode 1: number of m-tiles of the list actually in use (device scalar written by the permutation kernel);
   // group_mode 2: the permutation kernel's flag that the routing is even (null: treated as uneven)
   const int* tile_count = nullptr;
   const int* tile_first = nullptr;       // per tile: (first tile of its expert) << 16 | tiles of that expert
-  // MFMA kernel, dense problems without split-k: n_sub > 1 launches that many problems of one shape, layout and
+  // MFMA kernel, dense problems: n_sub > 1 launches that many problems of one shape, layout and
   // strides together (grid z = problem); problem z >= 1 takes its operands, result and bias from sub*[z-1]
   int n_sub = 1;
   const void* subA[2] = {nullptr, nullptr}; const void* subB[2] = {nullptr, nullptr};
@@ -142,8 +138,6 @@ inline int dense_grid_x(int xcd_m, int tiles_m, int tiles_n) {
 struct GemmTypes { int ta, tb, tc, tside; };
 
 int launch_gemm_generic(const GemmArgs& g, GemmTypes t, hipStream_t s);
-// second stage of a split-k GEMM: adds the slices in splitk_ws in index order, applies the epilogue
-void launch_splitk_reduce(const GemmArgs& g, GemmTypes t, hipStream_t s);
 // bf16 x bf16 MFMA path; returns 1 if the problem does not meet its alignment rules
 // (nothing launched), 0 if launched.
 int launch_gemm_mfma(const GemmArgs& g, GemmTypes t, hipStream_t s);
@@ -205,7 +199,7 @@ void launch_conv_finalize(const ConvState& cs, float* residual_out, hipStream_t 
 
 // ---- routing ---------------------------------------------------------------------
 // zraw[T,E1] = Y1 . (gain * wrp)^T in fp32 (E1 = E (+1: shared gate row)); the kernel scales by 1/rms(Y1)
-void launch_router(int dt, const void* y1, i64 ld, const float* zparts, int n_parts, const float* b_router,
+void launch_router(int dt, const void* y1, i64 ld, const float* zraw, const float* b_router,
                    float* probs, int* idx, float* wts, float* gamma, int T, int h, int E, int k, int has_gate,
                    int norm_topk, float eps, hipStream_t s);
 // m-tile lists of the grouped GEMMs for three tile heights: list i covers every expert's rows with
