@@ -92,7 +92,7 @@ struct revffn_ctx {
   // backward
   void *dRS, *dYp, *dYs, *dHs, *dGUs, *dUm_sh, *dHh, *dGU, *dXg, *dUm, *dn3, *g1;
   float *dw, *dzext, *rinv, *rinv3, *partial;
-  float* zraw;                      // router logits before the 1/rms scale [T, E1]
+  int* blk_cnt;                     // entries per token block and expert, from the router kernel to the permutation
   bool fold_queued = false;         // the router fold of this call is already enqueued on helper stream 2
   // the workspace still holds every activation of this revffn_forward call (stored-activation backward)
   const void *fwd_x1 = nullptr, *fwd_x2 = nullptr, *fwd_y1 = nullptr;
@@ -214,7 +214,7 @@ size_t carve(revffn_ctx* c, char* base) {
   c->wr_ext = cv.take(E1p * d * es);
   c->dzb = cv.take(T * E1p * 2);
   c->dUm_r = cv.take(T * d * es);
-  c->zraw = (float*)cv.take(T * E1 * 4);
+  c->blk_cnt = (int*)cv.take(router_blocks(T) * E * 4);
   c->rinv = (float*)cv.take(2 * T * 4);
   c->rinv3 = (float*)cv.take(T * 4);
   size_t maxcols = d > E1 ? d : E1;
@@ -372,17 +372,20 @@ void p_rope(revffn_ctx* c, int dt, void* buf, const float* cs, int T, int S, int
   launch_rope(dt, buf, cs, T, S, H, dh, sign, s, buf2, skip);
   ps.done(KID_ROPE);
 }
-void p_router(revffn_ctx* c, int dt, const void* y1, i64 ld, const float* zraw, const float* b_router,
-              float* probs, int* idx, float* wts, float* gamma, int T, int h, int E, int k, int has_gate, int norm_topk,
-              float eps, hipStream_t s) {
-  ProfScope ps(c, s, 0, (double)T * (h * esz(dt) + (E + has_gate) * 4.0 + E * 4 + k * 8 + has_gate * 4));
-  launch_router(dt, y1, ld, zraw, b_router, probs, idx, wts, gamma, T, h, E, k, has_gate, norm_topk, eps, s);
-  ps.done(KID_ROUTER);
-}
-void p_permute(revffn_ctx* c, const int* idx, int T, int k, int E, int* counts, int* offsets, int* row_map, int* inv_map,
-               const TileLists& tl, hipStream_t s) {
-  ProfScope ps(c, s, 0, (double)T * k * 4 * 4);                    // idx read twice, row_map and inv_map written
-  launch_permute(idx, T, k, E, counts, offsets, row_map, inv_map, tl, s);
+// the routing chain: logits, softmax and selection, then the permutation
+void p_routing(revffn_ctx* c, const void* y1, i64 ld, const float* wrp, const float* b_router, int T, hipStream_t s) {
+  const revffn_config& f = c->cfg;
+  const int h = f.d_model / 2, E = f.n_experts, k = f.top_k, gate = f.d_shared ? 1 : 0;
+  {
+    ProfScope ps(c, s, 0, (double)T * (h * esz(c->sdt) + E * 4 + k * 8 + gate * 4) + (double)(E + gate) * h * 4);
+    launch_router(c->sdt, y1, ld, wrp, b_router, c->probs, c->idx, c->wts, c->gamma, c->blk_cnt, T, h, E, k, gate,
+                  f.norm_topk_prob, f.rms_eps, s);
+    ps.done(KID_ROUTER);
+  }
+  TileLists tl{{c->tg_a, c->tg_b, c->tg_c}, {c->tm_a, c->tm_b, c->tm_c}, {c->tf_a, c->tf_b, c->tf_c},
+               {c->max_tiles_a, c->max_tiles_b, c->max_tiles_c}, {BM_A, c->bm_b, BM_C}, c->tile_cnt};
+  ProfScope ps(c, s, 0, (double)T * k * 4 * 3);                    // idx read, row_map and inv_map written
+  launch_permute(c->idx, c->blk_cnt, T, k, E, c->counts, c->offsets, c->row_map, c->inv_map, tl, s);
   ps.done(KID_PERMUTE);
 }
 void p_combine(revffn_ctx* c, int dt, const void* yp, const int* inv_map, const float* wts, const void* ys,
@@ -606,14 +609,9 @@ void router_fold(revffn_ctx* c, const revffn_weights* w, hipStream_t s, float* d
   const revffn_config& f = c->cfg;
   const int d = f.d_model, h = d / 2, E = f.n_experts, Is = f.d_shared, dt = c->dt;
   hipStream_t sr = dst ? s : side(c, s, 2);
-  after(c, s, sr);                        // everything that read wr_ext / wrp before is on s
-  // [W_r ; w_shared_gate] stacked into one [E1, d] matrix so that the fold is a single GEMM
-  {
-    ProfScope ps(c, sr, 0, 2.0 * (E + (Is ? 1 : 0)) * d * esz(dt));
-    launch_copy_rows2(dt, w->w_router, d, E, Is ? w->ws_gate : w->w_router, d, Is ? 1 : 0, c->wr_ext, d, d, sr);
-    ps.done(KID_COPY_ROWS);
-  }
-  GemmArgs a = nn(c->wr_ext, d, w->pup_m, h, dst ? dst : c->wrp, h, E + (Is ? 1 : 0), h, d);
+  after(c, s, sr);                        // everything that read wrp before is on s
+  GemmArgs a = nn(w->w_router, d, w->pup_m, h, dst ? dst : c->wrp, h, E + (Is ? 1 : 0), h, d);
+  if (Is) a.a_last_row = w->ws_gate;      // the shared expert's gate vector is the last row
   a.col_scale = w->norm_m;
   (void)launch_gemm_generic(a, GemmTypes{dt, dt, 0, dt}, sr);
   if (!dst) c->fold_queued = true;
@@ -646,16 +644,7 @@ int moe_acts(revffn_ctx* c, const revffn_weights* w, const void* y1, i64 ld, int
   if (c->fold_queued) after(c, s, sr);    // y1 is complete on s
   else router_fold(c, w, s);              // (forks from s as well)
   c->fold_queued = false;
-  {
-    GemmArgs z = nt(y1, ld, c->wrp, h, c->zraw, E1, T, E1, h);
-    GemmTypes tz{c->sdt, 0, 0, dt};
-    if (launch_gemm_generic(z, tz, sr)) return REVFFN_EUNSUPPORTED;
-  }
-  p_router(c, c->sdt, y1, ld, c->zraw, w->b_router, c->probs, c->idx, c->wts, c->gamma, T, h, E, k,
-                Is ? 1 : 0, f.norm_topk_prob, f.rms_eps, sr);
-  TileLists tl{{c->tg_a, c->tg_b, c->tg_c}, {c->tm_a, c->tm_b, c->tm_c}, {c->tf_a, c->tf_b, c->tf_c},
-               {c->max_tiles_a, c->max_tiles_b, c->max_tiles_c}, {BM_A, c->bm_b, BM_C}, c->tile_cnt};
-  p_permute(c, c->idx, T, k, E, c->counts, c->offsets, c->row_map, c->inv_map, tl, sr);
+  p_routing(c, y1, ld, c->wrp, w->b_router, T, sr);
   p_rmsnorm_fwd(c, dt, c->sdt, y1, ld, w->norm_m, c->n3, h, T, h, f.rms_eps, s);
   TRY(run_gemm(c, nt(c->n3, h, w->pup_m, h, c->Um, d, T, d, h), s));
   hipStream_t s0 = side(c, s, 0);
@@ -787,16 +776,7 @@ int moe_merged(revffn_ctx* c, const revffn_weights* w, const revffn_merged* m, c
   c->bm_b = expert_rows_b(c, N, E);
   hipStream_t sr = side(c, s, 2), s0 = side(c, s, 0);
   after(c, s, sr);
-  {
-    GemmArgs z = nt(y1, ld, m->w_router, h, c->zraw, E1, T, E1, h);
-    GemmTypes tz{c->sdt, 0, 0, dt};
-    if (launch_gemm_generic(z, tz, sr)) return REVFFN_EUNSUPPORTED;
-  }
-  p_router(c, c->sdt, y1, ld, c->zraw, w->b_router, c->probs, c->idx, c->wts, c->gamma, T, h, E, k,
-           Is ? 1 : 0, f.norm_topk_prob, f.rms_eps, sr);
-  TileLists tl{{c->tg_a, c->tg_b, c->tg_c}, {c->tm_a, c->tm_b, c->tm_c}, {c->tf_a, c->tf_b, c->tf_c},
-               {c->max_tiles_a, c->max_tiles_b, c->max_tiles_c}, {BM_A, c->bm_b, BM_C}, c->tile_cnt};
-  p_permute(c, c->idx, T, k, E, c->counts, c->offsets, c->row_map, c->inv_map, tl, sr);
+  p_routing(c, y1, ld, m->w_router, w->b_router, T, sr);
   p_rmsnorm_fwd(c, dt, c->sdt, y1, ld, w->norm_m, c->n3, h, T, h, f.rms_eps, s);
   if (Is) {
     after(c, s, s0);
@@ -1025,6 +1005,11 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
   const void* dum_r = nullptr;
   if (dz_bf16) {
     // router term of dUm on the matrix cores: dUm_r = dz . [W_r ; w_gate ; 0], contraction over E1p
+    {
+      ProfScope ps(c, s, 0, 2.0 * E1 * d * esz(dt));
+      launch_copy_rows2(dt, w->w_router, d, E, Is ? w->ws_gate : w->w_router, d, Is ? 1 : 0, c->wr_ext, d, d, s);
+      ps.done(KID_COPY_ROWS);
+    }
     GemmArgs a = nn(c->dzb, E1p, c->wr_ext, d, c->dUm_r, d, T, d, E1p);
     GemmTypes tt{1, 1, 1, 1};
     if (launch_gemm_mfma(a, tt, s) == 0) dum_r = c->dUm_r;

@@ -24,6 +24,7 @@ struct GemmArgs {
   i64 lda = 0, ldb = 0, ldc = 0;
   int a_trans = 0, b_trans = 0;
   const int* a_gather = nullptr; int gather_div = 1;
+  const void* a_last_row = nullptr;      // generic kernel, a_trans = 0: row M - 1 of A is stored there
   const void* bias = nullptr;
   const void* resid = nullptr; i64 ldr = 0; float resid_sign = 1.f;
   int resid_f32 = 0;                     // resid holds float32 whatever the side type is (fp32 residual streams)
@@ -198,17 +199,19 @@ void launch_conv_decide(const ConvState& cs, int rows, float tol, int it, hipStr
 void launch_conv_finalize(const ConvState& cs, float* residual_out, hipStream_t s);
 
 // ---- routing ---------------------------------------------------------------------
-// zraw[T,E1] = Y1 . (gain * wrp)^T in fp32 (E1 = E (+1: shared gate row)); the kernel scales by 1/rms(Y1)
-void launch_router(int dt, const void* y1, i64 ld, const float* zraw, const float* b_router,
-                   float* probs, int* idx, float* wts, float* gamma, int T, int h, int E, int k, int has_gate,
-                   int norm_topk, float eps, hipStream_t s);
+// wrp[E1, h]: folded router matrix (E1 = E (+1: shared gate row)); blk_cnt[router_blocks(T)][E]: entries per token block
+// and expert, which the permutation needs
+void launch_router(int dt, const void* y1, i64 ld, const float* wrp, const float* b_router, float* probs, int* idx,
+                   float* wts, float* gamma, int* blk_cnt, int T, int h, int E, int k, int has_gate, int norm_topk,
+                   float eps, hipStream_t s);
+size_t router_blocks(size_t T);
 // m-tile lists of the grouped GEMMs for three tile heights: list i covers every expert's rows with
 // tiles of bm[i] rows (group[i][t] = expert or -1 for an unused slot, m0[i][t] = first row, first[i][t] = packed
 // (first tile of t's expert) * 65536 + (tiles of that expert), count[i] = tiles in use)
 // count[0..2]: tiles in use of the three lists; count[3]: 1 if the rows are spread evenly over the experts (place_tile)
 struct TileLists { int* group[3]; int* m0[3]; int* first[3]; int max_tiles[3]; int bm[3]; int* count; };
 // counts/offsets/row_map/inv_map and the tile lists
-void launch_permute(const int* idx, int T, int k, int E, int* counts, int* offsets, int* row_map, int* inv_map,
+void launch_permute(const int* idx, const int* blk_cnt, int T, int k, int E, int* counts, int* offsets, int* row_map, int* inv_map,
                     const TileLists& tl, hipStream_t s);
 void launch_combine(int dt, const void* yp, const int* inv_map, const float* wts, const void* ys,
                     const float* gamma, void* rs, int T, int d, int k, hipStream_t s);

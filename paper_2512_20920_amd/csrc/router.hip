@@ -3,6 +3,7 @@
 // weighted combine, and the element-wise parts of their backward passes.
 // Everything here is deterministic: integer results depend only on the logits' bits.
 #include "kernels.h"
+#include "operand_f32.h"
 #include <initializer_list>
 
 #define DISPATCH_DT(dt, ...)                                  \
@@ -13,98 +14,165 @@
 
 // ---------------------------------------------------------------------------------
 // Router.  The logits are z = W_r (P_up_m Norm(Y1)) + b.  They are evaluated as
-// (W_r P_up_m diag(gain)) Y1 / rms(Y1) with the product matrix held in fp32 and applied to the
-// stored Y1 by an fp32 GEMM (zraw), so the selection depends only on the bits of Y1 and the
-// weights, not on the rounding of the bf16 intermediate P_up_m Norm(Y1).  Column E of zraw
-// (optional) is the shared expert's gate vector folded the same way.
-// One wave per token.  Outputs: probs[T,E] (softmax over all experts), idx/wts[T,k] (slots
-// by descending logit, equal logits -> lower expert index), gamma[T] = sigmoid(gate logit).
+// (W_r P_up_m diag(gain)) Y1 / rms(Y1) with the product matrix wrp[E1, h] held in fp32 and applied to the stored Y1 with
+// float32 products, so the selection depends only on the bits of Y1 and the weights, not on the rounding of the bf16
+// intermediate P_up_m Norm(Y1).  Row E of wrp (optional) is the shared expert's gate vector folded the same way.
+// Outputs: probs[T,E] (softmax over all experts), idx/wts[T,k] (slots by descending logit, equal logits -> lower expert
+// index), gamma[T] = sigmoid(gate logit), and blk_cnt[block][E], how often the block's tokens chose each expert.
+//
+// One workgroup of 16 waves per block of 32 tokens.  The routing chain (this kernel, then the permutation) is latency:
+// a few MFLOP per workgroup.  The 32 x E1 logits are cut over the waves by column tile and by slices of h (operands
+// straight from memory, the squares for 1/rms are summed from the same registers), added in slice order through LDS,
+// and a wave then finishes two tokens with one lane per expert.  Logits, softmax and selection as one kernel instead of
+// two, with the logits kept on the chip: 14 + 15 us -> 9 us at T = 128, 19 + 16 -> 11 us at T = 2048.
 // ---------------------------------------------------------------------------------
+#define ROUTER_TOKENS 32
+#define ROUTER_WAVES 16
+__host__ __device__ inline int router_slices(int tiles) { return tiles >= ROUTER_WAVES ? 1 : ROUTER_WAVES / tiles; }
+
 template <class T>
-__global__ void __launch_bounds__(256) router_k(const T* __restrict__ y1, i64 ld, const float* __restrict__ zraw,
-                                                const float* __restrict__ b_router,
-                                                float* __restrict__ probs, int* __restrict__ idx,
-                                                float* __restrict__ wts, float* __restrict__ gamma, int Tn, int h,
-                                                int E, int k, int has_gate, int norm_topk, float eps) {
-  extern __shared__ float sm[];          // per wave: z[E1]
-  const int E1 = E + (has_gate ? 1 : 0);
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  float* z = sm + (size_t)wv * E1;
-  const int t = blockIdx.x * 4 + wv;
-  if (t >= Tn) return;                   // whole wave leaves; no block barriers below
-  const T* yr = y1 + (i64)t * ld;
-  float ss = 0.f;
-  for (int j = lane; j < h; j += 64) { float v = to_f(yr[j]); ss += v * v; }
-  ss = wave_sum(ss);
-  const float r = 1.0f / sqrtf(ss / (float)h + eps);
-  for (int e = lane; e < E1; e += 64) {
-    z[e] = zraw[(i64)t * E1 + e] * r + ((e < E && b_router) ? b_router[e] : 0.f);
-  }
-  __builtin_amdgcn_wave_barrier();       // LDS traffic of one wave is executed in order
-  // softmax over the E routed logits
-  float mx = -INFINITY;
-  for (int e = lane; e < E; e += 64) mx = fmaxf(mx, z[e]);
-  mx = wave_max(mx);
-  float sum = 0.f;
-  for (int e = lane; e < E; e += 64) sum += __expf(z[e] - mx);
-  sum = wave_sum(sum);
-  const float inv = 1.0f / sum;
-  for (int e = lane; e < E; e += 64) probs[(i64)t * E + e] = __expf(z[e] - mx) * inv;
-  // top-k by k rounds of (value desc, index asc) arg-max over the experts not chosen yet.  A logit that is not a
-  // number ranks as minus infinity, and a lane remembers which of its own experts (e = lane + 64 j, E <= 256) are
-  // taken, so every round finds a valid expert that no earlier round has chosen, whatever the logits hold: a token
-  // with a non-finite input cannot disturb the tables of other tokens.
-  __builtin_amdgcn_wave_barrier();
-  float wsum = 0.f;
-  float myw = 0.f;                        // lane s keeps the weight of slot s
-  unsigned taken = 0;                     // bit j: expert lane + 64 j has been chosen
-  for (int s = 0; s < k; s++) {
-    float bv = -INFINITY;
-    int bi = 0x7fffffff;
-    for (int e = lane, j = 0; e < E; e += 64, j++) {
-      if ((taken >> j) & 1u) continue;
-      float v = z[e];
-      v = (v == v) ? v : -INFINITY;
-      if (v > bv || (v == bv && e < bi)) { bv = v; bi = e; }
-    }
+__global__ void __launch_bounds__(ROUTER_WAVES * 64) router_k(
+    const T* __restrict__ y1, i64 ld, const float* __restrict__ wrp, const float* __restrict__ b_router,
+    float* __restrict__ probs, int* __restrict__ idx, float* __restrict__ wts, float* __restrict__ gamma,
+    int* __restrict__ blk_cnt, int Tn, int h, int E, int k, int has_gate, int norm_topk, float eps) {
+  extern __shared__ __attribute__((aligned(16))) float sm[];
+  const int E1 = E + (has_gate ? 1 : 0), tiles = (E1 + 31) >> 5, ns = router_slices(tiles), zc = tiles * 32;
+  float* zpart = sm;                              // [ns][32][zc]
+  float* sspart = sm + ns * 32 * zc;              // [ns][32]
+  int* cnt = (int*)(sspart + ns * 32);            // [E]
+  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, gh = lane >> 5;
+  const int t0 = blockIdx.x * ROUTER_TOKENS;
+  for (int e = threadIdx.x; e < E; e += blockDim.x) cnt[e] = 0;
+  const int nchunk = (h + GKC - 1) / GKC;
+  for (int item = wv; item < tiles * ns; item += ROUTER_WAVES) {
+    const int sl = item / tiles, tt = item - sl * tiles;
+    f32x16 acc;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      float ov = __shfl_xor(bv, o, WAVE);
-      int oi = __shfl_xor(bi, o, WAVE);
-      if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+    for (int e = 0; e < 16; e++) acc[e] = 0.f;
+    float ss = 0.f;
+    Operand<T, false> oa;
+    Operand<float, false> ob;
+    oa.init(y1, ld, t0, Tn, lane);
+    ob.init(wrp, h, tt * 32, E1, lane);
+    float va[2][16], vb[2][16];
+    auto mul = [&](float (&a)[16], float (&b)[16]) {
+#pragma unroll
+      for (int s = 0; s < 16; s++) { acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[s], b[s], acc, 0, 0, 0); ss += a[s] * a[s]; }
+    };
+    int c = sl;
+    if (c < nchunk) { oa.load(c * GKC, h, gh, va[0]); ob.load(c * GKC, h, gh, vb[0]); }
+    for (; c + ns < nchunk; c += 2 * ns) {
+      oa.load((c + ns) * GKC, h, gh, va[1]); ob.load((c + ns) * GKC, h, gh, vb[1]);
+      mul(va[0], vb[0]);
+      if (c + 2 * ns < nchunk) { oa.load((c + 2 * ns) * GKC, h, gh, va[0]); ob.load((c + 2 * ns) * GKC, h, gh, vb[0]); }
+      mul(va[1], vb[1]);
     }
-    // the comparator is a total order (no NaN takes part), so every lane now holds the same (bv, bi); with
-    // top_k <= E at least one expert was left, so bi < E (the clamp only guards the stores below)
-    bi = min(bi, E - 1);
-    if ((bi & 63) == lane) taken |= 1u << (bi >> 6);
-    float p = __expf(bv - mx) * inv;
-    wsum += p;
-    if (lane == s) myw = p;
-    if (lane == 0) idx[(i64)t * k + s] = bi;
+    if (c < nchunk) mul(va[0], vb[0]);
+#pragma unroll
+    for (int e = 0; e < 16; e++)
+      zpart[(sl * 32 + (e >> 2) * 8 + gh * 4 + (e & 3)) * zc + tt * 32 + (lane & 31)] = acc[e];
+    ss += __shfl_xor(ss, 32, WAVE);
+    if (tt == 0 && lane < 32) sspart[sl * 32 + lane] = ss;
   }
-  if (lane < k) wts[(i64)t * k + lane] = norm_topk ? myw / wsum : myw;
-  if (has_gate && lane == 0) gamma[t] = sigmoid_f(z[E]);
+  __syncthreads();
+  for (int q = 0; q < ROUTER_TOKENS / ROUTER_WAVES; q++) {
+    const int tok = wv * (ROUTER_TOKENS / ROUTER_WAVES) + q, t = t0 + tok;
+    if (t >= Tn) break;
+    float ss = 0.f;
+    for (int s = 0; s < ns; s++) ss += sspart[s * 32 + tok];
+    const float r = 1.0f / sqrtf(ss / (float)h + eps);
+    auto logit = [&](int e) {
+      float raw = 0.f;
+      for (int s = 0; s < ns; s++) raw += zpart[(s * 32 + tok) * zc + e];
+      return raw * r;
+    };
+    float z[4];                           // the logits of experts lane + 64 j (E <= 256)
+    float mx = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+      const int e = lane + 64 * j;
+      z[j] = -INFINITY;
+      if (e < E) { z[j] = logit(e) + (b_router ? b_router[e] : 0.f); mx = fmaxf(mx, z[j]); }
+    }
+    // softmax over the E routed logits
+    mx = wave_max(mx);
+    float p[4], sum = 0.f;
+#pragma unroll
+    for (int j = 0; j < 4; j++) { p[j] = lane + 64 * j < E ? __expf(z[j] - mx) : 0.f; sum += p[j]; }
+    sum = wave_sum(sum);
+    const float inv = 1.0f / sum;
+#pragma unroll
+    for (int j = 0; j < 4; j++) if (lane + 64 * j < E) probs[(i64)t * E + lane + 64 * j] = p[j] * inv;
+    // top-k by k rounds of (value desc, index asc) arg-max over the experts not chosen yet.  A logit that is not a
+    // number ranks as minus infinity, and a lane remembers which of its own experts are taken, so every round finds a
+    // valid expert that no earlier round has chosen, whatever the logits hold: a token with a non-finite input cannot
+    // disturb the tables of other tokens.
+    float wsum = 0.f;
+    float myw = 0.f;                      // lane s keeps the weight of slot s
+    unsigned taken = 0;                   // bit j: expert lane + 64 j has been chosen
+    for (int s = 0; s < k; s++) {
+      float bv = -INFINITY;
+      int bi = 0x7fffffff;
+#pragma unroll
+      for (int j = 0; j < 4; j++) {
+        const int e = lane + 64 * j;
+        if (e >= E || ((taken >> j) & 1u)) continue;
+        const float v = (z[j] == z[j]) ? z[j] : -INFINITY;
+        if (v > bv || (v == bv && e < bi)) { bv = v; bi = e; }
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        const float ov = __shfl_xor(bv, o, WAVE);
+        const int oi = __shfl_xor(bi, o, WAVE);
+        if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+      }
+      // the comparator is a total order (no NaN takes part), so every lane now holds the same (bv, bi); with
+      // top_k <= E at least one expert was left, so bi < E (the clamp only guards the stores below)
+      bi = min(bi, E - 1);
+      if ((bi & 63) == lane) taken |= 1u << (bi >> 6);
+      const float pb = __expf(bv - mx) * inv;
+      wsum += pb;
+      if (lane == s) myw = pb;
+      if (lane == 0) { idx[(i64)t * k + s] = bi; atomicAdd(&cnt[bi], 1); }
+    }
+    if (lane < k) wts[(i64)t * k + lane] = norm_topk ? myw / wsum : myw;
+    if (has_gate) {
+      const float zg = logit(E);
+      if (lane == 0) gamma[t] = sigmoid_f(zg);
+    }
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < E; e += blockDim.x) blk_cnt[(i64)blockIdx.x * E + e] = cnt[e];
 }
 
-void launch_router(int dt, const void* y1, i64 ld, const float* zraw, const float* b_router, float* probs, int* idx,
-                   float* wts, float* gamma, int Tn, int h, int E, int k, int has_gate, int norm_topk, float eps,
-                   hipStream_t s) {
+void launch_router(int dt, const void* y1, i64 ld, const float* wrp, const float* b_router, float* probs, int* idx,
+                   float* wts, float* gamma, int* blk_cnt, int Tn, int h, int E, int k, int has_gate, int norm_topk,
+                   float eps, hipStream_t s) {
   if (Tn <= 0) return;
-  size_t smem = (size_t)4 * (E + 1) * sizeof(float);
-  DISPATCH_DT(dt, hipLaunchKernelGGL(router_k<T>, dim3(cdiv(Tn, 4)), dim3(256), smem, s, (const T*)y1, ld, zraw,
-                                     b_router, probs, idx, wts, gamma, Tn, h, E, k, has_gate, norm_topk, eps));
+  const int tiles = (E + (has_gate ? 1 : 0) + 31) / 32, ns = router_slices(tiles);
+  const size_t smem = ((size_t)ns * 32 * (tiles * 32 + 1) + E) * 4;         // at most 70 KB
+  static std::atomic<unsigned long long> attr_mask{0};
+  if (attr_needed(attr_mask)) {
+    (void)hipFuncSetAttribute((const void*)router_k<float>, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
+    (void)hipFuncSetAttribute((const void*)router_k<bf16>, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
+    attr_done(attr_mask);
+  }
+  DISPATCH_DT(dt, hipLaunchKernelGGL(router_k<T>, dim3(cdiv(Tn, ROUTER_TOKENS)), dim3(ROUTER_WAVES * 64), smem, s,
+                                     (const T*)y1, ld, wrp, b_router, probs, idx, wts, gamma, blk_cnt, Tn, h, E, k,
+                                     has_gate, norm_topk, eps));
 }
+size_t router_blocks(size_t Tn) { return (Tn + ROUTER_TOKENS - 1) / ROUTER_TOKENS; }
 
 // ---------------------------------------------------------------------------------
-// Permutation.  One workgroup of 16 waves; wave w owns the contiguous slice of the T*k
-// (token, slot) entries [w*per, (w+1)*per).  Pass 1 counts per (wave, expert); the prefix
-// over waves gives each wave its first row inside every expert; pass 2 hands out rows in
-// entry order, which keeps (token, slot) order inside an expert (a stable grouping).
-// Also emits the m-tile lists used by the grouped GEMMs: tile i covers rows
+// Permutation: a stable grouping of the T*k (token, slot) entries by expert.  The router kernel has counted, per block
+// of 32 tokens, the entries of every expert, so a block's first row inside every expert is a column sum of that table
+// and blocks need nothing of each other: one wave per block, 16 per workgroup, every workgroup adding the columns for
+// itself (one workgroup that counted and placed all entries took 13.5 us at T = 2048 and 52 us at T = 8192; now 7 and
+// 8 us).  Inside its block a wave hands out rows in entry order, which keeps (token, slot) order inside an expert.
+// One more workgroup writes counts, offsets and the m-tile lists used by the grouped GEMMs: tile i covers rows
 // [tile_m0[i], min(tile_m0[i]+bm, offsets[g+1])) of expert g = tile_group[i]; unused = -1.
 // ---------------------------------------------------------------------------------
 #define PERM_WAVES 16
-#define PERM_UNROLL 8
 __device__ __forceinline__ void same_expert_mask(int x, bool valid, int nbits, unsigned long long& same) {
   same = __ballot(valid);
   for (int b = 0; b < nbits; b++) {
@@ -128,42 +196,38 @@ __device__ __forceinline__ int wave_sum(int v) {
 }
 
 __global__ void __launch_bounds__(PERM_WAVES * 64) permute_k(
-    const int* __restrict__ idx, int N, int E, int* __restrict__ counts, int* __restrict__ offsets,
-    int* __restrict__ row_map, int* __restrict__ inv_map, TileLists tl) {
-  extern __shared__ int ism[];            // cnt[PERM_WAVES][E], off[E+1], tile counts [E+1]
-  int* cnt = ism;
-  int* off = ism + PERM_WAVES * E;
+    const int* __restrict__ idx, const int* __restrict__ blk_cnt, int nblk, int N, int k, int E, int epad,
+    int* __restrict__ counts, int* __restrict__ offsets, int* __restrict__ row_map, int* __restrict__ inv_map,
+    TileLists tl) {
+  extern __shared__ int ism[];            // column sums [2][1024], next row of (wave, expert) [16][E], off[E + 1]
+  int* csum = ism;
+  int* next = ism + 2 * PERM_WAVES * 64;
+  int* off = next + PERM_WAVES * E;
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  int nbits = 0;
-  while ((1 << nbits) < E) nbits++;
-  for (int i = threadIdx.x; i < PERM_WAVES * E; i += blockDim.x) cnt[i] = 0;
-  __syncthreads();
-  const int per = (N + PERM_WAVES - 1) / PERM_WAVES;
-  const int lo = wv * per, hi = min(N, lo + per);
-  int* mycnt = cnt + wv * E;
-  for (int base0 = lo; base0 < hi; base0 += 64 * PERM_UNROLL) {
-    int xs[PERM_UNROLL];                  // the loads of a batch are independent: one memory latency per batch
-#pragma unroll
-    for (int u = 0; u < PERM_UNROLL; u++) { int f = base0 + u * 64 + lane; xs[u] = f < hi ? idx[f] : 0; }
-#pragma unroll
-    for (int u = 0; u < PERM_UNROLL; u++) {
-      int f = base0 + u * 64 + lane;
-      bool valid = f < hi;
-      int x = min(max(xs[u], 0), E - 1);    // an index outside [0, E) cannot reach the LDS tables
-      unsigned long long same;
-      same_expert_mask(x, valid, nbits, same);
-      if (valid && (same & below) == 0) mycnt[x] += __popcll(same);   // group leader; groups are disjoint
-      __builtin_amdgcn_wave_barrier();
+  const int b0 = blockIdx.x * PERM_WAVES;           // first block of this workgroup (the last workgroup has none)
+  // column sums: epad (E rounded up to a power of two) columns, 1024 / epad row lanes
+  {
+    const int e = threadIdx.x & (epad - 1), part = threadIdx.x / epad, parts = PERM_WAVES * 64 / epad;
+    int all = 0, before = 0;
+    if (e < E) {
+#pragma unroll 8
+      for (int b = part; b < nblk; b += parts) {
+        const int c = blk_cnt[(i64)b * E + e];
+        all += c;
+        before += b < b0 ? c : 0;
+      }
     }
+    csum[threadIdx.x] = all;
+    csum[PERM_WAVES * 64 + threadIdx.x] = before;
   }
+  for (int i = threadIdx.x; i < PERM_WAVES * E; i += blockDim.x) next[i] = b0 + i / E < nblk ? blk_cnt[(i64)b0 * E + i] : 0;
   __syncthreads();
-  // exclusive prefix over waves per expert, totals, offsets
-  for (int e = threadIdx.x; e < E; e += blockDim.x) {
-    int run = 0;
-    for (int w = 0; w < PERM_WAVES; w++) { int c = cnt[w * E + e]; cnt[w * E + e] = run; run += c; }
-    counts[e] = run;
-    off[e + 1] = run;                     // totals for now
+  if (threadIdx.x < E) {
+    const int e = threadIdx.x;
+    int all = 0, run = 0;
+    for (int i = e; i < PERM_WAVES * 64; i += epad) { all += csum[i]; run += csum[PERM_WAVES * 64 + i]; }
+    off[e + 1] = all;                     // totals for now
+    for (int w = 0; w < PERM_WAVES; w++) { const int c = next[w * E + e]; next[w * E + e] = run; run += c; }
   }
   __syncthreads();
   if (wv == 0) {                          // offsets = prefix sums of the totals, 64 experts per step
@@ -177,79 +241,88 @@ __global__ void __launch_bounds__(PERM_WAVES * 64) permute_k(
     }
   }
   __syncthreads();
-  for (int e = threadIdx.x; e <= E; e += blockDim.x) offsets[e] = off[e];
-  // Waves 0-2 write one tile list each, wave 3 the evenness flag; none of them changes what the row pass below
-  // reads (off, cnt), so nothing waits for them.
-  if (wv < 3) {
-    // tile lists: expert e owns the slots after the tiles of experts 0..e-1; slots past the last tile are marked
-    // unused.  The number of tiles of an expert is an exact division: the fill loop below writes ceil(rows / bm)
-    // slots per expert, and a count taken any other way (a shift, for a height that is not a power of two) would
-    // leave slots of the list unwritten, with whatever the workspace held, for the GEMM to use as an expert index.
-    const int pass = wv;
-    const int bm = tl.bm[pass], mx = tl.max_tiles[pass];
-    int* tg = tl.group[pass];
-    int* tm = tl.m0[pass];
-    int* tf = tl.first[pass];
-    int total = 0;
-    for (int base = 0; base < E; base += 64) {
-      const int e = base + lane;
-      const int m_lo = e < E ? off[e] : 0, m_hi = e < E ? off[e + 1] : 0;
-      const int mine = (m_hi - m_lo + bm - 1) / bm;
-      const int incl = wave_inclusive_scan(mine, lane);
-      const int first = total + incl - mine;
-      int i = first;
-      for (int m = m_lo; m < m_hi; m += bm, i++)
-        if (i < mx) { tg[i] = e; tm[i] = m; tf[i] = (first << 16) | mine; }
-      total += __shfl(incl, 63, WAVE);
-    }
-    for (int i = total + lane; i < mx; i += 64) { tg[i] = -1; tm[i] = 0; tf[i] = (i << 16) | 1; }
-    if (lane == 0) tl.count[pass] = min(total, mx);
-  } else if (wv == 3) {
-    // Is the routing even enough for the per-expert weight-gradient launches to give each expert to two XCDs?  Then
-    // experts e = 4 r + q (q = 0..3) are worked on by XCD pair q in round r, and the pairs finish together only if
-    // their experts cost about the same: a tile costs a fixed part (first loads, stores: about 5 k-steps' worth) plus
-    // one k-step per 64 rows of the expert.  Even = no pair more than 6 % above the mean.
-    int cost[4] = {0, 0, 0, 0};
-    for (int base = 0; base < E; base += 64) {
-      const int e = base + lane;
-      const int mine = e < E ? 5 + (off[e + 1] - off[e] + 63) / 64 : 0;
-#pragma unroll
-      for (int q = 0; q < 4; q++) cost[q] += wave_sum((e & 3) == q ? mine : 0);
-    }
-    const int tot = cost[0] + cost[1] + cost[2] + cost[3];
-    const int mx = max(max(cost[0], cost[1]), max(cost[2], cost[3]));
-    if (lane == 0) tl.count[3] = (E >= 8 && 400 * mx <= 106 * tot) ? 1 : 0;
-  }
-  for (int base0 = lo; base0 < hi; base0 += 64 * PERM_UNROLL) {
-    int xs[PERM_UNROLL];
-#pragma unroll
-    for (int u = 0; u < PERM_UNROLL; u++) { int f = base0 + u * 64 + lane; xs[u] = f < hi ? idx[f] : 0; }
-#pragma unroll
-    for (int u = 0; u < PERM_UNROLL; u++) {
-      int f = base0 + u * 64 + lane;
-      bool valid = f < hi;
-      int x = min(max(xs[u], 0), E - 1);
-      unsigned long long same;
-      same_expert_mask(x, valid, nbits, same);
-      int rank = __popcll(same & below);
-      int start = valid ? mycnt[x] : 0;     // every lane of a group reads before its leader updates
-      __builtin_amdgcn_wave_barrier();
-      if (valid && rank == 0) mycnt[x] = start + __popcll(same);
-      __builtin_amdgcn_wave_barrier();
-      if (valid) {
-        int pos = off[x] + start + rank;
-        row_map[pos] = f;
-        inv_map[f] = pos;
+  if (blockIdx.x == gridDim.x - 1) {
+    // Waves 0-2 write one tile list each, wave 3 the evenness flag, the others counts and offsets.
+    if (wv < 3) {
+      // tile lists: expert e owns the slots after the tiles of experts 0..e-1; slots past the last tile are marked
+      // unused.  The number of tiles of an expert is an exact division: the fill loop below writes ceil(rows / bm)
+      // slots per expert, and a count taken any other way (a shift, for a height that is not a power of two) would
+      // leave slots of the list unwritten, with whatever the workspace held, for the GEMM to use as an expert index.
+      const int pass = wv;
+      const int bm = tl.bm[pass], mx = tl.max_tiles[pass];
+      int* tg = tl.group[pass];
+      int* tm = tl.m0[pass];
+      int* tf = tl.first[pass];
+      int total = 0;
+      for (int base = 0; base < E; base += 64) {
+        const int e = base + lane;
+        const int m_lo = e < E ? off[e] : 0, m_hi = e < E ? off[e + 1] : 0;
+        const int mine = (m_hi - m_lo + bm - 1) / bm;
+        const int incl = wave_inclusive_scan(mine, lane);
+        const int first = total + incl - mine;
+        int i = first;
+        for (int m = m_lo; m < m_hi; m += bm, i++)
+          if (i < mx) { tg[i] = e; tm[i] = m; tf[i] = (first << 16) | mine; }
+        total += __shfl(incl, 63, WAVE);
       }
+      for (int i = total + lane; i < mx; i += 64) { tg[i] = -1; tm[i] = 0; tf[i] = (i << 16) | 1; }
+      if (lane == 0) tl.count[pass] = min(total, mx);
+    } else if (wv == 3) {
+      // Is the routing even enough for the per-expert weight-gradient launches to give each expert to two XCDs?  Then
+      // experts e = 4 r + q (q = 0..3) are worked on by XCD pair q in round r, and the pairs finish together only if
+      // their experts cost about the same: a tile costs a fixed part (first loads, stores: about 5 k-steps' worth) plus
+      // one k-step per 64 rows of the expert.  Even = no pair more than 6 % above the mean.
+      int cost[4] = {0, 0, 0, 0};
+      for (int base = 0; base < E; base += 64) {
+        const int e = base + lane;
+        const int mine = e < E ? 5 + (off[e + 1] - off[e] + 63) / 64 : 0;
+#pragma unroll
+        for (int q = 0; q < 4; q++) cost[q] += wave_sum((e & 3) == q ? mine : 0);
+      }
+      const int tot = cost[0] + cost[1] + cost[2] + cost[3];
+      const int mx = max(max(cost[0], cost[1]), max(cost[2], cost[3]));
+      if (lane == 0) tl.count[3] = (E >= 8 && 400 * mx <= 106 * tot) ? 1 : 0;
+    } else {
+      for (int e = threadIdx.x - 256; e <= E; e += PERM_WAVES * 64 - 256) {
+        offsets[e] = off[e];
+        if (e < E) counts[e] = off[e + 1] - off[e];
+      }
+    }
+    return;
+  }
+  if (b0 + wv >= nblk) return;            // whole wave; no barriers below
+  const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+  int nbits = 0;
+  while ((1 << nbits) < E) nbits++;
+  int* mine = next + wv * E;
+  const int lo = (b0 + wv) * ROUTER_TOKENS * k, hi = min(N, lo + ROUTER_TOKENS * k);
+  for (int f0 = lo; f0 < hi; f0 += 64) {
+    const int f = f0 + lane;
+    const bool valid = f < hi;
+    const int x = valid ? min(max(idx[f], 0), E - 1) : 0;    // an index outside [0, E) cannot reach the LDS tables
+    unsigned long long same;
+    same_expert_mask(x, valid, nbits, same);
+    const int rank = __popcll(same & below);
+    const int start = valid ? mine[x] : 0;  // every lane of a group reads before its leader updates
+    __builtin_amdgcn_wave_barrier();
+    if (valid && rank == 0) mine[x] = start + __popcll(same);
+    __builtin_amdgcn_wave_barrier();
+    if (valid) {
+      const int pos = off[x] + start + rank;
+      row_map[pos] = f;
+      inv_map[f] = pos;
     }
   }
 }
 
-void launch_permute(const int* idx, int Tn, int k, int E, int* counts, int* offsets, int* row_map, int* inv_map,
-                    const TileLists& tl, hipStream_t s) {
-  size_t smem = (size_t)(PERM_WAVES * E + 2 * (E + 1)) * sizeof(int);
-  hipLaunchKernelGGL(permute_k, dim3(1), dim3(PERM_WAVES * 64), smem, s, idx, Tn * k, E, counts, offsets, row_map,
-                     inv_map, tl);
+void launch_permute(const int* idx, const int* blk_cnt, int Tn, int k, int E, int* counts, int* offsets, int* row_map,
+                    int* inv_map, const TileLists& tl, hipStream_t s) {
+  const int nblk = (int)router_blocks(Tn);
+  int epad = 1;
+  while (epad < E) epad *= 2;
+  const size_t smem = (size_t)(2 * PERM_WAVES * 64 + PERM_WAVES * E + E + 1) * sizeof(int);
+  hipLaunchKernelGGL(permute_k, dim3(cdiv(nblk, PERM_WAVES) + 1), dim3(PERM_WAVES * 64), smem, s, idx, blk_cnt, nblk,
+                     Tn * k, k, E, epad, counts, offsets, row_map, inv_map, tl);
 }
 
 // ---------------------------------------------------------------------------------
