@@ -60,6 +60,7 @@ struct revffn_ctx {
   std::vector<hipEvent_t>* sync_ev = nullptr;  // ring of timing-free events for fork/join
   size_t sync_next = 0;
   bool use_streams = true;
+  bool par = false;           // this call spreads independent branches over the helper streams (see fork_pays)
   int lastT = 0;
   int lastT_rows = 0;         // lastT * top_k: permuted rows of the current routing
   // attention half
@@ -92,13 +93,12 @@ struct revffn_ctx {
   // backward
   void *dRS, *dYp, *dYs, *dHs, *dGUs, *dUm_sh, *dHh, *dGU, *dXg, *dUm, *dn3, *g1;
   float *dw, *dzext, *rinv, *rinv3, *partial;
+  int* ticket;                // of the column sums
   int* blk_cnt;                     // entries per token block and expert, from the router kernel to the permutation
-  bool fold_queued = false;         // the router fold of this call is already enqueued on helper stream 2
   // the workspace still holds every activation of this revffn_forward call (stored-activation backward)
   const void *fwd_x1 = nullptr, *fwd_x2 = nullptr, *fwd_y1 = nullptr;
   int fwd_B = 0, fwd_S = 0;
   i64 fwd_ld = 0;
-  void* dwr_tmp;
   void* wr_ext;               // [E1p, d]: router rows, shared-gate row, zero rows up to a multiple of 8
   void *dzb, *dUm_r;          // bf16 logit gradients [T, E1p] and the router term of dUm [T, d]
   void *dAO, *dO, *dQ, *dK, *dV, *dU12, *dn12;
@@ -209,7 +209,6 @@ size_t carve(revffn_ctx* c, char* base) {
   c->g1 = cv.take(T * h * es);
   c->dw = (float*)cv.take(N * 4);
   c->dzext = (float*)cv.take(T * E1 * 4);
-  c->dwr_tmp = cv.take(E1 * d * c->ges);
   const size_t E1p = (E1 + 7) / 8 * 8;
   c->wr_ext = cv.take(E1p * d * es);
   c->dzb = cv.take(T * E1p * 2);
@@ -217,8 +216,9 @@ size_t carve(revffn_ctx* c, char* base) {
   c->blk_cnt = (int*)cv.take(router_blocks(T) * E * 4);
   c->rinv = (float*)cv.take(2 * T * 4);
   c->rinv3 = (float*)cv.take(T * 4);
-  size_t maxcols = d > E1 ? d : E1;
-  c->partial = (float*)cv.take(colsum_partial_floats((int)(2 * T), (int)maxcols) * 4);
+  const size_t colsums = 3 * d + 3 * h + E;      // at most this many columns are summed in a call
+  c->partial = (float*)cv.take(colsum_partial_floats(colsums) * 4);
+  c->ticket = (int*)cv.take(colsum_tickets(colsums) * 4);
   c->dAO = cv.take(T * d * es);
   c->dO = cv.take(T * d * es);
   c->dQ = cv.take(T * d * es);
@@ -346,7 +346,7 @@ int run_gemm(revffn_ctx* c, const GemmArgs& g, hipStream_t s) { return run_gemm(
 // GemmArgs::bulk; measured 1.3 % of a headline step with the shared expert's forward GEMMs treated the same way)
 int run_wgrad(revffn_ctx* c, const GemmArgs& g0, hipStream_t s) {
   GemmArgs g = g0;
-  g.bulk = c->use_streams;
+  g.bulk = c->par;
   return run_gemm(c, g, c->dt, c->dt, c->gdt, s);
 }
 
@@ -419,17 +419,18 @@ void p_swiglu_bwd(revffn_ctx* c, int dt, const void* dhh, const void* gu, void* 
   launch_swiglu_bwd(dt, dhh, gu, dgu, rows, I, s);
   ps.done(KID_SWIGLU_BWD);
 }
-void p_colsum(revffn_ctx* c, int ta, const void* a, i64 lda, int tb, const void* b, i64 ldb, const float* sc, int tout,
-              void* out, float* partial, int rows, int cols, hipStream_t s) {
-  ProfScope ps(c, s, 0, (double)rows * cols * (esz(ta) + (b ? esz(tb) : 0.0)) + (sc ? rows * 4.0 : 0.0));
-  launch_colsum(ta, a, lda, tb, b, ldb, sc, tout, out, partial, rows, cols, s);
-  ps.done(KID_COLSUM);
+void add_colsum(ColsumBatch& q, int ta, const void* a, i64 lda, int tb, const void* b, i64 ldb,
+                const float* sc, int tout, void* out, int rows, int cols) {
+  if (!out) return;
+  q.p[q.n++] = Colsum{a, b, sc, out, lda, ldb, rows, cols, ta == 0, tb == 0, tout == 0, 0};
 }
-void p_colsum_batch(revffn_ctx* c, int n, int ta, const void* const* a, const i64* lda, int tb, const void* const* b,
-                    const i64* ldb, const float* const* sc, int tout, void* const* out, int rows, int cols, hipStream_t s) {
-  if (n <= 0) return;
-  ProfScope ps(c, s, 0, (double)n * ((double)rows * cols * (esz(ta) + (b ? esz(tb) : 0.0)) + (sc ? rows * 4.0 : 0.0)));
-  launch_colsum_batch(n, ta, a, lda, tb, b, ldb, sc, tout, out, c->partial, rows, cols, s);
+void p_colsum_batch(revffn_ctx* c, ColsumBatch& q, hipStream_t s) {
+  if (!q.n) return;
+  double by = 0;
+  for (int i = 0; i < q.n; i++)
+    by += (double)q.p[i].rows * (q.p[i].cols * ((q.p[i].a_f32 ? 4.0 : 2.0) + (q.p[i].b ? (q.p[i].b_f32 ? 4.0 : 2.0) : 0.0)) + (q.p[i].sc ? 4.0 : 0.0));
+  ProfScope ps(c, s, 0, by);
+  launch_colsum_batch(q, c->partial, c->ticket, s);
   ps.done(KID_COLSUM);
 }
 void p_gather_rows(revffn_ctx* c, int dt, const void* src, const int* row_map, int div, void* dst, int rows, int cols,
@@ -471,12 +472,46 @@ int run_gemm_multi(revffn_ctx* c, const GemmArgs* subs, int n, int tc, hipStream
   return 0;
 }
 
+// the weight gradients of several dense layers as one launch; where the matrix-core kernel does not take them they run
+// one after the other
+int run_wgrad_batch(revffn_ctx* c, const GemmArgs* subs, int n, bool bulk, hipStream_t s) {
+  if (n <= 0) return 0;
+  if (c->dt == 1 && c->mode == 0) {
+    GemmBatch b;
+    double fl = 0, by = 0;
+    for (int i = 0; i < n; i++) {
+      const GemmArgs& g = subs[i];
+      b.p[b.n++] = GemmProb{g.A, g.B, g.C, g.M, g.N, g.K, (int)g.lda, (int)g.ldb, (int)g.ldc, 0, 0, 0};
+      double f1, b1;
+      if (c->prof_on) { gemm_work(c, g, c->dt, c->dt, c->gdt, &f1, &b1); fl += f1; by += b1; }
+    }
+    ProfScope ps(c, s, fl, by);
+    if (launch_gemm_batch_tn(b, c->gdt == 0, bulk, s) == 0) { ps.done(KID_GEMM_TN); return 0; }
+  }
+  for (int i = 0; i < n; i++) {
+    int e = run_gemm(c, subs[i], c->dt, c->dt, c->gdt, s);
+    if (e) return e;
+  }
+  return 0;
+}
+
 #define TRY(x) do { int _e = (x); if (_e) return _e; } while (0)
 
 // ---- fork / join between the caller's stream and the context's helper streams ----------
-// Independent branches of one call (K and V projections next to Q, the shared expert next to
-// the routed experts, every weight-gradient GEMM next to the data-gradient chain) run on helper
-// streams of default priority, so that launches too small to fill 256 CUs overlap.
+// Independent branches of one call run on helper streams of default priority, so that launches that do not fill the
+// chip overlap: the shared expert next to the routed experts, the rebuilding of X1^ and the attention half's
+// recomputation next to the MoE half's backward pass, the MoE half's weight gradients next to the attention half's
+// backward pass.  Recording an event and making another stream wait for it costs the host 13 us (a launch: 3 us), so
+// there are about ten such edges in a training step, between long branches only, and none at all in a call too small
+// for them to pay: below about 60 us of GPU time per evaluation of the block the host would be what the GPU waits for
+// (a step of a 512-wide block of 400 tokens: 909 us with 45 edges, 609 us on one stream).
+bool fork_pays(const revffn_ctx* c, i64 T) {
+  const revffn_config& f = c->cfg;
+  const double d = f.d_model, dense = 6 * d * d + 3 * d * f.d_shared, per_expert = 3 * d * f.d_expert;
+  const double hit = (double)T * f.top_k < f.n_experts ? (double)T * f.top_k : f.n_experts;
+  const double weights = (dense + hit * per_expert) * c->es, flops = 2.0 * T * (dense + f.top_k * per_expert);
+  return weights / 5e12 + flops / (c->dt == 1 ? 7e14 : 1e14) > 60e-6;
+}
 hipEvent_t next_sync(revffn_ctx* c) {
   hipEvent_t e = (*c->sync_ev)[c->sync_next % c->sync_ev->size()];
   c->sync_next++;
@@ -489,15 +524,8 @@ void after(revffn_ctx* c, hipStream_t from, hipStream_t to) {
   (void)hipEventRecord(e, from);
   (void)hipStreamWaitEvent(to, e, 0);
 }
-// the two halves of after(): an event that marks what `from` holds now, waited for later
-hipEvent_t mark(revffn_ctx* c, hipStream_t from) {
-  hipEvent_t e = next_sync(c);
-  (void)hipEventRecord(e, from);
-  return e;
-}
-void wait_for(hipStream_t to, hipEvent_t e) { (void)hipStreamWaitEvent(to, e, 0); }
 // helper stream i, or the main stream when helper streams are switched off
-hipStream_t side(revffn_ctx* c, hipStream_t main, int i) { return c->use_streams ? c->side[i] : main; }
+hipStream_t side(revffn_ctx* c, hipStream_t main, int i) { return c->par ? c->side[i] : main; }
 
 // ---- attention half ---------------------------------------------------------------
 // Query side of the attention half at x1: n12[0:T], U12[0:T], Q.
@@ -602,19 +630,15 @@ int attn_out(revffn_ctx* c, const revffn_weights* w, const void* resid, i64 ldr,
 }
 
 // ---- MoE half ---------------------------------------------------------------------
-// Folded fp32 router matrix wrp = [W_r ; w_shared_gate] . P_up_m . diag(gain).  It depends on the weights only, so a
-// call that starts with the attention half enqueues it at once on helper stream 2, next to that half.
-// dst != null: the fold goes there (pre-merged weights) and runs on s itself.
-void router_fold(revffn_ctx* c, const revffn_weights* w, hipStream_t s, float* dst = nullptr) {
+// Folded fp32 router matrix wrp = [W_r ; w_shared_gate] . P_up_m . diag(gain), into dst.
+void router_fold(revffn_ctx* c, const revffn_weights* w, float* dst, hipStream_t s) {
   const revffn_config& f = c->cfg;
   const int d = f.d_model, h = d / 2, E = f.n_experts, Is = f.d_shared, dt = c->dt;
-  hipStream_t sr = dst ? s : side(c, s, 2);
-  after(c, s, sr);                        // everything that read wrp before is on s
-  GemmArgs a = nn(w->w_router, d, w->pup_m, h, dst ? dst : c->wrp, h, E + (Is ? 1 : 0), h, d);
+  GemmArgs a = nn(w->w_router, d, w->pup_m, h, dst, h, E + (Is ? 1 : 0), h, d);
   if (Is) a.a_last_row = w->ws_gate;      // the shared expert's gate vector is the last row
   a.col_scale = w->norm_m;
-  (void)launch_gemm_generic(a, GemmTypes{dt, dt, 0, dt}, sr);
-  if (!dst) c->fold_queued = true;
+  a.small_tiles = 1;
+  (void)launch_gemm_generic(a, GemmTypes{dt, dt, 0, dt}, s);
 }
 
 // Height of the tiles in list b (the routed experts' forward GEMMs) for N permuted rows over E experts.  An expert's
@@ -638,21 +662,19 @@ int moe_acts(revffn_ctx* c, const revffn_weights* w, const void* y1, i64 ld, int
   c->lastT = T;
   c->lastT_rows = N;
   c->bm_b = expert_rows_b(c, N, E);
-  // Routing needs Y1 and the weights only (the logits are Y1 . wrp^T in fp32, scaled by 1/rms(Y1) in the router
-  // kernel), so fold, logits, top-k and the permutation run on helper stream 2 next to the norm and the up-projection.
+  // routing needs Y1 and the weights only: next to the norm, the up-projection and the first query side
   hipStream_t sr = side(c, s, 2);
-  if (c->fold_queued) after(c, s, sr);    // y1 is complete on s
-  else router_fold(c, w, s);              // (forks from s as well)
-  c->fold_queued = false;
+  after(c, s, sr);
+  router_fold(c, w, c->wrp, sr);
   p_routing(c, y1, ld, c->wrp, w->b_router, T, sr);
   p_rmsnorm_fwd(c, dt, c->sdt, y1, ld, w->norm_m, c->n3, h, T, h, f.rms_eps, s);
   TRY(run_gemm(c, nt(c->n3, h, w->pup_m, h, c->Um, d, T, d, h), s));
   hipStream_t s0 = side(c, s, 0);
-  if (Is) {                               // the shared expert needs Um only: next to routing + routed experts
+  if (Is) {                               // the shared expert needs Um only: next to the routed experts
     after(c, s, s0);
     GemmArgs gs = nt(c->Um, d, w->ws_gate_up, d, c->GUs, 2 * Is, T, 2 * Is, d);
     gs.act_out = c->Hs; gs.ldact = Is; gs.act_half = Is;      // Hs = silu(gate) * up with the GEMM
-    gs.bulk = c->use_streams;                                 // beside the routed experts' GEMMs
+    gs.bulk = c->par;                                 // beside the routed experts' GEMMs
     TRY(run_gemm(c, gs, s0));
     GemmArgs gd = nt(c->Hs, Is, w->ws_down, Is, c->Ys, d, T, d, Is);
     gd.bulk = gs.bulk;
@@ -688,7 +710,7 @@ int moe_out(revffn_ctx* c, const revffn_weights* w, const void* resid, i64 ldr, 
 // onto the helper streams; the caller's stream is made to wait for them, so that whatever was enqueued is ordered
 // before the caller's next work.
 int finish(revffn_ctx* c, hipStream_t s, int e) {
-  if (e && c && c->use_streams)
+  if (e && c && c->par)
     for (int i = 0; i < 4; i++) after(c, c->side[i], s);
   return e;
 }
@@ -718,7 +740,7 @@ int merge_impl(revffn_ctx* c, const revffn_weights* w, const revffn_merged* m, h
     TRY(run_gemm(c, nn(w->ws_gate_up, d, w->pup_m, h, m->ws_gate_up, h, 2 * Is, h, d), s));
     TRY(run_gemm(c, nn(w->pdn_m, d, w->ws_down, Is, m->ws_down, Is, h, Is, d), s));
   }
-  router_fold(c, w, s, m->w_router);
+  router_fold(c, w, m->w_router, s);
   return 0;
 }
 
@@ -774,21 +796,19 @@ int moe_merged(revffn_ctx* c, const revffn_weights* w, const revffn_merged* m, c
   c->lastT = T;
   c->lastT_rows = N;
   c->bm_b = expert_rows_b(c, N, E);
-  hipStream_t sr = side(c, s, 2), s0 = side(c, s, 0);
-  after(c, s, sr);
-  p_routing(c, y1, ld, m->w_router, w->b_router, T, sr);
+  hipStream_t s0 = side(c, s, 0);
   p_rmsnorm_fwd(c, dt, c->sdt, y1, ld, w->norm_m, c->n3, h, T, h, f.rms_eps, s);
   if (Is) {
     after(c, s, s0);
     GemmArgs gs = nt(c->n3, h, m->ws_gate_up, h, c->GUs, 2 * Is, T, 2 * Is, h);
     gs.act_out = c->Hs; gs.ldact = Is; gs.act_half = Is;
-    gs.bulk = c->use_streams;
+    gs.bulk = c->par;
     TRY(run_gemm(c, gs, s0));
     GemmArgs gd = nt(c->Hs, Is, m->ws_down, Is, c->Ys, h, T, h, Is);
     gd.bulk = gs.bulk;
     TRY(run_gemm(c, gd, s0));
   }
-  after(c, sr, s);
+  p_routing(c, y1, ld, m->w_router, w->b_router, T, s);
   GemmArgs g1 = nt(c->n3, h, m->w_gate_up, h, c->GU, 2 * I, N, 2 * I, h);
   g1.group_mode = 1; g1.n_groups = E; g1.offsets = c->offsets; g1.b_group_stride = (i64)2 * I * h;
   g1.a_gather = c->row_map; g1.gather_div = k;
@@ -816,11 +836,11 @@ int check_merged(const revffn_ctx* c, const revffn_merged* m) {
 
 int check_call(revffn_ctx* c, const revffn_weights* w, int B, int S, i64 ld) {
   if (!c || !w) return REVFFN_ENULL;
-  c->fold_queued = false;
   c->fwd_x1 = nullptr;                    // any call invalidates the activations a forward call left behind
   if (B < 1 || S < 1) return REVFFN_ESHAPE;
   if ((i64)B * S > c->maxT) return REVFFN_ESHAPE;
   if (ld < c->cfg.d_model / 2) return REVFFN_ESHAPE;
+  c->par = c->use_streams && fork_pays(c, (i64)B * S);
   if (!w->norm_a1 || !w->norm_a2 || !w->norm_m || !w->pup_a || !w->pdn_a || !w->pup_m || !w->pdn_m || !w->wq ||
       !w->wk || !w->wv || !w->wo || !w->w_router || !w->w_gate_up || !w->w_down)
     return REVFFN_ENULL;
@@ -831,7 +851,6 @@ int check_call(revffn_ctx* c, const revffn_weights* w, int B, int S, i64 ld) {
 int forward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const void* x2, void* y1, void* y2, int B,
                  int S, i64 ld, hipStream_t s) {
   const int T = B * S;
-  router_fold(c, w, s);
   TRY(attn_acts(c, w, x1, ld, x2, ld, B, S, true, s));
   TRY(attn_out(c, w, x1, ld, 1.f, y1, ld, T, s));                 // Eq. 1
   TRY(moe_acts(c, w, y1, ld, T, s));
@@ -878,7 +897,7 @@ int inverse_impl(revffn_ctx* c, const revffn_weights* w, const void* y1, const v
   // (the fused sweep step: the MoE half's backward pass) hands over a stream of its own for it and joins that stream
   // itself, where X1^ is first needed.
   hipStream_t sa = s;
-  if (s_attn && c->use_streams && n >= 1) { sa = s_attn; after(c, s, sa); }
+  if (s_attn && c->par && n >= 1) { sa = s_attn; after(c, s, sa); }
   if (s_attn_used) *s_attn_used = sa;     // == s: nothing was left on another stream
   for (int it = 1; it <= n; it++) {
     const void* xin = (it == 1) ? y1k : x1;                       // iterate, started at Y1
@@ -920,13 +939,12 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
   // it on a stream of its own (sa) and joined where its activations are first used.  (With y1 == NULL the MoE half
   // needs the recomputed Y1 first: one stream.)  s_attn: the stream the caller's inverse left X1^ on.
   hipStream_t sa = s;
-  if (y1 && c->use_streams && !reuse_attn) {
+  if (y1 && c->par && !reuse_attn) {
     sa = s_attn ? s_attn : c->side[3];
     if (!s_attn) after(c, s, sa);
   } else if (s_attn && s_attn != s) {
     after(c, s_attn, s);                  // no overlap in this call: X1^ is needed on s from here on
   }
-  if (!y1 || !reuse_moe) router_fold(c, w, s);
   if (!reuse_attn) TRY(attn_acts(c, w, x1, ld, x2, ld, B, S, !reuse_kv, sa));
   if (!y1) {
     TRY(attn_out(c, w, x1, ld, 1.f, c->y1c, h, T, s));
@@ -937,32 +955,31 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
   // ---- recompute the MoE half at the exact y1
   if (!reuse_moe) TRY(moe_acts(c, w, y1, ldy, T, s));
   // ---- MoE half backward: Y2 = X2 + P_dn_m(RS)
-  // sw: weight gradients of the MoE half (leaves of the graph, joined at the very end); s0: shared-expert branch,
-  // then the weight gradients of the attention half
+  // Weight gradients are leaves of the computation.  With helper streams they run on sw, the experts' next to the data
+  // gradients of the experts, the dense layers' known before the attention core's backward pass as one launch next to
+  // that, so that each launch's last, partly filled round of workgroups is filled by the other stream; the rest, or
+  // without helper streams all of the dense ones, are one launch near the end.  The column sums (bias and gain
+  // gradients) are one launch at the end.
   hipStream_t sw = side(c, s, 1), s0 = side(c, s, 0);
-  if (GF(pdn_m)) {
-    // reads dy2: stays on the caller's stream when dx2 aliases dy2 (dx2 is written at the very end)
-    hipStream_t sp = (dx2 == dy2) ? s : sw;
-    after(c, s, sp);
-    TRY(run_wgrad(c, tn(dy2, ld, c->RS, d, GF(pdn_m), d, h, d, T), sp));
-  }
+  GemmArgs wg[GEMM_BATCH];
+  int nwg = 0;
+  bool sw_used = false;
+  auto to_sw = [&]() { after(c, s, sw); sw_used = true; };      // sw may use what s has computed so far
+  ColsumBatch cs;
   TRY(run_gemm(c, nn(dy2, ld, w->pdn_m, d, c->dRS, d, T, d, h), s));
   p_moe_bwd_rows(c, dt, c->dRS, c->Yp, c->Ys, c->inv_map, c->wts, c->gamma, c->dYp, c->dYs, c->dw, c->dzext, T, d,
                       k, E1, Is ? 1 : 0, s);
   if (Is) {
     after(c, s, s0);
-    if (GF(ws_down)) { after(c, s, sw); TRY(run_wgrad(c, tn(c->dYs, d, c->Hs, Is, GF(ws_down), Is, d, Is, T), sw)); }
     TRY(run_gemm(c, nn(c->dYs, d, w->ws_down, Is, c->dHs, Is, T, Is, d), s0));
     p_swiglu_bwd(c, dt, c->dHs, c->GUs, c->dGUs, T, Is, s0);
-    if (GF(ws_gate_up)) {
-      after(c, s0, sw);
-      TRY(run_wgrad(c, tn(c->dGUs, 2 * Is, c->Um, d, GF(ws_gate_up), d, 2 * Is, d, T), sw));
-    }
     TRY(run_gemm(c, nn(c->dGUs, 2 * Is, w->ws_gate_up, d, c->dUm_sh, d, T, d, 2 * Is), s0));
+    if (GF(ws_down)) wg[nwg++] = tn(c->dYs, d, c->Hs, Is, GF(ws_down), Is, d, Is, T);
+    if (GF(ws_gate_up)) wg[nwg++] = tn(c->dGUs, 2 * Is, c->Um, d, GF(ws_gate_up), d, 2 * Is, d, T);
   }
   {
     if (GF(w_down)) {
-      after(c, s, sw);
+      to_sw();
       GemmArgs b = tn(c->dYp, d, c->Hh, I, GF(w_down), I, d, I, N);        // dWd_e = dYp_e^T . Hh_e
       b.group_mode = 2; b.n_groups = E; b.offsets = c->offsets; b.tile_count = c->tile_cnt + 3; b.c_group_stride = (i64)d * I;
       TRY(run_wgrad(c, b, sw));
@@ -973,7 +990,7 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
     p_swiglu_bwd(c, dt, c->dHh, c->GU, c->dGU, N, I, s);
     if (GF(w_gate_up)) {
       // dWgu_e = dGU_e^T . Xg_e, with the permuted input rows Xg materialised once
-      after(c, s, sw);
+      to_sw();
       p_gather_rows(c, dt, c->Um, c->row_map, k, c->Xg, N, d, sw);
       GemmArgs b = tn(c->dGU, 2 * I, c->Xg, d, GF(w_gate_up), d, 2 * I, d, N);
       b.group_mode = 2; b.n_groups = E; b.offsets = c->offsets; b.tile_count = c->tile_cnt + 3; b.c_group_stride = (i64)2 * I * d;
@@ -988,20 +1005,7 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
   const int E1p = (E1 + 7) / 8 * 8;
   p_router_bwd(c, c->probs, c->idx, c->wts, c->dw, c->dzext, T, E, k, E1, f.norm_topk_prob, s,
                     dz_bf16 ? c->dzb : nullptr, E1p);
-  // every column sum (bias and gain gradients) goes to helper stream 2: they share one scratch buffer, and the
-  // weight-gradient GEMMs keep helper stream 1 to themselves.  The router weight gradient goes there too.
-  hipStream_t sc = side(c, s, 2);
-  if (GF(w_router) || (Is && GF(ws_gate)) || (g && g->b_router)) after(c, s, sc);
-  if (GF(w_router) || (Is && GF(ws_gate))) {
-    // [dW_r ; dw_shared_gate] = dzext^T . Um in one fp32-A GEMM, then the rows go to their buffers
-    GemmArgs a = tn(c->dzext, E1, c->Um, d, c->dwr_tmp, d, E1, d, T);
-    GemmTypes t{0, dt, c->gdt, dt};
-    if (launch_gemm_generic(a, t, sc)) return REVFFN_EUNSUPPORTED;
-    if (GF(w_router)) p_copy_rows(c, c->gdt, c->dwr_tmp, d, GF(w_router), d, E, d, sc);
-    if (Is && GF(ws_gate)) p_copy_rows(c, c->gdt, at(c->dwr_tmp, (size_t)E * d, c->ges), d, GF(ws_gate), d, 1, d, sc);
-  }
-  if (g && g->b_router) p_colsum(c, 0, c->dzext, E1, 0, nullptr, 0, nullptr, 0, g->b_router, c->partial, T, E, sc);
-  if (Is) after(c, s0, s);
+  if (g && g->b_router) add_colsum(cs, 0, c->dzext, E1, 0, nullptr, 0, nullptr, 0, g->b_router, T, E);
   const void* dum_r = nullptr;
   if (dz_bf16) {
     // router term of dUm on the matrix cores: dUm_r = dz . [W_r ; w_gate ; 0], contraction over E1p
@@ -1014,18 +1018,34 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
     GemmTypes tt{1, 1, 1, 1};
     if (launch_gemm_mfma(a, tt, s) == 0) dum_r = c->dUm_r;
   }
+  if (Is) after(c, s0, s);
   p_dum_finalize(c, dt, c->dXg, c->inv_map, Is ? c->dUm_sh : nullptr, dum_r, c->dzext, w->w_router, w->ws_gate,
                       c->dUm, T, d, k, E, E1, s);
-  if (GF(pup_m)) { after(c, s, sw); TRY(run_wgrad(c, tn(c->dUm, d, c->n3, h, GF(pup_m), h, d, h, T), sw)); }
+  if (GF(pup_m)) wg[nwg++] = tn(c->dUm, d, c->n3, h, GF(pup_m), h, d, h, T);
   TRY(run_gemm(c, nn(c->dUm, d, w->pup_m, h, c->dn3, h, T, h, d), s));
   // g1 = dY1 + Norm'(dn3): total gradient at Y1
   p_rmsnorm_bwd(c, dt, c->sdt, c->dn3, h, y1, ldy, w->norm_m, dy1, ld, c->g1, h, c->rinv3, T, h, f.rms_eps, s);
+  add_colsum(cs, c->sdt, y1, ldy, dt, c->dn3, h, c->rinv3, c->gdt, GF(norm_m), T, h);
   // ---- attention half backward: Y1 = X1 + P_dn_a(AO)
   if (sa != s) after(c, sa, s);           // the recomputed attention activations (and X1^ of a fused call)
-  if (GF(norm_m)) { after(c, s, sc); p_colsum(c, c->sdt, y1, ldy, dt, c->dn3, h, c->rinv3, c->gdt, GF(norm_m), c->partial, T, h, sc); }
-  if (GF(pdn_a)) { after(c, s, s0); TRY(run_wgrad(c, tn(c->g1, h, c->AO, d, GF(pdn_a), d, h, d, T), s0)); }
+  if (GF(pdn_m)) wg[nwg++] = tn(dy2, ld, c->RS, d, GF(pdn_m), d, h, d, T);
+  if (GF(pdn_a)) wg[nwg++] = tn(c->g1, h, c->AO, d, GF(pdn_a), d, h, d, T);
   TRY(run_gemm(c, nn(c->g1, h, w->pdn_a, d, c->dAO, d, T, d, h), s));
-  if (GF(wo)) { after(c, s, s0); TRY(run_wgrad(c, tn(c->dAO, d, c->O, d, GF(wo), d, d, d, T), s0)); }
+  if (GF(wo)) wg[nwg++] = tn(c->dAO, d, c->O, d, GF(wo), d, d, d, T);
+  {
+    const bool router_w = GF(w_router) != nullptr, gate_w = Is && GF(ws_gate);
+    if (router_w || gate_w || (c->par && nwg)) to_sw();
+    if (router_w || gate_w) {
+      // [dW_r ; dw_shared_gate] = dzext^T . Um in one fp32-A GEMM (the gate row alone if that is all that is wanted)
+      GemmArgs a = router_w ? tn(c->dzext, E1, c->Um, d, GF(w_router), d, gate_w ? E1 : E, d, T)
+                            : tn(c->dzext + E, E1, c->Um, d, GF(ws_gate), d, 1, d, T);
+      if (router_w && gate_w) a.c_last_row = GF(ws_gate);
+      a.small_tiles = 1;
+      GemmTypes t{0, dt, c->gdt, dt};
+      if (launch_gemm_generic(a, t, sw)) return REVFFN_EUNSUPPORTED;
+    }
+    if (c->par) { TRY(run_wgrad_batch(c, wg, nwg, true, sw)); nwg = 0; }
+  }
   TRY(run_gemm(c, nn(c->dAO, d, w->wo, d, c->dO, d, T, d, d), s));
   {
     // five S x S x dh products (scores, dP, dV, dQ, dK), halved by the causal mask
@@ -1048,75 +1068,48 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
   void* dU1 = c->dU12;
   void* dU2 = at(c->dU12, (size_t)T * d, es);
   const bool sym = f.symmetric != 0;
-  after(c, s, s0);
-  after(c, s, sc);
-  // s0: dU1 next to dU2 on the main stream, then the projection weight gradients
-  hipEvent_t du1_done = nullptr;
-  if (!sym) {
-    TRY(run_gemm(c, nn(c->dQ, d, w->wq, d, dU1, d, T, d, d), s0));
-    du1_done = mark(c, s0);
-  }
-  {
-    // the projection weight gradients asked for, as one launch (problems of one shape)
-    GemmArgs wg[3];
-    int nw = 0;
-    if (GF(wq)) wg[nw++] = tn(c->dQ, d, sym ? U2 : U1, d, GF(wq), d, d, d, T);
-    if (GF(wk)) wg[nw++] = tn(c->dK, d, U2, d, GF(wk), d, d, d, T);
-    if (GF(wv)) wg[nw++] = tn(c->dV, d, U2, d, GF(wv), d, d, d, T);
-    if (nw) wg[0].bulk = c->use_streams;
-    TRY(run_gemm_multi(c, wg, nw, c->gdt, s0));
-  }
-  {
-    // the three bias gradients (column sums of dQ, dK, dV) in one launch pair
-    const void* ba[3]; void* bo[3]; i64 bl[3]; int nb = 0;
-    if (GF(bq) && w->bq) { ba[nb] = c->dQ; bo[nb] = GF(bq); bl[nb++] = d; }
-    if (GF(bk) && w->bk) { ba[nb] = c->dK; bo[nb] = GF(bk); bl[nb++] = d; }
-    if (GF(bv) && w->bv) { ba[nb] = c->dV; bo[nb] = GF(bv); bl[nb++] = d; }
-    p_colsum_batch(c, nb, dt, ba, bl, dt, nullptr, nullptr, nullptr, c->gdt, bo, T, d, sc);
-  }
+  if (GF(wq)) wg[nwg++] = tn(c->dQ, d, sym ? U2 : U1, d, GF(wq), d, d, d, T);
+  if (GF(wk)) wg[nwg++] = tn(c->dK, d, U2, d, GF(wk), d, d, d, T);
+  if (GF(wv)) wg[nwg++] = tn(c->dV, d, U2, d, GF(wv), d, d, d, T);
+  if (w->bq) add_colsum(cs, dt, c->dQ, d, dt, nullptr, 0, nullptr, c->gdt, GF(bq), T, d);
+  if (w->bk) add_colsum(cs, dt, c->dK, d, dt, nullptr, 0, nullptr, c->gdt, GF(bk), T, d);
+  if (w->bv) add_colsum(cs, dt, c->dV, d, dt, nullptr, 0, nullptr, c->gdt, GF(bv), T, d);
   TRY(run_gemm(c, nn(c->dK, d, w->wk, d, dU2, d, T, d, d), s));
   {
     GemmArgs a = nn(c->dV, d, w->wv, d, dU2, d, T, d, d);        // dU2 += dV . Wv
     a.resid = dU2; a.ldr = d; a.resid_sign = 1.f;
     TRY(run_gemm(c, a, s));
   }
+  // sw's weight gradients read dy2, which dx2, written below, may alias
+  auto before_dx2 = [&]() { if (sw_used && dx2 == dy2) { after(c, sw, s); sw_used = false; } };
+  void* n2 = at(c->n12, (size_t)T * h, es);
+  void* dn2 = at(c->dn12, (size_t)T * h, es);
   if (sym) {
     // the query path ends in stream 2 too: dU2 += dQ . Wq; stream 1 only carries the residual path
     GemmArgs a = nn(c->dQ, d, w->wq, d, dU2, d, T, d, d);
     a.resid = dU2; a.ldr = d; a.resid_sign = 1.f;
     TRY(run_gemm(c, a, s));
-    void* n2 = at(c->n12, (size_t)T * h, es);
-    void* dn2 = at(c->dn12, (size_t)T * h, es);
-    if (GF(pup_a)) { after(c, s, s0); TRY(run_wgrad(c, tn(dU2, d, n2, h, GF(pup_a), h, d, h, T), s0)); }
+    if (GF(pup_a)) wg[nwg++] = tn(dU2, d, n2, h, GF(pup_a), h, d, h, T);
     TRY(run_gemm(c, nn(dU2, d, w->pup_a, h, dn2, h, T, h, d), s));
+    TRY(run_wgrad_batch(c, wg, nwg, false, s));
+    before_dx2();
     p_rmsnorm_bwd(c, dt, c->sdt, dn2, h, x2, ld, w->norm_a2, dy2, ld, dx2, ld, c->rinv + T, T, h, f.rms_eps, s);
     p_copy_rows(c, dt, c->g1, h, dx1, ld, T, h, s);              // dX1 = total gradient at Y1
-    after(c, s, sc);
-    if (GF(norm_a1)) launch_zero(c->gdt, GF(norm_a1), h, sc);          // stream 1 is not normalised in this block
-    if (GF(norm_a2)) p_colsum(c, c->sdt, x2, ld, dt, dn2, h, c->rinv + T, c->gdt, GF(norm_a2), c->partial, T, h, sc);
-    after(c, sw, s);
-    after(c, s0, s);
-    after(c, sc, s);
-    return 0;
+    if (GF(norm_a1)) launch_zero(c->gdt, GF(norm_a1), h, s);           // stream 1 is not normalised in this block
+  } else {
+    TRY(run_gemm(c, nn(c->dQ, d, w->wq, d, dU1, d, T, d, d), s));
+    if (GF(pup_a)) wg[nwg++] = tn(c->dU12, d, c->n12, h, GF(pup_a), h, d, h, 2 * T);
+    TRY(run_gemm(c, nn(c->dU12, d, w->pup_a, h, c->dn12, h, 2 * T, h, d), s));
+    TRY(run_wgrad_batch(c, wg, nwg, false, s));
+    before_dx2();
+    // dX1 = g1 + Norm'(dn1);  dX2 = dY2 + Norm'(dn2)
+    p_rmsnorm_bwd(c, dt, c->sdt, c->dn12, h, x1, ld, w->norm_a1, c->g1, h, dx1, ld, c->rinv, T, h, f.rms_eps, s);
+    p_rmsnorm_bwd(c, dt, c->sdt, dn2, h, x2, ld, w->norm_a2, dy2, ld, dx2, ld, c->rinv + T, T, h, f.rms_eps, s);
+    add_colsum(cs, c->sdt, x1, ld, dt, c->dn12, h, c->rinv, c->gdt, GF(norm_a1), T, h);
   }
-  if (s0 != s) wait_for(s, du1_done);
-  if (GF(pup_a)) { after(c, s, s0); TRY(run_wgrad(c, tn(c->dU12, d, c->n12, h, GF(pup_a), h, d, h, 2 * T), s0)); }
-  TRY(run_gemm(c, nn(c->dU12, d, w->pup_a, h, c->dn12, h, 2 * T, h, d), s));
-  // dX1 = g1 + Norm'(dn1);  dX2 = dY2 + Norm'(dn2)
-  p_rmsnorm_bwd(c, dt, c->sdt, c->dn12, h, x1, ld, w->norm_a1, c->g1, h, dx1, ld, c->rinv, T, h, f.rms_eps, s);
-  p_rmsnorm_bwd(c, dt, c->sdt, at(c->dn12, (size_t)T * h, es), h, x2, ld, w->norm_a2, dy2, ld, dx2, ld, c->rinv + T, T, h,
-                     f.rms_eps, s);
-  after(c, s, sc);
-  {
-    // the two gain gradients (sum over tokens of x * dn / rms) in one launch pair
-    const void* ga[2]; const void* gb[2]; const float* gs[2]; void* go[2]; i64 gla[2], glb[2]; int ng = 0;
-    if (GF(norm_a1)) { ga[ng] = x1; gb[ng] = c->dn12; gs[ng] = c->rinv; go[ng] = GF(norm_a1); gla[ng] = ld; glb[ng++] = h; }
-    if (GF(norm_a2)) { ga[ng] = x2; gb[ng] = at(c->dn12, (size_t)T * h, es); gs[ng] = c->rinv + T; go[ng] = GF(norm_a2); gla[ng] = ld; glb[ng++] = h; }
-    p_colsum_batch(c, ng, c->sdt, ga, gla, dt, gb, glb, gs, c->gdt, go, T, h, sc);
-  }
-  after(c, sw, s);                       // every weight gradient is complete for the caller's stream
-  after(c, s0, s);
-  after(c, sc, s);
+  add_colsum(cs, c->sdt, x2, ld, dt, dn2, h, c->rinv + T, c->gdt, GF(norm_a2), T, h);
+  p_colsum_batch(c, cs, s);
+  if (sw_used) after(c, sw, s);          // every weight gradient is complete for the caller's stream
   return 0;
 }
 
@@ -1171,6 +1164,7 @@ int revffn_create(revffn_ctx** out, const revffn_config* cfg, int32_t max_B, int
   carve(c, (char*)c->slab);
   (void)hipMemset(c->wr_ext, 0, (size_t)((c->cfg.n_experts + (c->cfg.d_shared ? 1 : 0) + 7) / 8 * 8) * c->cfg.d_model * c->es);
   (void)hipMemset(c->conv.stats, 0, 4 * sizeof(int));
+  (void)hipMemset(c->ticket, 0, colsum_tickets((size_t)9 * (cfg->d_model / 2) + cfg->n_experts) * 4);
   c->use_streams = getenv("REVFFN_NO_STREAMS") == nullptr;
   { const char* e = getenv("REVFFN_EXPERT_TILE"); if (e && (atoi(e) == 256 || atoi(e) == 128)) c->expert_tile = atoi(e); }
   { const char* e = getenv("REVFFN_NO_FUSED_SWIGLU"); c->no_fused_swiglu = e && atoi(e) != 0; }

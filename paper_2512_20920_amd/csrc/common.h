@@ -11,16 +11,30 @@ typedef long long i64;
 template <class T> __device__ __forceinline__ float to_f(T v) { return (float)v; }
 template <class T> __device__ __forceinline__ T from_f(float v) { return (T)v; }
 
-// xor-butterfly over the 64 lanes: every lane ends with the same, order-fixed sum
+// Reductions over the 64 lanes in a fixed order, result in every lane: inclusive combination inside the rows of 16 lanes,
+// then across rows with the row broadcasts, all as data-parallel-primitive moves (a register-to-register instruction per
+// step; __shfl_xor goes through the LDS crossbar, some 100 clocks a step), and lane 63 read back.
+template <int CTRL, int ROW_MASK> __device__ __forceinline__ float dpp_f(float keep, float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, keep), __builtin_bit_cast(int, v), CTRL, ROW_MASK, 0xf, false));
+}
+__device__ __forceinline__ float lane63(float v) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63)); }
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, WAVE);
-  return v;
+  v += dpp_f<0x111, 0xf>(0.f, v);          // row_shr:1
+  v += dpp_f<0x112, 0xf>(0.f, v);          // row_shr:2
+  v += dpp_f<0x114, 0xf>(0.f, v);          // row_shr:4
+  v += dpp_f<0x118, 0xf>(0.f, v);          // row_shr:8
+  v += dpp_f<0x142, 0xa>(0.f, v);          // row_bcast:15 into rows 1 and 3
+  v += dpp_f<0x143, 0xc>(0.f, v);          // row_bcast:31 into rows 2 and 3
+  return lane63(v);
 }
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, WAVE));
-  return v;
+  v = fmaxf(v, dpp_f<0x111, 0xf>(v, v));
+  v = fmaxf(v, dpp_f<0x112, 0xf>(v, v));
+  v = fmaxf(v, dpp_f<0x114, 0xf>(v, v));
+  v = fmaxf(v, dpp_f<0x118, 0xf>(v, v));
+  v = fmaxf(v, dpp_f<0x142, 0xa>(v, v));
+  v = fmaxf(v, dpp_f<0x143, 0xc>(v, v));
+  return lane63(v);
 }
 
 // Block-wide sum for blockDim.x = 256 (4 waves); result valid in every thread.

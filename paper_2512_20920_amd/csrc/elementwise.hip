@@ -196,139 +196,94 @@ void launch_rmsnorm_bwd(int dt, int tx, const void* dy, i64 ldd, const void* x, 
 }
 
 // ---------------------------------------------------------------------------------
-// Deterministic column sum in two stages (used for gain, bias and router-bias gradients).
-// Stage 1: block (column tile of 64, row chunk c) -> partial[c][col]; stage 2 adds the
-// chunks in index order.
+// Deterministic column sums (gain, bias and router-bias gradients), all of a call in one launch.  A workgroup adds one
+// chunk of rows of 256 columns (a thread owns 8 adjacent columns and every 8th row) and leaves the chunk's sums in
+// `partial`; the last workgroup of those columns to finish, told by a ticket, adds the chunks in index order, so the
+// result does not depend on which one that is.  Latency-bound (8-25 MB in all): one launch instead of four pairs.
 // ---------------------------------------------------------------------------------
 #define COLSUM_CHUNKS 32
-static int colsum_chunk_rows(int rows) { int c = cdiv(rows > 0 ? rows : 1, COLSUM_CHUNKS); return c < 32 ? 32 : c; }
-size_t colsum_partial_floats(int rows, int cols) { return (size_t)COLSUM_BATCH * (COLSUM_CHUNKS + 1) * cols; }
+__host__ __device__ inline int colsum_chunk_rows(int rows) { const int c = (rows + COLSUM_CHUNKS - 1) / COLSUM_CHUNKS; return c < 32 ? 32 : c; }
+size_t colsum_tickets(size_t cols_sum) { return (cols_sum + 255) / 256 + COLSUM_MAX; }
+size_t colsum_partial_floats(size_t cols_sum) { return colsum_tickets(cols_sum) * (COLSUM_CHUNKS + 1) * 256; }
 
-// Up to COLSUM_BATCH problems of one shape and type go into one launch pair (blockIdx.z = problem).
-struct ColsumBatch {
-  const void* a[COLSUM_BATCH]; const void* b[COLSUM_BATCH]; const float* sc[COLSUM_BATCH]; void* out[COLSUM_BATCH];
-  i64 lda[COLSUM_BATCH], ldb[COLSUM_BATCH];
-};
-template <class TA, class TB>
-__global__ void __launch_bounds__(256) colsum1_k(ColsumBatch q, float* __restrict__ partial_all, int rows, int cols,
-                                                 int chunk, int chunks) {
-  __shared__ float red[4][64];
-  const int z = blockIdx.z;
-  const TA* __restrict__ a = (const TA*)q.a[z];
-  const TB* __restrict__ b = (const TB*)q.b[z];
-  const float* __restrict__ sc = q.sc[z];
-  const i64 lda = q.lda[z], ldb = q.ldb[z];
-  float* partial = partial_all + (i64)z * chunks * cols;
-  int c = blockIdx.x * 64 + (threadIdx.x & 63);
-  int qd = threadIdx.x >> 6;
-  int r0 = blockIdx.y * chunk;
-  int r1 = min(rows, r0 + chunk);
-  float acc = 0.f;
-  if (c < cols) {
-    for (int t = r0 + qd; t < r1; t += 4) {
-      float v = to_f(a[(i64)t * lda + c]);
-      if (b) v *= to_f(b[(i64)t * ldb + c]);
-      if (sc) v *= sc[t];
-      acc += v;
-    }
-  }
-  red[qd][threadIdx.x & 63] = acc;
-  __syncthreads();
-  if (qd == 0 && c < cols) {
-    float v = (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
-    partial[(i64)blockIdx.y * cols + c] = v;
-  }
+// 8 consecutive elements from column c on, of which those below cols exist; vec: all 8 at once
+__device__ __forceinline__ f32x8 colsum_load(const void* p, bool f32, i64 off, int n, bool vec) {
+  f32x8 o;
+  if (vec) return f32 ? load8((const float*)p + off) : load8((const bf16*)p + off);
+#pragma unroll
+  for (int i = 0; i < 8; i++) o.v[i] = i < n ? (f32 ? ((const float*)p)[off + i] : (float)((const bf16*)p)[off + i]) : 0.f;
+  return o;
 }
-// bf16 operands with 8 | cols at 16-byte aligned addresses: a thread owns 8 adjacent columns (16-byte loads) and every
-// 8th row of the chunk; the 8 row lanes are added in lane order.  Same two-stage, fixed-order scheme.
-__global__ void __launch_bounds__(256) colsum1_v8_k(ColsumBatch q, float* __restrict__ partial_all, int rows, int cols,
-                                                    int chunk, int chunks) {
+__global__ void __launch_bounds__(256) colsum_k(ColsumBatch q, float* __restrict__ partial_all, int* __restrict__ ticket) {
   __shared__ float red[8][256];
-  const int z = blockIdx.z;
-  const bf16* __restrict__ a = (const bf16*)q.a[z];
-  const bf16* __restrict__ b = (const bf16*)q.b[z];
-  const float* __restrict__ sc = q.sc[z];
-  const i64 lda = q.lda[z], ldb = q.ldb[z];
-  float* partial = partial_all + (i64)z * chunks * cols;
+  __shared__ int last;
+  int z = 0;
+#pragma unroll
+  for (int i = 1; i < COLSUM_MAX; i++) if (i < q.n && (int)blockIdx.x >= q.p[i].tile0) z = i;
+  Colsum p = q.p[0];
+#pragma unroll
+  for (int i = 1; i < COLSUM_MAX; i++) if (z == i) p = q.p[i];     // (constant indices: no copy of the arguments)
+  const int chunk = colsum_chunk_rows(p.rows), chunks = (p.rows + chunk - 1) / chunk;
+  if ((int)blockIdx.y >= chunks) return;
+  float* partial = partial_all + (i64)blockIdx.x * (COLSUM_CHUNKS + 1) * 256;
   const int cg = threadIdx.x & 31, qd = threadIdx.x >> 5;
-  const int c = blockIdx.x * 256 + cg * 8;
-  const int r0 = blockIdx.y * chunk, r1 = min(rows, r0 + chunk);
+  const int c0 = ((int)blockIdx.x - p.tile0) * 256, c = c0 + cg * 8;
+  const int r0 = blockIdx.y * chunk, r1 = min(p.rows, r0 + chunk);
+  const int n = min(8, p.cols - c);
+  const bool va = n == 8 && (p.lda & 7) == 0 && ((uintptr_t)p.a & 15) == 0, vb = n == 8 && (p.ldb & 7) == 0 && ((uintptr_t)p.b & 15) == 0;
   float acc[8];
 #pragma unroll
   for (int i = 0; i < 8; i++) acc[i] = 0.f;
-  if (c < cols) {
+  if (n > 0) {
 #pragma unroll 4
     for (int t = r0 + qd; t < r1; t += 8) {
-      const bf16x8_v av = *(const bf16x8_v*)(a + (i64)t * lda + c);
-      const float w = sc ? sc[t] : 1.f;
-      if (b) {
-        const bf16x8_v bv = *(const bf16x8_v*)(b + (i64)t * ldb + c);
+      const f32x8 av = colsum_load(p.a, p.a_f32, (i64)t * p.lda + c, n, va);
+      const float w = p.sc ? p.sc[t] : 1.f;
+      if (p.b) {
+        const f32x8 bv = colsum_load(p.b, p.b_f32, (i64)t * p.ldb + c, n, vb);
 #pragma unroll
-        for (int i = 0; i < 8; i++) acc[i] += (float)av[i] * (float)bv[i] * w;
+        for (int i = 0; i < 8; i++) acc[i] += av.v[i] * bv.v[i] * w;
       } else {
 #pragma unroll
-        for (int i = 0; i < 8; i++) acc[i] += (float)av[i] * w;
+        for (int i = 0; i < 8; i++) acc[i] += av.v[i] * w;
       }
     }
   }
 #pragma unroll
   for (int i = 0; i < 8; i++) red[qd][cg * 8 + i] = acc[i];
   __syncthreads();
-  const int cc = blockIdx.x * 256 + threadIdx.x;
-  if (cc < cols) {
-    float v = 0.f;
+  float v = 0.f;
 #pragma unroll
-    for (int j = 0; j < 8; j++) v += red[j][threadIdx.x];
-    partial[(i64)blockIdx.y * cols + cc] = v;
+  for (int j = 0; j < 8; j++) v += red[j][threadIdx.x];
+  if (chunks > 1) {
+    // Agent scope: the other chunks' workgroups may run on other XCDs.  The stores go through to memory by themselves,
+    // so waiting for them is all the ticket needs; a release fence would write the whole L2 back in every workgroup
+    // (151 us instead of 9 at T = 2048).
+    __hip_atomic_store(partial + (i64)blockIdx.y * 256 + threadIdx.x, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) last = __hip_atomic_fetch_add(ticket + blockIdx.x, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == chunks - 1;
+    __syncthreads();
+    if (!last) return;
+    v = 0.f;
+#pragma unroll 8
+    for (int i = 0; i < chunks; i++) v += __hip_atomic_load(partial + (i64)i * 256 + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x == 0) __hip_atomic_store(ticket + blockIdx.x, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  if (c0 + (int)threadIdx.x < p.cols) {
+    if (p.out_f32) ((float*)p.out)[c0 + threadIdx.x] = v;
+    else ((bf16*)p.out)[c0 + threadIdx.x] = (bf16)v;
   }
 }
-template <class TO>
-__global__ void colsum2_k(const float* __restrict__ partial_all, ColsumBatch q, int chunks, int cols) {
-  int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= cols) return;
-  const float* partial = partial_all + (i64)blockIdx.z * chunks * cols;
-  float acc = 0.f;
-  for (int i = 0; i < chunks; i++) acc += partial[(i64)i * cols + c];
-  ((TO*)q.out[blockIdx.z])[c] = from_f<TO>(acc);
-}
-
-template <class TA, class TB>
-static void colsum_go(const ColsumBatch& q, int n, int tout, float* partial, int rows, int cols, hipStream_t s) {
-  int chunk = colsum_chunk_rows(rows);
-  int chunks = cdiv(rows > 0 ? rows : 1, chunk);
-  constexpr bool both_bf16 = sizeof(TA) == 2 && sizeof(TB) == 2;
-  bool v8 = both_bf16 && (cols & 7) == 0;
-  for (int z = 0; z < n; z++)
-    v8 = v8 && (q.lda[z] & 7) == 0 && (!q.b[z] || (q.ldb[z] & 7) == 0) && ((uintptr_t)q.a[z] & 15) == 0 && ((uintptr_t)q.b[z] & 15) == 0;
-  if (v8) {
-    hipLaunchKernelGGL(colsum1_v8_k, dim3(cdiv(cols, 256), chunks, n), dim3(256), 0, s, q, partial, rows, cols, chunk, chunks);
-  } else {
-    hipLaunchKernelGGL((colsum1_k<TA, TB>), dim3(cdiv(cols, 64), chunks, n), dim3(256), 0, s, q, partial, rows, cols, chunk, chunks);
+void launch_colsum_batch(ColsumBatch& q, float* partial, int* ticket, hipStream_t s) {
+  int tiles = 0, chunks = 1;
+  for (int i = 0; i < q.n; i++) {
+    q.p[i].tile0 = tiles;
+    tiles += cdiv(q.p[i].cols, 256);
+    const int ch = cdiv(q.p[i].rows, colsum_chunk_rows(q.p[i].rows));
+    if (ch > chunks) chunks = ch;
   }
-  if (tout == 0)
-    hipLaunchKernelGGL(colsum2_k<float>, dim3(cdiv(cols, 256), 1, n), dim3(256), 0, s, partial, q, chunks, cols);
-  else
-    hipLaunchKernelGGL(colsum2_k<bf16>, dim3(cdiv(cols, 256), 1, n), dim3(256), 0, s, partial, q, chunks, cols);
-}
-
-void launch_colsum_batch(int n, int ta, const void* const* a, const i64* lda, int tb, const void* const* b, const i64* ldb,
-                         const float* const* sc, int tout, void* const* out, float* partial, int rows, int cols,
-                         hipStream_t s) {
-  if (cols <= 0 || n <= 0 || n > COLSUM_BATCH) return;
-  ColsumBatch q;
-  for (int z = 0; z < COLSUM_BATCH; z++) {
-    const int y = z < n ? z : 0;
-    q.a[z] = a[y]; q.b[z] = b ? b[y] : nullptr; q.sc[z] = sc ? sc[y] : nullptr; q.out[z] = out[y];
-    q.lda[z] = lda[y]; q.ldb[z] = ldb ? ldb[y] : 0;
-  }
-  if (ta == 0 && tb == 0) colsum_go<float, float>(q, n, tout, partial, rows, cols, s);
-  else if (ta == 0 && tb == 1) colsum_go<float, bf16>(q, n, tout, partial, rows, cols, s);
-  else if (ta == 1 && tb == 0) colsum_go<bf16, float>(q, n, tout, partial, rows, cols, s);
-  else colsum_go<bf16, bf16>(q, n, tout, partial, rows, cols, s);
-}
-void launch_colsum(int ta, const void* a, i64 lda, int tb, const void* b, i64 ldb, const float* sc, int tout,
-                   void* out, float* partial, int rows, int cols, hipStream_t s) {
-  launch_colsum_batch(1, ta, &a, &lda, tb, &b, &ldb, &sc, tout, &out, partial, rows, cols, s);
+  if (tiles > 0) hipLaunchKernelGGL(colsum_k, dim3(tiles, chunks), dim3(256), 0, s, q, partial, ticket);
 }
 
 // ---------------------------------------------------------------------------------

@@ -13,10 +13,10 @@
 
 #include "operand_f32.h"
 
-template <class TA, class TB, class TC, class TS, bool AT, bool BT, int TM, int TN>
-__global__ void __launch_bounds__(TM * TN == 1 ? 512 : 256) gemm_f32_k(GemmArgs g) {
-  extern __shared__ __attribute__((aligned(16))) float part[];      // [waves][32 TM][32 TN]
-  constexpr int BM = 32 * TM, BN = 32 * TN;
+template <class TA, class TB, class TC, class TS, bool AT, bool BT, int R, int TM, int TN>
+__global__ void __launch_bounds__(R == 16 ? 1024 : 512) gemm_f32_k(GemmArgs g) {
+  extern __shared__ __attribute__((aligned(16))) float part[];      // [waves][R TM][R TN]
+  constexpr int BM = R * TM, BN = R * TN, EL = R * R / 64;   // (EL elements of a tile per lane)
   const TA* A = (const TA*)g.A;
   const TB* Bm = (const TB*)g.B;
   TC* C = (TC*)g.C;
@@ -43,102 +43,110 @@ __global__ void __launch_bounds__(TM * TN == 1 ? 512 : 256) gemm_f32_k(GemmArgs 
     if (!__any(live)) return;
   }
   const int n0 = blockIdx.x * BN;
-  const int lane = threadIdx.x & 63, gh = lane >> 5, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  f32x16 acc[TM][TN];
+  const int lane = threadIdx.x & 63, gh = lane / R, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = g.k_waves;
+  typename AccOf<R>::type acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; i++)
 #pragma unroll
     for (int j = 0; j < TN; j++)
 #pragma unroll
-      for (int e = 0; e < 16; e++) acc[i][j][e] = 0.f;
-  const int nchunk = (k_end - k0 + GKC - 1) / GKC;
-  if (wv < nchunk) {
-    Operand<TA, AT> oa[TM];
-    Operand<TB, BT> ob[TN];
+      for (int e = 0; e < EL; e++) acc[i][j][e] = 0.f;
+  const int nchunk = (k_end - k0 + GKC(R) - 1) / GKC(R);
+  const int parts = min(nw, max(nchunk, 1));
+  if (wv < min(nchunk, nw)) {
+    Operand<TA, AT, R> oa[TM];
+    Operand<TB, BT, R> ob[TN];
 #pragma unroll
-    for (int i = 0; i < TM; i++) oa[i].init(A, g.lda, m0 + 32 * i, m_end, lane, g.a_gather, g.gather_div, k0, (const TA*)g.a_last_row);
+    for (int i = 0; i < TM; i++) oa[i].init(A, g.lda, m0 + R * i, m_end, lane, g.a_gather, g.gather_div, k0, (const TA*)g.a_last_row);
 #pragma unroll
-    for (int j = 0; j < TN; j++) ob[j].init(Bm, g.ldb, n0 + 32 * j, g.N, lane, nullptr, 1, k0);
-    float va[2][TM][16], vb[2][TN][16];
-    auto fetch = [&](int c, float (&a)[TM][16], float (&b)[TN][16]) {
-#pragma unroll
-      for (int i = 0; i < TM; i++) oa[i].load(k0 + c * GKC, k_end, gh, a[i]);
-#pragma unroll
-      for (int j = 0; j < TN; j++) ob[j].load(k0 + c * GKC, k_end, gh, b[j]);
-    };
-    auto mul = [&](float (&a)[TM][16], float (&b)[TN][16]) {
+    for (int j = 0; j < TN; j++) ob[j].init(Bm, g.ldb, n0 + R * j, g.N, lane, nullptr, 1, k0);
+    k_loop<R, TM, TN>(oa, ob, k0, k_end, wv, nw, nchunk, gh, [&](float (&a)[TM][16], float (&b)[TN][16]) {
 #pragma unroll
       for (int s = 0; s < 16; s++)
 #pragma unroll
         for (int i = 0; i < TM; i++)
 #pragma unroll
-          for (int j = 0; j < TN; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][s], b[j][s], acc[i][j], 0, 0, 0);
-    };
-    int c = wv;
-    fetch(c, va[0], vb[0]);
-    for (; c + nw < nchunk; c += 2 * nw) {           // one chunk in flight while the one before it is multiplied
-      fetch(c + nw, va[1], vb[1]);
-      mul(va[0], vb[0]);
-      if (c + 2 * nw < nchunk) fetch(c + 2 * nw, va[0], vb[0]);
-      mul(va[1], vb[1]);
-    }
-    if (c < nchunk) mul(va[0], vb[0]);
+          for (int j = 0; j < TN; j++) acc[i][j] = mfma_f32(a[i][s], b[j][s], acc[i][j]);
+    });
   }
   // ---- partial tiles to LDS, added in wave order by all threads, then the epilogue on whole output rows
-  float* mine = part + wv * (BM * BN);
+  if (wv < parts) {
+    float* mine = part + wv * (BM * BN);
 #pragma unroll
-  for (int i = 0; i < TM; i++)
+    for (int i = 0; i < TM; i++)
 #pragma unroll
-    for (int j = 0; j < TN; j++)
+      for (int j = 0; j < TN; j++)
 #pragma unroll
-      for (int e = 0; e < 16; e++)
-        mine[(i * 32 + (e >> 2) * 8 + gh * 4 + (e & 3)) * BN + j * 32 + (lane & 31)] = acc[i][j][e];
+        for (int e = 0; e < EL; e++) mine[(i * R + acc_row<R>(lane, e)) * BN + j * R + (lane & (R - 1))] = acc[i][j][e];
+  }
   __syncthreads();
+  constexpr int EPT = BM * BN / 256;                 // elements per thread
+  float v[EPT];
+#pragma unroll
+  for (int u = 0; u < EPT; u++) v[u] = 0.f;
+  if (threadIdx.x >= 256) return;
+#pragma unroll 2
+  for (int w = 0; w < parts; w++)
+#pragma unroll
+    for (int u = 0; u < EPT; u++) v[u] += part[w * (BM * BN) + threadIdx.x + u * 256];
   const TS* bias = (const TS*)g.bias;
   const TS* resid = (const TS*)g.resid;
   const TS* cscale = (const TS*)g.col_scale;
-  const int parts = min(nw, max(nchunk, 1));
-  for (int e = threadIdx.x; e < BM * BN; e += blockDim.x) {
-    const int m = m0 + e / BN, n = n0 + e % BN;
+  // (loads of all elements first, from clamped positions, so that they are in flight together)
+  float sc[EPT], bi[EPT], rs[EPT];
+#pragma unroll
+  for (int u = 0; u < EPT; u++) {
+    const int e = threadIdx.x + u * 256, m = min(m0 + e / BN, m_end - 1), n = min(n0 + e % BN, g.N - 1);
+    sc[u] = cscale ? to_f(cscale[n]) : 1.f;
+    bi[u] = bias ? to_f(bias[n]) : 0.f;
+    rs[u] = resid ? (g.resid_f32 ? ((const float*)g.resid)[(i64)m * g.ldr + n] : to_f(resid[(i64)m * g.ldr + n])) : 0.f;
+  }
+#pragma unroll
+  for (int u = 0; u < EPT; u++) {
+    const int e = threadIdx.x + u * 256, m = m0 + e / BN, n = n0 + e % BN;
     if (m >= m_end || n >= g.N) continue;
-    float v = 0.f;
-    for (int w = 0; w < parts; w++) v += part[w * (BM * BN) + e];
-    if (cscale) v *= to_f(cscale[n]);
-    if (bias) v += to_f(bias[n]);
-    if (g.tap) g.tap[(i64)m * g.ldtap + n] = v;
-    if (resid) v = (g.resid_f32 ? ((const float*)g.resid)[(i64)m * g.ldr + n] : to_f(resid[(i64)m * g.ldr + n])) + g.resid_sign * v;
-    C[(i64)m * g.ldc + n] = from_f<TC>(v);
+    const float x = v[u] * sc[u] + bi[u];
+    if (g.tap) g.tap[(i64)m * g.ldtap + n] = x;
+    TC* crow = g.c_last_row && m == g.M - 1 ? (TC*)g.c_last_row : C + (i64)m * g.ldc;
+    crow[n] = from_f<TC>(resid ? rs[u] + g.resid_sign * x : x);
   }
 }
 
-template <class TA, class TB, class TC, class TS, bool AT, bool BT, int TM, int TN>
+template <class TA, class TB, class TC, class TS, bool AT, bool BT, int R, int TM, int TN>
 static void go_shape(const GemmArgs& g, int nw, hipStream_t s) {
-  const int gy = g.group_mode == 1 ? g.max_tiles : cdiv(g.M, 32 * TM);
-  const dim3 grid(cdiv(g.N, 32 * TN), gy, g.group_mode == 2 ? g.n_groups : 1);
+  const int gy = g.group_mode == 1 ? g.max_tiles : cdiv(g.M, R * TM);
+  const dim3 grid(cdiv(g.N, R * TN), gy, g.group_mode == 2 ? g.n_groups : 1);
   if (grid.x == 0 || grid.y == 0 || grid.z == 0) return;
-  const size_t smem = (size_t)nw * 1024 * TM * TN * sizeof(float);
+  const size_t smem = (size_t)nw * (R * TM) * (R * TN) * sizeof(float);
   static std::atomic<unsigned long long> attr_mask{0};
-  if (smem > 65536 - 1024 && attr_needed(attr_mask)) {
-    (void)hipFuncSetAttribute((const void*)gemm_f32_k<TA, TB, TC, TS, AT, BT, TM, TN>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, 65536);
+  if (smem >= 65536 && attr_needed(attr_mask)) {
+    (void)hipFuncSetAttribute((const void*)gemm_f32_k<TA, TB, TC, TS, AT, BT, R, TM, TN>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, 8 * 4096 * TM * TN);
     attr_done(attr_mask);
   }
-  hipLaunchKernelGGL((gemm_f32_k<TA, TB, TC, TS, AT, BT, TM, TN>), grid, dim3(64 * nw), smem, s, g);
+  GemmArgs a = g;
+  a.k_waves = nw;
+  hipLaunchKernelGGL((gemm_f32_k<TA, TB, TC, TS, AT, BT, R, TM, TN>), grid, dim3(64 * (nw > 4 ? nw : 4)), smem, s, a);
 }
 
 template <class TA, class TB, class TC, class TS, bool AT, bool BT>
 static void go(const GemmArgs& g, hipStream_t s) {
-  // 64x64 tiles of 4 waves (half the operand traffic per product) once they alone are a workgroup per CU; otherwise
-  // 32x32 tiles, with as many waves as leave each two chunks of k (one to multiply, one in flight), at most 8.  Where
-  // the tiles alone put more than 16 waves on a CU, further cutting of k only adds partial sums.
-  const i64 z = g.group_mode == 2 ? g.n_groups : 1;
-  if (g.group_mode != 1 && (i64)cdiv(g.M, 64) * cdiv(g.N, 64) * z >= 256) { go_shape<TA, TB, TC, TS, AT, BT, 2, 2>(g, 4, s); return; }
-  const i64 tiles = (i64)(g.group_mode == 1 ? g.max_tiles : cdiv(g.M, 32)) * cdiv(g.N, 32) * z;
+  // One wave per chunk of k, at most 8 (of a workgroup of at least 4: the epilogue wants the threads).  The cut depends
+  // on k alone, so that a result has the same bits whatever else is in the launch (a product over 2 T rows and one over
+  // T rows, say).  64x32 tiles (a quarter less operand traffic per product) where they alone are 16 waves per CU, else
+  // 32x32.  small_tiles (the caller's choice, since it changes the order of the sum): 16x16 tiles and up to 16 waves, for
+  // the few dozen rows of the router matrices, whose 32x32 tiles would leave most CUs idle.
   const int krange = g.group_mode == 2 ? cdiv(g.K, g.n_groups) : g.K;    // (per expert: the mean)
   int nw = 1;
-  while (nw < 8 && krange >= 4 * GKC * nw) nw *= 2;
-  while (nw > 4 && tiles * nw > 8192) nw /= 2;
-  go_shape<TA, TB, TC, TS, AT, BT, 1, 1>(g, nw, s);
+  if (g.small_tiles && g.group_mode == 0) {
+    while (nw < 16 && krange > GKC(16) * nw) nw *= 2;
+    go_shape<TA, TB, TC, TS, AT, BT, 16, 1, 1>(g, nw, s);
+    return;
+  }
+  while (nw < 8 && krange > GKC(32) * nw) nw *= 2;
+  const i64 z = g.group_mode == 2 ? g.n_groups : 1;
+  if (g.group_mode != 1 && (i64)cdiv(g.M, 64) * cdiv(g.N, 32) * z * nw >= 4096) go_shape<TA, TB, TC, TS, AT, BT, 32, 2, 1>(g, nw, s);
+  else go_shape<TA, TB, TC, TS, AT, BT, 32, 1, 1>(g, nw, s);
 }
 
 template <class TA, class TB, class TC, class TS>

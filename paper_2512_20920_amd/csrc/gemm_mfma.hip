@@ -21,6 +21,7 @@
 //    of 16 lanes, lane j receives element (j & 3) of the 8-byte words addressed by lanes
 //    4*e + (j >> 2), e = 0..3.
 #include "kernels.h"
+#include <math.h>
 #include <stdlib.h>
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
@@ -621,6 +622,66 @@ static void pick_tile(const GemmArgs& g, hipStream_t s) {
   }
 }
 
+// ---- several weight gradients as one launch ------------------------------------------------------------------------
+// The dense layers' weight gradients (4 to 10 per call, K = tokens) are leaves of the computation, so they can wait for
+// each other and share the rounds of workgroups: alone a 2048 x 2048 result is 64 tiles of 256x256 for 256 CUs, so each
+// ran on smaller, dearer tiles, and every launch had a last round of its own.
+// Tiles are numbered over the problems, inside a problem in bands of 4 tile rows with the row fastest; XCD c takes one
+// consecutive run of them, so that what it holds in its L2 at a time is a 4 x 8 block of one problem.
+template <int BM, int BN, int WGM, class TC, int NW, int NS, int KB>
+__global__ void __launch_bounds__(NW * 64) gemm_batch_tn_k(GemmBatch b) {
+  typedef const __attribute__((address_space(4))) GemmBatch* KernArg;     // (indexed in the kernel-argument segment, where
+  const KernArg ka = (KernArg)__builtin_amdgcn_kernarg_segment_ptr();     // a copy by value would go through scratch)
+  const int total = ka->total, n = ka->n;
+  const int c = (int)blockIdx.x & 7, loc = (int)blockIdx.x >> 3, q = total >> 3, r = total & 7;
+  if (loc >= q + (c < r ? 1 : 0)) return;
+  const int id = c * q + (c < r ? c : r) + loc;
+  int i = 0;
+  while (i + 1 < n && id >= ka->p[i + 1].tile0) i++;
+  const int tm = ka->p[i].tiles_m, tn = ka->p[i].tiles_n;
+  const int local = id - ka->p[i].tile0, band = local / (4 * tn), rem = local - band * 4 * tn;
+  const int bh = tm - band * 4 < 4 ? tm - band * 4 : 4;
+  const int bx = rem / bh, by = band * 4 + rem - bx * bh;
+  GemmArgs g;
+  g.M = ka->p[i].M; g.N = ka->p[i].N; g.K = ka->p[i].K;
+  g.lda = ka->p[i].lda; g.ldb = ka->p[i].ldb; g.ldc = ka->p[i].ldc;
+  gemm_tile<BM, BN, WGM, true, true, TC, NW, NS, BM / WGM / 32, KB>(g, (const bf16*)ka->p[i].A, (const bf16*)ka->p[i].B,
+                                                                    (TC*)ka->p[i].C, nullptr, bx, 0, by * BM, g.M, 0, g.K, 0);
+}
+template <int BM, int BN, int WGM, class TC, int NW, int NS, int KB = BK>
+static void go_batch(GemmBatch& b, hipStream_t s) {
+  b.total = 0;
+  for (int i = 0; i < b.n; i++) {
+    GemmProb& p = b.p[i];
+    p.tile0 = b.total; p.tiles_m = cdiv(p.M, BM); p.tiles_n = cdiv(p.N, BN);
+    b.total += p.tiles_m * p.tiles_n;
+  }
+  constexpr size_t smem = (size_t)NS * (BM + BN) * KB * 2;
+  static std::atomic<unsigned long long> attr_mask{0};
+  if (attr_needed(attr_mask)) {
+    (void)hipFuncSetAttribute((const void*)gemm_batch_tn_k<BM, BN, WGM, TC, NW, NS, KB>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    attr_done(attr_mask);
+  }
+  if (b.total > 0)
+    hipLaunchKernelGGL((gemm_batch_tn_k<BM, BN, WGM, TC, NW, NS, KB>), dim3(cdiv(b.total, 8) * 8), dim3(NW * 64), smem, s, b);
+}
+template <class TC> static void pick_batch_tile(GemmBatch& b, bool bulk, hipStream_t s) {
+  // the same costs per tile as for a single problem (pick_tile), over the tiles of all problems
+  double t64 = 0, t128 = 0, t256x128 = 0, t256 = 0;
+  for (int i = 0; i < b.n; i++) {
+    t64 += (double)cdiv(b.p[i].M, 128) * cdiv(b.p[i].N, 64);
+    t128 += (double)cdiv(b.p[i].M, 128) * cdiv(b.p[i].N, 128);
+    t256x128 += (double)cdiv(b.p[i].M, 256) * cdiv(b.p[i].N, 128);
+    t256 += (double)cdiv(b.p[i].M, 256) * cdiv(b.p[i].N, 256);
+  }
+  auto rounds = [&](double t) { return bulk && t256 >= 128 ? t / 256.0 : ceil(t / 256.0); };
+  const double c2 = rounds(t128), c3 = 1.72 * rounds(t256x128), c4 = 3.05 * rounds(t256);
+  if (c4 < c2 && c4 < c3) go_batch<256, 256, 2, TC, 8, 4, 32>(b, s);
+  else if (c3 < c2) go_batch<256, 128, 4, TC, 8, 3>(b, s);
+  else if (t128 >= 200) go_batch<128, 128, 4, TC, 8, 4>(b, s);
+  else go_batch<128, 64, 4, TC, 8, 3>(b, s);
+}
 static bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 int launch_gemm_mfma(const GemmArgs& g, GemmTypes t, hipStream_t s) {
@@ -658,5 +719,16 @@ int launch_gemm_mfma(const GemmArgs& g, GemmTypes t, hipStream_t s) {
   } else {
     if (f32out) pick_tile<true, true, float>(g, s); else pick_tile<true, true, bf16>(g, s);
   }
+  return 0;
+}
+
+int launch_gemm_batch_tn(GemmBatch& b, int out_f32, int bulk, hipStream_t s) {
+  for (int i = 0; i < b.n; i++) {
+    const GemmProb& p = b.p[i];
+    if (!aligned16(p.A) || !aligned16(p.B) || (p.lda & 7) || (p.ldb & 7) || (p.M & 7) || (p.N & 7) || p.M <= 0) return 1;
+    if ((i64)p.K * p.lda >= (i64)1 << 30 || (i64)p.K * p.ldb >= (i64)1 << 30) return 1;
+  }
+  if (b.n == 0) return 0;
+  if (out_f32) pick_batch_tile<float>(b, bulk, s); else pick_batch_tile<bf16>(b, bulk, s);
   return 0;
 }

@@ -24,7 +24,10 @@ struct GemmArgs {
   i64 lda = 0, ldb = 0, ldc = 0;
   int a_trans = 0, b_trans = 0;
   const int* a_gather = nullptr; int gather_div = 1;
+  int small_tiles = 0;                   // generic kernel, dense problems of few rows: 16x16 tiles
+  int k_waves = 1;                       // set by its launcher
   const void* a_last_row = nullptr;      // generic kernel, a_trans = 0: row M - 1 of A is stored there
+  void* c_last_row = nullptr;            // generic kernel: row M - 1 of C goes there
   const void* bias = nullptr;
   const void* resid = nullptr; i64 ldr = 0; float resid_sign = 1.f;
   int resid_f32 = 0;                     // resid holds float32 whatever the side type is (fp32 residual streams)
@@ -143,6 +146,14 @@ int launch_gemm_generic(const GemmArgs& g, GemmTypes t, hipStream_t s);
 // (nothing launched), 0 if launched.
 int launch_gemm_mfma(const GemmArgs& g, GemmTypes t, hipStream_t s);
 
+// Weight gradients of several dense layers, C_i[M_i,N_i] = A_i^T . B_i with A_i [K_i, M_i], B_i [K_i, N_i] row-major
+// (bf16 operands, bf16 or float32 results), as one launch.  Returns 1 (nothing launched) if a problem does not meet
+// the matrix-core kernel's alignment rules.
+#define GEMM_BATCH 12
+struct GemmProb { const void *A, *B; void* C; int M, N, K, lda, ldb, ldc; int tile0, tiles_m, tiles_n; };
+struct GemmBatch { int n = 0, total = 0; GemmProb p[GEMM_BATCH]; };
+int launch_gemm_batch_tn(GemmBatch& b, int out_f32, int bulk, hipStream_t s);
+
 // ---- normalisation / element-wise ------------------------------------------------
 // tx: element type of x (0 float32, 1 bf16); gains, outputs and gradients have type dt
 // row_skip (may be null): rows marked there are left alone (see GemmArgs::row_skip)
@@ -154,16 +165,15 @@ void launch_rmsnorm_fwd(int dt, int tx, const void* x, i64 ldx, const void* g, v
 void launch_rmsnorm_bwd(int dt, int tx, const void* dy, i64 ldd, const void* x, i64 ldx, const void* g,
                         const void* base, i64 ldb, void* dx, i64 ldo, float* rinv,
                         int rows, int h, float eps, hipStream_t s);
-// out[j] = sum_t a[t*lda+j] * (b ? b[t*ldb+j] : 1) * (sc ? sc[t] : 1); ta/tb/tout element types.
-// partial must hold >= colsum_partial_floats(rows, cols) floats.
-#define COLSUM_BATCH 3
-size_t colsum_partial_floats(int rows, int cols);
-// n <= COLSUM_BATCH column sums of one shape and type in one launch pair (b, ldb, sc may be null arrays)
-void launch_colsum_batch(int n, int ta, const void* const* a, const i64* lda, int tb, const void* const* b, const i64* ldb,
-                         const float* const* sc, int tout, void* const* out, float* partial, int rows, int cols,
-                         hipStream_t s);
-void launch_colsum(int ta, const void* a, i64 lda, int tb, const void* b, i64 ldb, const float* sc,
-                   int tout, void* out, float* partial, int rows, int cols, hipStream_t s);
+// Column sums out[j] = sum_t a[t*lda+j] * (b ? b[t*ldb+j] : 1) * (sc ? sc[t] : 1), up to COLSUM_MAX of them, of any
+// shapes, in one launch.  partial: colsum_partial_floats(sum of the cols) floats; ticket: colsum_tickets(..) ints, zero
+// before the first launch (every launch leaves them zero).
+#define COLSUM_MAX 8
+struct Colsum { const void *a, *b; const float* sc; void* out; i64 lda, ldb; int rows, cols, a_f32, b_f32, out_f32, tile0; };
+struct ColsumBatch { int n = 0; Colsum p[COLSUM_MAX]; };
+size_t colsum_partial_floats(size_t cols_sum);
+size_t colsum_tickets(size_t cols_sum);
+void launch_colsum_batch(ColsumBatch& q, float* partial, int* ticket, hipStream_t s);
 // rotates buf (and, in the same launch, buf2 of the same shape when it is not null) in place
 void launch_rope(int dt, void* buf, const float* cs_table, int T, int S, int H, int dh, float sign,
                  hipStream_t s, void* buf2 = nullptr, const unsigned char* row_skip = nullptr);

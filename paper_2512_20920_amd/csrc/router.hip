@@ -20,13 +20,13 @@
 // Outputs: probs[T,E] (softmax over all experts), idx/wts[T,k] (slots by descending logit, equal logits -> lower expert
 // index), gamma[T] = sigmoid(gate logit), and blk_cnt[block][E], how often the block's tokens chose each expert.
 //
-// One workgroup of 16 waves per block of 32 tokens.  The routing chain (this kernel, then the permutation) is latency:
-// a few MFLOP per workgroup.  The 32 x E1 logits are cut over the waves by column tile and by slices of h (operands
-// straight from memory, the squares for 1/rms are summed from the same registers), added in slice order through LDS,
-// and a wave then finishes two tokens with one lane per expert.  Logits, softmax and selection as one kernel instead of
-// two, with the logits kept on the chip: 14 + 15 us -> 9 us at T = 128, 19 + 16 -> 11 us at T = 2048.
+// One workgroup of 16 waves per block of 16 tokens.  The routing chain (this kernel, then the permutation) is latency:
+// 2 MFLOP and the whole of wrp per workgroup.  The 16 x E1 logits are cut over the waves by column tile and by slices of
+// h (operands straight from memory, the squares for 1/rms are summed from the same registers), added in slice order
+// through LDS, and then a wave finishes one token with one lane per expert (reductions by data-parallel moves, the
+// arg-max as maximum and ballot).  (32 tokens per workgroup: half the CUs, twice the matrix-core time on each.)
 // ---------------------------------------------------------------------------------
-#define ROUTER_TOKENS 32
+#define ROUTER_TOKENS 16
 #define ROUTER_WAVES 16
 __host__ __device__ inline int router_slices(int tiles) { return tiles >= ROUTER_WAVES ? 1 : ROUTER_WAVES / tiles; }
 
@@ -36,63 +36,54 @@ __global__ void __launch_bounds__(ROUTER_WAVES * 64) router_k(
     float* __restrict__ probs, int* __restrict__ idx, float* __restrict__ wts, float* __restrict__ gamma,
     int* __restrict__ blk_cnt, int Tn, int h, int E, int k, int has_gate, int norm_topk, float eps) {
   extern __shared__ __attribute__((aligned(16))) float sm[];
-  const int E1 = E + (has_gate ? 1 : 0), tiles = (E1 + 31) >> 5, ns = router_slices(tiles), zc = tiles * 32;
-  float* zpart = sm;                              // [ns][32][zc]
-  float* sspart = sm + ns * 32 * zc;              // [ns][32]
-  int* cnt = (int*)(sspart + ns * 32);            // [E]
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, gh = lane >> 5;
+  const int E1 = E + (has_gate ? 1 : 0), tiles = (E1 + 15) >> 4, ns = router_slices(tiles), zc = tiles * 16;
+  float* zpart = sm;                              // [ns][16][zc]: slice partials; slice 0 then takes the sums
+  float* sspart = sm + ns * 16 * zc;              // [ns][16]
+  int* cnt = (int*)(sspart + ns * 16);            // [E]
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, gh = lane >> 4;
   const int t0 = blockIdx.x * ROUTER_TOKENS;
   for (int e = threadIdx.x; e < E; e += blockDim.x) cnt[e] = 0;
-  const int nchunk = (h + GKC - 1) / GKC;
+  const int nchunk = (h + GKC(16) - 1) / GKC(16);
   for (int item = wv; item < tiles * ns; item += ROUTER_WAVES) {
     const int sl = item / tiles, tt = item - sl * tiles;
-    f32x16 acc;
-#pragma unroll
-    for (int e = 0; e < 16; e++) acc[e] = 0.f;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     float ss = 0.f;
-    Operand<T, false> oa;
-    Operand<float, false> ob;
-    oa.init(y1, ld, t0, Tn, lane);
-    ob.init(wrp, h, tt * 32, E1, lane);
-    float va[2][16], vb[2][16];
-    auto mul = [&](float (&a)[16], float (&b)[16]) {
+    Operand<T, false, 16> oa[1];
+    Operand<float, false, 16> ob[1];
+    oa[0].init(y1, ld, t0, Tn, lane);
+    ob[0].init(wrp, h, tt * 16, E1, lane);
+    k_loop<16, 1, 1>(oa, ob, 0, h, sl, ns, nchunk, gh, [&](float (&a)[1][16], float (&b)[1][16]) {
 #pragma unroll
-      for (int s = 0; s < 16; s++) { acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[s], b[s], acc, 0, 0, 0); ss += a[s] * a[s]; }
-    };
-    int c = sl;
-    if (c < nchunk) { oa.load(c * GKC, h, gh, va[0]); ob.load(c * GKC, h, gh, vb[0]); }
-    for (; c + ns < nchunk; c += 2 * ns) {
-      oa.load((c + ns) * GKC, h, gh, va[1]); ob.load((c + ns) * GKC, h, gh, vb[1]);
-      mul(va[0], vb[0]);
-      if (c + 2 * ns < nchunk) { oa.load((c + 2 * ns) * GKC, h, gh, va[0]); ob.load((c + 2 * ns) * GKC, h, gh, vb[0]); }
-      mul(va[1], vb[1]);
-    }
-    if (c < nchunk) mul(va[0], vb[0]);
+      for (int s = 0; s < 16; s++) { acc = mfma_f32(a[0][s], b[0][s], acc); ss += a[0][s] * a[0][s]; }
+    });
 #pragma unroll
-    for (int e = 0; e < 16; e++)
-      zpart[(sl * 32 + (e >> 2) * 8 + gh * 4 + (e & 3)) * zc + tt * 32 + (lane & 31)] = acc[e];
+    for (int e = 0; e < 4; e++) zpart[(sl * 16 + gh * 4 + e) * zc + tt * 16 + (lane & 15)] = acc[e];
+    ss += __shfl_xor(ss, 16, WAVE);
     ss += __shfl_xor(ss, 32, WAVE);
-    if (tt == 0 && lane < 32) sspart[sl * 32 + lane] = ss;
+    if (tt == 0 && lane < 16) sspart[sl * 16 + lane] = ss;
   }
   __syncthreads();
-  for (int q = 0; q < ROUTER_TOKENS / ROUTER_WAVES; q++) {
-    const int tok = wv * (ROUTER_TOKENS / ROUTER_WAVES) + q, t = t0 + tok;
-    if (t >= Tn) break;
+  for (int e = threadIdx.x; e < 16 * zc; e += ROUTER_WAVES * 64) {       // the slices, added in order
+    float v = 0.f;
+#pragma unroll 4
+    for (int s = 0; s < ns; s++) v += zpart[s * 16 * zc + e];
+    zpart[e] = v;
+  }
+  __syncthreads();
+  const int t = t0 + wv;                  // one token per wave
+  if (t < Tn) {
     float ss = 0.f;
-    for (int s = 0; s < ns; s++) ss += sspart[s * 32 + tok];
+#pragma unroll 4
+    for (int s = 0; s < ns; s++) ss += sspart[s * 16 + wv];
     const float r = 1.0f / sqrtf(ss / (float)h + eps);
-    auto logit = [&](int e) {
-      float raw = 0.f;
-      for (int s = 0; s < ns; s++) raw += zpart[(s * 32 + tok) * zc + e];
-      return raw * r;
-    };
+    const float* zt = zpart + wv * zc;
     float z[4];                           // the logits of experts lane + 64 j (E <= 256)
     float mx = -INFINITY;
 #pragma unroll
     for (int j = 0; j < 4; j++) {
       const int e = lane + 64 * j;
       z[j] = -INFINITY;
-      if (e < E) { z[j] = logit(e) + (b_router ? b_router[e] : 0.f); mx = fmaxf(mx, z[j]); }
+      if (e < E) { z[j] = zt[e] * r + (b_router ? b_router[e] : 0.f); mx = fmaxf(mx, z[j]); }
     }
     // softmax over the E routed logits
     mx = wave_max(mx);
@@ -112,23 +103,23 @@ __global__ void __launch_bounds__(ROUTER_WAVES * 64) router_k(
     unsigned taken = 0;                   // bit j: expert lane + 64 j has been chosen
     for (int s = 0; s < k; s++) {
       float bv = -INFINITY;
-      int bi = 0x7fffffff;
 #pragma unroll
       for (int j = 0; j < 4; j++) {
-        const int e = lane + 64 * j;
-        if (e >= E || ((taken >> j) & 1u)) continue;
-        const float v = (z[j] == z[j]) ? z[j] : -INFINITY;
-        if (v > bv || (v == bv && e < bi)) { bv = v; bi = e; }
+        const bool open = lane + 64 * j < E && !((taken >> j) & 1u);
+        if (open && z[j] > bv) bv = z[j];             // (false for a NaN)
       }
+      bv = wave_max(bv);
+      int bi = -1;                                    // lowest index among the experts that hold the maximum
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        const float ov = __shfl_xor(bv, o, WAVE);
-        const int oi = __shfl_xor(bi, o, WAVE);
-        if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+      for (int j = 0; j < 4; j++) {
+        const bool open = lane + 64 * j < E && !((taken >> j) & 1u);
+        const float v = (z[j] == z[j]) ? z[j] : -INFINITY;
+        const unsigned long long m = __ballot(open && v == bv);
+        if (bi < 0 && m) bi = 64 * j + __ffsll(m) - 1;
       }
-      // the comparator is a total order (no NaN takes part), so every lane now holds the same (bv, bi); with
-      // top_k <= E at least one expert was left, so bi < E (the clamp only guards the stores below)
-      bi = min(bi, E - 1);
+      // (with top_k <= E at least one expert was left and the comparison is a total order, so one was found; the clamp
+      // only guards the stores below)
+      bi = min(max(bi, 0), E - 1);
       if ((bi & 63) == lane) taken |= 1u << (bi >> 6);
       const float pb = __expf(bv - mx) * inv;
       wsum += pb;
@@ -136,10 +127,7 @@ __global__ void __launch_bounds__(ROUTER_WAVES * 64) router_k(
       if (lane == 0) { idx[(i64)t * k + s] = bi; atomicAdd(&cnt[bi], 1); }
     }
     if (lane < k) wts[(i64)t * k + lane] = norm_topk ? myw / wsum : myw;
-    if (has_gate) {
-      const float zg = logit(E);
-      if (lane == 0) gamma[t] = sigmoid_f(zg);
-    }
+    if (has_gate && lane == 0) gamma[t] = sigmoid_f(zt[E] * r);
   }
   __syncthreads();
   for (int e = threadIdx.x; e < E; e += blockDim.x) blk_cnt[(i64)blockIdx.x * E + e] = cnt[e];
@@ -149,14 +137,8 @@ void launch_router(int dt, const void* y1, i64 ld, const float* wrp, const float
                    float* wts, float* gamma, int* blk_cnt, int Tn, int h, int E, int k, int has_gate, int norm_topk,
                    float eps, hipStream_t s) {
   if (Tn <= 0) return;
-  const int tiles = (E + (has_gate ? 1 : 0) + 31) / 32, ns = router_slices(tiles);
-  const size_t smem = ((size_t)ns * 32 * (tiles * 32 + 1) + E) * 4;         // at most 70 KB
-  static std::atomic<unsigned long long> attr_mask{0};
-  if (attr_needed(attr_mask)) {
-    (void)hipFuncSetAttribute((const void*)router_k<float>, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
-    (void)hipFuncSetAttribute((const void*)router_k<bf16>, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
-    attr_done(attr_mask);
-  }
+  const int tiles = (E + (has_gate ? 1 : 0) + 15) / 16, ns = router_slices(tiles);
+  const size_t smem = ((size_t)ns * 16 * (tiles * 16 + 1) + E) * 4;         // at most 20 KB
   DISPATCH_DT(dt, hipLaunchKernelGGL(router_k<T>, dim3(cdiv(Tn, ROUTER_TOKENS)), dim3(ROUTER_WAVES * 64), smem, s,
                                      (const T*)y1, ld, wrp, b_router, probs, idx, wts, gamma, blk_cnt, Tn, h, E, k,
                                      has_gate, norm_topk, eps));
@@ -165,7 +147,7 @@ size_t router_blocks(size_t Tn) { return (Tn + ROUTER_TOKENS - 1) / ROUTER_TOKEN
 
 // ---------------------------------------------------------------------------------
 // Permutation: a stable grouping of the T*k (token, slot) entries by expert.  The router kernel has counted, per block
-// of 32 tokens, the entries of every expert, so a block's first row inside every expert is a column sum of that table
+// of 16 tokens, the entries of every expert, so a block's first row inside every expert is a column sum of that table
 // and blocks need nothing of each other: one wave per block, 16 per workgroup, every workgroup adding the columns for
 // itself (one workgroup that counted and placed all entries took 13.5 us at T = 2048 and 52 us at T = 8192; now 7 and
 // 8 us).  Inside its block a wave hands out rows in entry order, which keeps (token, slot) order inside an expert.

@@ -16,7 +16,7 @@ def _dev(a):
 
 @pytest.mark.parametrize("a_trans,b_trans", [(0, 0), (0, 1), (1, 1), (1, 0)])
 # one element, tails in every dimension around 32 and the 32-wide chunks of k, rows that are not 16-byte aligned
-# (odd leading dimensions), no k at all, and enough 64x64 tiles for the larger tile shape
+# (odd leading dimensions), no k at all, and enough tiles for the larger tile shape
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (33, 31, 65), (64, 96, 64), (61, 130, 2048), (7, 200, 31), (40, 40, 0),
                                    (1030, 1040, 70), (1024, 1056, 33)])
 def test_f32_gemm(M, N, K, a_trans, b_trans):
