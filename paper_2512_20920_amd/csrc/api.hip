@@ -303,21 +303,28 @@ int run_gemm(revffn_ctx* c, GemmArgs g, int ta, int tb, int tc, hipStream_t s) {
   auto swiglu_after = [&]() { if (act_half && !g.act_half) launch_swiglu_fwd(c->dt, g.C, act_out, act_rows, act_half, s); };
   if (c->dt == 1 && c->mode == 0 && ta == 1 && tb == 1) {
     if (g.group_mode == 1) {
-      // Expert tiles stream weights that nothing else reads, so what counts is weight bytes in flight per CU: a
-      // 128x256 tile (3 stages) keeps 64 KiB of them in flight, 256x128 and 128x128 half of that.  Measured: 128x256
-      // is 1.5-3 % of a step faster on every workload and both layouts, except the weights-as-[k,n] layout (data
-      // gradients) while one 256-row tile holds a typical expert (96 < mean rows <= 192), where 256x128 is 3 % of
-      // that kernel faster.  Shapes: 1 = 128x128, 2 = 256x128, 3 = 128x256 (REVFFN_EXPERT_NT / REVFFN_EXPERT_NN force one);
-      // where list b was built 160 rows high (expert_rows_b), shape 3 is the 160x256 tile.
+      // Expert tiles stream weights that nothing else reads, so with few rows per expert what counts is weight bytes in
+      // flight per CU: a 128x256 tile (3 stages) keeps 64 KiB of them in flight, the other shapes half of that.  With
+      // many rows the matrix pipe counts: 256x256 in phases.  Measured, us per launch (mean rows per expert):
+      //   forward gate/up      68: 161 (128x256), 183 (256x256)   137: 191 (160x256, see expert_rows_b), 210   273: 276, 291
+      //                        546: 495, 453      512 of width 14336: 1133, 1004
+      //   data gradient dXg    68: 185, 182    137: 218 (256x128), 195    273: 268, 240    546: 454, 417
+      //   data gradient dHh    137: 119, 127 (1408 columns: the sixth column of tiles is half empty)    546: 254, 247
+      // Shapes: 1 = 128x128, 2 = 256x128, 3 = 128x256 (160x256 where list b was built that high), 4 = 256x256
+      // (REVFFN_EXPERT_NT / REVFFN_EXPERT_NN force one).
       const i64 rows = c->lastT_rows, E = c->cfg.n_experts;
       int shape = g.b_trans ? c->expert_nn : c->expert_nt;
       if (c->expert_tile) shape = c->expert_tile == 256 ? 2 : 1;
-      if (!shape) shape = (g.b_trans && rows > 96 * E && rows <= 192 * E) ? 2 : 3;
-      bool tall = shape == 2;
-      g.tile_bn = shape == 3 ? 256 : 128;
+      if (!shape) {
+        if (!g.b_trans) shape = rows > 384 * E ? 4 : 3;
+        else if (rows > 192 * E || (rows > 96 * E && g.N % 256 == 0)) shape = 4;
+        else shape = rows > 96 * E ? 2 : 3;
+      }
+      bool tall = shape == 2 || shape == 4;
+      g.tile_bn = shape >= 3 ? 256 : 128;
       const bool mid = c->bm_b == BM_B_MID;              // list b holds 160-row tiles: for the 160x256 forward kernel only
       if (mid && !tall) { if (g.b_trans) tall = true; else g.tile_bn = 256; }
-      if (tall && g.b_trans) g.tile_bn = 128;
+      if (tall && g.b_trans && shape != 4) g.tile_bn = 128;
       if (tall) {
         g.tile_group = c->tg_c; g.tile_m0 = c->tm_c; g.max_tiles = c->max_tiles_c; g.tile_bm = BM_C; g.tile_count = c->tile_cnt + 2;
         if (c->max_tiles_c < 32768) g.tile_first = c->tf_c;      // (the packed entry holds 15 + 16 bits)
@@ -1168,8 +1175,8 @@ int revffn_create(revffn_ctx** out, const revffn_config* cfg, int32_t max_B, int
   c->use_streams = getenv("REVFFN_NO_STREAMS") == nullptr;
   { const char* e = getenv("REVFFN_EXPERT_TILE"); if (e && (atoi(e) == 256 || atoi(e) == 128)) c->expert_tile = atoi(e); }
   { const char* e = getenv("REVFFN_NO_FUSED_SWIGLU"); c->no_fused_swiglu = e && atoi(e) != 0; }
-  { const char* e = getenv("REVFFN_EXPERT_NT"); if (e && atoi(e) >= 1 && atoi(e) <= 3) c->expert_nt = atoi(e); }
-  { const char* e = getenv("REVFFN_EXPERT_NN"); if (e && atoi(e) >= 1 && atoi(e) <= 3) c->expert_nn = atoi(e); }
+  { const char* e = getenv("REVFFN_EXPERT_NT"); if (e && atoi(e) >= 1 && atoi(e) <= 4) c->expert_nt = atoi(e); }
+  { const char* e = getenv("REVFFN_EXPERT_NN"); if (e && atoi(e) >= 1 && atoi(e) <= 4) c->expert_nn = atoi(e); }
   c->sync_ev = new (std::nothrow) std::vector<hipEvent_t>();
   bool ok = c->sync_ev != nullptr;
   for (int i = 0; ok && i < 4; i++) ok = hipStreamCreateWithFlags(&c->side[i], hipStreamNonBlocking) == hipSuccess;

@@ -38,11 +38,19 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 #define BUF_RECORDS 0x80000000u
 #define OOB 0x80000000u
 #define BK 64
+#define PHASED 0          // (as the number of LDS stages: the 256x256 tile in phases)
 
 // one wave-load: 64 lanes x 16 bytes from desc + voff (per lane) to LDS at lds_addr + 16 * lane
 __device__ __forceinline__ void load_lds_b128(u32x4 desc, unsigned lds_addr, unsigned voff) {
   asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                :: "s"(lds_addr), "v"(voff), "s"(desc) : "memory", "m0");
+}
+// the same with a wave-uniform byte offset added
+__device__ __forceinline__ void load_lds_b128_s(u32x4 desc, unsigned lds_addr, unsigned voff, unsigned soff) {
+  soff = __builtin_amdgcn_readfirstlane(soff);
+  asm("" : "+s"(soff));                             // (a literal is no offset operand)
+  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :: "s"(lds_addr), "v"(voff), "s"(desc), "s"(soff) : "memory", "m0");
 }
 template <int N> __device__ __forceinline__ void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
 
@@ -133,6 +141,213 @@ __device__ __forceinline__ void pair_rows(bool odd, float x0, float x1, float* l
   const float recv = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, send), 0xB1, 0xf, 0xf, false));
   *left = odd ? recv : x0;
   *right = odd ? x1 : recv;
+}
+
+// Epilogue of one output tile.  rb, cb: first row (column) of the wave's 32-row (32-column) blocks inside the tile;
+// act_col: with the SwiGLU epilogue, the wave's first gate column inside the tile's BN / 2.
+template <int BM, int BN, bool AT, bool BT, class TC, int TE, int TN>
+__device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, TC* C, const void* bias_ptr, int bx, int m0, int m_end,
+                                              const int (&rb)[TE], const int (&cb)[TN], int act_col, f32x16 (&acc)[TE][TN]) {
+  const int n0 = bx * BN, lane = threadIdx.x & 63;
+  // ---- epilogue: lane holds column n = lane & 31 and rows (e>>2)*8 + (lane>>5)*4 + (e&3)
+  if (g.act_half) {
+    // gate/up GEMM with the SwiGLU epilogue: this wave's first 32-column block is gate columns, its second the up
+    // columns of the same indices.  Both go to C (the backward pass needs them), and silu(gate) * up, from the
+    // rounded values, to act_out.
+    if constexpr (!AT && !BT && TN == 2) {
+      TC* H = (TC*)g.act_out;
+      const int half = g.act_half;
+      const int col = bx * (BN / 2) + act_col + (lane & 31);
+      if constexpr (sizeof(TC) == 2) {
+        // pairs of lanes store two columns of one row each (see the plain store below); rows past the end are masked
+        // per lane after the swap, columns per pair (the width is even)
+        if (!(g.ldc & 1) && !(g.ldact & 1) && !(half & 1) && !((uintptr_t)C & 3) && !((uintptr_t)H & 3) && !g.no_packed_stores) {
+          const bool odd = lane & 1;
+          const int colp = col - (odd ? 1 : 0);
+          typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_v;
+          if (colp < half) {
+#pragma unroll
+            for (int i = 0; i < TE; i++)
+#pragma unroll
+              for (int e = 0; e < 16; e += 2) {
+                const int m = m0 + rb[i] + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3) + (odd ? 1 : 0);
+                float gq[2], uq[2], hq[2];
+#pragma unroll
+                for (int p = 0; p < 2; p++) {
+                  const TC gb = (TC)acc[i][0][e + p], ub = (TC)acc[i][1][e + p];
+                  gq[p] = (float)gb; uq[p] = (float)ub;
+                  hq[p] = (float)(TC)(gq[p] * sigmoid_f(gq[p]) * uq[p]);
+                }
+                float l, r;
+                bf16x2_v wg, wu, wh;
+                pair_rows(odd, gq[0], gq[1], &l, &r); wg[0] = (__bf16)l; wg[1] = (__bf16)r;
+                pair_rows(odd, uq[0], uq[1], &l, &r); wu[0] = (__bf16)l; wu[1] = (__bf16)r;
+                pair_rows(odd, hq[0], hq[1], &l, &r); wh[0] = (__bf16)l; wh[1] = (__bf16)r;
+                if (m < m_end) {
+                  *(bf16x2_v*)(C + (i64)m * g.ldc + colp) = wg;
+                  *(bf16x2_v*)(C + (i64)m * g.ldc + half + colp) = wu;
+                  *(bf16x2_v*)(H + (i64)m * g.ldact + colp) = wh;
+                }
+              }
+          }
+          return;
+        }
+      }
+      if (col < half) {
+#pragma unroll
+        for (int i = 0; i < TE; i++)
+#pragma unroll
+          for (int e = 0; e < 16; e++) {
+            const int m = m0 + rb[i] + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
+            if (m < m_end) {
+              const TC gb = (TC)acc[i][0][e], ub = (TC)acc[i][1][e];
+              const float gv = (float)gb;
+              C[(i64)m * g.ldc + col] = gb;
+              C[(i64)m * g.ldc + half + col] = ub;
+              H[(i64)m * g.ldact + col] = (TC)(gv * sigmoid_f(gv) * (float)ub);
+            }
+          }
+      }
+    }
+    return;
+  }
+  const bf16* bias = (const bf16*)bias_ptr;
+  const bf16* resid = (const bf16*)g.resid;
+  if (!bias && !g.tap && !resid) {
+    // plain store (all weight gradients, most projections): no per-element epilogue work
+    // the column blocks of one row are stored back to back, so that the 64-byte pieces of a line reach L2 together.
+    // (Staging the tile through LDS to store whole 128-byte lines, 16 bytes per lane, measured no faster: these
+    // stores are not what bounds the weight-gradient kernels.)
+    const bool full = (m0 + BM <= m_end) && (n0 + BN <= g.N);
+    if constexpr (sizeof(TC) == 2) {
+      // Whole tiles of 2-byte results: neighbouring lanes hold neighbouring columns of the same rows, so a pair of
+      // lanes swaps one value per two rows (the even lane gives its value of the odd row and gets the neighbour's
+      // value of the even row) and each lane stores 4 bytes, two columns of one row: half as many store
+      // instructions, and the stores of a tile are bound by their number (per-expert weight gradients 10 % faster,
+      // 1-2 % of a step).  Going on to a 4x4 transpose inside a quad and 8-byte stores is slower than no packing at
+      // all: one instruction then touches eight rows.
+      if (full && !(g.ldc & 1) && !((uintptr_t)C & 3) && !g.no_packed_stores) {
+        const bool odd = lane & 1;
+        typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_v;
+#pragma unroll
+        for (int i = 0; i < TE; i++) {
+          // even lane: row of element e, its own column; odd lane: the row below, the column to its left
+          TC* cp = C + (i64)(m0 + rb[i] + (lane >> 5) * 4 + (odd ? 1 : 0)) * g.ldc + n0 + (lane & 31) - (odd ? 1 : 0);
+#pragma unroll
+          for (int e = 0; e < 16; e += 2) {
+            const int dm = (e >> 2) * 8 + (e & 3);
+#pragma unroll
+            for (int j = 0; j < TN; j++) {
+              float l, r;
+              pair_rows(odd, acc[i][j][e], acc[i][j][e + 1], &l, &r);
+              bf16x2_v w;
+              w[0] = (__bf16)l; w[1] = (__bf16)r;
+              *(bf16x2_v*)(cp + (i64)dm * g.ldc + cb[j]) = w;
+            }
+          }
+        }
+        return;
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < TE; i++) {
+      TC* cp = C + (i64)(m0 + rb[i] + (lane >> 5) * 4) * g.ldc + n0 + (lane & 31);
+#pragma unroll
+      for (int e = 0; e < 16; e++) {
+        const int dm = (e >> 2) * 8 + (e & 3);
+        const bool row_ok = full || (m0 + rb[i] + (lane >> 5) * 4 + dm < m_end);
+#pragma unroll
+        for (int j = 0; j < TN; j++)
+          if (row_ok && (full || n0 + cb[j] + (lane & 31) < g.N)) cp[(i64)dm * g.ldc + cb[j]] = (TC)acc[i][j][e];
+      }
+    }
+    return;
+  }
+  // Two phases per 32-column block: every load (bias, residual) and all arithmetic on loaded values
+  // first, then nothing but stores.  On this ISA one counter tracks loads and stores, and where a store may or may
+  // not have been issued (rows and columns past the problem's edge are masked per lane) the compiler can only wait
+  // for "everything": a use of a loaded value between two stores then waits for the earlier store to complete, and
+  // the 16 * TE * TN stores of a lane run one after the other (the coupling GEMMs with a residual operand took
+  // twice as long as the same GEMM with a plain store).  So loads are never masked (indices past the edge are
+  // clamped to the last valid row / column instead), the finished values are pinned in registers before the first
+  // store (the empty asm keeps the compiler from sinking the arithmetic into the masked store blocks), and the
+  // store phase has nothing to wait for.  The residual operand may be the output itself (in-place coupling update):
+  // it either is C, element for element, or does not overlap it, and each lane reads its elements before it writes.
+  constexpr int GI = 1;                              // 32-row blocks whose loads are issued together (more would spill at TE = 2)
+  const bool full = (m0 + BM <= m_end) && (n0 + BN <= g.N);
+  const int m_last = m_end - 1, n_last = g.N - 1;
+  auto row_of = [&](int i, int e) { return m0 + rb[i] + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3); };
+#pragma unroll
+  for (int j = 0; j < TN; j++) {
+    const int n = n0 + cb[j] + (lane & 31);
+    const bool n_ok = full || n < g.N;
+    const int nn = min(n, n_last);
+    const float bv = bias ? (float)bias[nn] : 0.f;
+#pragma unroll
+    for (int i0 = 0; i0 < TE; i0 += GI) {
+      // ---- phase 1: loads and arithmetic
+      float rv[GI][16];
+      if (resid) {
+        if (g.resid_f32) {
+#pragma unroll
+          for (int ii = 0; ii < GI; ii++)
+#pragma unroll
+            for (int e = 0; e < 16; e++)
+              rv[ii][e] = ((const float*)g.resid)[(i64)min(row_of(i0 + ii, e), m_last) * g.ldr + nn];
+        } else {
+#pragma unroll
+          for (int ii = 0; ii < GI; ii++)
+#pragma unroll
+            for (int e = 0; e < 16; e++) rv[ii][e] = (float)resid[(i64)min(row_of(i0 + ii, e), m_last) * g.ldr + nn];
+        }
+      } else {
+#pragma unroll
+        for (int ii = 0; ii < GI; ii++)
+#pragma unroll
+          for (int e = 0; e < 16; e++) rv[ii][e] = 0.f;
+      }
+#pragma unroll
+      for (int ii = 0; ii < GI; ii++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) {
+          float v = acc[i0 + ii][j][e] + bv;                   // the value the tap records
+          float o = resid ? rv[ii][e] + g.resid_sign * v : v;
+          asm volatile("" : "+v"(v), "+v"(o));
+          acc[i0 + ii][j][e] = v;
+          rv[ii][e] = o;
+        }
+      // ---- phase 2: stores
+      if constexpr (sizeof(TC) == 2) {
+        // two columns of one row per lane (see the plain store above); the swap runs on every lane, the masks after it
+        if (!g.tap && !(g.ldc & 1) && !(g.N & 1) && !((uintptr_t)C & 3) && !g.no_packed_stores) {
+          const bool odd = lane & 1;
+          typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_v;
+#pragma unroll
+          for (int ii = 0; ii < GI; ii++)
+#pragma unroll
+            for (int e = 0; e < 16; e += 2) {
+              float l, r;
+              pair_rows(odd, rv[ii][e], rv[ii][e + 1], &l, &r);
+              bf16x2_v w;
+              w[0] = (__bf16)l; w[1] = (__bf16)r;
+              const int m = row_of(i0 + ii, e) + (odd ? 1 : 0);
+              if (n_ok && (full || m < m_end)) *(bf16x2_v*)(C + (i64)m * g.ldc + n - (odd ? 1 : 0)) = w;
+            }
+          continue;
+        }
+      }
+#pragma unroll
+      for (int ii = 0; ii < GI; ii++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) {
+          const int m = row_of(i0 + ii, e);
+          if (n_ok && (full || m < m_end)) {
+            if (g.tap) g.tap[(i64)m * g.ldtap + n] = acc[i0 + ii][j][e];
+            C[(i64)m * g.ldc + n] = (TC)rv[ii][e];
+          }
+        }
+    }
+  }
 }
 
 // One output tile; TE = 32-row blocks per wave.
@@ -238,205 +453,147 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const bf16* A, cons
   }
   wait_vmcnt<0>();                                   // the zero-filled loads past the last tile
 
-  // ---- epilogue: lane holds column n = lane & 31 and rows (e>>2)*8 + (lane>>5)*4 + (e&3)
-  if (g.act_half) {
-    // gate/up GEMM with the SwiGLU epilogue: this wave's first 32-column block is gate columns, its second the up
-    // columns of the same indices.  Both go to C (the backward pass needs them), and silu(gate) * up, from the
-    // rounded values, to act_out.
-    if constexpr (!AT && !BT && TN == 2) {
-      TC* H = (TC*)g.act_out;
-      const int half = g.act_half;
-      const int col = bx * (BN / 2) + (wn >> 6) * 32 + (lane & 31);
-      if constexpr (sizeof(TC) == 2) {
-        // pairs of lanes store two columns of one row each (see the plain store below); rows past the end are masked
-        // per lane after the swap, columns per pair (the width is even)
-        if (!(g.ldc & 1) && !(g.ldact & 1) && !(half & 1) && !((uintptr_t)C & 3) && !((uintptr_t)H & 3) && !g.no_packed_stores) {
-          const bool odd = lane & 1;
-          const int colp = col - (odd ? 1 : 0);
-          typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_v;
-          if (colp < half) {
+  int rb[TE], cb[TN];
 #pragma unroll
-            for (int i = 0; i < TE; i++)
+  for (int i = 0; i < TE; i++) rb[i] = wm + i * 32;
 #pragma unroll
-              for (int e = 0; e < 16; e += 2) {
-                const int m = m0 + wm + i * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3) + (odd ? 1 : 0);
-                float gq[2], uq[2], hq[2];
+  for (int j = 0; j < TN; j++) cb[j] = wn + j * 32;
+  gemm_epilogue<BM, BN, AT, BT, TC, TE, TN>(g, C, bias_ptr, bx, m0, m_end, rb, cb, (wn >> 6) * 32, acc);
+}
+
+// ---- 256x256 tile in phases ------------------------------------------------------------------------------------------
+// The plain loop above waits once per k-tile for everything it has asked for; with 64 KiB per stage only two stages fit,
+// so the last loads of a k-tile are issued right before the wait for them and their latency (1300-2200 clocks) is in the
+// open.  Here a k-tile is two phases, the upper and the lower half of the tile's rows, and LDS holds two k-tiles as half
+// tiles of 16 KiB (A0 A1: 128 rows each, B0 B1: 128 columns each):
+//   phase 0: read A0 B0 B1, multiply A0 x (B0 B1), ask for A1 of k-tile t + 1
+//   phase 1: read A1,       multiply A1 x (B0 B1), ask for A0 B0 B1 of k-tile t + 2
+// (8 waves as 2 x 4, a wave owns 64 rows x 2 x 32 columns of each half).  Every load has three phases to arrive and a wait
+// never asks for the youngest four half tiles.
+// The two waves of a SIMD run half a phase apart: while one multiplies (16 MFMAs), the other reads its next fragments and
+// issues loads; a barrier at each half phase keeps them so.  Measured, 8192 x 2048 with k = 2048 / 4096: 81 -> 61 / 153 ->
+// 108 us, i.e. 1.47 us per k-tile (1.46 PFLOP/s) once running; with all-zero operands 0.99 us (2.2 PFLOP/s, 86 % of the
+// pipe), so what is left is the power limit, and 13 us of launch, first loads and 33 MB of results.
+// (Four phases of 8 MFMAs: 5 % slower, the barriers; all eight waves in step: 25 % slower; one wave per SIMD with 128 x 128
+// outputs, a third less LDS traffic: 6-15 % slower, its loads hold up its own MFMAs.)
+//
+// What the barriers guarantee (segment n lies between barriers n and n+1; waves 0-3 read fragments of phase p in segment
+// 2p and multiply in 2p+1, waves 4-7 one segment later):
+//  * at the end of a read segment a wave waits for all but its youngest 8 loads, which covers the half tiles that the next
+//    phase reads; the first reader comes after a barrier that everybody passes after that wait;
+//  * a wave has its fragments in registers when its read segment ends (lgkmcnt(0)), so those of phase p have been read by
+//    everybody before segment 2p+2, and the first load into their half tile is issued in segment 2p+2 (phase p+1) or later.
+template <bool AT, bool BT, class TC>
+__device__ __forceinline__ void gemm_tile_phased(const GemmArgs& g, const bf16* A, const bf16* Bm, TC* C, const void* bias_ptr,
+                                                 int bx, int m0, int m_end, int k0, int k_end) {
+  constexpr unsigned HALF = 128 * BK * 2, STAGE = 4 * HALF;       // A0 A1 B0 B1
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  const int n0 = bx * 256;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = (wv >> 2) * 64, wn = (wv & 3) * 32;              // inside a half
+  const int krange = k_end - k0;
+  const int nk = (krange + BK - 1) / BK;
+  const u32x4 da = make_desc(A), db = make_desc(Bm);
+  const unsigned lda_b = (unsigned)g.lda * 2u, ldb_b = (unsigned)g.ldb * 2u;
+  const unsigned kstep_a = AT ? BK * lda_b : BK * 2u, kstep_b = BT ? BK * ldb_b : BK * 2u;
+  // wave-loads 2 wv and 2 wv + 1 of each half tile.  A row (column) past the end has an offset out of range for good; k's
+  // past the end can only be in the last k-tile.
+  unsigned base[4][2];
 #pragma unroll
-                for (int p = 0; p < 2; p++) {
-                  const TC gb = (TC)acc[i][0][e + p], ub = (TC)acc[i][1][e + p];
-                  gq[p] = (float)gb; uq[p] = (float)ub;
-                  hq[p] = (float)(TC)(gq[p] * sigmoid_f(gq[p]) * uq[p]);
-                }
-                float l, r;
-                bf16x2_v wg, wu, wh;
-                pair_rows(odd, gq[0], gq[1], &l, &r); wg[0] = (__bf16)l; wg[1] = (__bf16)r;
-                pair_rows(odd, uq[0], uq[1], &l, &r); wu[0] = (__bf16)l; wu[1] = (__bf16)r;
-                pair_rows(odd, hq[0], hq[1], &l, &r); wh[0] = (__bf16)l; wh[1] = (__bf16)r;
-                if (m < m_end) {
-                  *(bf16x2_v*)(C + (i64)m * g.ldc + colp) = wg;
-                  *(bf16x2_v*)(C + (i64)m * g.ldc + half + colp) = wu;
-                  *(bf16x2_v*)(H + (i64)m * g.ldact + colp) = wh;
-                }
-              }
-          }
-          return;
-        }
-      }
-      if (col < half) {
+  for (int h = 0; h < 2; h++)
 #pragma unroll
-        for (int i = 0; i < TE; i++)
+    for (int i = 0; i < 2; i++) {
+      const int pos = (wv * 2 + i) * 64 + lane;
+      int in;
+      chunk_source<AT, 128>(pos, m0 + h * 128, m_end, lda_b, k0, 1 << 30, g.a_gather, g.gather_div, &base[h][i], &in);
+      if (!in) base[h][i] = OOB;
+      // (SwiGLU epilogue: B0 holds gate columns, B1 the up columns of the same indices)
+      const int r0 = !BT && g.act_half ? h * g.act_half + bx * 128 : n0 + h * 128;
+      const int lim = !BT && g.act_half ? (h + 1) * g.act_half : g.N;
+      chunk_source<BT, 128>(pos, r0, lim, ldb_b, k0, 1 << 30, nullptr, 1, &base[2 + h][i], &in);
+      if (!in) base[2 + h][i] = OOB;
+    }
+  const unsigned lds0 = (unsigned)(unsigned long long)(__attribute__((address_space(3))) unsigned char*)smem;
+  const unsigned lw = __builtin_amdgcn_readfirstlane(lds0 + (unsigned)wv * 2048u);
+  const int kfull = krange / BK;                     // whole k-tiles
+  auto issue = [&](int kt, int hf) {                 // this wave's part of half tile hf (A0 A1 B0 B1) of k-tile kt
+    const unsigned soff = (unsigned)kt * (hf < 2 ? kstep_a : kstep_b), dst = lw + (unsigned)(kt & 1) * STAGE + hf * HALF;
+    if (kt < kfull) {
 #pragma unroll
-          for (int e = 0; e < 16; e++) {
-            const int m = m0 + wm + i * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
-            if (m < m_end) {
-              const TC gb = (TC)acc[i][0][e], ub = (TC)acc[i][1][e];
-              const float gv = (float)gb;
-              C[(i64)m * g.ldc + col] = gb;
-              C[(i64)m * g.ldc + half + col] = ub;
-              H[(i64)m * g.ldact + col] = (TC)(gv * sigmoid_f(gv) * (float)ub);
-            }
-          }
+      for (int i = 0; i < 2; i++) load_lds_b128_s(hf < 2 ? da : db, dst + i * 1024, base[hf][i], soff);
+    } else {
+      const int krem = krange - kt * BK;
+#pragma unroll
+      for (int i = 0; i < 2; i++) {
+        const int pos = (wv * 2 + i) * 64 + lane;
+        const bool in = (hf < 2 ? AT : BT) ? pos / 16 < krem : (((pos & 7) ^ ((pos >> 4) & 7)) << 3) < krem;
+        load_lds_b128_s(hf < 2 ? da : db, dst + i * 1024, in ? base[hf][i] : OOB, soff);
       }
     }
-    return;
-  }
-  const bf16* bias = (const bf16*)bias_ptr;
-  const bf16* resid = (const bf16*)g.resid;
-  if (!bias && !g.tap && !resid) {
-    // plain store (all weight gradients, most projections): no per-element epilogue work
-    // the column blocks of one row are stored back to back, so that the 64-byte pieces of a line reach L2 together.
-    // (Staging the tile through LDS to store whole 128-byte lines, 16 bytes per lane, measured no faster: these
-    // stores are not what bounds the weight-gradient kernels.)
-    const bool full = (m0 + BM <= m_end) && (n0 + BN <= g.N);
-    if constexpr (sizeof(TC) == 2) {
-      // Whole tiles of 2-byte results: neighbouring lanes hold neighbouring columns of the same rows, so a pair of
-      // lanes swaps one value per two rows (the even lane gives its value of the odd row and gets the neighbour's
-      // value of the even row) and each lane stores 4 bytes, two columns of one row: half as many store
-      // instructions, and the stores of a tile are bound by their number (per-expert weight gradients 10 % faster,
-      // 1-2 % of a step).  Going on to a 4x4 transpose inside a quad and 8-byte stores is slower than no packing at
-      // all: one instruction then touches eight rows.
-      if (full && !(g.ldc & 1) && !((uintptr_t)C & 3) && !g.no_packed_stores) {
-        const bool odd = lane & 1;
-        typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_v;
+  };
+  f32x16 acc[4][2];
 #pragma unroll
-        for (int i = 0; i < TE; i++) {
-          // even lane: row of element e, its own column; odd lane: the row below, the column to its left
-          TC* cp = C + (i64)(m0 + wm + i * 32 + (lane >> 5) * 4 + (odd ? 1 : 0)) * g.ldc + n0 + wn + (lane & 31) - (odd ? 1 : 0);
+  for (int i = 0; i < 4; i++)
 #pragma unroll
-          for (int e = 0; e < 16; e += 2) {
-            const int dm = (e >> 2) * 8 + (e & 3);
+    for (int j = 0; j < 2; j++)
 #pragma unroll
-            for (int j = 0; j < TN; j++) {
-              float l, r;
-              pair_rows(odd, acc[i][j][e], acc[i][j][e + 1], &l, &r);
-              bf16x2_v w;
-              w[0] = (__bf16)l; w[1] = (__bf16)r;
-              *(bf16x2_v*)(cp + (i64)dm * g.ldc + j * 32) = w;
-            }
-          }
-        }
-        return;
+      for (int e = 0; e < 16; e++) acc[i][j][e] = 0.f;
+  unsigned fba[2], fbb;
+#pragma unroll
+  for (int i = 0; i < 2; i++) fba[i] = frag_base<AT, 128>(wm + i * 32, lane);
+  fbb = frag_base<BT, 128>(wn, lane);
+
+  auto issue3 = [&](int kt) { issue(kt, 0); issue(kt, 2); issue(kt, 3); };
+  issue3(0); issue(0, 1); issue3(1);
+  wait_vmcnt<8>();                                   // A0 B0 B1 of k-tile 0
+  __builtin_amdgcn_s_barrier();
+  if (wv >= 4) __builtin_amdgcn_s_barrier();         // waves 4-7 half a phase behind
+  // a tile with no row in its lower half (the last one of an expert, often) does only its loads (out of range, to keep
+  // the counts) and barriers in phase 1
+  const bool lower = m_end - m0 > 128;
+  bf16x8 fa[2][4], fb[2][4];
+  for (int kt = 0; kt < nk; kt++) {
+    const unsigned char* st = smem + (unsigned)(kt & 1) * STAGE;
+#pragma unroll
+    for (int p = 0; p < 2; p++) {
+      // ---- read this phase's new fragments, ask for the half tiles whose places are free
+      if (p == 0 || lower)
+#pragma unroll
+      for (int kk = 0; kk < 4; kk++) {
+#pragma unroll
+        for (int i = 0; i < 2; i++) fa[i][kk] = load_frag<AT, 128>(st + p * HALF, fba[i], wm + i * 32, kk, lane);
+        if (p == 0)
+#pragma unroll
+          for (int j = 0; j < 2; j++) fb[j][kk] = load_frag<BT, 128>(st + (2 + j) * HALF, fbb, wn, kk, lane);
       }
-    }
+      if (p == 0) issue(kt + 1, 1); else issue3(kt + 2);
+      wait_vmcnt<8>();
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      // ---- multiply
+      __builtin_amdgcn_s_setprio(1);
+      if (p == 0 || lower)
 #pragma unroll
-    for (int i = 0; i < TE; i++) {
-      TC* cp = C + (i64)(m0 + wm + i * 32 + (lane >> 5) * 4) * g.ldc + n0 + wn + (lane & 31);
+      for (int kk = 0; kk < 4; kk++)
 #pragma unroll
-      for (int e = 0; e < 16; e++) {
-        const int dm = (e >> 2) * 8 + (e & 3);
-        const bool row_ok = full || (m0 + wm + i * 32 + (lane >> 5) * 4 + dm < m_end);
+        for (int i = 0; i < 2; i++)
 #pragma unroll
-        for (int j = 0; j < TN; j++)
-          if (row_ok && (full || n0 + wn + j * 32 + (lane & 31) < g.N)) cp[(i64)dm * g.ldc + j * 32] = (TC)acc[i][j][e];
-      }
-    }
-    return;
-  }
-  // Two phases per 32-column block: every load (bias, residual) and all arithmetic on loaded values
-  // first, then nothing but stores.  On this ISA one counter tracks loads and stores, and where a store may or may
-  // not have been issued (rows and columns past the problem's edge are masked per lane) the compiler can only wait
-  // for "everything": a use of a loaded value between two stores then waits for the earlier store to complete, and
-  // the 16 * TE * TN stores of a lane run one after the other (the coupling GEMMs with a residual operand took
-  // twice as long as the same GEMM with a plain store).  So loads are never masked (indices past the edge are
-  // clamped to the last valid row / column instead), the finished values are pinned in registers before the first
-  // store (the empty asm keeps the compiler from sinking the arithmetic into the masked store blocks), and the
-  // store phase has nothing to wait for.  The residual operand may be the output itself (in-place coupling update):
-  // it either is C, element for element, or does not overlap it, and each lane reads its elements before it writes.
-  constexpr int GI = 1;                              // 32-row blocks whose loads are issued together (more would spill at TE = 2)
-  const bool full = (m0 + BM <= m_end) && (n0 + BN <= g.N);
-  const int m_last = m_end - 1, n_last = g.N - 1;
-  auto row_of = [&](int i, int e) { return m0 + wm + i * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3); };
-#pragma unroll
-  for (int j = 0; j < TN; j++) {
-    const int n = n0 + wn + j * 32 + (lane & 31);
-    const bool n_ok = full || n < g.N;
-    const int nn = min(n, n_last);
-    const float bv = bias ? (float)bias[nn] : 0.f;
-#pragma unroll
-    for (int i0 = 0; i0 < TE; i0 += GI) {
-      // ---- phase 1: loads and arithmetic
-      float rv[GI][16];
-      if (resid) {
-        if (g.resid_f32) {
-#pragma unroll
-          for (int ii = 0; ii < GI; ii++)
-#pragma unroll
-            for (int e = 0; e < 16; e++)
-              rv[ii][e] = ((const float*)g.resid)[(i64)min(row_of(i0 + ii, e), m_last) * g.ldr + nn];
-        } else {
-#pragma unroll
-          for (int ii = 0; ii < GI; ii++)
-#pragma unroll
-            for (int e = 0; e < 16; e++) rv[ii][e] = (float)resid[(i64)min(row_of(i0 + ii, e), m_last) * g.ldr + nn];
-        }
-      } else {
-#pragma unroll
-        for (int ii = 0; ii < GI; ii++)
-#pragma unroll
-          for (int e = 0; e < 16; e++) rv[ii][e] = 0.f;
-      }
-#pragma unroll
-      for (int ii = 0; ii < GI; ii++)
-#pragma unroll
-        for (int e = 0; e < 16; e++) {
-          float v = acc[i0 + ii][j][e] + bv;                   // the value the tap records
-          float o = resid ? rv[ii][e] + g.resid_sign * v : v;
-          asm volatile("" : "+v"(v), "+v"(o));
-          acc[i0 + ii][j][e] = v;
-          rv[ii][e] = o;
-        }
-      // ---- phase 2: stores
-      if constexpr (sizeof(TC) == 2) {
-        // two columns of one row per lane (see the plain store above); the swap runs on every lane, the masks after it
-        if (!g.tap && !(g.ldc & 1) && !(g.N & 1) && !((uintptr_t)C & 3) && !g.no_packed_stores) {
-          const bool odd = lane & 1;
-          typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_v;
-#pragma unroll
-          for (int ii = 0; ii < GI; ii++)
-#pragma unroll
-            for (int e = 0; e < 16; e += 2) {
-              float l, r;
-              pair_rows(odd, rv[ii][e], rv[ii][e + 1], &l, &r);
-              bf16x2_v w;
-              w[0] = (__bf16)l; w[1] = (__bf16)r;
-              const int m = row_of(i0 + ii, e) + (odd ? 1 : 0);
-              if (n_ok && (full || m < m_end)) *(bf16x2_v*)(C + (i64)m * g.ldc + n - (odd ? 1 : 0)) = w;
-            }
-          continue;
-        }
-      }
-#pragma unroll
-      for (int ii = 0; ii < GI; ii++)
-#pragma unroll
-        for (int e = 0; e < 16; e++) {
-          const int m = row_of(i0 + ii, e);
-          if (n_ok && (full || m < m_end)) {
-            if (g.tap) g.tap[(i64)m * g.ldtap + n] = acc[i0 + ii][j][e];
-            C[(i64)m * g.ldc + n] = (TC)rv[ii][e];
-          }
-        }
+          for (int j = 0; j < 2; j++)
+            acc[p * 2 + i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i][kk], fb[j][kk], acc[p * 2 + i][j], 0, 0, 0);
+      __builtin_amdgcn_s_setprio(0);
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
     }
   }
+  if (wv < 4) __builtin_amdgcn_s_barrier();
+  wait_vmcnt<0>();                                   // the zero-filled loads past the last k-tile
+  int rb[4], cb[2];
+#pragma unroll
+  for (int i = 0; i < 4; i++) rb[i] = (i >> 1) * 128 + wm + (i & 1) * 32;
+  cb[0] = wn; cb[1] = 128 + wn;
+  gemm_epilogue<256, 256, AT, BT, TC, 4, 2>(g, C, bias_ptr, bx, m0, m_end, rb, cb, wn, acc);
 }
 
 template <int BM, int BN, int WGM, bool AT, bool BT, class TC, int NW, int NS, int KB = BK>
@@ -481,7 +638,8 @@ __global__ void __launch_bounds__(NW * 64) gemm_mfma_k(GemmArgs g) {
     for (int r = m0 + (int)(threadIdx.x & 63); r < min(m_end, m0 + BM); r += 64) live |= g.row_skip[r] == 0;
     if (!__any(live)) return;
   }
-  gemm_tile<BM, BN, WGM, AT, BT, TC, NW, NS, TM, KB>(g, A, Bm, C, bias, bx, bz, m0, m_end, k0, k_end, rot_seed);
+  if constexpr (NS == PHASED) gemm_tile_phased<AT, BT, TC>(g, A, Bm, C, bias, bx, m0, m_end, k0, k_end);
+  else gemm_tile<BM, BN, WGM, AT, BT, TC, NW, NS, TM, KB>(g, A, Bm, C, bias, bx, bz, m0, m_end, k0, k_end, rot_seed);
 }
 
 // REVFFN_XCD (tuning aid): 0 = plain 2-D grids, tiles land on the XCDs round-robin
@@ -514,7 +672,7 @@ static void go(const GemmArgs& g0, hipStream_t s) {
       grid = dim3(dense_grid_x(g.xcd_m, g.tiles_m, g.tiles_n), 1, zdim);
     }
   }
-  constexpr size_t smem = (size_t)NS * (BM + BN) * KB * 2;
+  constexpr size_t smem = (size_t)(NS == PHASED ? 2 : NS) * (BM + BN) * KB * 2;
   static_assert(smem <= 160 * 1024, "LDS stages exceed the CU's 160 KiB");
   static std::atomic<unsigned long long> attr_mask{0};
   if (attr_needed(attr_mask)) {
@@ -530,7 +688,7 @@ static void go(const GemmArgs& g0, hipStream_t s) {
 // 4 waves of 64x64 on the 2048^3 projections) and 128x64 (8 waves of 32x32, two workgroups per CU; 1.5 % of a step
 // over 4 waves of 64x32, measured on one box with both builds).
 template <bool AT, bool BT, class TC> static void go_256x128(const GemmArgs& g, hipStream_t s) { go<256, 128, 4, AT, BT, TC, 8, 3>(g, s); }
-template <bool AT, bool BT, class TC> static void go_256x256(const GemmArgs& g, hipStream_t s) { go<256, 256, 2, AT, BT, TC, 8, 2>(g, s); }
+template <bool AT, bool BT, class TC> static void go_256x256(const GemmArgs& g, hipStream_t s) { go<256, 256, 2, AT, BT, TC, 8, PHASED>(g, s); }
 template <bool AT, bool BT, class TC> static void go_128x128(const GemmArgs& g, hipStream_t s) { go<128, 128, 4, AT, BT, TC, 8, 4>(g, s); }
 template <bool AT, bool BT, class TC> static void go_128x256(const GemmArgs& g, hipStream_t s) { go<128, 256, 2, AT, BT, TC, 8, 3>(g, s); }
 template <bool AT, bool BT, class TC> static void go_128x64(const GemmArgs& g, hipStream_t s) { go<128, 64, 4, AT, BT, TC, 8, 3>(g, s); }
@@ -541,7 +699,7 @@ template <bool AT, bool BT, class TC> static void go_160x256(const GemmArgs& g, 
 template <bool AT, bool BT, class TC>
 static void pick_tile(const GemmArgs& g, hipStream_t s) {
   // Dense problems: the tile whose rounds of workgroups over the 256 CUs cost least.  One tile of 256x128 takes about
-  // 1.72 times, one of 256x256 about 3.05 times as long as one of 128x128 (measured on this block's shapes at 1024 to
+  // 1.85 times, one of 256x256 (in phases) about 2.6 times as long as one of 128x128 (measured at 1024 to
   // 8192 tokens: larger tiles do more work per loaded byte, but a last, partly filled round costs a whole tile's time).
   auto dense_choice = [&]() {
     const int z = g.n_sub;
@@ -554,7 +712,7 @@ static void pick_tile(const GemmArgs& g, hipStream_t s) {
       const i64 tiles = (i64)cdiv(g.M, bm) * cdiv(g.N, bn) * z;
       return bulk ? (double)tiles / 256.0 : (double)cdiv(tiles, 256);
     };
-    const double c2 = rounds(128, 128), c3 = 1.72 * rounds(256, 128), c4 = 3.05 * rounds(256, 256);
+    const double c2 = rounds(128, 128), c3 = 1.85 * rounds(256, 128), c4 = 2.6 * rounds(256, 256);
     return (c4 < c3 && c4 < c2) ? 4 : (c3 < c2 ? 3 : 2);
   };
   if (g.act_half && g.group_mode == 0) {
@@ -572,8 +730,7 @@ static void pick_tile(const GemmArgs& g, hipStream_t s) {
       case 2: go_128x128<AT, BT, TC>(g, s); return;
       case 3: go_256x128<AT, BT, TC>(g, s); return;
       case 4:
-        if constexpr (AT && BT) go<256, 256, 2, AT, BT, TC, 8, 4, 32>(g, s);
-        else go_256x256<AT, BT, TC>(g, s);
+        go_256x256<AT, BT, TC>(g, s);
         return;
     }
   }
@@ -582,7 +739,8 @@ static void pick_tile(const GemmArgs& g, hipStream_t s) {
     // specialised per block count) measured no gain, and neither did a fifth LDS stage.
     if constexpr (!AT) {
       if constexpr (!BT) { if (g.tile_bm == 160) { go_160x256<AT, BT, TC>(g, s); return; } }
-      if (g.tile_bm == 256) go_256x128<AT, BT, TC>(g, s);
+      if (g.tile_bm == 256 && g.tile_bn == 256) go_256x256<AT, BT, TC>(g, s);
+      else if (g.tile_bm == 256) go_256x128<AT, BT, TC>(g, s);
       else if (g.tile_bn == 256) go_128x256<AT, BT, TC>(g, s);
       else go_128x128<AT, BT, TC>(g, s);
     }
@@ -600,6 +758,7 @@ static void pick_tile(const GemmArgs& g, hipStream_t s) {
     // With k-tiles of 32 rows (4 stages of 32 KiB) an expert of 137 rows is 5 k-tiles instead of 3 of 64 (17 % fewer
     // multiplied zero rows), and all but the last are in flight at once: these kernels 10 % faster, a step 1.1 %.
     // (5 stages: 8 % slower again; 3: the same.)
+    // (The tile in phases is 6-25 % slower here at 8 to 546 rows per expert.)
     if constexpr (AT && BT) { go<256, 256, 2, AT, BT, TC, 8, 4, 32>(g, s); return; }
     return;                                            // (launch_gemm_mfma admits this mode for that layout only)
   }
@@ -608,10 +767,7 @@ static void pick_tile(const GemmArgs& g, hipStream_t s) {
   if (t128 < 200 && g.N >= 128) { go_128x64<AT, BT, TC>(g, s); return; }
   switch (dense_choice()) {
     case 4:
-      // (weight gradients: four stages of 32 rows of k instead of two of 64 keep more loads in flight; 0.5-1.2 % of a
-      // step on the skewed and long-sequence workloads)
-      if constexpr (AT && BT) go<256, 256, 2, AT, BT, TC, 8, 4, 32>(g, s);
-      else go_256x256<AT, BT, TC>(g, s);
+      go_256x256<AT, BT, TC>(g, s);
       break;
     case 3:
       // (the same tile count either way; with k contiguous in both operands the wide tile measured 1-4 % faster)
@@ -645,8 +801,10 @@ __global__ void __launch_bounds__(NW * 64) gemm_batch_tn_k(GemmBatch b) {
   GemmArgs g;
   g.M = ka->p[i].M; g.N = ka->p[i].N; g.K = ka->p[i].K;
   g.lda = ka->p[i].lda; g.ldb = ka->p[i].ldb; g.ldc = ka->p[i].ldc;
-  gemm_tile<BM, BN, WGM, true, true, TC, NW, NS, BM / WGM / 32, KB>(g, (const bf16*)ka->p[i].A, (const bf16*)ka->p[i].B,
-                                                                    (TC*)ka->p[i].C, nullptr, bx, 0, by * BM, g.M, 0, g.K, 0);
+  const bf16 *A = (const bf16*)ka->p[i].A, *B = (const bf16*)ka->p[i].B;
+  TC* C = (TC*)ka->p[i].C;
+  if constexpr (NS == PHASED) gemm_tile_phased<true, true, TC>(g, A, B, C, nullptr, bx, by * BM, g.M, 0, g.K);
+  else gemm_tile<BM, BN, WGM, true, true, TC, NW, NS, BM / WGM / 32, KB>(g, A, B, C, nullptr, bx, 0, by * BM, g.M, 0, g.K, 0);
 }
 template <int BM, int BN, int WGM, class TC, int NW, int NS, int KB = BK>
 static void go_batch(GemmBatch& b, hipStream_t s) {
@@ -656,7 +814,7 @@ static void go_batch(GemmBatch& b, hipStream_t s) {
     p.tile0 = b.total; p.tiles_m = cdiv(p.M, BM); p.tiles_n = cdiv(p.N, BN);
     b.total += p.tiles_m * p.tiles_n;
   }
-  constexpr size_t smem = (size_t)NS * (BM + BN) * KB * 2;
+  constexpr size_t smem = (size_t)(NS == PHASED ? 2 : NS) * (BM + BN) * KB * 2;
   static std::atomic<unsigned long long> attr_mask{0};
   if (attr_needed(attr_mask)) {
     (void)hipFuncSetAttribute((const void*)gemm_batch_tn_k<BM, BN, WGM, TC, NW, NS, KB>,
@@ -676,8 +834,8 @@ template <class TC> static void pick_batch_tile(GemmBatch& b, bool bulk, hipStre
     t256 += (double)cdiv(b.p[i].M, 256) * cdiv(b.p[i].N, 256);
   }
   auto rounds = [&](double t) { return bulk && t256 >= 128 ? t / 256.0 : ceil(t / 256.0); };
-  const double c2 = rounds(t128), c3 = 1.72 * rounds(t256x128), c4 = 3.05 * rounds(t256);
-  if (c4 < c2 && c4 < c3) go_batch<256, 256, 2, TC, 8, 4, 32>(b, s);
+  const double c2 = rounds(t128), c3 = 1.85 * rounds(t256x128), c4 = 2.6 * rounds(t256);
+  if (c4 < c2 && c4 < c3) go_batch<256, 256, 2, TC, 8, PHASED>(b, s);
   else if (c3 < c2) go_batch<256, 128, 4, TC, 8, 3>(b, s);
   else if (t128 >= 200) go_batch<128, 128, 4, TC, 8, 4>(b, s);
   else go_batch<128, 64, 4, TC, 8, 3>(b, s);
