@@ -62,6 +62,7 @@ struct revffn_ctx {
   bool use_streams = true;
   bool par = false;           // this call spreads independent branches over the helper streams (see fork_pays)
   int lastT = 0;
+  i64 call_T = 0;             // tokens of the current call
   int lastT_rows = 0;         // lastT * top_k: permuted rows of the current routing
   // attention half
   void *n12, *U12, *Q, *K, *V, *O, *AO;
@@ -289,7 +290,13 @@ void gemm_work(const revffn_ctx* c, const GemmArgs& g, int ta, int tb, int tc, d
   if (g.act_half) *bytes += M * (double)g.act_half * ec;
 }
 
+// a layer's GEMM over the rows of the call (one or both streams), few enough for the kernel of that name
+bool few_rows(const revffn_ctx* c, const GemmArgs& g) {
+  return g.group_mode == 0 && !g.a_trans && g.M <= 2 * c->call_T && gemm_few_rows(c->call_T, g.N);
+}
+
 int run_gemm(revffn_ctx* c, GemmArgs g, int ta, int tb, int tc, hipStream_t s) {
+  g.few_rows = few_rows(c, g);
   GemmTypes t{ta, tb, tc, c->dt};
   double fl = 0, by = 0;
   if (c->prof_on) gemm_work(c, g, ta, tb, tc, &fl, &by);
@@ -460,6 +467,7 @@ int run_gemm_multi(revffn_ctx* c, const GemmArgs* subs, int n, int tc, hipStream
   if (n > 1 && c->dt == 1 && c->mode == 0) {
     GemmArgs g = subs[0];
     g.n_sub = n;
+    g.few_rows = few_rows(c, g);
     for (int z = 1; z < n; z++) {
       g.subA[z - 1] = subs[z].A; g.subB[z - 1] = subs[z].B; g.subC[z - 1] = subs[z].C; g.subBias[z - 1] = subs[z].bias;
     }
@@ -847,6 +855,7 @@ int check_call(revffn_ctx* c, const revffn_weights* w, int B, int S, i64 ld) {
   if (B < 1 || S < 1) return REVFFN_ESHAPE;
   if ((i64)B * S > c->maxT) return REVFFN_ESHAPE;
   if (ld < c->cfg.d_model / 2) return REVFFN_ESHAPE;
+  c->call_T = (i64)B * S;
   c->par = c->use_streams && fork_pays(c, (i64)B * S);
   if (!w->norm_a1 || !w->norm_a2 || !w->norm_m || !w->pup_a || !w->pdn_a || !w->pup_m || !w->pdn_m || !w->wq ||
       !w->wk || !w->wv || !w->wo || !w->w_router || !w->w_gate_up || !w->w_down)
@@ -1516,6 +1525,7 @@ int revffn_op_gemm(int32_t dtype, int32_t kernel_mode, const void* a, const void
     return REVFFN_EINVAL;
   GemmArgs g = nt(a, lda, b, ldb, c, ldc, M, N, K);
   g.force_tile = tile;
+  g.few_rows = gemm_few_rows(M, N);
   g.a_trans = a_trans ? 1 : 0;
   g.b_trans = b_trans ? 1 : 0;
   GemmTypes t{dtype, dtype, out_f32 ? 0 : dtype, dtype};

@@ -1,0 +1,197 @@
+// bf16 GEMM for few rows (short prompts, one example per step): 32 x 32 tiles, the contraction cut among the waves of a
+// workgroup.
+//
+// With few rows a dense layer is its weight matrix read once, and what bounds it is how much of that is in flight.  The
+// tile kernel walks k in one chain per tile: 128 rows x 2048 columns x k = 2048 is 32 workgroups of 128x64 with three
+// k-tiles in flight each, and 32 dependent steps.  Here the same problem is 256 workgroups of 8 waves; wave w multiplies
+// the 64-wide pieces w, w + 8, ... of k with two pieces of its own in flight, and the partial tiles are added in wave
+// order through LDS, so that a result's bits depend on k alone.
+// Each wave stages its pieces in LDS that no other wave touches (direct loads, no barrier before the end): a fragment
+// read from memory by the lane that needs it puts every lane on a cache line of its own, 94 clocks per KiB.
+//  * rows x k operands: 128-byte rows, 16-byte chunk c of row r in slot c ^ ((r >> 1) & 7);
+//  * B stored k x columns: 64-byte rows, transposing reads (rows 0-3 and 8-11 of a k-step cover all banks twice, the
+//    least that 512 bytes can take).
+// Workgroups of one XCD take a run of column tiles with the row tile fastest, so a weight line enters one L2 only.
+#include "kernels.h"
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) short s16x4;
+typedef __attribute__((ext_vector_type(8))) short s16x8;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+
+#define OOB 0x80000000u              // byte offset past every descriptor's end: reads as zeros without traffic
+
+#define NW 8
+
+__device__ __forceinline__ u32x4 make_desc(const void* p) {
+  const unsigned long long a = (unsigned long long)p;
+  u32x4 d = {(unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)a),
+             (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(a >> 32)), OOB, 0x00020000u};
+  return d;
+}
+// one wave-load: 64 lanes x 16 bytes from desc + voff (per lane) to LDS at lds_addr + 16 * lane
+__device__ __forceinline__ void load_lds(u32x4 desc, unsigned lds_addr, unsigned voff) {
+  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+               :: "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(voff), "s"(desc) : "memory", "m0");
+}
+
+// NB = 32-column blocks of a tile: 2 with the SwiGLU epilogue (gate columns and the up columns of the same indices);
+// NS = pieces of a wave in flight
+template <bool BT, class TC, int NB, int NS>
+__global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
+  constexpr int RS = NB * 32 + 8;                    // row stride of a partial tile (floats): rows 4 apart are 32 banks apart
+  constexpr unsigned OPD = 64 * 32 * 2, STAGE = (1 + NB) * OPD;     // LDS bytes of a piece: A, then B
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  const bf16* A = (const bf16*)g.A;
+  const bf16* B = (const bf16*)g.B;
+  TC* C = (TC*)g.C;
+  const bf16* bias = (const bf16*)g.bias;
+  if (blockIdx.z == 1) { A = (const bf16*)g.subA[0]; B = (const bf16*)g.subB[0]; C = (TC*)g.subC[0]; bias = (const bf16*)g.subBias[0]; }
+  if (blockIdx.z == 2) { A = (const bf16*)g.subA[1]; B = (const bf16*)g.subB[1]; C = (TC*)g.subC[1]; bias = (const bf16*)g.subBias[1]; }
+  const int run = (g.tiles_n + 7) >> 3, c = (int)blockIdx.x & 7, loc = (int)blockIdx.x >> 3;
+  const int bx = c * run + loc / g.tiles_m, by = loc % g.tiles_m;
+  if (bx >= g.tiles_n) return;
+  const int m0 = by * 32, n0 = bx * 32, ncols = NB == 2 ? g.act_half : g.N;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5;
+  if (g.row_skip) {                                  // every wave looks at all rows of the tile: same answer, no barrier
+    const int r = m0 + (lane & 31);
+    if (!__any(r < g.M && g.row_skip[r] == 0)) return;
+  }
+  const u32x4 da = make_desc(A), db = make_desc(B);
+  const unsigned lda_b = (unsigned)g.lda * 2u, ldb_b = (unsigned)g.ldb * 2u;
+  // where this lane's share of the four wave-loads of each operand comes from at k = 0, and which k it is (relative to
+  // the piece): a load at or past K is out of range, rows and columns past the end repeat the last one or are zeros
+  unsigned aoff[4], boff[NB][4];
+  int akc[4];
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    const int r = i * 8 + (lane >> 3), ch = (lane & 7) ^ ((r >> 1) & 7);
+    akc[i] = ch * 8;
+    aoff[i] = (unsigned)min(m0 + r, g.M - 1) * lda_b + (unsigned)ch * 16u;
+    if constexpr (!BT) {
+#pragma unroll
+      for (int j = 0; j < NB; j++) boff[j][i] = (unsigned)(min(n0 + r, ncols - 1) + j * ncols) * ldb_b + (unsigned)ch * 16u;
+    } else {                                         // 16 k's: lane l brings columns (l & 3) * 8 .. + 7 of row l >> 2
+      const int col = n0 + (lane & 3) * 8;
+      boff[0][i] = col < g.N ? (unsigned)(i * 16 + (lane >> 2)) * ldb_b + (unsigned)col * 2u : OOB;
+    }
+  }
+  const unsigned my = (unsigned)wv * NS * STAGE;     // this wave's part of LDS
+  const unsigned lds0 = (unsigned)(unsigned long long)(__attribute__((address_space(3))) unsigned char*)smem + my;
+  auto issue = [&](int p, int stage) {
+    const int k0 = p * 64;
+    const unsigned dst = lds0 + (unsigned)stage * STAGE;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      const bool in = k0 + akc[i] < g.K;
+      load_lds(da, dst + i * 1024u, in ? aoff[i] + (unsigned)k0 * 2u : OOB);
+      if constexpr (!BT) {
+#pragma unroll
+        for (int j = 0; j < NB; j++) load_lds(db, dst + (1 + j) * OPD + i * 1024u, in ? boff[j][i] + (unsigned)k0 * 2u : OOB);
+      } else {
+        const bool kin = k0 + i * 16 + (lane >> 2) < g.K && boff[0][i] != OOB;
+        load_lds(db, dst + OPD + i * 1024u, kin ? boff[0][i] + (unsigned)k0 * ldb_b : OOB);
+      }
+    }
+  };
+  f32x16 acc[NB];
+#pragma unroll
+  for (int j = 0; j < NB; j++)
+#pragma unroll
+    for (int e = 0; e < 16; e++) acc[j][e] = 0.f;
+
+  const int fr = lane & 31, fsw = (fr >> 1) & 7;
+  const unsigned tr = (unsigned)((lane >> 5) * 8 + ((lane & 15) >> 2)) * 64u + (unsigned)(((lane >> 4) & 1) * 16 + (lane & 3) * 4) * 2u;
+  const int np = (g.K + 63) >> 6;
+#pragma unroll
+  for (int st = 0; st < NS; st++) issue(wv + st * NW, st);          // (pieces past the end load zeros, to keep the count)
+  int st = 0;
+  for (int p = wv; p < np; p += NW) {
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"((NS - 1) * 4 * (1 + NB)) : "memory");
+    const unsigned char* t = smem + my + (unsigned)st * STAGE;
+    bf16x8 fa[4], fb[NB][4];
+#pragma unroll
+    for (int s = 0; s < 4; s++) {
+      const unsigned at = (unsigned)fr * 128u + (unsigned)((2 * s + half) ^ fsw) * 16u;
+      fa[s] = *(const bf16x8*)(t + at);
+      if constexpr (!BT) {
+#pragma unroll
+        for (int j = 0; j < NB; j++) fb[j][s] = *(const bf16x8*)(t + (1 + j) * OPD + at);
+      } else {
+        const unsigned char* q = t + OPD + tr + s * 1024u;
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)q);
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(q + 4 * 64));
+        fb[0][s] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+      }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");              // the fragments are in registers: the stage is free
+    __builtin_amdgcn_sched_barrier(0);
+    issue(p + NS * NW, st);
+    st = st + 1 == NS ? 0 : st + 1;
+#pragma unroll
+    for (int s = 0; s < 4; s++)
+#pragma unroll
+      for (int j = 0; j < NB; j++) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[s], fb[j][s], acc[j], 0, 0, 0);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                  // the zero-filled loads past the end
+  __syncthreads();                                   // the partial tiles overlay the stages
+  float* part = (float*)smem;
+#pragma unroll
+  for (int j = 0; j < NB; j++)
+#pragma unroll
+    for (int e = 0; e < 16; e++)
+      part[wv * 32 * RS + ((e >> 2) * 8 + half * 4 + (e & 3)) * RS + j * 32 + (lane & 31)] = acc[j][e];
+  __syncthreads();
+  const int n = n0 + (int)(threadIdx.x & 31);
+  if (n >= ncols) return;
+#pragma unroll
+  for (int r = (int)threadIdx.x >> 5; r < 32; r += NW * 2) {
+    const int m = m0 + r;
+    if (m >= g.M) break;
+    float v[NB];
+#pragma unroll
+    for (int j = 0; j < NB; j++) {
+      v[j] = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; w++) v[j] += part[w * 32 * RS + r * RS + j * 32 + (int)(threadIdx.x & 31)];
+    }
+    if constexpr (NB == 2) {                         // silu(gate) * up from the rounded values, as the tile kernel
+      const TC gb = (TC)v[0], ub = (TC)v[1];
+      const float gv = (float)gb;
+      C[(i64)m * g.ldc + n] = gb;
+      C[(i64)m * g.ldc + ncols + n] = ub;
+      ((TC*)g.act_out)[(i64)m * g.ldact + n] = (TC)(gv * sigmoid_f(gv) * (float)ub);
+    } else {
+      float o = v[0] + (bias ? (float)bias[n] : 0.f);
+      if (g.tap) g.tap[(i64)m * g.ldtap + n] = o;
+      if (g.resid) {
+        const i64 at = (i64)m * g.ldr + n;
+        o = (g.resid_f32 ? ((const float*)g.resid)[at] : (float)((const bf16*)g.resid)[at]) + g.resid_sign * o;
+      }
+      C[(i64)m * g.ldc + n] = (TC)o;
+    }
+  }
+}
+
+template <bool BT, class TC, int NB, int NS>
+static void go(GemmArgs g, hipStream_t s) {
+  g.tiles_m = cdiv(g.M, 32);
+  g.tiles_n = cdiv(NB == 2 ? g.act_half : g.N, 32);
+  constexpr size_t part = (size_t)NW * 32 * (NB * 32 + 8) * 4, bufs = (size_t)NW * NS * (1 + NB) * 64 * 32 * 2;
+  constexpr size_t smem = part > bufs ? part : bufs;
+  static_assert(smem <= 160 * 1024, "LDS of a CU");
+  static std::atomic<unsigned long long> attr_mask{0};
+  if (attr_needed(attr_mask)) {
+    (void)hipFuncSetAttribute((const void*)gemm_skinny_k<BT, TC, NB, NS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    attr_done(attr_mask);
+  }
+  hipLaunchKernelGGL((gemm_skinny_k<BT, TC, NB, NS>), dim3(8 * cdiv(g.tiles_n, 8) * g.tiles_m, 1, g.n_sub), dim3(NW * 64), smem, s, g);
+}
+
+void launch_gemm_skinny(const GemmArgs& g, int out_f32, hipStream_t s) {
+  if (g.act_half) { if (out_f32) go<false, float, 2, 1>(g, s); else go<false, bf16, 2, 1>(g, s); }
+  else if (g.b_trans) { if (out_f32) go<true, float, 1, 2>(g, s); else go<true, bf16, 1, 2>(g, s); }
+  else { if (out_f32) go<false, float, 1, 2>(g, s); else go<false, bf16, 1, 2>(g, s); }
+}

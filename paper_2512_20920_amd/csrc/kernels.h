@@ -56,6 +56,7 @@ struct GemmArgs {
   // iteration of the inverse); a workgroup whose rows are all marked exits at once, the others compute every row
   int bulk = 0;                           // 1: not on the caller's critical path (runs beside other kernels): least CU-time wins
   const unsigned char* row_skip = nullptr;
+  int few_rows = 0;                       // MFMA kernel, dense problems, a_trans = 0: the kernel for few rows (gemm_skinny.hip)
   // set by the MFMA launcher: XCD-aware placement of the tiles (0 = plain 2-D grid), tile counts of the problem
   int xcd_m = 0, tiles_m = 0, tiles_n = 0;
 };
@@ -145,6 +146,15 @@ int launch_gemm_generic(const GemmArgs& g, GemmTypes t, hipStream_t s);
 // bf16 x bf16 MFMA path; returns 1 if the problem does not meet its alignment rules
 // (nothing launched), 0 if launched.
 int launch_gemm_mfma(const GemmArgs& g, GemmTypes t, hipStream_t s);
+// its form for few rows (problems that launch_gemm_mfma has accepted)
+// When a dense layer of N outputs goes there, for a call of T tokens (a rule on the call and the layer, never on how many
+// rows or problems one launch stacks: the kernels add in different orders, and results that are promised to be the same
+// bits may come from launches of T or 2 T rows).  Measured, us, weights from HBM, tile kernel -> this one:
+//   2048 outputs of k = 2048, both layouts: T = 128: 17.6 -> 7.9 / 18.0 -> 10.6   256: 18.0 -> 13.5 / 18.8 -> 17.4
+//   512: 17.9 -> 25.0    k = 5632: T = 128: 43 -> 15.6, 512: 42 -> 52    11264 outputs: T = 37: 19.4 -> 19.5, 128: 20.6 -> 38
+// so up to 512 tiles; three problems in one launch cross at 256, and 384 lies between.
+inline bool gemm_few_rows(i64 T, i64 N) { return ((T + 31) / 32) * ((N + 31) / 32) <= 384; }
+void launch_gemm_skinny(const GemmArgs& g, int out_f32, hipStream_t s);
 
 // Weight gradients of several dense layers, C_i[M_i,N_i] = A_i^T . B_i with A_i [K_i, M_i], B_i [K_i, N_i] row-major
 // (bf16 operands, bf16 or float32 results), as one launch.  Returns 1 (nothing launched) if a problem does not meet

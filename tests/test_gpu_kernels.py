@@ -68,6 +68,24 @@ def test_mfma_gemm_every_tile_shape(layout, tile):
             assert relerr(Hn.download(cd), ref) < (1e-5 if out_f32 else 6e-3), (layout, tile, M, N, K, out_f32)
 
 
+@pytest.mark.parametrize("layout", ["nt", "nn"])
+# one row, tails in every dimension around 32 rows and columns and the 64-wide pieces of k, fewer pieces than waves, one
+# more than a round of them, and the most tiles the rule sends there
+@pytest.mark.parametrize("M,N,K", [(1, 8, 8), (31, 40, 72), (33, 64, 504), (64, 1000, 520), (97, 264, 1096), (384, 1024, 64)])
+def test_few_rows_gemm(layout, M, N, K):
+    rng = np.random.default_rng(M + 3 * N + 5 * K)
+    A, Bm = _bf(rng, (M, K)), _bf(rng, (K, N))
+    b_trans = layout == "nn"
+    ad, bd = Hn.upload(A, "bf16"), Hn.upload(Bm if b_trans else Bm.T.copy(), "bf16")
+    for out_f32 in (False, True):
+        cd = torch.full((M + 1, N), float("nan"), dtype=torch.float32 if out_f32 else torch.bfloat16, device="cuda")
+        R.revffn_op_gemm(1, 2, ad, bd, cd, M, N, K, K, bd.shape[1], N, 0, b_trans, out_f32)
+        torch.cuda.synchronize()
+        # 24-bit sums of at most 1096 products; 2 ** -9 for a result rounded to bfloat16
+        assert relerr(Hn.download(cd[:M]), A @ Bm) < (1e-5 if out_f32 else 6e-3)
+        assert torch.isnan(cd[M]).all()                       # nothing past the last row
+
+
 def _attention_case(B, S, H, dh, causal, mode, dtype):
     rng = np.random.default_rng(S * 31 + H + (7 if causal else 0))
     rnd = (lambda s, sc=1.0: _bf(rng, s, sc)) if dtype == 1 else \
