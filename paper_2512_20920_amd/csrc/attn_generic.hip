@@ -1,6 +1,6 @@
 // Generic softmax attention (Attn_pt of section 3.2) on the vector ALUs: any head_dim,
-// any sequence length, float32 or bfloat16 storage with fp32 arithmetic.  It serves the
-// float32 configuration and head dims the MFMA flash kernels do not take.
+// any sequence length, float32 or bfloat16 storage with fp32 arithmetic.  It serves
+// head dims that neither matrix-core form (attn_flash.hip: bf16, 128; attn_f32.hip: 16, 32, 64, 128) takes.
 // Layout: q,k,v,o,do,dq,dk,dv are [T, H*dh] token-major (token t = b*S+s), head hh in
 // columns hh*dh..hh*dh+dh-1.  lse and dvec are [B,H,S] float.
 #include "kernels.h"
@@ -80,6 +80,7 @@ __global__ void __launch_bounds__(256) attn_fwd_generic_k(const T* __restrict__ 
 void launch_attn_fwd_generic(int dt, const void* q, const void* k, const void* v, void* o, float* lse, int B,
                              int S, int H, int dh, int causal, hipStream_t s, const unsigned char* row_skip) {
   if (B <= 0 || S <= 0) return;
+  if (launch_attn_fwd_f32(dt, q, k, v, o, lse, B, S, H, dh, causal, s, row_skip) == 0) return;
   size_t smem = (size_t)(dh + 256 + 4) * sizeof(float);
   float scale = 1.0f / sqrtf((float)dh);
   DISPATCH_DT(dt, hipLaunchKernelGGL(attn_fwd_generic_k<T>, dim3(S, H, B), dim3(256), smem, s, (const T*)q,
@@ -236,6 +237,7 @@ void launch_attn_bwd_generic(int dt, const void* q, const void* k, const void* v
                              int dh, int causal, hipStream_t s) {
   if (B <= 0 || S <= 0) return;
   launch_attn_dvec(dt, o, d_o, dvec, B, S, H, dh, s);
+  if (launch_attn_bwd_f32(dt, q, k, v, d_o, lse, dvec, dq, dk, dv, B, S, H, dh, causal, s) == 0) return;
   float scale = 1.0f / sqrtf((float)dh);
   size_t sm1 = (size_t)(2 * dh + 256) * sizeof(float);
   size_t sm2 = (size_t)(2 * dh + 512) * sizeof(float);

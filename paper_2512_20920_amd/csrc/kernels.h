@@ -259,6 +259,12 @@ void launch_attn_dvec(int dt, const void* o, const void* d_o, float* dvec, int B
 void launch_attn_bwd_generic(int dt, const void* q, const void* k, const void* v, const void* o,
                              const void* d_o, const float* lse, float* dvec, void* dq, void* dk, void* dv,
                              int B, int S, int H, int dh, int causal, hipStream_t s);
+// the same in float32 on the matrix cores; return 1 (nothing launched) for head widths other than 16, 32, 64, 128 and
+// pointers that are not aligned to 4 elements
+int launch_attn_fwd_f32(int dt, const void* q, const void* k, const void* v, void* o, float* lse, int B, int S, int H, int dh,
+                        int causal, hipStream_t s, const unsigned char* row_skip);
+int launch_attn_bwd_f32(int dt, const void* q, const void* k, const void* v, const void* d_o, const float* lse,
+                        const float* dvec, void* dq, void* dk, void* dv, int B, int S, int H, int dh, int causal, hipStream_t s);
 // MFMA flash kernels (bf16, dh = 128); return 1 if unsupported shape.
 int launch_attn_fwd_flash(const void* q, const void* k, const void* v, void* o, float* lse,
                           int B, int S, int H, int dh, int causal, hipStream_t s,

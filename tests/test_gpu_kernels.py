@@ -141,3 +141,11 @@ def test_flash_attention_ragged_long_sequence():
 def test_generic_attention(dtype, dh):
     _attention_case(2, 70, 3, dh, True, 1, dtype)
     _attention_case(1, 33, 2, dh, False, 1, dtype)
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+# every head width; one row, a tail of one past a tile of 32, more tiles than the four waves of a workgroup
+@pytest.mark.parametrize("dh,B,S,H", [(16, 2, 33, 2), (32, 1, 1, 1), (64, 3, 131, 2), (64, 1, 300, 1), (128, 2, 97, 1)])
+def test_float32_matrix_attention(dtype, dh, B, S, H):
+    _attention_case(B, S, H, dh, True, 1, dtype)
+    _attention_case(B, S, H, dh, False, 1, dtype)
