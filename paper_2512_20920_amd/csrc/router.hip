@@ -22,13 +22,15 @@
 //
 // One workgroup of 16 waves per block of 16 tokens.  The routing chain (this kernel, then the permutation) is latency:
 // 2 MFLOP and the whole of wrp per workgroup.  The 16 x E1 logits are cut over the waves by column tile and by slices of
-// h (operands straight from memory, the squares for 1/rms are summed from the same registers), added in slice order
+// h (the squares for 1/rms are summed from the same registers), added in slice order
 // through LDS, and then a wave finishes one token with one lane per expert (reductions by data-parallel moves, the
 // arg-max as maximum and ballot).  (32 tokens per workgroup: half the CUs, twice the matrix-core time on each.)
 // ---------------------------------------------------------------------------------
 #define ROUTER_TOKENS 16
 #define ROUTER_WAVES 16
 __host__ __device__ inline int router_slices(int tiles) { return tiles >= ROUTER_WAVES ? 1 : ROUTER_WAVES / tiles; }
+// bytes of the logits, squares and counts (at most 20 KB), to a multiple of 16; the operand chunks of the waves follow
+__host__ __device__ inline size_t router_lds(int E, int tiles, int ns) { return (((size_t)ns * 16 * (tiles * 16 + 1) + E) * 4 + 15) & ~(size_t)15; }
 
 template <class T>
 __global__ void __launch_bounds__(ROUTER_WAVES * 64) router_k(
@@ -40,18 +42,21 @@ __global__ void __launch_bounds__(ROUTER_WAVES * 64) router_k(
   float* zpart = sm;                              // [ns][16][zc]: slice partials; slice 0 then takes the sums
   float* sspart = sm + ns * 16 * zc;              // [ns][16]
   int* cnt = (int*)(sspart + ns * 16);            // [E]
+  typedef Operand<T, false, 16, true> OA;
+  typedef Operand<float, false, 16, true> OB;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, gh = lane >> 4;
   const int t0 = blockIdx.x * ROUTER_TOKENS;
+  char* lds = (char*)sm + router_lds(E, tiles, ns) + (size_t)wv * (OA::lds_bytes + OB::lds_bytes);     // the wave's operand chunks
   for (int e = threadIdx.x; e < E; e += blockDim.x) cnt[e] = 0;
   const int nchunk = (h + GKC(16) - 1) / GKC(16);
   for (int item = wv; item < tiles * ns; item += ROUTER_WAVES) {
     const int sl = item / tiles, tt = item - sl * tiles;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     float ss = 0.f;
-    Operand<T, false, 16> oa[1];
-    Operand<float, false, 16> ob[1];
-    oa[0].init(y1, ld, t0, Tn, lane);
-    ob[0].init(wrp, h, tt * 16, E1, lane);
+    OA oa[1];
+    OB ob[1];
+    oa[0].init(y1, ld, t0, Tn, lane, nullptr, 1, 0, nullptr, lds);
+    ob[0].init(wrp, h, tt * 16, E1, lane, nullptr, 1, 0, nullptr, lds + OA::lds_bytes);
     k_loop<16, 1, 1>(oa, ob, 0, h, sl, ns, nchunk, gh, [&](float (&a)[1][16], float (&b)[1][16]) {
 #pragma unroll
       for (int s = 0; s < 16; s++) { acc = mfma_f32(a[0][s], b[0][s], acc); ss += a[0][s] * a[0][s]; }
@@ -138,7 +143,13 @@ void launch_router(int dt, const void* y1, i64 ld, const float* wrp, const float
                    float eps, hipStream_t s) {
   if (Tn <= 0) return;
   const int tiles = (E + (has_gate ? 1 : 0) + 15) / 16, ns = router_slices(tiles);
-  const size_t smem = ((size_t)ns * 16 * (tiles * 16 + 1) + E) * 4;         // at most 20 KB
+  const size_t smem = router_lds(E, tiles, ns) + (size_t)ROUTER_WAVES * 1024 * ((dt == 0 ? 4 : 2) + 4);
+  static std::atomic<unsigned long long> attr_mask{0};
+  if (attr_needed(attr_mask)) {
+    (void)hipFuncSetAttribute((const void*)router_k<float>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    (void)hipFuncSetAttribute((const void*)router_k<bf16>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    attr_done(attr_mask);
+  }
   DISPATCH_DT(dt, hipLaunchKernelGGL(router_k<T>, dim3(cdiv(Tn, ROUTER_TOKENS)), dim3(ROUTER_WAVES * 64), smem, s,
                                      (const T*)y1, ld, wrp, b_router, probs, idx, wts, gamma, blk_cnt, Tn, h, E, k,
                                      has_gate, norm_topk, eps));
