@@ -81,19 +81,34 @@ __device__ __forceinline__ void store_rows64(bf16* lds, int stride, const uint4 
   }
 }
 
+// Which tile a workgroup takes (1-D grid of tiles x B x H workgroups; tile 0 has the most work when causal).  Heads are the
+// fastest index, so that an XCD (id & 7) keeps to H / 8 heads, and long tiles come first.  Two workgroups fit on a CU: where
+// the whole grid is resident at once, workgroups i and i + 256 share one, so the second 256 run from short to long (with
+// both halves long first the slowest CU has a long tile of either batch: 2 x 2048 tokens, 16 heads, forward, dQ, dK/dV 83,
+// 119, 154 -> 67, 100, 141 us).
+__device__ __forceinline__ void place(int H, int B, int tiles, int* t, int* hh, int* b) {
+  const int rows = tiles * B, first = 256 / H;
+  int row = (int)blockIdx.x / H;
+  *hh = (int)blockIdx.x - row * H;
+  if ((int)gridDim.x <= 512 && row >= first) row = rows - 1 - (row - first);
+  *t = row / B;
+  *b = row - *t * B;
+}
+
 // ------------------------------------------------------------------------------------
 // Forward.  Workgroup = 128 queries of one (batch, head); wave = 32 queries; keys/values
 // streamed in tiles of 64.
 // ------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(256, 2) flash_fwd_k(const bf16* __restrict__ q, const bf16* __restrict__ k,
                                                    const bf16* __restrict__ v, bf16* __restrict__ o,
-                                                   float* __restrict__ lse, int S, int H, int causal, float scale,
+                                                   float* __restrict__ lse, int B, int S, int H, int causal, float scale,
                                                    const unsigned char* __restrict__ row_skip) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   bf16* sK = (bf16*)smem_raw;               // 2 stages [64][KST]
   bf16* sV = sK + 2 * BKV * KST;            // 2 stages [64][VST]
-  const int qt = gridDim.y - 1 - blockIdx.y;        // long (late) query tiles first, for every head
-  const int hh = blockIdx.x, b = blockIdx.z;
+  int qt, hh, b;
+  place(H, B, (S + 127) / 128, &qt, &hh, &b);
+  qt = (S + 127) / 128 - 1 - qt;            // late query tiles are the long ones
   if (row_skip) {                           // every query of the tile is a finished row of the inverse's iteration
     int live = 0;                           // every wave checks all 128 rows of the tile: same answer, no LDS
     for (int r = qt * 128 + (int)(threadIdx.x & 63); r < min(S, qt * 128 + 128); r += 64) live |= row_skip[(i64)b * S + r] == 0;
@@ -247,8 +262,8 @@ int launch_attn_fwd_flash(const void* q, const void* k, const void* v, void* o, 
     (void)hipFuncSetAttribute((const void*)flash_fwd_k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     attr_done(attr_mask);
   }
-  hipLaunchKernelGGL(flash_fwd_k, dim3(H, cdiv(S, 128), B), dim3(256), smem, s, (const bf16*)q, (const bf16*)k,
-                     (const bf16*)v, (bf16*)o, lse, S, H, causal, 1.0f / sqrtf((float)dh), row_skip);
+  hipLaunchKernelGGL(flash_fwd_k, dim3((unsigned)((i64)H * cdiv(S, 128) * B)), dim3(256), smem, s, (const bf16*)q, (const bf16*)k,
+                     (const bf16*)v, (bf16*)o, lse, B, S, H, causal, 1.0f / sqrtf((float)dh), row_skip);
   return 0;
 }
 
@@ -261,12 +276,13 @@ int launch_attn_fwd_flash(const void* q, const void* k, const void* v, void* o, 
 __global__ void __launch_bounds__(256, 2) flash_bwd_dq_k(const bf16* __restrict__ q, const bf16* __restrict__ k,
                                                       const bf16* __restrict__ v, const bf16* __restrict__ d_o,
                                                       const float* __restrict__ lse, const float* __restrict__ dvec,
-                                                      bf16* __restrict__ dq, int S, int H, int causal, float scale) {
+                                                      bf16* __restrict__ dq, int B, int S, int H, int causal, float scale) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   bf16* sK = (bf16*)smem_raw;               // 2 stages [64][BST]
   bf16* sV = sK + 2 * BKV * BST;            // 2 stages [64][BST]
-  const int qt = gridDim.y - 1 - blockIdx.y;
-  const int hh = blockIdx.x, b = blockIdx.z;
+  int qt, hh, b;
+  place(H, B, (S + 127) / 128, &qt, &hh, &b);
+  qt = (S + 127) / 128 - 1 - qt;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, g = lane >> 5;
   const i64 ld = (i64)H * DH;
   const i64 boff = (i64)b * S * ld + hh * DH;
@@ -418,11 +434,11 @@ __device__ __forceinline__ bf16x8 swz_cols(const unsigned char* tile, unsigned b
 __global__ void __launch_bounds__(256, 2) flash_bwd_dkv_k(const bf16* __restrict__ q, const bf16* __restrict__ k,
                                                        const bf16* __restrict__ v, const bf16* __restrict__ d_o,
                                                        const float* __restrict__ lse, const float* __restrict__ dvec,
-                                                       bf16* __restrict__ dk, bf16* __restrict__ dv, int S, int H,
+                                                       bf16* __restrict__ dk, bf16* __restrict__ dv, int B, int S, int H,
                                                        int causal, float scale) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];      // 2 stages
-  const int kt = blockIdx.y;                // early key tiles see the most queries when causal: first
-  const int hh = blockIdx.x, b = blockIdx.z;
+  int kt, hh, b;
+  place(H, B, (S + 127) / 128, &kt, &hh, &b);       // early key tiles see the most queries
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 5;
   const i64 ld = (i64)H * DH;
   const i64 boff = (i64)b * S * ld + hh * DH;
@@ -552,10 +568,10 @@ int launch_attn_bwd_flash(const void* q, const void* k, const void* v, const voi
     (void)hipFuncSetAttribute((const void*)flash_bwd_dkv_k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm2);
     attr_done(attr_mask);
   }
-  dim3 grid(H, cdiv(S, 128), B);
+  dim3 grid((unsigned)((i64)H * cdiv(S, 128) * B));
   hipLaunchKernelGGL(flash_bwd_dq_k, grid, dim3(256), sm1, s, (const bf16*)q, (const bf16*)k, (const bf16*)v,
-                     (const bf16*)d_o, lse, dvec, (bf16*)dq, S, H, causal, scale);
+                     (const bf16*)d_o, lse, dvec, (bf16*)dq, B, S, H, causal, scale);
   hipLaunchKernelGGL(flash_bwd_dkv_k, grid, dim3(256), sm2, s, (const bf16*)q, (const bf16*)k, (const bf16*)v,
-                     (const bf16*)d_o, lse, dvec, (bf16*)dk, (bf16*)dv, S, H, causal, scale);
+                     (const bf16*)d_o, lse, dvec, (bf16*)dk, (bf16*)dv, B, S, H, causal, scale);
   return 0;
 }

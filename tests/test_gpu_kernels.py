@@ -143,6 +143,13 @@ def test_generic_attention(dtype, dh):
     _attention_case(1, 33, 2, dh, False, 1, dtype)
 
 
+# more workgroups than CUs and no more than two for each: the second part of the grid runs in reverse (48 and 100 heads: a
+# whole and a broken row of heads where it starts)
+@pytest.mark.parametrize("B,S,H", [(2, 451, 48), (1, 300, 100)])
+def test_flash_attention_paired_tiles(B, S, H):
+    _attention_case(B, S, H, 128, True, 2, 1)
+
+
 @pytest.mark.parametrize("dtype", [0, 1])
 # every head width; one row, a tail of one past a tile of 32, more tiles than the four waves of a workgroup
 @pytest.mark.parametrize("dh,B,S,H", [(16, 2, 33, 2), (32, 1, 1, 1), (64, 3, 131, 2), (64, 1, 300, 1), (128, 2, 97, 1)])
