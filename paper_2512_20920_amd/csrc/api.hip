@@ -184,6 +184,7 @@ size_t carve(revffn_ctx* c, char* base) {
   c->y1c = cv.take(T * h * c->ses);
   c->xtmp = cv.take(T * h * c->ses);
   c->resid_dev = (float*)cv.take(256);
+  const size_t colsums = 3 * d + 3 * h + E;      // at most this many columns are summed in a call
   {
     // state of the device-side stopping rule: the four arrays that start every inverse at zero are contiguous
     const size_t Tp = (T + 3) & ~(size_t)3;
@@ -195,6 +196,7 @@ size_t carve(revffn_ctx* c, char* base) {
     c->conv_zero_words = Tp * 10 / 4;
     c->conv.blk_res = (float*)cv.take(Tp * 4);
     c->conv.stats = (int*)cv.take(256);
+    c->ticket = (int*)cv.take(colsum_tickets(colsums) * 4);       // (behind the statistics: cleared together)
   }
   c->dRS = cv.take(T * d * es);
   c->dYp = cv.take(N * d * es);
@@ -217,9 +219,7 @@ size_t carve(revffn_ctx* c, char* base) {
   c->blk_cnt = (int*)cv.take(router_blocks(T) * E * 4);
   c->rinv = (float*)cv.take(2 * T * 4);
   c->rinv3 = (float*)cv.take(T * 4);
-  const size_t colsums = 3 * d + 3 * h + E;      // at most this many columns are summed in a call
   c->partial = (float*)cv.take(colsum_partial_floats(colsums) * 4);
-  c->ticket = (int*)cv.take(colsum_tickets(colsums) * 4);
   c->dAO = cv.take(T * d * es);
   c->dO = cv.take(T * d * es);
   c->dQ = cv.take(T * d * es);
@@ -1179,8 +1179,8 @@ int revffn_create(revffn_ctx** out, const revffn_config* cfg, int32_t max_B, int
   }
   carve(c, (char*)c->slab);
   (void)hipMemset(c->wr_ext, 0, (size_t)((c->cfg.n_experts + (c->cfg.d_shared ? 1 : 0) + 7) / 8 * 8) * c->cfg.d_model * c->es);
-  (void)hipMemset(c->conv.stats, 0, 4 * sizeof(int));
-  (void)hipMemset(c->ticket, 0, colsum_tickets((size_t)9 * (cfg->d_model / 2) + cfg->n_experts) * 4);
+  const size_t ticket_bytes = colsum_tickets((size_t)9 * (cfg->d_model / 2) + cfg->n_experts) * 4;
+  (void)hipMemset(c->conv.stats, 0, (size_t)((char*)c->ticket - (char*)c->conv.stats) + ticket_bytes);
   c->use_streams = getenv("REVFFN_NO_STREAMS") == nullptr;
   { const char* e = getenv("REVFFN_EXPERT_TILE"); if (e && (atoi(e) == 256 || atoi(e) == 128)) c->expert_tile = atoi(e); }
   { const char* e = getenv("REVFFN_NO_FUSED_SWIGLU"); c->no_fused_swiglu = e && atoi(e) != 0; }
