@@ -42,8 +42,8 @@ __global__ void __launch_bounds__(ROUTER_WAVES * 64) router_k(
   float* zpart = sm;                              // [ns][16][zc]: slice partials; slice 0 then takes the sums
   float* sspart = sm + ns * 16 * zc;              // [ns][16]
   int* cnt = (int*)(sspart + ns * 16);            // [E]
-  typedef Operand<T, false, 16, true> OA;
-  typedef Operand<float, false, 16, true> OB;
+  typedef StagedOperand<T, 16> OA;
+  typedef StagedOperand<float, 16> OB;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, gh = lane >> 4;
   const int t0 = blockIdx.x * ROUTER_TOKENS;
   char* lds = (char*)sm + router_lds(E, tiles, ns) + (size_t)wv * (OA::lds_bytes + OB::lds_bytes);     // the wave's operand chunks
@@ -55,8 +55,8 @@ __global__ void __launch_bounds__(ROUTER_WAVES * 64) router_k(
     float ss = 0.f;
     OA oa[1];
     OB ob[1];
-    oa[0].init(y1, ld, t0, Tn, lane, nullptr, 1, 0, nullptr, lds);
-    ob[0].init(wrp, h, tt * 16, E1, lane, nullptr, 1, 0, nullptr, lds + OA::lds_bytes);
+    oa[0].init(y1, ld, t0, Tn, lane, lds);
+    ob[0].init(wrp, h, tt * 16, E1, lane, lds + OA::lds_bytes);
     k_loop<16, 1, 1>(oa, ob, 0, h, sl, ns, nchunk, gh, [&](float (&a)[1][16], float (&b)[1][16]) {
 #pragma unroll
       for (int s = 0; s < 16; s++) { acc = mfma_f32(a[0][s], b[0][s], acc); ss += a[0][s] * a[0][s]; }
