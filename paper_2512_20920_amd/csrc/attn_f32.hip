@@ -9,8 +9,8 @@
 // A workgroup is 32 queries (keys) of one head and its 4 waves share the keys (queries) out, tile w, w + 4, ..; partial
 // results meet in LDS in wave order.  These are short sequences of few heads, and what bounds them is one wave's chain:
 // one workgroup per query on the vector units walked the keys twice, one fused multiply-add per loaded element.
-// Forward, dQ, dK/dV: 251 tokens, 3 x 4 heads of 64, bfloat16 storage: 78, 53, 57 -> 16, 18, 23 us; 200 tokens, 2 x 4 heads
-// of 128, float32: 66, 55, 55 -> 21, 29, 54.
+// Forward, dQ, dK/dV: 251 tokens, 3 x 4 heads of 64, bfloat16 storage: 55, 51, 56 -> 12, 14, 23 us; 700 tokens, 4 heads of
+// 128, float32: 262, 225, 232 -> 42, 65, 88.
 #include "kernels.h"
 
 typedef __attribute__((ext_vector_type(16))) float f32x16;
@@ -48,13 +48,68 @@ __device__ __forceinline__ int elem_row(int e, int half) { return (e >> 2) * 8 +
 // that one: p is zero there)
 template <class T, int DH, int DT>
 __device__ __forceinline__ void accumulate(f32x16 (&acc)[DT], const T* x, i64 ld, int r0, int last, const f32x16& p, int lane) {
+  T v[16][DT];
 #pragma unroll
   for (int e = 0; e < 16; e++) {
     const T* row = x + (i64)min(r0 + elem_row(e, lane >> 5), last) * ld + (lane & (DH < 32 ? DH - 1 : 31));
 #pragma unroll
-    for (int i = 0; i < DT; i++) acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32((float)row[i * 32], p[e], acc[i], 0, 0, 0);
+    for (int i = 0; i < DT; i++) v[e][i] = row[i * 32];
+  }
+  // all loads in flight before the first product: left to itself the compiler takes a few at a time as soon as registers
+  // are short (128-wide dK/dV at 700 tokens 137 us, 88 like this)
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int e = 0; e < 16; e++)
+#pragma unroll
+    for (int i = 0; i < DT; i++) acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32((float)v[e][i], p[e], acc[i], 0, 0, 0);
+}
+// The same for a wave that starts over because its result was not finite (see finite), on a tile of which lanes see only
+// the rows lo .. hi - 1 (p is zero in the others).  A value of X that is not finite enters the product as a zero, so that a
+// lane that does not see it keeps the bits it has with any finite value; the lanes that see it then get p times it from the
+// same instruction on counts: per result element the +infinities (in units of 1) and the -infinities (of 128) among those
+// products, a NaN or an infinity times zero counting as both.
+template <class T, int DH, int DT>
+__device__ __forceinline__ void accumulate_apart(f32x16 (&acc)[DT], const T* x, i64 ld, int r0, int last, const f32x16& p, int lane,
+                                                 int lo, int hi) {
+#pragma unroll
+  for (int i = 0; i < DT; i++) {
+    f32x16 n = {};
+#pragma unroll
+    for (int e = 0; e < 16; e++) {
+      if (e % 4 == 0) {                              // (a few loads at a time: this must not cost the other path registers)
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" : "+v"(lane), "+v"(lo), "+v"(hi));
+      }
+      const int r = r0 + elem_row(e, lane >> 5);
+      const float v = (float)x[(i64)min(r, last) * ld + (lane & (DH < 32 ? DH - 1 : 31)) + i * 32];
+      const float up = v < INFINITY ? 0.f : 1.f, down = v > -INFINITY ? 0.f : 1.f;
+      const bool sees = r >= lo && r < hi;
+      acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(up + down > 0.f ? 0.f : v, p[e], acc[i], 0, 0, 0);
+      n = __builtin_amdgcn_mfma_f32_32x32x2f32(up + 128.f * down, sees && !(p[e] < 0.f) ? 1.f : 0.f, n, 0, 0, 0);
+      n = __builtin_amdgcn_mfma_f32_32x32x2f32(down + 128.f * up, sees && !(p[e] > 0.f) ? 1.f : 0.f, n, 0, 0, 0);
+    }
+#pragma unroll
+    for (int e = 0; e < 16; e++) {
+      const float down = floorf(n[e] * (1.f / 128.f));
+      acc[i][e] += n[e] - 128.f * down > 0.f ? INFINITY : 0.f;
+      acc[i][e] += down > 0.f ? -INFINITY : 0.f;
+    }
   }
 }
+// On tiles that some lanes see only in part the matrix instruction multiplies the rest by their zero probabilities, and a
+// value that is not finite would reach queries before it (keys after it).  That always shows in the result, so the tiles
+// are multiplied plainly first (looking at every element on the way: 128-wide forward 46 -> 149 us at 700 tokens) and a
+// wave whose result is not finite starts over, keeping such values apart on those tiles.
+template <int DT> __device__ __forceinline__ bool finite(const f32x16 (&acc)[DT]) {
+  bool all = true;
+#pragma unroll
+  for (int i = 0; i < DT; i++)
+#pragma unroll
+    for (int e = 0; e < 16; e++) all &= __builtin_fabsf(acc[i][e]) < INFINITY;
+  return __all(all);
+}
+// the lane for the second pass, so that nothing of the first one is kept in registers for it
+__device__ __forceinline__ int opaque(int lane) { asm volatile("" : "+v"(lane)); return lane; }
 // a wave's accumulators to its LDS tile [32 rows][DH + 1] (row = lane & 31)
 template <int DH, int DT> __device__ __forceinline__ void spill_tile(float* t, const f32x16 (&acc)[DT], int lane) {
 #pragma unroll
@@ -77,6 +132,39 @@ template <class T, int DH> __device__ __forceinline__ void store_sum(const float
   }
 }
 
+// A wave's share of the forward pass of 32 queries (a lane owns one; its keys are 0 .. seen - 1).  APART: see finite.
+template <class T, int DH, bool APART, int DT>
+__device__ __forceinline__ void fwd_keys(const T* k, const T* v, i64 ld, int S, int nt, int wv, int lane, int seen,
+                                         const float (&qf)[DH / 2], f32x16 (&acc)[DT], float& m, float& l) {
+  const int half = lane >> 5;
+#pragma unroll
+  for (int i = 0; i < DT; i++) acc[i] = f32x16{};
+  m = -INFINITY;
+  l = 0.f;
+  for (int t = wv; t < nt; t += NW) {
+    const int kv0 = t * 32;
+    f32x16 s = scores<T, DH>(k + (i64)min(kv0 + (lane & 31), S - 1) * ld, half, qf);
+    float mx = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < 16; e++) {
+      if (kv0 + elem_row(e, half) >= seen) s[e] = -INFINITY;
+      mx = fmaxf(mx, s[e]);
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE));
+    const float mn = fmaxf(m, mx), ms = mn == -INFINITY ? 0.f : mn;
+    float rs = 0.f;
+#pragma unroll
+    for (int e = 0; e < 16; e++) { s[e] = __expf(s[e] - ms); rs += s[e]; }
+    rs += __shfl_xor(rs, 32, WAVE);
+    const float alpha = __expf(m - ms);
+    l = l * alpha + rs;
+    m = mn;
+#pragma unroll
+    for (int i = 0; i < DT; i++) acc[i] *= alpha;
+    if constexpr (APART) accumulate_apart<T, DH, DT>(acc, v, ld, kv0, S - 1, s, lane, 0, seen);
+    else accumulate<T, DH, DT>(acc, v, ld, kv0, S - 1, s, lane);
+  }
+}
 template <class T, int DH>
 __global__ void __launch_bounds__(NW * 64) attn_fwd_f32_k(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
                                                           T* __restrict__ o, float* __restrict__ lse, int S, int H, int causal,
@@ -92,31 +180,11 @@ __global__ void __launch_bounds__(NW * 64) attn_fwd_f32_k(const T* __restrict__ 
   float qf[DH / 2];
   load_row<T, DH>(q + base + (i64)min(myq, S - 1) * ld, half, scale, qf);
   const int nt = ((causal ? min(S, q0 + 32) : S) + 31) / 32;
-  f32x16 acc[DT] = {};
-  float m = -INFINITY, l = 0.f;
-  for (int t = wv; t < nt; t += NW) {
-    const int kv0 = t * 32;
-    f32x16 s = scores<T, DH>(k + base + (i64)min(kv0 + (lane & 31), S - 1) * ld, half, qf);
-    float mx = -INFINITY;
-#pragma unroll
-    for (int e = 0; e < 16; e++) {
-      const int kv = kv0 + elem_row(e, half);
-      if (kv >= S || (causal && kv > myq)) s[e] = -INFINITY;
-      mx = fmaxf(mx, s[e]);
-    }
-    mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE));
-    const float mn = fmaxf(m, mx), ms = mn == -INFINITY ? 0.f : mn;
-    float rs = 0.f;
-#pragma unroll
-    for (int e = 0; e < 16; e++) { s[e] = __expf(s[e] - ms); rs += s[e]; }
-    rs += __shfl_xor(rs, 32, WAVE);
-    const float alpha = __expf(m - ms);
-    l = l * alpha + rs;
-    m = mn;
-#pragma unroll
-    for (int i = 0; i < DT; i++) acc[i] *= alpha;
-    accumulate<T, DH, DT>(acc, v + base, ld, kv0, S - 1, s, lane);
-  }
+  const int seen = causal ? min(S, myq + 1) : S;
+  f32x16 acc[DT];
+  float m, l;
+  fwd_keys<T, DH, false>(k + base, v + base, ld, S, nt, wv, lane, seen, qf, acc, m, l);
+  if (!finite<DT>(acc)) fwd_keys<T, DH, true>(k + base, v + base, ld, S, nt, wv, opaque(lane), seen, qf, acc, m, l);
   spill_tile<DH, DT>(sm + wv * 32 * (DH + 1), acc, lane);
   if (half == 0) { sM[wv * 32 + lane] = m; sL[wv * 32 + lane] = l; }
   __syncthreads();
@@ -139,7 +207,24 @@ __global__ void __launch_bounds__(NW * 64) attn_fwd_f32_k(const T* __restrict__ 
   }
 }
 
-// dQ: dS^T = P^T (dP^T - D), dP^T = V dO^T, dQ^T += K^T dS^T
+// A wave's share of dQ of 32 queries: dS^T = P^T (dP^T - D), dP^T = V dO^T, dQ^T += K^T dS^T
+template <class T, int DH, bool APART, int DT>
+__device__ __forceinline__ void dq_keys(const T* k, const T* v, i64 ld, int S, int nt, int wv, int lane, int seen, float L, float D,
+                                        const float (&qf)[DH / 2], const float (&dof)[DH / 2], f32x16 (&acc)[DT]) {
+  const int half = lane >> 5;
+#pragma unroll
+  for (int i = 0; i < DT; i++) acc[i] = f32x16{};
+  for (int t = wv; t < nt; t += NW) {
+    const int kv0 = t * 32;
+    const i64 row = (i64)min(kv0 + (lane & 31), S - 1) * ld;
+    f32x16 s = scores<T, DH>(k + row, half, qf);
+    const f32x16 dp = scores<T, DH>(v + row, half, dof);
+#pragma unroll
+    for (int e = 0; e < 16; e++) s[e] = kv0 + elem_row(e, half) >= seen ? 0.f : __expf(s[e] - L) * (dp[e] - D);
+    if constexpr (APART) accumulate_apart<T, DH, DT>(acc, k, ld, kv0, S - 1, s, lane, 0, seen);
+    else accumulate<T, DH, DT>(acc, k, ld, kv0, S - 1, s, lane);
+  }
+}
 template <class T, int DH>
 __global__ void __launch_bounds__(NW * 64) attn_bwd_dq_f32_k(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
                                                              const T* __restrict__ d_o, const float* __restrict__ lse,
@@ -155,25 +240,46 @@ __global__ void __launch_bounds__(NW * 64) attn_bwd_dq_f32_k(const T* __restrict
   load_row<T, DH>(d_o + base + (i64)qc * ld, half, 1.f, dof);
   const float L = lse[stat + qc], D = dvec[stat + qc];
   const int nt = ((causal ? min(S, q0 + 32) : S) + 31) / 32;
-  f32x16 acc[DT] = {};
-  for (int t = wv; t < nt; t += NW) {
-    const int kv0 = t * 32;
-    const i64 row = base + (i64)min(kv0 + (lane & 31), S - 1) * ld;
-    f32x16 s = scores<T, DH>(k + row, half, qf);
-    const f32x16 dp = scores<T, DH>(v + row, half, dof);
-#pragma unroll
-    for (int e = 0; e < 16; e++) {
-      const int kv = kv0 + elem_row(e, half);
-      s[e] = kv >= S || (causal && kv > myq) ? 0.f : __expf(s[e] - L) * (dp[e] - D);
-    }
-    accumulate<T, DH, DT>(acc, k + base, ld, kv0, S - 1, s, lane);
-  }
+  const int seen = causal ? min(S, myq + 1) : S;
+  f32x16 acc[DT];
+  dq_keys<T, DH, false>(k + base, v + base, ld, S, nt, wv, lane, seen, L, D, qf, dof, acc);
+  if (!finite<DT>(acc)) dq_keys<T, DH, true>(k + base, v + base, ld, S, nt, wv, opaque(lane), seen, L, D, qf, dof, acc);
   spill_tile<DH, DT>(sm + wv * 32 * (DH + 1), acc, lane);
   __syncthreads();
   store_sum<T, DH>(sm, dq + base, ld, q0, S, scale);
 }
 
-// dK, dV of 32 keys (a lane owns one): S = Q K^T, dP = dO V^T, dV^T += dO^T P, dK^T += Q^T dS
+// A wave's share of dK, dV of 32 keys (a lane owns one; its queries are first .. S - 1):
+// S = Q K^T, dP = dO V^T, dV^T += dO^T P, dK^T += Q^T dS
+template <class T, int DH, bool APART, int DT>
+__device__ __forceinline__ void dkv_queries(const T* q, const T* d_o, const float* lse, const float* dvec, i64 ld, int S, int t_lo,
+                                            int lane, int first, const float (&kf)[DH / 2], const float (&vf)[DH / 2],
+                                            f32x16 (&dka)[DT], f32x16 (&dva)[DT]) {
+  const int half = lane >> 5, nt = (S + 31) / 32;
+#pragma unroll
+  for (int i = 0; i < DT; i++) { dka[i] = f32x16{}; dva[i] = f32x16{}; }
+  for (int t = t_lo; t < nt; t += NW) {
+    const int q0 = t * 32;
+    const i64 row = (i64)min(q0 + (lane & 31), S - 1) * ld;
+    f32x16 s = scores<T, DH>(q + row, half, kf);
+    f32x16 dp = scores<T, DH>(d_o + row, half, vf);
+#pragma unroll
+    for (int e = 0; e < 16; e++) {
+      const int qq = q0 + elem_row(e, half), qs = min(qq, S - 1);
+      const bool masked = qq >= S || qq < first;
+      const float p = __expf(s[e] - lse[qs]);
+      dp[e] = masked ? 0.f : p * (dp[e] - dvec[qs]);
+      s[e] = masked ? 0.f : p;
+    }
+    if constexpr (APART) {
+      accumulate_apart<T, DH, DT>(dva, d_o, ld, q0, S - 1, s, lane, first, S);
+      accumulate_apart<T, DH, DT>(dka, q, ld, q0, S - 1, dp, lane, first, S);
+    } else {
+      accumulate<T, DH, DT>(dva, d_o, ld, q0, S - 1, s, lane);
+      accumulate<T, DH, DT>(dka, q, ld, q0, S - 1, dp, lane);
+    }
+  }
+}
 template <class T, int DH>
 __global__ void __launch_bounds__(NW * 64) attn_bwd_dkv_f32_k(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
                                                               const T* __restrict__ d_o, const float* __restrict__ lse,
@@ -187,24 +293,11 @@ __global__ void __launch_bounds__(NW * 64) attn_bwd_dkv_f32_k(const T* __restric
   float kf[DH / 2], vf[DH / 2];
   load_row<T, DH>(k + base + (i64)kc * ld, half, scale, kf);
   load_row<T, DH>(v + base + (i64)kc * ld, half, 1.f, vf);
-  const int nt = (S + 31) / 32;
-  f32x16 dka[DT] = {}, dva[DT] = {};
-  for (int t = (causal ? k0 / 32 : 0) + wv; t < nt; t += NW) {
-    const int q0 = t * 32;
-    const i64 row = base + (i64)min(q0 + (lane & 31), S - 1) * ld;
-    f32x16 s = scores<T, DH>(q + row, half, kf);
-    f32x16 dp = scores<T, DH>(d_o + row, half, vf);
-#pragma unroll
-    for (int e = 0; e < 16; e++) {
-      const int qq = q0 + elem_row(e, half), qs = min(qq, S - 1);
-      const bool masked = qq >= S || (causal && myk > qq);
-      const float p = __expf(s[e] - lse[stat + qs]);
-      dp[e] = masked ? 0.f : p * (dp[e] - dvec[stat + qs]);
-      s[e] = masked ? 0.f : p;
-    }
-    accumulate<T, DH, DT>(dva, d_o + base, ld, q0, S - 1, s, lane);
-    accumulate<T, DH, DT>(dka, q + base, ld, q0, S - 1, dp, lane);
-  }
+  const int first = causal ? myk : 0, t_lo = (causal ? k0 / 32 : 0) + wv;
+  f32x16 dka[DT], dva[DT];
+  dkv_queries<T, DH, false>(q + base, d_o + base, lse + stat, dvec + stat, ld, S, t_lo, lane, first, kf, vf, dka, dva);
+  if (!finite<DT>(dva) || !finite<DT>(dka))
+    dkv_queries<T, DH, true>(q + base, d_o + base, lse + stat, dvec + stat, ld, S, t_lo, opaque(lane), first, kf, vf, dka, dva);
   spill_tile<DH, DT>(sm + wv * 32 * (DH + 1), dka, lane);
   __syncthreads();
   store_sum<T, DH>(sm, dk + base, ld, k0, S, scale);

@@ -156,3 +156,59 @@ def test_flash_attention_paired_tiles(B, S, H):
 def test_float32_matrix_attention(dtype, dh, B, S, H):
     _attention_case(B, S, H, dh, True, 1, dtype)
     _attention_case(B, S, H, dh, False, 1, dtype)
+
+
+# (dtype, head width, mode, granularity): the float32 matrix kernels and the vector kernel keep a token that is not finite from
+# every token that does not see it; the bf16 kernels, which multiply whole tiles by zero probabilities, only from those outside
+# its block of 64
+@pytest.mark.parametrize("dtype,dh,mode,block", [(0, 16, 1, 1), (0, 32, 1, 1), (0, 64, 1, 1), (0, 128, 1, 1), (1, 16, 1, 1), (1, 32, 1, 1),
+                                                 (1, 64, 1, 1), (1, 128, 1, 1), (0, 80, 1, 1), (1, 80, 1, 1), (1, 128, 2, 64)])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), -float("inf")])
+# the middle of a tile, the last row of a ragged one, and the first row of one
+@pytest.mark.parametrize("t", [77, 130, 96])
+def test_attention_keeps_non_finite_tokens_apart(dtype, dh, mode, block, bad, t):
+    B, S, H = 1, 131, 2
+    rng = np.random.default_rng(dh + t)
+    up = lambda a: Hn.upload(a, "bf16" if dtype == 1 else "f32")
+    base = {n: _bf(rng, (B * S, H * dh), sc) for n, sc in (("q", 0.5), ("k", 0.5), ("v", 1.0), ("do", 1.0))}
+
+    def run(causal, **poison):
+        x = {n: a.copy() for n, a in base.items()}
+        for n, cells in poison.items():
+            for row, value in cells:
+                x[n][row, 3] = value
+        q, k, v, do = (up(x[n]) for n in ("q", "k", "v", "do"))
+        o, dq, dk, dv = (torch.zeros_like(q) for _ in range(4))
+        lse, dvec = (torch.zeros((B, H, S), dtype=torch.float32, device="cuda") for _ in range(2))
+        R.revffn_op_attention_fwd(dtype, mode, q, k, v, o, lse, B, S, H, dh, causal)
+        R.revffn_op_attention_bwd(dtype, mode, q, k, v, o, do, lse, dvec, dq, dk, dv, B, S, H, dh, causal)
+        torch.cuda.synchronize()
+        return [a.float().cpu().numpy() for a in (o, dq, dk, dv)]
+
+    o0, dq0, dk0, dv0 = run(True)
+    lo, hi = t // block * block, t // block * block + block
+    for n in ("k", "v"):                                   # a key (value): queries before it do not see it
+        o, dq, _, _ = run(True, **{n: [(t, bad)]})
+        assert np.array_equal(o[:lo], o0[:lo]) and np.array_equal(dq[:lo], dq0[:lo]), n
+    for n in ("q", "do"):                                  # a query: nothing but the keys up to it
+        o, dq, dk, dv = run(True, **{n: [(t, bad)]})
+        rest = np.arange(S) != t
+        assert np.array_equal(o[rest], o0[rest]) and np.array_equal(dq[rest], dq0[rest]), n
+        assert np.array_equal(dk[hi:], dk0[hi:]) and np.array_equal(dv[hi:], dv0[hi:]), n
+    # the values: a probability is positive, so a column of V with one infinity sums to it, with two opposite ones to no
+    # number, and the other columns keep their bits
+    cols = np.arange(H * dh) != 3
+    same = lambda a, b: np.array_equal(np.isnan(a), np.isnan(b)) and np.array_equal(a[~np.isnan(a)], b[~np.isnan(b)])
+    o, _, _, _ = run(True, v=[(t, bad)])
+    assert np.array_equal(o[:, cols], o0[:, cols]) and same(o[t:, 3], np.full(S - t, bad, np.float32))
+    o, _, _, _ = run(True, v=[(40, bad), (t, -bad)])
+    first = 40 // block * block
+    assert np.array_equal(o[:first], o0[:first]) and np.isnan(o[t:, 3]).all()
+    if block == 1:
+        assert same(o[40:t, 3], np.full(t - 40, bad, np.float32))
+    _, _, _, dv = run(True, do=[(t, bad)])
+    assert np.array_equal(dv[:, cols], dv0[:, cols]) and same(dv[:t + 1, 3], np.full(t + 1, bad, np.float32))
+    o1, _, _, _ = run(False)
+    o, _, _, dv = run(False, v=[(t, bad)], do=[(t, bad)])   # (every query sees every key, and the last row is read for the tail)
+    assert np.array_equal(o[:, cols], o1[:, cols]) and same(o[:, 3], np.full(S, bad, np.float32))
+    assert same(dv[:, 3], np.full(S, bad, np.float32))
