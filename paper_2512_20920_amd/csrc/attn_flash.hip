@@ -82,10 +82,10 @@ __device__ __forceinline__ void store_rows64(bf16* lds, int stride, const uint4 
 }
 
 // Which tile a workgroup takes (1-D grid of tiles x B x H workgroups; tile 0 has the most work when causal).  Heads are the
-// fastest index, so that an XCD (id & 7) keeps to H / 8 heads, and long tiles come first.  Two workgroups fit on a CU: where
-// the whole grid is resident at once, workgroups i and i + 256 share one, so the second 256 run from short to long (with
-// both halves long first the slowest CU has a long tile of either batch: 2 x 2048 tokens, 16 heads, forward, dQ, dK/dV 83,
-// 119, 154 -> 67, 100, 141 us).
+// fastest index, so that an XCD (id & 7) keeps to H / 8 heads, then batches, so that long tiles of all batches come first
+// (a 3-D grid with the batch slowest: 2 x 2048 tokens, 16 heads, forward and dQ 78 and 111 us, 65 and 98 like this).  Two
+// workgroups fit on a CU: where the whole grid is resident at once, workgroups i and i + 256 share one, so the second 256
+// run from short to long (forward, dQ, dK/dV: 65, 98, 137 -> 63, 95, 134).
 __device__ __forceinline__ void place(int H, int B, int tiles, int* t, int* hh, int* b) {
   const int rows = tiles * B, first = 256 / H;
   int row = (int)blockIdx.x / H;
@@ -424,14 +424,16 @@ __device__ __forceinline__ bf16x8 swz_cols(const unsigned char* tile, unsigned b
 // queries (with dO, lse, D) streamed in tiles of 64, starting at the diagonal when causal.
 //   S = Q K^T,  P = exp(S*scale - lse),  dP = dO V^T,  dS = P (dP - D) scale,
 //   dV^T += dO^T P,   dK^T += Q^T dS.
-// Accumulators and the wave's K and V take 192 registers, so the queries of a tile are worked on 32 at a time and the
-// next tile goes straight to LDS: that fits two workgroups on a CU, and one wave's exponentials run beside the other's
-// products.  8192 tokens,
-// 16 heads: 983 -> 622 us (one wave per SIMD, tiles staged through registers: 0.56 PFLOP/s executed), 2048 tokens x 2:
-// 137 -> 145, 512 x 4 (one workgroup per CU either way): 37 -> 38.
+// Tiles go straight to LDS.  Accumulators and the wave's K and V take 192 registers, so with the queries of a tile worked on
+// QB = 1 block of 32 at a time two workgroups fit on a CU, and one wave's exponentials run beside the other's products:
+// 8192 tokens, 16 heads: 885 -> 620 us (against one wave per SIMD, 64 queries at a time, tiles staged through registers).
+// A grid that has one workgroup per CU at most gains nothing from that; there QB = 2, 64 queries at a time, leaves the
+// compiler more to overlap inside the wave: 4 x 512 tokens, 16 heads: 39.1 -> 35.8 us, 2048: 115 -> 102, 3 x 333: 29.1 -> 27.0.
+// Both add the queries in the same order, so the results have the same bits.
 // ------------------------------------------------------------------------------------
 #define DKV_STAGE (2 * 64 * 256 + 2 * 256)      // Q, dO, lse, D
-__global__ void __launch_bounds__(256, 2) flash_bwd_dkv_k(const bf16* __restrict__ q, const bf16* __restrict__ k,
+template <int QB>
+__global__ void __launch_bounds__(256, QB == 1 ? 2 : 1) flash_bwd_dkv_k(const bf16* __restrict__ q, const bf16* __restrict__ k,
                                                        const bf16* __restrict__ v, const bf16* __restrict__ d_o,
                                                        const float* __restrict__ lse, const float* __restrict__ dvec,
                                                        bf16* __restrict__ dk, bf16* __restrict__ dv, int B, int S, int H,
@@ -491,44 +493,52 @@ __global__ void __launch_bounds__(256, 2) flash_bwd_dkv_k(const bf16* __restrict
     const float* cL = (const float*)(cQ + 32768);
     const float* cD = cL + 64;
 #pragma unroll 1
-    for (int j = 0; j < 2; j++) {
-      if (causal && q0 + j * 32 + 31 < kw) continue;           // no query of the block can see a key of this wave
-      f32x16 s, dp;
+    for (int j0 = 0; j0 < 2; j0 += QB) {
+      if (causal && q0 + (j0 + QB) * 32 - 1 < kw) continue;    // no query of the block can see a key of this wave
+      f32x16 s[QB], dp[QB];
 #pragma unroll
-      for (int e = 0; e < 16; e++) { s[e] = 0.f; dp[e] = 0.f; }
+      for (int j = 0; j < QB; j++)
 #pragma unroll
-      for (int kk = 0; kk < 8; kk++) {
-        const unsigned at = (unsigned)(j * 32 * 256) + (rbase ^ (unsigned)(kk * 32));
-        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(cQ + at), kf[kk], s, 0, 0, 0);
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(cO + at), vf[kk], dp, 0, 0, 0);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      const bool need_mask = causal && (q0 + j * 32 < kw + 31);      // some query of the block precedes some key of the wave
+        for (int e = 0; e < 16; e++) { s[j][e] = 0.f; dp[j][e] = 0.f; }
 #pragma unroll
-      for (int eb = 0; eb < 4; eb++) {
-        const int r0 = j * 32 + eb * 8 + g * 4;                 // 4 consecutive query rows inside the tile
-        const float4 l4 = *(const float4*)(cL + r0), d4 = *(const float4*)(cD + r0);
-        const float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dv4[4] = {d4.x, d4.y, d4.z, d4.w};
+      for (int kk = 0; kk < 8; kk++)
 #pragma unroll
-        for (int i = 0; i < 4; i++) {
-          const int e = eb * 4 + i;
-          float p = fast_exp2(s[e] * sl2 - lv[i] * LOG2E);
-          if (need_mask && mykv > q0 + r0 + i) p = 0.f;
-          dp[e] = p * (dp[e] - dv4[i]) * scale;                 // dS
-          s[e] = p;                                             // P
+        for (int j = 0; j < QB; j++) {
+          const unsigned at = (unsigned)((j0 + j) * 32 * 256) + (rbase ^ (unsigned)(kk * 32));
+          s[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(cQ + at), kf[kk], s[j], 0, 0, 0);
+          dp[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(cO + at), vf[kk], dp[j], 0, 0, 0);
         }
-      }
-      __builtin_amdgcn_sched_barrier(0);
+      if (QB == 1) __builtin_amdgcn_sched_barrier(0);
+      const bool need_mask = causal && (q0 + j0 * 32 < kw + 31);     // some query of the block precedes some key of the wave
 #pragma unroll
-      for (int c = 0; c < 2; c++) {
-        bf16x8 pf = acc_to_frag(s, c);
-        bf16x8 dsf = acc_to_frag(dp, c);
+      for (int j = 0; j < QB; j++)
 #pragma unroll
-        for (int dtile = 0; dtile < 4; dtile++) {
-          dvacc[dtile] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(swz_cols(cO, cbase, j * 32 + c * 16, dtile), pf, dvacc[dtile], 0, 0, 0);
-          dkacc[dtile] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(swz_cols(cQ, cbase, j * 32 + c * 16, dtile), dsf, dkacc[dtile], 0, 0, 0);
+        for (int eb = 0; eb < 4; eb++) {
+          const int r0 = (j0 + j) * 32 + eb * 8 + g * 4;        // 4 consecutive query rows inside the tile
+          const float4 l4 = *(const float4*)(cL + r0), d4 = *(const float4*)(cD + r0);
+          const float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dv4[4] = {d4.x, d4.y, d4.z, d4.w};
+#pragma unroll
+          for (int i = 0; i < 4; i++) {
+            const int e = eb * 4 + i;
+            float p = fast_exp2(s[j][e] * sl2 - lv[i] * LOG2E);
+            if (need_mask && mykv > q0 + r0 + i) p = 0.f;
+            dp[j][e] = p * (dp[j][e] - dv4[i]) * scale;         // dS
+            s[j][e] = p;                                        // P
+          }
         }
-      }
+      if (QB == 1) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < QB; j++)
+#pragma unroll
+        for (int c = 0; c < 2; c++) {
+          bf16x8 pf = acc_to_frag(s[j], c);
+          bf16x8 dsf = acc_to_frag(dp[j], c);
+#pragma unroll
+          for (int dtile = 0; dtile < 4; dtile++) {
+            dvacc[dtile] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(swz_cols(cO, cbase, (j0 + j) * 32 + c * 16, dtile), pf, dvacc[dtile], 0, 0, 0);
+            dkacc[dtile] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(swz_cols(cQ, cbase, (j0 + j) * 32 + c * 16, dtile), dsf, dkacc[dtile], 0, 0, 0);
+          }
+        }
     }
     // this wave's part of the next tile has landed, and its reads of this one have returned
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
@@ -565,13 +575,18 @@ int launch_attn_bwd_flash(const void* q, const void* k, const void* v, const voi
   static std::atomic<unsigned long long> attr_mask{0};
   if (attr_needed(attr_mask)) {
     (void)hipFuncSetAttribute((const void*)flash_bwd_dq_k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm1);
-    (void)hipFuncSetAttribute((const void*)flash_bwd_dkv_k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm2);
+    (void)hipFuncSetAttribute((const void*)flash_bwd_dkv_k<1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm2);
+    (void)hipFuncSetAttribute((const void*)flash_bwd_dkv_k<2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm2);
     attr_done(attr_mask);
   }
   dim3 grid((unsigned)((i64)H * cdiv(S, 128) * B));
   hipLaunchKernelGGL(flash_bwd_dq_k, grid, dim3(256), sm1, s, (const bf16*)q, (const bf16*)k, (const bf16*)v,
                      (const bf16*)d_o, lse, dvec, (bf16*)dq, B, S, H, causal, scale);
-  hipLaunchKernelGGL(flash_bwd_dkv_k, grid, dim3(256), sm2, s, (const bf16*)q, (const bf16*)k, (const bf16*)v,
-                     (const bf16*)d_o, lse, dvec, (bf16*)dk, (bf16*)dv, B, S, H, causal, scale);
+  if (grid.x <= 256)         // one workgroup on a CU at most (512 of them, 2 x 2048 tokens: QB = 1 135 us, QB = 2 157)
+    hipLaunchKernelGGL(flash_bwd_dkv_k<2>, grid, dim3(256), sm2, s, (const bf16*)q, (const bf16*)k, (const bf16*)v,
+                       (const bf16*)d_o, lse, dvec, (bf16*)dk, (bf16*)dv, B, S, H, causal, scale);
+  else
+    hipLaunchKernelGGL(flash_bwd_dkv_k<1>, grid, dim3(256), sm2, s, (const bf16*)q, (const bf16*)k, (const bf16*)v,
+                       (const bf16*)d_o, lse, dvec, (bf16*)dk, (bf16*)dv, B, S, H, causal, scale);
   return 0;
 }

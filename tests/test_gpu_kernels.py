@@ -150,6 +150,30 @@ def test_flash_attention_paired_tiles(B, S, H):
     _attention_case(B, S, H, 128, True, 2, 1)
 
 
+# more heads than 256 workgroups take, against the same heads a quarter at a time (one workgroup per CU): dK/dV works on 32
+# queries at a time in the one and 64 in the other, in the same order
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("B,S,H", [(2, 451, 48), (1, 129, 160), (8, 33, 40)])
+def test_flash_attention_gradients_do_not_depend_on_the_grid(B, S, H, causal):
+    rng = np.random.default_rng(S + H)
+    q, k, v, do = (Hn.upload(_bf(rng, (B * S, H * 128)), "bf16") for _ in range(4))
+
+    def run(h0, h1):
+        cut = lambda a: a[:, h0 * 128:h1 * 128].contiguous()
+        qh, kh, vh, doh = cut(q), cut(k), cut(v), cut(do)
+        o, dq, dk, dv = (torch.full_like(qh, float("nan")) for _ in range(4))
+        lse, dvec = (torch.empty((B, h1 - h0, S), dtype=torch.float32, device="cuda") for _ in range(2))
+        R.revffn_op_attention_fwd(1, 2, qh, kh, vh, o, lse, B, S, h1 - h0, 128, causal)
+        R.revffn_op_attention_bwd(1, 2, qh, kh, vh, o, doh, lse, dvec, dq, dk, dv, B, S, h1 - h0, 128, causal)
+        torch.cuda.synchronize()
+        return o, dq, dk, dv
+
+    whole, n = run(0, H), H // 4
+    for i in range(4):
+        for a, b in zip(whole, run(i * n, i * n + n)):
+            assert torch.isfinite(b).all() and torch.equal(a[:, i * n * 128:(i + 1) * n * 128], b)
+
+
 @pytest.mark.parametrize("dtype", [0, 1])
 # every head width; one row, a tail of one past a tile of 32, more tiles than the four waves of a workgroup
 @pytest.mark.parametrize("dh,B,S,H", [(16, 2, 33, 2), (32, 1, 1, 1), (64, 3, 131, 2), (64, 1, 300, 1), (128, 2, 97, 1)])
