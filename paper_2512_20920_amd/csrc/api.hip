@@ -673,7 +673,7 @@ int moe_acts(revffn_ctx* c, const revffn_weights* w, const void* y1, i64 ld, int
              const void* q_x1 = nullptr, i64 q_ld = 0, int qB = 0, int qS = 0, const unsigned char* q_skip = nullptr) {
   const revffn_config& f = c->cfg;
   const int d = f.d_model, h = d / 2, E = f.n_experts, k = f.top_k, I = f.d_expert, Is = f.d_shared, dt = c->dt;
-  const int N = T * k, E1 = E + (Is ? 1 : 0);
+  const int N = T * k;
   c->lastT = T;
   c->lastT_rows = N;
   c->bm_b = expert_rows_b(c, N, E);
@@ -807,7 +807,7 @@ int moe_merged(revffn_ctx* c, const revffn_weights* w, const revffn_merged* m, c
                i64 ldr, float sign, void* dst, i64 ldd, int T, hipStream_t s) {
   const revffn_config& f = c->cfg;
   const int d = f.d_model, h = d / 2, E = f.n_experts, k = f.top_k, I = f.d_expert, Is = f.d_shared, dt = c->dt;
-  const int N = T * k, E1 = E + (Is ? 1 : 0);
+  const int N = T * k;
   c->lastT = T;
   c->lastT_rows = N;
   c->bm_b = expert_rows_b(c, N, E);
@@ -878,7 +878,7 @@ int forward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const v
 int inverse_impl(revffn_ctx* c, const revffn_weights* w, const void* y1, const void* y2, void* x1, void* x2, int B,
                  int S, i64 ld, float* residual, hipStream_t s, const void** y1_kept, i64* ld_kept,
                  hipStream_t s_attn = nullptr, hipStream_t* s_attn_used = nullptr) {
-  const int T = B * S, h = c->cfg.d_model / 2, dt = c->dt;
+  const int T = B * S, h = c->cfg.d_model / 2;
   const bool sym = c->cfg.symmetric != 0;  // closed-form inverse: one evaluation of the branch at X2^, no iteration
   const bool conv = !sym && c->inv_tol > 0.f;      // stop on the residual instead of after a fixed count
   const int n = sym ? 1 : conv ? c->inv_max_iters : c->cfg.n_inv_iters;

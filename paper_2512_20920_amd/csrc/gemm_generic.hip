@@ -1,11 +1,11 @@
 // GEMM with float32 products on the matrix cores (v_mfma_f32_32x32x2_f32: every operand element enters as float32,
 // bf16 ones exactly), for any shape and any of the operand layouts of GemmArgs.  It serves the float32 configuration,
-// whose tolerance needs float32 products, the three GEMMs around the router (logits, folded router matrix, router
-// weight gradient), and every bf16 problem whose shape the bf16 kernels do not take.
+// whose tolerance needs float32 products, two GEMMs around the router (folded router matrix, router weight gradient), and
+// every bf16 problem whose shape the bf16 kernels do not take.
 //
 // These problems are small (one to a few hundred 32x32 tiles), so what bounds them is latency, not the matrix pipe: a
 // workgroup owns one tile of 32 TM x 32 TN outputs and cuts the contraction among its waves (wave w takes the chunks of
-// 32 k's w, w + NW, ...), operands go from memory (L2) straight into the operand registers, two chunks ahead, and the
+// 32 k's w, w + NW, ...), operands go from memory (L2) straight into the operand registers, one chunk ahead, and the
 // waves' partial tiles are added in wave order through LDS.  No LDS staging: inside a workgroup no two waves want the
 // same element.  At T = 400, d = 512 (float32) a GEMM of 400 x 512 x 512 takes 4 us where the LDS-tiled vector kernel
 // that it replaced took 64 us (56 workgroups, one dependent load -> LDS -> barrier chain per 16 k's).
@@ -163,8 +163,6 @@ int launch_gemm_generic(const GemmArgs& g, GemmTypes t, hipStream_t s) {
     case 15: go_types<bf16, bf16, bf16, bf16>(g, s); break;               // bf16 everything
     case 13: go_types<bf16, bf16, float, bf16>(g, s); break;              // bf16 in, fp32 out (router fold)
     case 7: go_types<float, bf16, bf16, bf16>(g, s); break;               // fp32 A (router logit gradients), bf16 B/C
-    case 9: go_types<bf16, float, float, bf16>(g, s); break;              // bf16 A, fp32 B/C (router logits)
-    case 1: go_types<float, float, float, bf16>(g, s); break;             // router logits from float32 residual streams
     case 5: go_types<float, bf16, float, bf16>(g, s); break;              // router weight gradient in float32
     default: return -1;
   }

@@ -138,8 +138,7 @@ inline int dense_grid_x(int xcd_m, int tiles_m, int tiles_n) {
   return 8 * ((tiles_m + xcd_m - 1) / xcd_m) * ((tiles_n + 8 / xcd_m - 1) / (8 / xcd_m));
 }
 
-// element types of A, B, C: 0 = f32, 1 = bf16.  bias and resid have C's... no: the
-// storage dtype `dt` of the call (bias/resid are streams or weights).
+// element types of A, B, C, and of bias, residual and column scale (the storage type of streams and weights): 0 = f32, 1 = bf16
 struct GemmTypes { int ta, tb, tc, tside; };
 
 int launch_gemm_generic(const GemmArgs& g, GemmTypes t, hipStream_t s);
