@@ -8,7 +8,7 @@
 // already in the operand layout of the second product.  The operand that has to be read
 // against its storage order (V^T, K^T, Q^T, dO^T) comes from LDS through the transposing
 // read ds_read_b64_tr_b16.
-#include "kernels.h"
+#include "lds_load.h"
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
@@ -56,7 +56,6 @@ __device__ __forceinline__ bf16x8 acc_to_frag(const f32x16& a, int c) {
 // (batch, head) up to the last byte of row S - 1, so a row past the end is out of range and reads as zeros with no
 // branch and no traffic, the address is one 32-bit offset per lane, and the loads of a tile issue back to back.
 // (Predicated pointer loads put a branch and a full wait after every load and spilled their 64-bit addresses.)
-typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 struct RowSlice { __amdgpu_buffer_rsrc_t rs; unsigned ldb; };    // ldb = row stride in bytes
 __device__ __forceinline__ RowSlice row_slice(const bf16* base, i64 ld, int S) {
   RowSlice r;
@@ -69,7 +68,7 @@ __device__ __forceinline__ void load_rows64(const RowSlice& sl, int row0, uint4 
   for (int i = 0; i < 4; i++) {
     const int c = threadIdx.x + 256 * i;
     const unsigned voff = (unsigned)(row0 + (c >> 4)) * sl.ldb + (unsigned)(c & 15) * 16u;
-    const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(sl.rs, (int)voff, 0, 0);
+    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(sl.rs, (int)voff, 0, 0);
     r[i] = make_uint4(v[0], v[1], v[2], v[3]);
   }
 }
@@ -390,21 +389,18 @@ __global__ void __launch_bounds__(256, 2) flash_bwd_dq_k(const bf16* __restrict_
 // rows of a transposing read differ in the upper two bits, i.e. in which quarter of the banks their 64 bytes fall.
 // ------------------------------------------------------------------------------------
 __device__ __forceinline__ int swz(int r) { return ((r & 3) << 2) | ((r >> 2) & 3); }
-typedef __attribute__((address_space(3))) unsigned char lds_u8;
 // 16 rows (4 wave-loads) of the slice, from row0 on, to LDS at dst
 __device__ __forceinline__ void load_rows16_lds(const RowSlice& sl, int row0, unsigned dst, int lane) {
 #pragma unroll
   for (int i = 0; i < 4; i++) {
     const int r = i * 4 + (lane >> 4);
     const unsigned voff = (unsigned)(row0 + r) * sl.ldb + (unsigned)((lane & 15) ^ swz(r)) * 16u;
-    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                 :: "s"(__builtin_amdgcn_readfirstlane(dst + i * 1024u)), "v"(voff), "s"(sl.rs) : "memory", "m0");
+    load_lds_b128(sl.rs, __builtin_amdgcn_readfirstlane(dst + i * 1024u), voff);
   }
 }
 // 64 floats
 __device__ __forceinline__ void load_stats64_lds(__amdgpu_buffer_rsrc_t rs, int row0, unsigned dst, int lane) {
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, 0 offen lds"
-               :: "s"(__builtin_amdgcn_readfirstlane(dst)), "v"((unsigned)(row0 + lane) * 4u), "s"(rs) : "memory", "m0");
+  load_lds_b32(rs, __builtin_amdgcn_readfirstlane(dst), (unsigned)(row0 + lane) * 4u);
 }
 // per-lane byte offsets: frag_rows (k-step kk: ^ kk * 32), frag_cols_tr (column block: ^ dtile * 64)
 __device__ __forceinline__ unsigned swz_row_base(int lane) { return (unsigned)(lane & 31) * 256u + (unsigned)((lane >> 5) ^ swz(lane & 15)) * 16u; }
@@ -472,7 +468,7 @@ __global__ void __launch_bounds__(256, QB == 1 ? 2 : 1) flash_bwd_dkv_k(const bf
   const RowSlice slQ = row_slice(q + boff, ld, S), slO = row_slice(d_o + boff, ld, S);
   const __amdgpu_buffer_rsrc_t rsL = __builtin_amdgcn_make_buffer_rsrc((void*)(lse + soff), (short)0, S * 4, 0x00020000);
   const __amdgpu_buffer_rsrc_t rsD = __builtin_amdgcn_make_buffer_rsrc((void*)(dvec + soff), (short)0, S * 4, 0x00020000);
-  const unsigned lds0 = (unsigned)(unsigned long long)(lds_u8*)smem_raw;
+  const unsigned lds0 = lds_address(smem_raw);
   // rows past the end are zeros throughout: whatever their probabilities, they add Q = dO = 0
   auto issue = [&](int t, int stage) {
     const unsigned dst = lds0 + (unsigned)stage * DKV_STAGE;
@@ -483,7 +479,7 @@ __global__ void __launch_bounds__(256, QB == 1 ? 2 : 1) flash_bwd_dkv_k(const bf
   };
   const unsigned rbase = swz_row_base(lane), cbase = swz_col_base(lane);
   issue(t_lo, 0);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  wait_vmcnt<0>();
   __syncthreads();
   for (int t = t_lo; t < nt; t++) {
     const int cur = (t - t_lo) & 1, q0 = t * BKV;

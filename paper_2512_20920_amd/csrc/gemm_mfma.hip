@@ -20,7 +20,7 @@
 //    come from the transposing read ds_read_b64_tr_b16, whose lane mapping is: inside each block
 //    of 16 lanes, lane j receives element (j & 3) of the 8-byte words addressed by lanes
 //    4*e + (j >> 2), e = 0..3.
-#include "kernels.h"
+#include "lds_load.h"
 #include <math.h>
 #include <stdlib.h>
 
@@ -29,39 +29,11 @@ typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(8))) short s16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 
-// Operands are read through raw buffer descriptors with num_records = 2 GiB: a load whose byte
-// offset is at or past that returns zeros (into LDS here) without traffic.  Every matrix handed
-// to this kernel spans less than 2 GiB from its base (checked on the host), so the offset OOB
-// stands for "outside the k range / past the last row" without a branch.
-#define BUF_RECORDS 0x80000000u
-#define OOB 0x80000000u
+// Every matrix handed to this kernel spans less than 2 GiB from its base (checked on the host): the offset OOB stands for
+// "outside the k range / past the last row".
 #define BK 64
 #define PHASED 0          // (as the number of LDS stages: the 256x256 tile in phases)
-
-// one wave-load: 64 lanes x 16 bytes from desc + voff (per lane) to LDS at lds_addr + 16 * lane
-__device__ __forceinline__ void load_lds_b128(u32x4 desc, unsigned lds_addr, unsigned voff) {
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-               :: "s"(lds_addr), "v"(voff), "s"(desc) : "memory", "m0");
-}
-// the same with a wave-uniform byte offset added
-__device__ __forceinline__ void load_lds_b128_s(u32x4 desc, unsigned lds_addr, unsigned voff, unsigned soff) {
-  soff = __builtin_amdgcn_readfirstlane(soff);
-  asm("" : "+s"(soff));                             // (a literal is no offset operand)
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               :: "s"(lds_addr), "v"(voff), "s"(desc), "s"(soff) : "memory", "m0");
-}
-template <int N> __device__ __forceinline__ void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
-
-__device__ __forceinline__ u32x4 make_desc(const void* p) {
-  // (operand bases are the same for every lane; saying so keeps the descriptor in scalar registers whatever the
-  // compiler can prove about how the base was picked)
-  const unsigned long long a = (unsigned long long)p;
-  u32x4 d = {(unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)a),
-             (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(a >> 32)), BUF_RECORDS, 0x00020000u};
-  return d;
-}
 
 // Where the 16-byte chunk at LDS position `pos` (in chunks, lane order of the wave-loads) of one operand tile
 // comes from: byte offset of that chunk at k-tile 0 relative to the operand base, and the number of k-tiles for
@@ -387,7 +359,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const bf16* A, cons
       chunk_source_gate_up((j - ALOADS) * 64 + lane, bx * (BN / 2), g.act_half, ldb_b, k0, krange, &base[i], &ntile[i]);
     else chunk_source<BT, BN, KB>((j - ALOADS) * 64 + lane, n0, g.N, ldb_b, k0, krange, nullptr, 1, &base[i], &ntile[i]);
   }
-  const unsigned lds0 = (unsigned)(unsigned long long)(__attribute__((address_space(3))) unsigned char*)smem;
+  const unsigned lds0 = lds_address(smem);
   const unsigned lw = __builtin_amdgcn_readfirstlane(lds0 + (unsigned)wv * LPW * 1024u);
   // The k-tiles are walked from a start that differs from workgroup to workgroup (and wraps around): workgroups
   // that stream weights from HBM otherwise all ask for the same address bits above the cache-line offset at the
@@ -513,7 +485,7 @@ __device__ __forceinline__ void gemm_tile_phased(const GemmArgs& g, const bf16* 
       chunk_source<BT, 128>(pos, r0, lim, ldb_b, k0, 1 << 30, nullptr, 1, &base[2 + h][i], &in);
       if (!in) base[2 + h][i] = OOB;
     }
-  const unsigned lds0 = (unsigned)(unsigned long long)(__attribute__((address_space(3))) unsigned char*)smem;
+  const unsigned lds0 = lds_address(smem);
   const unsigned lw = __builtin_amdgcn_readfirstlane(lds0 + (unsigned)wv * 2048u);
   const int kfull = krange / BK;                     // whole k-tiles
   auto issue = [&](int kt, int hf) {                 // this wave's part of half tile hf (A0 A1 B0 B1) of k-tile kt

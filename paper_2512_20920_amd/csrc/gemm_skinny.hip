@@ -12,30 +12,15 @@
 //  * B stored k x columns: 64-byte rows, transposing reads (rows 0-3 and 8-11 of a k-step cover all banks twice, the
 //    least that 512 bytes can take).
 // Workgroups of one XCD take a run of column tiles with the row tile fastest, so a weight line enters one L2 only.
-#include "kernels.h"
+#include "lds_load.h"
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(8))) short s16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
-#define OOB 0x80000000u              // byte offset past every descriptor's end: reads as zeros without traffic
-
 #define NW 8
-
-__device__ __forceinline__ u32x4 make_desc(const void* p) {
-  const unsigned long long a = (unsigned long long)p;
-  u32x4 d = {(unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)a),
-             (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(a >> 32)), OOB, 0x00020000u};
-  return d;
-}
-// one wave-load: 64 lanes x 16 bytes from desc + voff (per lane) to LDS at lds_addr + 16 * lane
-__device__ __forceinline__ void load_lds(u32x4 desc, unsigned lds_addr, unsigned voff) {
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-               :: "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(voff), "s"(desc) : "memory", "m0");
-}
 
 // NB = 32-column blocks of a tile: 2 with the SwiGLU epilogue (gate columns and the up columns of the same indices);
 // NS = pieces of a wave in flight
@@ -79,20 +64,20 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
     }
   }
   const unsigned my = (unsigned)wv * NS * STAGE;     // this wave's part of LDS
-  const unsigned lds0 = (unsigned)(unsigned long long)(__attribute__((address_space(3))) unsigned char*)smem + my;
+  const unsigned lds0 = lds_address(smem) + my;
   auto issue = [&](int p, int stage) {
     const int k0 = p * 64;
     const unsigned dst = lds0 + (unsigned)stage * STAGE;
 #pragma unroll
     for (int i = 0; i < 4; i++) {
       const bool in = k0 + akc[i] < g.K;
-      load_lds(da, dst + i * 1024u, in ? aoff[i] + (unsigned)k0 * 2u : OOB);
+      load_lds_b128(da, __builtin_amdgcn_readfirstlane(dst + i * 1024u), in ? aoff[i] + (unsigned)k0 * 2u : OOB);
       if constexpr (!BT) {
 #pragma unroll
-        for (int j = 0; j < NB; j++) load_lds(db, dst + (1 + j) * OPD + i * 1024u, in ? boff[j][i] + (unsigned)k0 * 2u : OOB);
+        for (int j = 0; j < NB; j++) load_lds_b128(db, __builtin_amdgcn_readfirstlane(dst + (1 + j) * OPD + i * 1024u), in ? boff[j][i] + (unsigned)k0 * 2u : OOB);
       } else {
         const bool kin = k0 + i * 16 + (lane >> 2) < g.K && boff[0][i] != OOB;
-        load_lds(db, dst + OPD + i * 1024u, kin ? boff[0][i] + (unsigned)k0 * ldb_b : OOB);
+        load_lds_b128(db, __builtin_amdgcn_readfirstlane(dst + OPD + i * 1024u), kin ? boff[0][i] + (unsigned)k0 * ldb_b : OOB);
       }
     }
   };
@@ -109,7 +94,7 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
   for (int st = 0; st < NS; st++) issue(wv + st * NW, st);          // (pieces past the end load zeros, to keep the count)
   int st = 0;
   for (int p = wv; p < np; p += NW) {
-    asm volatile("s_waitcnt vmcnt(%0)" :: "n"((NS - 1) * 4 * (1 + NB)) : "memory");
+    wait_vmcnt<(NS - 1) * 4 * (1 + NB)>();
     const unsigned char* t = smem + my + (unsigned)st * STAGE;
     bf16x8 fa[4], fb[NB][4];
 #pragma unroll
@@ -135,7 +120,7 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
 #pragma unroll
       for (int j = 0; j < NB; j++) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[s], fb[j][s], acc[j], 0, 0, 0);
   }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                  // the zero-filled loads past the end
+  wait_vmcnt<0>();                                                  // the zero-filled loads past the end
   __syncthreads();                                   // the partial tiles overlay the stages
   float* part = (float*)smem;
 #pragma unroll
