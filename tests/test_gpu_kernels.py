@@ -86,7 +86,7 @@ def test_few_rows_gemm(layout, M, N, K):
         assert torch.isnan(cd[M]).all()                       # nothing past the last row
 
 
-def _attention_case(B, S, H, dh, causal, mode, dtype):
+def _attention_case(B, S, H, dh, causal, mode, dtype, offset=0):
     rng = np.random.default_rng(S * 31 + H + (7 if causal else 0))
     rnd = (lambda s, sc=1.0: _bf(rng, s, sc)) if dtype == 1 else \
           (lambda s, sc=1.0: (sc * rng.standard_normal(s)).astype(np.float32).astype(np.float64))
@@ -100,7 +100,10 @@ def _attention_case(B, S, H, dh, causal, mode, dtype):
         o_ref, P = O.attention_core(r4(q), r4(k), r4(v), causal)
         dq_ref, dk_ref, dv_ref = O.attention_core_backward(r4(do), r4(q), r4(k), r4(v), P)
     sname = "bf16" if dtype == 1 else "f32"
-    qd, kd, vd, dod = (Hn.upload(a, sname) for a in (q, k, v, do))
+    def put(a):                  # a tensor that starts `offset` elements into its allocation
+        t = Hn.upload(a, sname)
+        return torch.cat([t.new_zeros(offset), t.flatten()])[offset:].view(t.shape)
+    qd, kd, vd, dod = (put(a) for a in (q, k, v, do))
     od = torch.full_like(qd, float("nan"))
     lse = torch.full((B, H, S), float("nan"), dtype=torch.float32, device="cuda")
     R.revffn_op_attention_fwd(dtype, mode, qd, kd, vd, od, lse, B, S, H, dh, causal)
@@ -141,6 +144,14 @@ def test_flash_attention_ragged_long_sequence():
 def test_generic_attention(dtype, dh):
     _attention_case(2, 70, 3, dh, True, 1, dtype)
     _attention_case(1, 33, 2, dh, False, 1, dtype)
+
+
+# what neither matrix-core form takes: other head widths, up to several columns per thread, and rows that are not aligned to
+# four elements
+@pytest.mark.parametrize("dtype,dh,offset", [(1, 80, 0), (0, 6, 0), (1, 300, 0)] + [(t, w, 1) for t in (0, 1) for w in (16, 32, 64, 128)])
+def test_vector_attention(dtype, dh, offset):
+    _attention_case(2, 70, 3, dh, True, 1, dtype, offset)
+    _attention_case(1, 261, 1, dh, False, 1, dtype, offset)
 
 
 # more workgroups than CUs and no more than two for each: the second part of the grid runs in reverse (48 and 100 heads: a

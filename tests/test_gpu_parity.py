@@ -143,6 +143,18 @@ def test_block_parity_drawn_geometries(wl):
     print(wl.name, "ties", rep, {k: f"{v:.2e}" for k, v in errs.items()})
 
 
+# The dense layers' weight gradients are one launch, on the tile whose rounds over 256 CUs cost least for all of them
+# together: widths that give 216 tiles of 128x128 (one round of those), 172 of 256x128 (one round, against two of 128x128)
+# and 216 of 256x256 (in phases), each with tiles that end outside the results; 70 tokens: a second, partly filled k-tile.
+@pytest.mark.parametrize("d", [656, 784, 1296])
+@pytest.mark.parametrize("fp32_grads", [False, True])
+def test_batched_weight_gradients_tile_shapes(d, fp32_grads):
+    wl = synth.Workload(f"wgrad_d{d}", d, d // 16, 16, 3, 2, 40, 0, 1, 70, "bf16", gain_jitter=0.02, seed=d)
+    case = Case(wl, fp32_grads=fp32_grads)
+    y1d, _ = case.forward()
+    _backward_checks(case, case.up(case.x1), case.up(case.x2), y1d, TOL["bf16"])
+
+
 @pytest.mark.parametrize("flags", [dict(causal=False, use_rope=False, norm_topk_prob=True),
                                    dict(causal=True, use_rope=True, norm_topk_prob=True)])
 @pytest.mark.parametrize("name", ["mid_f32", "mid_bf16"])
