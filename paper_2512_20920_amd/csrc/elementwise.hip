@@ -256,9 +256,14 @@ __global__ void __launch_bounds__(256) colsum_k(ColsumBatch q, float* __restrict
 #pragma unroll
   for (int j = 0; j < 8; j++) v += red[j][threadIdx.x];
   if (chunks > 1) {
-    // Agent scope: the other chunks' workgroups may run on other XCDs.  The stores go through to memory by themselves,
-    // so waiting for them is all the ticket needs; a release fence would write the whole L2 back in every workgroup
-    // (151 us instead of 9 at T = 2048).
+    // Agent scope: the other chunks' workgroups may run on other XCDs.  What orders the sums before the ticket is not the
+    // memory model, which would ask for a release here and an acquire below, but this chip: an agent-scope store is written
+    // through to where every XCD reads it, s_waitcnt vmcnt(0) returns when that has happened, the barrier makes it so for
+    // all four waves, and agent-scope loads do not read the caches of their own XCD.  (The release writes the whole L2
+    // back in every workgroup: 151 us instead of 9 at T = 2048.)
+#if defined(__HIP_DEVICE_COMPILE__) && !defined(__gfx950__)
+#error "the ticket below rests on how gfx950 carries out agent-scope stores"
+#endif
     __hip_atomic_store(partial + (i64)blockIdx.y * 256 + threadIdx.x, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();

@@ -1,6 +1,6 @@
 """GPU parity at the full workload sizes, in the launch configuration bench.py times
-(default kernel mode, bf16, Qwen1.5-MoE-A2.7B layer shape).  The host cores of the GPU machine
-run the fp64 oracle on the whole batch, so the comparison is element by element here too."""
+(default kernel mode, bf16, Qwen1.5-MoE-A2.7B layer shape).  The host cores run
+the fp64 oracle on the whole batch, so the comparison is element by element here too."""
 import dataclasses
 import time
 
