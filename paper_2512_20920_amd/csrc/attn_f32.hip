@@ -9,8 +9,8 @@
 // A workgroup is 32 queries (keys) of one head and its 4 waves share the keys (queries) out, tile w, w + 4, ..; partial
 // results meet in LDS in wave order.  These are short sequences of few heads, and what bounds them is one wave's chain:
 // one workgroup per query on the vector units walked the keys twice, one fused multiply-add per loaded element.
-// Forward, dQ, dK/dV: 251 tokens, 3 x 4 heads of 64, bfloat16 storage: 55, 51, 56 -> 12, 14, 23 us; 700 tokens, 4 heads of
-// 128, float32: 262, 225, 232 -> 42, 65, 88.
+// Forward, dQ, dK/dV: 251 tokens, 3 x 4 heads of 64, bfloat16 storage: 55, 51, 56 -> 13, 14, 22 us; 700 tokens, 4 heads of
+// 128, float32: 262, 225, 232 -> 41, 61, 87.
 #include "kernels.h"
 
 typedef __attribute__((ext_vector_type(16))) float f32x16;
@@ -56,7 +56,7 @@ __device__ __forceinline__ void accumulate(f32x16 (&acc)[DT], const T* x, i64 ld
     for (int i = 0; i < DT; i++) v[e][i] = row[i * 32];
   }
   // all loads in flight before the first product: left to itself the compiler takes a few at a time as soon as registers
-  // are short (128-wide dK/dV at 700 tokens 137 us, 88 like this)
+  // are short (128-wide dK/dV at 700 tokens 136 us, 87 like this)
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int e = 0; e < 16; e++)
@@ -99,14 +99,15 @@ __device__ __forceinline__ void accumulate_apart(f32x16 (&acc)[DT], const T* x, 
 // On tiles that some lanes see only in part the matrix instruction multiplies the rest by their zero probabilities, and a
 // value that is not finite would reach queries before it (keys after it).  That always shows in the result, so the tiles
 // are multiplied plainly first (looking at every element on the way: 128-wide forward 46 -> 149 us at 700 tokens) and a
-// wave whose result is not finite starts over, keeping such values apart on those tiles.
+// wave whose result is not finite starts over, keeping such values apart on those tiles.  It then has accumulators of its
+// own: as a second value of the first ones they cost 1-3 us of every call in register moves.
 template <int DT> __device__ __forceinline__ bool finite(const f32x16 (&acc)[DT]) {
-  bool all = true;
+  float z[4] = {0.f, 0.f, 0.f, 0.f};                 // (a value that is not finite times zero is no number)
 #pragma unroll
   for (int i = 0; i < DT; i++)
 #pragma unroll
-    for (int e = 0; e < 16; e++) all &= __builtin_fabsf(acc[i][e]) < INFINITY;
-  return __all(all);
+    for (int e = 0; e < 16; e++) z[e & 3] = __builtin_fmaf(acc[i][e], 0.f, z[e & 3]);
+  return __all((z[0] + z[1]) + (z[2] + z[3]) == 0.f);
 }
 // the lane for the second pass, so that nothing of the first one is kept in registers for it
 __device__ __forceinline__ int opaque(int lane) { asm volatile("" : "+v"(lane)); return lane; }
@@ -184,8 +185,13 @@ __global__ void __launch_bounds__(NW * 64) attn_fwd_f32_k(const T* __restrict__ 
   f32x16 acc[DT];
   float m, l;
   fwd_keys<T, DH, false>(k + base, v + base, ld, S, nt, wv, lane, seen, qf, acc, m, l);
-  if (!finite<DT>(acc)) fwd_keys<T, DH, true>(k + base, v + base, ld, S, nt, wv, opaque(lane), seen, qf, acc, m, l);
-  spill_tile<DH, DT>(sm + wv * 32 * (DH + 1), acc, lane);
+  float* mine = sm + wv * 32 * (DH + 1);
+  if (__builtin_expect(finite<DT>(acc), 1)) spill_tile<DH, DT>(mine, acc, lane);
+  else {
+    f32x16 again[DT];
+    fwd_keys<T, DH, true>(k + base, v + base, ld, S, nt, wv, opaque(lane), seen, qf, again, m, l);
+    spill_tile<DH, DT>(mine, again, lane);
+  }
   if (half == 0) { sM[wv * 32 + lane] = m; sL[wv * 32 + lane] = l; }
   __syncthreads();
   for (int i = threadIdx.x; i < 32 * DH; i += NW * 64) {
@@ -243,8 +249,13 @@ __global__ void __launch_bounds__(NW * 64) attn_bwd_dq_f32_k(const T* __restrict
   const int seen = causal ? min(S, myq + 1) : S;
   f32x16 acc[DT];
   dq_keys<T, DH, false>(k + base, v + base, ld, S, nt, wv, lane, seen, L, D, qf, dof, acc);
-  if (!finite<DT>(acc)) dq_keys<T, DH, true>(k + base, v + base, ld, S, nt, wv, opaque(lane), seen, L, D, qf, dof, acc);
-  spill_tile<DH, DT>(sm + wv * 32 * (DH + 1), acc, lane);
+  float* mine = sm + wv * 32 * (DH + 1);
+  if (__builtin_expect(finite<DT>(acc), 1)) spill_tile<DH, DT>(mine, acc, lane);
+  else {
+    f32x16 again[DT];
+    dq_keys<T, DH, true>(k + base, v + base, ld, S, nt, wv, opaque(lane), seen, L, D, qf, dof, again);
+    spill_tile<DH, DT>(mine, again, lane);
+  }
   __syncthreads();
   store_sum<T, DH>(sm, dq + base, ld, q0, S, scale);
 }
@@ -296,13 +307,22 @@ __global__ void __launch_bounds__(NW * 64) attn_bwd_dkv_f32_k(const T* __restric
   const int first = causal ? myk : 0, t_lo = (causal ? k0 / 32 : 0) + wv;
   f32x16 dka[DT], dva[DT];
   dkv_queries<T, DH, false>(q + base, d_o + base, lse + stat, dvec + stat, ld, S, t_lo, lane, first, kf, vf, dka, dva);
-  if (!finite<DT>(dva) || !finite<DT>(dka))
-    dkv_queries<T, DH, true>(q + base, d_o + base, lse + stat, dvec + stat, ld, S, t_lo, opaque(lane), first, kf, vf, dka, dva);
-  spill_tile<DH, DT>(sm + wv * 32 * (DH + 1), dka, lane);
+  const bool as_is = finite<DT>(dva) && finite<DT>(dka);
+  float* mine = sm + wv * 32 * (DH + 1);
+  auto spill = [&](const f32x16 (&acc)[DT], bool keys) __attribute__((always_inline)) {
+    if (__builtin_expect(as_is, 1)) spill_tile<DH, DT>(mine, acc, lane);
+    else {
+      f32x16 dka2[DT], dva2[DT];                     // (each time, so that the usual way holds no registers for it)
+      dkv_queries<T, DH, true>(q + base, d_o + base, lse + stat, dvec + stat, ld, S, t_lo, opaque(lane), first, kf, vf, dka2, dva2);
+      if (keys) spill_tile<DH, DT>(mine, dka2, lane);
+      else spill_tile<DH, DT>(mine, dva2, lane);
+    }
+  };
+  spill(dka, true);
   __syncthreads();
   store_sum<T, DH>(sm, dk + base, ld, k0, S, scale);
   __syncthreads();
-  spill_tile<DH, DT>(sm + wv * 32 * (DH + 1), dva, lane);
+  spill(dva, false);
   __syncthreads();
   store_sum<T, DH>(sm, dv + base, ld, k0, S, 1.f);
 }
