@@ -517,7 +517,7 @@ int run_wgrad_batch(revffn_ctx* c, const GemmArgs* subs, int n, bool bulk, hipSt
 // chip overlap: the shared expert next to the routed experts, the rebuilding of X1^ and the attention half's
 // recomputation next to the MoE half's backward pass, the MoE half's weight gradients next to the attention half's
 // backward pass.  Recording an event and making another stream wait for it costs the host 13 us (a launch: 3 us), so
-// there are about ten such edges in a training step, between long branches only, and none at all in a call too small
+// there are sixteen such edges in a training step, between long branches only, and none at all in a call too small
 // for them to pay: below about 60 us of GPU time per evaluation of the block the host would be what the GPU waits for
 // (a step of a 512-wide block of 400 tokens: 909 us with 45 edges, 609 us on one stream).
 bool fork_pays(const revffn_ctx* c, i64 T) {

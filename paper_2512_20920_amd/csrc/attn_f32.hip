@@ -99,8 +99,8 @@ __device__ __forceinline__ void accumulate_apart(f32x16 (&acc)[DT], const T* x, 
 // On tiles that some lanes see only in part the matrix instruction multiplies the rest by their zero probabilities, and a
 // value that is not finite would reach queries before it (keys after it).  That always shows in the result, so the tiles
 // are multiplied plainly first (looking at every element on the way: 128-wide forward 46 -> 149 us at 700 tokens) and a
-// wave whose result is not finite starts over, keeping such values apart on those tiles.  It then has accumulators of its
-// own: as a second value of the first ones they cost 1-3 us of every call in register moves.
+// wave whose result is not finite starts over, keeping such values apart.  It then has accumulators of its own: as a second
+// value of the first ones they cost a short sequence 1-2 us of register moves in every call.
 template <int DT> __device__ __forceinline__ bool finite(const f32x16 (&acc)[DT]) {
   float z[4] = {0.f, 0.f, 0.f, 0.f};                 // (a value that is not finite times zero is no number)
 #pragma unroll
