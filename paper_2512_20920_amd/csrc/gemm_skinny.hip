@@ -20,11 +20,9 @@ typedef __attribute__((ext_vector_type(8))) short s16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
-#define NW 8
-
 // NB = 32-column blocks of a tile: 2 with the SwiGLU epilogue (gate columns and the up columns of the same indices);
-// NS = pieces of a wave in flight
-template <bool BT, class TC, int NB, int NS>
+// NW = waves; NS = pieces of a wave in flight
+template <bool BT, class TC, int NB, int NW, int NS>
 __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
   constexpr int RS = NB * 32 + 8;                    // row stride of a partial tile (floats): rows 4 apart are 32 banks apart
   constexpr unsigned OPD = 64 * 32 * 2, STAGE = (1 + NB) * OPD;     // LDS bytes of a piece: A, then B
@@ -160,7 +158,7 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
   }
 }
 
-template <bool BT, class TC, int NB, int NS>
+template <bool BT, class TC, int NB, int NW, int NS>
 static void go(GemmArgs g, hipStream_t s) {
   g.tiles_m = cdiv(g.M, 32);
   g.tiles_n = cdiv(NB == 2 ? g.act_half : g.N, 32);
@@ -169,14 +167,23 @@ static void go(GemmArgs g, hipStream_t s) {
   static_assert(smem <= 160 * 1024, "LDS of a CU");
   static std::atomic<unsigned long long> attr_mask{0};
   if (attr_needed(attr_mask)) {
-    (void)hipFuncSetAttribute((const void*)gemm_skinny_k<BT, TC, NB, NS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    (void)hipFuncSetAttribute((const void*)gemm_skinny_k<BT, TC, NB, NW, NS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     attr_done(attr_mask);
   }
-  hipLaunchKernelGGL((gemm_skinny_k<BT, TC, NB, NS>), dim3(8 * cdiv(g.tiles_n, 8) * g.tiles_m, 1, g.n_sub), dim3(NW * 64), smem, s, g);
+  hipLaunchKernelGGL((gemm_skinny_k<BT, TC, NB, NW, NS>), dim3(8 * cdiv(g.tiles_n, 8) * g.tiles_m, 1, g.n_sub), dim3(NW * 64), smem, s, g);
+}
+
+// Pieces in flight are LDS, and LDS decides how many workgroups share a CU: up to 8 pieces every wave has one (64 KiB, two
+// workgroups), up to 4 there are 4 waves (32 KiB, four).
+template <bool BT, class TC, int NB>
+static void by_k(const GemmArgs& g, hipStream_t s) {
+  if (g.K <= 256) go<BT, TC, NB, 4, 1>(g, s);
+  else if (g.K <= 512 || NB == 2) go<BT, TC, NB, 8, 1>(g, s);
+  else if constexpr (NB == 1) go<BT, TC, NB, 8, 2>(g, s);
 }
 
 void launch_gemm_skinny(const GemmArgs& g, int out_f32, hipStream_t s) {
-  if (g.act_half) { if (out_f32) go<false, float, 2, 1>(g, s); else go<false, bf16, 2, 1>(g, s); }
-  else if (g.b_trans) { if (out_f32) go<true, float, 1, 2>(g, s); else go<true, bf16, 1, 2>(g, s); }
-  else { if (out_f32) go<false, float, 1, 2>(g, s); else go<false, bf16, 1, 2>(g, s); }
+  if (g.act_half) { if (out_f32) by_k<false, float, 2>(g, s); else by_k<false, bf16, 2>(g, s); }
+  else if (g.b_trans) { if (out_f32) by_k<true, float, 1>(g, s); else by_k<true, bf16, 1>(g, s); }
+  else { if (out_f32) by_k<false, float, 1>(g, s); else by_k<false, bf16, 1>(g, s); }
 }
