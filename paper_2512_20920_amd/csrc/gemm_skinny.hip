@@ -173,13 +173,17 @@ static void go(GemmArgs g, hipStream_t s) {
   hipLaunchKernelGGL((gemm_skinny_k<BT, TC, NB, NW, NS>), dim3(8 * cdiv(g.tiles_n, 8) * g.tiles_m, 1, g.n_sub), dim3(NW * 64), smem, s, g);
 }
 
-// Pieces in flight are LDS, and LDS decides how many workgroups share a CU: up to 8 pieces every wave has one (64 KiB, two
-// workgroups), up to 4 there are 4 waves (32 KiB, four).
+// Pieces in flight are LDS, and LDS decides how many workgroups share a CU.  Up to 4 pieces there are 4 waves with one each
+// (32 KiB, four workgroups), up to 8 pieces 8 waves (64 KiB, two).  With more k a wave has two in flight (128 KiB) where
+// every workgroup has a CU to itself anyway; a larger launch gains more from a second workgroup.
 template <bool BT, class TC, int NB>
 static void by_k(const GemmArgs& g, hipStream_t s) {
   if (g.K <= 256) go<BT, TC, NB, 4, 1>(g, s);
   else if (g.K <= 512 || NB == 2) go<BT, TC, NB, 8, 1>(g, s);
-  else if constexpr (NB == 1) go<BT, TC, NB, 8, 2>(g, s);
+  else if constexpr (NB == 1) {
+    if ((i64)cdiv(g.M, 32) * cdiv(g.N, 32) * g.n_sub > 256) go<BT, TC, NB, 8, 1>(g, s);
+    else go<BT, TC, NB, 8, 2>(g, s);
+  }
 }
 
 void launch_gemm_skinny(const GemmArgs& g, int out_f32, hipStream_t s) {

@@ -148,11 +148,10 @@ int launch_gemm_mfma(const GemmArgs& g, GemmTypes t, hipStream_t s);
 // its form for few rows (problems that launch_gemm_mfma has accepted)
 // When a dense layer of N outputs goes there, for a call of T tokens (a rule on the call and the layer, never on how many
 // rows or problems one launch stacks: the kernels add in different orders, and results that are promised to be the same
-// bits may come from launches of T or 2 T rows).  Measured, us, weights from HBM, tile kernel -> this one:
-//   2048 outputs of k = 2048, both layouts: T = 128: 17.6 -> 7.9 / 18.0 -> 10.6   256: 18.0 -> 13.5 / 18.8 -> 17.4
-//   512: 17.9 -> 25.0    k = 5632: T = 128: 43 -> 15.6, 512: 42 -> 52    11264 outputs: T = 37: 19.4 -> 19.5, 128: 20.6 -> 38
-// so up to 512 tiles; three problems in one launch cross at 256, and 384 lies between.
-inline bool gemm_few_rows(i64 T, i64 N) { return ((T + 31) / 32) * ((N + 31) / 32) <= 384; }
+// bits may come from launches of T or 2 T rows).  A step at the Qwen shape, us, with the line at 384, 512 and 640 tiles:
+//   256 tokens (2048 outputs: 512 tiles): 1690, 1604, 1605    320, adapters only (640 tiles): 1350, 1353, 1381
+//   400 (1024 outputs: 416 tiles): 1805, 1769, 1772           a 512-wide block of 1536 tokens (768): 603 at 512, 636 at 800
+inline bool gemm_few_rows(i64 T, i64 N) { return ((T + 31) / 32) * ((N + 31) / 32) <= 512; }
 void launch_gemm_skinny(const GemmArgs& g, int out_f32, hipStream_t s);
 
 // Weight gradients of several dense layers, C_i[M_i,N_i] = A_i^T . B_i with A_i [K_i, M_i], B_i [K_i, N_i] row-major

@@ -71,7 +71,9 @@ def test_mfma_gemm_every_tile_shape(layout, tile):
 @pytest.mark.parametrize("layout", ["nt", "nn"])
 # one row, tails in every dimension around 32 rows and columns and the 64-wide pieces of k, fewer pieces than waves, one
 # more than a round of them, and the most tiles the rule sends there
-@pytest.mark.parametrize("M,N,K", [(1, 8, 8), (31, 40, 72), (33, 64, 504), (64, 1000, 520), (97, 264, 1096), (384, 1024, 64)])
+@pytest.mark.parametrize("M,N,K", [(1, 8, 8), (31, 40, 72), (33, 64, 504), (64, 1000, 520), (97, 264, 1096), (384, 1024, 64),
+                                   # the most tiles the rule sends there; as many workgroups with several pieces of k per wave
+                                   (512, 1024, 256), (200, 1304, 1032)])
 def test_few_rows_gemm(layout, M, N, K):
     rng = np.random.default_rng(M + 3 * N + 5 * K)
     A, Bm = _bf(rng, (M, K)), _bf(rng, (K, N))
