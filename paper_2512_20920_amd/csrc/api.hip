@@ -29,7 +29,8 @@ struct Carver {            // hands out 256-byte aligned slices of one allocatio
 // HBM) are kept apart from the dense GEMMs of the same operand layout (bound by the matrix cores).
 enum { KID_GEMM_NT = 0, KID_GEMM_NN, KID_GEMM_TN, KID_GEMM_GENERIC, KID_ATTN_FWD_FLASH, KID_ATTN_BWD_FLASH,
        KID_ATTN_FWD_GENERIC, KID_ATTN_BWD_GENERIC, KID_GEMM_NT_EXPERTS, KID_GEMM_NN_EXPERTS, KID_GEMM_TN_EXPERTS,
-       // the memory-bound kernels: algorithmic bytes only (every input read once, every output written once)
+       // the memory-bound kernels: algorithmic bytes only (every input read once, every output written once; the family
+       // router_bwd is part of moe_bwd_rows now and keeps its place in the list)
        KID_RMSNORM_FWD, KID_RMSNORM_BWD, KID_ROPE, KID_ROUTER, KID_PERMUTE, KID_COMBINE, KID_MOE_BWD_ROWS,
        KID_ROUTER_BWD, KID_DUM_FINALIZE, KID_SWIGLU_BWD, KID_COLSUM, KID_GATHER_ROWS, KID_COPY_ROWS,
        KID_COUNT };
@@ -93,7 +94,7 @@ struct revffn_ctx {
   int conv_last_nblk = 0;
   // backward
   void *dRS, *dYp, *dYs, *dHs, *dGUs, *dUm_sh, *dHh, *dGU, *dXg, *dUm, *dn3, *g1;
-  float *dw, *dzext, *rinv, *rinv3, *partial;
+  float *dzext, *rinv, *rinv3, *partial;
   int* ticket;                // of the column sums
   int* blk_cnt;                     // entries per token block and expert, from the router kernel to the permutation
   // the workspace still holds every activation of this revffn_forward call (stored-activation backward)
@@ -210,7 +211,6 @@ size_t carve(revffn_ctx* c, char* base) {
   c->dUm = cv.take(T * d * es);
   c->dn3 = cv.take(T * h * es);
   c->g1 = cv.take(T * h * es);
-  c->dw = (float*)cv.take(N * 4);
   c->dzext = (float*)cv.take(T * E1 * 4);
   const size_t E1p = (E1 + 7) / 8 * 8;
   c->wr_ext = cv.take(E1p * d * es);
@@ -374,10 +374,10 @@ void p_rmsnorm_fwd(revffn_ctx* c, int dt, int tx, const void* x, i64 ldx, const 
   launch_rmsnorm_fwd(dt, tx, x, ldx, g, out, ldo, rows, h, eps, s, skip, x2, g2, out2);
   ps.done(KID_RMSNORM_FWD);
 }
-void p_rmsnorm_bwd(revffn_ctx* c, int dt, int tx, const void* dy, i64 ldd, const void* x, i64 ldx, const void* g,
-                   const void* base, i64 ldb, void* dx, i64 ldo, float* rinv, int rows, int h, float eps, hipStream_t s) {
-  ProfScope ps(c, s, 0, (double)rows * h * (esz(tx) + (base ? 3 : 2) * esz(dt)) + rows * 4.0);
-  launch_rmsnorm_bwd(dt, tx, dy, ldd, x, ldx, g, base, ldb, dx, ldo, rinv, rows, h, eps, s);
+void p_rmsnorm_bwd(revffn_ctx* c, int dt, int tx, const NormBwd& p, const NormBwd* p2, i64 ldd, i64 ldx, i64 ldo, int rows, int h,
+                   float eps, hipStream_t s) {
+  ProfScope ps(c, s, 0, (p2 ? 2.0 : 1.0) * ((double)rows * h * (esz(tx) + (p.base ? 3 : 2) * esz(dt)) + rows * 4.0));
+  launch_rmsnorm_bwd(dt, tx, p, p2, ldd, ldx, ldo, rows, h, eps, s);
   ps.done(KID_RMSNORM_BWD);
 }
 void p_rope(revffn_ctx* c, int dt, void* buf, const float* cs, int T, int S, int H, int dh, float sign, hipStream_t s,
@@ -409,17 +409,12 @@ void p_combine(revffn_ctx* c, int dt, const void* yp, const int* inv_map, const 
   ps.done(KID_COMBINE);
 }
 void p_moe_bwd_rows(revffn_ctx* c, int dt, const void* drs, const void* yp, const void* ys, const int* inv_map,
-                    const float* wts, const float* gamma, void* dyp, void* dys, float* dw, float* dzext, int T, int d,
-                    int k, int E1, int has_gate, hipStream_t s) {
-  ProfScope ps(c, s, 0, (double)T * d * esz(dt) * (1 + 2 * k + (has_gate ? 2 : 0)) + (double)T * k * 12);
-  launch_moe_bwd_rows(dt, drs, yp, ys, inv_map, wts, gamma, dyp, dys, dw, dzext, T, d, k, E1, has_gate, s);
+                    const float* wts, const float* gamma, void* dyp, void* dys, float* dzext, int T, int d,
+                    int k, int E1, int has_gate, const RouterBwd& r, const RowCopy& copy, hipStream_t s) {
+  ProfScope ps(c, s, 0, (double)T * d * esz(dt) * (1 + 2 * k + (has_gate ? 2 : 0)) + 2.0 * (copy.rows_a + copy.rows_b) * d * esz(dt) +
+                        (double)T * (r.E * 8.0 + k * 12.0 + (r.dzb ? r.E1p * 2.0 : 0.0)));
+  launch_moe_bwd_rows(dt, drs, yp, ys, inv_map, wts, gamma, dyp, dys, dzext, T, d, k, E1, has_gate, r, copy, s);
   ps.done(KID_MOE_BWD_ROWS);
-}
-void p_router_bwd(revffn_ctx* c, const float* probs, const int* idx, const float* wts, const float* dw, float* dzext,
-                  int T, int E, int k, int E1, int norm_topk, hipStream_t s, void* dzb = nullptr, int E1p = 0) {
-  ProfScope ps(c, s, 0, (double)T * (E * 8.0 + k * 12.0 + (dzb ? E1p * 2.0 : 0.0)));
-  launch_router_bwd(probs, idx, wts, dw, dzext, T, E, k, E1, norm_topk, s, dzb, E1p);
-  ps.done(KID_ROUTER_BWD);
 }
 void p_dum_finalize(revffn_ctx* c, int dt, const void* dxg, const int* inv_map, const void* dum_sh, const void* dum_r,
                     const float* dzext, const void* w_router, const void* ws_gate, void* dum, int T, int d, int k, int E,
@@ -985,8 +980,12 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
   auto to_sw = [&]() { after(c, s, sw); sw_used = true; };      // sw may use what s has computed so far
   ColsumBatch cs;
   TRY(run_gemm(c, nn(dy2, ld, w->pdn_m, d, c->dRS, d, T, d, h), s));
-  p_moe_bwd_rows(c, dt, c->dRS, c->Yp, c->Ys, c->inv_map, c->wts, c->gamma, c->dYp, c->dYs, c->dw, c->dzext, T, d,
-                      k, E1, Is ? 1 : 0, s);
+  // (for the matrix-core router GEMM below: the logit gradients also in bf16, and the router rows stacked, dz . [W_r ; w_gate ; 0])
+  const bool dz_bf16 = dt == 1 && c->mode == 0;
+  const int E1p = (E1 + 7) / 8 * 8;
+  const RouterBwd rb{c->probs, c->idx, E, f.norm_topk_prob, dz_bf16 ? c->dzb : nullptr, E1p};
+  const RowCopy rc{w->w_router, Is ? w->ws_gate : w->w_router, c->wr_ext, dz_bf16 ? E : 0, dz_bf16 && Is ? 1 : 0};
+  p_moe_bwd_rows(c, dt, c->dRS, c->Yp, c->Ys, c->inv_map, c->wts, c->gamma, c->dYp, c->dYs, c->dzext, T, d, k, E1, Is ? 1 : 0, rb, rc, s);
   if (Is) {
     after(c, s, s0);
     TRY(run_gemm(c, nn(c->dYs, d, w->ws_down, Is, c->dHs, Is, T, Is, d), s0));
@@ -1018,20 +1017,10 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
     e.group_mode = 1; e.n_groups = E; e.offsets = c->offsets; e.b_group_stride = (i64)2 * I * d;
     TRY(run_gemm(c, e, s));
   }
-  // (the bf16 copy of the logit gradients for the matrix-core router GEMM below is written by the same kernel)
-  const bool dz_bf16 = dt == 1 && c->mode == 0;
-  const int E1p = (E1 + 7) / 8 * 8;
-  p_router_bwd(c, c->probs, c->idx, c->wts, c->dw, c->dzext, T, E, k, E1, f.norm_topk_prob, s,
-                    dz_bf16 ? c->dzb : nullptr, E1p);
   if (g && g->b_router) add_colsum(cs, 0, c->dzext, E1, 0, nullptr, 0, nullptr, 0, g->b_router, T, E);
   const void* dum_r = nullptr;
   if (dz_bf16) {
-    // router term of dUm on the matrix cores: dUm_r = dz . [W_r ; w_gate ; 0], contraction over E1p
-    {
-      ProfScope ps(c, s, 0, 2.0 * E1 * d * esz(dt));
-      launch_copy_rows2(dt, w->w_router, d, E, Is ? w->ws_gate : w->w_router, d, Is ? 1 : 0, c->wr_ext, d, d, s);
-      ps.done(KID_COPY_ROWS);
-    }
+    // router term of dUm on the matrix cores, contraction over E1p
     GemmArgs a = nn(c->dzb, E1p, c->wr_ext, d, c->dUm_r, d, T, d, E1p);
     GemmTypes tt{1, 1, 1, 1};
     if (launch_gemm_mfma(a, tt, s) == 0) dum_r = c->dUm_r;
@@ -1042,7 +1031,7 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
   if (GF(pup_m)) wg[nwg++] = tn(c->dUm, d, c->n3, h, GF(pup_m), h, d, h, T);
   TRY(run_gemm(c, nn(c->dUm, d, w->pup_m, h, c->dn3, h, T, h, d), s));
   // g1 = dY1 + Norm'(dn3): total gradient at Y1
-  p_rmsnorm_bwd(c, dt, c->sdt, c->dn3, h, y1, ldy, w->norm_m, dy1, ld, c->g1, h, c->rinv3, T, h, f.rms_eps, s);
+  p_rmsnorm_bwd(c, dt, c->sdt, NormBwd{c->dn3, y1, w->norm_m, dy1, ld, c->g1, c->rinv3}, nullptr, h, ldy, h, T, h, f.rms_eps, s);
   add_colsum(cs, c->sdt, y1, ldy, dt, c->dn3, h, c->rinv3, c->gdt, GF(norm_m), T, h);
   // ---- attention half backward: Y1 = X1 + P_dn_a(AO)
   if (sa != s) after(c, sa, s);           // the recomputed attention activations (and X1^ of a fused call)
@@ -1111,7 +1100,7 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
     TRY(run_gemm(c, nn(dU2, d, w->pup_a, h, dn2, h, T, h, d), s));
     TRY(run_wgrad_batch(c, wg, nwg, false, s));
     before_dx2();
-    p_rmsnorm_bwd(c, dt, c->sdt, dn2, h, x2, ld, w->norm_a2, dy2, ld, dx2, ld, c->rinv + T, T, h, f.rms_eps, s);
+    p_rmsnorm_bwd(c, dt, c->sdt, NormBwd{dn2, x2, w->norm_a2, dy2, ld, dx2, c->rinv + T}, nullptr, h, ld, ld, T, h, f.rms_eps, s);
     p_copy_rows(c, dt, c->g1, h, dx1, ld, T, h, s);              // dX1 = total gradient at Y1
     if (GF(norm_a1)) launch_zero(c->gdt, GF(norm_a1), h, s);           // stream 1 is not normalised in this block
   } else {
@@ -1121,8 +1110,8 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
     TRY(run_wgrad_batch(c, wg, nwg, false, s));
     before_dx2();
     // dX1 = g1 + Norm'(dn1);  dX2 = dY2 + Norm'(dn2)
-    p_rmsnorm_bwd(c, dt, c->sdt, c->dn12, h, x1, ld, w->norm_a1, c->g1, h, dx1, ld, c->rinv, T, h, f.rms_eps, s);
-    p_rmsnorm_bwd(c, dt, c->sdt, dn2, h, x2, ld, w->norm_a2, dy2, ld, dx2, ld, c->rinv + T, T, h, f.rms_eps, s);
+    const NormBwd nb2{dn2, x2, w->norm_a2, dy2, ld, dx2, c->rinv + T};
+    p_rmsnorm_bwd(c, dt, c->sdt, NormBwd{c->dn12, x1, w->norm_a1, c->g1, h, dx1, c->rinv}, &nb2, h, ld, ld, T, h, f.rms_eps, s);
     add_colsum(cs, c->sdt, x1, ld, dt, c->dn12, h, c->rinv, c->gdt, GF(norm_a1), T, h);
   }
   add_colsum(cs, c->sdt, x2, ld, dt, dn2, h, c->rinv + T, c->gdt, GF(norm_a2), T, h);

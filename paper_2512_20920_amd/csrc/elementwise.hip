@@ -106,16 +106,17 @@ void launch_rmsnorm_fwd(int dt, int tx, const void* x, i64 ldx, const void* g, v
 
 // RMSNorm backward for the input:  dx = r*(g.dy) - x*r^3*mean_j(x_j g_j dy_j), plus an
 // optional base term (the residual path of Eq. 1-2).  1/rms is kept per row.
+// (blockIdx.y == 1: the second problem of the launch, same rows, width and strides but for the base's)
 template <class T, class TX>
-__global__ void __launch_bounds__(256) rmsnorm_bwd_k(const T* __restrict__ dy, i64 ldd, const TX* __restrict__ x,
-                                                     i64 ldx, const T* __restrict__ g, const T* base, i64 ldb,
-                                                     T* dx, i64 ldo, float* __restrict__ rinv, int rows, int h,
-                                                     float eps) {
+__global__ void __launch_bounds__(256) rmsnorm_bwd_k(NormBwd p, NormBwd p2, i64 ldd, i64 ldx, i64 ldo, int rows, int h, float eps) {
   int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   int lane = threadIdx.x & 63;
   if (row >= rows) return;
-  const TX* xr = x + (i64)row * ldx;
-  const T* dr = dy + (i64)row * ldd;
+  if (blockIdx.y) p = p2;
+  const TX* xr = (const TX*)p.x + (i64)row * ldx;
+  const T* dr = (const T*)p.dy + (i64)row * ldd;
+  const T *g = (const T*)p.g, *base = (const T*)p.base;
+  T* dx = (T*)p.dx;
   float ss = 0.f, sd = 0.f;
   for (int j = lane; j < h; j += 64) {
     float v = to_f(xr[j]);
@@ -126,23 +127,23 @@ __global__ void __launch_bounds__(256) rmsnorm_bwd_k(const T* __restrict__ dy, i
   sd = wave_sum(sd);
   float r = 1.0f / sqrtf(ss / (float)h + eps);
   float c = r * r * r * sd / (float)h;
-  if (lane == 0) rinv[row] = r;
+  if (lane == 0) p.rinv[row] = r;
   for (int j = lane; j < h; j += 64) {
     float v = r * to_f(g[j]) * to_f(dr[j]) - to_f(xr[j]) * c;
-    if (base) v += to_f(base[(i64)row * ldb + j]);
+    if (base) v += to_f(base[(i64)row * p.ldb + j]);
     dx[(i64)row * ldo + j] = from_f<T>(v);
   }
 }
 
 template <class TX>
-__global__ void __launch_bounds__(256) rmsnorm_bwd_v8_k(const bf16* __restrict__ dy, i64 ldd, const TX* __restrict__ x,
-                                                        i64 ldx, const bf16* __restrict__ g, const bf16* base, i64 ldb,
-                                                        bf16* dx, i64 ldo, float* __restrict__ rinv, int rows, int h,
-                                                        float eps) {
+__global__ void __launch_bounds__(256) rmsnorm_bwd_v8_k(NormBwd p, NormBwd p2, i64 ldd, i64 ldx, i64 ldo, int rows, int h, float eps) {
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (row >= rows) return;
-  const TX* xr = x + (i64)row * ldx;
-  const bf16* dr = dy + (i64)row * ldd;
+  if (blockIdx.y) p = p2;
+  const TX* xr = (const TX*)p.x + (i64)row * ldx;
+  const bf16* dr = (const bf16*)p.dy + (i64)row * ldd;
+  const bf16 *g = (const bf16*)p.g, *base = (const bf16*)p.base;
+  bf16* dx = (bf16*)p.dx;
   float ss = 0.f, sd = 0.f;
   for (int j = lane * 8; j < h; j += 512) {
     const f32x8 v = load8(xr + j);
@@ -154,13 +155,13 @@ __global__ void __launch_bounds__(256) rmsnorm_bwd_v8_k(const bf16* __restrict__
   sd = wave_sum(sd);
   const float r = 1.0f / sqrtf(ss / (float)h + eps);
   const float c = r * r * r * sd / (float)h;
-  if (lane == 0) rinv[row] = r;
+  if (lane == 0) p.rinv[row] = r;
   for (int j = lane * 8; j < h; j += 512) {
     // (dx may alias base or dy: every lane reads its 8 elements of all inputs before it writes them)
     const f32x8 v = load8(xr + j);
     const bf16x8_v gv = *(const bf16x8_v*)(g + j), d = *(const bf16x8_v*)(dr + j);
     bf16x8_v b;
-    if (base) b = *(const bf16x8_v*)(base + (i64)row * ldb + j);
+    if (base) b = *(const bf16x8_v*)(base + (i64)row * p.ldb + j);
     bf16x8_v o;
 #pragma unroll
     for (int q = 0; q < 8; q++) {
@@ -172,27 +173,18 @@ __global__ void __launch_bounds__(256) rmsnorm_bwd_v8_k(const bf16* __restrict__
   }
 }
 
-void launch_rmsnorm_bwd(int dt, int tx, const void* dy, i64 ldd, const void* x, i64 ldx, const void* g,
-                        const void* base, i64 ldb, void* dx, i64 ldo, float* rinv, int rows, int h, float eps,
+void launch_rmsnorm_bwd(int dt, int tx, const NormBwd& p, const NormBwd* p2, i64 ldd, i64 ldx, i64 ldo, int rows, int h, float eps,
                         hipStream_t s) {
   if (rows <= 0) return;
-  const dim3 grid(cdiv(rows, 4)), block(256);
-  if (rows_vec8(dt, h, {dy, x, g, base, dx}, {ldd, ldx, ldb, ldo})) {
-    if (tx == 0)
-      hipLaunchKernelGGL(rmsnorm_bwd_v8_k<float>, grid, block, 0, s, (const bf16*)dy, ldd, (const float*)x, ldx,
-                         (const bf16*)g, (const bf16*)base, ldb, (bf16*)dx, ldo, rinv, rows, h, eps);
-    else
-      hipLaunchKernelGGL(rmsnorm_bwd_v8_k<bf16>, grid, block, 0, s, (const bf16*)dy, ldd, (const bf16*)x, ldx,
-                         (const bf16*)g, (const bf16*)base, ldb, (bf16*)dx, ldo, rinv, rows, h, eps);
+  const dim3 grid(cdiv(rows, 4), p2 ? 2 : 1), block(256);
+  const NormBwd q = p2 ? *p2 : p;
+  if (rows_vec8(dt, h, {p.dy, p.x, p.g, p.base, p.dx, q.dy, q.x, q.g, q.base, q.dx}, {ldd, ldx, p.ldb, q.ldb, ldo})) {
+    if (tx == 0) hipLaunchKernelGGL(rmsnorm_bwd_v8_k<float>, grid, block, 0, s, p, q, ldd, ldx, ldo, rows, h, eps);
+    else hipLaunchKernelGGL(rmsnorm_bwd_v8_k<bf16>, grid, block, 0, s, p, q, ldd, ldx, ldo, rows, h, eps);
     return;
   }
-  if (dt == 1 && tx == 0) {
-    hipLaunchKernelGGL((rmsnorm_bwd_k<bf16, float>), grid, block, 0, s, (const bf16*)dy, ldd, (const float*)x, ldx,
-                       (const bf16*)g, (const bf16*)base, ldb, (bf16*)dx, ldo, rinv, rows, h, eps);
-    return;
-  }
-  DISPATCH_DT(dt, hipLaunchKernelGGL((rmsnorm_bwd_k<T, T>), grid, block, 0, s, (const T*)dy, ldd, (const T*)x, ldx,
-                                     (const T*)g, (const T*)base, ldb, (T*)dx, ldo, rinv, rows, h, eps));
+  if (dt == 1 && tx == 0) hipLaunchKernelGGL((rmsnorm_bwd_k<bf16, float>), grid, block, 0, s, p, q, ldd, ldx, ldo, rows, h, eps);
+  else DISPATCH_DT(dt, hipLaunchKernelGGL((rmsnorm_bwd_k<T, T>), grid, block, 0, s, p, q, ldd, ldx, ldo, rows, h, eps));
 }
 
 // ---------------------------------------------------------------------------------
@@ -470,25 +462,6 @@ void launch_copy_rows(int dt, const void* src, i64 lds_, void* dst, i64 ldd, int
   if (total <= 0) return;
   DISPATCH_DT(dt, hipLaunchKernelGGL(copy_rows_k<T>, dim3(cdiv(total, 256)), dim3(256), 0, s, (const T*)src, lds_,
                                      (T*)dst, ldd, rows, cols));
-}
-
-// dst rows [0, rows_a) = src_a rows, dst rows [rows_a, rows_a + rows_b) = src_b rows (the stacked router matrix)
-template <class T>
-__global__ void __launch_bounds__(256) copy_rows2_k(const T* __restrict__ src_a, i64 lds_a, int rows_a,
-                                                    const T* __restrict__ src_b, i64 lds_b, int rows_b,
-                                                    T* __restrict__ dst, i64 ldd, int cols) {
-  i64 e = (i64)blockIdx.x * 256 + threadIdx.x;
-  if (e >= (i64)(rows_a + rows_b) * cols) return;
-  i64 r = e / cols;
-  int c = (int)(e % cols);
-  dst[r * ldd + c] = r < rows_a ? src_a[r * lds_a + c] : src_b[(r - rows_a) * lds_b + c];
-}
-void launch_copy_rows2(int dt, const void* src_a, i64 lds_a, int rows_a, const void* src_b, i64 lds_b, int rows_b,
-                       void* dst, i64 ldd, int cols, hipStream_t s) {
-  i64 total = (i64)(rows_a + rows_b) * cols;
-  if (total <= 0) return;
-  DISPATCH_DT(dt, hipLaunchKernelGGL(copy_rows2_k<T>, dim3(cdiv(total, 256)), dim3(256), 0, s, (const T*)src_a, lds_a,
-                                     rows_a, (const T*)src_b, lds_b, rows_b, (T*)dst, ldd, cols));
 }
 
 template <class T>

@@ -169,10 +169,11 @@ int launch_gemm_batch_tn(GemmBatch& b, int out_f32, int bulk, hipStream_t s);
 void launch_rmsnorm_fwd(int dt, int tx, const void* x, i64 ldx, const void* g, void* out, i64 ldo,
                         int rows, int h, float eps, hipStream_t s, const unsigned char* row_skip = nullptr,
                         const void* x2 = nullptr, const void* g2 = nullptr, void* out2 = nullptr);
-// dx = base + rmsnorm_bwd(dy; x, g);  rinv[rows] receives 1/rms per row (for the gain gradient)
-void launch_rmsnorm_bwd(int dt, int tx, const void* dy, i64 ldd, const void* x, i64 ldx, const void* g,
-                        const void* base, i64 ldb, void* dx, i64 ldo, float* rinv,
-                        int rows, int h, float eps, hipStream_t s);
+// dx = base + rmsnorm_bwd(dy; x, g);  rinv[rows] receives 1/rms per row (for the gain gradient).  p2 (may be null): a second
+// problem of the same launch
+struct NormBwd { const void *dy, *x, *g, *base; i64 ldb; void* dx; float* rinv; };
+void launch_rmsnorm_bwd(int dt, int tx, const NormBwd& p, const NormBwd* p2, i64 ldd, i64 ldx, i64 ldo, int rows, int h, float eps,
+                        hipStream_t s);
 // Column sums out[j] = sum_t a[t*lda+j] * (b ? b[t*ldb+j] : 1) * (sc ? sc[t] : 1), up to COLSUM_MAX of them, of any
 // shapes, in one launch.  partial: colsum_partial_floats(sum of the cols) floats; ticket: colsum_tickets(..) ints, zero
 // before the first launch (every launch leaves them zero).
@@ -190,8 +191,6 @@ void launch_swiglu_bwd(int dt, const void* dhh, const void* gu, void* dgu, i64 r
 void launch_gather_rows(int dt, const void* src, const int* row_map, int div, void* dst, int rows, int cols,
                         hipStream_t s);
 void launch_copy_rows(int dt, const void* src, i64 lds_, void* dst, i64 ldd, int rows, int cols, hipStream_t s);
-void launch_copy_rows2(int dt, const void* src_a, i64 lds_a, int rows_a, const void* src_b, i64 lds_b, int rows_b,
-                       void* dst, i64 ldd, int cols, hipStream_t s);
 void launch_zero(int dt, void* p, int n, hipStream_t s);           // n elements of type dt set to zero
 // res[0] = max |a - b| (bitwise max of non-negative floats; res must be zeroed first) ; dst = a
 void launch_fill_u32(uint32_t* p, uint32_t v, int n, hipStream_t s);
@@ -237,12 +236,14 @@ void launch_combine(int dt, const void* yp, const int* inv_map, const float* wts
 void launch_combine_couple(int dt, int ts, const void* yp, const int* inv_map, const float* wts, const void* ys,
                            const float* gamma, const void* resid, i64 ldr, float sign, void* dst, i64 ldd, float* tap,
                            int T, int h, int k, hipStream_t s);
+// Backward of the combine and of the routing weights.  copy: rows of width d that the same launch copies to dst, src_a's and
+// then src_b's (the stacked router matrix; rows_a = rows_b = 0: none)
+struct RowCopy { const void *src_a, *src_b; void* dst; int rows_a, rows_b; };
+struct RouterBwd { const float* probs; const int* idx; int E, norm_topk; void* dzb; int E1p; };
+// dzext[T, E1]: logit gradients; r.dzb != null: also as bf16 rows of width E1p (zero padded) for the matrix-core GEMMs
 void launch_moe_bwd_rows(int dt, const void* drs, const void* yp, const void* ys, const int* inv_map,
-                         const float* wts, const float* gamma, void* dyp, void* dys, float* dw, float* dzext,
-                         int T, int d, int k, int E1, int has_gate, hipStream_t s);
-// dzb != null: also writes all E1 columns of dzext as bf16 rows of width E1p (zero padded) for the matrix-core GEMMs
-void launch_router_bwd(const float* probs, const int* idx, const float* wts, const float* dw, float* dzext,
-                       int T, int E, int k, int E1, int norm_topk, hipStream_t s, void* dzb = nullptr, int E1p = 0);
+                         const float* wts, const float* gamma, void* dyp, void* dys, float* dzext, int T, int d,
+                         int k, int E1, int has_gate, const RouterBwd& r, const RowCopy& copy, hipStream_t s);
 void launch_dum_finalize(int dt, const void* dxg, const int* inv_map, const void* dum_sh, const void* dum_r,
                          const float* dzext, const void* w_router, const void* ws_gate, void* dum, int T, int d,
                          int k, int E, int E1, hipStream_t s);

@@ -420,19 +420,62 @@ void launch_combine_couple(int dt, int ts, const void* yp, const int* inv_map, c
 }
 
 // ---------------------------------------------------------------------------------
-// Backward of the combine, one workgroup per token:
+// Backward of the combine and of the routing weights, one workgroup per token:
 //   dgamma = <drs, ys>, gate-logit gradient dzext[t,E] = dgamma*gamma*(1-gamma), dys = gamma*drs
-//   dw[t,slot] = <drs, yp[pos]>,  dyp[pos] = wts[t,slot]*drs
+//   dw[slot] = <drs, yp[pos]>,  dyp[pos] = wts[t,slot]*drs
+// and, once a token's dw are known, softmax + top-k weights (the selection itself carries no gradient):
+//   dp_sel = dw                      (or (dw - sum dw*w) / sum_sel p with renormalisation)
+//   dz_j   = p_j * ([j selected] dp_j - sum_sel dp_e p_e)        for every expert j
+// (a kernel of its own for the second part, and one that stacks the router rows for the GEMM that follows, were 5 us each of
+// every step at any size: both are latency)
 // ---------------------------------------------------------------------------------
+// dz of one token by one wave, lanes over the experts; sdw: its dw, sgate: dz of the gate logit
+__device__ __forceinline__ void router_bwd_token(const RouterBwd& r, const float* wts, const float* sdw, float sgate, float* dzext,
+                                                 int t, int k, int E1, int lane) {
+  const int E = r.E;
+  const float* p = r.probs + (i64)t * E;
+  // slot s lives in lane s (k <= 16); sums over the slots run in slot order on every lane
+  const int my_sel = lane < k ? r.idx[(i64)t * k + lane] : -1;
+  const float my_dw = lane < k ? sdw[lane] : 0.f;
+  const float my_w = lane < k ? wts[(i64)t * k + lane] : 0.f;
+  const float my_p = lane < k ? p[my_sel] : 0.f;
+  float ssum = 0.f, dww = 0.f;
+  for (int s = 0; s < k; s++) { ssum += __shfl(my_p, s, WAVE); dww += __shfl(my_dw, s, WAVE) * __shfl(my_w, s, WAVE); }
+  const float my_dp = r.norm_topk ? (my_dw - dww) / ssum : my_dw;
+  float inner = 0.f;
+  for (int s = 0; s < k; s++) inner += __shfl(my_dp, s, WAVE) * __shfl(my_p, s, WAVE);
+  bf16* dzb = (bf16*)r.dzb;
+  for (int j0 = 0; j0 < E; j0 += 64) {               // (every lane takes part in the exchanges)
+    const int j = j0 + lane;
+    float dp = 0.f;
+    for (int s = 0; s < k; s++) { const int sel = __shfl(my_sel, s, WAVE); const float v = __shfl(my_dp, s, WAVE); if (sel == j) dp = v; }
+    if (j < E) {
+      const float dz = p[j] * (dp - inner);
+      dzext[(i64)t * E1 + j] = dz;
+      if (dzb) dzb[(i64)t * r.E1p + j] = (bf16)dz;
+    }
+  }
+  // the remaining columns of the bf16 copy: the shared-gate column, zeros
+  if (dzb)
+    for (int j = E + lane; j < r.E1p; j += 64) dzb[(i64)t * r.E1p + j] = j < E1 ? (bf16)sgate : (bf16)0.f;
+}
 template <class T>
 __global__ void __launch_bounds__(256) moe_bwd_rows_k(const T* __restrict__ drs, const T* __restrict__ yp,
                                                       const T* __restrict__ ys, const int* __restrict__ inv_map,
                                                       const float* __restrict__ wts, const float* __restrict__ gamma,
-                                                      T* __restrict__ dyp, T* __restrict__ dys, float* __restrict__ dw,
-                                                      float* __restrict__ dzext, int d, int k, int E1, int has_gate) {
-  __shared__ float red[4];
+                                                      T* __restrict__ dyp, T* __restrict__ dys,
+                                                      float* __restrict__ dzext, int Tn, int d, int k, int E1, int has_gate,
+                                                      RouterBwd r, RowCopy copy) {
+  __shared__ float red[4], sdw[16];
   const int t = blockIdx.x;
+  if (t >= Tn) {
+    const int row = t - Tn;
+    const T* sp = row < copy.rows_a ? (const T*)copy.src_a + (i64)row * d : (const T*)copy.src_b + (i64)(row - copy.rows_a) * d;
+    for (int c = threadIdx.x; c < d; c += 256) ((T*)copy.dst)[(i64)row * d + c] = sp[c];
+    return;
+  }
   const T* dr = drs + (i64)t * d;
+  float gate = 0.f;
   if (has_gate) {
     float g = gamma[t];
     float acc = 0.f;
@@ -441,8 +484,8 @@ __global__ void __launch_bounds__(256) moe_bwd_rows_k(const T* __restrict__ drs,
       acc += v * to_f(ys[(i64)t * d + c]);
       dys[(i64)t * d + c] = from_f<T>(g * v);
     }
-    acc = block_sum_256(acc, red);
-    if (threadIdx.x == 0) dzext[(i64)t * E1 + (E1 - 1)] = acc * g * (1.f - g);
+    gate = block_sum_256(acc, red) * g * (1.f - g);
+    if (threadIdx.x == 0) dzext[(i64)t * E1 + (E1 - 1)] = gate;
   }
   for (int s = 0; s < k; s++) {
     int pos = inv_map[(i64)t * k + s];
@@ -454,18 +497,27 @@ __global__ void __launch_bounds__(256) moe_bwd_rows_k(const T* __restrict__ drs,
       dyp[(i64)pos * d + c] = from_f<T>(w * v);
     }
     acc = block_sum_256(acc, red);
-    if (threadIdx.x == 0) dw[(i64)t * k + s] = acc;
+    if (threadIdx.x == 0) sdw[s] = acc;
   }
+  // (wave 0 wrote sdw and is the one that reads it)
+  if (threadIdx.x < 64) { __builtin_amdgcn_wave_barrier(); router_bwd_token(r, wts, sdw, gate, dzext, t, k, E1, threadIdx.x); }
 }
 __global__ void __launch_bounds__(256) moe_bwd_rows_v8_k(const bf16* __restrict__ drs, const bf16* __restrict__ yp,
                                                          const bf16* __restrict__ ys, const int* __restrict__ inv_map,
                                                          const float* __restrict__ wts, const float* __restrict__ gamma,
                                                          bf16* __restrict__ dyp, bf16* __restrict__ dys,
-                                                         float* __restrict__ dw, float* __restrict__ dzext, int d, int k,
-                                                         int E1, int has_gate) {
-  __shared__ float red[4];
+                                                         float* __restrict__ dzext, int Tn, int d, int k,
+                                                         int E1, int has_gate, RouterBwd r, RowCopy copy) {
+  __shared__ float red[4], sdw[16];
   const int t = blockIdx.x;
+  if (t >= Tn) {
+    const int row = t - Tn;
+    const bf16* sp = row < copy.rows_a ? (const bf16*)copy.src_a + (i64)row * d : (const bf16*)copy.src_b + (i64)(row - copy.rows_a) * d;
+    for (int c = threadIdx.x * 8; c < d; c += 256 * 8) *(bf16x8_t*)((bf16*)copy.dst + (i64)row * d + c) = *(const bf16x8_t*)(sp + c);
+    return;
+  }
   const bf16* dr = drs + (i64)t * d;
+  float gate = 0.f;
   if (has_gate) {
     const float g = gamma[t];
     float acc = 0.f;
@@ -476,8 +528,8 @@ __global__ void __launch_bounds__(256) moe_bwd_rows_v8_k(const bf16* __restrict_
       for (int q = 0; q < 8; q++) { acc += (float)v[q] * (float)y[q]; o[q] = (__bf16)(g * (float)v[q]); }
       *(bf16x8_t*)(dys + (i64)t * d + c) = o;
     }
-    acc = block_sum_256(acc, red);
-    if (threadIdx.x == 0) dzext[(i64)t * E1 + (E1 - 1)] = acc * g * (1.f - g);
+    gate = block_sum_256(acc, red) * g * (1.f - g);
+    if (threadIdx.x == 0) dzext[(i64)t * E1 + (E1 - 1)] = gate;
   }
   for (int s = 0; s < k; s++) {
     const int pos = inv_map[(i64)t * k + s];
@@ -491,62 +543,23 @@ __global__ void __launch_bounds__(256) moe_bwd_rows_v8_k(const bf16* __restrict_
       *(bf16x8_t*)(dyp + (i64)pos * d + c) = o;
     }
     acc = block_sum_256(acc, red);
-    if (threadIdx.x == 0) dw[(i64)t * k + s] = acc;
+    if (threadIdx.x == 0) sdw[s] = acc;
   }
+  if (threadIdx.x < 64) { __builtin_amdgcn_wave_barrier(); router_bwd_token(r, wts, sdw, gate, dzext, t, k, E1, threadIdx.x); }
 }
 void launch_moe_bwd_rows(int dt, const void* drs, const void* yp, const void* ys, const int* inv_map,
-                         const float* wts, const float* gamma, void* dyp, void* dys, float* dw, float* dzext,
-                         int Tn, int d, int k, int E1, int has_gate, hipStream_t s) {
+                         const float* wts, const float* gamma, void* dyp, void* dys, float* dzext, int Tn, int d,
+                         int k, int E1, int has_gate, const RouterBwd& r, const RowCopy& copy, hipStream_t s) {
   if (Tn <= 0) return;
-  if (vec8_ok(dt, d, {drs, yp, ys, dyp, dys})) {
-    hipLaunchKernelGGL(moe_bwd_rows_v8_k, dim3(Tn), dim3(256), 0, s, (const bf16*)drs, (const bf16*)yp, (const bf16*)ys,
-                       inv_map, wts, gamma, (bf16*)dyp, (bf16*)dys, dw, dzext, d, k, E1, has_gate);
+  const dim3 grid(Tn + copy.rows_a + copy.rows_b);
+  if (vec8_ok(dt, d, {drs, yp, ys, dyp, dys, copy.src_a, copy.src_b, copy.dst})) {
+    hipLaunchKernelGGL(moe_bwd_rows_v8_k, grid, dim3(256), 0, s, (const bf16*)drs, (const bf16*)yp, (const bf16*)ys,
+                       inv_map, wts, gamma, (bf16*)dyp, (bf16*)dys, dzext, Tn, d, k, E1, has_gate, r, copy);
     return;
   }
-  DISPATCH_DT(dt, hipLaunchKernelGGL(moe_bwd_rows_k<T>, dim3(Tn), dim3(256), 0, s, (const T*)drs, (const T*)yp,
-                                     (const T*)ys, inv_map, wts, gamma, (T*)dyp, (T*)dys, dw, dzext, d, k, E1,
-                                     has_gate));
-}
-
-// ---------------------------------------------------------------------------------
-// Backward of softmax + top-k weights (the selection itself carries no gradient):
-//   dp_sel = dw                      (or (dw - sum dw*w) / sum_sel p with renormalisation)
-//   dz_j   = p_j * ([j selected] dp_j - sum_sel dp_e p_e)        for every expert j
-// One wave per token, lanes over the experts; writes columns 0..E-1 of dzext[T,E1].
-// ---------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) router_bwd_k(const float* __restrict__ probs, const int* __restrict__ idx,
-                                                    const float* __restrict__ wts, const float* __restrict__ dw,
-                                                    float* __restrict__ dzext, int Tn, int E, int k, int E1,
-                                                    int norm_topk, bf16* __restrict__ dzb, int E1p) {
-  const int t = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (t >= Tn) return;                     // whole wave
-  const float* p = probs + (i64)t * E;
-  // slot s lives in lane s (k <= 16); sums over the slots run in slot order on every lane
-  const int my_sel = lane < k ? idx[(i64)t * k + lane] : -1;
-  const float my_dw = lane < k ? dw[(i64)t * k + lane] : 0.f;
-  const float my_w = lane < k ? wts[(i64)t * k + lane] : 0.f;
-  const float my_p = lane < k ? p[my_sel] : 0.f;
-  float ssum = 0.f, dww = 0.f;
-  for (int s = 0; s < k; s++) { ssum += __shfl(my_p, s, WAVE); dww += __shfl(my_dw, s, WAVE) * __shfl(my_w, s, WAVE); }
-  const float my_dp = norm_topk ? (my_dw - dww) / ssum : my_dw;
-  float inner = 0.f;
-  for (int s = 0; s < k; s++) inner += __shfl(my_dp, s, WAVE) * __shfl(my_p, s, WAVE);
-  for (int j = lane; j < E; j += 64) {
-    float dp = 0.f;
-    for (int s = 0; s < k; s++) { const int sel = __shfl(my_sel, s, WAVE); const float v = __shfl(my_dp, s, WAVE); if (sel == j) dp = v; }
-    const float dz = p[j] * (dp - inner);
-    dzext[(i64)t * E1 + j] = dz;
-    if (dzb) dzb[(i64)t * E1p + j] = (bf16)dz;
-  }
-  // the remaining columns of the bf16 copy: the shared-gate column (written to dzext by an earlier kernel), zeros
-  if (dzb)
-    for (int j = E + lane; j < E1p; j += 64) dzb[(i64)t * E1p + j] = j < E1 ? (bf16)dzext[(i64)t * E1 + j] : (bf16)0.f;
-}
-void launch_router_bwd(const float* probs, const int* idx, const float* wts, const float* dw, float* dzext, int Tn,
-                       int E, int k, int E1, int norm_topk, hipStream_t s, void* dzb, int E1p) {
-  if (Tn <= 0) return;
-  hipLaunchKernelGGL(router_bwd_k, dim3(cdiv(Tn, 4)), dim3(256), 0, s, probs, idx, wts, dw, dzext, Tn, E, k, E1,
-                     norm_topk, (bf16*)dzb, E1p);
+  DISPATCH_DT(dt, hipLaunchKernelGGL(moe_bwd_rows_k<T>, grid, dim3(256), 0, s, (const T*)drs, (const T*)yp,
+                                     (const T*)ys, inv_map, wts, gamma, (T*)dyp, (T*)dys, dzext, Tn, d, k, E1,
+                                     has_gate, r, copy));
 }
 
 // ---------------------------------------------------------------------------------
