@@ -285,7 +285,7 @@ void gemm_work(const revffn_ctx* c, const GemmArgs& g, int ta, int tb, int tc, d
   if (g.group_mode == 1) { *flops = 2 * M * N * K; *bytes = M * K * ea + G * N * K * eb + M * N * ec; }
   else if (g.group_mode == 2) { double R = K;                                     // rows summed over groups
     *flops = 2 * M * N * R; *bytes = R * M * ea + R * N * eb + G * M * N * ec; }
-  else { *flops = 2 * M * N * K; *bytes = M * K * ea + N * K * eb + M * N * ec; }
+  else { if (g.A2) K *= 2; *flops = 2 * M * N * K; *bytes = M * K * ea + N * K * eb + M * N * ec; }
   if (g.resid) *bytes += M * N * (g.resid_f32 ? 4 : c->es);
   if (g.act_half) *bytes += M * (double)g.act_half * ec;
 }
@@ -301,13 +301,20 @@ int run_gemm(revffn_ctx* c, GemmArgs g, int ta, int tb, int tc, hipStream_t s) {
   double fl = 0, by = 0;
   if (c->prof_on) gemm_work(c, g, ta, tb, tc, &fl, &by);
   ProfScope ps(c, s, fl, by);
-  // A gate/up GEMM asks for silu(gate) * up beside its output.  The matrix-core kernel does that in its epilogue;
-  // on every other route the GEMM is followed by the SwiGLU kernel, which reads the output back.
-  void* act_out = g.act_out;
+  // A gate/up GEMM asks for silu(gate) * up beside its output, a data gradient at that product for the gradients at gate and
+  // up instead of its output.  A kernel that cannot do so in its epilogue is followed by one that reads the output back.
+  void *act_out = g.act_out, *dact_out = g.dact_out;
   const int act_half = g.act_half;
-  const i64 act_rows = g.group_mode == 1 ? c->lastT_rows : g.M;
-  if (act_half && c->no_fused_swiglu) { g.act_out = nullptr; g.act_half = 0; }
-  auto swiglu_after = [&]() { if (act_half && !g.act_half) launch_swiglu_fwd(c->dt, g.C, act_out, act_rows, act_half, s); };
+  const i64 out_rows = g.group_mode == 1 ? c->lastT_rows : g.M;
+  if (c->no_fused_swiglu) { g.act_out = nullptr; g.act_half = 0; g.dact_out = nullptr; }
+  auto swiglu_after = [&]() {
+    if (act_half && !g.act_half) launch_swiglu_fwd(c->dt, g.C, act_out, out_rows, act_half, s);
+    if (dact_out && !g.dact_out) {
+      ProfScope q(c, s, 0, 5.0 * out_rows * g.N * c->es);
+      launch_swiglu_bwd(c->dt, g.C, g.dact_gu, dact_out, out_rows, g.N, s);
+      q.done(KID_SWIGLU_BWD);
+    }
+  };
   if (c->dt == 1 && c->mode == 0 && ta == 1 && tb == 1) {
     if (g.group_mode == 1) {
       // Expert tiles stream weights that nothing else reads, so with few rows per expert what counts is weight bytes in
@@ -340,6 +347,7 @@ int run_gemm(revffn_ctx* c, GemmArgs g, int ta, int tb, int tc, hipStream_t s) {
         if (c->max_tiles_b < 32768) g.tile_first = c->tf_b;
       }
     }
+    if (!g.few_rows) g.dact_out = nullptr;
     if (launch_gemm_mfma(g, t, s) == 0) {
       if (g.group_mode) ps.done(g.a_trans ? KID_GEMM_TN_EXPERTS : (g.b_trans ? KID_GEMM_NN_EXPERTS : KID_GEMM_NT_EXPERTS));
       else ps.done(g.a_trans ? KID_GEMM_TN : (g.b_trans ? KID_GEMM_NN : KID_GEMM_NT));
@@ -348,7 +356,7 @@ int run_gemm(revffn_ctx* c, GemmArgs g, int ta, int tb, int tc, hipStream_t s) {
     }
   }
   if (g.group_mode == 1) { g.tile_group = c->tg_a; g.tile_m0 = c->tm_a; g.max_tiles = c->max_tiles_a; g.tile_bm = BM_A; g.tile_count = c->tile_cnt; }
-  g.act_out = nullptr; g.act_half = 0;
+  if (!c->no_fused_swiglu) g.dact_out = dact_out;
   int e = launch_gemm_generic(g, t, s) == 0 ? 0 : REVFFN_EUNSUPPORTED;
   ps.done(KID_GEMM_GENERIC);
   if (!e) swiglu_after();
@@ -423,11 +431,6 @@ void p_dum_finalize(revffn_ctx* c, int dt, const void* dxg, const int* inv_map, 
   launch_dum_finalize(dt, dxg, inv_map, dum_sh, dum_r, dzext, w_router, ws_gate, dum, T, d, k, E, E1, s);
   ps.done(KID_DUM_FINALIZE);
 }
-void p_swiglu_bwd(revffn_ctx* c, int dt, const void* dhh, const void* gu, void* dgu, i64 rows, int I, hipStream_t s) {
-  ProfScope ps(c, s, 0, 5.0 * rows * I * esz(dt));
-  launch_swiglu_bwd(dt, dhh, gu, dgu, rows, I, s);
-  ps.done(KID_SWIGLU_BWD);
-}
 void add_colsum(ColsumBatch& q, int ta, const void* a, i64 lda, int tb, const void* b, i64 ldb,
                 const float* sc, int tout, void* out, int rows, int cols) {
   if (!out) return;
@@ -455,11 +458,11 @@ void p_copy_rows(revffn_ctx* c, int dt, const void* src, i64 lds_, void* dst, i6
 }
 
 // n <= 3 dense GEMMs of one shape, layout and strides as ONE launch of the matrix-core kernel (the 2048-wide
-// projections are one round of workgroups each: together they fill the chip for several rounds); where that kernel
-// does not take the problem they run one after the other.  tc: element type of the results.
+// projections are one round of workgroups each: together they fill the chip for several rounds), or of the float32 one;
+// bf16 problems that the former does not take run one after the other.  tc: element type of the results.
 int run_gemm_multi(revffn_ctx* c, const GemmArgs* subs, int n, int tc, hipStream_t s) {
   if (n <= 0) return 0;
-  if (n > 1 && c->dt == 1 && c->mode == 0) {
+  if (n > 1) {
     GemmArgs g = subs[0];
     g.n_sub = n;
     g.few_rows = few_rows(c, g);
@@ -468,10 +471,20 @@ int run_gemm_multi(revffn_ctx* c, const GemmArgs* subs, int n, int tc, hipStream
     }
     GemmTypes t{c->dt, c->dt, tc, c->dt};
     double fl = 0, by = 0;
-    if (c->prof_on) { gemm_work(c, subs[0], c->dt, c->dt, tc, &fl, &by); fl *= n; by *= n; }
+    if (c->prof_on)
+      for (int z = 0; z < n; z++) {
+        double f1, b1;
+        gemm_work(c, subs[z], c->dt, c->dt, tc, &f1, &b1);
+        fl += f1; by += b1;
+      }
     ProfScope ps(c, s, fl, by);
-    if (launch_gemm_mfma(g, t, s) == 0) {
-      ps.done(g.a_trans ? KID_GEMM_TN : (g.b_trans ? KID_GEMM_NN : KID_GEMM_NT));
+    if (c->dt == 1 && c->mode == 0) {
+      if (launch_gemm_mfma(g, t, s) == 0) {
+        ps.done(g.a_trans ? KID_GEMM_TN : (g.b_trans ? KID_GEMM_NN : KID_GEMM_NT));
+        return 0;
+      }
+    } else if (launch_gemm_generic(g, t, s) == 0) {
+      ps.done(KID_GEMM_GENERIC);
       return 0;
     }
   }
@@ -482,11 +495,12 @@ int run_gemm_multi(revffn_ctx* c, const GemmArgs* subs, int n, int tc, hipStream
   return 0;
 }
 
-// the weight gradients of several dense layers as one launch; where the matrix-core kernel does not take them they run
-// one after the other
+// the weight gradients of several dense layers as one launch; where the bf16 kernel does not take them they run one after
+// the other
 int run_wgrad_batch(revffn_ctx* c, const GemmArgs* subs, int n, bool bulk, hipStream_t s) {
   if (n <= 0) return 0;
-  if (c->dt == 1 && c->mode == 0) {
+  const bool f32 = c->dt == 0 && c->gdt == 0;
+  if (f32 || (c->dt == 1 && c->mode == 0)) {
     GemmBatch b;
     double fl = 0, by = 0;
     for (int i = 0; i < n; i++) {
@@ -496,7 +510,7 @@ int run_wgrad_batch(revffn_ctx* c, const GemmArgs* subs, int n, bool bulk, hipSt
       if (c->prof_on) { gemm_work(c, g, c->dt, c->dt, c->gdt, &f1, &b1); fl += f1; by += b1; }
     }
     ProfScope ps(c, s, fl, by);
-    if (launch_gemm_batch_tn(b, c->gdt == 0, bulk, s) == 0) { ps.done(KID_GEMM_TN); return 0; }
+    if (f32 ? launch_gemm_f32_batch_tn(b, s) == 0 : launch_gemm_batch_tn(b, c->gdt == 0, bulk, s) == 0) { ps.done(f32 ? KID_GEMM_GENERIC : KID_GEMM_TN); return 0; }
   }
   for (int i = 0; i < n; i++) {
     int e = run_gemm(c, subs[i], c->dt, c->dt, c->gdt, s);
@@ -988,8 +1002,9 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
   p_moe_bwd_rows(c, dt, c->dRS, c->Yp, c->Ys, c->inv_map, c->wts, c->gamma, c->dYp, c->dYs, c->dzext, T, d, k, E1, Is ? 1 : 0, rb, rc, s);
   if (Is) {
     after(c, s, s0);
-    TRY(run_gemm(c, nn(c->dYs, d, w->ws_down, Is, c->dHs, Is, T, Is, d), s0));
-    p_swiglu_bwd(c, dt, c->dHs, c->GUs, c->dGUs, T, Is, s0);
+    GemmArgs dh = nn(c->dYs, d, w->ws_down, Is, c->dHs, Is, T, Is, d);
+    dh.dact_gu = c->GUs; dh.dact_out = c->dGUs;
+    TRY(run_gemm(c, dh, s0));
     TRY(run_gemm(c, nn(c->dGUs, 2 * Is, w->ws_gate_up, d, c->dUm_sh, d, T, d, 2 * Is), s0));
     if (GF(ws_down)) wg[nwg++] = tn(c->dYs, d, c->Hs, Is, GF(ws_down), Is, d, Is, T);
     if (GF(ws_gate_up)) wg[nwg++] = tn(c->dGUs, 2 * Is, c->Um, d, GF(ws_gate_up), d, 2 * Is, d, T);
@@ -1003,8 +1018,8 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
     }
     GemmArgs a = nn(c->dYp, d, w->w_down, I, c->dHh, I, N, I, d);          // dHh = dYp . Wd_e
     a.group_mode = 1; a.n_groups = E; a.offsets = c->offsets; a.b_group_stride = (i64)d * I;
+    a.dact_gu = c->GU; a.dact_out = c->dGU;
     TRY(run_gemm(c, a, s));
-    p_swiglu_bwd(c, dt, c->dHh, c->GU, c->dGU, N, I, s);
     if (GF(w_gate_up)) {
       // dWgu_e = dGU_e^T . Xg_e, with the permuted input rows Xg materialised once
       to_sw();
@@ -1081,8 +1096,15 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
   if (w->bq) add_colsum(cs, dt, c->dQ, d, dt, nullptr, 0, nullptr, c->gdt, GF(bq), T, d);
   if (w->bk) add_colsum(cs, dt, c->dK, d, dt, nullptr, 0, nullptr, c->gdt, GF(bk), T, d);
   if (w->bv) add_colsum(cs, dt, c->dV, d, dt, nullptr, 0, nullptr, c->gdt, GF(bv), T, d);
-  TRY(run_gemm(c, nn(c->dK, d, w->wk, d, dU2, d, T, d, d), s));
-  {
+  // dU2 = dK . Wk + dV . Wv: one contraction over both where the kernel takes two pairs of operands (then in one launch with
+  // dU1 = dQ . Wq), else one after the other
+  const bool pairs = dt == 0 || c->mode == 1 || gemm_few_rows(T, d);
+  GemmArgs du[2] = {nn(c->dK, d, w->wk, d, dU2, d, T, d, d), nn(c->dQ, d, w->wq, d, dU1, d, T, d, d)};
+  if (pairs) {
+    du[0].A2 = c->dV; du[0].B2 = w->wv;
+    TRY(run_gemm_multi(c, du, sym ? 1 : 2, dt, s));
+  } else {
+    TRY(run_gemm(c, du[0], s));
     GemmArgs a = nn(c->dV, d, w->wv, d, dU2, d, T, d, d);        // dU2 += dV . Wv
     a.resid = dU2; a.ldr = d; a.resid_sign = 1.f;
     TRY(run_gemm(c, a, s));
@@ -1104,7 +1126,7 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
     p_copy_rows(c, dt, c->g1, h, dx1, ld, T, h, s);              // dX1 = total gradient at Y1
     if (GF(norm_a1)) launch_zero(c->gdt, GF(norm_a1), h, s);           // stream 1 is not normalised in this block
   } else {
-    TRY(run_gemm(c, nn(c->dQ, d, w->wq, d, dU1, d, T, d, d), s));
+    if (!pairs) TRY(run_gemm(c, du[1], s));
     if (GF(pup_a)) wg[nwg++] = tn(c->dU12, d, c->n12, h, GF(pup_a), h, d, h, 2 * T);
     TRY(run_gemm(c, nn(c->dU12, d, w->pup_a, h, c->dn12, h, 2 * T, h, d), s));
     TRY(run_wgrad_batch(c, wg, nwg, false, s));

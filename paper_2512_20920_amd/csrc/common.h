@@ -49,6 +49,13 @@ __device__ __forceinline__ float block_sum_256(float v, float* red) {
 
 __device__ __forceinline__ float sigmoid_f(float x) { return 1.0f / (1.0f + __expf(-x)); }
 
+// gradients at gate and up of silu(gate) * up, whose gradient is d
+__device__ __forceinline__ void swiglu_grad(float d, float gate, float up, float* dgate, float* dup) {
+  const float sg = sigmoid_f(gate);
+  *dgate = d * up * sg * (1.f + gate * (1.f - sg));
+  *dup = d * gate * sg;
+}
+
 static inline int cdiv(i64 a, i64 b) { return (int)((a + b - 1) / b); }
 
 // A kernel's dynamic-LDS limit is an attribute per device: `mask` (one per kernel instantiation) keeps one bit per

@@ -369,10 +369,10 @@ __global__ void __launch_bounds__(256) swiglu_bwd_k(const T* __restrict__ dhh, c
   i64 r = e / I;
   int j = (int)(e % I);
   float g = to_f(gu[r * 2 * I + j]), u = to_f(gu[r * 2 * I + I + j]);
-  float dh = to_f(dhh[e]);
-  float sg = sigmoid_f(g);
-  dgu[r * 2 * I + j] = from_f<T>(dh * u * sg * (1.f + g * (1.f - sg)));
-  dgu[r * 2 * I + I + j] = from_f<T>(dh * g * sg);
+  float dg, du;
+  swiglu_grad(to_f(dhh[e]), g, u, &dg, &du);
+  dgu[r * 2 * I + j] = from_f<T>(dg);
+  dgu[r * 2 * I + I + j] = from_f<T>(du);
 }
 // bf16, I % 8 == 0: one thread handles 8 consecutive columns with 16-byte accesses
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
@@ -399,9 +399,10 @@ __global__ void __launch_bounds__(256) swiglu_bwd_v8_k(const bf16* __restrict__ 
   bf16x8_t dh = *(const bf16x8_t*)(dhh + r * I + j), og, ou;
 #pragma unroll
   for (int q = 0; q < 8; q++) {
-    float gv = (float)g[q], d = (float)dh[q], sg = sigmoid_f(gv);
-    og[q] = (__bf16)(d * (float)u[q] * sg * (1.f + gv * (1.f - sg)));
-    ou[q] = (__bf16)(d * gv * sg);
+    float dg, du;
+    swiglu_grad((float)dh[q], (float)g[q], (float)u[q], &dg, &du);
+    og[q] = (__bf16)dg;
+    ou[q] = (__bf16)du;
   }
   *(bf16x8_t*)(dgu + r * 2 * I + j) = og;
   *(bf16x8_t*)(dgu + r * 2 * I + I + j) = ou;

@@ -13,37 +13,20 @@
 
 #include "operand_f32.h"
 
-template <class TA, class TB, class TC, class TS, bool AT, bool BT, int R, int TM, int TN>
-__global__ void __launch_bounds__(R == 16 ? 1024 : 512) gemm_f32_k(GemmArgs g) {
+// waves that share a contraction of k: one per chunk, at most `most`
+__host__ __device__ inline int f32_k_waves(int k, int R, int most) {
+  int nw = 1;
+  while (nw < most && k > GKC(R) * nw) nw *= 2;
+  return nw;
+}
+
+// ACT: a gate/up GEMM (TM = 1, TN = 2): the two column blocks are gate columns n0 .. and the up columns of the same indices
+template <class TA, class TB, class TC, class TS, bool AT, bool BT, int R, int TM, int TN, bool ACT>
+__device__ __forceinline__ void f32_tile(const GemmArgs& g, const TA* A, const TB* Bm, TC* C, const TS* bias, int m0, int m_end,
+                                         int n0, int k0, int k_end, int nw, const TA* A2, const TB* B2) {
   extern __shared__ __attribute__((aligned(16))) float part[];      // [waves][R TM][R TN]
   constexpr int BM = R * TM, BN = R * TN, EL = R * R / 64;   // (EL elements of a tile per lane)
-  const TA* A = (const TA*)g.A;
-  const TB* Bm = (const TB*)g.B;
-  TC* C = (TC*)g.C;
-  int m0, m_end, k0 = 0, k_end = g.K;
-  if (g.group_mode == 1) {
-    const int grp = g.tile_group[blockIdx.y];
-    if (grp < 0) return;
-    m0 = g.tile_m0[blockIdx.y];
-    m_end = min(g.offsets[grp + 1], m0 + BM);
-    Bm += (i64)grp * g.b_group_stride;
-  } else {
-    m0 = blockIdx.y * BM;
-    m_end = g.M;
-    if (g.group_mode == 2) {
-      const int grp = blockIdx.z;
-      k0 = g.offsets[grp];
-      k_end = g.offsets[grp + 1];
-      C += (i64)grp * g.c_group_stride;
-    }
-  }
-  if (g.row_skip && g.group_mode == 0) {             // nothing to do if every row of the tile is marked as finished
-    int live = 0;                                    // every wave checks all rows of the tile: same answer, no LDS
-    for (int r = m0 + (int)(threadIdx.x & 63); r < min(m_end, m0 + BM); r += 64) live |= g.row_skip[r] == 0;
-    if (!__any(live)) return;
-  }
-  const int n0 = blockIdx.x * BN;
-  const int lane = threadIdx.x & 63, gh = lane / R, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = g.k_waves;
+  const int lane = threadIdx.x & 63, gh = lane / R, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   typename AccOf<R>::type acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; i++)
@@ -51,16 +34,21 @@ __global__ void __launch_bounds__(R == 16 ? 1024 : 512) gemm_f32_k(GemmArgs g) {
     for (int j = 0; j < TN; j++)
 #pragma unroll
       for (int e = 0; e < EL; e++) acc[i][j][e] = 0.f;
-  const int nchunk = (k_end - k0 + GKC(R) - 1) / GKC(R);
-  const int parts = min(nw, max(nchunk, 1));
-  if (wv < min(nchunk, nw)) {
+  const int nchunk = (k_end - k0 + GKC(R) - 1) / GKC(R), all = A2 ? 2 * nchunk : nchunk;
+  const int parts = min(nw, max(all, 1));
+  // this wave's chunks of one pair of operands; the second pair goes on dealing where the first ended
+  auto contract = [&](const TA* pa, const TB* pb, int first) {
+    if (wv >= nw || first >= nchunk) return;
     Operand<TA, AT, R> oa[TM];
     Operand<TB, BT, R> ob[TN];
 #pragma unroll
-    for (int i = 0; i < TM; i++) oa[i].init(A, g.lda, m0 + R * i, m_end, lane, g.a_gather, g.gather_div, k0, (const TA*)g.a_last_row);
+    for (int i = 0; i < TM; i++) oa[i].init(pa, g.lda, m0 + R * i, m_end, lane, g.a_gather, g.gather_div, k0, (const TA*)g.a_last_row);
 #pragma unroll
-    for (int j = 0; j < TN; j++) ob[j].init(Bm, g.ldb, n0 + R * j, g.N, lane, nullptr, 1, k0);
-    k_loop<R, TM, TN>(oa, ob, k0, k_end, wv, nw, nchunk, gh, [&](float (&a)[TM][16], float (&b)[TN][16]) {
+    for (int j = 0; j < TN; j++) {
+      if (ACT) ob[j].init(pb, g.ldb, j * g.act_half + n0, (j + 1) * g.act_half, lane, nullptr, 1, k0);
+      else ob[j].init(pb, g.ldb, n0 + R * j, g.N, lane, nullptr, 1, k0);
+    }
+    k_loop<R, TM, TN>(oa, ob, k0, k_end, first, nw, nchunk, gh, [&](float (&a)[TM][16], float (&b)[TN][16]) {
 #pragma unroll
       for (int s = 0; s < 16; s++)
 #pragma unroll
@@ -68,7 +56,9 @@ __global__ void __launch_bounds__(R == 16 ? 1024 : 512) gemm_f32_k(GemmArgs g) {
 #pragma unroll
           for (int j = 0; j < TN; j++) acc[i][j] = mfma_f32(a[i][s], b[j][s], acc[i][j]);
     });
-  }
+  };
+  contract(A, Bm, wv);
+  if (A2) contract(A2, B2, (wv + nw - nchunk % nw) % nw);
   // ---- partial tiles to LDS, added in wave order by all threads, then the epilogue on whole output rows
   if (wv < parts) {
     float* mine = part + wv * (BM * BN);
@@ -89,9 +79,42 @@ __global__ void __launch_bounds__(R == 16 ? 1024 : 512) gemm_f32_k(GemmArgs g) {
   for (int w = 0; w < parts; w++)
 #pragma unroll
     for (int u = 0; u < EPT; u++) v[u] += part[w * (BM * BN) + threadIdx.x + u * 256];
-  const TS* bias = (const TS*)g.bias;
   const TS* resid = (const TS*)g.resid;
   const TS* cscale = (const TS*)g.col_scale;
+  if constexpr (ACT) {                               // silu(gate) * up from the stored values, as the separate kernel
+#pragma unroll
+    for (int u = 0; u < EPT; u++) {
+      const int e = threadIdx.x + u * 256, c = e % BN, m = m0 + e / BN, n = n0 + (c & (R - 1));
+      // (a row's 32 gate values and its 32 up values are in the two halves of one wave)
+      const TC x = from_f<TC>(v[u]);
+      const float up = __shfl(to_f(x), (lane & 31) + 32, WAVE);
+      if (m >= m_end || n >= g.act_half) continue;
+      C[(i64)m * g.ldc + (c / R) * g.act_half + n] = x;
+      if (c < R) ((TC*)g.act_out)[(i64)m * g.ldact + n] = from_f<TC>(to_f(x) * sigmoid_f(to_f(x)) * up);
+    }
+    return;
+  }
+  if (g.dact_out) {                                  // SwiGLU's backward, from what C would have held
+    const TS* gu = (const TS*)g.dact_gu;
+    float ga[EPT], ua[EPT];
+#pragma unroll
+    for (int u = 0; u < EPT; u++) {
+      const int e = threadIdx.x + u * 256, m = min(m0 + e / BN, m_end - 1), n = min(n0 + e % BN, g.N - 1);
+      ga[u] = to_f(gu[(i64)m * 2 * g.N + n]);
+      ua[u] = to_f(gu[(i64)m * 2 * g.N + g.N + n]);
+    }
+#pragma unroll
+    for (int u = 0; u < EPT; u++) {
+      const int e = threadIdx.x + u * 256, m = m0 + e / BN, n = n0 + e % BN;
+      if (m >= m_end || n >= g.N) continue;
+      float dg, du;
+      swiglu_grad(to_f(from_f<TC>(v[u])), ga[u], ua[u], &dg, &du);
+      TC* o = (TC*)g.dact_out + (i64)m * 2 * g.N + n;
+      o[0] = from_f<TC>(dg);
+      o[g.N] = from_f<TC>(du);
+    }
+    return;
+  }
   // (loads of all elements first, from clamped positions, so that they are in flight together)
   float sc[EPT], bi[EPT], rs[EPT];
 #pragma unroll
@@ -112,21 +135,73 @@ __global__ void __launch_bounds__(R == 16 ? 1024 : 512) gemm_f32_k(GemmArgs g) {
   }
 }
 
-template <class TA, class TB, class TC, class TS, bool AT, bool BT, int R, int TM, int TN>
+template <class TA, class TB, class TC, class TS, bool AT, bool BT, int R, int TM, int TN, bool ACT>
+__global__ void __launch_bounds__(R == 16 ? 1024 : 512) gemm_f32_k(GemmArgs g) {
+  constexpr int BM = R * TM, BN = ACT ? R : R * TN;
+  const TA *A = (const TA*)g.A, *A2 = (const TA*)g.A2;
+  const TB *Bm = (const TB*)g.B, *B2 = (const TB*)g.B2;
+  TC* C = (TC*)g.C;
+  const TS* bias = (const TS*)g.bias;
+  int m0, m_end, k0 = 0, k_end = g.K;
+  if (g.group_mode == 1) {
+    const int grp = g.tile_group[blockIdx.y];
+    if (grp < 0) return;
+    m0 = g.tile_m0[blockIdx.y];
+    m_end = min(g.offsets[grp + 1], m0 + BM);
+    Bm += (i64)grp * g.b_group_stride;
+  } else {
+    m0 = blockIdx.y * BM;
+    m_end = g.M;
+    if (g.group_mode == 2) {
+      const int grp = blockIdx.z;
+      k0 = g.offsets[grp];
+      k_end = g.offsets[grp + 1];
+      C += (i64)grp * g.c_group_stride;
+    } else {                                         // one of several problems of one shape launched together
+      if (blockIdx.z > 0) A2 = nullptr;
+      if (blockIdx.z == 1) { A = (const TA*)g.subA[0]; Bm = (const TB*)g.subB[0]; C = (TC*)g.subC[0]; bias = (const TS*)g.subBias[0]; }
+      if (blockIdx.z == 2) { A = (const TA*)g.subA[1]; Bm = (const TB*)g.subB[1]; C = (TC*)g.subC[1]; bias = (const TS*)g.subBias[1]; }
+    }
+  }
+  if (g.row_skip && g.group_mode == 0) {             // nothing to do if every row of the tile is marked as finished
+    int live = 0;                                    // every wave checks all rows of the tile: same answer, no LDS
+    for (int r = m0 + (int)(threadIdx.x & 63); r < min(m_end, m0 + BM); r += 64) live |= g.row_skip[r] == 0;
+    if (!__any(live)) return;
+  }
+  f32_tile<TA, TB, TC, TS, AT, BT, R, TM, TN, ACT>(g, A, Bm, C, bias, m0, m_end, blockIdx.x * BN, k0, k_end, g.k_waves, A2, B2);
+}
+
+// The weight gradients of several dense layers as one launch, tiles numbered over the problems: alone each is a launch of one
+// to a few hundred workgroups that mostly wait for their loads (ten of them at 400 tokens, d = 512: 95 us, together 48).  The sum is
+// cut as in a launch of its own, so the bits are the same.
+__global__ void __launch_bounds__(512) gemm_f32_batch_tn_k(GemmBatch b) {
+  typedef const __attribute__((address_space(4))) GemmBatch* KernArg;     // (indexed in the kernel-argument segment)
+  const KernArg ka = (KernArg)__builtin_amdgcn_kernarg_segment_ptr();
+  int i = 0;
+  while (i + 1 < ka->n && (int)blockIdx.x >= ka->p[i + 1].tile0) i++;
+  const int local = (int)blockIdx.x - ka->p[i].tile0, by = local / ka->p[i].tiles_n, bx = local - by * ka->p[i].tiles_n;
+  GemmArgs g;
+  g.M = ka->p[i].M; g.N = ka->p[i].N; g.K = ka->p[i].K;
+  g.lda = ka->p[i].lda; g.ldb = ka->p[i].ldb; g.ldc = ka->p[i].ldc;
+  f32_tile<float, float, float, float, true, true, 32, 1, 1, false>(g, (const float*)ka->p[i].A, (const float*)ka->p[i].B, (float*)ka->p[i].C,
+                                                                    nullptr, by * 32, g.M, bx * 32, 0, g.K, f32_k_waves(g.K, 32, 8), nullptr, nullptr);
+}
+
+template <class TA, class TB, class TC, class TS, bool AT, bool BT, int R, int TM, int TN, bool ACT = false>
 static void go_shape(const GemmArgs& g, int nw, hipStream_t s) {
   const int gy = g.group_mode == 1 ? g.max_tiles : cdiv(g.M, R * TM);
-  const dim3 grid(cdiv(g.N, R * TN), gy, g.group_mode == 2 ? g.n_groups : 1);
+  const dim3 grid(ACT ? cdiv(g.act_half, R) : cdiv(g.N, R * TN), gy, g.group_mode == 2 ? g.n_groups : g.group_mode == 0 ? g.n_sub : 1);
   if (grid.x == 0 || grid.y == 0 || grid.z == 0) return;
   const size_t smem = (size_t)nw * (R * TM) * (R * TN) * sizeof(float);
   static std::atomic<unsigned long long> attr_mask{0};
   if (smem >= 65536 && attr_needed(attr_mask)) {
-    (void)hipFuncSetAttribute((const void*)gemm_f32_k<TA, TB, TC, TS, AT, BT, R, TM, TN>,
+    (void)hipFuncSetAttribute((const void*)gemm_f32_k<TA, TB, TC, TS, AT, BT, R, TM, TN, ACT>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, 8 * 4096 * TM * TN);
     attr_done(attr_mask);
   }
   GemmArgs a = g;
   a.k_waves = nw;
-  hipLaunchKernelGGL((gemm_f32_k<TA, TB, TC, TS, AT, BT, R, TM, TN>), grid, dim3(64 * (nw > 4 ? nw : 4)), smem, s, a);
+  hipLaunchKernelGGL((gemm_f32_k<TA, TB, TC, TS, AT, BT, R, TM, TN, ACT>), grid, dim3(64 * (nw > 4 ? nw : 4)), smem, s, a);
 }
 
 template <class TA, class TB, class TC, class TS, bool AT, bool BT>
@@ -136,14 +211,14 @@ static void go(const GemmArgs& g, hipStream_t s) {
   // T rows, say).  64x32 tiles (a quarter less operand traffic per product) where they alone are 16 waves per CU, else
   // 32x32.  small_tiles (the caller's choice, since it changes the order of the sum): 16x16 tiles and up to 16 waves, for
   // the few dozen rows of the router matrices, whose 32x32 tiles would leave most CUs idle.
-  const int krange = g.group_mode == 2 ? cdiv(g.K, g.n_groups) : g.K;    // (per expert: the mean)
-  int nw = 1;
+  const int krange = (g.group_mode == 2 ? cdiv(g.K, g.n_groups) : g.K) * (g.A2 ? 2 : 1);    // (per expert: the mean)
   if (g.small_tiles && g.group_mode == 0) {
-    while (nw < 16 && krange > GKC(16) * nw) nw *= 2;
-    go_shape<TA, TB, TC, TS, AT, BT, 16, 1, 1>(g, nw, s);
+    go_shape<TA, TB, TC, TS, AT, BT, 16, 1, 1>(g, f32_k_waves(krange, 16, 16), s);
     return;
   }
-  while (nw < 8 && krange > GKC(32) * nw) nw *= 2;
+  const int nw = f32_k_waves(krange, 32, 8);
+  if constexpr (!AT && !BT)
+    if (g.act_half) { go_shape<TA, TB, TC, TS, AT, BT, 32, 1, 2, true>(g, nw, s); return; }
   const i64 z = g.group_mode == 2 ? g.n_groups : 1;
   if (g.group_mode != 1 && (i64)cdiv(g.M, 64) * cdiv(g.N, 32) * z * nw >= 4096) go_shape<TA, TB, TC, TS, AT, BT, 32, 2, 1>(g, nw, s);
   else go_shape<TA, TB, TC, TS, AT, BT, 32, 1, 1>(g, nw, s);
@@ -157,6 +232,7 @@ static void go_types(const GemmArgs& g, hipStream_t s) {
 
 int launch_gemm_generic(const GemmArgs& g, GemmTypes t, hipStream_t s) {
   if (g.group_mode == 1 && g.tile_bm != 32) return -1;
+  if (g.act_half && (g.a_trans || g.b_trans || g.group_mode == 2 || g.bias || g.resid || g.tap || g.N != 2 * g.act_half)) return -1;
   int key = t.ta * 8 + t.tb * 4 + t.tc * 2 + t.tside;
   switch (key) {
     case 0: go_types<float, float, float, float>(g, s); break;            // fp32 everything
@@ -166,5 +242,19 @@ int launch_gemm_generic(const GemmArgs& g, GemmTypes t, hipStream_t s) {
     case 5: go_types<float, bf16, float, bf16>(g, s); break;              // router weight gradient in float32
     default: return -1;
   }
+  return 0;
+}
+
+int launch_gemm_f32_batch_tn(GemmBatch& b, hipStream_t s) {
+  b.total = 0;
+  int nw = 1;
+  for (int i = 0; i < b.n; i++) {
+    GemmProb& p = b.p[i];
+    p.tile0 = b.total; p.tiles_m = cdiv(p.M, 32); p.tiles_n = cdiv(p.N, 32);
+    b.total += p.tiles_m * p.tiles_n;
+    const int w = f32_k_waves(p.K, 32, 8);
+    if (w > nw) nw = w;
+  }
+  if (b.total > 0) hipLaunchKernelGGL(gemm_f32_batch_tn_k, dim3(b.total), dim3(64 * (nw > 4 ? nw : 4)), (size_t)nw * 4096, s, b);
   return 0;
 }

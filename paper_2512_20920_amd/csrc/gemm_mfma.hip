@@ -842,10 +842,12 @@ int launch_gemm_mfma(const GemmArgs& g, GemmTypes t, hipStream_t s) {
     if (a_rows * g.lda >= lim || b_rows * g.ldb >= lim) return 1;
   }
   const bool f32out = t.tc == 0;
+  if (g.A2 && (!aligned16(g.A2) || !aligned16(g.B2) || !g.b_trans || f32out)) return 1;
   if (g.few_rows && g.group_mode == 0 && !g.a_trans && !g.a_gather && !g.force_tile) {
     launch_gemm_skinny(g, f32out, s);
     return 0;
   }
+  if (g.A2 || g.dact_out) return 1;
   if (!g.a_trans && !g.b_trans) {
     if (f32out) pick_tile<false, false, float>(g, s); else pick_tile<false, false, bf16>(g, s);
   } else if (!g.a_trans && g.b_trans) {

@@ -21,8 +21,8 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 // NB = 32-column blocks of a tile: 2 with the SwiGLU epilogue (gate columns and the up columns of the same indices);
-// NW = waves; NS = pieces of a wave in flight
-template <bool BT, class TC, int NB, int NW, int NS>
+// NW = waves; NS = pieces of a wave in flight; PAIR: problem 0 has a second pair of operands, its pieces follow the first's
+template <bool BT, class TC, int NB, int NW, int NS, bool PAIR>
 __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
   constexpr int RS = NB * 32 + 8;                    // row stride of a partial tile (floats): rows 4 apart are 32 banks apart
   constexpr unsigned OPD = 64 * 32 * 2, STAGE = (1 + NB) * OPD;     // LDS bytes of a piece: A, then B
@@ -42,7 +42,9 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
     const int r = m0 + (lane & 31);
     if (!__any(r < g.M && g.row_skip[r] == 0)) return;
   }
-  const u32x4 da = make_desc(A), db = make_desc(B);
+  const bool pair = PAIR && blockIdx.z == 0;
+  const u32x4 da = make_desc(A), db = make_desc(B), da2 = make_desc(PAIR ? g.A2 : A), db2 = make_desc(PAIR ? g.B2 : B);
+  const int np1 = (g.K + 63) >> 6, np = pair ? 2 * np1 : np1;
   const unsigned lda_b = (unsigned)g.lda * 2u, ldb_b = (unsigned)g.ldb * 2u;
   // where this lane's share of the four wave-loads of each operand comes from at k = 0, and which k it is (relative to
   // the piece): a load at or past K is out of range, rows and columns past the end repeat the last one or are zeros
@@ -64,18 +66,20 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
   const unsigned my = (unsigned)wv * NS * STAGE;     // this wave's part of LDS
   const unsigned lds0 = lds_address(smem) + my;
   auto issue = [&](int p, int stage) {
-    const int k0 = p * 64;
+    const bool second = pair && p >= np1;
+    const int k0 = (second ? p - np1 : p) * 64;
+    const u32x4 ra = second ? da2 : da, rb = second ? db2 : db;
     const unsigned dst = lds0 + (unsigned)stage * STAGE;
 #pragma unroll
     for (int i = 0; i < 4; i++) {
       const bool in = k0 + akc[i] < g.K;
-      load_lds_b128(da, __builtin_amdgcn_readfirstlane(dst + i * 1024u), in ? aoff[i] + (unsigned)k0 * 2u : OOB);
+      load_lds_b128(ra, __builtin_amdgcn_readfirstlane(dst + i * 1024u), in ? aoff[i] + (unsigned)k0 * 2u : OOB);
       if constexpr (!BT) {
 #pragma unroll
-        for (int j = 0; j < NB; j++) load_lds_b128(db, __builtin_amdgcn_readfirstlane(dst + (1 + j) * OPD + i * 1024u), in ? boff[j][i] + (unsigned)k0 * 2u : OOB);
+        for (int j = 0; j < NB; j++) load_lds_b128(rb, __builtin_amdgcn_readfirstlane(dst + (1 + j) * OPD + i * 1024u), in ? boff[j][i] + (unsigned)k0 * 2u : OOB);
       } else {
         const bool kin = k0 + i * 16 + (lane >> 2) < g.K && boff[0][i] != OOB;
-        load_lds_b128(db, __builtin_amdgcn_readfirstlane(dst + OPD + i * 1024u), kin ? boff[0][i] + (unsigned)k0 * ldb_b : OOB);
+        load_lds_b128(rb, __builtin_amdgcn_readfirstlane(dst + OPD + i * 1024u), kin ? boff[0][i] + (unsigned)k0 * ldb_b : OOB);
       }
     }
   };
@@ -87,7 +91,6 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
 
   const int fr = lane & 31, fsw = (fr >> 1) & 7;
   const unsigned tr = (unsigned)((lane >> 5) * 8 + ((lane & 15) >> 2)) * 64u + (unsigned)(((lane >> 4) & 1) * 16 + (lane & 3) * 4) * 2u;
-  const int np = (g.K + 63) >> 6;
 #pragma unroll
   for (int st = 0; st < NS; st++) issue(wv + st * NW, st);          // (pieces past the end load zeros, to keep the count)
   int st = 0;
@@ -146,6 +149,13 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
       C[(i64)m * g.ldc + n] = gb;
       C[(i64)m * g.ldc + ncols + n] = ub;
       ((TC*)g.act_out)[(i64)m * g.ldact + n] = (TC)(gv * sigmoid_f(gv) * (float)ub);
+    } else if (g.dact_out) {                         // SwiGLU's backward, from what C would have held
+      const bf16* gu = (const bf16*)g.dact_gu + (i64)m * 2 * g.N + n;
+      float dg, du;
+      swiglu_grad((float)(TC)v[0], (float)gu[0], (float)gu[g.N], &dg, &du);
+      TC* out = (TC*)g.dact_out + (i64)m * 2 * g.N + n;
+      out[0] = (TC)dg;
+      out[g.N] = (TC)du;
     } else {
       float o = v[0] + (bias ? (float)bias[n] : 0.f);
       if (g.tap) g.tap[(i64)m * g.ldtap + n] = o;
@@ -158,7 +168,7 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
   }
 }
 
-template <bool BT, class TC, int NB, int NW, int NS>
+template <bool BT, class TC, int NB, int NW, int NS, bool PAIR = false>
 static void go(GemmArgs g, hipStream_t s) {
   g.tiles_m = cdiv(g.M, 32);
   g.tiles_n = cdiv(NB == 2 ? g.act_half : g.N, 32);
@@ -167,27 +177,29 @@ static void go(GemmArgs g, hipStream_t s) {
   static_assert(smem <= 160 * 1024, "LDS of a CU");
   static std::atomic<unsigned long long> attr_mask{0};
   if (attr_needed(attr_mask)) {
-    (void)hipFuncSetAttribute((const void*)gemm_skinny_k<BT, TC, NB, NW, NS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    (void)hipFuncSetAttribute((const void*)gemm_skinny_k<BT, TC, NB, NW, NS, PAIR>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     attr_done(attr_mask);
   }
-  hipLaunchKernelGGL((gemm_skinny_k<BT, TC, NB, NW, NS>), dim3(8 * cdiv(g.tiles_n, 8) * g.tiles_m, 1, g.n_sub), dim3(NW * 64), smem, s, g);
+  hipLaunchKernelGGL((gemm_skinny_k<BT, TC, NB, NW, NS, PAIR>), dim3(8 * cdiv(g.tiles_n, 8) * g.tiles_m, 1, g.n_sub), dim3(NW * 64), smem, s, g);
 }
 
 // Pieces in flight are LDS, and LDS decides how many workgroups share a CU.  Up to 4 pieces there are 4 waves with one each
 // (32 KiB, four workgroups), up to 8 pieces 8 waves (64 KiB, two).  With more k a wave has two in flight (128 KiB) where
 // every workgroup has a CU to itself anyway; a larger launch gains more from a second workgroup.
-template <bool BT, class TC, int NB>
+template <bool BT, class TC, int NB, bool PAIR = false>
 static void by_k(const GemmArgs& g, hipStream_t s) {
-  if (g.K <= 256) go<BT, TC, NB, 4, 1>(g, s);
-  else if (g.K <= 512 || NB == 2) go<BT, TC, NB, 8, 1>(g, s);
+  const int k = PAIR ? 2 * g.K : g.K;
+  if (k <= 256) go<BT, TC, NB, 4, 1, PAIR>(g, s);
+  else if (k <= 512 || NB == 2) go<BT, TC, NB, 8, 1, PAIR>(g, s);
   else if constexpr (NB == 1) {
-    if ((i64)cdiv(g.M, 32) * cdiv(g.N, 32) * g.n_sub > 256) go<BT, TC, NB, 8, 1>(g, s);
-    else go<BT, TC, NB, 8, 2>(g, s);
+    if ((i64)cdiv(g.M, 32) * cdiv(g.N, 32) * g.n_sub > 256) go<BT, TC, NB, 8, 1, PAIR>(g, s);
+    else go<BT, TC, NB, 8, 2, PAIR>(g, s);
   }
 }
 
 void launch_gemm_skinny(const GemmArgs& g, int out_f32, hipStream_t s) {
   if (g.act_half) { if (out_f32) by_k<false, float, 2>(g, s); else by_k<false, bf16, 2>(g, s); }
+  else if (g.A2) by_k<true, bf16, 1, true>(g, s);    // (launch_gemm_mfma admits that form only)
   else if (g.b_trans) { if (out_f32) by_k<true, float, 1>(g, s); else by_k<true, bf16, 1>(g, s); }
   else { if (out_f32) by_k<false, float, 1>(g, s); else by_k<false, bf16, 1>(g, s); }
 }

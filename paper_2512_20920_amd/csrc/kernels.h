@@ -40,8 +40,13 @@ struct GemmArgs {
   i64 b_group_stride = 0, c_group_stride = 0;
   // MFMA kernel, [out,in] weights whose rows are [gate rows | up rows] (N = 2 * act_half): a tile holds matching gate
   // and up columns and also writes act_out[m*ldact + c] = silu(gate) * up, computed from the rounded outputs exactly
-  // as the separate SwiGLU kernel does from C.  Ignored by the generic kernel (the caller runs that kernel instead).
+  // as the separate SwiGLU kernel does from C.  The generic kernel does the same.
   void* act_out = nullptr; i64 ldact = 0; int act_half = 0;
+  // the other way (generic kernel, kernel for few rows): the output would be the gradient at silu(gate) * up; with dact_gu =
+  // [gate | up] rows (width 2 N), dact_out gets [dgate | dup] and C is not written
+  const void* dact_gu = nullptr; void* dact_out = nullptr;
+  // (the same two kernels) a second pair of operands of the same shapes and strides: C = A B + A2 B2 (problem 0 of a launch)
+  const void* A2 = nullptr; const void* B2 = nullptr;
   const void* col_scale = nullptr;       // generic kernel only
   // group_mode 1: number of m-tiles of the list actually in use (device scalar written by the permutation kernel);
   // group_mode 2: the permutation kernel's flag that the routing is even (null: treated as uneven)
@@ -161,6 +166,9 @@ void launch_gemm_skinny(const GemmArgs& g, int out_f32, hipStream_t s);
 struct GemmProb { const void *A, *B; void* C; int M, N, K, lda, ldb, ldc; int tile0, tiles_m, tiles_n; };
 struct GemmBatch { int n = 0, total = 0; GemmProb p[GEMM_BATCH]; };
 int launch_gemm_batch_tn(GemmBatch& b, int out_f32, int bulk, hipStream_t s);
+
+// the same for float32 operands and results
+int launch_gemm_f32_batch_tn(GemmBatch& b, hipStream_t s);
 
 // ---- normalisation / element-wise ------------------------------------------------
 // tx: element type of x (0 float32, 1 bf16); gains, outputs and gradients have type dt

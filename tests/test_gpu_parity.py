@@ -143,6 +143,21 @@ def test_block_parity_drawn_geometries(wl):
     print(wl.name, "ties", rep, {k: f"{v:.2e}" for k, v in errs.items()})
 
 
+# What the kernels for small problems do beside a plain product: SwiGLU and its gradient in the epilogue, two pairs of operands
+# in one contraction, several problems in one launch.  One token, one past a tile of 32 and several tiles, with gate/up widths
+# that end inside a tile, fewer chunks of k than waves and more; 50 wide rows of 2 bytes are not 16-byte aligned (bf16 goes to
+# the float32 kernel).  Every expert selected at the small widths, whose logits lie too close for a selection to be compared.
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d,H,E,k,I,Is,B,S", [(32, 2, 1, 1, 33, 70, 1, 1), (64, 4, 4, 4, 40, 24, 1, 33), (320, 5, 4, 1, 104, 168, 3, 47), (50, 5, 3, 3, 25, 50, 2, 9)])
+def test_block_parity_small_problems(dtype, d, H, E, k, I, Is, B, S):
+    wl = synth.Workload(f"small_d{d}", d, H, d // H, E, k, I, Is, B, S, dtype, gain_jitter=0.02, seed=d + I)
+    case = Case(wl)
+    tol = TOL[dtype]
+    y1d, y2d, _ = _forward_checks(case, tol, min_same=0.9)
+    x1d, x2d = _inverse_checks(case, y1d, y2d, tol, 1)
+    _backward_checks(case, x1d, x2d, y1d, tol)
+
+
 # The dense layers' weight gradients are one launch, on the tile whose rounds over 256 CUs cost least for all of them
 # together: widths that give 216 tiles of 128x128 (one round of those), 172 of 256x128 (one round, against two of 128x128)
 # and 216 of 256x256 (in phases), each with tiles that end outside the results; 70 tokens: a second, partly filled k-tile.
