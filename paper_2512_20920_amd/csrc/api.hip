@@ -334,12 +334,23 @@ int run_gemm(revffn_ctx* c, GemmArgs g, int ta, int tb, int tc, hipStream_t s) {
         else if (rows > 192 * E || (rows > 96 * E && g.N % 256 == 0)) shape = 4;
         else shape = rows > 96 * E ? 2 : 3;
       }
+      // Small problems are latency: 32x32 tiles with k cut among the waves, up to about as many as the chip holds at once.
+      // Measured, us per pass: a 512-wide block of 12 experts, 400 tokens (294 to 784 tiles) 420 -> 392, 1536 tokens (at most 936
+      // of 2496: 595 -> 585; all of them 597); 256 wide, 15 experts, 753 tokens, k = 256: 872 tiles 460 -> 448, 1308 -> 440.
+      // One token of merged Qwen weights (352) 199 -> 153.  With a row or two per expert the weights are the same traffic in
+      // either form and more of them are in flight here: 16 tokens at the Qwen shape (5368) 1180 -> 1154; with 8 rows, 128
+      // tokens, 1457 -> 1520.
+      const i64 low = rows < rows / 32 + E ? rows : rows / 32 + E;          // row tiles, at most
+      const i64 tiles32 = low * ((g.N + 31) / 32);
+      g.few_rows = tiles32 <= (g.K <= 256 ? 1600 : 1000) || (rows <= 2 * E && g.K <= 4096 && tiles32 <= 6000);
       bool tall = shape == 2 || shape == 4;
       g.tile_bn = shape >= 3 ? 256 : 128;
       const bool mid = c->bm_b == BM_B_MID;              // list b holds 160-row tiles: for the 160x256 forward kernel only
       if (mid && !tall) { if (g.b_trans) tall = true; else g.tile_bn = 256; }
       if (tall && g.b_trans && shape != 4) g.tile_bn = 128;
-      if (tall) {
+      if (g.few_rows) {
+        g.tile_group = c->tg_a; g.tile_m0 = c->tm_a; g.max_tiles = (int)low; g.tile_bm = BM_A; g.tile_count = c->tile_cnt; g.tile_first = c->tf_a;
+      } else if (tall) {
         g.tile_group = c->tg_c; g.tile_m0 = c->tm_c; g.max_tiles = c->max_tiles_c; g.tile_bm = BM_C; g.tile_count = c->tile_cnt + 2;
         if (c->max_tiles_c < 32768) g.tile_first = c->tf_c;      // (the packed entry holds 15 + 16 bits)
       } else {

@@ -824,7 +824,7 @@ int launch_gemm_mfma(const GemmArgs& g, GemmTypes t, hipStream_t s) {
   if (g.b_trans && (g.N & 7)) return 1;
   if (g.a_trans && !g.b_trans) return 1;                 // layout not used by the block
   if (g.group_mode == 2 && !(g.a_trans && g.b_trans)) return 1;
-  if (g.group_mode == 1 && (g.a_trans || (g.tile_bm != 128 && g.tile_bm != 256 && !(g.tile_bm == 160 && !g.b_trans && g.tile_bn == 256)))) return 1;
+  if (g.group_mode == 1 && (g.a_trans || (g.tile_bm != 128 && !(g.few_rows && g.tile_bm == 32 && t.tc == 1) && g.tile_bm != 256 && !(g.tile_bm == 160 && !g.b_trans && g.tile_bn == 256)))) return 1;
   if (g.a_gather && g.a_trans) return 1;
   if (g.group_mode != 1 && g.M <= 0) return 1;
   if (g.n_sub < 1 || g.n_sub > 3 || (g.n_sub > 1 && (g.group_mode != 0 || g.resid || g.tap || g.act_half))) return 1;
@@ -843,7 +843,7 @@ int launch_gemm_mfma(const GemmArgs& g, GemmTypes t, hipStream_t s) {
   }
   const bool f32out = t.tc == 0;
   if (g.A2 && (!aligned16(g.A2) || !aligned16(g.B2) || !g.b_trans || f32out)) return 1;
-  if (g.few_rows && g.group_mode == 0 && !g.a_trans && !g.a_gather && !g.force_tile) {
+  if (g.few_rows && !g.a_trans && !g.force_tile && (g.group_mode == 1 || (g.group_mode == 0 && !g.a_gather))) {
     launch_gemm_skinny(g, f32out, s);
     return 0;
   }

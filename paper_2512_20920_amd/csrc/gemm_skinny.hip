@@ -22,7 +22,7 @@ typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 // NB = 32-column blocks of a tile: 2 with the SwiGLU epilogue (gate columns and the up columns of the same indices);
 // NW = waves; NS = pieces of a wave in flight; PAIR: problem 0 has a second pair of operands, its pieces follow the first's
-template <bool BT, class TC, int NB, int NW, int NS, bool PAIR>
+template <bool BT, class TC, int NB, int NW, int NS, bool PAIR, bool GRP>
 __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
   constexpr int RS = NB * 32 + 8;                    // row stride of a partial tile (floats): rows 4 apart are 32 banks apart
   constexpr unsigned OPD = 64 * 32 * 2, STAGE = (1 + NB) * OPD;     // LDS bytes of a piece: A, then B
@@ -31,16 +31,28 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
   const bf16* B = (const bf16*)g.B;
   TC* C = (TC*)g.C;
   const bf16* bias = (const bf16*)g.bias;
-  if (blockIdx.z == 1) { A = (const bf16*)g.subA[0]; B = (const bf16*)g.subB[0]; C = (TC*)g.subC[0]; bias = (const bf16*)g.subBias[0]; }
-  if (blockIdx.z == 2) { A = (const bf16*)g.subA[1]; B = (const bf16*)g.subB[1]; C = (TC*)g.subC[1]; bias = (const bf16*)g.subBias[1]; }
-  const int run = (g.tiles_n + 7) >> 3, c = (int)blockIdx.x & 7, loc = (int)blockIdx.x >> 3;
-  const int bx = c * run + loc / g.tiles_m, by = loc % g.tiles_m;
-  if (bx >= g.tiles_n) return;
-  const int m0 = by * 32, n0 = bx * 32, ncols = NB == 2 ? g.act_half : g.N;
+  int bx, by, m0, m_end;
+  if constexpr (GRP) {                               // routed experts: row tiles from the list, 32 high
+    int bz = 0;
+    if (!place_tile(1, 1, 0, g.tiles_n, 1, g.tile_count[0], g.tile_first, (int)blockIdx.x, &bx, &by, &bz)) return;
+    const int grp = g.tile_group[by];
+    if (grp < 0) return;
+    m0 = g.tile_m0[by];
+    m_end = min(g.offsets[grp + 1], m0 + 32);
+    B += (i64)grp * g.b_group_stride;
+  } else {
+    if (blockIdx.z == 1) { A = (const bf16*)g.subA[0]; B = (const bf16*)g.subB[0]; C = (TC*)g.subC[0]; bias = (const bf16*)g.subBias[0]; }
+    if (blockIdx.z == 2) { A = (const bf16*)g.subA[1]; B = (const bf16*)g.subB[1]; C = (TC*)g.subC[1]; bias = (const bf16*)g.subBias[1]; }
+    const int run = (g.tiles_n + 7) >> 3, c = (int)blockIdx.x & 7, loc = (int)blockIdx.x >> 3;
+    bx = c * run + loc / g.tiles_m; by = loc % g.tiles_m;
+    if (bx >= g.tiles_n) return;
+    m0 = by * 32; m_end = g.M;
+  }
+  const int n0 = bx * 32, ncols = NB == 2 ? g.act_half : g.N;
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5;
-  if (g.row_skip) {                                  // every wave looks at all rows of the tile: same answer, no barrier
+  if (!GRP && g.row_skip) {                          // every wave looks at all rows of the tile: same answer, no barrier
     const int r = m0 + (lane & 31);
-    if (!__any(r < g.M && g.row_skip[r] == 0)) return;
+    if (!__any(r < m_end && g.row_skip[r] == 0)) return;
   }
   const bool pair = PAIR && blockIdx.z == 0;
   const u32x4 da = make_desc(A), db = make_desc(B), da2 = make_desc(PAIR ? g.A2 : A), db2 = make_desc(PAIR ? g.B2 : B);
@@ -54,7 +66,8 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
   for (int i = 0; i < 4; i++) {
     const int r = i * 8 + (lane >> 3), ch = (lane & 7) ^ ((r >> 1) & 7);
     akc[i] = ch * 8;
-    aoff[i] = (unsigned)min(m0 + r, g.M - 1) * lda_b + (unsigned)ch * 16u;
+    const int row = min(m0 + r, m_end - 1);
+    aoff[i] = (unsigned)(GRP && g.a_gather ? g.a_gather[row] / g.gather_div : row) * lda_b + (unsigned)ch * 16u;
     if constexpr (!BT) {
 #pragma unroll
       for (int j = 0; j < NB; j++) boff[j][i] = (unsigned)(min(n0 + r, ncols - 1) + j * ncols) * ldb_b + (unsigned)ch * 16u;
@@ -135,7 +148,7 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
 #pragma unroll
   for (int r = (int)threadIdx.x >> 5; r < 32; r += NW * 2) {
     const int m = m0 + r;
-    if (m >= g.M) break;
+    if (m >= m_end) break;
     float v[NB];
 #pragma unroll
     for (int j = 0; j < NB; j++) {
@@ -168,36 +181,42 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
   }
 }
 
-template <bool BT, class TC, int NB, int NW, int NS, bool PAIR = false>
+template <bool BT, class TC, int NB, int NW, int NS, bool PAIR = false, bool GRP = false>
 static void go(GemmArgs g, hipStream_t s) {
-  g.tiles_m = cdiv(g.M, 32);
+  g.tiles_m = GRP ? g.max_tiles : cdiv(g.M, 32);
   g.tiles_n = cdiv(NB == 2 ? g.act_half : g.N, 32);
   constexpr size_t part = (size_t)NW * 32 * (NB * 32 + 8) * 4, bufs = (size_t)NW * NS * (1 + NB) * 64 * 32 * 2;
   constexpr size_t smem = part > bufs ? part : bufs;
   static_assert(smem <= 160 * 1024, "LDS of a CU");
   static std::atomic<unsigned long long> attr_mask{0};
   if (attr_needed(attr_mask)) {
-    (void)hipFuncSetAttribute((const void*)gemm_skinny_k<BT, TC, NB, NW, NS, PAIR>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    (void)hipFuncSetAttribute((const void*)gemm_skinny_k<BT, TC, NB, NW, NS, PAIR, GRP>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     attr_done(attr_mask);
   }
-  hipLaunchKernelGGL((gemm_skinny_k<BT, TC, NB, NW, NS, PAIR>), dim3(8 * cdiv(g.tiles_n, 8) * g.tiles_m, 1, g.n_sub), dim3(NW * 64), smem, s, g);
+  hipLaunchKernelGGL((gemm_skinny_k<BT, TC, NB, NW, NS, PAIR, GRP>), dim3(GRP ? g.tiles_n * g.tiles_m : 8 * cdiv(g.tiles_n, 8) * g.tiles_m, 1, g.n_sub), dim3(NW * 64), smem, s, g);
 }
 
 // Pieces in flight are LDS, and LDS decides how many workgroups share a CU.  Up to 4 pieces there are 4 waves with one each
 // (32 KiB, four workgroups), up to 8 pieces 8 waves (64 KiB, two).  With more k a wave has two in flight (128 KiB) where
 // every workgroup has a CU to itself anyway; a larger launch gains more from a second workgroup.
-template <bool BT, class TC, int NB, bool PAIR = false>
+template <bool BT, class TC, int NB, bool PAIR = false, bool GRP = false>
 static void by_k(const GemmArgs& g, hipStream_t s) {
   const int k = PAIR ? 2 * g.K : g.K;
-  if (k <= 256) go<BT, TC, NB, 4, 1, PAIR>(g, s);
-  else if (k <= 512 || NB == 2) go<BT, TC, NB, 8, 1, PAIR>(g, s);
+  if (k <= 256) go<BT, TC, NB, 4, 1, PAIR, GRP>(g, s);
+  else if (k <= 512 || NB == 2) go<BT, TC, NB, 8, 1, PAIR, GRP>(g, s);
   else if constexpr (NB == 1) {
-    if ((i64)cdiv(g.M, 32) * cdiv(g.N, 32) * g.n_sub > 256) go<BT, TC, NB, 8, 1, PAIR>(g, s);
-    else go<BT, TC, NB, 8, 2, PAIR>(g, s);
+    if ((i64)(GRP ? g.max_tiles : cdiv(g.M, 32)) * cdiv(g.N, 32) * g.n_sub > 256) go<BT, TC, NB, 8, 1, PAIR, GRP>(g, s);
+    else go<BT, TC, NB, 8, 2, PAIR, GRP>(g, s);
   }
 }
 
 void launch_gemm_skinny(const GemmArgs& g, int out_f32, hipStream_t s) {
+  if (g.group_mode == 1) {                           // (bf16 results, launch_gemm_mfma)
+    if (g.act_half) by_k<false, bf16, 2, false, true>(g, s);
+    else if (g.b_trans) by_k<true, bf16, 1, false, true>(g, s);
+    else by_k<false, bf16, 1, false, true>(g, s);
+    return;
+  }
   if (g.act_half) { if (out_f32) by_k<false, float, 2>(g, s); else by_k<false, bf16, 2>(g, s); }
   else if (g.A2) by_k<true, bf16, 1, true>(g, s);    // (launch_gemm_mfma admits that form only)
   else if (g.b_trans) { if (out_f32) by_k<true, float, 1>(g, s); else by_k<true, bf16, 1>(g, s); }

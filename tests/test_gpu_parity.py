@@ -158,6 +158,17 @@ def test_block_parity_small_problems(dtype, d, H, E, k, I, Is, B, S):
     _backward_checks(case, x1d, x2d, y1d, tol)
 
 
+# More routed work than the kernel for few rows takes: the tiles of the expert GEMMs with widths and row counts that end inside
+# them, at 50 rows per expert (128x256), 137 (160x256, 256x256, 256x128) and 391 (256x256 throughout)
+@pytest.mark.parametrize("E,k,I,B,S", [(24, 2, 600, 2, 300), (12, 3, 600, 2, 274), (6, 3, 440, 3, 261)])
+def test_block_parity_expert_tiles(E, k, I, B, S):
+    wl = synth.Workload(f"tiles_E{E}", 640, 5, 128, E, k, I, 0, B, S, "bf16", gain_jitter=0.02, seed=E)
+    case = Case(wl)
+    y1d, y2d, _ = _forward_checks(case, TOL["bf16"])
+    x1d, x2d = _inverse_checks(case, y1d, y2d, TOL["bf16"], 1)
+    _backward_checks(case, x1d, x2d, y1d, TOL["bf16"])
+
+
 # The dense layers' weight gradients are one launch, on the tile whose rounds over 256 CUs cost least for all of them
 # together: widths that give 216 tiles of 128x128 (one round of those), 172 of 256x128 (one round, against two of 128x128)
 # and 216 of 256x256 (in phases), each with tiles that end outside the results; 70 tokens: a second, partly filled k-tile.
