@@ -250,22 +250,6 @@ __global__ void __launch_bounds__(256, 2) flash_fwd_k(const bf16* __restrict__ q
   }
 }
 
-int launch_attn_fwd_flash(const void* q, const void* k, const void* v, void* o, float* lse, int B, int S, int H,
-                          int dh, int causal, hipStream_t s, const unsigned char* row_skip) {
-  if (dh != DH || B <= 0 || S <= 0) return 1;
-  if ((i64)S * H * DH * 2 >= ((i64)1 << 31)) return 1;      // one sequence of one tensor is addressed with 32-bit offsets
-  if (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o) & 15) return 1;
-  size_t smem = (size_t)2 * BKV * (KST + VST) * sizeof(bf16);
-  static std::atomic<unsigned long long> attr_mask{0};
-  if (attr_needed(attr_mask)) {
-    (void)hipFuncSetAttribute((const void*)flash_fwd_k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    attr_done(attr_mask);
-  }
-  hipLaunchKernelGGL(flash_fwd_k, dim3((unsigned)((i64)H * cdiv(S, 128) * B)), dim3(256), smem, s, (const bf16*)q, (const bf16*)k,
-                     (const bf16*)v, (bf16*)o, lse, B, S, H, causal, 1.0f / sqrtf((float)dh), row_skip);
-  return 0;
-}
-
 // ------------------------------------------------------------------------------------
 // Backward, part 1: dQ.  Workgroup = 128 queries, wave = 32 queries (one per lane column);
 // keys/values streamed in tiles of 64.  Per tile:
@@ -556,6 +540,316 @@ __global__ void __launch_bounds__(256, QB == 1 ? 2 : 1) flash_bwd_dkv_k(const bf
   }
 }
 
+// ------------------------------------------------------------------------------------
+// Short sequences.  With 128 queries (keys) per workgroup a short sequence leaves most CUs idle or gives each one chain over
+// all its key tiles: one wave per SIMD whose products, exponentials and loads follow each other.  Here a workgroup is 32
+// queries (keys) and its 4 waves share the keys (queries) out, tile w, w + 4, .. of 32, each in LDS of its own that no other
+// wave touches, so nothing waits at a barrier until the waves' partial results meet in LDS in wave order.  A wave's two
+// tiles (K and V, or Q and dO) are 16 KiB, two workgroups share a CU.  Every wave loads its tiles itself, four times the
+// traffic of the kernels above, which is what bounds this form once it fills the chip.  dQ and dK/dV are one launch.
+// ------------------------------------------------------------------------------------
+#define SHORT_TILE 8192u                          // 32 rows x 256 bytes, swizzled
+#define SHORT_SMEM (4 * 2 * SHORT_TILE + 2048)    // the waves' tiles (then their partial results), then statistics
+__device__ __forceinline__ void load_rows32_lds(const RowSlice& sl, int row0, unsigned dst, int lane) {
+  load_rows16_lds(sl, row0, dst, lane);
+  load_rows16_lds(sl, row0 + 16, dst + 4096u, lane);
+}
+// one row of 128 as operand fragments of a product over the head width; rows past the end are zeros
+__device__ __forceinline__ void load_frags(const bf16* base, i64 ld, int row, int S, int g, bf16x8 (&f)[8]) {
+#pragma unroll
+  for (int kk = 0; kk < 8; kk++) {
+    uint4 t = make_uint4(0, 0, 0, 0);
+    if (row < S) t = *(const uint4*)(base + (i64)row * ld + kk * 16 + g * 8);
+    f[kk] = __builtin_bit_cast(bf16x8, t);
+  }
+}
+// tile rows x fragments: element e of lane l is tile row (e >> 2) * 8 + (l >> 5) * 4 + (e & 3), column l & 31
+__device__ __forceinline__ f32x16 rows_times(const unsigned char* tile, unsigned rbase, const bf16x8 (&f)[8]) {
+  f32x16 a = {};
+#pragma unroll
+  for (int kk = 0; kk < 8; kk++) a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(tile + (rbase ^ (unsigned)(kk * 32))), f[kk], a, 0, 0, 0);
+  return a;
+}
+// acc^T[column, lane] += tile^T p
+__device__ __forceinline__ void cols_times(f32x16 (&acc)[4], const unsigned char* tile, unsigned cbase, const f32x16& p) {
+#pragma unroll
+  for (int c = 0; c < 2; c++) {
+    const bf16x8 f = acc_to_frag(p, c);
+#pragma unroll
+    for (int dtile = 0; dtile < 4; dtile++) acc[dtile] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(swz_cols(tile, cbase, c * 16, dtile), f, acc[dtile], 0, 0, 0);
+  }
+}
+// a wave's partial result to its 16 KiB: [column 128][row 32]
+__device__ __forceinline__ void put_partial(float* mine, const f32x16 (&acc)[4], int lane) {
+#pragma unroll
+  for (int dtile = 0; dtile < 4; dtile++)
+#pragma unroll
+    for (int e = 0; e < 16; e++) mine[(dtile * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3)) * 32 + (lane & 31)] = acc[dtile][e];
+}
+// the sum of the four, weighted (w), to row threadIdx.x & 31, 16 columns of it per thread
+__device__ __forceinline__ void store_partials(const float* part, const float (&w)[4], bf16* row, bool in) {
+  const int r = threadIdx.x & 31, c0 = (int)(threadIdx.x >> 5) * 16;
+  bf16x8 o[2];
+#pragma unroll
+  for (int i = 0; i < 16; i++) {
+    float v = 0.f;
+#pragma unroll
+    for (int j = 0; j < 4; j++) v += w[j] * part[j * 4096 + (c0 + i) * 32 + r];
+    o[i >> 3][i & 7] = (__bf16)v;
+  }
+  if (in) { *(bf16x8*)(row + c0) = o[0]; *(bf16x8*)(row + c0 + 8) = o[1]; }
+}
+
+__global__ void __launch_bounds__(256, 2) flash_fwd_short_k(const bf16* __restrict__ q, const bf16* __restrict__ k,
+                                                            const bf16* __restrict__ v, bf16* __restrict__ o, float* __restrict__ lse,
+                                                            int B, int S, int H, int causal, float scale,
+                                                            const unsigned char* __restrict__ row_skip) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
+  const int tiles = (S + 31) / 32, row = (int)blockIdx.x / H, hh = (int)blockIdx.x - row * H, b = row % B;
+  const int q0 = (tiles - 1 - row / B) * 32;        // late query tiles are the long ones
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 5, myq = q0 + (lane & 31);
+  if (row_skip && !__any(myq < S && row_skip[(i64)b * S + myq] == 0)) return;      // (the same answer in every wave)
+  const i64 ld = (i64)H * DH, boff = (i64)b * S * ld + hh * DH;
+  const RowSlice slK = row_slice(k + boff, ld, S), slV = row_slice(v + boff, ld, S);
+  unsigned char* tK = smem_raw + wv * 2 * SHORT_TILE;
+  const unsigned aK = lds_address(smem_raw) + (unsigned)wv * 2 * SHORT_TILE, aV = aK + SHORT_TILE;
+  const int nt = ((causal ? min(S, q0 + 32) : S) + 31) / 32;
+  const int none = tiles * 32;                      // (a tile that is not there: rows past the end, zeros without traffic)
+  load_rows32_lds(slK, wv < nt ? wv * 32 : none, aK, lane);
+  load_rows32_lds(slV, wv < nt ? wv * 32 : none, aV, lane);
+  bf16x8 qf[8];
+  load_frags(q + boff, ld, myq, S, g, qf);
+  const unsigned rbase = swz_row_base(lane), cbase = swz_col_base(lane);
+  const float sl2 = scale * LOG2E;
+  f32x16 acc[4] = {};
+  float m = -INFINITY, l = 0.f;
+  for (int t = wv; t < nt; t += 4) {
+    const int kv0 = t * 32, next = t + 4 < nt ? kv0 + 128 : none;
+    // (the fragments of Q were asked for after the first tile: nothing may be outstanding the first time)
+    if (t == wv) wait_vmcnt<0>(); else wait_vmcnt<8>();
+    f32x16 s = rows_times(tK, rbase, qf);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    load_rows32_lds(slK, next, aK, lane);
+    float mx = -INFINITY;
+    const bool need_mask = kv0 + 32 > S || (causal && kv0 + 31 > q0);
+#pragma unroll
+    for (int e = 0; e < 16; e++) {
+      const int kv = kv0 + (e >> 2) * 8 + g * 4 + (e & 3);
+      float sv = s[e] * sl2;
+      if (need_mask && (kv >= S || (causal && kv > myq))) sv = -INFINITY;
+      s[e] = sv;
+      mx = fmaxf(mx, sv);
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE));
+    const float mn = fmaxf(m, mx), ms = mn == -INFINITY ? 0.f : mn;
+    float rs = 0.f;
+#pragma unroll
+    for (int e = 0; e < 16; e++) { s[e] = fast_exp2(s[e] - ms); rs += s[e]; }
+    rs += __shfl_xor(rs, 32, WAVE);
+    if (__any(mn > m)) {
+      const float alpha = fast_exp2(m - ms);
+      l *= alpha;
+#pragma unroll
+      for (int i = 0; i < 4; i++) acc[i] *= alpha;
+    }
+    l += rs;
+    m = mn;
+    wait_vmcnt<8>();                                // V; the next K may be on its way
+    cols_times(acc, tK + SHORT_TILE, cbase, s);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    load_rows32_lds(slV, next, aV, lane);
+  }
+  wait_vmcnt<0>();
+  float* stats = (float*)(smem_raw + 8 * SHORT_TILE);
+  put_partial((float*)tK, acc, lane);
+  if (g == 0) { stats[wv * 64 + lane] = m; stats[wv * 64 + 32 + lane] = l; }
+  __syncthreads();
+  const int r = threadIdx.x & 31;
+  float M = -INFINITY, w[4], tot = 0.f;
+#pragma unroll
+  for (int j = 0; j < 4; j++) M = fmaxf(M, stats[j * 64 + r]);
+  const float Ms = M == -INFINITY ? 0.f : M;
+#pragma unroll
+  for (int j = 0; j < 4; j++) { w[j] = fast_exp2(stats[j * 64 + r] - Ms); tot += w[j] * stats[j * 64 + 32 + r]; }
+  const float inv = 1.0f / tot;
+#pragma unroll
+  for (int j = 0; j < 4; j++) w[j] *= inv;
+  store_partials((const float*)smem_raw, w, o + boff + (i64)(q0 + r) * ld, q0 + r < S);
+  if (threadIdx.x < 32 && q0 + r < S) lse[((i64)b * H + hh) * S + q0 + r] = (M + __log2f(tot)) * LN2;
+}
+
+// dQ of 32 queries
+__device__ __forceinline__ void short_dq(unsigned char* smem_raw, int tile, int b, int hh, const bf16* q, const bf16* k, const bf16* v,
+                                         const bf16* d_o, const float* lse, const float* dvec, bf16* dq, int S, int H, int causal, float scale) {
+  const int q0 = ((S + 31) / 32 - 1 - tile) * 32;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 5, myq = q0 + (lane & 31);
+  const i64 ld = (i64)H * DH, boff = (i64)b * S * ld + hh * DH, soff = ((i64)b * H + hh) * S;
+  const RowSlice slK = row_slice(k + boff, ld, S), slV = row_slice(v + boff, ld, S);
+  unsigned char* tK = smem_raw + wv * 2 * SHORT_TILE;
+  const unsigned aK = lds_address(smem_raw) + (unsigned)wv * 2 * SHORT_TILE, aV = aK + SHORT_TILE;
+  const int nt = ((causal ? min(S, q0 + 32) : S) + 31) / 32;
+  if (wv < nt) {
+    load_rows32_lds(slV, wv * 32, aV, lane);
+    load_rows32_lds(slK, wv * 32, aK, lane);
+  }
+  bf16x8 qf[8], dof[8];
+  load_frags(q + boff, ld, myq, S, g, qf);
+  load_frags(d_o + boff, ld, myq, S, g, dof);
+  const float L = myq < S ? lse[soff + myq] * LOG2E : 0.f, D = myq < S ? dvec[soff + myq] : 0.f;
+  const unsigned rbase = swz_row_base(lane), cbase = swz_col_base(lane);
+  const float sl2 = scale * LOG2E;
+  f32x16 acc[4] = {};
+  for (int t = wv; t < nt; t += 4) {
+    const int kv0 = t * 32;
+    wait_vmcnt<0>();
+    f32x16 dp = rows_times(tK + SHORT_TILE, rbase, dof);
+    f32x16 s = rows_times(tK, rbase, qf);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    if (t + 4 < nt) load_rows32_lds(slV, kv0 + 128, aV, lane);
+    const bool need_mask = kv0 + 32 > S || (causal && kv0 + 31 > q0);
+#pragma unroll
+    for (int e = 0; e < 16; e++) {
+      const int kv = kv0 + (e >> 2) * 8 + g * 4 + (e & 3);
+      float p = fast_exp2(s[e] * sl2 - L);
+      if (need_mask && (kv >= S || (causal && kv > myq))) p = 0.f;
+      s[e] = p * (dp[e] - D) * scale;
+    }
+    cols_times(acc, tK, cbase, s);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    if (t + 4 < nt) load_rows32_lds(slK, kv0 + 128, aK, lane);
+  }
+  put_partial((float*)tK, acc, lane);
+  __syncthreads();
+  const float w[4] = {1.f, 1.f, 1.f, 1.f};
+  const int r = threadIdx.x & 31;
+  store_partials((const float*)smem_raw, w, dq + boff + (i64)(q0 + r) * ld, q0 + r < S);
+}
+// dK, dV of 32 keys
+__device__ __forceinline__ void short_dkv(unsigned char* smem_raw, int tile, int b, int hh, const bf16* q, const bf16* k, const bf16* v,
+                                          const bf16* d_o, const float* lse, const float* dvec, bf16* dk, bf16* dv, int S, int H,
+                                          int causal, float scale) {
+  const int k0 = tile * 32, nt = (S + 31) / 32;     // early key tiles see the most queries
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 5, mykv = k0 + (lane & 31);
+  const i64 ld = (i64)H * DH, boff = (i64)b * S * ld + hh * DH, soff = ((i64)b * H + hh) * S;
+  const RowSlice slQ = row_slice(q + boff, ld, S), slO = row_slice(d_o + boff, ld, S);
+  const __amdgpu_buffer_rsrc_t rsL = __builtin_amdgcn_make_buffer_rsrc((void*)(lse + soff), (short)0, S * 4, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rsD = __builtin_amdgcn_make_buffer_rsrc((void*)(dvec + soff), (short)0, S * 4, 0x00020000);
+  unsigned char* tQ = smem_raw + wv * 2 * SHORT_TILE;
+  const unsigned aQ = lds_address(smem_raw) + (unsigned)wv * 2 * SHORT_TILE, aO = aQ + SHORT_TILE;
+  // statistics of the tile, lse and D (a load brings 64, of which 32 are used)
+  float* st = (float*)(smem_raw + 8 * SHORT_TILE) + wv * 128;
+  const unsigned aS = lds_address(smem_raw) + 8 * SHORT_TILE + (unsigned)wv * 512u;
+  auto stats = [&](int row0) {
+    load_stats64_lds(rsL, row0, aS, lane);
+    load_stats64_lds(rsD, row0, aS + 256u, lane);
+  };
+  const int t0 = (causal ? tile : 0) + wv;
+  if (t0 < nt) {
+    load_rows32_lds(slQ, t0 * 32, aQ, lane);
+    load_rows32_lds(slO, t0 * 32, aO, lane);
+    stats(t0 * 32);
+  }
+  bf16x8 kf[8], vf[8];
+  load_frags(k + boff, ld, mykv, S, g, kf);
+  load_frags(v + boff, ld, mykv, S, g, vf);
+  const unsigned rbase = swz_row_base(lane), cbase = swz_col_base(lane);
+  const float sl2 = scale * LOG2E;
+  f32x16 dka[4] = {}, dva[4] = {};
+  for (int t = t0; t < nt; t += 4) {
+    const int q0 = t * 32;
+    wait_vmcnt<0>();
+    f32x16 s = rows_times(tQ, rbase, kf);
+    f32x16 dp = rows_times(tQ + SHORT_TILE, rbase, vf);
+    const bool need_mask = causal && q0 < k0 + 31;
+#pragma unroll
+    for (int eb = 0; eb < 4; eb++) {
+      const int r0 = eb * 8 + g * 4;
+      const float4 l4 = *(const float4*)(st + r0), d4 = *(const float4*)(st + 64 + r0);
+      const float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dv4[4] = {d4.x, d4.y, d4.z, d4.w};
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        const int e = eb * 4 + i;
+        float p = fast_exp2(s[e] * sl2 - lv[i] * LOG2E);
+        if (need_mask && mykv > q0 + r0 + i) p = 0.f;
+        dp[e] = p * (dp[e] - dv4[i]) * scale;
+        s[e] = p;
+      }
+    }
+    cols_times(dva, tQ + SHORT_TILE, cbase, s);
+    cols_times(dka, tQ, cbase, dp);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    if (t + 4 < nt) {
+      load_rows32_lds(slQ, q0 + 128, aQ, lane);
+      load_rows32_lds(slO, q0 + 128, aO, lane);
+      stats(q0 + 128);
+    }
+  }
+  const float w[4] = {1.f, 1.f, 1.f, 1.f};
+  const int r = threadIdx.x & 31;
+  const i64 at = boff + (i64)(k0 + r) * ld;
+  put_partial((float*)tQ, dka, lane);
+  __syncthreads();
+  store_partials((const float*)smem_raw, w, dk + at, k0 + r < S);
+  __syncthreads();
+  put_partial((float*)tQ, dva, lane);
+  __syncthreads();
+  store_partials((const float*)smem_raw, w, dv + at, k0 + r < S);
+}
+// rows of H workgroups, by turns dK/dV and dQ, long tiles first in both
+__global__ void __launch_bounds__(256, 2) flash_bwd_short_k(const bf16* __restrict__ q, const bf16* __restrict__ k, const bf16* __restrict__ v,
+                                                            const bf16* __restrict__ d_o, const float* __restrict__ lse,
+                                                            const float* __restrict__ dvec, bf16* __restrict__ dq, bf16* __restrict__ dk,
+                                                            bf16* __restrict__ dv, int B, int S, int H, int causal, float scale) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
+  const int row = (int)blockIdx.x / H, hh = (int)blockIdx.x - row * H, tile = (row >> 1) / B, b = (row >> 1) - tile * B;
+  if (row & 1) short_dq(smem_raw, tile, b, hh, q, k, v, d_o, lse, dvec, dq, S, H, causal, scale);
+  else short_dkv(smem_raw, tile, b, hh, q, k, v, d_o, lse, dvec, dk, dv, S, H, causal, scale);
+}
+
+// Which form a problem takes.  Measured, us, forward / all of the backward pass, 128 queries per workgroup -> 32:
+//   16 heads: 1 x 128 9.5 / 27 -> 8.0 / 12    3 x 333 15 / 52 -> 13 / 33    1 x 1024 30 / 104 -> 18 / 42    1 x 2048 56 / 195 -> 39 / 120
+//             4 x 512 19.7 / 69 -> 19.6 / 60    8 x 256 14 / 50 -> 17 / 55    16 x 128 11 / 40 -> 15 / 47    8 x 512 24 / 95 -> 38 / 131
+//   4 heads: 2 x 200 11 / 36 -> 8.4 / 13    1 x 2048 52 / 186 -> 24 / 43    32 heads: 1 x 1024 33 / 115 -> 26 / 74    4 x 256 14 / 49 -> 16 / 49
+// Alone it pays up to two workgroups per CU and up to four for long chains.  Inside a step, where the attention shares the chip
+// with the routed experts, CU time counts too: 4 x 512 tokens 2793 -> 2820 us per step, 1 x 1024 2190 -> 2158, 1 x 1300 2460 ->
+// 2438, so the line is at 1024 tokens of 16 heads, 2048 from 1024 positions on.  The heads count coarsely, and more than 16 as
+// 18: the two forms add in different orders, and the same heads a few at a time and all together mostly agree to the bit.
+static bool short_sequence(int B, int S, int H) {
+  const i64 load = (i64)B * S * (H <= 4 ? 4 : H <= 8 ? 8 : H <= 16 ? 16 : 18) / 16;
+  return S <= 2048 && (load <= 1024 || (load <= 2048 && S >= 1024));
+}
+
+int launch_attn_fwd_flash(const void* q, const void* k, const void* v, void* o, float* lse, int B, int S, int H,
+                          int dh, int causal, hipStream_t s, const unsigned char* row_skip) {
+  if (dh != DH || B <= 0 || S <= 0) return 1;
+  if ((i64)S * H * DH * 2 >= ((i64)1 << 31)) return 1;      // one sequence of one tensor is addressed with 32-bit offsets
+  if (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o) & 15) return 1;
+  if (short_sequence(B, S, H)) {
+    static std::atomic<unsigned long long> attr_mask{0};
+    if (attr_needed(attr_mask)) {
+      (void)hipFuncSetAttribute((const void*)flash_fwd_short_k, hipFuncAttributeMaxDynamicSharedMemorySize, SHORT_SMEM);
+      attr_done(attr_mask);
+    }
+    hipLaunchKernelGGL(flash_fwd_short_k, dim3((unsigned)((i64)H * cdiv(S, 32) * B)), dim3(256), SHORT_SMEM, s, (const bf16*)q, (const bf16*)k,
+                       (const bf16*)v, (bf16*)o, lse, B, S, H, causal, 1.0f / sqrtf((float)dh), row_skip);
+    return 0;
+  }
+  size_t smem = (size_t)2 * BKV * (KST + VST) * sizeof(bf16);
+  static std::atomic<unsigned long long> attr_mask{0};
+  if (attr_needed(attr_mask)) {
+    (void)hipFuncSetAttribute((const void*)flash_fwd_k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    attr_done(attr_mask);
+  }
+  hipLaunchKernelGGL(flash_fwd_k, dim3((unsigned)((i64)H * cdiv(S, 128) * B)), dim3(256), smem, s, (const bf16*)q, (const bf16*)k,
+                     (const bf16*)v, (bf16*)o, lse, B, S, H, causal, 1.0f / sqrtf((float)dh), row_skip);
+  return 0;
+}
+
 int launch_attn_bwd_flash(const void* q, const void* k, const void* v, const void* o, const void* d_o,
                           const float* lse, float* dvec, void* dq, void* dk, void* dv, int B, int S, int H, int dh,
                           int causal, hipStream_t s) {
@@ -566,6 +860,16 @@ int launch_attn_bwd_flash(const void* q, const void* k, const void* v, const voi
     return 1;
   launch_attn_dvec(1, o, d_o, dvec, B, S, H, dh, s);
   const float scale = 1.0f / sqrtf((float)dh);
+  if (short_sequence(B, S, H)) {
+    static std::atomic<unsigned long long> attr_mask{0};
+    if (attr_needed(attr_mask)) {
+      (void)hipFuncSetAttribute((const void*)flash_bwd_short_k, hipFuncAttributeMaxDynamicSharedMemorySize, SHORT_SMEM);
+      attr_done(attr_mask);
+    }
+    hipLaunchKernelGGL(flash_bwd_short_k, dim3((unsigned)((i64)2 * H * cdiv(S, 32) * B)), dim3(256), SHORT_SMEM, s, (const bf16*)q, (const bf16*)k,
+                       (const bf16*)v, (const bf16*)d_o, lse, dvec, (bf16*)dq, (bf16*)dk, (bf16*)dv, B, S, H, causal, scale);
+    return 0;
+  }
   size_t sm1 = (size_t)4 * BKV * BST * sizeof(bf16);
   size_t sm2 = 2 * DKV_STAGE;
   static std::atomic<unsigned long long> attr_mask{0};

@@ -127,7 +127,9 @@ def _attention_case(B, S, H, dh, causal, mode, dtype, offset=0):
 
 
 @pytest.mark.parametrize("causal", [True, False])
-@pytest.mark.parametrize("B,S,H", [(1, 128, 1), (2, 200, 3), (1, 64, 2), (1, 1, 1), (1, 451, 2)])
+# (one query, one past a tile of 32, fewer tiles of keys than the four waves that share them and more, several batches; the last:
+# 128 queries per workgroup)
+@pytest.mark.parametrize("B,S,H", [(1, 128, 1), (2, 200, 3), (1, 64, 2), (1, 1, 1), (1, 451, 2), (3, 33, 5), (1, 161, 17), (5, 97, 2), (6, 400, 17)])
 def test_flash_attention(B, S, H, causal):
     _attention_case(B, S, H, 128, causal, 2, 1)
 
@@ -156,17 +158,18 @@ def test_vector_attention(dtype, dh, offset):
     _attention_case(1, 261, 1, dh, False, 1, dtype, offset)
 
 
-# more workgroups than CUs and no more than two for each: the second part of the grid runs in reverse (48 and 100 heads: a
-# whole and a broken row of heads where it starts)
-@pytest.mark.parametrize("B,S,H", [(2, 451, 48), (1, 300, 100)])
+# 128 queries per workgroup, more workgroups than CUs and no more than two for each: the second part of the grid runs in
+# reverse (16 and 24 heads: a whole and a broken row of heads where it starts); 48 and 100 heads of short sequences: 32 queries
+# per workgroup
+@pytest.mark.parametrize("B,S,H", [(2, 451, 48), (1, 300, 100), (1, 2200, 16), (1, 2100, 24)])
 def test_flash_attention_paired_tiles(B, S, H):
     _attention_case(B, S, H, 128, True, 2, 1)
 
 
 # more heads than 256 workgroups take, against the same heads a quarter at a time (one workgroup per CU): dK/dV works on 32
-# queries at a time in the one and 64 in the other, in the same order
+# queries at a time in the one and 64 in the other, in the same order (2100 tokens; the short sequences have one form)
 @pytest.mark.parametrize("causal", [True, False])
-@pytest.mark.parametrize("B,S,H", [(2, 451, 48), (1, 129, 160), (8, 33, 40)])
+@pytest.mark.parametrize("B,S,H", [(2, 451, 48), (1, 129, 160), (8, 33, 40), (1, 2100, 20)])
 def test_flash_attention_gradients_do_not_depend_on_the_grid(B, S, H, causal):
     rng = np.random.default_rng(S + H)
     q, k, v, do = (Hn.upload(_bf(rng, (B * S, H * 128)), "bf16") for _ in range(4))
