@@ -160,7 +160,7 @@ size_t router_blocks(size_t Tn) { return (Tn + ROUTER_TOKENS - 1) / ROUTER_TOKEN
 // Permutation: a stable grouping of the T*k (token, slot) entries by expert.  The router kernel has counted, per block
 // of 16 tokens, the entries of every expert, so a block's first row inside every expert is a column sum of that table
 // and blocks need nothing of each other: one wave per block, 16 per workgroup, every workgroup adding the columns for
-// itself (one workgroup that counted and placed all entries took 13.5 us at T = 2048 and 52 us at T = 8192; now 7 and
+// itself (one workgroup that counted and placed all entries took 13.5 us at T = 2048 and 52 us at T = 8192; now 5 and
 // 8 us).  Inside its block a wave hands out rows in entry order, which keeps (token, slot) order inside an expert.
 // One more workgroup writes counts, offsets and the m-tile lists used by the grouped GEMMs: tile i covers rows
 // [tile_m0[i], min(tile_m0[i]+bm, offsets[g+1])) of expert g = tile_group[i]; unused = -1.
@@ -198,7 +198,10 @@ __global__ void __launch_bounds__(PERM_WAVES * 64) permute_k(
   int* off = next + PERM_WAVES * E;
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int b0 = blockIdx.x * PERM_WAVES;           // first block of this workgroup (the last workgroup has none)
-  // column sums: epad (E rounded up to a power of two) columns, 1024 / epad row lanes
+  // column sums: epad (E rounded up to a power of two) columns, 1024 / epad row lanes; those of one wave are added by
+  // exchanges, so that at most 16 partial sums per column are left (with 8 experts 128 of them, read one after the other, were
+  // 6 of the kernel's 10 us)
+  const int cols = max(epad, 64);         // columns per row of the partial sums
   {
     const int e = threadIdx.x & (epad - 1), part = threadIdx.x / epad, parts = PERM_WAVES * 64 / epad;
     int all = 0, before = 0;
@@ -210,6 +213,7 @@ __global__ void __launch_bounds__(PERM_WAVES * 64) permute_k(
         before += b < b0 ? c : 0;
       }
     }
+    for (int o = epad; o < 64; o <<= 1) { all += __shfl_xor(all, o, WAVE); before += __shfl_xor(before, o, WAVE); }
     csum[threadIdx.x] = all;
     csum[PERM_WAVES * 64 + threadIdx.x] = before;
   }
@@ -217,10 +221,18 @@ __global__ void __launch_bounds__(PERM_WAVES * 64) permute_k(
   __syncthreads();
   if (threadIdx.x < E) {
     const int e = threadIdx.x;
-    int all = 0, run = 0;
-    for (int i = e; i < PERM_WAVES * 64; i += epad) { all += csum[i]; run += csum[PERM_WAVES * 64 + i]; }
+    int all = 0, run = 0, c[PERM_WAVES];
+#pragma unroll
+    for (int i = 0; i < PERM_WAVES; i++) {
+      const bool in = i * cols < PERM_WAVES * 64;
+      all += in ? csum[i * cols + e] : 0;
+      run += in ? csum[PERM_WAVES * 64 + i * cols + e] : 0;
+    }
+#pragma unroll
+    for (int w = 0; w < PERM_WAVES; w++) c[w] = next[w * E + e];
     off[e + 1] = all;                     // totals for now
-    for (int w = 0; w < PERM_WAVES; w++) { const int c = next[w * E + e]; next[w * E + e] = run; run += c; }
+#pragma unroll
+    for (int w = 0; w < PERM_WAVES; w++) { next[w * E + e] = run; run += c[w]; }
   }
   __syncthreads();
   if (wv == 0) {                          // offsets = prefix sums of the totals, 64 experts per step
