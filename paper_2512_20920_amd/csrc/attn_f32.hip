@@ -10,7 +10,7 @@
 // results meet in LDS in wave order.  These are short sequences of few heads, and what bounds them is one wave's chain:
 // one workgroup per query on the vector units walked the keys twice, one fused multiply-add per loaded element.
 // Forward, dQ, dK/dV: 251 tokens, 3 x 4 heads of 64, bfloat16 storage: 55, 51, 56 -> 13, 14, 22 us; 700 tokens, 4 heads of
-// 128, float32: 262, 225, 232 -> 41, 61, 87.
+// 128, float32: 262, 225, 232 -> 41, 61, 87.  dQ and dK/dV are one launch (251 tokens: 15 + 23 -> 24 us).
 #include "kernels.h"
 
 typedef __attribute__((ext_vector_type(16))) float f32x16;
@@ -232,13 +232,10 @@ __device__ __forceinline__ void dq_keys(const T* k, const T* v, i64 ld, int S, i
   }
 }
 template <class T, int DH>
-__global__ void __launch_bounds__(NW * 64) attn_bwd_dq_f32_k(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
-                                                             const T* __restrict__ d_o, const float* __restrict__ lse,
-                                                             const float* __restrict__ dvec, T* __restrict__ dq, int S, int H,
-                                                             int causal, float scale) {
+__device__ __forceinline__ void bwd_dq(float* sm, int hh, int b, const T* q, const T* k, const T* v, const T* d_o, const float* lse,
+                                       const float* dvec, T* dq, int S, int H, int causal, float scale) {
   constexpr int DT = DH < 32 ? 1 : DH / 32;
-  extern __shared__ float sm[];
-  const int q0 = ((int)gridDim.x - 1 - (int)blockIdx.x) * 32, hh = blockIdx.y, b = blockIdx.z;
+  const int q0 = ((int)gridDim.x - 1 - (int)blockIdx.x) * 32;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, half = lane >> 5, myq = q0 + (lane & 31), qc = min(myq, S - 1);
   const i64 ld = (i64)H * DH, base = (i64)b * S * ld + (i64)hh * DH, stat = ((i64)b * H + hh) * S;
   float qf[DH / 2], dof[DH / 2];
@@ -292,13 +289,10 @@ __device__ __forceinline__ void dkv_queries(const T* q, const T* d_o, const floa
   }
 }
 template <class T, int DH>
-__global__ void __launch_bounds__(NW * 64) attn_bwd_dkv_f32_k(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
-                                                              const T* __restrict__ d_o, const float* __restrict__ lse,
-                                                              const float* __restrict__ dvec, T* __restrict__ dk, T* __restrict__ dv,
-                                                              int S, int H, int causal, float scale) {
+__device__ __forceinline__ void bwd_dkv(float* sm, int hh, int b, const T* q, const T* k, const T* v, const T* d_o, const float* lse,
+                                        const float* dvec, T* dk, T* dv, int S, int H, int causal, float scale) {
   constexpr int DT = DH < 32 ? 1 : DH / 32;
-  extern __shared__ float sm[];
-  const int k0 = (int)blockIdx.x * 32, hh = blockIdx.y, b = blockIdx.z;
+  const int k0 = (int)blockIdx.x * 32;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, half = lane >> 5, myk = k0 + (lane & 31), kc = min(myk, S - 1);
   const i64 ld = (i64)H * DH, base = (i64)b * S * ld + (i64)hh * DH, stat = ((i64)b * H + hh) * S;
   float kf[DH / 2], vf[DH / 2];
@@ -327,6 +321,18 @@ __global__ void __launch_bounds__(NW * 64) attn_bwd_dkv_f32_k(const T* __restric
   store_sum<T, DH>(sm, dv + base, ld, k0, S, 1.f);
 }
 
+// Both in one launch (grid z: dK/dV of every batch, then dQ): neither fills the chip.
+template <class T, int DH>
+__global__ void __launch_bounds__(NW * 64) attn_bwd_f32_k(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
+                                                          const T* __restrict__ d_o, const float* __restrict__ lse,
+                                                          const float* __restrict__ dvec, T* __restrict__ dq, T* __restrict__ dk,
+                                                          T* __restrict__ dv, int B, int S, int H, int causal, float scale) {
+  extern __shared__ float sm[];
+  const int b = blockIdx.z;
+  if (b < B) bwd_dkv<T, DH>(sm, blockIdx.y, b, q, k, v, d_o, lse, dvec, dk, dv, S, H, causal, scale);
+  else bwd_dq<T, DH>(sm, blockIdx.y, b - B, q, k, v, d_o, lse, dvec, dq, S, H, causal, scale);
+}
+
 // rows are read 4 elements at a time
 static bool takes(int dt, int dh, const void* a, const void* b, const void* c, const void* d) {
   const uintptr_t mask = dt == 0 ? 15 : 7;
@@ -351,16 +357,11 @@ static void bwd(const void* q, const void* k, const void* v, const void* d_o, co
   constexpr size_t smem = (size_t)NW * 32 * (DH + 1) * 4;
   static std::atomic<unsigned long long> attr_mask{0};
   if (attr_needed(attr_mask)) {
-    (void)hipFuncSetAttribute((const void*)attn_bwd_dq_f32_k<T, DH>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    (void)hipFuncSetAttribute((const void*)attn_bwd_dkv_f32_k<T, DH>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    (void)hipFuncSetAttribute((const void*)attn_bwd_f32_k<T, DH>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     attr_done(attr_mask);
   }
-  const dim3 grid(cdiv(S, 32), H, B);
-  const float scale = 1.0f / sqrtf((float)DH);
-  hipLaunchKernelGGL((attn_bwd_dq_f32_k<T, DH>), grid, dim3(NW * 64), smem, s, (const T*)q, (const T*)k, (const T*)v,
-                     (const T*)d_o, lse, dvec, (T*)dq, S, H, causal, scale);
-  hipLaunchKernelGGL((attn_bwd_dkv_f32_k<T, DH>), grid, dim3(NW * 64), smem, s, (const T*)q, (const T*)k, (const T*)v,
-                     (const T*)d_o, lse, dvec, (T*)dk, (T*)dv, S, H, causal, scale);
+  hipLaunchKernelGGL((attn_bwd_f32_k<T, DH>), dim3(cdiv(S, 32), H, 2 * B), dim3(NW * 64), smem, s, (const T*)q, (const T*)k, (const T*)v,
+                     (const T*)d_o, lse, dvec, (T*)dq, (T*)dk, (T*)dv, B, S, H, causal, 1.0f / sqrtf((float)DH));
 }
 
 #define BY_WIDTH(T, call)                                  \
