@@ -731,7 +731,13 @@ static void pick_tile(const GemmArgs& g, hipStream_t s) {
     // multiplied zero rows), and all but the last are in flight at once: these kernels 10 % faster, a step 1.1 %.
     // (5 stages: 8 % slower again; 3: the same.)
     // (The tile in phases is 6-25 % slower here at 8 to 546 rows per expert.)
-    if constexpr (AT && BT) { go<256, 256, 2, AT, BT, TC, 8, 4, 32>(g, s); return; }
+    // All that holds from about one such tile per CU on.  With fewer (small blocks) 128x64 tiles put eight times the CUs to
+    // work: a 512-wide block of 12 experts (48 and 24 tiles), 400 tokens 354 -> 344 us per step, 1536 tokens 518 -> 499.
+    if constexpr (AT && BT) {
+      if ((i64)cdiv(g.M, 256) * cdiv(g.N, 256) * g.n_groups <= 256) go_128x64<AT, BT, TC>(g, s);
+      else go<256, 256, 2, AT, BT, TC, 8, 4, 32>(g, s);
+      return;
+    }
     return;                                            // (launch_gemm_mfma admits this mode for that layout only)
   }
   // below ~200 tiles of 128x128: 128x64 (two workgroups per CU)
