@@ -9,9 +9,9 @@
 // waves' partial tiles are added in wave order through LDS.  No LDS staging: inside a workgroup no two waves want the
 // same element.  At T = 400, d = 512 (float32) a GEMM of 400 x 512 x 512 takes 4 us where the LDS-tiled vector kernel
 // that it replaced took 64 us (56 workgroups, one dependent load -> LDS -> barrier chain per 16 k's).
-#include "kernels.h"
-
+#include "lds_load.h"
 #include "operand_f32.h"
+#include <type_traits>
 
 // waves that share a contraction of k: one per chunk, at most `most`
 __host__ __device__ inline int f32_k_waves(int k, int R, int most) {
@@ -21,44 +21,11 @@ __host__ __device__ inline int f32_k_waves(int k, int R, int most) {
 }
 
 // ACT: a gate/up GEMM (TM = 1, TN = 2): the two column blocks are gate columns n0 .. and the up columns of the same indices
-template <class TA, class TB, class TC, class TS, bool AT, bool BT, int R, int TM, int TN, bool ACT>
-__device__ __forceinline__ void f32_tile(const GemmArgs& g, const TA* A, const TB* Bm, TC* C, const TS* bias, int m0, int m_end,
-                                         int n0, int k0, int k_end, int nw, const TA* A2, const TB* B2) {
-  extern __shared__ __attribute__((aligned(16))) float part[];      // [waves][R TM][R TN]
+// End of a tile: the waves' partial tiles are added and go through the epilogue.
+template <class TC, class TS, int R, int TM, int TN, bool ACT, class Acc>
+__device__ __forceinline__ void f32_finish(const GemmArgs& g, TC* C, const TS* bias, float* part, const Acc (&acc)[TM][TN], int parts, int wv,
+                                           int lane, int m0, int m_end, int n0) {
   constexpr int BM = R * TM, BN = R * TN, EL = R * R / 64;   // (EL elements of a tile per lane)
-  const int lane = threadIdx.x & 63, gh = lane / R, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  typename AccOf<R>::type acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; i++)
-#pragma unroll
-    for (int j = 0; j < TN; j++)
-#pragma unroll
-      for (int e = 0; e < EL; e++) acc[i][j][e] = 0.f;
-  const int nchunk = (k_end - k0 + GKC(R) - 1) / GKC(R), all = A2 ? 2 * nchunk : nchunk;
-  const int parts = min(nw, max(all, 1));
-  // this wave's chunks of one pair of operands; the second pair goes on dealing where the first ended
-  auto contract = [&](const TA* pa, const TB* pb, int first) {
-    if (wv >= nw || first >= nchunk) return;
-    Operand<TA, AT, R> oa[TM];
-    Operand<TB, BT, R> ob[TN];
-#pragma unroll
-    for (int i = 0; i < TM; i++) oa[i].init(pa, g.lda, m0 + R * i, m_end, lane, g.a_gather, g.gather_div, k0, (const TA*)g.a_last_row);
-#pragma unroll
-    for (int j = 0; j < TN; j++) {
-      if (ACT) ob[j].init(pb, g.ldb, j * g.act_half + n0, (j + 1) * g.act_half, lane, nullptr, 1, k0);
-      else ob[j].init(pb, g.ldb, n0 + R * j, g.N, lane, nullptr, 1, k0);
-    }
-    k_loop<R, TM, TN>(oa, ob, k0, k_end, first, nw, nchunk, gh, [&](float (&a)[TM][16], float (&b)[TN][16]) {
-#pragma unroll
-      for (int s = 0; s < 16; s++)
-#pragma unroll
-        for (int i = 0; i < TM; i++)
-#pragma unroll
-          for (int j = 0; j < TN; j++) acc[i][j] = mfma_f32(a[i][s], b[j][s], acc[i][j]);
-    });
-  };
-  contract(A, Bm, wv);
-  if (A2) contract(A2, B2, (wv + nw - nchunk % nw) % nw);
   // ---- partial tiles to LDS, added in wave order by all threads, then the epilogue on whole output rows
   if (wv < parts) {
     float* mine = part + wv * (BM * BN);
@@ -136,6 +103,139 @@ __device__ __forceinline__ void f32_tile(const GemmArgs& g, const TA* A, const T
 }
 
 template <class TA, class TB, class TC, class TS, bool AT, bool BT, int R, int TM, int TN, bool ACT>
+__device__ __forceinline__ void f32_tile(const GemmArgs& g, const TA* A, const TB* Bm, TC* C, const TS* bias, int m0, int m_end,
+                                         int n0, int k0, int k_end, int nw, const TA* A2, const TB* B2) {
+  extern __shared__ __attribute__((aligned(16))) float part[];      // [waves][R TM][R TN]
+  constexpr int EL = R * R / 64;
+  const int lane = threadIdx.x & 63, gh = lane / R, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  typename AccOf<R>::type acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; i++)
+#pragma unroll
+    for (int j = 0; j < TN; j++)
+#pragma unroll
+      for (int e = 0; e < EL; e++) acc[i][j][e] = 0.f;
+  const int nchunk = (k_end - k0 + GKC(R) - 1) / GKC(R), all = A2 ? 2 * nchunk : nchunk;
+  const int parts = min(nw, max(all, 1));
+  // this wave's chunks of one pair of operands; the second pair goes on dealing where the first ended
+  auto contract = [&](const TA* pa, const TB* pb, int first) {
+    if (wv >= nw || first >= nchunk) return;
+    Operand<TA, AT, R> oa[TM];
+    Operand<TB, BT, R> ob[TN];
+#pragma unroll
+    for (int i = 0; i < TM; i++) oa[i].init(pa, g.lda, m0 + R * i, m_end, lane, g.a_gather, g.gather_div, k0, (const TA*)g.a_last_row);
+#pragma unroll
+    for (int j = 0; j < TN; j++) {
+      if (ACT) ob[j].init(pb, g.ldb, j * g.act_half + n0, (j + 1) * g.act_half, lane, nullptr, 1, k0);
+      else ob[j].init(pb, g.ldb, n0 + R * j, g.N, lane, nullptr, 1, k0);
+    }
+    k_loop<R, TM, TN>(oa, ob, k0, k_end, first, nw, nchunk, gh, [&](float (&a)[TM][16], float (&b)[TN][16]) {
+#pragma unroll
+      for (int s = 0; s < 16; s++)
+#pragma unroll
+        for (int i = 0; i < TM; i++)
+#pragma unroll
+          for (int j = 0; j < TN; j++) acc[i][j] = mfma_f32(a[i][s], b[j][s], acc[i][j]);
+    });
+  };
+  contract(A, Bm, wv);
+  if (A2) contract(A2, B2, (wv + nw - nchunk % nw) % nw);
+  f32_finish<TC, TS, R, TM, TN, ACT>(g, C, bias, part, acc, parts, wv, lane, m0, m_end, n0);
+}
+
+// The same for float32 operands on 16-byte boundaries (see staged_ok): a wave's pieces of 32 k's go straight into LDS that no
+// other wave touches, one piece in flight while the one before it is multiplied.  Loaded into registers by the lane that needs
+// them, the 4 k's of a row that runs along k put every lane on a cache line of its own, which a CU's waves then fetch
+// several times over (QKV of 400 tokens, d = 512: 21 us).
+//  * operand with k along memory: 128-byte rows, 16-byte chunk c of row r in slot c ^ ((r >> 1) & 7);
+//  * operand stored k x rows: 32 rows of 128 bytes, k in row k ^ ((k >> 2) & 1), so that the two k's (4 apart) that the halves of
+//    a wave read at a time lie in different halves of the banks.
+template <bool TR> struct StagedF32 {
+  u32x4 d;
+  unsigned off[4];
+  int kc[4];                // k of this lane's share of wave-load i, relative to the piece
+  unsigned ks;              // bytes per k
+  __device__ __forceinline__ void init(const float* p, i64 ld, int r0, int r_end, int lane, const int* gather, int div) {
+    d = make_desc(p);
+    const unsigned ldb = (unsigned)ld * 4u;
+    ks = TR ? ldb : 4u;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      if (!TR) {
+        const int r = i * 8 + (lane >> 3), ch = (lane & 7) ^ ((r >> 1) & 7), row = min(r0 + r, r_end - 1);
+        kc[i] = ch * 4;
+        off[i] = (unsigned)(gather ? gather[row] / div : row) * ldb + (unsigned)ch * 16u;
+      } else {
+        const int slot = i * 8 + (lane >> 3), col = r0 + (lane & 7) * 4;
+        kc[i] = slot ^ ((slot >> 2) & 1);
+        off[i] = col < r_end ? (unsigned)kc[i] * ldb + (unsigned)col * 4u : OOB;
+      }
+    }
+  }
+  __device__ __forceinline__ void issue(unsigned lds, int k0, int k_end) const {
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+      load_lds_b128(d, __builtin_amdgcn_readfirstlane(lds + i * 1024u), k0 + kc[i] < k_end && off[i] != OOB ? off[i] + (unsigned)k0 * ks : OOB);
+  }
+  // what the lane feeds to the 16 steps: step 4 j + i takes k = 8 j + 4 (lane >> 5) + i
+  __device__ __forceinline__ static void read(const unsigned char* t, int lane, float (&v)[16]) {
+    const int half = lane >> 5, r = lane & 31;
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+      if (!TR) {
+        const float4 x = *(const float4*)(t + r * 128 + ((2 * j + half) ^ ((r >> 1) & 7)) * 16);
+        v[4 * j] = x.x; v[4 * j + 1] = x.y; v[4 * j + 2] = x.z; v[4 * j + 3] = x.w;
+      } else
+#pragma unroll
+        for (int i = 0; i < 4; i++) v[4 * j + i] = *(const float*)(t + ((8 * j + 4 * half + i) ^ half) * 128 + r * 4);
+    }
+  }
+};
+template <bool AT, bool BT, bool ACT>
+__device__ __forceinline__ void f32_tile_staged(const GemmArgs& g, const float* A, const float* Bm, float* C, const float* bias, int m0, int m_end,
+                                                int n0, int k0, int k_end, int nw, const float* A2, const float* B2) {
+  constexpr int TN = ACT ? 2 : 1;
+  constexpr unsigned STAGE = (1 + TN) * 4096u;
+  extern __shared__ __attribute__((aligned(1024))) float part[];    // the waves' pieces, then their partial tiles
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  f32x16 acc[1][TN] = {};
+  const int nchunk = (k_end - k0 + 31) / 32, all = A2 ? 2 * nchunk : nchunk;
+  const int parts = min(nw, max(all, 1));
+  unsigned char* mine = (unsigned char*)part + wv * STAGE;
+  const unsigned lds = lds_address(part) + (unsigned)wv * STAGE;
+  if (wv < parts && all > 0) {
+    StagedF32<AT> oa;
+    StagedF32<BT> ob[TN];
+    oa.init(A, g.lda, m0, m_end, lane, AT ? nullptr : g.a_gather, g.gather_div);
+#pragma unroll
+    for (int j = 0; j < TN; j++) ob[j].init(Bm, g.ldb, ACT ? j * g.act_half + n0 : n0, ACT ? (j + 1) * g.act_half : g.N, lane, nullptr, 1);
+    auto issue = [&](int c) {                        // (a piece of the second pair of operands: the same offsets)
+      if (A2 && c >= nchunk) { oa.d = make_desc(A2); ob[0].d = make_desc(B2); c -= nchunk; }
+      oa.issue(lds, k0 + c * 32, k_end);
+#pragma unroll
+      for (int j = 0; j < TN; j++) ob[j].issue(lds + (1 + j) * 4096u, k0 + c * 32, k_end);
+    };
+    issue(wv);
+    for (int c = wv; c < all; c += nw) {
+      wait_vmcnt<0>();
+      float a[16], b[TN][16];
+      StagedF32<AT>::read(mine, lane, a);
+#pragma unroll
+      for (int j = 0; j < TN; j++) StagedF32<BT>::read(mine + (1 + j) * 4096, lane, b[j]);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");            // the piece is in registers: its place is free
+      __builtin_amdgcn_sched_barrier(0);
+      if (c + nw < all) issue(c + nw);
+#pragma unroll
+      for (int s = 0; s < 16; s++)
+#pragma unroll
+        for (int j = 0; j < TN; j++) acc[0][j] = mfma_f32(a[s], b[j][s], acc[0][j]);
+    }
+  }
+  __syncthreads();                                   // the partial tiles overlay the pieces
+  f32_finish<float, float, 32, 1, TN, ACT>(g, C, bias, part, acc, parts, wv, lane, m0, m_end, n0);
+}
+
+template <class TA, class TB, class TC, class TS, bool AT, bool BT, int R, int TM, int TN, bool ACT, bool STG>
 __global__ void __launch_bounds__(R == 16 ? 1024 : 512) gemm_f32_k(GemmArgs g) {
   constexpr int BM = R * TM, BN = ACT ? R : R * TN;
   const TA *A = (const TA*)g.A, *A2 = (const TA*)g.A2;
@@ -168,12 +268,14 @@ __global__ void __launch_bounds__(R == 16 ? 1024 : 512) gemm_f32_k(GemmArgs g) {
     for (int r = m0 + (int)(threadIdx.x & 63); r < min(m_end, m0 + BM); r += 64) live |= g.row_skip[r] == 0;
     if (!__any(live)) return;
   }
-  f32_tile<TA, TB, TC, TS, AT, BT, R, TM, TN, ACT>(g, A, Bm, C, bias, m0, m_end, blockIdx.x * BN, k0, k_end, g.k_waves, A2, B2);
+  if constexpr (STG) f32_tile_staged<AT, BT, ACT>(g, A, Bm, C, bias, m0, m_end, blockIdx.x * BN, k0, k_end, g.k_waves, A2, B2);
+  else f32_tile<TA, TB, TC, TS, AT, BT, R, TM, TN, ACT>(g, A, Bm, C, bias, m0, m_end, blockIdx.x * BN, k0, k_end, g.k_waves, A2, B2);
 }
 
 // The weight gradients of several dense layers as one launch, tiles numbered over the problems: alone each is a launch of one
 // to a few hundred workgroups that mostly wait for their loads (ten of them at 400 tokens, d = 512: 95 us, together 48).  The sum is
 // cut as in a launch of its own, so the bits are the same.
+template <bool STG>
 __global__ void __launch_bounds__(512) gemm_f32_batch_tn_k(GemmBatch b) {
   typedef const __attribute__((address_space(4))) GemmBatch* KernArg;     // (indexed in the kernel-argument segment)
   const KernArg ka = (KernArg)__builtin_amdgcn_kernarg_segment_ptr();
@@ -183,25 +285,44 @@ __global__ void __launch_bounds__(512) gemm_f32_batch_tn_k(GemmBatch b) {
   GemmArgs g;
   g.M = ka->p[i].M; g.N = ka->p[i].N; g.K = ka->p[i].K;
   g.lda = ka->p[i].lda; g.ldb = ka->p[i].ldb; g.ldc = ka->p[i].ldc;
-  f32_tile<float, float, float, float, true, true, 32, 1, 1, false>(g, (const float*)ka->p[i].A, (const float*)ka->p[i].B, (float*)ka->p[i].C,
-                                                                    nullptr, by * 32, g.M, bx * 32, 0, g.K, f32_k_waves(g.K, 32, 8), nullptr, nullptr);
+  const float *A = (const float*)ka->p[i].A, *B = (const float*)ka->p[i].B;
+  float* C = (float*)ka->p[i].C;
+  const int nw = f32_k_waves(g.K, 32, 8);
+  if constexpr (STG) f32_tile_staged<true, true, false>(g, A, B, C, nullptr, by * 32, g.M, bx * 32, 0, g.K, nw, nullptr, nullptr);
+  else f32_tile<float, float, float, float, true, true, 32, 1, 1, false>(g, A, B, C, nullptr, by * 32, g.M, bx * 32, 0, g.K, nw, nullptr, nullptr);
 }
 
-template <class TA, class TB, class TC, class TS, bool AT, bool BT, int R, int TM, int TN, bool ACT = false>
+template <class TA, class TB, class TC, class TS, bool AT, bool BT, int R, int TM, int TN, bool ACT = false, bool STG = false>
 static void go_shape(const GemmArgs& g, int nw, hipStream_t s) {
   const int gy = g.group_mode == 1 ? g.max_tiles : cdiv(g.M, R * TM);
   const dim3 grid(ACT ? cdiv(g.act_half, R) : cdiv(g.N, R * TN), gy, g.group_mode == 2 ? g.n_groups : g.group_mode == 0 ? g.n_sub : 1);
   if (grid.x == 0 || grid.y == 0 || grid.z == 0) return;
-  const size_t smem = (size_t)nw * (R * TM) * (R * TN) * sizeof(float);
+  const size_t smem = (size_t)nw * (STG ? (1 + TN) * 4096 : (R * TM) * (R * TN) * sizeof(float));
   static std::atomic<unsigned long long> attr_mask{0};
   if (smem >= 65536 && attr_needed(attr_mask)) {
-    (void)hipFuncSetAttribute((const void*)gemm_f32_k<TA, TB, TC, TS, AT, BT, R, TM, TN, ACT>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, 8 * 4096 * TM * TN);
+    (void)hipFuncSetAttribute((const void*)gemm_f32_k<TA, TB, TC, TS, AT, BT, R, TM, TN, ACT, STG>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, STG ? 8 * 4096 * (1 + TN) : 8 * 4096 * TM * TN);
     attr_done(attr_mask);
   }
   GemmArgs a = g;
   a.k_waves = nw;
-  hipLaunchKernelGGL((gemm_f32_k<TA, TB, TC, TS, AT, BT, R, TM, TN, ACT>), grid, dim3(64 * (nw > 4 ? nw : 4)), smem, s, a);
+  hipLaunchKernelGGL((gemm_f32_k<TA, TB, TC, TS, AT, BT, R, TM, TN, ACT, STG>), grid, dim3(64 * (nw > 4 ? nw : 4)), smem, s, a);
+}
+
+// whether f32_tile_staged takes the problem: loads of 4 elements inside the operands, which span less than 2 GiB
+static bool quads(const void* p, i64 ld, i64 rows, i64 inner) {
+  return !((uintptr_t)p & 15) && !(ld & 3) && !(inner & 3) && rows * ld < (i64)1 << 29;
+}
+static bool staged_ok(const GemmArgs& g) {
+  if (g.group_mode == 2 ? g.K <= 0 : g.M <= 0) return false;
+  if (g.a_last_row || (g.a_trans && g.a_gather)) return false;
+  auto a_ok = [&](const void* p) { return g.a_trans ? quads(p, g.lda, g.K, g.M) : quads(p, g.lda, g.M, g.K); };
+  auto b_ok = [&](const void* p) { return g.b_trans ? quads(p, g.ldb, g.K, g.N) : quads(p, g.ldb, g.N, g.K); };
+  if (!a_ok(g.A) || !b_ok(g.B) || (g.b_group_stride & 3) || (g.act_half & 3)) return false;
+  if (g.A2 && (!a_ok(g.A2) || !b_ok(g.B2))) return false;
+  for (int z = 1; z < g.n_sub; z++)
+    if (!a_ok(g.subA[z - 1]) || !b_ok(g.subB[z - 1])) return false;
+  return true;
 }
 
 template <class TA, class TB, class TC, class TS, bool AT, bool BT>
@@ -217,6 +338,13 @@ static void go(const GemmArgs& g, hipStream_t s) {
     return;
   }
   const int nw = f32_k_waves(krange, 32, 8);
+  if constexpr (std::is_same<TA, float>::value && std::is_same<TB, float>::value && !(AT && !BT))
+    if (staged_ok(g)) {
+      if constexpr (!AT && !BT)
+        if (g.act_half) { go_shape<TA, TB, TC, TS, AT, BT, 32, 1, 2, true, true>(g, nw, s); return; }
+      go_shape<TA, TB, TC, TS, AT, BT, 32, 1, 1, false, true>(g, nw, s);
+      return;
+    }
   if constexpr (!AT && !BT)
     if (g.act_half) { go_shape<TA, TB, TC, TS, AT, BT, 32, 1, 2, true>(g, nw, s); return; }
   const i64 z = g.group_mode == 2 ? g.n_groups : 1;
@@ -255,6 +383,19 @@ int launch_gemm_f32_batch_tn(GemmBatch& b, hipStream_t s) {
     const int w = f32_k_waves(p.K, 32, 8);
     if (w > nw) nw = w;
   }
-  if (b.total > 0) hipLaunchKernelGGL(gemm_f32_batch_tn_k, dim3(b.total), dim3(64 * (nw > 4 ? nw : 4)), (size_t)nw * 4096, s, b);
+  if (b.total <= 0) return 0;
+  bool stg = true;
+  for (int i = 0; i < b.n; i++) stg = stg && quads(b.p[i].A, b.p[i].lda, b.p[i].K, b.p[i].M) && quads(b.p[i].B, b.p[i].ldb, b.p[i].K, b.p[i].N);
+  const dim3 block(64 * (nw > 4 ? nw : 4));
+  if (stg) {
+    static std::atomic<unsigned long long> attr_mask{0};
+    if (attr_needed(attr_mask)) {
+      (void)hipFuncSetAttribute((const void*)gemm_f32_batch_tn_k<true>, hipFuncAttributeMaxDynamicSharedMemorySize, 8 * 8192);
+      attr_done(attr_mask);
+    }
+    hipLaunchKernelGGL(gemm_f32_batch_tn_k<true>, dim3(b.total), block, (size_t)nw * 8192, s, b);
+  } else {
+    hipLaunchKernelGGL(gemm_f32_batch_tn_k<false>, dim3(b.total), block, (size_t)nw * 4096, s, b);
+  }
   return 0;
 }

@@ -18,7 +18,10 @@ def _dev(a):
 # one element, tails in every dimension around 32 and the 32-wide chunks of k, rows that are not 16-byte aligned
 # (odd leading dimensions), no k at all, and enough tiles for the larger tile shape
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (33, 31, 65), (64, 96, 64), (61, 130, 2048), (7, 200, 31), (40, 40, 0),
-                                   (1030, 1040, 70), (1024, 1056, 33)])
+                                   (1030, 1040, 70), (1024, 1056, 33),
+                                   # whole groups of four throughout (straight into LDS without the odd padding): less than a
+                                   # piece, one past it, fewer pieces than waves, several per wave, ragged tiles
+                                   (4, 8, 4), (36, 44, 68), (64, 32, 36), (132, 260, 516), (400, 512, 1024)])
 def test_f32_gemm(M, N, K, a_trans, b_trans):
     rng = np.random.default_rng(M + 3 * N + 7 * K)
     A, B = (rng.standard_normal(s).astype(np.float32) for s in ((M, K), (K, N)))
