@@ -20,12 +20,12 @@ typedef __attribute__((ext_vector_type(8))) short s16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
-// NB = 32-column blocks of a tile: 2 with the SwiGLU epilogue (gate columns and the up columns of the same indices);
-// NW = waves; NS = pieces of a wave in flight; PAIR: problem 0 has a second pair of operands, its pieces follow the first's
-template <bool BT, class TC, int NB, int NW, int NS, bool PAIR, bool GRP>
+// ACT: a gate/up GEMM with the SwiGLU epilogue, columns 0-15 of a tile are gate columns and 16-31 the up columns of the same
+// indices; NW = waves; NS = pieces of a wave in flight; PAIR: problem 0 has a second pair of operands, its pieces follow the first's
+template <bool BT, class TC, bool ACT, int NW, int NS, bool PAIR, bool GRP>
 __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
-  constexpr int RS = NB * 32 + 8;                    // row stride of a partial tile (floats): rows 4 apart are 32 banks apart
-  constexpr unsigned OPD = 64 * 32 * 2, STAGE = (1 + NB) * OPD;     // LDS bytes of a piece: A, then B
+  constexpr int RS = 32 + 8;                         // row stride of a partial tile (floats): rows 4 apart are 32 banks apart
+  constexpr unsigned OPD = 64 * 32 * 2, STAGE = 2 * OPD;     // LDS bytes of a piece: A, then B
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const bf16* A = (const bf16*)g.A;
   const bf16* B = (const bf16*)g.B;
@@ -48,7 +48,7 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
     if (bx >= g.tiles_n) return;
     m0 = by * 32; m_end = g.M;
   }
-  const int n0 = bx * 32, ncols = NB == 2 ? g.act_half : g.N;
+  const int n0 = bx * (ACT ? 16 : 32), ncols = ACT ? g.act_half : g.N;
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5;
   if (!GRP && g.row_skip) {                          // every wave looks at all rows of the tile: same answer, no barrier
     const int r = m0 + (lane & 31);
@@ -60,7 +60,7 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
   const unsigned lda_b = (unsigned)g.lda * 2u, ldb_b = (unsigned)g.ldb * 2u;
   // where this lane's share of the four wave-loads of each operand comes from at k = 0, and which k it is (relative to
   // the piece): a load at or past K is out of range, rows and columns past the end repeat the last one or are zeros
-  unsigned aoff[4], boff[NB][4];
+  unsigned aoff[4], boff[4];
   int akc[4];
 #pragma unroll
   for (int i = 0; i < 4; i++) {
@@ -69,11 +69,11 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
     const int row = min(m0 + r, m_end - 1);
     aoff[i] = (unsigned)(GRP && g.a_gather ? g.a_gather[row] / g.gather_div : row) * lda_b + (unsigned)ch * 16u;
     if constexpr (!BT) {
-#pragma unroll
-      for (int j = 0; j < NB; j++) boff[j][i] = (unsigned)(min(n0 + r, ncols - 1) + j * ncols) * ldb_b + (unsigned)ch * 16u;
+      const int col = ACT ? (r >> 4) * ncols + min(n0 + (r & 15), ncols - 1) : min(n0 + r, ncols - 1);
+      boff[i] = (unsigned)col * ldb_b + (unsigned)ch * 16u;
     } else {                                         // 16 k's: lane l brings columns (l & 3) * 8 .. + 7 of row l >> 2
       const int col = n0 + (lane & 3) * 8;
-      boff[0][i] = col < g.N ? (unsigned)(i * 16 + (lane >> 2)) * ldb_b + (unsigned)col * 2u : OOB;
+      boff[i] = col < g.N ? (unsigned)(i * 16 + (lane >> 2)) * ldb_b + (unsigned)col * 2u : OOB;
     }
   }
   const unsigned my = (unsigned)wv * NS * STAGE;     // this wave's part of LDS
@@ -88,19 +88,14 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
       const bool in = k0 + akc[i] < g.K;
       load_lds_b128(ra, __builtin_amdgcn_readfirstlane(dst + i * 1024u), in ? aoff[i] + (unsigned)k0 * 2u : OOB);
       if constexpr (!BT) {
-#pragma unroll
-        for (int j = 0; j < NB; j++) load_lds_b128(rb, __builtin_amdgcn_readfirstlane(dst + (1 + j) * OPD + i * 1024u), in ? boff[j][i] + (unsigned)k0 * 2u : OOB);
+        load_lds_b128(rb, __builtin_amdgcn_readfirstlane(dst + OPD + i * 1024u), in ? boff[i] + (unsigned)k0 * 2u : OOB);
       } else {
-        const bool kin = k0 + i * 16 + (lane >> 2) < g.K && boff[0][i] != OOB;
-        load_lds_b128(rb, __builtin_amdgcn_readfirstlane(dst + OPD + i * 1024u), kin ? boff[0][i] + (unsigned)k0 * ldb_b : OOB);
+        const bool kin = k0 + i * 16 + (lane >> 2) < g.K && boff[i] != OOB;
+        load_lds_b128(rb, __builtin_amdgcn_readfirstlane(dst + OPD + i * 1024u), kin ? boff[i] + (unsigned)k0 * ldb_b : OOB);
       }
     }
   };
-  f32x16 acc[NB];
-#pragma unroll
-  for (int j = 0; j < NB; j++)
-#pragma unroll
-    for (int e = 0; e < 16; e++) acc[j][e] = 0.f;
+  f32x16 acc = {};
 
   const int fr = lane & 31, fsw = (fr >> 1) & 7;
   const unsigned tr = (unsigned)((lane >> 5) * 8 + ((lane & 15) >> 2)) * 64u + (unsigned)(((lane >> 4) & 1) * 16 + (lane & 3) * 4) * 2u;
@@ -108,21 +103,20 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
   for (int st = 0; st < NS; st++) issue(wv + st * NW, st);          // (pieces past the end load zeros, to keep the count)
   int st = 0;
   for (int p = wv; p < np; p += NW) {
-    wait_vmcnt<(NS - 1) * 4 * (1 + NB)>();
+    wait_vmcnt<(NS - 1) * 8>();
     const unsigned char* t = smem + my + (unsigned)st * STAGE;
-    bf16x8 fa[4], fb[NB][4];
+    bf16x8 fa[4], fb[4];
 #pragma unroll
     for (int s = 0; s < 4; s++) {
       const unsigned at = (unsigned)fr * 128u + (unsigned)((2 * s + half) ^ fsw) * 16u;
       fa[s] = *(const bf16x8*)(t + at);
       if constexpr (!BT) {
-#pragma unroll
-        for (int j = 0; j < NB; j++) fb[j][s] = *(const bf16x8*)(t + (1 + j) * OPD + at);
+        fb[s] = *(const bf16x8*)(t + OPD + at);
       } else {
         const unsigned char* q = t + OPD + tr + s * 1024u;
         const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)q);
         const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(q + 4 * 64));
-        fb[0][s] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+        fb[s] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
       }
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");              // the fragments are in registers: the stage is free
@@ -130,47 +124,37 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
     issue(p + NS * NW, st);
     st = st + 1 == NS ? 0 : st + 1;
 #pragma unroll
-    for (int s = 0; s < 4; s++)
-#pragma unroll
-      for (int j = 0; j < NB; j++) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[s], fb[j][s], acc[j], 0, 0, 0);
+    for (int s = 0; s < 4; s++) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[s], fb[s], acc, 0, 0, 0);
   }
   wait_vmcnt<0>();                                                  // the zero-filled loads past the end
   __syncthreads();                                   // the partial tiles overlay the stages
   float* part = (float*)smem;
 #pragma unroll
-  for (int j = 0; j < NB; j++)
-#pragma unroll
-    for (int e = 0; e < 16; e++)
-      part[wv * 32 * RS + ((e >> 2) * 8 + half * 4 + (e & 3)) * RS + j * 32 + (lane & 31)] = acc[j][e];
+  for (int e = 0; e < 16; e++) part[wv * 32 * RS + ((e >> 2) * 8 + half * 4 + (e & 3)) * RS + (lane & 31)] = acc[e];
   __syncthreads();
-  const int n = n0 + (int)(threadIdx.x & 31);
-  if (n >= ncols) return;
+  const int col = (int)(threadIdx.x & 31), n = n0 + (ACT ? col & 15 : col);
+  if (n >= ncols) return;                            // (ACT: a gate column and its up column both)
 #pragma unroll
   for (int r = (int)threadIdx.x >> 5; r < 32; r += NW * 2) {
     const int m = m0 + r;
     if (m >= m_end) break;
-    float v[NB];
+    float v = 0.f;
 #pragma unroll
-    for (int j = 0; j < NB; j++) {
-      v[j] = 0.f;
-#pragma unroll
-      for (int w = 0; w < NW; w++) v[j] += part[w * 32 * RS + r * RS + j * 32 + (int)(threadIdx.x & 31)];
-    }
-    if constexpr (NB == 2) {                         // silu(gate) * up from the rounded values, as the tile kernel
-      const TC gb = (TC)v[0], ub = (TC)v[1];
-      const float gv = (float)gb;
-      C[(i64)m * g.ldc + n] = gb;
-      C[(i64)m * g.ldc + ncols + n] = ub;
-      ((TC*)g.act_out)[(i64)m * g.ldact + n] = (TC)(gv * sigmoid_f(gv) * (float)ub);
+    for (int w = 0; w < NW; w++) v += part[w * 32 * RS + r * RS + col];
+    if constexpr (ACT) {                             // silu(gate) * up from the rounded values, as the tile kernel
+      const TC x = (TC)v;
+      const float own = (float)x, up = __shfl(own, lane | 16, WAVE);
+      C[(i64)m * g.ldc + (col >> 4) * ncols + n] = x;
+      if (col < 16) ((TC*)g.act_out)[(i64)m * g.ldact + n] = (TC)(own * sigmoid_f(own) * up);
     } else if (g.dact_out) {                         // SwiGLU's backward, from what C would have held
       const bf16* gu = (const bf16*)g.dact_gu + (i64)m * 2 * g.N + n;
       float dg, du;
-      swiglu_grad((float)(TC)v[0], (float)gu[0], (float)gu[g.N], &dg, &du);
+      swiglu_grad((float)(TC)v, (float)gu[0], (float)gu[g.N], &dg, &du);
       TC* out = (TC*)g.dact_out + (i64)m * 2 * g.N + n;
       out[0] = (TC)dg;
       out[g.N] = (TC)du;
     } else {
-      float o = v[0] + (bias ? (float)bias[n] : 0.f);
+      float o = v + (bias ? (float)bias[n] : 0.f);
       if (g.tap) g.tap[(i64)m * g.ldtap + n] = o;
       if (g.resid) {
         const i64 at = (i64)m * g.ldr + n;
@@ -181,44 +165,41 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
   }
 }
 
-template <bool BT, class TC, int NB, int NW, int NS, bool PAIR = false, bool GRP = false>
+template <bool BT, class TC, bool ACT, int NW, int NS, bool PAIR = false, bool GRP = false>
 static void go(GemmArgs g, hipStream_t s) {
   g.tiles_m = GRP ? g.max_tiles : cdiv(g.M, 32);
-  g.tiles_n = cdiv(NB == 2 ? g.act_half : g.N, 32);
-  constexpr size_t part = (size_t)NW * 32 * (NB * 32 + 8) * 4, bufs = (size_t)NW * NS * (1 + NB) * 64 * 32 * 2;
+  g.tiles_n = ACT ? cdiv(g.act_half, 16) : cdiv(g.N, 32);
+  constexpr size_t part = (size_t)NW * 32 * 40 * 4, bufs = (size_t)NW * NS * 2 * 64 * 32 * 2;
   constexpr size_t smem = part > bufs ? part : bufs;
   static_assert(smem <= 160 * 1024, "LDS of a CU");
   static std::atomic<unsigned long long> attr_mask{0};
   if (attr_needed(attr_mask)) {
-    (void)hipFuncSetAttribute((const void*)gemm_skinny_k<BT, TC, NB, NW, NS, PAIR, GRP>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    (void)hipFuncSetAttribute((const void*)gemm_skinny_k<BT, TC, ACT, NW, NS, PAIR, GRP>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     attr_done(attr_mask);
   }
-  hipLaunchKernelGGL((gemm_skinny_k<BT, TC, NB, NW, NS, PAIR, GRP>), dim3(GRP ? g.tiles_n * g.tiles_m : 8 * cdiv(g.tiles_n, 8) * g.tiles_m, 1, g.n_sub), dim3(NW * 64), smem, s, g);
+  hipLaunchKernelGGL((gemm_skinny_k<BT, TC, ACT, NW, NS, PAIR, GRP>), dim3(GRP ? g.tiles_n * g.tiles_m : 8 * cdiv(g.tiles_n, 8) * g.tiles_m, 1, g.n_sub), dim3(NW * 64), smem, s, g);
 }
 
 // Pieces in flight are LDS, and LDS decides how many workgroups share a CU.  Up to 4 pieces there are 4 waves with one each
 // (32 KiB, four workgroups), up to 8 pieces 8 waves (64 KiB, two).  With more k a wave has two in flight (128 KiB) where
 // every workgroup has a CU to itself anyway; a larger launch gains more from a second workgroup.
-template <bool BT, class TC, int NB, bool PAIR = false, bool GRP = false>
+template <bool BT, class TC, bool ACT, bool PAIR = false, bool GRP = false>
 static void by_k(const GemmArgs& g, hipStream_t s) {
   const int k = PAIR ? 2 * g.K : g.K;
-  if (k <= 256) go<BT, TC, NB, 4, 1, PAIR, GRP>(g, s);
-  else if (k <= 512 || NB == 2) go<BT, TC, NB, 8, 1, PAIR, GRP>(g, s);
-  else if constexpr (NB == 1) {
-    if ((i64)(GRP ? g.max_tiles : cdiv(g.M, 32)) * cdiv(g.N, 32) * g.n_sub > 256) go<BT, TC, NB, 8, 1, PAIR, GRP>(g, s);
-    else go<BT, TC, NB, 8, 2, PAIR, GRP>(g, s);
-  }
+  if (k <= 256) go<BT, TC, ACT, 4, 1, PAIR, GRP>(g, s);
+  else if (k <= 512 || (i64)(GRP ? g.max_tiles : cdiv(g.M, 32)) * cdiv(g.N, 32) * g.n_sub > 256) go<BT, TC, ACT, 8, 1, PAIR, GRP>(g, s);
+  else go<BT, TC, ACT, 8, 2, PAIR, GRP>(g, s);
 }
 
 void launch_gemm_skinny(const GemmArgs& g, int out_f32, hipStream_t s) {
   if (g.group_mode == 1) {                           // (bf16 results, launch_gemm_mfma)
-    if (g.act_half) by_k<false, bf16, 2, false, true>(g, s);
-    else if (g.b_trans) by_k<true, bf16, 1, false, true>(g, s);
-    else by_k<false, bf16, 1, false, true>(g, s);
+    if (g.act_half) by_k<false, bf16, true, false, true>(g, s);
+    else if (g.b_trans) by_k<true, bf16, false, false, true>(g, s);
+    else by_k<false, bf16, false, false, true>(g, s);
     return;
   }
-  if (g.act_half) { if (out_f32) by_k<false, float, 2>(g, s); else by_k<false, bf16, 2>(g, s); }
-  else if (g.A2) by_k<true, bf16, 1, true>(g, s);    // (launch_gemm_mfma admits that form only)
-  else if (g.b_trans) { if (out_f32) by_k<true, float, 1>(g, s); else by_k<true, bf16, 1>(g, s); }
-  else { if (out_f32) by_k<false, float, 1>(g, s); else by_k<false, bf16, 1>(g, s); }
+  if (g.act_half) { if (out_f32) by_k<false, float, true>(g, s); else by_k<false, bf16, true>(g, s); }
+  else if (g.A2) by_k<true, bf16, false, true>(g, s);    // (launch_gemm_mfma admits that form only)
+  else if (g.b_trans) { if (out_f32) by_k<true, float, false>(g, s); else by_k<true, bf16, false>(g, s); }
+  else { if (out_f32) by_k<false, float, false>(g, s); else by_k<false, bf16, false>(g, s); }
 }
