@@ -506,6 +506,27 @@ int run_gemm_multi(revffn_ctx* c, const GemmArgs* subs, int n, int tc, hipStream
   return 0;
 }
 
+// One to three problems of one shape with the norm of A's rows or the rotation of the outputs in the same launch, where the
+// kernel for small problems takes them (a rule on the call and the layer, as gemm_few_rows); 1: nothing launched.
+int run_gemm_small(revffn_ctx* c, const GemmArgs* subs, int n, hipStream_t s) {
+  GemmArgs g = subs[0];
+  if (c->dt == 1 && (c->mode != 0 || !few_rows(c, g))) return 1;
+  g.n_sub = n;
+  g.few_rows = 1;
+  for (int z = 1; z < n; z++) {
+    if (subs[z].lda != g.lda) return 1;
+    g.subA[z - 1] = subs[z].A; g.subB[z - 1] = subs[z].B; g.subC[z - 1] = subs[z].C; g.subBias[z - 1] = subs[z].bias;
+    g.norm_g[z] = subs[z].norm_g[0]; g.norm_out[z] = subs[z].norm_out[0];
+  }
+  double fl = 0, by = 0;
+  if (c->prof_on) { gemm_work(c, subs[0], c->dt, c->dt, c->dt, &fl, &by); fl *= n; by *= n; }
+  const GemmTypes t{c->dt, c->dt, c->dt, c->dt};
+  ProfScope ps(c, s, fl, by);
+  if (c->dt == 1 ? launch_gemm_mfma(g, t, s) : launch_gemm_generic(g, t, s)) return 1;
+  ps.done(c->dt == 1 ? KID_GEMM_NT : KID_GEMM_GENERIC);
+  return 0;
+}
+
 // the weight gradients of several dense layers as one launch; where the bf16 kernel does not take them they run one after
 // the other
 int run_wgrad_batch(revffn_ctx* c, const GemmArgs* subs, int n, bool bulk, hipStream_t s) {
@@ -563,80 +584,78 @@ void after(revffn_ctx* c, hipStream_t from, hipStream_t to) {
 hipStream_t side(revffn_ctx* c, hipStream_t main, int i) { return c->par ? c->side[i] : main; }
 
 // ---- attention half ---------------------------------------------------------------
-// Query side of the attention half at x1: n12[0:T], U12[0:T], Q.
+// U = Norm(x) . P_up^T for one stream or both (U and the normalised rows of the second behind those of the first).
 // skip (may be null): rows marked there are finished rows of the inverse's iteration and are left alone.
+struct NormUp { const void* x; i64 ldx; const void* gain; void *nout, *U; };
+int norm_up(revffn_ctx* c, const NormUp* p, int n, const void* pup, int T, hipStream_t s, const unsigned char* skip = nullptr) {
+  const revffn_config& f = c->cfg;
+  const int d = f.d_model, h = d / 2, dt = c->dt;
+  if (n == 2 && p[0].ldx != p[1].ldx) {
+    TRY(norm_up(c, p, 1, pup, T, s, skip));
+    return norm_up(c, p + 1, 1, pup, T, s, skip);
+  }
+  if (c->sdt == dt) {
+    GemmArgs g[2];
+    for (int i = 0; i < n; i++) {
+      g[i] = nt(p[i].x, p[i].ldx, pup, h, p[i].U, d, T, d, h);
+      g[i].row_skip = skip;
+      g[i].norm_g[0] = p[i].gain; g[i].norm_out[0] = p[i].nout; g[i].norm_eps = f.rms_eps;
+    }
+    if (run_gemm_small(c, g, n, s) == 0) return 0;
+  }
+  p_rmsnorm_fwd(c, dt, c->sdt, p[0].x, p[0].ldx, p[0].gain, p[0].nout, h, T, h, f.rms_eps, s, skip, n == 2 ? p[1].x : nullptr,
+                n == 2 ? p[1].gain : nullptr, n == 2 ? p[1].nout : nullptr);
+  GemmArgs g = nt(p[0].nout, h, pup, h, p[0].U, d, n * T, d, h);       // the same P_up serves both streams: stacked rows
+  g.row_skip = skip;
+  return run_gemm(c, g, s);
+}
+// n <= 3 projections of one shape, the outputs of the first n_rot rotated
+int project(revffn_ctx* c, GemmArgs* q, int n, int n_rot, int T, int S, hipStream_t s, const unsigned char* skip = nullptr) {
+  const revffn_config& f = c->cfg;
+  if (!f.use_rope) n_rot = 0;
+  if (n_rot) {
+    GemmArgs& g = q[0];
+    g.rope_cs = c->rope_cs; g.rope_S = S; g.rope_dh = f.head_dim; g.rope_mask = (1 << n_rot) - 1;
+    if (run_gemm_small(c, q, n, s) == 0) return 0;
+    g.rope_cs = nullptr;
+  }
+  TRY(run_gemm_multi(c, q, n, c->dt, s));
+  if (n_rot) p_rope(c, c->dt, q[0].C, c->rope_cs, T, S, f.n_heads, f.head_dim, 1.f, s, n_rot == 2 ? q[1].C : nullptr, skip);
+  return 0;
+}
+// Query side of the attention half at x1: n12[0:T], U12[0:T], Q.
 int attn_q(revffn_ctx* c, const revffn_weights* w, const void* x1, i64 ld1, int B, int S, hipStream_t s,
            const unsigned char* skip = nullptr) {
-  const revffn_config& f = c->cfg;
-  const int T = B * S, d = f.d_model, h = d / 2, dt = c->dt;
-  p_rmsnorm_fwd(c, dt, c->sdt, x1, ld1, w->norm_a1, c->n12, h, T, h, f.rms_eps, s, skip);
-  GemmArgs gu = nt(c->n12, h, w->pup_a, h, c->U12, d, T, d, h);
-  gu.row_skip = skip;
-  TRY(run_gemm(c, gu, s));
+  const int T = B * S, d = c->cfg.d_model;
+  const NormUp nu{x1, ld1, w->norm_a1, c->n12, c->U12};
+  TRY(norm_up(c, &nu, 1, w->pup_a, T, s, skip));
   GemmArgs gq = nt(c->U12, d, w->wq, d, c->Q, d, T, d, d);
   gq.bias = w->bq;
   gq.row_skip = skip;
-  TRY(run_gemm(c, gq, s));
-  if (f.use_rope) p_rope(c, dt, c->Q, c->rope_cs, T, S, f.n_heads, f.head_dim, 1.f, s, nullptr, skip);
-  return 0;
+  return project(c, &gq, 1, 1, T, S, s, skip);
 }
 // Recomputes n12, U12, Q, (K, V), O, lse, AO at streams (x1, x2).  q_done: attn_q(x1) has been enqueued already.
 int attn_acts(revffn_ctx* c, const revffn_weights* w, const void* x1, i64 ld1, const void* x2, i64 ld2, int B, int S,
               bool do_kv, hipStream_t s, bool q_done = false, const unsigned char* skip = nullptr) {
   const revffn_config& f = c->cfg;
   const int T = B * S, d = f.d_model, h = d / 2, es = c->es, dt = c->dt;
-  if (f.symmetric) {
-    // comparison block: queries from stream 2 as well.  n2, U2 keep their places in the second halves of n12, U12.
-    void* n2 = at(c->n12, (size_t)T * h, es);
-    void* U2s = at(c->U12, (size_t)T * d, es);
-    p_rmsnorm_fwd(c, dt, c->sdt, x2, ld2, w->norm_a2, n2, h, T, h, f.rms_eps, s);
-    TRY(run_gemm(c, nt(n2, h, w->pup_a, h, U2s, d, T, d, h), s));
-    GemmArgs gq = nt(U2s, d, w->wq, d, c->Q, d, T, d, d);
-    gq.bias = w->bq;
-    TRY(run_gemm(c, gq, s));
-    if (f.use_rope) p_rope(c, dt, c->Q, c->rope_cs, T, S, f.n_heads, f.head_dim, 1.f, s);
-    do_kv = true;
-  } else if (q_done) {
-    if (do_kv) {
-      p_rmsnorm_fwd(c, dt, c->sdt, x2, ld2, w->norm_a2, at(c->n12, (size_t)T * h, es), h, T, h, f.rms_eps, s);
-      TRY(run_gemm(c, nt(at(c->n12, (size_t)T * h, es), h, w->pup_a, h, at(c->U12, (size_t)T * d, es), d, T, d, h), s));
-    }
+  void* U2 = at(c->U12, (size_t)T * d, es);
+  // queries (which the comparison block takes from stream 2 as well), keys and values: up to three problems of one shape
+  GemmArgs q3[3] = {nt(f.symmetric ? U2 : c->U12, d, w->wq, d, c->Q, d, T, d, d), nt(U2, d, w->wk, d, c->K, d, T, d, d),
+                    nt(U2, d, w->wv, d, c->V, d, T, d, d)};
+  q3[0].bias = w->bq; q3[1].bias = w->bk; q3[2].bias = w->bv;
+  const NormUp nu[2] = {{x1, ld1, w->norm_a1, c->n12, c->U12}, {x2, ld2, w->norm_a2, at(c->n12, (size_t)T * h, es), U2}};
+  if (f.symmetric) {                                    // n2, U2 keep their places in the second halves of n12, U12
+    TRY(norm_up(c, nu + 1, 1, w->pup_a, T, s));
+    TRY(project(c, q3, 3, 2, T, S, s));
   } else if (!do_kv) {
-    TRY(attn_q(c, w, x1, ld1, B, S, s, skip));          // a later iterate of the inverse: query side only
+    if (!q_done) TRY(attn_q(c, w, x1, ld1, B, S, s, skip));          // a later iterate of the inverse: query side only
+  } else if (q_done) {                                 // (the query side was enqueued earlier)
+    TRY(norm_up(c, nu + 1, 1, w->pup_a, T, s));
+    TRY(project(c, q3 + 1, 2, 1, T, S, s));
   } else {
-    // both streams in one launch (the two streams of a call share their row stride)
-    if (do_kv && ld1 == ld2)
-      p_rmsnorm_fwd(c, dt, c->sdt, x1, ld1, w->norm_a1, c->n12, h, T, h, f.rms_eps, s, nullptr, x2, w->norm_a2,
-                    at(c->n12, (size_t)T * h, es));
-    else {
-      p_rmsnorm_fwd(c, dt, c->sdt, x1, ld1, w->norm_a1, c->n12, h, T, h, f.rms_eps, s);
-      if (do_kv) p_rmsnorm_fwd(c, dt, c->sdt, x2, ld2, w->norm_a2, at(c->n12, (size_t)T * h, es), h, T, h, f.rms_eps, s);
-    }
-    // the same P_up serves both streams: one GEMM over the stacked rows
-    TRY(run_gemm(c, nt(c->n12, h, w->pup_a, h, c->U12, d, do_kv ? 2 * T : T, d, h), s));
-    if (do_kv) {
-      // Q, K and V projections as one launch (three problems of one shape), then one rotary launch for Q and K
-      const void* U2 = at(c->U12, (size_t)T * d, es);
-      GemmArgs q3[3] = {nt(c->U12, d, w->wq, d, c->Q, d, T, d, d), nt(U2, d, w->wk, d, c->K, d, T, d, d),
-                        nt(U2, d, w->wv, d, c->V, d, T, d, d)};
-      q3[0].bias = w->bq; q3[1].bias = w->bk; q3[2].bias = w->bv;
-      TRY(run_gemm_multi(c, q3, 3, dt, s));
-      if (f.use_rope) p_rope(c, dt, c->Q, c->rope_cs, T, S, f.n_heads, f.head_dim, 1.f, s, c->K);
-      do_kv = false;                                   // done here
-    } else {
-      GemmArgs gq = nt(c->U12, d, w->wq, d, c->Q, d, T, d, d);
-      gq.bias = w->bq;
-      TRY(run_gemm(c, gq, s));
-      if (f.use_rope) p_rope(c, dt, c->Q, c->rope_cs, T, S, f.n_heads, f.head_dim, 1.f, s);
-    }
-  }
-  if (do_kv) {
-    // (the query side was enqueued earlier, or comes from stream 2 in the symmetric block): K and V as one launch
-    const void* U2 = at(c->U12, (size_t)T * d, es);
-    GemmArgs kv[2] = {nt(U2, d, w->wk, d, c->K, d, T, d, d), nt(U2, d, w->wv, d, c->V, d, T, d, d)};
-    kv[0].bias = w->bk; kv[1].bias = w->bv;
-    TRY(run_gemm_multi(c, kv, 2, dt, s));
-    if (f.use_rope) p_rope(c, dt, c->K, c->rope_cs, T, S, f.n_heads, f.head_dim, 1.f, s);
+    TRY(norm_up(c, nu, 2, w->pup_a, T, s));
+    TRY(project(c, q3, 3, 2, T, S, s));
   }
   {
     // algorithmic work of the attention core: QK^T and PV, halved by the causal mask
@@ -702,8 +721,8 @@ int moe_acts(revffn_ctx* c, const revffn_weights* w, const void* y1, i64 ld, int
   after(c, s, sr);
   router_fold(c, w, c->wrp, sr);
   p_routing(c, y1, ld, c->wrp, w->b_router, T, sr);
-  p_rmsnorm_fwd(c, dt, c->sdt, y1, ld, w->norm_m, c->n3, h, T, h, f.rms_eps, s);
-  TRY(run_gemm(c, nt(c->n3, h, w->pup_m, h, c->Um, d, T, d, h), s));
+  const NormUp nu{y1, ld, w->norm_m, c->n3, c->Um};
+  TRY(norm_up(c, &nu, 1, w->pup_m, T, s));
   hipStream_t s0 = side(c, s, 0);
   if (Is) {                               // the shared expert needs Um only: next to the routed experts
     after(c, s, s0);
@@ -786,27 +805,34 @@ int attn_acts_merged(revffn_ctx* c, const revffn_weights* w, const revffn_merged
   const revffn_config& f = c->cfg;
   const int T = B * S, d = f.d_model, h = d / 2, es = c->es, dt = c->dt;
   void* n2 = at(c->n12, (size_t)T * h, es);
-  if (do_kv) {
-    if (ld1 == ld2) p_rmsnorm_fwd(c, dt, c->sdt, x1, ld1, w->norm_a1, c->n12, h, T, h, f.rms_eps, s, nullptr, x2, w->norm_a2, n2);
+  const int n = do_kv ? 3 : 1;
+  GemmArgs q3[3] = {nt(c->n12, h, m->wq, h, c->Q, d, T, d, h), nt(n2, h, m->wk, h, c->K, d, T, d, h), nt(n2, h, m->wv, h, c->V, d, T, d, h)};
+  q3[0].bias = w->bq; q3[1].bias = w->bk; q3[2].bias = w->bv;
+  bool done = false;
+  // few tokens: norms, projections and rotation as one launch (two if the strides differ).  Rows wider than 512 take a workgroup's
+  // CU for itself there, which pays in one round of workgroups only.
+  if (c->sdt == dt && f.use_rope && (h <= 512 || (i64)cdiv(T, 32) * cdiv(d, 32) * 3 <= 256)) {
+    GemmArgs q[3] = {q3[0], q3[1], q3[2]};
+    for (int i = 0; i < n; i++) {
+      q[i].A = i ? x2 : x1; q[i].lda = i ? ld2 : ld1;
+      q[i].norm_g[0] = i ? w->norm_a2 : w->norm_a1; q[i].norm_eps = f.rms_eps;
+      q[i].rope_cs = c->rope_cs; q[i].rope_S = S; q[i].rope_dh = f.head_dim;
+    }
+    q[0].rope_mask = 3; q[1].rope_mask = 1;
+    if (n == 1 || ld1 == ld2) done = run_gemm_small(c, q, n, s) == 0;
+    else done = run_gemm_small(c, q, 1, s) == 0 && run_gemm_small(c, q + 1, 2, s) == 0;
+  }
+  if (!done) {
+    if (do_kv && ld1 == ld2) p_rmsnorm_fwd(c, dt, c->sdt, x1, ld1, w->norm_a1, c->n12, h, T, h, f.rms_eps, s, nullptr, x2, w->norm_a2, n2);
     else {
       p_rmsnorm_fwd(c, dt, c->sdt, x1, ld1, w->norm_a1, c->n12, h, T, h, f.rms_eps, s);
-      p_rmsnorm_fwd(c, dt, c->sdt, x2, ld2, w->norm_a2, n2, h, T, h, f.rms_eps, s);
+      if (do_kv) p_rmsnorm_fwd(c, dt, c->sdt, x2, ld2, w->norm_a2, n2, h, T, h, f.rms_eps, s);
     }
-    GemmArgs q3[3] = {nt(c->n12, h, m->wq, h, c->Q, d, T, d, h), nt(n2, h, m->wk, h, c->K, d, T, d, h),
-                      nt(n2, h, m->wv, h, c->V, d, T, d, h)};
-    q3[0].bias = w->bq; q3[1].bias = w->bk; q3[2].bias = w->bv;
-    TRY(run_gemm_multi(c, q3, 3, dt, s));
-    if (f.use_rope) p_rope(c, dt, c->Q, c->rope_cs, T, S, f.n_heads, f.head_dim, 1.f, s, c->K);
-  } else {
-    p_rmsnorm_fwd(c, dt, c->sdt, x1, ld1, w->norm_a1, c->n12, h, T, h, f.rms_eps, s);
-    GemmArgs gq = nt(c->n12, h, m->wq, h, c->Q, d, T, d, h);
-    gq.bias = w->bq;
-    TRY(run_gemm(c, gq, s));
-    if (f.use_rope) p_rope(c, dt, c->Q, c->rope_cs, T, S, f.n_heads, f.head_dim, 1.f, s);
+    TRY(project(c, q3, n, do_kv ? 2 : 1, T, S, s));
   }
   double fl = 4.0 * B * (double)S * S * d * (f.causal ? 0.5 : 1.0), by = 4.0 * T * d * es;
   ProfScope ps(c, s, fl, by);
-  bool done = false;
+  done = false;
   if (dt == 1 && c->mode == 0)
     done = launch_attn_fwd_flash(c->Q, c->K, c->V, c->O, c->lse, B, S, f.n_heads, f.head_dim, f.causal, s) == 0;
   if (!done) launch_attn_fwd_generic(dt, c->Q, c->K, c->V, c->O, c->lse, B, S, f.n_heads, f.head_dim, f.causal, s);

@@ -49,6 +49,10 @@ __device__ __forceinline__ float block_sum_256(float v, float* red) {
 
 __device__ __forceinline__ float sigmoid_f(float x) { return 1.0f / (1.0f + __expf(-x)); }
 
+// one of a pair of columns rotated by (cos, sin): the first one is own * cos - other * sin, the second own * cos + other * sin
+__device__ __forceinline__ float rope_value(float own, float other, bool second, float2 cs) {
+  return second ? own * cs.x + other * cs.y : own * cs.x - other * cs.y;
+}
 // gradients at gate and up of silu(gate) * up, whose gradient is d
 __device__ __forceinline__ void swiglu_grad(float d, float gate, float up, float* dgate, float* dup) {
   const float sg = sigmoid_f(gate);

@@ -23,9 +23,13 @@ __host__ __device__ inline int f32_k_waves(int k, int R, int most) {
 // ACT: a gate/up GEMM (32x32 tiles): columns 0-15 of a tile are gate columns n0 .., 16-31 the up columns of the same indices
 // (32 of each: fewer, larger workgroups, 19 us instead of 14 for 300 tiles of k = 512)
 // End of a tile: the waves' partial tiles are added and go through the epilogue.
-template <class TC, class TS, int R, int TM, int TN, bool ACT, class Acc>
+// bx: the column tile.  EPI_NORM: sq is this lane's share of the squares of row lane & 31; x, gain, nout: the rows, the gains and
+// where the normalised rows go (may be null).  The contraction has run over x g, and 1 / rms scales its sums.
+template <class TC, class TS, int R, int TM, int TN, int EPI, class Acc>
 __device__ __forceinline__ void f32_finish(const GemmArgs& g, TC* C, const TS* bias, float* part, const Acc (&acc)[TM][TN], int parts, int wv,
-                                           int lane, int m0, int m_end, int n0) {
+                                           int lane, int m0, int m_end, int n0, int bx = 0, float sq = 0.f, const float* x = nullptr,
+                                           const float* gain = nullptr, float* nout = nullptr) {
+  constexpr bool ACT = EPI & EPI_ACT, ROPE = EPI & EPI_ROPE, NORM = EPI & EPI_NORM;
   constexpr int BM = R * TM, BN = R * TN, EL = R * R / 64;   // (EL elements of a tile per lane)
   // ---- partial tiles to LDS, added in wave order by all threads, then the epilogue on whole output rows
   if (wv < parts) {
@@ -37,7 +41,28 @@ __device__ __forceinline__ void f32_finish(const GemmArgs& g, TC* C, const TS* b
 #pragma unroll
         for (int e = 0; e < EL; e++) mine[(i * R + acc_row<R>(lane, e)) * BN + j * R + (lane & (R - 1))] = acc[i][j][e];
   }
+  float* rows = part + parts * (BM * BN);            // NORM: the waves' squares per row
+  if constexpr (NORM) {
+    sq += __shfl_xor(sq, 32, WAVE);
+    if (wv < parts && lane < 32) rows[wv * 32 + lane] = sq;
+  }
   __syncthreads();
+  auto rms_inv = [&](int r) {
+    float q = 0.f;
+    for (int w = 0; w < parts; w++) q += rows[w * 32 + r];
+    return 1.0f / sqrtf(q / (float)g.K + g.norm_eps);
+  };
+  if constexpr (NORM)
+    if (nout) {                                      // the column tiles of these rows share the normalised rows out
+      const int items = 32 * (g.K >> 2), per = (items + (int)gridDim.x - 1) / (int)gridDim.x, end = min(items, (bx + 1) * per);
+      for (int i = bx * per + (int)threadIdx.x; i < end; i += (int)blockDim.x) {
+        const int r = i & 31, k = (i >> 5) * 4, m = m0 + r;
+        if (m >= m_end) continue;
+        const float4 v = *(const float4*)(x + (i64)m * g.lda + k), gv = *(const float4*)(gain + k);
+        const float ri = rms_inv(r);
+        *(float4*)(nout + (i64)m * g.K + k) = make_float4(v.x * ri * gv.x, v.y * ri * gv.y, v.z * ri * gv.z, v.w * ri * gv.w);
+      }
+    }
   constexpr int EPT = BM * BN / 256;                 // elements per thread
   float v[EPT];
 #pragma unroll
@@ -49,6 +74,21 @@ __device__ __forceinline__ void f32_finish(const GemmArgs& g, TC* C, const TS* b
     for (int u = 0; u < EPT; u++) v[u] += part[w * (BM * BN) + threadIdx.x + u * 256];
   const TS* resid = (const TS*)g.resid;
   const TS* cscale = (const TS*)g.col_scale;
+  if constexpr (NORM)
+#pragma unroll
+    for (int u = 0; u < EPT; u++) v[u] *= rms_inv((threadIdx.x + u * 256) / BN);
+  if constexpr (ROPE) {
+#pragma unroll
+    for (int u = 0; u < EPT; u++) {
+      const int e = threadIdx.x + u * 256, c = e % BN, m = m0 + e / BN, n = rope_tile_col(bx, c, g.rope_dh), step = g.rope_dh == 16 ? 8 : 16;
+      const float own = v[u] + (bias ? to_f(bias[n]) : 0.f), other = __shfl_xor(own, step, WAVE);
+      if (m >= m_end) continue;
+      const bool turn = (g.rope_mask >> blockIdx.z) & 1;
+      const float2 cs = turn ? ((const float2*)g.rope_cs)[(i64)(m % g.rope_S) * (g.rope_dh / 2) + (n & (g.rope_dh / 2 - 1))] : make_float2(1.f, 0.f);
+      C[(i64)m * g.ldc + n] = from_f<TC>(turn ? rope_value(own, other, c & step, cs) : own);
+    }
+    return;
+  }
   if constexpr (ACT) {                               // silu(gate) * up from the stored values, as the separate kernel
 #pragma unroll
     for (int u = 0; u < EPT; u++) {
@@ -140,7 +180,7 @@ __device__ __forceinline__ void f32_tile(const GemmArgs& g, const TA* A, const T
   };
   contract(A, Bm, wv);
   if (A2) contract(A2, B2, (wv + nw - nchunk % nw) % nw);
-  f32_finish<TC, TS, R, TM, TN, ACT>(g, C, bias, part, acc, parts, wv, lane, m0, m_end, n0);
+  f32_finish<TC, TS, R, TM, TN, ACT ? EPI_ACT : 0>(g, C, bias, part, acc, parts, wv, lane, m0, m_end, n0);
 }
 
 // The same for float32 operands on 16-byte boundaries (see staged_ok): a wave's pieces of 32 k's go straight into LDS that no
@@ -150,13 +190,15 @@ __device__ __forceinline__ void f32_tile(const GemmArgs& g, const TA* A, const T
 //  * operand with k along memory: 128-byte rows, 16-byte chunk c of row r in slot c ^ ((r >> 1) & 7);
 //  * operand stored k x rows: 32 rows of 128 bytes, k in row k ^ ((k >> 2) & 1), so that the two k's (4 apart) that the halves of
 //    a wave read at a time lie in different halves of the banks.
+#define STAGE_F32(EPI) (8192u + ((EPI) & EPI_NORM ? 256u : 0u))     // A, B, gains
 template <bool TR> struct StagedF32 {
   u32x4 d;
   unsigned off[4];
   int kc[4];                // k of this lane's share of wave-load i, relative to the piece
   unsigned ks;              // bytes per k
-  // act_half > 0: see ACT
-  __device__ __forceinline__ void init(const float* p, i64 ld, int r0, int r_end, int lane, const int* gather, int div, int act_half = 0) {
+  // act_half > 0: see ACT; rope_dh > 0: rows in the order of rope_tile_col, tile bx
+  __device__ __forceinline__ void init(const float* p, i64 ld, int r0, int r_end, int lane, const int* gather, int div, int act_half = 0,
+                                       int rope_dh = 0, int bx = 0) {
     d = make_desc(p);
     const unsigned ldb = (unsigned)ld * 4u;
     ks = TR ? ldb : 4u;
@@ -164,7 +206,7 @@ template <bool TR> struct StagedF32 {
     for (int i = 0; i < 4; i++) {
       if (!TR) {
         const int r = i * 8 + (lane >> 3), ch = (lane & 7) ^ ((r >> 1) & 7);
-        const int row = act_half ? (r >> 4) * act_half + min(r0 + (r & 15), act_half - 1) : min(r0 + r, r_end - 1);
+        const int row = act_half ? (r >> 4) * act_half + min(r0 + (r & 15), act_half - 1) : rope_dh ? rope_tile_col(bx, r, rope_dh) : min(r0 + r, r_end - 1);
         kc[i] = ch * 4;
         off[i] = (unsigned)(gather ? gather[row] / div : row) * ldb + (unsigned)ch * 16u;
       } else {
@@ -193,46 +235,63 @@ template <bool TR> struct StagedF32 {
     }
   }
 };
-template <bool AT, bool BT, bool ACT>
+template <bool AT, bool BT, int EPI>
 __device__ __forceinline__ void f32_tile_staged(const GemmArgs& g, const float* A, const float* Bm, float* C, const float* bias, int m0, int m_end,
-                                                int n0, int k0, int k_end, int nw, const float* A2, const float* B2) {
-  constexpr unsigned STAGE = 8192u;
+                                                int n0, int k0, int k_end, int nw, const float* A2, const float* B2, int bx = 0,
+                                                const float* gain = nullptr, float* nout = nullptr) {
+  constexpr bool ACT = EPI & EPI_ACT, ROPE = EPI & EPI_ROPE, NORM = EPI & EPI_NORM;
+  constexpr unsigned STAGE = STAGE_F32(EPI);
   extern __shared__ __attribute__((aligned(1024))) float part[];    // the waves' pieces, then their partial tiles
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   f32x16 acc[1][1] = {};
+  float sq = 0.f;
   const int nchunk = (k_end - k0 + 31) / 32, all = A2 ? 2 * nchunk : nchunk;
   const int parts = min(nw, max(all, 1));
   unsigned char* mine = (unsigned char*)part + wv * STAGE;
   const unsigned lds = lds_address(part) + (unsigned)wv * STAGE;
-  if (wv < parts && all > 0) {
-    StagedF32<AT> oa;
-    StagedF32<BT> ob;
+  StagedF32<AT> oa;
+  StagedF32<BT> ob;
+  const bool work = wv < parts && all > 0;
+  const u32x4 dg = make_desc(NORM ? gain : A);
+  auto issue = [&](int c) {                          // (a piece of the second pair of operands: the same offsets)
+    if (A2 && c >= nchunk) { oa.d = make_desc(A2); ob.d = make_desc(B2); c -= nchunk; }
+    oa.issue(lds, k0 + c * 32, k_end);
+    ob.issue(lds + 4096u, k0 + c * 32, k_end);
+    if constexpr (NORM) load_lds_b32(dg, __builtin_amdgcn_readfirstlane(lds + 8192u), c * 32 + lane < k_end ? (unsigned)(c * 32 + lane) * 4u : OOB);
+  };
+  if (work) {
     oa.init(A, g.lda, m0, m_end, lane, AT ? nullptr : g.a_gather, g.gather_div);
-    ob.init(Bm, g.ldb, n0, g.N, lane, nullptr, 1, ACT ? g.act_half : 0);
-    auto issue = [&](int c) {                        // (a piece of the second pair of operands: the same offsets)
-      if (A2 && c >= nchunk) { oa.d = make_desc(A2); ob.d = make_desc(B2); c -= nchunk; }
-      oa.issue(lds, k0 + c * 32, k_end);
-      ob.issue(lds + 4096u, k0 + c * 32, k_end);
-    };
+    ob.init(Bm, g.ldb, n0, g.N, lane, nullptr, 1, ACT ? g.act_half : 0, ROPE ? g.rope_dh : 0, bx);
     issue(wv);
+  }
+  if (work)
     for (int c = wv; c < all; c += nw) {
       wait_vmcnt<0>();
       float a[16], b[16];
       StagedF32<AT>::read(mine, lane, a);
       StagedF32<BT>::read(mine + 4096, lane, b);
+      if constexpr (NORM) {
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+          const float4 gv = *(const float4*)(mine + 8192 + (8 * j + 4 * (lane >> 5)) * 4);
+          const float gq[4] = {gv.x, gv.y, gv.z, gv.w};
+#pragma unroll
+          for (int i = 0; i < 4; i++) { sq += a[4 * j + i] * a[4 * j + i]; a[4 * j + i] *= gq[i]; }
+        }
+      }
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");            // the piece is in registers: its place is free
       __builtin_amdgcn_sched_barrier(0);
       if (c + nw < all) issue(c + nw);
 #pragma unroll
       for (int s = 0; s < 16; s++) acc[0][0] = mfma_f32(a[s], b[s], acc[0][0]);
     }
-  }
   __syncthreads();                                   // the partial tiles overlay the pieces
-  f32_finish<float, float, 32, 1, 1, ACT>(g, C, bias, part, acc, parts, wv, lane, m0, m_end, n0);
+  f32_finish<float, float, 32, 1, 1, EPI>(g, C, bias, part, acc, parts, wv, lane, m0, m_end, n0, bx, sq, A, gain, nout);
 }
 
-template <class TA, class TB, class TC, class TS, bool AT, bool BT, int R, int TM, int TN, bool ACT, bool STG>
+template <class TA, class TB, class TC, class TS, bool AT, bool BT, int R, int TM, int TN, int EPI, bool STG>
 __global__ void __launch_bounds__(R == 16 ? 1024 : 512) gemm_f32_k(GemmArgs g) {
+  constexpr bool ACT = EPI & EPI_ACT;
   constexpr int BM = R * TM, BN = ACT ? 16 : R * TN;
   const TA *A = (const TA*)g.A, *A2 = (const TA*)g.A2;
   const TB *Bm = (const TB*)g.B, *B2 = (const TB*)g.B2;
@@ -264,7 +323,11 @@ __global__ void __launch_bounds__(R == 16 ? 1024 : 512) gemm_f32_k(GemmArgs g) {
     for (int r = m0 + (int)(threadIdx.x & 63); r < min(m_end, m0 + BM); r += 64) live |= g.row_skip[r] == 0;
     if (!__any(live)) return;
   }
-  if constexpr (STG) f32_tile_staged<AT, BT, ACT>(g, A, Bm, C, bias, m0, m_end, blockIdx.x * BN, k0, k_end, g.k_waves, A2, B2);
+  if constexpr (STG) {
+    const float* gain = (const float*)(blockIdx.z == 0 ? g.norm_g[0] : blockIdx.z == 1 ? g.norm_g[1] : g.norm_g[2]);
+    float* nout = (float*)(blockIdx.z == 0 ? g.norm_out[0] : blockIdx.z == 1 ? g.norm_out[1] : g.norm_out[2]);
+    f32_tile_staged<AT, BT, EPI>(g, A, Bm, C, bias, m0, m_end, blockIdx.x * BN, k0, k_end, g.k_waves, A2, B2, blockIdx.x, gain, nout);
+  }
   else f32_tile<TA, TB, TC, TS, AT, BT, R, TM, TN, ACT>(g, A, Bm, C, bias, m0, m_end, blockIdx.x * BN, k0, k_end, g.k_waves, A2, B2);
 }
 
@@ -284,25 +347,25 @@ __global__ void __launch_bounds__(512) gemm_f32_batch_tn_k(GemmBatch b) {
   const float *A = (const float*)ka->p[i].A, *B = (const float*)ka->p[i].B;
   float* C = (float*)ka->p[i].C;
   const int nw = f32_k_waves(g.K, 32, 8);
-  if constexpr (STG) f32_tile_staged<true, true, false>(g, A, B, C, nullptr, by * 32, g.M, bx * 32, 0, g.K, nw, nullptr, nullptr);
+  if constexpr (STG) f32_tile_staged<true, true, 0>(g, A, B, C, nullptr, by * 32, g.M, bx * 32, 0, g.K, nw, nullptr, nullptr);
   else f32_tile<float, float, float, float, true, true, 32, 1, 1, false>(g, A, B, C, nullptr, by * 32, g.M, bx * 32, 0, g.K, nw, nullptr, nullptr);
 }
 
-template <class TA, class TB, class TC, class TS, bool AT, bool BT, int R, int TM, int TN, bool ACT = false, bool STG = false>
+template <class TA, class TB, class TC, class TS, bool AT, bool BT, int R, int TM, int TN, int EPI = 0, bool STG = false>
 static void go_shape(const GemmArgs& g, int nw, hipStream_t s) {
   const int gy = g.group_mode == 1 ? g.max_tiles : cdiv(g.M, R * TM);
-  const dim3 grid(ACT ? cdiv(g.act_half, 16) : cdiv(g.N, R * TN), gy, g.group_mode == 2 ? g.n_groups : g.group_mode == 0 ? g.n_sub : 1);
+  const dim3 grid(EPI & EPI_ACT ? cdiv(g.act_half, 16) : cdiv(g.N, R * TN), gy, g.group_mode == 2 ? g.n_groups : g.group_mode == 0 ? g.n_sub : 1);
   if (grid.x == 0 || grid.y == 0 || grid.z == 0) return;
-  const size_t smem = (size_t)nw * (STG ? 8192 : (R * TM) * (R * TN) * sizeof(float));
+  const size_t smem = (size_t)nw * (STG ? STAGE_F32(EPI) : (R * TM) * (R * TN) * sizeof(float));
   static std::atomic<unsigned long long> attr_mask{0};
   if (smem >= 65536 && attr_needed(attr_mask)) {
-    (void)hipFuncSetAttribute((const void*)gemm_f32_k<TA, TB, TC, TS, AT, BT, R, TM, TN, ACT, STG>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, STG ? 8 * 8192 : 8 * 4096 * TM * TN);
+    (void)hipFuncSetAttribute((const void*)gemm_f32_k<TA, TB, TC, TS, AT, BT, R, TM, TN, EPI, STG>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, STG ? 8 * STAGE_F32(EPI) : 8 * 4096 * TM * TN);
     attr_done(attr_mask);
   }
   GemmArgs a = g;
   a.k_waves = nw;
-  hipLaunchKernelGGL((gemm_f32_k<TA, TB, TC, TS, AT, BT, R, TM, TN, ACT, STG>), grid, dim3(64 * (nw > 4 ? nw : 4)), smem, s, a);
+  hipLaunchKernelGGL((gemm_f32_k<TA, TB, TC, TS, AT, BT, R, TM, TN, EPI, STG>), grid, dim3(64 * (nw > 4 ? nw : 4)), smem, s, a);
 }
 
 // whether f32_tile_staged takes the problem: loads of 4 elements inside the operands, which span less than 2 GiB
@@ -337,12 +400,16 @@ static void go(const GemmArgs& g, hipStream_t s) {
   if constexpr (std::is_same<TA, float>::value && std::is_same<TB, float>::value && !(AT && !BT))
     if (staged_ok(g)) {
       if constexpr (!AT && !BT)
-        if (g.act_half) { go_shape<TA, TB, TC, TS, AT, BT, 32, 1, 1, true, true>(g, nw, s); return; }
-      go_shape<TA, TB, TC, TS, AT, BT, 32, 1, 1, false, true>(g, nw, s);
+      {
+        if (g.act_half) { go_shape<TA, TB, TC, TS, AT, BT, 32, 1, 1, EPI_ACT, true>(g, nw, s); return; }
+        if (g.norm_g[0]) { go_shape<TA, TB, TC, TS, AT, BT, 32, 1, 1, EPI_NORM, true>(g, nw, s); return; }
+        if (g.rope_cs) { go_shape<TA, TB, TC, TS, AT, BT, 32, 1, 1, EPI_ROPE, true>(g, nw, s); return; }
+      }
+      go_shape<TA, TB, TC, TS, AT, BT, 32, 1, 1, 0, true>(g, nw, s);
       return;
     }
   if constexpr (!AT && !BT)
-    if (g.act_half) { go_shape<TA, TB, TC, TS, AT, BT, 32, 1, 1, true>(g, nw, s); return; }
+    if (g.act_half) { go_shape<TA, TB, TC, TS, AT, BT, 32, 1, 1, EPI_ACT>(g, nw, s); return; }
   const i64 z = g.group_mode == 2 ? g.n_groups : 1;
   if (g.group_mode != 1 && (i64)cdiv(g.M, 64) * cdiv(g.N, 32) * z * nw >= 4096) go_shape<TA, TB, TC, TS, AT, BT, 32, 2, 1>(g, nw, s);
   else go_shape<TA, TB, TC, TS, AT, BT, 32, 1, 1>(g, nw, s);
@@ -357,6 +424,15 @@ static void go_types(const GemmArgs& g, hipStream_t s) {
 int launch_gemm_generic(const GemmArgs& g, GemmTypes t, hipStream_t s) {
   if (g.group_mode == 1 && g.tile_bm != 32) return -1;
   if (g.act_half && (g.a_trans || g.b_trans || g.group_mode == 2 || g.bias || g.resid || g.tap || g.N != 2 * g.act_half)) return -1;
+  if (g.norm_g[0] || g.rope_cs) {
+    // norm or rotation: the staged float32 form only, with nothing else in the epilogue (and not both: no caller has that)
+    if (t.ta || t.tb || t.tc || t.tside || g.a_trans || g.b_trans || g.act_half || g.dact_out || g.resid || g.tap || g.A2 || g.group_mode ||
+        g.col_scale || (g.norm_g[0] && g.rope_cs) || !staged_ok(g))
+      return -1;
+    if (g.rope_cs && !rope_fits(g.rope_dh, g.N)) return -1;
+    for (int z = 0; g.norm_g[0] && z < g.n_sub; z++)
+      if (!g.norm_g[z] || ((uintptr_t)g.norm_g[z] & 15) || ((uintptr_t)g.norm_out[z] & 15)) return -1;
+  }
   int key = t.ta * 8 + t.tb * 4 + t.tc * 2 + t.tside;
   switch (key) {
     case 0: go_types<float, float, float, float>(g, s); break;            // fp32 everything

@@ -820,6 +820,17 @@ template <class TC> static void pick_batch_tile(GemmBatch& b, bool bulk, hipStre
 }
 static bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
+// norm and rotation: rows of 16-byte pieces, whole tiles of heads, and nothing else in the epilogue
+static bool norm_rope_ok(const GemmArgs& g, bool f32out) {
+  if (!g.norm_g[0] && !g.rope_cs) return true;
+  if (f32out || g.b_trans || g.act_half || g.resid || g.tap || g.group_mode != 0) return false;
+  if (g.rope_cs && !rope_fits(g.rope_dh, g.N)) return false;
+  if (g.norm_g[0] && g.K > 1024) return false;             // (a workgroup's pieces of the rows are in LDS all at once)
+  for (int z = 0; g.norm_g[0] && z < g.n_sub; z++)
+    if (!g.norm_g[z] || !aligned16(g.norm_g[z]) || !aligned16(g.norm_out[z])) return false;
+  return true;
+}
+
 int launch_gemm_mfma(const GemmArgs& g, GemmTypes t, hipStream_t s) {
   if (t.ta != 1 || t.tb != 1 || t.tside != 1) return 1;
   if (!aligned16(g.A) || !aligned16(g.B) || (g.lda & 7) || (g.ldb & 7)) return 1;
@@ -848,12 +859,13 @@ int launch_gemm_mfma(const GemmArgs& g, GemmTypes t, hipStream_t s) {
     if (a_rows * g.lda >= lim || b_rows * g.ldb >= lim) return 1;
   }
   const bool f32out = t.tc == 0;
+  if (!norm_rope_ok(g, f32out)) return 1;
   if (g.A2 && (!aligned16(g.A2) || !aligned16(g.B2) || !g.b_trans || f32out)) return 1;
   if (g.few_rows && !g.a_trans && !g.force_tile && (g.group_mode == 1 || (g.group_mode == 0 && !g.a_gather))) {
     launch_gemm_skinny(g, f32out, s);
     return 0;
   }
-  if (g.A2 || g.dact_out) return 1;
+  if (g.A2 || g.dact_out || g.norm_g[0] || g.rope_cs) return 1;
   if (!g.a_trans && !g.b_trans) {
     if (f32out) pick_tile<false, false, float>(g, s); else pick_tile<false, false, bf16>(g, s);
   } else if (!g.a_trans && g.b_trans) {

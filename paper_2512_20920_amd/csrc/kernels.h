@@ -45,6 +45,13 @@ struct GemmArgs {
   // the other way (generic kernel, kernel for few rows): the output would be the gradient at silu(gate) * up; with dact_gu =
   // [gate | up] rows (width 2 N), dact_out gets [dgate | dup] and C is not written
   const void* dact_gu = nullptr; void* dact_out = nullptr;
+  // Kernel for few rows and aligned float32 problems, both operands with k along memory:
+  //  * rotary encoding of the rounded output of the problems in rope_mask (bit per problem), heads of rope_dh columns (16 or a
+  //    multiple of 32), position = row % rope_S, table rope_cs[position][rope_dh / 2] of (cos, sin);
+  //  * RMSNorm of A's rows first: norm_g[problem] = gains (K of them), norm_out[problem] (may be null) = the normalised rows, dense.
+  //    (every column tile sums the squares of its rows, which it stages anyway)
+  const void* rope_cs = nullptr; int rope_S = 1, rope_dh = 0, rope_mask = 0;
+  const void* norm_g[3] = {nullptr, nullptr, nullptr}; void* norm_out[3] = {nullptr, nullptr, nullptr}; float norm_eps = 0.f;
   // (the same two kernels) a second pair of operands of the same shapes and strides: C = A B + A2 B2 (problem 0 of a launch)
   const void* A2 = nullptr; const void* B2 = nullptr;
   const void* col_scale = nullptr;       // generic kernel only
@@ -142,6 +149,18 @@ inline long long wgrad_grid_x(int xcd_m, int tiles_m, int tiles_n, int n_groups)
 inline int dense_grid_x(int xcd_m, int tiles_m, int tiles_n) {
   return 8 * ((tiles_m + xcd_m - 1) / xcd_m) * ((tiles_n + 8 / xcd_m - 1) / (8 / xcd_m));
 }
+
+// Tiles of the epilogues that pair columns: a 32-column tile holds two blocks of 16 that belong together, `first` and the columns
+// `apart` after it.  SwiGLU: 16 gate columns and the up columns of the same indices; rotary encoding: 16 columns of a head's
+// first half and their partners in its second (heads of 16: two whole heads, partners 8 apart).
+enum { EPI_ACT = 1, EPI_ROPE = 2, EPI_NORM = 4 };
+__host__ __device__ inline int rope_tile_col(int bx, int c, int dh) {
+  if (dh == 16) return bx * 32 + c;
+  const int hb = dh / 32, head = bx / hb;
+  return head * dh + (bx - head * hb) * 16 + (c >> 4) * (dh / 2) + (c & 15);
+}
+
+inline bool rope_fits(int dh, int N) { return (dh == 16 || (dh % 32 == 0 && (dh & (dh - 1)) == 0)) && N % dh == 0 && N % 32 == 0; }
 
 // element types of A, B, C, and of bias, residual and column scale (the storage type of streams and weights): 0 = f32, 1 = bf16
 struct GemmTypes { int ta, tb, tc, tside; };

@@ -144,11 +144,13 @@ def test_block_parity_drawn_geometries(wl):
 
 
 # What the kernels for small problems do beside a plain product: SwiGLU and its gradient in the epilogue, two pairs of operands
-# in one contraction, several problems in one launch.  One token, one past a tile of 32 and several tiles, with gate/up widths
+# in one contraction, several problems in one launch, norm and rotation with the projections (heads of 16, 64 and 128, two
+# pieces of a row per wave at 640).  One token, one past a tile of 32 and several tiles, with gate/up widths
 # that end inside a tile, fewer chunks of k than waves and more; 50 wide rows of 2 bytes are not 16-byte aligned (bf16 goes to
 # the float32 kernel).  Every expert selected at the small widths, whose logits lie too close for a selection to be compared.
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("d,H,E,k,I,Is,B,S", [(32, 2, 1, 1, 33, 70, 1, 1), (64, 4, 4, 4, 40, 24, 1, 33), (320, 5, 4, 1, 104, 168, 3, 47), (50, 5, 3, 3, 25, 50, 2, 9)])
+@pytest.mark.parametrize("d,H,E,k,I,Is,B,S", [(32, 2, 1, 1, 33, 70, 1, 1), (64, 4, 4, 4, 40, 24, 1, 33), (320, 5, 4, 1, 104, 168, 3, 47), (50, 5, 3, 3, 25, 50, 2, 9),
+                                              (1280, 10, 2, 2, 72, 64, 1, 37)])
 def test_block_parity_small_problems(dtype, d, H, E, k, I, Is, B, S):
     wl = synth.Workload(f"small_d{d}", d, H, d // H, E, k, I, Is, B, S, dtype, gain_jitter=0.02, seed=d + I)
     case = Case(wl)
