@@ -742,7 +742,16 @@ static void pick_tile(const GemmArgs& g, hipStream_t s) {
   }
   // below ~200 tiles of 128x128: 128x64 (two workgroups per CU)
   const i64 t128 = (i64)cdiv(g.M, 128) * cdiv(g.N, 128) * g.n_sub;
-  if (t128 < 200 && g.N >= 128) { go_128x64<AT, BT, TC>(g, s); return; }
+  if (t128 < 200 && g.N >= 128) {
+    // With a CU per workgroup a fourth stage (a third k-tile in flight) is free: 1024 rows, 2048 outputs, k = 2048: 17.0 -> 16.0 us,
+    // data gradient 19.1 -> 18.0; 700 rows 15.9 -> 14.8, 18.3 -> 16.4 (fifth and sixth: no change).  Half as many workgroups
+    // as CUs: half as large tiles (1024 outputs: 19.1 -> 15.4 us, 17.2 with a fourth stage alone).
+    const i64 t64 = (i64)cdiv(g.M, 128) * cdiv(g.N, 64) * g.n_sub;
+    if (t64 <= 128) go<64, 64, 2, AT, BT, TC, 4, 4>(g, s);
+    else if (t64 <= 256) go<128, 64, 4, AT, BT, TC, 8, 4>(g, s);
+    else go_128x64<AT, BT, TC>(g, s);
+    return;
+  }
   switch (dense_choice()) {
     case 4:
       go_256x256<AT, BT, TC>(g, s);
