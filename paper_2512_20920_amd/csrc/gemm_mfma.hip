@@ -583,7 +583,8 @@ __global__ void __launch_bounds__(NW * 64) gemm_mfma_k(GemmArgs g) {
   int m0, m_end, k0 = 0, k_end = g.K, rot_seed = 0;
   if (g.group_mode == 1) {
     if (!BT) rot_seed = by;     // per row tile (weights with k as the slow index are spread by their column tile already)
-    int ti = by;
+    int ti = g.reverse ? g.tile_count[0] - 1 - by : by;
+    if (ti < 0) return;         // (a plain grid is sized for the list's longest form)
     int grp = g.tile_group[ti];
     if (grp < 0) return;
     m0 = g.tile_m0[ti];

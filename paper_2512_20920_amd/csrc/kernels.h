@@ -58,6 +58,12 @@ struct GemmArgs {
   // group_mode 1: number of m-tiles of the list actually in use (device scalar written by the permutation kernel);
   // group_mode 2: the permutation kernel's flag that the routing is even (null: treated as uneven)
   const int* tile_count = nullptr;
+  // group_mode 1, MFMA kernel: the list's tiles in falling order, so the experts too.  A pass over expert weights that
+  // an earlier pass went over in rising order then begins with those that the 256 MB memory-side cache still holds;
+  // the results do not depend on it.  Merged gate/up pass of the inverse, whole step, falling / rising: 37 tokens
+  // 349 / 355 us, 300 and 1000 equal; dHh of the three-call step of 700 tokens 2209 / 2230, of the fused step of
+  // 128 tokens 1379 / 1385, of 300 1529 / 1543, of 700 1840 / 1854, from 1000 tokens on equal.
+  int reverse = 0;
   const int* tile_first = nullptr;       // per tile: (first tile of its expert) << 16 | tiles of that expert
   // MFMA kernel, dense problems: n_sub > 1 launches that many problems of one shape, layout and
   // strides together (grid z = problem); problem z >= 1 takes its operands, result and bias from sub*[z-1]
