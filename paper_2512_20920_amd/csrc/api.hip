@@ -57,7 +57,9 @@ struct revffn_ctx {
   int device = 0;
   void* slab = nullptr;
   size_t slab_bytes = 0;
-  hipStream_t side[4] = {nullptr, nullptr, nullptr, nullptr};   // helper streams for independent branches of one call
+  // helper streams for independent branches of one call: 0 beside the MoE half (the shared expert, the first query side;
+  // going back also the weight gradients), 1 the attention half of a sweep step
+  hipStream_t side[2] = {nullptr, nullptr};
   std::vector<hipEvent_t>* sync_ev = nullptr;  // ring of timing-free events for fork/join
   size_t sync_next = 0;
   bool use_streams = true;
@@ -558,7 +560,7 @@ int run_wgrad_batch(revffn_ctx* c, const GemmArgs* subs, int n, bool bulk, hipSt
 // chip overlap: the shared expert next to the routed experts, the rebuilding of X1^ and the attention half's
 // recomputation next to the MoE half's backward pass, the MoE half's weight gradients next to the attention half's
 // backward pass.  Recording an event and making another stream wait for it costs the host 13 us (a launch: 3 us), so
-// there are sixteen such edges in a training step, between long branches only, and none at all in a call too small
+// there are eleven such edges in a training step, between long branches only, and none at all in a call too small
 // for them to pay: below about 60 us of GPU time per evaluation of the block the host would be what the GPU waits for
 // (a step of a 512-wide block of 400 tokens: 909 us with 45 edges, 609 us on one stream).
 bool fork_pays(const revffn_ctx* c, i64 T) {
@@ -707,7 +709,7 @@ static int expert_rows_b(const revffn_ctx* c, i64 N, i64 E) {
 }
 
 // Recomputes n3, Um, routing, GU, Hh, Yp, shared expert and RS at y1.  q_x1 != null: the query side of the attention
-// half at q_x1 (which must not depend on this MoE evaluation) is enqueued on s while the routing chain runs.
+// half at q_x1 (which must not depend on this MoE evaluation) is enqueued beside it and done when s goes on.
 int moe_acts(revffn_ctx* c, const revffn_weights* w, const void* y1, i64 ld, int T, hipStream_t s,
              const void* q_x1 = nullptr, i64 q_ld = 0, int qB = 0, int qS = 0, const unsigned char* q_skip = nullptr) {
   const revffn_config& f = c->cfg;
@@ -716,16 +718,17 @@ int moe_acts(revffn_ctx* c, const revffn_weights* w, const void* y1, i64 ld, int
   c->lastT = T;
   c->lastT_rows = N;
   c->bm_b = expert_rows_b(c, N, E);
-  // routing needs Y1 and the weights only: next to the norm, the up-projection and the first query side
-  hipStream_t sr = side(c, s, 2);
-  after(c, s, sr);
-  router_fold(c, w, c->wrp, sr);
-  p_routing(c, y1, ld, c->wrp, w->b_router, T, sr);
+  // The norm and the up-projection come first, then one fork: the first query side and the shared expert (which needs Um
+  // only) run beside the routing chain and the routed experts, and join where the results are combined.  An edge costs
+  // the chain of launches more than the 6 us of the up-projection in front of the routing chain: with the routing chain
+  // on a helper stream instead (two forks, two joins) a step of 128 tokens took 1412 us, now 1391; 300 tokens 1646 and
+  // 1628, 4 x 512 2831 and 2809, four blocks of 1024 8421 and 8358; 20, 3000, 8192 tokens and few large experts within 1 %.
   const NormUp nu{y1, ld, w->norm_m, c->n3, c->Um};
   TRY(norm_up(c, &nu, 1, w->pup_m, T, s));
   hipStream_t s0 = side(c, s, 0);
-  if (Is) {                               // the shared expert needs Um only: next to the routed experts
-    after(c, s, s0);
+  if (q_x1 || Is) after(c, s, s0);
+  if (q_x1) TRY(attn_q(c, w, q_x1, q_ld, qB, qS, s0, q_skip));
+  if (Is) {
     GemmArgs gs = nt(c->Um, d, w->ws_gate_up, d, c->GUs, 2 * Is, T, 2 * Is, d);
     gs.act_out = c->Hs; gs.ldact = Is; gs.act_half = Is;      // Hs = silu(gate) * up with the GEMM
     gs.bulk = c->par;                                 // beside the routed experts' GEMMs
@@ -734,8 +737,8 @@ int moe_acts(revffn_ctx* c, const revffn_weights* w, const void* y1, i64 ld, int
     gd.bulk = gs.bulk;
     TRY(run_gemm(c, gd, s0));
   }
-  if (q_x1) TRY(attn_q(c, w, q_x1, q_ld, qB, qS, s, q_skip));
-  after(c, sr, s);                        // routing and permutation are ready
+  router_fold(c, w, c->wrp, s);
+  p_routing(c, y1, ld, c->wrp, w->b_router, T, s);
   // routed experts: GU = Xg . Wgu_e^T (rows gathered from Um through row_map), SwiGLU, Yp = Hh . Wd_e^T
   GemmArgs g1 = nt(c->Um, d, w->w_gate_up, d, c->GU, 2 * I, N, 2 * I, d);
   g1.group_mode = 1; g1.n_groups = E; g1.offsets = c->offsets; g1.b_group_stride = (i64)2 * I * d;
@@ -745,7 +748,7 @@ int moe_acts(revffn_ctx* c, const revffn_weights* w, const void* y1, i64 ld, int
   GemmArgs g2 = nt(c->Hh, I, w->w_down, I, c->Yp, d, N, d, I);
   g2.group_mode = 1; g2.n_groups = E; g2.offsets = c->offsets; g2.b_group_stride = (i64)d * I;
   TRY(run_gemm(c, g2, s));
-  if (Is) after(c, s0, s);
+  if (q_x1 || Is) after(c, s0, s);
   p_combine(c, dt, c->Yp, c->inv_map, c->wts, Is ? c->Ys : nullptr, c->gamma, c->RS, T, d, k, s);
   c->lastT = T;
   return 0;
@@ -765,7 +768,7 @@ int moe_out(revffn_ctx* c, const revffn_weights* w, const void* resid, i64 ldr, 
 // before the caller's next work.
 int finish(revffn_ctx* c, hipStream_t s, int e) {
   if (e && c && c->par)
-    for (int i = 0; i < 4; i++) after(c, c->side[i], s);
+    for (int i = 0; i < 2; i++) after(c, c->side[i], s);
   return e;
 }
 
@@ -1005,7 +1008,7 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
   // needs the recomputed Y1 first: one stream.)  s_attn: the stream the caller's inverse left X1^ on.
   hipStream_t sa = s;
   if (y1 && c->par && !reuse_attn) {
-    sa = s_attn ? s_attn : c->side[3];
+    sa = s_attn ? s_attn : c->side[1];
     if (!s_attn) after(c, s, sa);
   } else if (s_attn && s_attn != s) {
     after(c, s_attn, s);                  // no overlap in this call: X1^ is needed on s from here on
@@ -1025,7 +1028,7 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
   // that, so that each launch's last, partly filled round of workgroups is filled by the other stream; the rest, or
   // without helper streams all of the dense ones, are one launch near the end.  The column sums (bias and gain
   // gradients) are one launch at the end.
-  hipStream_t sw = side(c, s, 1), s0 = side(c, s, 0);
+  hipStream_t sw = side(c, s, 0);
   GemmArgs wg[GEMM_BATCH];
   int nwg = 0;
   bool sw_used = false;
@@ -1038,12 +1041,17 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
   const RouterBwd rb{c->probs, c->idx, E, f.norm_topk_prob, dz_bf16 ? c->dzb : nullptr, E1p};
   const RowCopy rc{w->w_router, Is ? w->ws_gate : w->w_router, c->wr_ext, dz_bf16 ? E : 0, dz_bf16 && Is ? 1 : 0};
   p_moe_bwd_rows(c, dt, c->dRS, c->Yp, c->Ys, c->inv_map, c->wts, c->gamma, c->dYp, c->dYs, c->dzext, T, d, k, E1, Is ? 1 : 0, rb, rc, s);
+  // The shared expert's data gradients go in front of the weight gradients on sw: a stream of their own is one more edge in
+  // the chain, and one more hardware queue (see the streams' creation).  Own stream / sw: 128 tokens 1386 / 1370 us,
+  // 3 x 333, adapters only, 1633 / 1626, skewed 2 x 2048 4553 / 4580, four blocks of 1024 8302 / 8255, others within 1 %.
+  hipEvent_t shared_done = nullptr;
   if (Is) {
-    after(c, s, s0);
+    after(c, s, sw);
     GemmArgs dh = nn(c->dYs, d, w->ws_down, Is, c->dHs, Is, T, Is, d);
     dh.dact_gu = c->GUs; dh.dact_out = c->dGUs;
-    TRY(run_gemm(c, dh, s0));
-    TRY(run_gemm(c, nn(c->dGUs, 2 * Is, w->ws_gate_up, d, c->dUm_sh, d, T, d, 2 * Is), s0));
+    TRY(run_gemm(c, dh, sw));
+    TRY(run_gemm(c, nn(c->dGUs, 2 * Is, w->ws_gate_up, d, c->dUm_sh, d, T, d, 2 * Is), sw));
+    if (sw != s) { shared_done = next_sync(c); (void)hipEventRecord(shared_done, sw); }
     if (GF(ws_down)) wg[nwg++] = tn(c->dYs, d, c->Hs, Is, GF(ws_down), Is, d, Is, T);
     if (GF(ws_gate_up)) wg[nwg++] = tn(c->dGUs, 2 * Is, c->Um, d, GF(ws_gate_up), d, 2 * Is, d, T);
   }
@@ -1057,7 +1065,8 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
     const bool down_behind = T >= 4096;
     auto down_wgrad = [&]() -> int {
       if (!GF(w_down)) return REVFFN_OK;
-      to_sw();
+      if (!Is || down_behind) to_sw();                                   // (else sw has waited for dYp already)
+      sw_used = true;
       GemmArgs b = tn(c->dYp, d, c->Hh, I, GF(w_down), I, d, I, N);        // dWd_e = dYp_e^T . Hh_e
       b.group_mode = 2; b.n_groups = E; b.offsets = c->offsets; b.tile_count = c->tile_cnt + 3; b.c_group_stride = (i64)d * I;
       return run_wgrad(c, b, sw);
@@ -1089,7 +1098,7 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
     GemmTypes tt{1, 1, 1, 1};
     if (launch_gemm_mfma(a, tt, s) == 0) dum_r = c->dUm_r;
   }
-  if (Is) after(c, s0, s);
+  if (shared_done) (void)hipStreamWaitEvent(s, shared_done, 0);
   p_dum_finalize(c, dt, c->dXg, c->inv_map, Is ? c->dUm_sh : nullptr, dum_r, c->dzext, w->w_router, w->ws_gate,
                       c->dUm, T, d, k, E, E1, s);
   if (GF(pup_m)) wg[nwg++] = tn(c->dUm, d, c->n3, h, GF(pup_m), h, d, h, T);
@@ -1250,7 +1259,10 @@ int revffn_create(revffn_ctx** out, const revffn_config* cfg, int32_t max_B, int
   { const char* e = getenv("REVFFN_EXPERT_NN"); if (e && atoi(e) >= 1 && atoi(e) <= 4) c->expert_nn = atoi(e); }
   c->sync_ev = new (std::nothrow) std::vector<hipEvent_t>();
   bool ok = c->sync_ev != nullptr;
-  for (int i = 0; ok && i < 4; i++) ok = hipStreamCreateWithFlags(&c->side[i], hipStreamNonBlocking) == hipSuccess;
+  // Two streams: a process has four hardware queues by default, streams beyond them share one, and work of streams that share
+  // runs one after the other.  With four helper streams two of them (of a second context even the caller's and one of them)
+  // did: a step of 300 tokens 1627 us, of 512 1790, of 3 x 333 without block gradients 1713; with two 1520, 1687, 1625.
+  for (int i = 0; ok && i < 2; i++) ok = hipStreamCreateWithFlags(&c->side[i], hipStreamNonBlocking) == hipSuccess;
   for (int i = 0; ok && i < 96; i++) {
     hipEvent_t e;
     ok = hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
@@ -1294,7 +1306,7 @@ void revffn_destroy(revffn_ctx* c) {
     for (hipEvent_t e : *c->sync_ev) (void)hipEventDestroy(e);
     delete c->sync_ev;
   }
-  for (int i = 0; i < 4; i++) if (c->side[i]) (void)hipStreamDestroy(c->side[i]);
+  for (int i = 0; i < 2; i++) if (c->side[i]) (void)hipStreamDestroy(c->side[i]);
   if (c->slab) (void)hipFree(c->slab);
   delete c;
 }
@@ -1464,8 +1476,8 @@ int revffn_inverse_backward(revffn_ctx* c, const revffn_weights* w, const void* 
   hipStream_t s = (hipStream_t)stream;
   const void* y1k = nullptr;
   i64 ldk = 0;
-  hipStream_t sa = s;                     // the stream the inverse leaves X1^ on (helper stream 3 beside the MoE backward pass)
-  TRY(finish(c, s, inverse_impl(c, w, y1, y2, x1, x2, B, S, ld, residual, s, &y1k, &ldk, c->side[3], &sa)));
+  hipStream_t sa = s;                     // the stream the inverse leaves X1^ on (helper stream 1 beside the MoE backward pass)
+  TRY(finish(c, s, inverse_impl(c, w, y1, y2, x1, x2, B, S, ld, residual, s, &y1k, &ldk, c->side[1], &sa)));
   return finish(c, s, backward_impl(c, w, x1, x2, y1k, ldk, dy1, dy2, dx1, dx2, g, B, S, ld, true, c->cfg.n_inv_iters >= 1, s,
                                     false, sa == s ? nullptr : sa));
 }
@@ -1547,7 +1559,7 @@ int revffn_stack_backward(revffn_ctx* c, const revffn_weights* w, const revffn_g
     const void* y1k = nullptr;
     i64 ldk = 0;
     hipStream_t sa = s;
-    TRY(finish(c, s, inverse_impl(c, w + l, y1, y2, y1, y2, B, S, ld, nullptr, s, &y1k, &ldk, c->side[3], &sa)));
+    TRY(finish(c, s, inverse_impl(c, w + l, y1, y2, y1, y2, B, S, ld, nullptr, s, &y1k, &ldk, c->side[1], &sa)));
     TRY(finish(c, s, backward_impl(c, w + l, y1, y2, y1k, ldk, dy1, dy2, dy1, dy2, g ? g + l : nullptr, B, S, ld, true, c->cfg.n_inv_iters >= 1, s,
                                    false, sa == s ? nullptr : sa)));
   }
