@@ -297,6 +297,15 @@ bool few_rows(const revffn_ctx* c, const GemmArgs& g) {
   return g.group_mode == 0 && !g.a_trans && g.M <= 2 * c->call_T && gemm_few_rows(c->call_T, g.N);
 }
 
+// Up to this mean of rows per expert nearly all experts fit in one tile of 128 rows
+constexpr i64 ROWS_ONE_TILE = 118;
+// the routed experts' weights are more than the memory-side cache keeps from one pass over them to the next
+// (of the experts that the rows reach)
+bool experts_pass_through(const revffn_ctx* c, i64 rows) {
+  const revffn_config& f = c->cfg;
+  return 3.0 * (double)(rows < f.n_experts ? rows : f.n_experts) * f.d_expert * f.d_model * c->es >= (double)(1 << 28);
+}
+
 int run_gemm(revffn_ctx* c, GemmArgs g, int ta, int tb, int tc, hipStream_t s) {
   g.few_rows = few_rows(c, g);
   GemmTypes t{ta, tb, tc, c->dt};
@@ -352,12 +361,17 @@ int run_gemm(revffn_ctx* c, GemmArgs g, int ta, int tb, int tc, hipStream_t s) {
       if (tall && g.b_trans && shape != 4) g.tile_bn = 128;
       if (g.few_rows) {
         g.tile_group = c->tg_a; g.tile_m0 = c->tm_a; g.max_tiles = (int)low; g.tile_bm = BM_A; g.tile_count = c->tile_cnt; g.tile_first = c->tf_a;
+        // (Weights past the caches, see GemmArgs::once; with k as the slow index a line belongs to two tiles, which does not pay
+        // where k is long.  Through / past, us: 8, 16, 25 tokens at the Qwen shape 862, 1005, 1107 / 816, 972, 1043;
+        // merged 16, 29 tokens 300, 344 / 280, 318; 8 experts of 14336, 8 tokens, the forward layout only / both 2589 / 2629.)
+        g.once = rows <= 16 * E && (!g.b_trans || g.K <= 2048) && experts_pass_through(c, rows);
       } else if (tall) {
         g.tile_group = c->tg_c; g.tile_m0 = c->tm_c; g.max_tiles = c->max_tiles_c; g.tile_bm = BM_C; g.tile_count = c->tile_cnt + 2;
         if (c->max_tiles_c < 32768) g.tile_first = c->tf_c;      // (the packed entry holds 15 + 16 bits)
       } else {
         g.tile_group = c->tg_b; g.tile_m0 = c->tm_b; g.max_tiles = c->max_tiles_b; g.tile_bm = c->bm_b; g.tile_count = c->tile_cnt + 1;
         if (c->max_tiles_b < 32768) g.tile_first = c->tf_b;
+        g.once = rows <= ROWS_ONE_TILE * E && experts_pass_through(c, rows);
       }
     }
     if (!g.few_rows) g.dact_out = nullptr;
@@ -382,6 +396,7 @@ int run_gemm(revffn_ctx* c, const GemmArgs& g, hipStream_t s) { return run_gemm(
 int run_wgrad(revffn_ctx* c, const GemmArgs& g0, hipStream_t s) {
   GemmArgs g = g0;
   g.bulk = c->par;
+  g.once = experts_pass_through(c, c->lastT_rows);
   return run_gemm(c, g, c->dt, c->dt, c->gdt, s);
 }
 
@@ -536,6 +551,7 @@ int run_wgrad_batch(revffn_ctx* c, const GemmArgs* subs, int n, bool bulk, hipSt
   const bool f32 = c->dt == 0 && c->gdt == 0;
   if (f32 || (c->dt == 1 && c->mode == 0)) {
     GemmBatch b;
+    b.once = experts_pass_through(c, c->lastT_rows);
     double fl = 0, by = 0;
     for (int i = 0; i < n; i++) {
       const GemmArgs& g = subs[i];
@@ -705,7 +721,7 @@ void router_fold(revffn_ctx* c, const revffn_weights* w, float* dst, hipStream_t
 // that reuses a routing sees the height its lists were built with.
 static int expert_rows_b(const revffn_ctx* c, i64 N, i64 E) {
   if (c->expert_tile || c->expert_nt || c->expert_nn) return BM_B;          // a forced shape (tuning aid) keeps 128
-  return (N > 118 * E && N <= 152 * E) ? BM_B_MID : BM_B;
+  return (N > ROWS_ONE_TILE * E && N <= 152 * E) ? BM_B_MID : BM_B;
 }
 
 // Recomputes n3, Um, routing, GU, Hh, Yp, shared expert and RS at y1.  q_x1 != null: the query side of the attention

@@ -191,48 +191,56 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, TC* C, const vo
     // (Staging the tile through LDS to store whole 128-byte lines, 16 bytes per lane, measured no faster: these
     // stores are not what bounds the weight-gradient kernels.)
     const bool full = (m0 + BM <= m_end) && (n0 + BN <= g.N);
-    if constexpr (sizeof(TC) == 2) {
-      // Whole tiles of 2-byte results: neighbouring lanes hold neighbouring columns of the same rows, so a pair of
-      // lanes swaps one value per two rows (the even lane gives its value of the odd row and gets the neighbour's
-      // value of the even row) and each lane stores 4 bytes, two columns of one row: half as many store
-      // instructions, and the stores of a tile are bound by their number (per-expert weight gradients 10 % faster,
-      // 1-2 % of a step).  Going on to a 4x4 transpose inside a quad and 8-byte stores is slower than no packing at
-      // all: one instruction then touches eight rows.
-      if (full && !(g.ldc & 1) && !((uintptr_t)C & 3) && !g.no_packed_stores) {
-        const bool odd = lane & 1;
-        typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_v;
+    auto store = [&](auto once) {                    // (weight gradients that nothing on the chip will read: see GemmArgs::once)
+      auto put = [](auto v, auto* p) {
+        if constexpr (decltype(once)::value) __builtin_nontemporal_store(v, p);
+        else *p = v;
+      };
+      if constexpr (sizeof(TC) == 2) {
+        // Whole tiles of 2-byte results: neighbouring lanes hold neighbouring columns of the same rows, so a pair of
+        // lanes swaps one value per two rows (the even lane gives its value of the odd row and gets the neighbour's
+        // value of the even row) and each lane stores 4 bytes, two columns of one row: half as many store
+        // instructions, and the stores of a tile are bound by their number (per-expert weight gradients 10 % faster,
+        // 1-2 % of a step).  Going on to a 4x4 transpose inside a quad and 8-byte stores is slower than no packing at
+        // all: one instruction then touches eight rows.
+        if (full && !(g.ldc & 1) && !((uintptr_t)C & 3) && !g.no_packed_stores) {
+          const bool odd = lane & 1;
+          typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_v;
 #pragma unroll
-        for (int i = 0; i < TE; i++) {
-          // even lane: row of element e, its own column; odd lane: the row below, the column to its left
-          TC* cp = C + (i64)(m0 + rb[i] + (lane >> 5) * 4 + (odd ? 1 : 0)) * g.ldc + n0 + (lane & 31) - (odd ? 1 : 0);
+          for (int i = 0; i < TE; i++) {
+            // even lane: row of element e, its own column; odd lane: the row below, the column to its left
+            TC* cp = C + (i64)(m0 + rb[i] + (lane >> 5) * 4 + (odd ? 1 : 0)) * g.ldc + n0 + (lane & 31) - (odd ? 1 : 0);
 #pragma unroll
-          for (int e = 0; e < 16; e += 2) {
-            const int dm = (e >> 2) * 8 + (e & 3);
+            for (int e = 0; e < 16; e += 2) {
+              const int dm = (e >> 2) * 8 + (e & 3);
 #pragma unroll
-            for (int j = 0; j < TN; j++) {
-              float l, r;
-              pair_rows(odd, acc[i][j][e], acc[i][j][e + 1], &l, &r);
-              bf16x2_v w;
-              w[0] = (__bf16)l; w[1] = (__bf16)r;
-              *(bf16x2_v*)(cp + (i64)dm * g.ldc + cb[j]) = w;
+              for (int j = 0; j < TN; j++) {
+                float l, r;
+                pair_rows(odd, acc[i][j][e], acc[i][j][e + 1], &l, &r);
+                bf16x2_v w;
+                w[0] = (__bf16)l; w[1] = (__bf16)r;
+                put(w, (bf16x2_v*)(cp + (i64)dm * g.ldc + cb[j]));
+              }
             }
           }
+          return;
         }
-        return;
       }
-    }
 #pragma unroll
-    for (int i = 0; i < TE; i++) {
-      TC* cp = C + (i64)(m0 + rb[i] + (lane >> 5) * 4) * g.ldc + n0 + (lane & 31);
+      for (int i = 0; i < TE; i++) {
+        TC* cp = C + (i64)(m0 + rb[i] + (lane >> 5) * 4) * g.ldc + n0 + (lane & 31);
 #pragma unroll
-      for (int e = 0; e < 16; e++) {
-        const int dm = (e >> 2) * 8 + (e & 3);
-        const bool row_ok = full || (m0 + rb[i] + (lane >> 5) * 4 + dm < m_end);
+        for (int e = 0; e < 16; e++) {
+          const int dm = (e >> 2) * 8 + (e & 3);
+          const bool row_ok = full || (m0 + rb[i] + (lane >> 5) * 4 + dm < m_end);
 #pragma unroll
-        for (int j = 0; j < TN; j++)
-          if (row_ok && (full || n0 + cb[j] + (lane & 31) < g.N)) cp[(i64)dm * g.ldc + cb[j]] = (TC)acc[i][j][e];
+          for (int j = 0; j < TN; j++)
+            if (row_ok && (full || n0 + cb[j] + (lane & 31) < g.N)) put((TC)acc[i][j][e], cp + (i64)dm * g.ldc + cb[j]);
+        }
       }
-    }
+    };
+    if constexpr (AT && BT) { if (g.once) { store(std::true_type{}); return; } }
+    store(std::false_type{});
     return;
   }
   // Two phases per 32-column block: every load (bias, residual) and all arithmetic on loaded values
@@ -336,6 +344,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const bf16* A, cons
   static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile must be made of 32x32 blocks");
   static_assert(((BM + BN) * KB) % (512 * NW) == 0 && (BM * KB) % 512 == 0 && LPW % KS == 0 || KB == BK, "wave-loads must divide evenly");
   static_assert((BM + BN) % (8 * NW) == 0 && BM % 8 == 0, "wave-loads must divide evenly");
+  constexpr bool ONCE = !AT && BM == 128 && BN == 256;       // (the routed experts' tile for few rows)
   static_assert(KB == BK || (AT && BT), "a shorter k-tile only for operands stored k x rows");
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int n0 = bx * BN;
@@ -371,7 +380,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const bf16* A, cons
     const bool isA = (wv * LPW + i) < ALOADS;        // wave-uniform
     const int kr = kt + rot >= nk ? kt + rot - nk : kt + rot;
     const unsigned off = (kt < nk && kr < ntile[i]) ? base[i] + (unsigned)kr * (isA ? kstep_a : kstep_b) : OOB;
-    load_lds_b128(isA ? da : db, lw + (unsigned)(kt % NS) * STAGE + i * 1024, off);
+    const unsigned dst = lw + (unsigned)(kt % NS) * STAGE + i * 1024;
+    if (ONCE && !isA && g.once) load_lds_b128_once(db, dst, off);
+    else load_lds_b128(isA ? da : db, dst, off);
   };
 
   f32x16 acc[TE][TN];
@@ -789,6 +800,7 @@ __global__ void __launch_bounds__(NW * 64) gemm_batch_tn_k(GemmBatch b) {
   GemmArgs g;
   g.M = ka->p[i].M; g.N = ka->p[i].N; g.K = ka->p[i].K;
   g.lda = ka->p[i].lda; g.ldb = ka->p[i].ldb; g.ldc = ka->p[i].ldc;
+  g.once = ka->once;
   const bf16 *A = (const bf16*)ka->p[i].A, *B = (const bf16*)ka->p[i].B;
   TC* C = (TC*)ka->p[i].C;
   if constexpr (NS == PHASED) gemm_tile_phased<true, true, TC>(g, A, B, C, nullptr, bx, by * BM, g.M, 0, g.K);

@@ -81,6 +81,10 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
   const u32x4 dg = make_desc(NORM ? gain : A);
   const unsigned my = (unsigned)wv * NS * STAGE;     // this wave's part of LDS
   const unsigned lds0 = lds_address(smem) + my;
+  auto load_b = [&](u32x4 rb, unsigned lds, unsigned off) {
+    if (GRP && g.once) load_lds_b128_once(rb, lds, off);
+    else load_lds_b128(rb, lds, off);
+  };
   auto issue = [&](int p, int stage) {
     const bool second = pair && p >= np1;
     const int k0 = (second ? p - np1 : p) * 64;
@@ -92,10 +96,10 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
       const bool in = k0 + akc[i] < g.K;
       load_lds_b128(ra, __builtin_amdgcn_readfirstlane(dst + i * 1024u), in ? aoff[i] + (unsigned)k0 * 2u : OOB);
       if constexpr (!BT) {
-        load_lds_b128(rb, __builtin_amdgcn_readfirstlane(dst + OPD + i * 1024u), in ? boff[i] + (unsigned)k0 * 2u : OOB);
+        load_b(rb, __builtin_amdgcn_readfirstlane(dst + OPD + i * 1024u), in ? boff[i] + (unsigned)k0 * 2u : OOB);
       } else {
         const bool kin = k0 + i * 16 + (lane >> 2) < g.K && boff[i] != OOB;
-        load_lds_b128(rb, __builtin_amdgcn_readfirstlane(dst + OPD + i * 1024u), kin ? boff[i] + (unsigned)k0 * ldb_b : OOB);
+        load_b(rb, __builtin_amdgcn_readfirstlane(dst + OPD + i * 1024u), kin ? boff[i] + (unsigned)k0 * ldb_b : OOB);
       }
     }
   };

@@ -24,6 +24,11 @@ template <class D> __device__ __forceinline__ void load_lds_b128(D desc, unsigne
   asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                :: "s"(lds_addr), "v"(voff), "s"(desc) : "memory", "m0");
 }
+// the same for data that is used once: it does not push other lines out of the caches
+template <class D> __device__ __forceinline__ void load_lds_b128_once(D desc, unsigned lds_addr, unsigned voff) {
+  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds"
+               :: "s"(lds_addr), "v"(voff), "s"(desc) : "memory", "m0");
+}
 // the same with a wave-uniform byte offset added
 __device__ __forceinline__ void load_lds_b128_s(u32x4 desc, unsigned lds_addr, unsigned voff, unsigned soff) {
   soff = __builtin_amdgcn_readfirstlane(soff);
