@@ -396,7 +396,6 @@ int run_gemm(revffn_ctx* c, const GemmArgs& g, hipStream_t s) { return run_gemm(
 int run_wgrad(revffn_ctx* c, const GemmArgs& g0, hipStream_t s) {
   GemmArgs g = g0;
   g.bulk = c->par;
-  g.once = experts_pass_through(c, c->lastT_rows);
   return run_gemm(c, g, c->dt, c->dt, c->gdt, s);
 }
 
@@ -551,7 +550,6 @@ int run_wgrad_batch(revffn_ctx* c, const GemmArgs* subs, int n, bool bulk, hipSt
   const bool f32 = c->dt == 0 && c->gdt == 0;
   if (f32 || (c->dt == 1 && c->mode == 0)) {
     GemmBatch b;
-    b.once = experts_pass_through(c, c->lastT_rows);
     double fl = 0, by = 0;
     for (int i = 0; i < n; i++) {
       const GemmArgs& g = subs[i];
@@ -893,7 +891,6 @@ int moe_merged(revffn_ctx* c, const revffn_weights* w, const revffn_merged* m, c
   g1.group_mode = 1; g1.n_groups = E; g1.offsets = c->offsets; g1.b_group_stride = (i64)2 * I * h;
   g1.a_gather = c->row_map; g1.gather_div = k;
   g1.act_out = c->Hh; g1.ldact = I; g1.act_half = I;
-  g1.reverse = sign < 0;      // the inverse's pass over the experts, falling (see GemmArgs::reverse)
   TRY(run_gemm(c, g1, s));
   GemmArgs g2 = nt(c->Hh, I, m->w_down, I, c->Yp, h, N, h, I);
   g2.group_mode = 1; g2.n_groups = E; g2.offsets = c->offsets; g2.b_group_stride = (i64)h * I;
@@ -1091,7 +1088,6 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
     GemmArgs a = nn(c->dYp, d, w->w_down, I, c->dHh, I, N, I, d);          // dHh = dYp . Wd_e
     a.group_mode = 1; a.n_groups = E; a.offsets = c->offsets; a.b_group_stride = (i64)d * I;
     a.dact_gu = c->GU; a.dact_out = c->dGU;
-    a.reverse = 1;            // Yp's product went over w_down rising
     TRY(run_gemm(c, a, s));
     if (down_behind) TRY(down_wgrad());
     if (GF(w_gate_up)) {

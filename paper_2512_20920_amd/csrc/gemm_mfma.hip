@@ -191,56 +191,52 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, TC* C, const vo
     // (Staging the tile through LDS to store whole 128-byte lines, 16 bytes per lane, measured no faster: these
     // stores are not what bounds the weight-gradient kernels.)
     const bool full = (m0 + BM <= m_end) && (n0 + BN <= g.N);
-    auto store = [&](auto once) {                    // (weight gradients that nothing on the chip will read: see GemmArgs::once)
-      auto put = [](auto v, auto* p) {
-        if constexpr (decltype(once)::value) __builtin_nontemporal_store(v, p);
-        else *p = v;
-      };
-      if constexpr (sizeof(TC) == 2) {
-        // Whole tiles of 2-byte results: neighbouring lanes hold neighbouring columns of the same rows, so a pair of
-        // lanes swaps one value per two rows (the even lane gives its value of the odd row and gets the neighbour's
-        // value of the even row) and each lane stores 4 bytes, two columns of one row: half as many store
-        // instructions, and the stores of a tile are bound by their number (per-expert weight gradients 10 % faster,
-        // 1-2 % of a step).  Going on to a 4x4 transpose inside a quad and 8-byte stores is slower than no packing at
-        // all: one instruction then touches eight rows.
-        if (full && !(g.ldc & 1) && !((uintptr_t)C & 3) && !g.no_packed_stores) {
-          const bool odd = lane & 1;
-          typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_v;
+    auto put = [](auto v, auto* p) {                 // (weight gradients go past the caches, see GemmArgs::once)
+      if constexpr (AT && BT) __builtin_nontemporal_store(v, p);
+      else *p = v;
+    };
+    if constexpr (sizeof(TC) == 2) {
+      // Whole tiles of 2-byte results: neighbouring lanes hold neighbouring columns of the same rows, so a pair of
+      // lanes swaps one value per two rows (the even lane gives its value of the odd row and gets the neighbour's
+      // value of the even row) and each lane stores 4 bytes, two columns of one row: half as many store
+      // instructions, and the stores of a tile are bound by their number (per-expert weight gradients 10 % faster,
+      // 1-2 % of a step).  Going on to a 4x4 transpose inside a quad and 8-byte stores is slower than no packing at
+      // all: one instruction then touches eight rows.
+      if (full && !(g.ldc & 1) && !((uintptr_t)C & 3) && !g.no_packed_stores) {
+        const bool odd = lane & 1;
+        typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_v;
 #pragma unroll
-          for (int i = 0; i < TE; i++) {
-            // even lane: row of element e, its own column; odd lane: the row below, the column to its left
-            TC* cp = C + (i64)(m0 + rb[i] + (lane >> 5) * 4 + (odd ? 1 : 0)) * g.ldc + n0 + (lane & 31) - (odd ? 1 : 0);
+        for (int i = 0; i < TE; i++) {
+          // even lane: row of element e, its own column; odd lane: the row below, the column to its left
+          TC* cp = C + (i64)(m0 + rb[i] + (lane >> 5) * 4 + (odd ? 1 : 0)) * g.ldc + n0 + (lane & 31) - (odd ? 1 : 0);
 #pragma unroll
-            for (int e = 0; e < 16; e += 2) {
-              const int dm = (e >> 2) * 8 + (e & 3);
+          for (int e = 0; e < 16; e += 2) {
+            const int dm = (e >> 2) * 8 + (e & 3);
 #pragma unroll
-              for (int j = 0; j < TN; j++) {
-                float l, r;
-                pair_rows(odd, acc[i][j][e], acc[i][j][e + 1], &l, &r);
-                bf16x2_v w;
-                w[0] = (__bf16)l; w[1] = (__bf16)r;
-                put(w, (bf16x2_v*)(cp + (i64)dm * g.ldc + cb[j]));
-              }
+            for (int j = 0; j < TN; j++) {
+              float l, r;
+              pair_rows(odd, acc[i][j][e], acc[i][j][e + 1], &l, &r);
+              bf16x2_v w;
+              w[0] = (__bf16)l; w[1] = (__bf16)r;
+              put(w, (bf16x2_v*)(cp + (i64)dm * g.ldc + cb[j]));
             }
           }
-          return;
         }
+        return;
       }
+    }
 #pragma unroll
-      for (int i = 0; i < TE; i++) {
-        TC* cp = C + (i64)(m0 + rb[i] + (lane >> 5) * 4) * g.ldc + n0 + (lane & 31);
+    for (int i = 0; i < TE; i++) {
+      TC* cp = C + (i64)(m0 + rb[i] + (lane >> 5) * 4) * g.ldc + n0 + (lane & 31);
 #pragma unroll
-        for (int e = 0; e < 16; e++) {
-          const int dm = (e >> 2) * 8 + (e & 3);
-          const bool row_ok = full || (m0 + rb[i] + (lane >> 5) * 4 + dm < m_end);
+      for (int e = 0; e < 16; e++) {
+        const int dm = (e >> 2) * 8 + (e & 3);
+        const bool row_ok = full || (m0 + rb[i] + (lane >> 5) * 4 + dm < m_end);
 #pragma unroll
-          for (int j = 0; j < TN; j++)
-            if (row_ok && (full || n0 + cb[j] + (lane & 31) < g.N)) put((TC)acc[i][j][e], cp + (i64)dm * g.ldc + cb[j]);
-        }
+        for (int j = 0; j < TN; j++)
+          if (row_ok && (full || n0 + cb[j] + (lane & 31) < g.N)) put((TC)acc[i][j][e], cp + (i64)dm * g.ldc + cb[j]);
       }
-    };
-    if constexpr (AT && BT) { if (g.once) { store(std::true_type{}); return; } }
-    store(std::false_type{});
+    }
     return;
   }
   // Two phases per 32-column block: every load (bias, residual) and all arithmetic on loaded values
@@ -331,7 +327,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, TC* C, const vo
 }
 
 // One output tile; TE = 32-row blocks per wave.
-template <int BM, int BN, int WGM, bool AT, bool BT, class TC, int NW, int NS, int TE, int KB = BK>
+template <int BM, int BN, int WGM, bool AT, bool BT, class TC, int NW, int NS, int TE, int KB = BK, bool ONCE = false>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const bf16* A, const bf16* Bm, TC* C, const void* bias_ptr,
                                           int bx, int bz, int m0, int m_end, int k0, int k_end, int rot_seed) {
   constexpr int WGN = NW / WGM;                      // waves along n
@@ -344,7 +340,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const bf16* A, cons
   static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile must be made of 32x32 blocks");
   static_assert(((BM + BN) * KB) % (512 * NW) == 0 && (BM * KB) % 512 == 0 && LPW % KS == 0 || KB == BK, "wave-loads must divide evenly");
   static_assert((BM + BN) % (8 * NW) == 0 && BM % 8 == 0, "wave-loads must divide evenly");
-  constexpr bool ONCE = !AT && BM == 128 && BN == 256;       // (the routed experts' tile for few rows)
   static_assert(KB == BK || (AT && BT), "a shorter k-tile only for operands stored k x rows");
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int n0 = bx * BN;
@@ -381,7 +376,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const bf16* A, cons
     const int kr = kt + rot >= nk ? kt + rot - nk : kt + rot;
     const unsigned off = (kt < nk && kr < ntile[i]) ? base[i] + (unsigned)kr * (isA ? kstep_a : kstep_b) : OOB;
     const unsigned dst = lw + (unsigned)(kt % NS) * STAGE + i * 1024;
-    if (ONCE && !isA && g.once) load_lds_b128_once(db, dst, off);
+    if (ONCE && !isA) load_lds_b128_once(db, dst, off);
     else load_lds_b128(isA ? da : db, dst, off);
   };
 
@@ -579,7 +574,7 @@ __device__ __forceinline__ void gemm_tile_phased(const GemmArgs& g, const bf16* 
   gemm_epilogue<256, 256, AT, BT, TC, 4, 2>(g, C, bias_ptr, bx, m0, m_end, rb, cb, wn, acc);
 }
 
-template <int BM, int BN, int WGM, bool AT, bool BT, class TC, int NW, int NS, int KB = BK>
+template <int BM, int BN, int WGM, bool AT, bool BT, class TC, int NW, int NS, int KB = BK, bool ONCE = false>
 __global__ void __launch_bounds__(NW * 64) gemm_mfma_k(GemmArgs g) {
   constexpr int TM = BM / WGM / 32;
   const bf16* A = (const bf16*)g.A;
@@ -594,8 +589,7 @@ __global__ void __launch_bounds__(NW * 64) gemm_mfma_k(GemmArgs g) {
   int m0, m_end, k0 = 0, k_end = g.K, rot_seed = 0;
   if (g.group_mode == 1) {
     if (!BT) rot_seed = by;     // per row tile (weights with k as the slow index are spread by their column tile already)
-    int ti = g.reverse ? g.tile_count[0] - 1 - by : by;
-    if (ti < 0) return;         // (a plain grid is sized for the list's longest form)
+    int ti = by;
     int grp = g.tile_group[ti];
     if (grp < 0) return;
     m0 = g.tile_m0[ti];
@@ -623,7 +617,7 @@ __global__ void __launch_bounds__(NW * 64) gemm_mfma_k(GemmArgs g) {
     if (!__any(live)) return;
   }
   if constexpr (NS == PHASED) gemm_tile_phased<AT, BT, TC>(g, A, Bm, C, bias, bx, m0, m_end, k0, k_end);
-  else gemm_tile<BM, BN, WGM, AT, BT, TC, NW, NS, TM, KB>(g, A, Bm, C, bias, bx, bz, m0, m_end, k0, k_end, rot_seed);
+  else gemm_tile<BM, BN, WGM, AT, BT, TC, NW, NS, TM, KB, ONCE>(g, A, Bm, C, bias, bx, bz, m0, m_end, k0, k_end, rot_seed);
 }
 
 // REVFFN_XCD (tuning aid): 0 = plain 2-D grids, tiles land on the XCDs round-robin
@@ -633,7 +627,7 @@ static int xcd_enabled() {
   return v;
 }
 
-template <int BM, int BN, int WGM, bool AT, bool BT, class TC, int NW, int NS, int KB = BK>
+template <int BM, int BN, int WGM, bool AT, bool BT, class TC, int NW, int NS, int KB = BK, bool ONCE = false>
 static void go(const GemmArgs& g0, hipStream_t s) {
   GemmArgs g = g0;
   { static int off = -1; if (off < 0) { const char* e = getenv("REVFFN_NO_PACKED_STORES"); off = e ? atoi(e) : 0; } g.no_packed_stores = off; }
@@ -660,11 +654,11 @@ static void go(const GemmArgs& g0, hipStream_t s) {
   static_assert(smem <= 160 * 1024, "LDS stages exceed the CU's 160 KiB");
   static std::atomic<unsigned long long> attr_mask{0};
   if (attr_needed(attr_mask)) {
-    (void)hipFuncSetAttribute((const void*)gemm_mfma_k<BM, BN, WGM, AT, BT, TC, NW, NS, KB>,
+    (void)hipFuncSetAttribute((const void*)gemm_mfma_k<BM, BN, WGM, AT, BT, TC, NW, NS, KB, ONCE>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     attr_done(attr_mask);
   }
-  hipLaunchKernelGGL((gemm_mfma_k<BM, BN, WGM, AT, BT, TC, NW, NS, KB>), grid, dim3(NW * 64), smem, s, g);
+  hipLaunchKernelGGL((gemm_mfma_k<BM, BN, WGM, AT, BT, TC, NW, NS, KB, ONCE>), grid, dim3(NW * 64), smem, s, g);
 }
 
 // The tile shapes: 256x128 and 128x256 (8 waves, one workgroup per CU), 256x256 (2 stages), 128x128 (8 waves of 32x64,
@@ -725,6 +719,7 @@ static void pick_tile(const GemmArgs& g, hipStream_t s) {
       if constexpr (!BT) { if (g.tile_bm == 160) { go_160x256<AT, BT, TC>(g, s); return; } }
       if (g.tile_bm == 256 && g.tile_bn == 256) go_256x256<AT, BT, TC>(g, s);
       else if (g.tile_bm == 256) go_256x128<AT, BT, TC>(g, s);
+      else if (g.tile_bn == 256 && g.once) go<128, 256, 2, AT, BT, TC, 8, 3, BK, true>(g, s);   // (a kernel of its own: a branch costs 1 % of a skewed 2 x 2048 step)
       else if (g.tile_bn == 256) go_128x256<AT, BT, TC>(g, s);
       else go_128x128<AT, BT, TC>(g, s);
     }
@@ -800,7 +795,6 @@ __global__ void __launch_bounds__(NW * 64) gemm_batch_tn_k(GemmBatch b) {
   GemmArgs g;
   g.M = ka->p[i].M; g.N = ka->p[i].N; g.K = ka->p[i].K;
   g.lda = ka->p[i].lda; g.ldb = ka->p[i].ldb; g.ldc = ka->p[i].ldc;
-  g.once = ka->once;
   const bf16 *A = (const bf16*)ka->p[i].A, *B = (const bf16*)ka->p[i].B;
   TC* C = (TC*)ka->p[i].C;
   if constexpr (NS == PHASED) gemm_tile_phased<true, true, TC>(g, A, B, C, nullptr, bx, by * BM, g.M, 0, g.K);

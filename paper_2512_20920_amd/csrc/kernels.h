@@ -58,19 +58,13 @@ struct GemmArgs {
   // group_mode 1: number of m-tiles of the list actually in use (device scalar written by the permutation kernel);
   // group_mode 2: the permutation kernel's flag that the routing is even (null: treated as uneven)
   const int* tile_count = nullptr;
-  // group_mode 1, MFMA kernel: the list's tiles in falling order, so the experts too.  A pass over expert weights that
-  // an earlier pass went over in rising order then begins with those that the 256 MB memory-side cache still holds;
-  // the results do not depend on it.  Merged gate/up pass of the inverse, whole step, falling / rising: 37 tokens
-  // 349 / 355 us, 300 and 1000 equal; dHh of the three-call step of 700 tokens 2209 / 2230, of the fused step of
-  // 128 tokens 1379 / 1385, of 300 1529 / 1543, of 700 1840 / 1854, from 1000 tokens on equal.
-  int reverse = 0;
-  // group_mode 1, 128x256 tiles and the kernel for few rows: B goes past the caches, every weight is read by one row tile
-  // only; MFMA kernel, weight gradients: the result does.  Set where the block's expert weights are more than the memory-side cache holds (256 MB), so
-  // that no pass over them finds what the last one left: what passes through evicts the activations, the dense layers' and the
-  // shared expert's weights, and every line of a gradient that is pushed out later costs the reading launch its write.
-  // Qwen shape, us per step, neither / gradients / both: 128 tokens 1371, 1311, 1186; 300 1530, 1470, 1324; 512 1703, 1652,
-  // 1522; 1024 -, 2033, 1957; 4 blocks of 1024 8338, 8178, 7940; 4 x 512 2798, 2770; 8192 9446, 9420; merged 37 343, -, 327, 300
-  // 455, -, 425.  (160x256 and taller tiles, some experts in two: weights past the caches 0.7 to 4 % slower than through them.)
+  // group_mode 1, 128x256 tiles and the kernel for few rows: B goes past the caches, as results in the layout of weight
+  // gradients always do.  Set where every weight is read by one row tile and the block's expert weights are more than the
+  // memory-side cache holds (256 MB), so that no pass over them finds what the last one left: what passes through evicts
+  // the activations, the dense layers' and the shared expert's weights, and every line of a gradient that is pushed out later
+  // costs the reading launch its write.  Qwen shape, us per step, neither / gradients / both: 128 tokens 1371, 1311, 1186;
+  // 300 1530, 1470, 1324; 512 1703, 1652, 1522; 4 blocks of 1024 8338, 8178, 7940; 4 x 512 2798, 2770; 8192 9446, 9420;
+  // merged 37 tokens 343, -, 327, 300 455, -, 425.  (160x256 tiles 0.7 % slower so, where some experts have two tiles 4 %.)
   int once = 0;
   const int* tile_first = nullptr;       // per tile: (first tile of its expert) << 16 | tiles of that expert
   // MFMA kernel, dense problems: n_sub > 1 launches that many problems of one shape, layout and
@@ -197,7 +191,7 @@ void launch_gemm_skinny(const GemmArgs& g, int out_f32, hipStream_t s);
 // the matrix-core kernel's alignment rules.
 #define GEMM_BATCH 12
 struct GemmProb { const void *A, *B; void* C; int M, N, K, lda, ldb, ldc; int tile0, tiles_m, tiles_n; };
-struct GemmBatch { int n = 0, total = 0, once = 0; GemmProb p[GEMM_BATCH]; };
+struct GemmBatch { int n = 0, total = 0; GemmProb p[GEMM_BATCH]; };
 int launch_gemm_batch_tn(GemmBatch& b, int out_f32, int bulk, hipStream_t s);
 
 // the same for float32 operands and results
