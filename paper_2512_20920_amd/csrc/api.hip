@@ -1069,27 +1069,17 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
     if (GF(ws_gate_up)) wg[nwg++] = tn(c->dGUs, 2 * Is, c->Um, d, GF(ws_gate_up), d, 2 * Is, d, T);
   }
   {
-    // The w_down gradient starts beside the data gradient dHh, or behind it from 4096 tokens on: there dHh fills the
-    // chip by itself, and the leaf serves better as filling for what follows on the chain.  Behind / beside, whole step:
-    //   60 experts of 1408, k = 4    3000 tokens: 3795, 3794 us    4096: 4871, 4995    6000: 6676, 6790
-    //                                8000: 9106, 9258    8192: 9331, 9515    2 x 8192: 17850, 18050
-    //                                1024: 2119, 2093 (4 blocks of it: 8223, 8114)    4 x 512: 2739, 2731
-    //   8 experts of 14336, k = 2    2048: 9009, 9001    4096: 15762, 15922
-    const bool down_behind = T >= 4096;
-    auto down_wgrad = [&]() -> int {
-      if (!GF(w_down)) return REVFFN_OK;
-      if (!Is || down_behind) to_sw();                                   // (else sw has waited for dYp already)
+    if (GF(w_down)) {
+      if (!Is) to_sw();                                                    // (else sw has waited for dYp already)
       sw_used = true;
       GemmArgs b = tn(c->dYp, d, c->Hh, I, GF(w_down), I, d, I, N);        // dWd_e = dYp_e^T . Hh_e
       b.group_mode = 2; b.n_groups = E; b.offsets = c->offsets; b.tile_count = c->tile_cnt + 3; b.c_group_stride = (i64)d * I;
-      return run_wgrad(c, b, sw);
-    };
-    if (!down_behind) TRY(down_wgrad());
+      TRY(run_wgrad(c, b, sw));
+    }
     GemmArgs a = nn(c->dYp, d, w->w_down, I, c->dHh, I, N, I, d);          // dHh = dYp . Wd_e
     a.group_mode = 1; a.n_groups = E; a.offsets = c->offsets; a.b_group_stride = (i64)d * I;
     a.dact_gu = c->GU; a.dact_out = c->dGU;
     TRY(run_gemm(c, a, s));
-    if (down_behind) TRY(down_wgrad());
     if (GF(w_gate_up)) {
       // dWgu_e = dGU_e^T . Xg_e, with the permuted input rows Xg materialised once
       to_sw();

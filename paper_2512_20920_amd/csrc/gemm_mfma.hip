@@ -115,6 +115,20 @@ __device__ __forceinline__ void pair_rows(bool odd, float x0, float x1, float* l
   *right = odd ? x1 : recv;
 }
 
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+__device__ __forceinline__ bf16x2 pair_rows_bf16(bool odd, float x0, float x1) {
+  float l, r;
+  pair_rows(odd, x0, x1, &l, &r);
+  bf16x2 w;
+  w[0] = (__bf16)l; w[1] = (__bf16)r;
+  return w;
+}
+
+// a plain result that can be stored 16 bytes at a time (widths of this layout are multiples of 8)
+__device__ __forceinline__ bool whole_lines(const GemmArgs& g, const void* C, const void* bias) {
+  return !bias && !g.resid && !g.tap && !(g.ldc & 7) && !((uintptr_t)C & 15);
+}
+
 // Epilogue of one output tile.  rb, cb: first row (column) of the wave's 32-row (32-column) blocks inside the tile;
 // act_col: with the SwiGLU epilogue, the wave's first gate column inside the tile's BN / 2.
 template <int BM, int BN, bool AT, bool BT, class TC, int TE, int TN>
@@ -431,6 +445,32 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const bf16* A, cons
   }
   wait_vmcnt<0>();                                   // the zero-filled loads past the last tile
 
+  // Weight gradients go out in whole lines: through LDS (every wave its own rows of 128 bytes), 16 bytes per lane.  Stores
+  // past the caches are not merged on the way (see GemmArgs::once), and in pieces of 64 bytes they were what bound these
+  // kernels: 8 rows per expert 96 and 191 us; a step of 128 tokens 1176 -> 1130 us, of 512 1514 -> 1475, 4 x 512
+  // 2749 -> 2705, 4 blocks of 1024 7873 -> 7704, 8 experts of 14336, 60 tokens, 2683 -> 2529.
+  if constexpr (AT && BT && sizeof(TC) == 2 && TN == 2 && (unsigned)NW * TE * 32 * 128 <= NS * STAGE) {
+    if (whole_lines(g, C, bias_ptr)) {
+      const int mw = m0 + wm, nw = n0 + wn + (lane & 7) * 8;
+      unsigned char* own = smem + (unsigned)wv * (TE * 32 * 128);
+      const int lr = (lane >> 5) * 4 + (lane & 1), lc = ((lane & 31) & ~1) * 2;
+      __syncthreads();                               // every wave is done with the stages
+#pragma unroll
+      for (int i = 0; i < TE; i++)
+#pragma unroll
+        for (int e = 0; e < 16; e += 2)
+#pragma unroll
+          for (int j = 0; j < TN; j++)
+            *(bf16x2*)(own + (i * 32 + (e >> 2) * 8 + (e & 3) + lr) * 128 + j * 64 + lc) = pair_rows_bf16(lane & 1, acc[i][j][e], acc[i][j][e + 1]);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      TC* cp = C + (i64)(mw + (lane >> 3)) * g.ldc + nw;
+#pragma unroll
+      for (int t = 0; t < TE * 4; t++)               // (the width is a multiple of 8)
+        if (mw + t * 8 + (lane >> 3) < m_end && nw < g.N)
+          __builtin_nontemporal_store(*(const u32x4*)(own + t * 1024 + lane * 16), (u32x4*)(cp + (i64)t * 8 * g.ldc));
+      return;
+    }
+  }
   int rb[TE], cb[TN];
 #pragma unroll
   for (int i = 0; i < TE; i++) rb[i] = wm + i * 32;
@@ -571,6 +611,31 @@ __device__ __forceinline__ void gemm_tile_phased(const GemmArgs& g, const bf16* 
 #pragma unroll
   for (int i = 0; i < 4; i++) rb[i] = (i >> 1) * 128 + wm + (i & 1) * 32;
   cb[0] = wn; cb[1] = 128 + wn;
+  // weight gradients in whole lines, as above; a wave's columns are 64 bytes here and 64 there, so the tile is put together
+  // first.  (Rows are 512 bytes apart: the 16-byte chunk moves with the row, so that a write meets no bank twice.)
+  if constexpr (AT && BT && sizeof(TC) == 2) {
+    if (whole_lines(g, C, bias_ptr)) {
+      auto at = [&](int row, int byte) { return smem + row * 512 + ((unsigned)byte ^ ((unsigned)(row & 1) * 64u + (unsigned)((row >> 2) & 1) * 128u)); };
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < 4; i++)
+#pragma unroll
+        for (int e = 0; e < 16; e += 2)
+#pragma unroll
+          for (int j = 0; j < 2; j++)
+            *(bf16x2*)at(rb[i] + (e >> 2) * 8 + (e & 3) + (lane >> 5) * 4 + (lane & 1), cb[j] * 2 + ((lane & 31) & ~1) * 2) =
+                pair_rows_bf16(lane & 1, acc[i][j][e], acc[i][j][e + 1]);
+      __syncthreads();
+      const int n = bx * 256 + (lane & 31) * 8;
+#pragma unroll
+      for (int t = 0; t < 16; t++) {
+        const int row = wv * 32 + t * 2 + (lane >> 5);
+        if (m0 + row < m_end && n < g.N)
+          __builtin_nontemporal_store(*(const u32x4*)at(row, (lane & 31) * 16), (u32x4*)(C + (i64)(m0 + row) * g.ldc + n));
+      }
+      return;
+    }
+  }
   gemm_epilogue<256, 256, AT, BT, TC, 4, 2>(g, C, bias_ptr, bx, m0, m_end, rb, cb, wn, acc);
 }
 

@@ -161,8 +161,7 @@ def test_block_parity_small_problems(dtype, d, H, E, k, I, Is, B, S):
 
 
 # More routed work than the kernel for few rows takes: the tiles of the expert GEMMs with widths and row counts that end inside
-# them, at 50 rows per expert (128x256), 137 (160x256, 256x256, 256x128) and 391 (256x256 throughout); and 4100 tokens,
-# where the w_down gradient runs behind the data gradient that reads the same rows
+# them, at 50 rows per expert (128x256), 137 (160x256, 256x256, 256x128) and 391 (256x256 throughout); and 4100 tokens
 @pytest.mark.parametrize("E,k,I,B,S", [(24, 2, 600, 2, 300), (12, 3, 600, 2, 274), (6, 3, 440, 3, 261), (4, 2, 200, 20, 205)])
 def test_block_parity_expert_tiles(E, k, I, B, S):
     wl = synth.Workload(f"tiles_E{E}", 640, 5, 128, E, k, I, 0, B, S, "bf16", gain_jitter=0.02, seed=E)
