@@ -331,9 +331,9 @@ int run_gemm(revffn_ctx* c, GemmArgs g, int ta, int tb, int tc, hipStream_t s) {
       // Expert tiles stream weights that nothing else reads, so with few rows per expert what counts is weight bytes in
       // flight per CU: a 128x256 tile (3 stages) keeps 64 KiB of them in flight, the other shapes half of that.  With
       // many rows the matrix pipe counts: 256x256 in phases.  Measured, us per launch (mean rows per expert):
-      //   forward gate/up      68: 161 (128x256), 183 (256x256)   137: 191 (160x256, see expert_rows_b), 210   273: 276, 291
+      //   forward gate/up      68: 146 (128x256), 183 (256x256)   137: 191 (160x256, see expert_rows_b), 210   273: 276, 291
       //                        546: 495, 453      512 of width 14336: 1133, 1004
-      //   data gradient dXg    68: 185, 182    137: 218 (256x128), 195    273: 268, 240    546: 454, 417
+      //   data gradient dXg    68: 142, 182    137: 218 (256x128), 195    273: 268, 240    546: 454, 417
       //   data gradient dHh    137: 119, 127 (1408 columns: the sixth column of tiles is half empty)    546: 254, 247
       // Shapes: 1 = 128x128, 2 = 256x128, 3 = 128x256 (160x256 where list b was built that high), 4 = 256x256
       // (REVFFN_EXPERT_NT / REVFFN_EXPERT_NN force one).
@@ -964,9 +964,9 @@ int inverse_impl(revffn_ctx* c, const revffn_weights* w, const void* y1, const v
     launch_fill_u32((uint32_t*)c->conv.row_done, 0, (int)c->conv_zero_words, s);
     skip = c->conv.row_done;
   }
-  // the first fixed-point iterate is Y1 itself, so its query side does not wait for X2^: it fills the main stream
-  // while the routing chain runs on another one.  On one stream there is nothing to fill, and both streams' norms,
-  // projections and rotations are a launch each instead of two (a step of a 512-wide block of 400 tokens: 455 -> 446 us).
+  // the first fixed-point iterate is Y1 itself, so its query side does not wait for X2^: it runs beside the routing
+  // chain.  On one stream there is nothing to fill, and both streams' norms, projections and rotations are a launch each
+  // instead of two (a step of a 512-wide block of 400 tokens: 455 -> 446 us).
   const bool q_early = n >= 1 && !sym && c->par;
   TRY(moe_acts(c, w, y1k, ldk, T, s, q_early ? y1k : nullptr, ldk, B, S, skip));
   TRY(moe_out(c, w, y2, ld, -1.f, x2, ld, T, s));                 // X2^ = Y2 - MoE branch(Y1)

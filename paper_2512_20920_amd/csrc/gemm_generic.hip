@@ -5,10 +5,13 @@
 //
 // These problems are small (one to a few hundred 32x32 tiles), so what bounds them is latency, not the matrix pipe: a
 // workgroup owns one tile of 32 TM x 32 TN outputs and cuts the contraction among its waves (wave w takes the chunks of
-// 32 k's w, w + NW, ...), operands go from memory (L2) straight into the operand registers, one chunk ahead, and the
-// waves' partial tiles are added in wave order through LDS.  No LDS staging: inside a workgroup no two waves want the
-// same element.  At T = 400, d = 512 (float32) a GEMM of 400 x 512 x 512 takes 4 us where the LDS-tiled vector kernel
-// that it replaced took 64 us (56 workgroups, one dependent load -> LDS -> barrier chain per 16 k's).
+// 32 k's w, w + NW, ...) and the partial tiles are added in wave order through LDS.  Inside a workgroup no two waves want the
+// same element, so every wave brings its own.  Aligned float32 operands go straight into LDS of the wave (f32_tile_staged:
+// whole chunks in flight, no registers, no barrier before the end); everything else goes from memory (L2) into the operand
+// registers, one chunk ahead.  What a small launch is made of is its place in the chain, 3 to 5 us, so the SwiGLU formulas,
+// the norm in front of a projection and the rotation behind it are part of the GEMMs (EPI), and several problems of one
+// kind are one launch.  At T = 400, d = 512 (float32) a GEMM of 400 x 512 x 512 takes 4 us where the LDS-tiled vector
+// kernel that it replaced took 64 us (56 workgroups, one dependent load -> LDS -> barrier chain per 16 k's).
 #include "lds_load.h"
 #include "operand_f32.h"
 #include <type_traits>

@@ -4,8 +4,10 @@
 // With few rows a dense layer is its weight matrix read once, and what bounds it is how much of that is in flight.  The
 // tile kernel walks k in one chain per tile: 128 rows x 2048 columns x k = 2048 is 32 workgroups of 128x64 with three
 // k-tiles in flight each, and 32 dependent steps.  Here the same problem is 256 workgroups of 8 waves; wave w multiplies
-// the 64-wide pieces w, w + 8, ... of k with two pieces of its own in flight, and the partial tiles are added in wave
-// order through LDS, so that a result's bits depend on k alone.
+// the 64-wide pieces w, w + 8, ... of k with two pieces of its own in flight (short k's: fewer waves and pieces, see by_k),
+// and the partial tiles are added in wave order through LDS, so that a result's bits depend on k alone.
+// The routed experts' GEMMs of small calls come here too, by their list of row tiles, and what would be a launch of its own
+// around a small dense layer is part of it: norm of the rows, rotation, SwiGLU either way, a second pair of operands.
 // Each wave stages its pieces in LDS that no other wave touches (direct loads, no barrier before the end): a fragment
 // read from memory by the lane that needs it puts every lane on a cache line of its own, 94 clocks per KiB.
 //  * rows x k operands: 128-byte rows, 16-byte chunk c of row r in slot c ^ ((r >> 1) & 7);

@@ -1,5 +1,5 @@
-// Operands of the float32 matrix instructions v_mfma_f32_32x32x2_f32 and v_mfma_f32_16x16x4_f32, loaded straight from
-// memory into registers.
+// Operands of the float32 matrix instructions v_mfma_f32_32x32x2_f32 and v_mfma_f32_16x16x4_f32: loaded straight from
+// memory into registers, or (StagedOperand, the router's) through registers into LDS.
 //
 // The instruction wants row l % R of the operand (R = 32, 16) at k = l / R in lane l.  A sum over k may be taken in any
 // order as long as both operands agree, so lane group g = l / R takes the 4 consecutive k's 4 (64 / R) j + 4 g .. + 3 of
