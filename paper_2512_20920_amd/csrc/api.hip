@@ -574,15 +574,20 @@ int run_wgrad_batch(revffn_ctx* c, const GemmArgs* subs, int n, bool bulk, hipSt
 // chip overlap: the shared expert next to the routed experts, the rebuilding of X1^ and the attention half's
 // recomputation next to the MoE half's backward pass, the MoE half's weight gradients next to the attention half's
 // backward pass.  Recording an event and making another stream wait for it costs the host 13 us (a launch: 3 us), so
-// there are eleven such edges in a training step, between long branches only, and none at all in a call too small
-// for them to pay: below about 60 us of GPU time per evaluation of the block the host would be what the GPU waits for
-// (a step of a 512-wide block of 400 tokens: 909 us with 45 edges, 609 us on one stream).
-bool fork_pays(const revffn_ctx* c, i64 T) {
+// there are eleven such edges in a training step, between long branches only, and none at all in a call so small that the
+// host would be what the GPU waits for: below about 8 us per evaluation of the block at the rates below, which a call of a
+// few hundred tokens of a 512-wide block reaches.  One stream / helper streams, us per step: 512 wide, 12 experts, 400
+// tokens (5.6) 324 to 350 / 340 and up to 440 where the host is slow, 800 (9.0) 436 / 405, 1200 (12) 511 / 484, 1536 532 / 506,
+// float32, 60 (8.0) 400 / 393, 200 460 / 453, 400 541 / 508; 256 wide, 753 (5.9) 400 / 400, 1400 (9.3) 550 / 496, 2000 690 / 653;
+// one token at the Qwen shape (38) 617 / 527.  A merged pass is little more than its experts, with one fork in it: one token
+// 149 / 180, 4 tokens (64) 178 / 180, 37 tokens 354 / 337: there the line is at 60.
+constexpr double FORK_PAYS = 8e-6, FORK_PAYS_MERGED = 60e-6;
+bool fork_pays(const revffn_ctx* c, i64 T, double line) {
   const revffn_config& f = c->cfg;
   const double d = f.d_model, dense = 6 * d * d + 3 * d * f.d_shared, per_expert = 3 * d * f.d_expert;
   const double hit = (double)T * f.top_k < f.n_experts ? (double)T * f.top_k : f.n_experts;
   const double weights = (dense + hit * per_expert) * c->es, flops = 2.0 * T * (dense + f.top_k * per_expert);
-  return weights / 5e12 + flops / (c->dt == 1 ? 7e14 : 1e14) > 60e-6;
+  return weights / 5e12 + flops / (c->dt == 1 ? 7e14 : 1e14) > line;
 }
 hipEvent_t next_sync(revffn_ctx* c) {
   hipEvent_t e = (*c->sync_ev)[c->sync_next % c->sync_ev->size()];
@@ -912,14 +917,14 @@ int check_merged(const revffn_ctx* c, const revffn_merged* m) {
   return 0;
 }
 
-int check_call(revffn_ctx* c, const revffn_weights* w, int B, int S, i64 ld) {
+int check_call(revffn_ctx* c, const revffn_weights* w, int B, int S, i64 ld, double fork_line = FORK_PAYS) {
   if (!c || !w) return REVFFN_ENULL;
   c->fwd_x1 = nullptr;                    // any call invalidates the activations a forward call left behind
   if (B < 1 || S < 1) return REVFFN_ESHAPE;
   if ((i64)B * S > c->maxT) return REVFFN_ESHAPE;
   if (ld < c->cfg.d_model / 2) return REVFFN_ESHAPE;
   c->call_T = (i64)B * S;
-  c->par = c->use_streams && fork_pays(c, (i64)B * S);
+  c->par = c->use_streams && fork_pays(c, (i64)B * S, fork_line);
   if (!w->norm_a1 || !w->norm_a2 || !w->norm_m || !w->pup_a || !w->pdn_a || !w->pup_m || !w->pdn_m || !w->wq ||
       !w->wk || !w->wv || !w->wo || !w->w_router || !w->w_gate_up || !w->w_down)
     return REVFFN_ENULL;
@@ -1492,7 +1497,7 @@ int revffn_merge_adapters(revffn_ctx* c, const revffn_weights* w, const revffn_m
 
 int revffn_forward_merged(revffn_ctx* c, const revffn_weights* w, const revffn_merged* m, const void* x1, const void* x2,
                           void* y1, void* y2, int32_t B, int32_t S, int64_t ld, void* stream) {
-  TRY(check_call(c, w, B, S, ld));
+  TRY(check_call(c, w, B, S, ld, FORK_PAYS_MERGED));
   TRY(check_merged(c, m));
   if (!x1 || !x2 || !y1 || !y2) return REVFFN_ENULL;
   hipStream_t s = (hipStream_t)stream;
@@ -1504,7 +1509,7 @@ int revffn_forward_merged(revffn_ctx* c, const revffn_weights* w, const revffn_m
 
 int revffn_inverse_merged(revffn_ctx* c, const revffn_weights* w, const revffn_merged* m, const void* y1, const void* y2,
                           void* x1, void* x2, int32_t B, int32_t S, int64_t ld, float* residual, void* stream) {
-  TRY(check_call(c, w, B, S, ld));
+  TRY(check_call(c, w, B, S, ld, FORK_PAYS_MERGED));
   TRY(check_merged(c, m));
   if (!x1 || !x2 || !y1 || !y2) return REVFFN_ENULL;
   hipStream_t s = (hipStream_t)stream;

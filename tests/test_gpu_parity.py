@@ -603,6 +603,27 @@ def test_helper_streams_do_not_change_results(monkeypatch):
             assert torch.equal(a, b)
 
 
+# The same at sizes whose calls do spread over the helper streams, with and without the shared expert and the weight gradients
+@pytest.mark.parametrize("dtype,Is,B,S", [("bf16", 320, 2, 400), ("bf16", 0, 3, 333), ("f32", 320, 2, 200)])
+@pytest.mark.parametrize("train", [True, False])
+def test_helper_streams_same_bits(dtype, Is, B, S, train):
+    wl = synth.Workload("streams", 512, 4, 128, 12, 3, 192, Is, B, S, dtype, gain_jitter=0.02, seed=S)
+    case = Case(wl)
+    outs = []
+    for on in (True, False, True):
+        case.ctx.set_helper_streams(on)
+        y1d, y2d = case.forward()
+        r1, r2, o1, o2 = case.empty(), case.empty(), case.empty(), case.empty()
+        G = Hn.alloc_grads(case.Wd) if train else None
+        R.revffn_inverse_backward(case.ctx, case.Wd, y1d, y2d, r1, r2, case.up(case.dy1), case.up(case.dy2), o1, o2, G,
+                                  wl.B, wl.S, wl.h, None)
+        torch.cuda.synchronize()
+        outs.append([y1d, y2d, r1, r2, o1, o2] + ([G[k] for k in sorted(G) if G[k] is not None] if train else []))
+    for other in outs[1:]:
+        for a, b in zip(outs[0], other):
+            assert torch.equal(a, b)
+
+
 def test_frozen_groups_are_skipped():
     """NULL gradient fields (adapter-only stage; frozen routers) leave the others unchanged."""
     wl = synth.WORKLOADS["mid_f32"]
