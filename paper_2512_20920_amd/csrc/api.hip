@@ -337,13 +337,18 @@ int run_gemm(revffn_ctx* c, GemmArgs g, int ta, int tb, int tc, hipStream_t s) {
       //   data gradient dHh    137: 119, 127 (1408 columns: the sixth column of tiles is half empty)    546: 254, 247
       // Shapes: 1 = 128x128, 2 = 256x128, 3 = 128x256 (160x256 where list b was built that high), 4 = 256x256
       // (REVFFN_EXPERT_NT / REVFFN_EXPERT_NN force one).
+      // Data gradients on 128x256 as long as one such tile holds an expert, if the weights go past the caches (see GemmArgs::once);
+      // through them up to 96 rows.  Line at 96 / 118, us per step: 1450 tokens (97 rows) 2376, 2281   1600: 2386, 2318
+      // 1750: 2558, 2521   8 experts of 14336, 430 tokens (107 rows): 3564, 3447;  at 60: 1024 tokens 4 % slower.
       const i64 rows = c->lastT_rows, E = c->cfg.n_experts;
+      const bool past = experts_pass_through(c, rows);
+      const i64 one_tile = (past ? ROWS_ONE_TILE : 96) * E;
       int shape = g.b_trans ? c->expert_nn : c->expert_nt;
       if (c->expert_tile) shape = c->expert_tile == 256 ? 2 : 1;
       if (!shape) {
         if (!g.b_trans) shape = rows > 384 * E ? 4 : 3;
-        else if (rows > 192 * E || (rows > 96 * E && g.N % 256 == 0)) shape = 4;
-        else shape = rows > 96 * E ? 2 : 3;
+        else if (rows > 192 * E || (rows > one_tile && g.N % 256 == 0)) shape = 4;
+        else shape = rows > one_tile ? 2 : 3;
       }
       // Small problems are latency: 32x32 tiles with k cut among the waves, up to about as many as the chip holds at once.
       // Measured, us per pass: a 512-wide block of 12 experts, 400 tokens (294 to 784 tiles) 420 -> 392, 1536 tokens (at most 936
@@ -364,14 +369,14 @@ int run_gemm(revffn_ctx* c, GemmArgs g, int ta, int tb, int tc, hipStream_t s) {
         // (Weights past the caches, see GemmArgs::once; with k as the slow index a line belongs to two tiles, which does not pay
         // where k is long.  Through / past, us: 8, 16, 25 tokens at the Qwen shape 862, 1005, 1107 / 816, 972, 1043;
         // merged 16, 29 tokens 300, 344 / 280, 318; 8 experts of 14336, 8 tokens, the forward layout only / both 2589 / 2629.)
-        g.once = rows <= 16 * E && (!g.b_trans || g.K <= 2048) && experts_pass_through(c, rows);
+        g.once = rows <= 16 * E && (!g.b_trans || g.K <= 2048) && past;
       } else if (tall) {
         g.tile_group = c->tg_c; g.tile_m0 = c->tm_c; g.max_tiles = c->max_tiles_c; g.tile_bm = BM_C; g.tile_count = c->tile_cnt + 2;
         if (c->max_tiles_c < 32768) g.tile_first = c->tf_c;      // (the packed entry holds 15 + 16 bits)
       } else {
         g.tile_group = c->tg_b; g.tile_m0 = c->tm_b; g.max_tiles = c->max_tiles_b; g.tile_bm = c->bm_b; g.tile_count = c->tile_cnt + 1;
         if (c->max_tiles_b < 32768) g.tile_first = c->tf_b;
-        g.once = rows <= ROWS_ONE_TILE * E && experts_pass_through(c, rows);
+        g.once = rows <= ROWS_ONE_TILE * E && past;
       }
     }
     if (!g.few_rows) g.dact_out = nullptr;

@@ -200,10 +200,9 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, TC* C, const vo
   const bf16* bias = (const bf16*)bias_ptr;
   const bf16* resid = (const bf16*)g.resid;
   if (!bias && !g.tap && !resid) {
-    // plain store (all weight gradients, most projections): no per-element epilogue work
-    // the column blocks of one row are stored back to back, so that the 64-byte pieces of a line reach L2 together.
-    // (Staging the tile through LDS to store whole 128-byte lines, 16 bytes per lane, measured no faster: these
-    // stores are not what bounds the weight-gradient kernels.)
+    // plain store (most projections, data gradients, weight gradients in float32): no per-element epilogue work
+    // the column blocks of one row are stored back to back, so that the 64-byte pieces of a line reach L2 together and
+    // are merged there.  (Through LDS in whole lines, as the bf16 weight gradients go: no faster for stores that stay in L2.)
     const bool full = (m0 + BM <= m_end) && (n0 + BN <= g.N);
     auto put = [](auto v, auto* p) {                 // (weight gradients go past the caches, see GemmArgs::once)
       if constexpr (AT && BT) __builtin_nontemporal_store(v, p);
@@ -213,8 +212,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, TC* C, const vo
       // Whole tiles of 2-byte results: neighbouring lanes hold neighbouring columns of the same rows, so a pair of
       // lanes swaps one value per two rows (the even lane gives its value of the odd row and gets the neighbour's
       // value of the even row) and each lane stores 4 bytes, two columns of one row: half as many store
-      // instructions, and the stores of a tile are bound by their number (per-expert weight gradients 10 % faster,
-      // 1-2 % of a step).  Going on to a 4x4 transpose inside a quad and 8-byte stores is slower than no packing at
+      // instructions, and the stores of a tile are bound by their number (measured on the weight gradients when they
+      // came here: 10 %, 1-2 % of a step).  Going on to a 4x4 transpose inside a quad and 8-byte stores is slower than no packing at
       // all: one instruction then touches eight rows.
       if (full && !(g.ldc & 1) && !((uintptr_t)C & 3) && !g.no_packed_stores) {
         const bool odd = lane & 1;
@@ -729,7 +728,8 @@ static void go(const GemmArgs& g0, hipStream_t s) {
 // The tile shapes: 256x128 and 128x256 (8 waves, one workgroup per CU), 256x256 (2 stages), 128x128 (8 waves of 32x64,
 // 4 stages: with one workgroup per CU, two waves per SIMD hide each other's LDS and barrier waits; 10-17 % faster than
 // 4 waves of 64x64 on the 2048^3 projections) and 128x64 (8 waves of 32x32, two workgroups per CU; 1.5 % of a step
-// over 4 waves of 64x32, measured on one box with both builds).
+// over 4 waves of 64x32, measured on one box with both builds).  64x64 (4 waves of 32x32, 4 stages) and 128x64 with a fourth
+// stage for narrow results, 256x256 with 4 stages of 32 rows for per-expert weight gradients: see pick_tile.
 template <bool AT, bool BT, class TC> static void go_256x128(const GemmArgs& g, hipStream_t s) { go<256, 128, 4, AT, BT, TC, 8, 3>(g, s); }
 template <bool AT, bool BT, class TC> static void go_256x256(const GemmArgs& g, hipStream_t s) { go<256, 256, 2, AT, BT, TC, 8, PHASED>(g, s); }
 template <bool AT, bool BT, class TC> static void go_128x128(const GemmArgs& g, hipStream_t s) { go<128, 128, 4, AT, BT, TC, 8, 4>(g, s); }

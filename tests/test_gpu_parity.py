@@ -172,8 +172,8 @@ def test_block_parity_expert_tiles(E, k, I, B, S):
 
 
 # More expert weights than the memory-side cache holds: weights and gradients go past the caches, in the kernel for few rows (40
-# tokens, 2 rows per expert) and on 128x256 tiles (300 tokens), with widths that end inside the tiles
-@pytest.mark.parametrize("S", [40, 300])
+# tokens, 2 rows per expert) and on 128x256 tiles (300 tokens; 2140: 107 rows per expert), with widths that end inside the tiles
+@pytest.mark.parametrize("S", [40, 300, 2140])
 def test_block_parity_weights_past_the_caches(S):
     wl = synth.Workload("past_caches", 1024, 8, 128, 60, 3, 776, 0, 1, S, "bf16", gain_jitter=0.02, seed=S)
     assert 3 * wl.n_experts * wl.d_expert * wl.d_model * 2 >= 1 << 28
