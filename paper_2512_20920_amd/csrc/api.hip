@@ -527,11 +527,14 @@ int run_gemm_multi(revffn_ctx* c, const GemmArgs* subs, int n, int tc, hipStream
   return 0;
 }
 
-// One to three problems of one shape with the norm of A's rows or the rotation of the outputs in the same launch, where the
-// kernel for small problems takes them (a rule on the call and the layer, as gemm_few_rows); 1: nothing launched.
+// whether a layer of N outputs may take norm or rotation along (a rule on the call and the layer, as gemm_few_rows)
+bool norms_in_gemm(const revffn_ctx* c, i64 N) { return c->dt == 0 || (c->mode == 0 && gemm_few_rows(c->call_T, N)); }
+
+// One to three problems of one shape with the norm of A's rows (rows that suit, see suit_rows) or the rotation of the outputs in the
+// same launch, where the kernel for small problems takes them; 1: nothing launched.
 int run_gemm_small(revffn_ctx* c, const GemmArgs* subs, int n, hipStream_t s) {
   GemmArgs g = subs[0];
-  if (c->dt == 1 && (c->mode != 0 || !few_rows(c, g))) return 1;
+  if (!norms_in_gemm(c, g.N)) return 1;
   g.n_sub = n;
   g.few_rows = 1;
   for (int z = 1; z < n; z++) {
@@ -610,12 +613,26 @@ void after(revffn_ctx* c, hipStream_t from, hipStream_t to) {
 hipStream_t side(revffn_ctx* c, hipStream_t main, int i) { return c->par ? c->side[i] : main; }
 
 // ---- attention half ---------------------------------------------------------------
+// The GEMMs that take the norm of their rows along read them 16 bytes at a time, and add in another order than the norm kernel.
+// Which of the two runs may follow from the call and the layer only, never from where the caller's rows lie (a call in place works
+// from a dense copy of Y1, and promises the bits of the calls that do not): rows whose base or stride does not suit are copied to
+// `dense` ([T, h], of a backward buffer that is idle until every use of the copy is done) first.
+void suit_rows(revffn_ctx* c, const void** x, i64* ldx, void* dense, int T, hipStream_t s) {
+  const int h = c->cfg.d_model / 2, piece = 16 / c->es;
+  if (h % piece || (!((uintptr_t)*x & 15) && *ldx % piece == 0 && (i64)T * *ldx * c->es < (i64)1 << 31)) return;
+  p_copy_rows(c, c->dt, *x, *ldx, dense, h, T, h, s);
+  *x = dense;
+  *ldx = h;
+}
 // U = Norm(x) . P_up^T for one stream or both (U and the normalised rows of the second behind those of the first).
 // skip (may be null): rows marked there are finished rows of the inverse's iteration and are left alone.
-struct NormUp { const void* x; i64 ldx; const void* gain; void *nout, *U; };
-int norm_up(revffn_ctx* c, const NormUp* p, int n, const void* pup, int T, hipStream_t s, const unsigned char* skip = nullptr) {
+struct NormUp { const void* x; i64 ldx; const void* gain; void *nout, *U, *dense; };
+int norm_up(revffn_ctx* c, const NormUp* streams, int n, const void* pup, int T, hipStream_t s, const unsigned char* skip = nullptr) {
   const revffn_config& f = c->cfg;
   const int d = f.d_model, h = d / 2, dt = c->dt;
+  NormUp p[2] = {streams[0], streams[n - 1]};
+  if (c->sdt == dt && norms_in_gemm(c, d))
+    for (int i = 0; i < n; i++) suit_rows(c, &p[i].x, &p[i].ldx, p[i].dense, T, s);
   if (n == 2 && p[0].ldx != p[1].ldx) {
     TRY(norm_up(c, p, 1, pup, T, s, skip));
     return norm_up(c, p + 1, 1, pup, T, s, skip);
@@ -653,7 +670,7 @@ int project(revffn_ctx* c, GemmArgs* q, int n, int n_rot, int T, int S, hipStrea
 int attn_q(revffn_ctx* c, const revffn_weights* w, const void* x1, i64 ld1, int B, int S, hipStream_t s,
            const unsigned char* skip = nullptr) {
   const int T = B * S, d = c->cfg.d_model;
-  const NormUp nu{x1, ld1, w->norm_a1, c->n12, c->U12};
+  const NormUp nu{x1, ld1, w->norm_a1, c->n12, c->U12, c->dn12};
   TRY(norm_up(c, &nu, 1, w->pup_a, T, s, skip));
   GemmArgs gq = nt(c->U12, d, w->wq, d, c->Q, d, T, d, d);
   gq.bias = w->bq;
@@ -670,7 +687,8 @@ int attn_acts(revffn_ctx* c, const revffn_weights* w, const void* x1, i64 ld1, c
   GemmArgs q3[3] = {nt(f.symmetric ? U2 : c->U12, d, w->wq, d, c->Q, d, T, d, d), nt(U2, d, w->wk, d, c->K, d, T, d, d),
                     nt(U2, d, w->wv, d, c->V, d, T, d, d)};
   q3[0].bias = w->bq; q3[1].bias = w->bk; q3[2].bias = w->bv;
-  const NormUp nu[2] = {{x1, ld1, w->norm_a1, c->n12, c->U12}, {x2, ld2, w->norm_a2, at(c->n12, (size_t)T * h, es), U2}};
+  const NormUp nu[2] = {{x1, ld1, w->norm_a1, c->n12, c->U12, c->dn12},
+                        {x2, ld2, w->norm_a2, at(c->n12, (size_t)T * h, es), U2, at(c->dn12, (size_t)T * h, es)}};
   if (f.symmetric) {                                    // n2, U2 keep their places in the second halves of n12, U12
     TRY(norm_up(c, nu + 1, 1, w->pup_a, T, s));
     TRY(project(c, q3, 3, 2, T, S, s));
@@ -747,7 +765,7 @@ int moe_acts(revffn_ctx* c, const revffn_weights* w, const void* y1, i64 ld, int
   // the chain of launches more than the 6 us of the up-projection in front of the routing chain: with the routing chain
   // on a helper stream instead (two forks, two joins) a step of 128 tokens took 1412 us, now 1391; 300 tokens 1646 and
   // 1628, 4 x 512 2831 and 2809, four blocks of 1024 8421 and 8358; 20, 3000, 8192 tokens and few large experts within 1 %.
-  const NormUp nu{y1, ld, w->norm_m, c->n3, c->Um};
+  const NormUp nu{y1, ld, w->norm_m, c->n3, c->Um, c->dn3};
   TRY(norm_up(c, &nu, 1, w->pup_m, T, s));
   hipStream_t s0 = side(c, s, 0);
   if (q_x1 || Is) after(c, s, s0);
@@ -840,6 +858,10 @@ int attn_acts_merged(revffn_ctx* c, const revffn_weights* w, const revffn_merged
   // CU for itself there, which pays in one round of workgroups only.
   if (c->sdt == dt && f.use_rope && (h <= 512 || (i64)cdiv(T, 32) * cdiv(d, 32) * 3 <= 256)) {
     GemmArgs q[3] = {q3[0], q3[1], q3[2]};
+    if (norms_in_gemm(c, d)) {
+      suit_rows(c, &x1, &ld1, c->dn12, T, s);
+      if (do_kv) suit_rows(c, &x2, &ld2, at(c->dn12, (size_t)T * h, es), T, s);
+    }
     for (int i = 0; i < n; i++) {
       q[i].A = i ? x2 : x1; q[i].lda = i ? ld2 : ld1;
       q[i].norm_g[0] = i ? w->norm_a2 : w->norm_a1; q[i].norm_eps = f.rms_eps;

@@ -9,11 +9,22 @@
     else { typedef bf16 T; __VA_ARGS__; }                     \
   } while (0)
 
+// element types of gains and results and of the rows, and columns per lane, of the norm kernels
+#define BY_NORM_TYPES(call)                                       \
+  do {                                                            \
+    if (dt == 0) call(float, float, 1);                           \
+    else if (tx == 0) { if (h & 7) call(bf16, float, 1); else call(bf16, float, 8); } \
+    else if (h & 7) call(bf16, bf16, 1);                          \
+    else call(bf16, bf16, 8);                                     \
+  } while (0)
+
 // ---------------------------------------------------------------------------------
 // RMSNorm forward: one wave per token row.
 // ---------------------------------------------------------------------------------
 // (blockIdx.y == 1: the second problem of the launch, same shape: x2, g2, out2)
-template <class T, class TX>
+// A lane takes V neighbouring columns at a time: 8 in bf16 rows of whole groups of 8, the order in which the form with 16-byte
+// accesses below adds, so that the result does not depend on the rows' addresses; else 1.
+template <class T, class TX, int V>
 __global__ void __launch_bounds__(256) rmsnorm_fwd_k(const TX* __restrict__ x, i64 ldx, const T* __restrict__ g,
                                                      T* __restrict__ out, i64 ldo, int rows, int h, float eps,
                                                      const unsigned char* __restrict__ row_skip,
@@ -24,7 +35,9 @@ __global__ void __launch_bounds__(256) rmsnorm_fwd_k(const TX* __restrict__ x, i
   if (blockIdx.y) { x = x2; g = g2; out = out2; }
   const TX* xr = x + (i64)row * ldx;
   float ss = 0.f;
-  for (int j = lane; j < h; j += 64) { float v = to_f(xr[j]); ss += v * v; }
+  for (int j0 = lane * V; j0 < h; j0 += 64 * V)
+#pragma unroll
+    for (int j = j0; j < j0 + V; j++) { float v = to_f(xr[j]); ss += v * v; }
   ss = wave_sum(ss);
   float r = 1.0f / sqrtf(ss / (float)h + eps);
   T* orow = out + (i64)row * ldo;
@@ -95,19 +108,15 @@ void launch_rmsnorm_fwd(int dt, int tx, const void* x, i64 ldx, const void* g, v
                          ldo, rows, h, eps, row_skip, (const bf16*)x2, (const bf16*)g2, (bf16*)out2);
     return;
   }
-  if (dt == 1 && tx == 0) {
-    hipLaunchKernelGGL((rmsnorm_fwd_k<bf16, float>), grid, block, 0, s, (const float*)x, ldx, (const bf16*)g,
-                       (bf16*)out, ldo, rows, h, eps, row_skip, (const float*)x2, (const bf16*)g2, (bf16*)out2);
-    return;
-  }
-  DISPATCH_DT(dt, hipLaunchKernelGGL((rmsnorm_fwd_k<T, T>), grid, block, 0, s, (const T*)x, ldx, (const T*)g, (T*)out,
-                                     ldo, rows, h, eps, row_skip, (const T*)x2, (const T*)g2, (T*)out2));
+#define NORM_FWD(T, TX, V) hipLaunchKernelGGL((rmsnorm_fwd_k<T, TX, V>), grid, block, 0, s, (const TX*)x, ldx, (const T*)g, (T*)out, \
+                                              ldo, rows, h, eps, row_skip, (const TX*)x2, (const T*)g2, (T*)out2)
+  BY_NORM_TYPES(NORM_FWD);
 }
 
 // RMSNorm backward for the input:  dx = r*(g.dy) - x*r^3*mean_j(x_j g_j dy_j), plus an
 // optional base term (the residual path of Eq. 1-2).  1/rms is kept per row.
-// (blockIdx.y == 1: the second problem of the launch, same rows, width and strides but for the base's)
-template <class T, class TX>
+// (blockIdx.y == 1: the second problem of the launch, same rows, width and strides but for the base's; V as above)
+template <class T, class TX, int V>
 __global__ void __launch_bounds__(256) rmsnorm_bwd_k(NormBwd p, NormBwd p2, i64 ldd, i64 ldx, i64 ldo, int rows, int h, float eps) {
   int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   int lane = threadIdx.x & 63;
@@ -118,11 +127,13 @@ __global__ void __launch_bounds__(256) rmsnorm_bwd_k(NormBwd p, NormBwd p2, i64 
   const T *g = (const T*)p.g, *base = (const T*)p.base;
   T* dx = (T*)p.dx;
   float ss = 0.f, sd = 0.f;
-  for (int j = lane; j < h; j += 64) {
-    float v = to_f(xr[j]);
-    ss += v * v;
-    sd += v * to_f(g[j]) * to_f(dr[j]);
-  }
+  for (int j0 = lane * V; j0 < h; j0 += 64 * V)
+#pragma unroll
+    for (int j = j0; j < j0 + V; j++) {
+      float v = to_f(xr[j]);
+      ss += v * v;
+      sd += v * to_f(g[j]) * to_f(dr[j]);
+    }
   ss = wave_sum(ss);
   sd = wave_sum(sd);
   float r = 1.0f / sqrtf(ss / (float)h + eps);
@@ -183,8 +194,8 @@ void launch_rmsnorm_bwd(int dt, int tx, const NormBwd& p, const NormBwd* p2, i64
     else hipLaunchKernelGGL(rmsnorm_bwd_v8_k<bf16>, grid, block, 0, s, p, q, ldd, ldx, ldo, rows, h, eps);
     return;
   }
-  if (dt == 1 && tx == 0) hipLaunchKernelGGL((rmsnorm_bwd_k<bf16, float>), grid, block, 0, s, p, q, ldd, ldx, ldo, rows, h, eps);
-  else DISPATCH_DT(dt, hipLaunchKernelGGL((rmsnorm_bwd_k<T, T>), grid, block, 0, s, p, q, ldd, ldx, ldo, rows, h, eps));
+#define NORM_BWD(T, TX, V) hipLaunchKernelGGL((rmsnorm_bwd_k<T, TX, V>), grid, block, 0, s, p, q, ldd, ldx, ldo, rows, h, eps)
+  BY_NORM_TYPES(NORM_BWD);
 }
 
 // ---------------------------------------------------------------------------------

@@ -624,6 +624,73 @@ def test_helper_streams_same_bits(dtype, Is, B, S, train):
             assert torch.equal(a, b)
 
 
+class _Placed:
+    """A [T, h] stream whose rows start `off` elements into an allocation and are `ld` apart."""
+
+    def __init__(self, t, ld, off):
+        self.buf = torch.zeros(off + t.shape[0] * ld, dtype=t.dtype, device="cuda")
+        self.rows = self.buf[off:].view(t.shape[0], ld)[:, :t.shape[1]]
+        self.rows.copy_(t)
+        self.at = self.buf.data_ptr() + off * t.element_size()
+
+
+# Where the caller's rows lie (first element, stride) decides neither what is added in which order nor, with it, any bit: odd
+# strides and first elements against dense rows, out of place against in place (which works from a dense copy of Y1), and the two
+# calls against the fused one.  Few rows (norm in the GEMM launches) and many (a kernel of its own), float32 streams.
+@pytest.mark.parametrize("dtype,d,H,T,fp32_streams", [("f32", 128, 4, 150, False), ("f32", 512, 4, 70, False), ("bf16", 512, 4, 200, False),
+                                                      ("bf16", 512, 4, 1300, False), ("bf16", 512, 4, 200, True)])
+@pytest.mark.parametrize("pad,off", [(1, 0), (8, 1), (3, 3)])
+def test_bits_do_not_depend_on_where_the_streams_lie(dtype, d, H, T, fp32_streams, pad, off):
+    wl = synth.Workload("placed", d, H, d // H, 6, 2, 96, 160, 1, T, dtype, gain_jitter=0.02, seed=T)
+    case = Case(wl, fp32_streams=fp32_streams)
+    w, h, ld = case.Wd, wl.h, wl.h + pad
+    y1d, y2d = case.forward()
+    put = lambda t: _Placed(t, ld, off)
+    x1, x2, y1, y2, r1, r2 = (put(t) for t in (case.up_s(case.x1), case.up_s(case.x2), y1d, y2d, y1d, y2d))
+    f1, f2 = put(torch.zeros_like(y1d)), put(torch.zeros_like(y1d))
+    R.revffn_forward(case.ctx, w, x1.at, x2.at, f1.at, f2.at, 1, T, ld)
+    torch.cuda.synchronize()
+    assert torch.equal(f1.rows, y1d) and torch.equal(f2.rows, y2d)
+    for n in (1, 2):
+        want1, want2 = case.inverse(y1d, y2d, n_iters=n)
+        R.revffn_inverse(case.ctx, w, y1.at, y2.at, r1.at, r2.at, 1, T, ld)
+        torch.cuda.synchronize()
+        assert torch.equal(r1.rows, want1) and torch.equal(r2.rows, want2), n
+        dy1, dy2, dx1, dx2 = (put(t) for t in (case.up(case.dy1), case.up(case.dy2), case.empty(), case.empty()))
+        G = Hn.alloc_grads(w)
+        R.revffn_backward(case.ctx, w, r1.at, r2.at, y1.at, dy1.at, dy2.at, dx1.at, dx2.at, G, 1, T, ld)
+        a, b, da, db = (put(t) for t in (y1d, y2d, case.up(case.dy1), case.up(case.dy2)))
+        F = Hn.alloc_grads(w)
+        R.revffn_inverse_backward(case.ctx, w, a.at, b.at, a.at, b.at, da.at, db.at, da.at, db.at, F, 1, T, ld)
+        torch.cuda.synchronize()
+        assert torch.equal(a.rows, want1) and torch.equal(b.rows, want2), n
+        assert torch.equal(da.rows, dx1.rows) and torch.equal(db.rows, dx2.rows), n
+        for k in G:
+            assert G[k] is None or torch.equal(G[k], F[k]), (n, k)
+
+
+# One stream on a 16-byte boundary and the other not, helper streams on (the first query side alone) and off (both streams'
+# in one launch)
+@pytest.mark.parametrize("dtype,B,S", [("f32", 2, 200), ("bf16", 3, 333)])
+@pytest.mark.parametrize("off", [(0, 1), (1, 0)])
+def test_helper_streams_same_bits_wherever_the_streams_lie(dtype, B, S, off):
+    wl = synth.Workload("streams", 512, 4, 128, 12, 3, 192, 320, B, S, dtype, gain_jitter=0.02, seed=S)
+    case = Case(wl)
+    y1d, y2d = case.forward()
+    y1, y2 = _Placed(y1d, wl.h, off[0]), _Placed(y2d, wl.h, off[1])
+    outs = []
+    for on in (True, False):
+        case.ctx.set_helper_streams(on)
+        r1, r2, o1, o2 = _Placed(y1d, wl.h, off[0]), _Placed(y2d, wl.h, off[1]), case.empty(), case.empty()
+        G = Hn.alloc_grads(case.Wd)
+        R.revffn_inverse_backward(case.ctx, case.Wd, y1.at, y2.at, r1.at, r2.at, case.up(case.dy1), case.up(case.dy2), o1, o2, G,
+                                  wl.B, wl.S, wl.h, None)
+        torch.cuda.synchronize()
+        outs.append([r1.rows, r2.rows, o1, o2] + [G[k] for k in sorted(G) if G[k] is not None])
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
+
+
 def test_frozen_groups_are_skipped():
     """NULL gradient fields (adapter-only stage; frozen routers) leave the others unchanged."""
     wl = synth.WORKLOADS["mid_f32"]
