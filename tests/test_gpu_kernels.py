@@ -200,6 +200,12 @@ def test_float32_matrix_attention(dtype, dh, B, S, H):
     _attention_case(B, S, H, dh, False, 1, dtype)
 
 
+# more sequences than half of what a grid's third dimension takes (65536): the batch alone is what counts along it
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_float32_matrix_attention_of_many_sequences(dtype):
+    _attention_case(33000, 1, 1, 16, True, 1, dtype)
+
+
 # (dtype, head width, mode, granularity): the float32 matrix kernels and the vector kernel keep a token that is not finite from
 # every token that does not see it; the bf16 kernels, which multiply whole tiles by zero probabilities, only from those outside
 # its block of 64
