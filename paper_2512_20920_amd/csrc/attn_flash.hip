@@ -817,11 +817,21 @@ __global__ void __launch_bounds__(256, 2) flash_bwd_short_k(const bf16* __restri
 //   4 heads: 2 x 200 11 / 36 -> 8.4 / 13    1 x 2048 52 / 186 -> 24 / 43    32 heads: 1 x 1024 33 / 115 -> 26 / 74    4 x 256 14 / 49 -> 16 / 49
 // Alone it pays up to two workgroups per CU and up to four for long chains.  Inside a step, where the attention shares the chip
 // with the routed experts, CU time counts too: 4 x 512 tokens 2793 -> 2820 us per step, 1 x 1024 2190 -> 2158, 1 x 1300 2460 ->
-// 2438, so the line is at 1024 tokens of 16 heads, 2048 from 1024 positions on.  The heads count coarsely, and more than 16 as
-// 18: the two forms add in different orders, and the same heads a few at a time and all together mostly agree to the bit.
+// 2438, so the line is at 1024 tokens of 16 heads, 2048 from 1024 positions on, with the heads counted coarsely and more than
+// 16 as 18.
+// Many heads fill the chip with few tokens, so from there on a second line bounds tokens x heads, in tokens of 16 heads (work).
+// Measured, us, two forward passes and a backward one, 128 queries -> 32 (heads, tokens: work):
+//   20, 1 x 1024: 1280 168 -> 93    48, 1 x 1024: 3072 197 -> 191    64, 1 x 1024: 4096 204 -> 244    128, 1 x 1024: 8192 330 -> 536
+//   64, 1 x 512: 2048 105 -> 96    48, 2 x 512: 3072 128 -> 143    128, 1 x 512: 4096 137 -> 188
+//   32, 3 x 256: 1536 70 -> 69    32, 4 x 256: 2048 73 -> 80    64, 4 x 256: 4096 109 -> 156
+//   64, 2 x 128: 1024 49 -> 41    48, 4 x 128: 1536 54 -> 59    64, 4 x 128: 2048 59 -> 70
+//   40, 4 x 64: 640 35 -> 34    48, 4 x 64: 768 35 -> 38    64, 8 x 64: 2048 51 -> 67
+// The two forms add in different orders.  A call on some of the heads takes the short form wherever the call on all of them does,
+// and gives the same bits then; where all of them take the long form, some alone need not.
 static bool short_sequence(int B, int S, int H) {
-  const i64 load = (i64)B * S * (H <= 4 ? 4 : H <= 8 ? 8 : H <= 16 ? 16 : 18) / 16;
-  return S <= 2048 && (load <= 1024 || (load <= 2048 && S >= 1024));
+  const i64 tokens = (i64)B * S, load = tokens * (H <= 4 ? 4 : H <= 8 ? 8 : H <= 16 ? 16 : 18) / 16;
+  if (S > 2048 || load > (S >= 1024 ? 2048 : 1024)) return false;
+  return H <= 16 || tokens * H <= 16 * (S >= 1024 ? 3072 : S >= 448 ? 2752 : S >= 256 ? 1856 : S >= 128 ? 1344 : 768);
 }
 
 int launch_attn_fwd_flash(const void* q, const void* k, const void* v, void* o, float* lse, int B, int S, int H,

@@ -131,7 +131,12 @@ def _attention_case(B, S, H, dh, causal, mode, dtype, offset=0):
 @pytest.mark.parametrize("causal", [True, False])
 # (one query, one past a tile of 32, fewer tiles of keys than the four waves that share them and more, several batches; the last:
 # 128 queries per workgroup)
-@pytest.mark.parametrize("B,S,H", [(1, 128, 1), (2, 200, 3), (1, 64, 2), (1, 1, 1), (1, 451, 2), (3, 33, 5), (1, 161, 17), (5, 97, 2), (6, 400, 17)])
+@pytest.mark.parametrize("B,S,H", [(1, 128, 1), (2, 200, 3), (1, 64, 2), (1, 1, 1), (1, 451, 2), (3, 33, 5), (1, 161, 17), (5, 97, 2), (6, 400, 17),
+                                   # 128 queries per workgroup for sequences that end inside their first tile: one row, one past
+                                   # a tile of 32, one past a tile of 64 keys, a whole one, one short of 128
+                                   (1100, 1, 16), (64, 33, 16), (40, 65, 17), (35, 64, 8), (17, 127, 8),
+                                   # both sides of the line for many heads
+                                   (1, 128, 168), (1, 128, 176), (1, 64, 192), (1, 64, 200)])
 def test_flash_attention(B, S, H, causal):
     _attention_case(B, S, H, 128, causal, 2, 1)
 
@@ -161,17 +166,18 @@ def test_vector_attention(dtype, dh, offset):
 
 
 # 128 queries per workgroup, more workgroups than CUs and no more than two for each: the second part of the grid runs in
-# reverse (16 and 24 heads: a whole and a broken row of heads where it starts); 48 and 100 heads of short sequences: 32 queries
-# per workgroup
+# reverse (16 and 24 heads: a whole and a broken row of heads where it starts; 100 heads: three tiles each); 48 heads of 2 x 451
+# tokens: 32 queries per workgroup
 @pytest.mark.parametrize("B,S,H", [(2, 451, 48), (1, 300, 100), (1, 2200, 16), (1, 2100, 24)])
 def test_flash_attention_paired_tiles(B, S, H):
     _attention_case(B, S, H, 128, True, 2, 1)
 
 
-# more heads than 256 workgroups take, against the same heads a quarter at a time (one workgroup per CU): dK/dV works on 32
-# queries at a time in the one and 64 in the other, in the same order (2100 tokens; the short sequences have one form)
+# more heads than 256 workgroups take, against the same heads a quarter at a time.  The first three take 32 queries per workgroup
+# both ways; in the others (128 per workgroup) dK/dV works on 32 queries at a time for all heads and on 64 for a quarter of them (one
+# workgroup per CU), in the same order
 @pytest.mark.parametrize("causal", [True, False])
-@pytest.mark.parametrize("B,S,H", [(2, 451, 48), (1, 129, 160), (8, 33, 40), (1, 2100, 20)])
+@pytest.mark.parametrize("B,S,H", [(2, 451, 48), (1, 129, 160), (8, 33, 40), (1, 2100, 20), (9, 127, 48), (5, 300, 40)])
 def test_flash_attention_gradients_do_not_depend_on_the_grid(B, S, H, causal):
     rng = np.random.default_rng(S + H)
     q, k, v, do = (Hn.upload(_bf(rng, (B * S, H * 128)), "bf16") for _ in range(4))
