@@ -76,6 +76,7 @@ struct revffn_ctx {
   int *idx, *counts, *offsets, *row_map, *inv_map;
   int *tg_a, *tm_a, *tg_b, *tm_b, *tf_a, *tf_b, *tg_c, *tm_c, *tf_c;
   int max_tiles_a, max_tiles_b, max_tiles_c;
+  int expert_width = 0;       // width of the routed experts' inputs and outputs: d_model, half of it with merged weights
   int bm_b = 128;             // height of the tiles in list b for the routing in the workspace: 128, or 160 (see expert_rows_b)
   int expert_nt = 0, expert_nn = 0;
   bool no_fused_swiglu = false; // REVFFN_NO_FUSED_SWIGLU (tuning aid): SwiGLU as a kernel of its own after the gate/up GEMM
@@ -300,10 +301,12 @@ bool few_rows(const revffn_ctx* c, const GemmArgs& g) {
 // Up to this mean of rows per expert nearly all experts fit in one tile of 128 rows
 constexpr i64 ROWS_ONE_TILE = 118;
 // the routed experts' weights are more than the memory-side cache keeps from one pass over them to the next
-// (of the experts that the rows reach)
+// (of the experts that the rows reach; merged weights are half as wide, and a few tokens' experts of them do stay: Qwen shape,
+// 4, 5, 6, 7 tokens, past the caches / through them, 176, 193, 207, 211 / 167, 183, 192, 202 us per forward and inverse pass,
+// 8 tokens (277 MB) 220 / 221, 12 245 / 259)
 bool experts_pass_through(const revffn_ctx* c, i64 rows) {
   const revffn_config& f = c->cfg;
-  return 3.0 * (double)(rows < f.n_experts ? rows : f.n_experts) * f.d_expert * f.d_model * c->es >= (double)(1 << 28);
+  return 3.0 * (double)(rows < f.n_experts ? rows : f.n_experts) * f.d_expert * c->expert_width * c->es >= (double)(1 << 28);
 }
 
 int run_gemm(revffn_ctx* c, GemmArgs g, int ta, int tb, int tc, hipStream_t s) {
@@ -759,6 +762,7 @@ int moe_acts(revffn_ctx* c, const revffn_weights* w, const void* y1, i64 ld, int
   const int N = T * k;
   c->lastT = T;
   c->lastT_rows = N;
+  c->expert_width = d;
   c->bm_b = expert_rows_b(c, N, E);
   // The norm and the up-projection come first, then one fork: the first query side and the shared expert (which needs Um
   // only) run beside the routing chain and the routed experts, and join where the results are combined.  An edge costs
@@ -905,6 +909,7 @@ int moe_merged(revffn_ctx* c, const revffn_weights* w, const revffn_merged* m, c
   const int N = T * k;
   c->lastT = T;
   c->lastT_rows = N;
+  c->expert_width = h;
   c->bm_b = expert_rows_b(c, N, E);
   hipStream_t s0 = side(c, s, 0);
   p_rmsnorm_fwd(c, dt, c->sdt, y1, ld, w->norm_m, c->n3, h, T, h, f.rms_eps, s);
