@@ -573,13 +573,15 @@ __global__ void __launch_bounds__(256) moe_bwd_rows_v8_k(const bf16* __restrict_
                                                          const float* __restrict__ wts, const float* __restrict__ gamma,
                                                          bf16* __restrict__ dyp, bf16* __restrict__ dys,
                                                          float* __restrict__ dzext, int Tn, int d, int k,
-                                                         int E1, int has_gate, RouterBwd r, RowCopy copy) {
+                                                         int E1, int has_gate, RouterBwd r, RowCopy copy, int copy8) {
   __shared__ float red[4], sdw[16];
   const int t = blockIdx.x;
   if (t >= Tn) {
     const int row = t - Tn;
     const bf16* sp = row < copy.rows_a ? (const bf16*)copy.src_a + (i64)row * d : (const bf16*)copy.src_b + (i64)(row - copy.rows_a) * d;
-    for (int c = threadIdx.x * 8; c < d; c += 256 * 8) *(bf16x8_t*)((bf16*)copy.dst + (i64)row * d + c) = *(const bf16x8_t*)(sp + c);
+    bf16* dp = (bf16*)copy.dst + (i64)row * d;
+    if (copy8) for (int c = threadIdx.x * 8; c < d; c += 256 * 8) *(bf16x8_t*)(dp + c) = *(const bf16x8_t*)(sp + c);
+    else for (int c = threadIdx.x; c < d; c += 256) dp[c] = sp[c];
     return;
   }
   const bf16* dr = drs + (i64)t * d;
@@ -618,9 +620,10 @@ void launch_moe_bwd_rows(int dt, const void* drs, const void* yp, const void* ys
                          int k, int E1, int has_gate, const RouterBwd& r, const RowCopy& copy, hipStream_t s) {
   if (Tn <= 0) return;
   const dim3 grid(Tn + copy.rows_a + copy.rows_b);
-  if (vec8_ok(dt, d, {drs, yp, ys, dyp, dys, copy.src_a, copy.src_b, copy.dst})) {
+  if (vec8_ok(dt, d, {drs, yp, ys, dyp, dys})) {          // (buffers of the workspace; the copied rows are the caller's weights)
     hipLaunchKernelGGL(moe_bwd_rows_v8_k, grid, dim3(256), 0, s, (const bf16*)drs, (const bf16*)yp, (const bf16*)ys,
-                       inv_map, wts, gamma, (bf16*)dyp, (bf16*)dys, dzext, Tn, d, k, E1, has_gate, r, copy);
+                       inv_map, wts, gamma, (bf16*)dyp, (bf16*)dys, dzext, Tn, d, k, E1, has_gate, r, copy,
+                       (int)vec8_ok(dt, d, {copy.src_a, copy.src_b, copy.dst}));
     return;
   }
   DISPATCH_DT(dt, hipLaunchKernelGGL(moe_bwd_rows_k<T>, grid, dim3(256), 0, s, (const T*)drs, (const T*)yp,

@@ -691,6 +691,23 @@ def test_helper_streams_same_bits_wherever_the_streams_lie(dtype, B, S, off):
         assert torch.equal(a, b)
 
 
+# Router rows and shared gate on any element: the launch that copies them along keeps the form it has for the tokens' own rows
+def test_router_rows_that_are_not_aligned():
+    wl = synth.WORKLOADS["mid_bf16"]
+    case = Case(wl, fp32_grads=True)
+    x1d, x2d = case.up(case.x1), case.up(case.x2)
+    y1d, _ = case.forward()
+    want = case.backward(x1d, x2d, y1d)
+    for n in ("w_router", "ws_gate"):
+        t = case.Wd[n]
+        case.Wd[n] = torch.cat([t.new_zeros(1), t.flatten()])[1:].view(t.shape)
+        assert case.Wd[n].data_ptr() % 16 != 0
+    got = case.backward(x1d, x2d, y1d)
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    for k in want[2]:
+        assert want[2][k] is None or torch.equal(got[2][k], want[2][k]), k
+
+
 def test_frozen_groups_are_skipped():
     """NULL gradient fields (adapter-only stage; frozen routers) leave the others unchanged."""
     wl = synth.WORKLOADS["mid_f32"]
