@@ -495,14 +495,13 @@ void launch_combine_couple(int dt, int ts, const void* yp, const int* inv_map, c
 // (a kernel of its own for the second part, and one that stacks the router rows for the GEMM that follows, were 5 us each of
 // every step at any size: both are latency)
 // ---------------------------------------------------------------------------------
-// dz of one token by one wave, lanes over the experts; sdw: its dw, sgate: dz of the gate logit
-__device__ __forceinline__ void router_bwd_token(const RouterBwd& r, const float* wts, const float* sdw, float sgate, float* dzext,
+// dz of one token by one wave, lanes over the experts; my_dw: dw of slot `lane`, sgate: dz of the gate logit
+__device__ __forceinline__ void router_bwd_token(const RouterBwd& r, const float* wts, float my_dw, float sgate, float* dzext,
                                                  int t, int k, int E1, int lane) {
   const int E = r.E;
   const float* p = r.probs + (i64)t * E;
   // slot s lives in lane s (k <= 16); sums over the slots run in slot order on every lane
   const int my_sel = lane < k ? r.idx[(i64)t * k + lane] : -1;
-  const float my_dw = lane < k ? sdw[lane] : 0.f;
   const float my_w = lane < k ? wts[(i64)t * k + lane] : 0.f;
   const float my_p = lane < k ? p[my_sel] : 0.f;
   float ssum = 0.f, dww = 0.f;
@@ -532,7 +531,7 @@ __global__ void __launch_bounds__(256) moe_bwd_rows_k(const T* __restrict__ drs,
                                                       T* __restrict__ dyp, T* __restrict__ dys,
                                                       float* __restrict__ dzext, int Tn, int d, int k, int E1, int has_gate,
                                                       RouterBwd r, RowCopy copy) {
-  __shared__ float red[4], sdw[16];
+  __shared__ float red[4];
   const int t = blockIdx.x;
   if (t >= Tn) {
     const int row = t - Tn;
@@ -553,6 +552,7 @@ __global__ void __launch_bounds__(256) moe_bwd_rows_k(const T* __restrict__ drs,
     gate = block_sum_256(acc, red) * g * (1.f - g);
     if (threadIdx.x == 0) dzext[(i64)t * E1 + (E1 - 1)] = gate;
   }
+  float my_dw = 0.f;                      // dw of slot threadIdx.x (k <= 16)
   for (int s = 0; s < k; s++) {
     int pos = inv_map[(i64)t * k + s];
     float w = wts[(i64)t * k + s];
@@ -563,10 +563,9 @@ __global__ void __launch_bounds__(256) moe_bwd_rows_k(const T* __restrict__ drs,
       dyp[(i64)pos * d + c] = from_f<T>(w * v);
     }
     acc = block_sum_256(acc, red);
-    if (threadIdx.x == 0) sdw[s] = acc;
+    if ((int)threadIdx.x == s) my_dw = acc;
   }
-  // (wave 0 wrote sdw and is the one that reads it)
-  if (threadIdx.x < 64) { __builtin_amdgcn_wave_barrier(); router_bwd_token(r, wts, sdw, gate, dzext, t, k, E1, threadIdx.x); }
+  if (threadIdx.x < 64) router_bwd_token(r, wts, my_dw, gate, dzext, t, k, E1, threadIdx.x);
 }
 __global__ void __launch_bounds__(256) moe_bwd_rows_v8_k(const bf16* __restrict__ drs, const bf16* __restrict__ yp,
                                                          const bf16* __restrict__ ys, const int* __restrict__ inv_map,
@@ -574,7 +573,7 @@ __global__ void __launch_bounds__(256) moe_bwd_rows_v8_k(const bf16* __restrict_
                                                          bf16* __restrict__ dyp, bf16* __restrict__ dys,
                                                          float* __restrict__ dzext, int Tn, int d, int k,
                                                          int E1, int has_gate, RouterBwd r, RowCopy copy, int copy8) {
-  __shared__ float red[4], sdw[16];
+  __shared__ float red[4];
   const int t = blockIdx.x;
   if (t >= Tn) {
     const int row = t - Tn;
@@ -599,6 +598,7 @@ __global__ void __launch_bounds__(256) moe_bwd_rows_v8_k(const bf16* __restrict_
     gate = block_sum_256(acc, red) * g * (1.f - g);
     if (threadIdx.x == 0) dzext[(i64)t * E1 + (E1 - 1)] = gate;
   }
+  float my_dw = 0.f;                      // dw of slot threadIdx.x (k <= 16)
   for (int s = 0; s < k; s++) {
     const int pos = inv_map[(i64)t * k + s];
     const float w = wts[(i64)t * k + s];
@@ -611,9 +611,9 @@ __global__ void __launch_bounds__(256) moe_bwd_rows_v8_k(const bf16* __restrict_
       *(bf16x8_t*)(dyp + (i64)pos * d + c) = o;
     }
     acc = block_sum_256(acc, red);
-    if (threadIdx.x == 0) sdw[s] = acc;
+    if ((int)threadIdx.x == s) my_dw = acc;
   }
-  if (threadIdx.x < 64) { __builtin_amdgcn_wave_barrier(); router_bwd_token(r, wts, sdw, gate, dzext, t, k, E1, threadIdx.x); }
+  if (threadIdx.x < 64) router_bwd_token(r, wts, my_dw, gate, dzext, t, k, E1, threadIdx.x);
 }
 void launch_moe_bwd_rows(int dt, const void* drs, const void* yp, const void* ys, const int* inv_map,
                          const float* wts, const float* gamma, void* dyp, void* dys, float* dzext, int Tn, int d,
