@@ -348,7 +348,8 @@ int run_gemm(revffn_ctx* c, GemmArgs g, int ta, int tb, int tc, hipStream_t s) {
       const i64 one_tile = (past ? ROWS_ONE_TILE : 96) * E;
       int shape = g.b_trans ? c->expert_nn : c->expert_nt;
       if (c->expert_tile) shape = c->expert_tile == 256 ? 2 : 1;
-      if (!shape) {
+      const bool forced = shape != 0;
+      if (!forced) {
         if (!g.b_trans) shape = rows > 384 * E ? 4 : 3;
         else if (rows > 192 * E || (rows > one_tile && g.N % 256 == 0)) shape = 4;
         else shape = rows > one_tile ? 2 : 3;
@@ -361,7 +362,7 @@ int run_gemm(revffn_ctx* c, GemmArgs g, int ta, int tb, int tc, hipStream_t s) {
       // tokens, 1457 -> 1520.
       const i64 low = rows < rows / 32 + E ? rows : rows / 32 + E;          // row tiles, at most
       const i64 tiles32 = low * ((g.N + 31) / 32);
-      g.few_rows = tiles32 <= (g.K <= 256 ? 1600 : 1000) || (rows <= 2 * E && g.K <= 4096 && tiles32 <= 6000);
+      g.few_rows = !forced && (tiles32 <= (g.K <= 256 ? 1600 : 1000) || (rows <= 2 * E && g.K <= 4096 && tiles32 <= 6000));
       bool tall = shape == 2 || shape == 4;
       g.tile_bn = shape >= 3 ? 256 : 128;
       const bool mid = c->bm_b == BM_B_MID;              // list b holds 160-row tiles: for the 160x256 forward kernel only

@@ -423,6 +423,21 @@ def test_fused_swiglu_epilogue_matches_the_separate_kernel(name, monkeypatch):
         assert torch.equal(a, b)
 
 
+# The tuning aids force a tile shape of the routed experts' GEMMs at any size, also where the kernel for few rows would take them
+# (whose sums are cut among waves: other bits)
+@pytest.mark.parametrize("shape", [1, 2, 3, 4])
+def test_forced_expert_tile_shapes(shape, monkeypatch):
+    wl = synth.WORKLOADS["mid_rows137_bf16"]
+    free = Case(wl).forward()
+    monkeypatch.setenv("REVFFN_EXPERT_NT", str(shape))
+    monkeypatch.setenv("REVFFN_EXPERT_NN", str(shape))
+    case = Case(wl)
+    y1d, y2d, _ = _forward_checks(case, TOL["bf16"])
+    assert torch.equal(y1d, free[0]) and not torch.equal(y2d, free[1])
+    x1d, x2d = _inverse_checks(case, y1d, y2d, TOL["bf16"], 1)
+    _backward_checks(case, x1d, x2d, y1d, TOL["bf16"])
+
+
 @pytest.mark.parametrize("mode", [0, 1])
 def test_fp32_weight_gradients(mode):
     """config.fp32_grads: every weight gradient lands in a float32 buffer.  Same parity bar against the oracle, and
