@@ -401,13 +401,17 @@ def test_symmetric_comparison_block(name, mode):
             assert torch.equal(G3[k], G4[k]), k
 
 
+# (137 rows per expert and more tiles than the kernel for few rows takes: 160x256 forward, 256x128 and 256x256 back)
+ROWS137_TILES = synth.Workload("rows137_tiles", 640, 5, 128, 12, 3, 600, 160, 2, 274, "bf16", gain_jitter=0.02, seed=5)
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("name", ["mid_bf16", "mid_fewbig_bf16", "mid_rows137_bf16"])
+@pytest.mark.parametrize("name", ["mid_bf16", "mid_fewbig_bf16", "mid_rows137_bf16", "rows137_tiles"])
 def test_fused_swiglu_epilogue_matches_the_separate_kernel(name, monkeypatch):
     """The gate/up GEMMs write silu(gate) * up from their epilogue (a tile holds matching gate and up columns).  Same
     bits as the GEMM followed by the SwiGLU kernel, through forward, inverse and every gradient; the expert widths of
-    these workloads (192 and 320; 712; 200 and 160) leave tiles whose gate columns end inside the tile."""
-    wl = synth.WORKLOADS[name]
+    these workloads (192 and 320; 712; 200 and 160; 600 and 160) leave tiles whose gate columns end inside the tile."""
+    wl = synth.WORKLOADS.get(name, ROWS137_TILES)
     outs = []
     for separate in (False, True):
         if separate:
@@ -898,11 +902,14 @@ def test_degenerate_routing_and_limits_bf16(mode):
     run(wl, min_same=0.6)
 
 
-def test_calls_can_be_captured_into_a_hip_graph():
+# (mid_bf16 runs on one stream; 3 x 333 tokens of it, and a shared expert ten times as wide, spread over the helper streams)
+@pytest.mark.parametrize("B,S,Is", [(2, 200, 320), (3, 333, 3200)])
+def test_calls_can_be_captured_into_a_hip_graph(B, S, Is):
     """A step (forward + fused inverse/backward, helper streams included) captured once into a HIP graph and
     replayed gives the bits of the eager calls, on every replay, with eager work and synchronisations between the
     replays: the calls only enqueue kernels and event dependencies (no allocation, no memset node, no host wait)."""
-    wl = synth.WORKLOADS["mid_bf16"]
+    import dataclasses
+    wl = dataclasses.replace(synth.WORKLOADS["mid_bf16"], B=B, S=S, d_shared=Is)
     case = Case(wl)
     x1d, x2d, dy1d, dy2d = case.up(case.x1), case.up(case.x2), case.up(case.dy1), case.up(case.dy2)
     y1d, y2d, r1d, r2d, dx1d, dx2d = (case.empty() for _ in range(6))
@@ -1066,7 +1073,20 @@ def _oracle_merged(case):
 
 @pytest.mark.parametrize("name", ["tiny_shared_f32", "mid_f32", "mid_bf16", "mid_fewbig_bf16", "mid_rows137_bf16"])
 def test_merged_adapters_parity(name):
-    wl = synth.WORKLOADS[name]
+    _merged_checks(synth.WORKLOADS[name])
+
+
+# Norm, projections and rotation of few tokens in one launch: every number of waves and pieces that the width of the rows gives (four
+# and one up to 256, eight and one up to 512, eight and two up to 1024, the last piece ragged at 320 and 640), heads of 16, 64 and
+# 128, one token, part of a tile, a whole one, several.  In place on the halves of one tensor the strides differ: two launches.
+@pytest.mark.parametrize("d,dh,T", [(512, 16, 17), (512, 64, 70), (640, 64, 1), (640, 128, 33), (1024, 16, 32), (1024, 64, 100),
+                                    (1280, 64, 17), (1280, 128, 40), (2048, 128, 1), (2048, 64, 17), (2048, 128, 32)])
+def test_merged_adapters_parity_few_tokens(d, dh, T):
+    _merged_checks(synth.Workload(f"merged_d{d}_dh{dh}", d, d // dh, dh, 4, 2, 64, 96, 1, T, "bf16", gain_jitter=0.02, seed=d + T))
+
+
+def _merged_checks(wl):
+    name = wl.name
     tol = TOL[wl.dtype]
     case = Case(wl)
     M, Mr = _oracle_merged(case)
