@@ -391,8 +391,10 @@ template <class TA, class TB, class TC, class TS, bool AT, bool BT>
 static void go(const GemmArgs& g, hipStream_t s) {
   // One wave per chunk of k, at most 8 (of a workgroup of at least 4: the epilogue wants the threads).  The cut depends
   // on k alone, so that a result has the same bits whatever else is in the launch (a product over 2 T rows and one over
-  // T rows, say).  64x32 tiles (a quarter less operand traffic per product) where they alone are 16 waves per CU, else
-  // 32x32.  small_tiles (the caller's choice, since it changes the order of the sum): 16x16 tiles and up to 16 waves, for
+  // T rows, say).  Operands that go straight into LDS are faster on 32x32 tiles at every size (us, so / 64x32 from registers:
+  // 1024 x 1024 x 512 16 / 23, 2048 x 2048 x 2048 167 / 233, 4096 x 4096 x 2048 674 / 913; a step of 2048 tokens, 1024 wide,
+  // 3171 / 3719).  The others take 64x32 tiles (a quarter less operand traffic per product) where they alone are 16 waves per
+  // CU, else 32x32.  small_tiles (the caller's choice, since it changes the order of the sum): 16x16 tiles and up to 16 waves, for
   // the few dozen rows of the router matrices, whose 32x32 tiles would leave most CUs idle.
   const int krange = (g.group_mode == 2 ? cdiv(g.K, g.n_groups) : g.K) * (g.A2 ? 2 : 1);    // (per expert: the mean)
   if (g.small_tiles && g.group_mode == 0) {

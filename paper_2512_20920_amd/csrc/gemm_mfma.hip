@@ -200,7 +200,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, TC* C, const vo
   const bf16* bias = (const bf16*)bias_ptr;
   const bf16* resid = (const bf16*)g.resid;
   if (!bias && !g.tap && !resid) {
-    // plain store (most projections, data gradients, weight gradients in float32): no per-element epilogue work
+    // plain store (most projections, data gradients, weight gradients in float32 and those in bf16 that do not leave through
+    // LDS, see gemm_tile): no per-element epilogue work
     // the column blocks of one row are stored back to back, so that the 64-byte pieces of a line reach L2 together and
     // are merged there.  (Through LDS in whole lines, as the bf16 weight gradients go: no faster for stores that stay in L2.)
     const bool full = (m0 + BM <= m_end) && (n0 + BN <= g.N);
@@ -448,6 +449,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const bf16* A, cons
   // past the caches are not merged on the way (see GemmArgs::once), and in pieces of 64 bytes they were what bound these
   // kernels: 8 rows per expert 96 and 191 us; a step of 128 tokens 1176 -> 1130 us, of 512 1514 -> 1475, 4 x 512
   // 2749 -> 2705, 4 blocks of 1024 7873 -> 7704, 8 experts of 14336, 60 tokens, 2683 -> 2529.
+  // (Tiles whose waves are 32 columns wide, for small gradients, store 64 bytes at a time from the registers.  Two waves' halves put
+  // together, past the caches or not, took the same time: 512-wide block, 400 tokens 323 us per step in all four forms, 1500 tokens
+  // 451 to 454, with a kernel that reads the gradients behind it 338 and 471.  The same for buffers that are not 16-byte aligned:
+  // 512 tokens at the Qwen shape 1676 us past the caches, 1680 through them.)
   if constexpr (AT && BT && sizeof(TC) == 2 && TN == 2 && (unsigned)NW * TE * 32 * 128 <= NS * STAGE) {
     if (whole_lines(g, C, bias_ptr)) {
       const int mw = m0 + wm, nw = n0 + wn + (lane & 7) * 8;

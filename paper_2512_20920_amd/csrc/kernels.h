@@ -59,12 +59,16 @@ struct GemmArgs {
   // group_mode 2: the permutation kernel's flag that the routing is even (null: treated as uneven)
   const int* tile_count = nullptr;
   // group_mode 1, 128x256 tiles and the kernel for few rows: B goes past the caches, as results in the layout of weight
-  // gradients always do.  Set where every weight is read by one row tile and the block's expert weights are more than the
-  // memory-side cache holds (256 MB), so that no pass over them finds what the last one left: what passes through evicts
-  // the activations, the dense layers' and the shared expert's weights, and every line of a gradient that is pushed out later
+  // gradients always do.  Set where the mean expert fits in one row tile, so that nearly every weight is read by one, and the
+  // weights of the experts reached are more than the memory-side cache holds (256 MB), so that no pass over them finds what
+  // the last one left: what passes through evicts the activations, the dense layers' and the shared expert's weights, and every line of a gradient that is pushed out later
   // costs the reading launch its write.  Qwen shape, us per step, neither / gradients / both: 128 tokens 1371, 1311, 1186;
   // 300 1530, 1470, 1324; 512 1703, 1652, 1522; 4 blocks of 1024 8338, 8178, 7940; 4 x 512 2798, 2770; 8192 9446, 9420;
   // merged 37 tokens 343, -, 327, 300 455, -, 425.  (160x256 tiles 0.7 % slower so, where some experts have two tiles 4 %.)
+  // The host knows the mean only.  Routing that gives the hottest experts 8 times that, several row tiles that would share their
+  // weights, gains up to 87 rows per expert and loses a little above; through / past the caches, us per step, skewed and even:
+  // 512 tokens 1594, 1491 and 1585, 1476   1024 1988, 1962 and 1974, 1912   1300 2379, 2363 and 2343, 2274   1600 2473, 2490
+  // and 2426, 2376   1750 2609, 2632 and 2573, 2538.
   int once = 0;
   const int* tile_first = nullptr;       // per tile: (first tile of its expert) << 16 | tiles of that expert
   // MFMA kernel, dense problems: n_sub > 1 launches that many problems of one shape, layout and
