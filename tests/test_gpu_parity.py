@@ -1149,6 +1149,34 @@ def _merged_checks(wl):
     print(name, "merged", rep)
 
 
+# Where the caller's rows lie decides no bit of the merged passes either: few rows in one launch with their norms and rotation (one
+# piece per wave, two), many rows, float32; in place works from a dense copy of Y1
+@pytest.mark.parametrize("dtype,d,dh,T", [("f32", 128, 32, 50), ("bf16", 512, 64, 70), ("bf16", 2048, 128, 17), ("bf16", 512, 128, 1300)])
+@pytest.mark.parametrize("pad,off", [(1, 0), (8, 1), (3, 3)])
+def test_merged_bits_do_not_depend_on_where_the_streams_lie(dtype, d, dh, T, pad, off):
+    wl = synth.Workload("placed_merged", d, d // dh, dh, 4, 2, 64, 96, 1, T, dtype, gain_jitter=0.02, seed=T)
+    case = Case(wl)
+    w, ld, Md = case.Wd, wl.h + pad, Hn.alloc_merged(wl)
+    R.revffn_merge_adapters(case.ctx, w, Md)
+    x1d, x2d, y1d, y2d = case.up_s(case.x1), case.up_s(case.x2), case.empty_s(), case.empty_s()
+    R.revffn_forward_merged(case.ctx, w, Md, x1d, x2d, y1d, y2d, 1, T, wl.h)
+    put = lambda t: _Placed(t, ld, off)
+    x1, x2, f1, f2 = put(x1d), put(x2d), put(torch.zeros_like(y1d)), put(torch.zeros_like(y1d))
+    R.revffn_forward_merged(case.ctx, w, Md, x1.at, x2.at, f1.at, f2.at, 1, T, ld)
+    torch.cuda.synchronize()
+    assert torch.equal(f1.rows, y1d) and torch.equal(f2.rows, y2d)
+    for n in (1, 2):
+        case.ctx.set_inv_iters(n)
+        r1, r2 = case.empty_s(), case.empty_s()
+        R.revffn_inverse_merged(case.ctx, w, Md, y1d, y2d, r1, r2, 1, T, wl.h)
+        y1, y2, o1, o2 = put(y1d), put(y2d), put(torch.zeros_like(y1d)), put(torch.zeros_like(y1d))
+        R.revffn_inverse_merged(case.ctx, w, Md, y1.at, y2.at, o1.at, o2.at, 1, T, ld)
+        R.revffn_inverse_merged(case.ctx, w, Md, y1.at, y2.at, y1.at, y2.at, 1, T, ld)
+        torch.cuda.synchronize()
+        for a, b in ((o1, o2), (y1, y2)):
+            assert torch.equal(a.rows, r1) and torch.equal(b.rows, r2), n
+
+
 def test_merged_adapters_argument_errors():
     wl = synth.WORKLOADS["tiny_shared_f32"]
     case = Case(wl)
