@@ -357,12 +357,19 @@ int run_gemm(revffn_ctx* c, GemmArgs g, int ta, int tb, int tc, hipStream_t s) {
       // Small problems are latency: 32x32 tiles with k cut among the waves, up to about as many as the chip holds at once.
       // Measured, us per pass: a 512-wide block of 12 experts, 400 tokens (294 to 784 tiles) 420 -> 392, 1536 tokens (at most 936
       // of 2496: 595 -> 585; all of them 597); 256 wide, 15 experts, 753 tokens, k = 256: 872 tiles 460 -> 448, 1308 -> 440.
-      // One token of merged Qwen weights (352) 199 -> 153.  With a row or two per expert the weights are the same traffic in
-      // either form and more of them are in flight here: 16 tokens at the Qwen shape (5368) 1180 -> 1154; with 8 rows, 128
-      // tokens, 1457 -> 1520.
+      // One token of merged Qwen weights (352) 199 -> 153.
       const i64 low = rows < rows / 32 + E ? rows : rows / 32 + E;          // row tiles, at most
       const i64 tiles32 = low * ((g.N + 31) / 32);
-      g.few_rows = !forced && (tiles32 <= (g.K <= 256 ? 1600 : 1000) || (rows <= 2 * E && g.K <= 4096 && tiles32 <= 6000));
+      // (A row or two per expert, and weights that stay in the caches: merged, 4 tokens 170, in the kernel below 180.)
+      const bool small = tiles32 <= (g.K <= 256 ? 1600 : 1000) || (!past && rows <= 2 * E && g.K <= 4096 && tiles32 <= 6000);
+      // Above that, as long as nearly every expert fits in one row tile: see gemm_experts.hip.  Old / new, us per pass at the Qwen
+      // shape: 16 tokens 925 / 895, 64 1050 / 993, 128 1105 / 1067, 240 (16 rows) 1284 / 1240, merged 37 tokens 323 / 294, 200 378 / 350;
+      // 8 experts of 14336, 64 tokens 2416 / 2317, 80 (20 rows) 2505 / 2575 (experts of two tiles are read twice); 260 tokens
+      // 1240 / 1337 (its workgroups leave no room for the shared expert's larger tiles beside them).  Data gradients with k long (dXg)
+      // are faster on 128x256 tiles, whose lines are 512 bytes: 64 tokens 108 / 116 us, unless an expert has a row or two:
+      // 20 tokens 101 / 93.
+      g.stream = !small && rows <= 16 * E && (!g.b_trans || g.K <= 2048 || (rows <= 2 * E && g.K <= 4096));
+      g.few_rows = !forced && (small || g.stream);
       bool tall = shape == 2 || shape == 4;
       g.tile_bn = shape >= 3 ? 256 : 128;
       const bool mid = c->bm_b == BM_B_MID;              // list b holds 160-row tiles: for the 160x256 forward kernel only

@@ -80,7 +80,8 @@ struct GemmArgs {
   // iteration of the inverse); a workgroup whose rows are all marked exits at once, the others compute every row
   int bulk = 0;                           // 1: not on the caller's critical path (runs beside other kernels): least CU-time wins
   const unsigned char* row_skip = nullptr;
-  int few_rows = 0;                       // MFMA kernel, dense problems, a_trans = 0: the kernel for few rows (gemm_skinny.hip)
+  int few_rows = 0;                       // MFMA kernel, a_trans = 0: the kernel for few rows (gemm_skinny.hip)
+  int stream = 0;                         // few_rows, group_mode 1: the one for weights that come from memory (gemm_experts.hip)
   // set by the MFMA launcher: XCD-aware placement of the tiles (0 = plain 2-D grid), tile counts of the problem
   int xcd_m = 0, tiles_m = 0, tiles_n = 0;
 };
@@ -185,10 +186,14 @@ int launch_gemm_mfma(const GemmArgs& g, GemmTypes t, hipStream_t s);
 // When a dense layer of N outputs goes there, for a call of T tokens (a rule on the call and the layer, never on how many
 // rows or problems one launch stacks: the kernels add in different orders, and results that are promised to be the same
 // bits may come from launches of T or 2 T rows).  A step at the Qwen shape, us, with the line at 384, 512 and 640 tiles:
-//   256 tokens (2048 outputs: 512 tiles): 1690, 1604, 1605    320, adapters only (640 tiles): 1350, 1353, 1381
-//   400 (1024 outputs: 416 tiles): 1805, 1769, 1772           a 512-wide block of 1536 tokens (768): 603 at 512, 636 at 800
-inline bool gemm_few_rows(i64 T, i64 N) { return ((T + 31) / 32) * ((N + 31) / 32) <= 512; }
+//   320, adapters only (640 tiles): 1350, 1353, 1381          400 (1024 outputs: 416 tiles): 1805, 1769, 1772
+//   a 512-wide block of 1536 tokens (768): 603 at 512, 636 at 800       1024 wide, 400 tokens (416): 476, 461, -
+// Layers 2048 wide and more leave at 384: what runs beside them there is the experts' stream of weights, and the tile kernels wait
+// for less of what it holds up.  Line at 256, 384, 512: 160 tokens (320 tiles) 1113, 1119, 1120   200 (448) 1151, 1146, 1182
+//   240 (512) 1165, 1163, 1242   4096 wide, 100 tokens (512) 2557, 2558, 2590
+inline bool gemm_few_rows(i64 T, i64 N) { return ((T + 31) / 32) * ((N + 31) / 32) <= (N >= 2048 ? 384 : 512); }
 void launch_gemm_skinny(const GemmArgs& g, int out_f32, hipStream_t s);
+void launch_gemm_experts(const GemmArgs& g, hipStream_t s);      // (bf16 results, rows from list a)
 
 // Weight gradients of several dense layers, C_i[M_i,N_i] = A_i^T . B_i with A_i [K_i, M_i], B_i [K_i, N_i] row-major
 // (bf16 operands, bf16 or float32 results), as one launch.  Returns 1 (nothing launched) if a problem does not meet

@@ -184,6 +184,18 @@ def test_block_parity_weights_past_the_caches(S):
     _backward_checks(case, x1d, x2d, y1d, TOL["bf16"])
 
 
+# The kernel for expert weights that come from memory: 3 rows per expert and weights that stay in the caches; the most rows it is
+# given (16 on average: some experts end inside their row tile, some take two); a row or two and k past 2048 in every layout.
+# Widths and contractions end inside a tile of 64 columns, of 32 gate columns and a piece of 64 k's.
+@pytest.mark.parametrize("E,k,I,S", [(64, 2, 600, 100), (64, 2, 600, 512), (60, 3, 1400, 40)])
+def test_block_parity_streamed_experts(E, k, I, S):
+    wl = synth.Workload(f"stream_E{E}", 640, 5, 128, E, k, I, 0, 1, S, "bf16", gain_jitter=0.02, seed=S)
+    case = Case(wl)
+    y1d, y2d, _ = _forward_checks(case, TOL["bf16"], min_same=0.9)
+    x1d, x2d = _inverse_checks(case, y1d, y2d, TOL["bf16"], 1)
+    _backward_checks(case, x1d, x2d, y1d, TOL["bf16"])
+
+
 # The dense layers' weight gradients are one launch, on the tile whose rounds over 256 CUs cost least for all of them
 # together: widths that give 216 tiles of 128x128 (one round of those), 172 of 256x128 (one round, against two of 128x128)
 # and 216 of 256x256 (in phases), each with tiles that end outside the results; 70 tokens: a second, partly filled k-tile.
