@@ -78,6 +78,7 @@ struct revffn_ctx {
   int max_tiles_a, max_tiles_b, max_tiles_c;
   int expert_width = 0;       // width of the routed experts' inputs and outputs: d_model, half of it with merged weights
   int bm_b = 128;             // height of the tiles in list b for the routing in the workspace: 128, or 160 (see expert_rows_b)
+  int bm_c = 256;             // height of the tiles in list c: 256, or 320 (see expert_rows_c)
   int expert_nt = 0, expert_nn = 0;
   bool no_fused_swiglu = false; // REVFFN_NO_FUSED_SWIGLU (tuning aid): SwiGLU as a kernel of its own after the gate/up GEMM
   int expert_tile = 0;        // m-tile height of the MFMA expert GEMMs forced to 128 or 256 (REVFFN_EXPERT_TILE), 0 = by rows per expert
@@ -117,6 +118,7 @@ const int BM_A = 32;    // m-tile height of the generic grouped GEMM
 const int BM_B = 128;   // m-tile heights of the MFMA grouped GEMM (list b is built 160 rows high instead where that
 const int BM_C = 256;   // holds a typical expert, see expert_rows_b)
 const int BM_B_MID = 160;
+const int BM_C_TALL = 320;      // list c where the last tile of an expert may be this high (expert_rows_c)
 
 int check_cfg(const revffn_config* c) {
   if (!c) return REVFFN_ENULL;
@@ -350,7 +352,17 @@ int run_gemm(revffn_ctx* c, GemmArgs g, int ta, int tb, int tc, hipStream_t s) {
       if (c->expert_tile) shape = c->expert_tile == 256 ? 2 : 1;
       const bool forced = shape != 0;
       if (!forced) {
-        if (!g.b_trans) shape = rows > 384 * E ? 4 : 3;
+        if (!g.b_trans) {
+          // Forward: 256 (320) rows in phases where their rounds over the 256 CUs cost less than those of 128x256, a tile of 256
+          // rows (with both phases at work) 1.8 times as much.  128x256 / this, us per launch, gate/up and down: 173 rows 241, 115 /
+          // 220, 102   200: a step 3750 / 3680   273: 285, 151 / 248, 120   347: 306, 160 / 321, 175 (two tiles of which one is
+          // mostly empty; the rule stays)   546: 495, 245 / 436, 206   8 experts of 14336, 175: down 221 / 316 (half the CUs; stays)
+          const i64 mean = (rows + E - 1) / E, cols = ((g.act_half ? 2 * g.act_half : g.N) + 255) / 256;
+          auto rounds = [&](i64 tiles) { return (double)((E * tiles * cols + 255) / 256); };
+          const i64 nt = mean <= c->bm_c ? 1 : (mean - (c->bm_c - BM_C) + BM_C - 1) / BM_C, last = mean - (nt - 1) * BM_C;
+          const double tile = 1.8 * ((nt - 1) + (last > 256 ? 1.25 : last > 128 ? 1.0 : 0.55)) / nt;
+          shape = rows > 152 * E && tile * rounds(nt) < rounds((mean + 127) / 128) ? 4 : 3;
+        }
         else if (rows > 192 * E || (rows > one_tile && g.N % 256 == 0)) shape = 4;
         else shape = rows > one_tile ? 2 : 3;
       }
@@ -382,7 +394,7 @@ int run_gemm(revffn_ctx* c, GemmArgs g, int ta, int tb, int tc, hipStream_t s) {
         // merged 16, 29 tokens 300, 344 / 280, 318; 8 experts of 14336, 8 tokens, the forward layout only / both 2589 / 2629.)
         g.once = rows <= 16 * E && (!g.b_trans || g.K <= 2048) && past;
       } else if (tall) {
-        g.tile_group = c->tg_c; g.tile_m0 = c->tm_c; g.max_tiles = c->max_tiles_c; g.tile_bm = BM_C; g.tile_count = c->tile_cnt + 2;
+        g.tile_group = c->tg_c; g.tile_m0 = c->tm_c; g.max_tiles = c->max_tiles_c; g.tile_bm = c->bm_c; g.tile_count = c->tile_cnt + 2;
         if (c->max_tiles_c < 32768) g.tile_first = c->tf_c;      // (the packed entry holds 15 + 16 bits)
       } else {
         g.tile_group = c->tg_b; g.tile_m0 = c->tm_b; g.max_tiles = c->max_tiles_b; g.tile_bm = c->bm_b; g.tile_count = c->tile_cnt + 1;
@@ -448,7 +460,7 @@ void p_routing(revffn_ctx* c, const void* y1, i64 ld, const float* wrp, const fl
     ps.done(KID_ROUTER);
   }
   TileLists tl{{c->tg_a, c->tg_b, c->tg_c}, {c->tm_a, c->tm_b, c->tm_c}, {c->tf_a, c->tf_b, c->tf_c},
-               {c->max_tiles_a, c->max_tiles_b, c->max_tiles_c}, {BM_A, c->bm_b, BM_C}, c->tile_cnt};
+               {c->max_tiles_a, c->max_tiles_b, c->max_tiles_c}, {BM_A, c->bm_b, BM_C}, c->tile_cnt, {0, 0, c->bm_c - BM_C}};
   ProfScope ps(c, s, 0, (double)T * k * 4 * 3);                    // idx read, row_map and inv_map written
   launch_permute(c->idx, c->blk_cnt, T, k, E, c->counts, c->offsets, c->row_map, c->inv_map, tl, s);
   ps.done(KID_PERMUTE);
@@ -761,6 +773,17 @@ static int expert_rows_b(const revffn_ctx* c, i64 N, i64 E) {
   return (N > ROWS_ONE_TILE * E && N <= 152 * E) ? BM_B_MID : BM_B;
 }
 
+// The same for list c, whose tiles are 256 rows high: where the mean is a little more than a multiple of that, the last tile of
+// an expert takes up to 64 rows more (320), instead of a tile of its own for them that costs more than half of a full one (the
+// results' bits are the same either way).  Us per launch, gate/up, down, dHh, dXg: 8 experts of 14336, 512 rows 1075, 635,
+// 513, 1250 / 910, 418, 517, 834 (320 tiles are two rounds of 256 CUs, 256 one); Qwen shape, 546 rows 464, 227, 245, 415 / 436, 206, 208, 367.
+// A step: 2 x 1024 tokens of the former 9030 -> 8340, 1200 6330 -> 5720, Qwen shape 4096 4860 -> 4645, 4600 5410 -> 5230, 8192 9390 -> 9210.
+static int expert_rows_c(const revffn_ctx* c, i64 N, i64 E) {
+  if (c->expert_tile || c->expert_nt || c->expert_nn) return BM_C;
+  const i64 mean = (N + E - 1) / E, over = mean % BM_C;
+  return mean >= 240 && (over <= 72 || over >= 240) ? BM_C_TALL : BM_C;
+}
+
 // Recomputes n3, Um, routing, GU, Hh, Yp, shared expert and RS at y1.  q_x1 != null: the query side of the attention
 // half at q_x1 (which must not depend on this MoE evaluation) is enqueued beside it and done when s goes on.
 int moe_acts(revffn_ctx* c, const revffn_weights* w, const void* y1, i64 ld, int T, hipStream_t s,
@@ -772,6 +795,7 @@ int moe_acts(revffn_ctx* c, const revffn_weights* w, const void* y1, i64 ld, int
   c->lastT_rows = N;
   c->expert_width = d;
   c->bm_b = expert_rows_b(c, N, E);
+  c->bm_c = expert_rows_c(c, N, E);
   // The norm and the up-projection come first, then one fork: the first query side and the shared expert (which needs Um
   // only) run beside the routing chain and the routed experts, and join where the results are combined.  An edge costs
   // the chain of launches more than the 6 us of the up-projection in front of the routing chain: with the routing chain
@@ -919,6 +943,7 @@ int moe_merged(revffn_ctx* c, const revffn_weights* w, const revffn_merged* m, c
   c->lastT_rows = N;
   c->expert_width = h;
   c->bm_b = expert_rows_b(c, N, E);
+  c->bm_c = expert_rows_c(c, N, E);
   hipStream_t s0 = side(c, s, 0);
   p_rmsnorm_fwd(c, dt, c->sdt, y1, ld, w->norm_m, c->n3, h, T, h, f.rms_eps, s);
   if (Is) {

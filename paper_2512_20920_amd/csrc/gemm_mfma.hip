@@ -44,12 +44,13 @@ __device__ __forceinline__ bool whole_lines(const GemmArgs& g, const void* C, co
 
 // Epilogue of one output tile.  rb, cb: first row (column) of the wave's 32-row (32-column) blocks inside the tile;
 // act_col: with the SwiGLU epilogue, the wave's first gate column inside the tile's BN / 2.
-template <int BM, int BN, bool AT, bool BT, class TC, int TE, int TN>
+// KIND: 0 = whatever the arguments ask for; the routed experts' 320-row tiles, whose registers are short: 1 = plain store only, 2 = SwiGLU only
+template <int BM, int BN, bool AT, bool BT, class TC, int TE, int TN, int KIND = 0>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, TC* C, const void* bias_ptr, int bx, int m0, int m_end,
                                               const int (&rb)[TE], const int (&cb)[TN], int act_col, f32x16 (&acc)[TE][TN]) {
   const int n0 = bx * BN, lane = threadIdx.x & 63;
   // ---- epilogue: lane holds column n = lane & 31 and rows (e>>2)*8 + (lane>>5)*4 + (e&3)
-  if (g.act_half) {
+  if (KIND == 2 || (KIND == 0 && g.act_half)) {
     // gate/up GEMM with the SwiGLU epilogue: this wave's first 32-column block is gate columns, its second the up
     // columns of the same indices.  Both go to C (the backward pass needs them), and silu(gate) * up, from the
     // rounded values, to act_out.
@@ -110,9 +111,10 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, TC* C, const vo
     }
     return;
   }
+  if constexpr (KIND == 2) return;
   const bf16* bias = (const bf16*)bias_ptr;
   const bf16* resid = (const bf16*)g.resid;
-  if (!bias && !g.tap && !resid) {
+  if (KIND == 1 || (!bias && !g.tap && !resid)) {
     // plain store (most projections, data gradients, weight gradients in float32 and those in bf16 that do not leave through
     // LDS, see gemm_tile): no per-element epilogue work
     // the column blocks of one row are stored back to back, so that the 64-byte pieces of a line reach L2 together and
@@ -166,6 +168,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, TC* C, const vo
     }
     return;
   }
+  if constexpr (KIND == 0) {
   // Two phases per 32-column block: every load (bias, residual) and all arithmetic on loaded values
   // first, then nothing but stores.  On this ISA one counter tracks loads and stores, and where a store may or may
   // not have been issued (rows and columns past the problem's edge are masked per lane) the compiler can only wait
@@ -250,6 +253,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, TC* C, const vo
           }
         }
     }
+  }
   }
 }
 
@@ -412,16 +416,22 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const bf16* A, cons
 // (Four phases of 8 MFMAs: 5 % slower, the barriers; all eight waves in step: 25 % slower; one wave per SIMD with 128 x 128
 // outputs, a third less LDS traffic: 6-15 % slower, its loads hold up its own MFMAs.)
 //
+// TE = 5: 320 rows, for an expert's last tile (expert_rows_c): a third phase reads A2 (64 rows, 32 per wave) and multiplies it by
+// the same B, 8 MFMAs more for the half that 64 rows would otherwise be a tile of their own for.  Loads: A2 of k-tile t + 1 in phase 0,
+// A0 B0 B1 of t + 2 in phase 1, A1 of t + 2 in phase 2.  251 to 256 registers, so its kernels have one epilogue each (KIND).
+//
 // What the barriers guarantee (segment n lies between barriers n and n+1; waves 0-3 read fragments of phase p in segment
 // 2p and multiply in 2p+1, waves 4-7 one segment later):
-//  * at the end of a read segment a wave waits for all but its youngest 8 loads, which covers the half tiles that the next
+//  * at the end of a read segment a wave waits for all but its youngest 8 loads (TE = 5: 10, 15, 11 by phase), which covers the half tiles that the next
 //    phase reads; the first reader comes after a barrier that everybody passes after that wait;
 //  * a wave has its fragments in registers when its read segment ends (lgkmcnt(0)), so those of phase p have been read by
 //    everybody before segment 2p+2, and the first load into their half tile is issued in segment 2p+2 (phase p+1) or later.
-template <bool AT, bool BT, class TC>
+template <bool AT, bool BT, class TC, int TE = 4, int KIND = 0>
 __device__ __forceinline__ void gemm_tile_phased(const GemmArgs& g, const bf16* A, const bf16* Bm, TC* C, const void* bias_ptr,
                                                  int bx, int m0, int m_end, int k0, int k_end) {
-  constexpr unsigned HALF = 128 * BK * 2, STAGE = 4 * HALF;       // A0 A1 B0 B1
+  constexpr bool TALL = TE == 5;                     // 320 rows
+  static_assert(TE == 4 || (TALL && !AT), "A2 is laid out rows x k");
+  constexpr unsigned HALF = 128 * BK * 2, STAGE = 4 * HALF + (TALL ? HALF / 2 : 0);       // A0 A1 B0 B1 (A2)
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int n0 = bx * 256;
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -448,6 +458,12 @@ __device__ __forceinline__ void gemm_tile_phased(const GemmArgs& g, const bf16* 
       chunk_source<BT, 128>(pos, r0, lim, ldb_b, k0, 1 << 30, nullptr, 1, &base[2 + h][i], &in);
       if (!in) base[2 + h][i] = OOB;
     }
+  unsigned base2 = OOB;                              // A2: 64 rows, a wave-load per wave
+  if constexpr (TALL) {
+    int in;
+    chunk_source<false, 64>(wv * 64 + lane, m0 + 256, m_end, lda_b, k0, 1 << 30, g.a_gather, g.gather_div, &base2, &in);
+    if (!in) base2 = OOB;
+  }
   const unsigned lds0 = lds_address(smem);
   const unsigned lw = __builtin_amdgcn_readfirstlane(lds0 + (unsigned)wv * 2048u);
   const int kfull = krange / BK;                     // whole k-tiles
@@ -466,9 +482,14 @@ __device__ __forceinline__ void gemm_tile_phased(const GemmArgs& g, const bf16* 
       }
     }
   };
-  f32x16 acc[4][2];
+  auto issue_a2 = [&](int kt) {
+    const int pos = wv * 64 + lane;
+    const bool in = (((pos & 7) ^ ((pos >> 4) & 7)) << 3) < krange - kt * BK;
+    load_lds_b128_s(da, __builtin_amdgcn_readfirstlane(lds0 + (unsigned)(kt & 1) * STAGE + 4 * HALF + (unsigned)wv * 1024u), in ? base2 : OOB, (unsigned)kt * kstep_a);
+  };
+  f32x16 acc[TE][2];
 #pragma unroll
-  for (int i = 0; i < 4; i++)
+  for (int i = 0; i < TE; i++)
 #pragma unroll
     for (int j = 0; j < 2; j++)
 #pragma unroll
@@ -477,10 +498,15 @@ __device__ __forceinline__ void gemm_tile_phased(const GemmArgs& g, const bf16* 
 #pragma unroll
   for (int i = 0; i < 2; i++) fba[i] = frag_base<AT, 128>(wm + i * 32, lane);
   fbb = frag_base<BT, 128>(wn, lane);
+  const int wm2 = (wv >> 2) * 32;
+  const unsigned fba2 = frag_base<false, 64>(wm2, lane);
 
   auto issue3 = [&](int kt) { issue(kt, 0); issue(kt, 2); issue(kt, 3); };
-  issue3(0); issue(0, 1); issue3(1);
-  wait_vmcnt<8>();                                   // A0 B0 B1 of k-tile 0
+  issue3(0); issue(0, 1);
+  if constexpr (TALL) issue_a2(0);
+  issue3(1);
+  if constexpr (TALL) issue(1, 1);
+  wait_vmcnt<TALL ? 11 : 8>();                                   // A0 B0 B1 of k-tile 0
   __builtin_amdgcn_s_barrier();
   if (wv >= 4) __builtin_amdgcn_s_barrier();         // waves 4-7 half a phase behind
   // a tile with no row in its lower half (the last one of an expert, often) does only its loads (out of range, to keep
@@ -501,8 +527,16 @@ __device__ __forceinline__ void gemm_tile_phased(const GemmArgs& g, const bf16* 
 #pragma unroll
           for (int j = 0; j < 2; j++) fb[j][kk] = load_frag<BT, 128>(st + (2 + j) * HALF, fbb, wn, kk, lane);
       }
-      if (p == 0) issue(kt + 1, 1); else issue3(kt + 2);
-      wait_vmcnt<8>();
+      if constexpr (!TALL) {
+        if (p == 0) issue(kt + 1, 1); else issue3(kt + 2);
+        wait_vmcnt<8>();
+      } else if (p == 0) {
+        issue_a2(kt + 1);
+        wait_vmcnt<10>();
+      } else {
+        issue3(kt + 2);
+        wait_vmcnt<15>();
+      }
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_sched_barrier(0);
@@ -521,10 +555,29 @@ __device__ __forceinline__ void gemm_tile_phased(const GemmArgs& g, const bf16* 
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
     }
+    if constexpr (TALL) {                            // phase 2
+#pragma unroll
+      for (int kk = 0; kk < 4; kk++) fa[0][kk] = load_frag<false, 64>(st + 4 * HALF, fba2, wm2, kk, lane);
+      issue(kt + 2, 1);
+      wait_vmcnt<11>();
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+      for (int kk = 0; kk < 4; kk++)
+#pragma unroll
+        for (int j = 0; j < 2; j++) acc[TE - 1][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[0][kk], fb[j][kk], acc[TE - 1][j], 0, 0, 0);
+      __builtin_amdgcn_s_setprio(0);
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+    }
   }
   if (wv < 4) __builtin_amdgcn_s_barrier();
   wait_vmcnt<0>();                                   // the zero-filled loads past the last k-tile
-  int rb[4], cb[2];
+  int rb[TE], cb[2];
+  if constexpr (TALL) rb[TE - 1] = 256 + wm2;
 #pragma unroll
   for (int i = 0; i < 4; i++) rb[i] = (i >> 1) * 128 + wm + (i & 1) * 32;
   cb[0] = wn; cb[1] = 128 + wn;
@@ -553,7 +606,7 @@ __device__ __forceinline__ void gemm_tile_phased(const GemmArgs& g, const bf16* 
       return;
     }
   }
-  gemm_epilogue<256, 256, AT, BT, TC, 4, 2>(g, C, bias_ptr, bx, m0, m_end, rb, cb, wn, acc);
+  gemm_epilogue<TE * 64, 256, AT, BT, TC, TE, 2, KIND>(g, C, bias_ptr, bx, m0, m_end, rb, cb, wn, acc);
 }
 
 template <int BM, int BN, int WGM, bool AT, bool BT, class TC, int NW, int NS, int KB = BK, bool ONCE = false>
@@ -600,6 +653,31 @@ __global__ void __launch_bounds__(NW * 64) gemm_mfma_k(GemmArgs g) {
   }
   if constexpr (NS == PHASED) gemm_tile_phased<AT, BT, TC>(g, A, Bm, C, bias, bx, m0, m_end, k0, k_end);
   else gemm_tile<BM, BN, WGM, AT, BT, TC, NW, NS, TM, KB, ONCE>(g, A, Bm, C, bias, bx, bz, m0, m_end, k0, k_end, rot_seed);
+}
+
+// The routed experts' 256x256 tiles where an expert's last one may have up to 320 rows (list c, expert_rows_c)
+template <bool BT, bool ACT>
+__global__ void __launch_bounds__(512) expert_tall_k(GemmArgs g) {
+  int bx, by, bz = 0;
+  if (!place_tile(1, 1, 0, g.tiles_n, 1, g.tile_count[0], g.tile_first, (int)blockIdx.x, &bx, &by, &bz)) return;
+  const int grp = g.tile_group[by];
+  if (grp < 0) return;
+  const int m0 = g.tile_m0[by], rows_end = g.offsets[grp + 1];
+  const bf16* B = (const bf16*)g.B + (i64)grp * g.b_group_stride;
+  if (rows_end - m0 > 256 && rows_end - m0 <= 320) gemm_tile_phased<false, BT, bf16, 5, ACT ? 2 : 1>(g, (const bf16*)g.A, B, (bf16*)g.C, nullptr, bx, m0, rows_end, 0, g.K);
+  else gemm_tile_phased<false, BT, bf16, 4, ACT ? 2 : 1>(g, (const bf16*)g.A, B, (bf16*)g.C, nullptr, bx, m0, min(rows_end, m0 + 256), 0, g.K);
+}
+template <bool BT, bool ACT>
+static void go_tall(GemmArgs g, hipStream_t s) {
+  g.tiles_n = ACT ? cdiv(g.act_half, 128) : cdiv(g.N, 256);
+  g.tiles_m = g.max_tiles;
+  constexpr size_t smem = 2 * (320 + 256) * BK * 2;
+  static std::atomic<unsigned long long> attr_mask{0};
+  if (attr_needed(attr_mask)) {
+    (void)hipFuncSetAttribute((const void*)expert_tall_k<BT, ACT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    attr_done(attr_mask);
+  }
+  hipLaunchKernelGGL((expert_tall_k<BT, ACT>), dim3(g.tiles_n * g.tiles_m), dim3(512), smem, s, g);
 }
 
 // REVFFN_XCD (tuning aid): 0 = plain 2-D grids, tiles land on the XCDs round-robin
@@ -840,7 +918,7 @@ int launch_gemm_mfma(const GemmArgs& g, GemmTypes t, hipStream_t s) {
   if (g.b_trans && (g.N & 7)) return 1;
   if (g.a_trans && !g.b_trans) return 1;                 // layout not used by the block
   if (g.group_mode == 2 && !(g.a_trans && g.b_trans)) return 1;
-  if (g.group_mode == 1 && (g.a_trans || (g.tile_bm != 128 && !(g.few_rows && g.tile_bm == 32 && t.tc == 1) && g.tile_bm != 256 && !(g.tile_bm == 160 && !g.b_trans && g.tile_bn == 256)))) return 1;
+  if (g.group_mode == 1 && (g.a_trans || (g.tile_bm != 128 && !(g.few_rows && g.tile_bm == 32 && t.tc == 1) && g.tile_bm != 256 && !(g.tile_bm == 320 && t.tc == 1) && !(g.tile_bm == 160 && !g.b_trans && g.tile_bn == 256)))) return 1;
   if (g.a_gather && g.a_trans) return 1;
   if (g.group_mode != 1 && g.M <= 0) return 1;
   if (g.n_sub < 1 || g.n_sub > 3 || (g.n_sub > 1 && (g.group_mode != 0 || g.resid || g.tap || g.act_half))) return 1;
@@ -860,6 +938,10 @@ int launch_gemm_mfma(const GemmArgs& g, GemmTypes t, hipStream_t s) {
   const bool f32out = t.tc == 0;
   if (!norm_rope_ok(g, f32out)) return 1;
   if (g.A2 && (!aligned16(g.A2) || !aligned16(g.B2) || !g.b_trans || f32out)) return 1;
+  if (g.group_mode == 1 && g.tile_bm == 320) {
+    if (g.act_half) go_tall<false, true>(g, s); else if (g.b_trans) go_tall<true, false>(g, s); else go_tall<false, false>(g, s);
+    return 0;
+  }
   if (g.few_rows && g.group_mode == 1 && g.stream) { launch_gemm_experts(g, s); return 0; }
   if (g.few_rows && !g.a_trans && !g.force_tile && (g.group_mode == 1 || (g.group_mode == 0 && !g.a_gather))) {
     launch_gemm_skinny(g, f32out, s);

@@ -269,8 +269,9 @@ size_t router_blocks(size_t T);
 // m-tile lists of the grouped GEMMs for three tile heights: list i covers every expert's rows with
 // tiles of bm[i] rows (group[i][t] = expert or -1 for an unused slot, m0[i][t] = first row, first[i][t] = packed
 // (first tile of t's expert) * 65536 + (tiles of that expert), count[i] = tiles in use)
+// slack[i]: the last tile of an expert is up to that many rows higher, where fewer tiles do so
 // count[0..2]: tiles in use of the three lists; count[3]: 1 if the rows are spread evenly over the experts (place_tile)
-struct TileLists { int* group[3]; int* m0[3]; int* first[3]; int max_tiles[3]; int bm[3]; int* count; };
+struct TileLists { int* group[3]; int* m0[3]; int* first[3]; int max_tiles[3]; int bm[3]; int* count; int slack[3]; };
 // counts/offsets/row_map/inv_map and the tile lists
 void launch_permute(const int* idx, const int* blk_cnt, int T, int k, int E, int* counts, int* offsets, int* row_map, int* inv_map,
                     const TileLists& tl, hipStream_t s);

@@ -250,11 +250,9 @@ __global__ void __launch_bounds__(PERM_WAVES * 64) permute_k(
     // Waves 0-2 write one tile list each, wave 3 the evenness flag, the others counts and offsets.
     if (wv < 3) {
       // tile lists: expert e owns the slots after the tiles of experts 0..e-1; slots past the last tile are marked
-      // unused.  The number of tiles of an expert is an exact division: the fill loop below writes ceil(rows / bm)
-      // slots per expert, and a count taken any other way (a shift, for a height that is not a power of two) would
-      // leave slots of the list unwritten, with whatever the workspace held, for the GEMM to use as an expert index.
+      // unused.  Every slot of the list is written: the fill loop runs over the count that the slots were numbered by.
       const int pass = wv;
-      const int bm = tl.bm[pass], mx = tl.max_tiles[pass];
+      const int bm = tl.bm[pass], slack = tl.slack[pass], mx = tl.max_tiles[pass];
       int* tg = tl.group[pass];
       int* tm = tl.m0[pass];
       int* tf = tl.first[pass];
@@ -262,11 +260,11 @@ __global__ void __launch_bounds__(PERM_WAVES * 64) permute_k(
       for (int base = 0; base < E; base += 64) {
         const int e = base + lane;
         const int m_lo = e < E ? off[e] : 0, m_hi = e < E ? off[e + 1] : 0;
-        const int mine = (m_hi - m_lo + bm - 1) / bm;
+        const int mine = m_hi > m_lo ? max((m_hi - m_lo - slack + bm - 1) / bm, 1) : 0;
         const int incl = wave_inclusive_scan(mine, lane);
         const int first = total + incl - mine;
         int i = first;
-        for (int m = m_lo; m < m_hi; m += bm, i++)
+        for (int m = m_lo; i < first + mine; m += bm, i++)
           if (i < mx) { tg[i] = e; tm[i] = m; tf[i] = (first << 16) | mine; }
         total += __shfl(incl, 63, WAVE);
       }

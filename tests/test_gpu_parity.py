@@ -171,6 +171,21 @@ def test_block_parity_expert_tiles(E, k, I, B, S):
     _backward_checks(case, x1d, x2d, y1d, TOL["bf16"])
 
 
+# An expert's last tile of 256 rows takes up to 64 rows more.  Every expert has all T rows (top-k of all): a whole tile, one row more,
+# the most one tile takes, one more than that, two tiles of which the last is a tall one; gate/up widths that give the forward
+# kernel enough tiles, ending inside one, and k that ends inside a k-tile.
+@pytest.mark.parametrize("T", [256, 257, 320, 321, 570])
+def test_block_parity_tall_expert_tiles(T):
+    wl = synth.Workload(f"tall_{T}", 256, 2, 128, 16, 16, 2024, 0, 1, T, "bf16", gain_jitter=0.02, seed=T)
+    case = Case(wl)
+    y1d, y2d = case.forward()
+    _, mo = case.branches()
+    cm, _, idx = check_routing(case, Hn.download(y1d))
+    ref, _ = O.moe_half_forward(Hn.download(y1d), case.W, case.ocfg, forced_idx=idx)
+    assert relerr(mo, ref) < TOL["bf16"]
+    _backward_checks(case, case.up(case.x1), case.up(case.x2), y1d, TOL["bf16"])
+
+
 # More expert weights than the memory-side cache holds: weights and gradients go past the caches, in the kernel for few rows (40
 # tokens, 2 rows per expert) and on 128x256 tiles (300 tokens; 2140: 107 rows per expert), with widths that end inside the tiles
 @pytest.mark.parametrize("S", [40, 300, 2140])
