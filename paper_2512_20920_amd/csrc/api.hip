@@ -65,6 +65,7 @@ struct revffn_ctx {
   bool use_streams = true;
   bool par = false;           // this call spreads independent branches over the helper streams (see fork_pays)
   int lastT = 0;
+  bool small = false;         // this call is too small for helper streams, whatever the switches say (see fork_pays)
   i64 call_T = 0;             // tokens of the current call
   int lastT_rows = 0;         // lastT * top_k: permuted rows of the current routing
   // attention half
@@ -311,19 +312,84 @@ bool experts_pass_through(const revffn_ctx* c, i64 rows) {
   return 3.0 * (double)(rows < f.n_experts ? rows : f.n_experts) * f.d_expert * c->expert_width * c->es >= (double)(1 << 28);
 }
 
+// the most row tiles of 32 that `rows` rows of E experts make
+i64 row_tiles32(i64 rows, i64 E) { return rows < rows / 32 + E ? rows : rows / 32 + E; }
+// Which kernel takes a GEMM of the routed experts (of N outputs, a contraction of K) for `rows` permuted rows: 0 one of the tile
+// kernels, 1 the one for few rows (gemm_skinny.hip), 2 the one for weights that come from memory (gemm_experts.hip)
+int experts_kernel(const revffn_ctx* c, i64 rows, i64 N, i64 K, bool b_trans) {
+  const i64 E = c->cfg.n_experts;
+  // Small problems are latency: 32x32 tiles with k cut among the waves, up to about as many as the chip holds at once.
+  // Measured, us per pass: a 512-wide block of 12 experts, 400 tokens (294 to 784 tiles) 420 -> 392, 1536 tokens (at most 936
+  // of 2496: 595 -> 585; all of them 597); 256 wide, 15 experts, 753 tokens, k = 256: 872 tiles 460 -> 448, 1308 -> 440.
+  // One token of merged Qwen weights (352) 199 -> 153.
+  const i64 tiles32 = row_tiles32(rows, E) * ((N + 31) / 32);
+  const bool past = experts_pass_through(c, rows);
+  // (A row or two per expert, and weights that stay in the caches: merged, 4 tokens 170, in the kernel below 180.)
+  if (tiles32 <= (K <= 256 ? 1600 : 1000) || (!past && rows <= 2 * E && K <= 4096 && tiles32 <= 6000)) return 1;
+  // Above that, as long as nearly every expert fits in one row tile: see gemm_experts.hip.  Old / new, us per pass at the Qwen
+  // shape: 16 tokens 925 / 895, 64 1050 / 993, 128 1105 / 1067, 240 (16 rows) 1284 / 1240, merged 37 tokens 323 / 294, 200 378 / 350;
+  // 8 experts of 14336, 64 tokens 2416 / 2317, 80 (20 rows) 2505 / 2575 (experts of two tiles are read twice); 260 tokens
+  // 1240 / 1337 (its workgroups leave no room for the shared expert's larger tiles beside them).  Data gradients with k long (dXg)
+  // are faster on 128x256 tiles, whose lines are 512 bytes: 64 tokens 108 / 116 us, unless an expert has a row or two:
+  // 20 tokens 101 / 93.
+  if (rows <= 16 * E && (!b_trans || K <= 2048 || (rows <= 2 * E && K <= 4096))) return 2;
+  return 0;
+}
+
+// Whether the shared expert's GEMM `d` goes into the launch of the routed experts' one `g`.  In calls that the kernels for few rows take,
+// a launch of its own is its place in the chain or, on a helper stream, a fork and a join of it, 13 us.
+bool rides(const revffn_ctx* c, const GemmArgs& g, const GemmArgs& d) {
+  if (c->dt != 1 || c->mode != 0 || c->expert_tile || c->expert_nt || c->expert_nn) return false;
+  if (!experts_kernel(c, c->lastT_rows, g.N, g.K, g.b_trans)) return false;
+  auto ok = [&](const GemmArgs& x) {                 // what launch_gemm_mfma asks for
+    return !(((uintptr_t)x.A | (uintptr_t)x.B) & 15) && !((x.lda | x.ldb | x.K) & 7) && (!x.b_trans || !(x.N & 7)) && !(x.b_group_stride & 7) &&
+           x.M * x.lda < (i64)1 << 30 && (x.b_trans ? x.K : x.N) * x.ldb < (i64)1 << 30;
+  };
+  return ok(g) && ok(d);
+}
+
+// the dense problem that came along with the routed experts' (GemmDense), as a launch of its own
+GemmArgs alone(const GemmDense& d, int b_trans) {
+  GemmArgs g;
+  g.A = d.A; g.lda = d.lda; g.B = d.B; g.ldb = d.ldb; g.C = d.C; g.ldc = d.ldc; g.M = d.M; g.N = d.N; g.K = d.K; g.b_trans = b_trans;
+  g.act_out = d.act_out; g.ldact = g.act_half = d.act_half;
+  g.dact_gu = d.dact_gu; g.dact_out = d.dact_out;
+  return g;
+}
+GemmDense along(const GemmArgs& g) {
+  GemmDense d;
+  d.A = g.A; d.B = g.B; d.C = g.C; d.M = g.M; d.N = g.N; d.K = g.K; d.lda = (int)g.lda; d.ldb = (int)g.ldb; d.ldc = (int)g.ldc;
+  d.act_out = g.act_out; d.act_half = g.act_half;
+  d.dact_gu = g.dact_gu; d.dact_out = g.dact_out;
+  return d;
+}
+
 int run_gemm(revffn_ctx* c, GemmArgs g, int ta, int tb, int tc, hipStream_t s) {
   g.few_rows = few_rows(c, g);
   GemmTypes t{ta, tb, tc, c->dt};
   double fl = 0, by = 0;
-  if (c->prof_on) gemm_work(c, g, ta, tb, tc, &fl, &by);
+  if (c->prof_on) {
+    gemm_work(c, g, ta, tb, tc, &fl, &by);
+    if (g.co) {
+      double f1, b1;
+      gemm_work(c, alone(*g.co, g.b_trans), ta, tb, tc, &f1, &b1);
+      fl += f1; by += b1;
+    }
+  }
   ProfScope ps(c, s, fl, by);
   // A gate/up GEMM asks for silu(gate) * up beside its output, a data gradient at that product for the gradients at gate and
   // up instead of its output.  A kernel that cannot do so in its epilogue is followed by one that reads the output back.
   void *act_out = g.act_out, *dact_out = g.dact_out;
   const int act_half = g.act_half;
   const i64 out_rows = g.group_mode == 1 ? c->lastT_rows : g.M;
-  if (c->no_fused_swiglu) { g.act_out = nullptr; g.act_half = 0; g.dact_out = nullptr; }
+  GemmDense co;
+  if (g.co) co = *g.co;
+  const GemmDense co_asked = co;
+  if (c->no_fused_swiglu) { g.act_out = co.act_out = nullptr; g.act_half = co.act_half = 0; g.dact_out = co.dact_out = nullptr; }
+  if (g.co) g.co = &co;
   auto swiglu_after = [&]() {
+    if (co_asked.act_half && !co.act_half) launch_swiglu_fwd(c->dt, co.C, co_asked.act_out, co.M, co_asked.act_half, s);
+    if (co_asked.dact_out && !co.dact_out) launch_swiglu_bwd(c->dt, co.C, co.dact_gu, co_asked.dact_out, co.M, co.N, s);
     if (act_half && !g.act_half) launch_swiglu_fwd(c->dt, g.C, act_out, out_rows, act_half, s);
     if (dact_out && !g.dact_out) {
       ProfScope q(c, s, 0, 5.0 * out_rows * g.N * c->es);
@@ -366,29 +432,16 @@ int run_gemm(revffn_ctx* c, GemmArgs g, int ta, int tb, int tc, hipStream_t s) {
         else if (rows > 192 * E || (rows > one_tile && g.N % 256 == 0)) shape = 4;
         else shape = rows > one_tile ? 2 : 3;
       }
-      // Small problems are latency: 32x32 tiles with k cut among the waves, up to about as many as the chip holds at once.
-      // Measured, us per pass: a 512-wide block of 12 experts, 400 tokens (294 to 784 tiles) 420 -> 392, 1536 tokens (at most 936
-      // of 2496: 595 -> 585; all of them 597); 256 wide, 15 experts, 753 tokens, k = 256: 872 tiles 460 -> 448, 1308 -> 440.
-      // One token of merged Qwen weights (352) 199 -> 153.
-      const i64 low = rows < rows / 32 + E ? rows : rows / 32 + E;          // row tiles, at most
-      const i64 tiles32 = low * ((g.N + 31) / 32);
-      // (A row or two per expert, and weights that stay in the caches: merged, 4 tokens 170, in the kernel below 180.)
-      const bool small = tiles32 <= (g.K <= 256 ? 1600 : 1000) || (!past && rows <= 2 * E && g.K <= 4096 && tiles32 <= 6000);
-      // Above that, as long as nearly every expert fits in one row tile: see gemm_experts.hip.  Old / new, us per pass at the Qwen
-      // shape: 16 tokens 925 / 895, 64 1050 / 993, 128 1105 / 1067, 240 (16 rows) 1284 / 1240, merged 37 tokens 323 / 294, 200 378 / 350;
-      // 8 experts of 14336, 64 tokens 2416 / 2317, 80 (20 rows) 2505 / 2575 (experts of two tiles are read twice); 260 tokens
-      // 1240 / 1337 (its workgroups leave no room for the shared expert's larger tiles beside them).  Data gradients with k long (dXg)
-      // are faster on 128x256 tiles, whose lines are 512 bytes: 64 tokens 108 / 116 us, unless an expert has a row or two:
-      // 20 tokens 101 / 93.
-      g.stream = !small && rows <= 16 * E && (!g.b_trans || g.K <= 2048 || (rows <= 2 * E && g.K <= 4096));
-      g.few_rows = !forced && (small || g.stream);
+      const int few = forced ? 0 : experts_kernel(c, rows, g.N, g.K, g.b_trans);
+      g.few_rows = few != 0;
+      g.stream = few == 2;
       bool tall = shape == 2 || shape == 4;
       g.tile_bn = shape >= 3 ? 256 : 128;
       const bool mid = c->bm_b == BM_B_MID;              // list b holds 160-row tiles: for the 160x256 forward kernel only
       if (mid && !tall) { if (g.b_trans) tall = true; else g.tile_bn = 256; }
       if (tall && g.b_trans && shape != 4) g.tile_bn = 128;
       if (g.few_rows) {
-        g.tile_group = c->tg_a; g.tile_m0 = c->tm_a; g.max_tiles = (int)low; g.tile_bm = BM_A; g.tile_count = c->tile_cnt; g.tile_first = c->tf_a;
+        g.tile_group = c->tg_a; g.tile_m0 = c->tm_a; g.max_tiles = (int)row_tiles32(rows, E); g.tile_bm = BM_A; g.tile_count = c->tile_cnt; g.tile_first = c->tf_a;
         // (Weights past the caches, see GemmArgs::once; with k as the slow index a line belongs to two tiles, which does not pay
         // where k is long.  Through / past, us: 8, 16, 25 tokens at the Qwen shape 862, 1005, 1107 / 816, 972, 1043;
         // merged 16, 29 tokens 300, 344 / 280, 318; 8 experts of 14336, 8 tokens, the forward layout only / both 2589 / 2629.)
@@ -403,7 +456,7 @@ int run_gemm(revffn_ctx* c, GemmArgs g, int ta, int tb, int tc, hipStream_t s) {
       }
     }
     if (!g.few_rows) g.dact_out = nullptr;
-    if (launch_gemm_mfma(g, t, s) == 0) {
+    if (launch_gemm_mfma(g, t, s) == 0) {                        // (its caller has asked rides() about a problem that comes along)
       if (g.group_mode) ps.done(g.a_trans ? KID_GEMM_TN_EXPERTS : (g.b_trans ? KID_GEMM_NN_EXPERTS : KID_GEMM_NT_EXPERTS));
       else ps.done(g.a_trans ? KID_GEMM_TN : (g.b_trans ? KID_GEMM_NN : KID_GEMM_NT));
       swiglu_after();
@@ -784,51 +837,83 @@ static int expert_rows_c(const revffn_ctx* c, i64 N, i64 E) {
   return mean >= 240 && (over <= 72 || over >= 240) ? BM_C_TALL : BM_C;
 }
 
+// the geometry of the routing that an evaluation of the MoE half is about to make; width: of the routed experts' inputs and outputs
+void moe_begin(revffn_ctx* c, int T, int width) {
+  c->lastT = T;
+  c->lastT_rows = T * c->cfg.top_k;
+  c->expert_width = width;
+  c->bm_b = expert_rows_b(c, c->lastT_rows, c->cfg.n_experts);
+  c->bm_c = expert_rows_c(c, c->lastT_rows, c->cfg.n_experts);
+}
+
+// The four GEMMs of the MoE half on inputs and outputs `width` wide (d_model; half of it with merged weights)
+void moe_gemms(revffn_ctx* c, const void* w_gu, const void* w_dn, const void* ws_gu, const void* ws_dn, const void* in, int width, int T,
+               GemmArgs* g1, GemmArgs* g2, GemmArgs* gs, GemmArgs* gd) {
+  const revffn_config& f = c->cfg;
+  const int E = f.n_experts, k = f.top_k, I = f.d_expert, Is = f.d_shared, N = T * k;
+  *g1 = nt(in, width, w_gu, width, c->GU, 2 * I, N, 2 * I, width);
+  g1->group_mode = 1; g1->n_groups = E; g1->offsets = c->offsets; g1->b_group_stride = (i64)2 * I * width;
+  g1->a_gather = c->row_map; g1->gather_div = k;
+  g1->act_out = c->Hh; g1->ldact = I; g1->act_half = I;          // Hh = silu(gate) * up with the GEMM
+  *g2 = nt(c->Hh, I, w_dn, I, c->Yp, width, N, width, I);
+  g2->group_mode = 1; g2->n_groups = E; g2->offsets = c->offsets; g2->b_group_stride = (i64)width * I;
+  if (!Is) return;
+  *gs = nt(in, width, ws_gu, width, c->GUs, 2 * Is, T, 2 * Is, width);
+  gs->act_out = c->Hs; gs->ldact = Is; gs->act_half = Is;        // Hs = silu(gate) * up with the GEMM
+  gs->bulk = c->par;                                  // beside the routed experts' GEMMs
+  *gd = nt(c->Hs, Is, ws_dn, Is, c->Ys, width, T, width, Is);
+  gd->bulk = gs->bulk;
+}
+// Which of the shared expert's forward GEMMs go along with the routed experts': both, or where the call has one stream anyway
+// either.  Not in training steps that have helper streams, where the first query side shares the fork and larger tiles run beside the
+// routing chain: with them along, 64 tokens at the Qwen shape 992 -> 1007 us, 128 1067 -> 1105, 160 1118 -> 1156.
+// A 512-wide block, 400 tokens, 323 -> 298 us (the backward's two as well); merged Qwen weights, 1 token 145 -> 125, 37 295 -> 274, 240 353 -> 351.
+struct Riders { bool gate_up = false, down = false; GemmDense d1, d2; bool both() const { return gate_up && down; } };
+Riders riders(const revffn_ctx* c, const GemmArgs& g1, const GemmArgs& g2, const GemmArgs& gs, const GemmArgs& gd) {
+  Riders r;
+  const bool merged = c->expert_width != c->cfg.d_model;
+  if (!c->cfg.d_shared || (!c->small && !merged)) return r;
+  r.gate_up = rides(c, g1, gs);
+  r.down = rides(c, g2, gd);
+  if (!c->small && !r.both()) r.gate_up = r.down = false;
+  r.d1 = along(gs);
+  r.d2 = along(gd);
+  return r;
+}
+
 // Recomputes n3, Um, routing, GU, Hh, Yp, shared expert and RS at y1.  q_x1 != null: the query side of the attention
 // half at q_x1 (which must not depend on this MoE evaluation) is enqueued beside it and done when s goes on.
 int moe_acts(revffn_ctx* c, const revffn_weights* w, const void* y1, i64 ld, int T, hipStream_t s,
              const void* q_x1 = nullptr, i64 q_ld = 0, int qB = 0, int qS = 0, const unsigned char* q_skip = nullptr) {
   const revffn_config& f = c->cfg;
-  const int d = f.d_model, h = d / 2, E = f.n_experts, k = f.top_k, I = f.d_expert, Is = f.d_shared, dt = c->dt;
-  const int N = T * k;
-  c->lastT = T;
-  c->lastT_rows = N;
-  c->expert_width = d;
-  c->bm_b = expert_rows_b(c, N, E);
-  c->bm_c = expert_rows_c(c, N, E);
-  // The norm and the up-projection come first, then one fork: the first query side and the shared expert (which needs Um
-  // only) run beside the routing chain and the routed experts, and join where the results are combined.  An edge costs
+  const int d = f.d_model, k = f.top_k, Is = f.d_shared, dt = c->dt;
+  moe_begin(c, T, d);
+  // The norm and the up-projection come first, then one fork (if there is work for it): the first query side and the shared expert
+  // (which needs Um only) run beside the routing chain and the routed experts, and join where the results are combined.  An edge costs
   // the chain of launches more than the 6 us of the up-projection in front of the routing chain: with the routing chain
   // on a helper stream instead (two forks, two joins) a step of 128 tokens took 1412 us, now 1391; 300 tokens 1646 and
   // 1628, 4 x 512 2831 and 2809, four blocks of 1024 8421 and 8358; 20, 3000, 8192 tokens and few large experts within 1 %.
   const NormUp nu{y1, ld, w->norm_m, c->n3, c->Um, c->dn3};
   TRY(norm_up(c, &nu, 1, w->pup_m, T, s));
+  // routed experts: GU = Xg . Wgu_e^T (rows gathered from Um through row_map), SwiGLU, Yp = Hh . Wd_e^T
+  GemmArgs g1, g2, gs, gd;
+  moe_gemms(c, w->w_gate_up, w->w_down, w->ws_gate_up, w->ws_down, c->Um, d, T, &g1, &g2, &gs, &gd);
+  const Riders ride = riders(c, g1, g2, gs, gd);
+  if (ride.gate_up) g1.co = &ride.d1;
+  if (ride.down) g2.co = &ride.d2;
+  const bool forks = q_x1 || (Is && !ride.both());
   hipStream_t s0 = side(c, s, 0);
-  if (q_x1 || Is) after(c, s, s0);
+  if (forks) after(c, s, s0);
   if (q_x1) TRY(attn_q(c, w, q_x1, q_ld, qB, qS, s0, q_skip));
-  if (Is) {
-    GemmArgs gs = nt(c->Um, d, w->ws_gate_up, d, c->GUs, 2 * Is, T, 2 * Is, d);
-    gs.act_out = c->Hs; gs.ldact = Is; gs.act_half = Is;      // Hs = silu(gate) * up with the GEMM
-    gs.bulk = c->par;                                 // beside the routed experts' GEMMs
-    TRY(run_gemm(c, gs, s0));
-    GemmArgs gd = nt(c->Hs, Is, w->ws_down, Is, c->Ys, d, T, d, Is);
-    gd.bulk = gs.bulk;
-    TRY(run_gemm(c, gd, s0));
-  }
+  if (Is && !ride.gate_up) TRY(run_gemm(c, gs, s0));
+  if (Is && !ride.down && !ride.gate_up) TRY(run_gemm(c, gd, s0));
   router_fold(c, w, c->wrp, s);
   p_routing(c, y1, ld, c->wrp, w->b_router, T, s);
-  // routed experts: GU = Xg . Wgu_e^T (rows gathered from Um through row_map), SwiGLU, Yp = Hh . Wd_e^T
-  GemmArgs g1 = nt(c->Um, d, w->w_gate_up, d, c->GU, 2 * I, N, 2 * I, d);
-  g1.group_mode = 1; g1.n_groups = E; g1.offsets = c->offsets; g1.b_group_stride = (i64)2 * I * d;
-  g1.a_gather = c->row_map; g1.gather_div = k;
-  g1.act_out = c->Hh; g1.ldact = I; g1.act_half = I;          // Hh = silu(gate) * up with the GEMM
   TRY(run_gemm(c, g1, s));
-  GemmArgs g2 = nt(c->Hh, I, w->w_down, I, c->Yp, d, N, d, I);
-  g2.group_mode = 1; g2.n_groups = E; g2.offsets = c->offsets; g2.b_group_stride = (i64)d * I;
+  if (Is && !ride.down && ride.gate_up) TRY(run_gemm(c, gd, s));
   TRY(run_gemm(c, g2, s));
-  if (q_x1 || Is) after(c, s0, s);
+  if (forks) after(c, s0, s);
   p_combine(c, dt, c->Yp, c->inv_map, c->wts, Is ? c->Ys : nullptr, c->gamma, c->RS, T, d, k, s);
-  c->lastT = T;
   return 0;
 }
 // dst = resid + sign * P_dn_m(RS)     (Eq. 2 and the first line of the inverse)
@@ -937,35 +1022,24 @@ int attn_out_merged(revffn_ctx* c, const revffn_merged* m, const void* resid, i6
 int moe_merged(revffn_ctx* c, const revffn_weights* w, const revffn_merged* m, const void* y1, i64 ld, const void* resid,
                i64 ldr, float sign, void* dst, i64 ldd, int T, hipStream_t s) {
   const revffn_config& f = c->cfg;
-  const int d = f.d_model, h = d / 2, E = f.n_experts, k = f.top_k, I = f.d_expert, Is = f.d_shared, dt = c->dt;
-  const int N = T * k;
-  c->lastT = T;
-  c->lastT_rows = N;
-  c->expert_width = h;
-  c->bm_b = expert_rows_b(c, N, E);
-  c->bm_c = expert_rows_c(c, N, E);
+  const int h = f.d_model / 2, k = f.top_k, Is = f.d_shared, dt = c->dt;
+  moe_begin(c, T, h);
   hipStream_t s0 = side(c, s, 0);
   p_rmsnorm_fwd(c, dt, c->sdt, y1, ld, w->norm_m, c->n3, h, T, h, f.rms_eps, s);
-  if (Is) {
-    after(c, s, s0);
-    GemmArgs gs = nt(c->n3, h, m->ws_gate_up, h, c->GUs, 2 * Is, T, 2 * Is, h);
-    gs.act_out = c->Hs; gs.ldact = Is; gs.act_half = Is;
-    gs.bulk = c->par;
-    TRY(run_gemm(c, gs, s0));
-    GemmArgs gd = nt(c->Hs, Is, m->ws_down, Is, c->Ys, h, T, h, Is);
-    gd.bulk = gs.bulk;
-    TRY(run_gemm(c, gd, s0));
-  }
+  GemmArgs g1, g2, gs, gd;
+  moe_gemms(c, m->w_gate_up, m->w_down, m->ws_gate_up, m->ws_down, c->n3, h, T, &g1, &g2, &gs, &gd);
+  const Riders ride = riders(c, g1, g2, gs, gd);
+  if (ride.gate_up) g1.co = &ride.d1;
+  if (ride.down) g2.co = &ride.d2;
+  const bool forks = Is && !ride.both();
+  if (forks) after(c, s, s0);
+  if (Is && !ride.gate_up) TRY(run_gemm(c, gs, s0));
+  if (Is && !ride.down && !ride.gate_up) TRY(run_gemm(c, gd, s0));
   p_routing(c, y1, ld, m->w_router, w->b_router, T, s);
-  GemmArgs g1 = nt(c->n3, h, m->w_gate_up, h, c->GU, 2 * I, N, 2 * I, h);
-  g1.group_mode = 1; g1.n_groups = E; g1.offsets = c->offsets; g1.b_group_stride = (i64)2 * I * h;
-  g1.a_gather = c->row_map; g1.gather_div = k;
-  g1.act_out = c->Hh; g1.ldact = I; g1.act_half = I;
   TRY(run_gemm(c, g1, s));
-  GemmArgs g2 = nt(c->Hh, I, m->w_down, I, c->Yp, h, N, h, I);
-  g2.group_mode = 1; g2.n_groups = E; g2.offsets = c->offsets; g2.b_group_stride = (i64)h * I;
+  if (Is && !ride.down && ride.gate_up) TRY(run_gemm(c, gd, s));
   TRY(run_gemm(c, g2, s));
-  if (Is) after(c, s0, s);
+  if (forks) after(c, s0, s);
   {
     ProfScope ps(c, s, 0, (double)T * h * esz(dt) * (k + (Is ? 1 : 0)) + 2.0 * T * h * esz(c->sdt));
     launch_combine_couple(dt, c->sdt, c->Yp, c->inv_map, c->wts, Is ? c->Ys : nullptr, c->gamma, resid, ldr, sign, dst, ldd,
@@ -989,7 +1063,8 @@ int check_call(revffn_ctx* c, const revffn_weights* w, int B, int S, i64 ld, dou
   if ((i64)B * S > c->maxT) return REVFFN_ESHAPE;
   if (ld < c->cfg.d_model / 2) return REVFFN_ESHAPE;
   c->call_T = (i64)B * S;
-  c->par = c->use_streams && fork_pays(c, (i64)B * S, fork_line);
+  c->small = !fork_pays(c, (i64)B * S, fork_line);
+  c->par = c->use_streams && !c->small;
   if (!w->norm_a1 || !w->norm_a2 || !w->norm_m || !w->pup_a || !w->pdn_a || !w->pup_m || !w->pdn_m || !w->wq ||
       !w->wk || !w->wv || !w->wo || !w->w_router || !w->w_gate_up || !w->w_down)
     return REVFFN_ENULL;
@@ -1128,12 +1203,25 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
   // the chain, and one more hardware queue (see the streams' creation).  Own stream / sw: 128 tokens 1386 / 1370 us,
   // 3 x 333, adapters only, 1633 / 1626, skewed 2 x 2048 4553 / 4580, four blocks of 1024 8302 / 8255, others within 1 %.
   hipEvent_t shared_done = nullptr;
+  GemmArgs a1 = nn(c->dYp, d, w->w_down, I, c->dHh, I, N, I, d);           // dHh = dYp . Wd_e
+  a1.group_mode = 1; a1.n_groups = E; a1.offsets = c->offsets; a1.b_group_stride = (i64)d * I;
+  a1.dact_gu = c->GU; a1.dact_out = c->dGU;
+  GemmArgs a2 = nn(c->dGU, 2 * I, w->w_gate_up, d, c->dXg, d, N, d, 2 * I);          // dXg = dGU . Wgu_e
+  a2.group_mode = 1; a2.n_groups = E; a2.offsets = c->offsets; a2.b_group_stride = (i64)2 * I * d;
+  GemmDense d1, d2;
   if (Is) {
-    after(c, s, sw);
     GemmArgs dh = nn(c->dYs, d, w->ws_down, Is, c->dHs, Is, T, Is, d);
     dh.dact_gu = c->GUs; dh.dact_out = c->dGUs;
-    TRY(run_gemm(c, dh, sw));
-    TRY(run_gemm(c, nn(c->dGUs, 2 * Is, w->ws_gate_up, d, c->dUm_sh, d, T, d, 2 * Is), sw));
+    const GemmArgs du = nn(c->dGUs, 2 * Is, w->ws_gate_up, d, c->dUm_sh, d, T, d, 2 * Is);
+    d1 = along(dh);
+    d2 = along(du);
+    if (c->small && rides(c, a1, dh)) a1.co = &d1;                         // (see riders)
+    if (a1.co && rides(c, a2, du)) a2.co = &d2;
+    after(c, s, sw);
+    if (!a1.co) {
+      TRY(run_gemm(c, dh, sw));
+      TRY(run_gemm(c, du, sw));
+    }
     if (sw != s) { shared_done = next_sync(c); (void)hipEventRecord(shared_done, sw); }
     if (GF(ws_down)) wg[nwg++] = tn(c->dYs, d, c->Hs, Is, GF(ws_down), Is, d, Is, T);
     if (GF(ws_gate_up)) wg[nwg++] = tn(c->dGUs, 2 * Is, c->Um, d, GF(ws_gate_up), d, 2 * Is, d, T);
@@ -1146,10 +1234,8 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
       b.group_mode = 2; b.n_groups = E; b.offsets = c->offsets; b.tile_count = c->tile_cnt + 3; b.c_group_stride = (i64)d * I;
       TRY(run_wgrad(c, b, sw));
     }
-    GemmArgs a = nn(c->dYp, d, w->w_down, I, c->dHh, I, N, I, d);          // dHh = dYp . Wd_e
-    a.group_mode = 1; a.n_groups = E; a.offsets = c->offsets; a.b_group_stride = (i64)d * I;
-    a.dact_gu = c->GU; a.dact_out = c->dGU;
-    TRY(run_gemm(c, a, s));
+    TRY(run_gemm(c, a1, s));
+    if (a1.co && !a2.co) TRY(run_gemm(c, nn(c->dGUs, 2 * Is, w->ws_gate_up, d, c->dUm_sh, d, T, d, 2 * Is), s));
     if (GF(w_gate_up)) {
       // dWgu_e = dGU_e^T . Xg_e, with the permuted input rows Xg materialised once
       to_sw();
@@ -1158,9 +1244,7 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
       b.group_mode = 2; b.n_groups = E; b.offsets = c->offsets; b.tile_count = c->tile_cnt + 3; b.c_group_stride = (i64)2 * I * d;
       TRY(run_wgrad(c, b, sw));
     }
-    GemmArgs e = nn(c->dGU, 2 * I, w->w_gate_up, d, c->dXg, d, N, d, 2 * I);     // dXg = dGU . Wgu_e
-    e.group_mode = 1; e.n_groups = E; e.offsets = c->offsets; e.b_group_stride = (i64)2 * I * d;
-    TRY(run_gemm(c, e, s));
+    TRY(run_gemm(c, a2, s));
   }
   if (g && g->b_router) add_colsum(cs, 0, c->dzext, E1, 0, nullptr, 0, nullptr, 0, g->b_router, T, E);
   const void* dum_r = nullptr;

@@ -18,24 +18,42 @@
 
 // A piece of a wave: A, then B's two blocks of 32 columns (ACT: 32 gate columns and the up columns of the same indices)
 template <bool BT, bool ACT>
-__global__ void __launch_bounds__(STREAM_WAVES * 64) expert_stream_k(GemmArgs g) {
+__global__ void __launch_bounds__(STREAM_WAVES * 64) expert_stream_k(GemmArgs g, GemmDense d) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  int bx, by, bz = 0;
-  if (!place_tile(1, 1, 0, g.tiles_n, 1, g.tile_count[0], g.tile_first, (int)blockIdx.x, &bx, &by, &bz)) return;
-  const int grp = g.tile_group[by];
-  if (grp < 0) return;
-  const int m0 = g.tile_m0[by], m_end = min(g.offsets[grp + 1], m0 + 32);
-  const int n0 = bx * (ACT ? 32 : 64), ncols = ACT ? g.act_half : g.N;
+  int bx, by, m0, m_end, K = g.K, N = g.N, act_half = g.act_half;
+  i64 lda = g.lda, ldb = g.ldb, ldc = g.ldc, ldact = g.ldact;
+  const bf16 *A = (const bf16*)g.A, *B = (const bf16*)g.B;
+  bf16* C = (bf16*)g.C;
+  const int* gather = g.a_gather;
+  void *act_out = g.act_out, *dact_out = g.dact_out;
+  const void* dact_gu = g.dact_gu;
+  bool once = g.once;
+  if ((int)blockIdx.x < d.blocks) {                  // the dense problem that came along
+    if (!place_dense(d, (int)blockIdx.x, &bx, &by)) return;
+    A = (const bf16*)d.A; B = (const bf16*)d.B; C = (bf16*)d.C;
+    K = d.K; N = d.N; act_half = d.act_half; lda = d.lda; ldb = d.ldb; ldc = d.ldc; ldact = d.act_half;
+    gather = nullptr; act_out = d.act_out; dact_out = d.dact_out; dact_gu = d.dact_gu; once = false;
+    m0 = by * 32; m_end = min(d.M, m0 + 32);
+  } else {
+    int bz = 0;
+    if (!place_tile(1, 1, 0, g.tiles_n, 1, g.tile_count[0], g.tile_first, (int)blockIdx.x - d.blocks, &bx, &by, &bz)) return;
+    const int grp = g.tile_group[by];
+    if (grp < 0) return;
+    m0 = g.tile_m0[by];
+    m_end = min(g.offsets[grp + 1], m0 + 32);
+    B += (i64)grp * g.b_group_stride;
+  }
+  const int n0 = bx * (ACT ? 32 : 64), ncols = ACT ? act_half : N;
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const u32x4 da = make_desc(g.A), db = make_desc((const bf16*)g.B + (i64)grp * g.b_group_stride);
-  const unsigned lda_b = (unsigned)g.lda * 2u, ldb_b = (unsigned)g.ldb * 2u, bstep = BT ? 64u * ldb_b : 128u;
-  const int np = (g.K + 63) >> 6;
+  const u32x4 da = make_desc(A), db = make_desc(B);
+  const unsigned lda_b = (unsigned)lda * 2u, ldb_b = (unsigned)ldb * 2u, bstep = BT ? 64u * ldb_b : 128u;
+  const int np = (K + 63) >> 6;
   // this lane's share of the wave-loads at k = 0; kc: its k relative to the piece (the contraction ends inside the last one)
   unsigned aoff[4], boff[8];
 #pragma unroll
   for (int i = 0; i < 4; i++) {
     int in;
-    chunk_source<false, 32>(i * 64 + lane, m0, m_end, lda_b, 0, 1 << 30, g.a_gather, g.gather_div, &aoff[i], &in);
+    chunk_source<false, 32>(i * 64 + lane, m0, m_end, lda_b, 0, 1 << 30, gather, g.gather_div, &aoff[i], &in);
     if (!in) aoff[i] = OOB;
   }
 #pragma unroll
@@ -48,7 +66,7 @@ __global__ void __launch_bounds__(STREAM_WAVES * 64) expert_stream_k(GemmArgs g)
   const unsigned char* mine = smem + (unsigned)wv * 3 * PIECE;
   const unsigned lds = lds_address(mine);
   auto issue = [&](int p) {                          // (pieces past the end load zeros)
-    const int krem = g.K - p * 64;
+    const int krem = K - p * 64;
 #pragma unroll
     for (int i = 0; i < 4; i++) {
       const int pos = i * 64 + lane, kc = ((pos & 7) ^ ((pos >> 4) & 7)) << 3;
@@ -58,7 +76,7 @@ __global__ void __launch_bounds__(STREAM_WAVES * 64) expert_stream_k(GemmArgs g)
     for (int i = 0; i < 8; i++) {
       const int pos = i * 64 + lane, kc = BT ? pos >> 3 : ((pos & 7) ^ ((pos >> 4) & 7)) << 3;
       const unsigned off = kc < krem && boff[i] != OOB ? boff[i] + (unsigned)p * bstep : OOB;
-      if (g.once) load_lds_b128_once(db, __builtin_amdgcn_readfirstlane(lds + PIECE + i * 1024u), off);
+      if (once) load_lds_b128_once(db, __builtin_amdgcn_readfirstlane(lds + PIECE + i * 1024u), off);
       else load_lds_b128(db, __builtin_amdgcn_readfirstlane(lds + PIECE + i * 1024u), off);
     }
   };
@@ -103,7 +121,6 @@ __global__ void __launch_bounds__(STREAM_WAVES * 64) expert_stream_k(GemmArgs g)
     for (int w = 0; w < STREAM_WAVES; w++) v += part[(w * 32 + r) * 64 + (c ^ ((r & 4) << 3))];
     return v;
   };
-  bf16* C = (bf16*)g.C;
   constexpr int CW = ACT ? 32 : 64;                  // columns that a row of threads shares out
   const int c = (int)threadIdx.x % CW, n = n0 + c;
   if (n >= ncols) return;
@@ -114,17 +131,17 @@ __global__ void __launch_bounds__(STREAM_WAVES * 64) expert_stream_k(GemmArgs g)
     const bf16 x = (bf16)sum(r, c);
     if constexpr (ACT) {                             // silu(gate) * up from the rounded values, as the other kernels
       const bf16 u = (bf16)sum(r, c + 32);
-      C[(i64)m * g.ldc + n] = x;
-      C[(i64)m * g.ldc + ncols + n] = u;
-      ((bf16*)g.act_out)[(i64)m * g.ldact + n] = (bf16)((float)x * sigmoid_f((float)x) * (float)u);
-    } else if (g.dact_out) {                         // SwiGLU's backward, from what C would have held
-      const bf16* gu = (const bf16*)g.dact_gu + (i64)m * 2 * g.N + n;
+      C[(i64)m * ldc + n] = x;
+      C[(i64)m * ldc + ncols + n] = u;
+      ((bf16*)act_out)[(i64)m * ldact + n] = (bf16)((float)x * sigmoid_f((float)x) * (float)u);
+    } else if (dact_out) {                         // SwiGLU's backward, from what C would have held
+      const bf16* gu = (const bf16*)dact_gu + (i64)m * 2 * N + n;
       float dg, du;
-      swiglu_grad((float)x, (float)gu[0], (float)gu[g.N], &dg, &du);
-      bf16* out = (bf16*)g.dact_out + (i64)m * 2 * g.N + n;
+      swiglu_grad((float)x, (float)gu[0], (float)gu[N], &dg, &du);
+      bf16* out = (bf16*)dact_out + (i64)m * 2 * N + n;
       out[0] = (bf16)dg;
-      out[g.N] = (bf16)du;
-    } else C[(i64)m * g.ldc + n] = x;
+      out[N] = (bf16)du;
+    } else C[(i64)m * ldc + n] = x;
   }
 }
 
@@ -133,7 +150,9 @@ static void go(GemmArgs g, hipStream_t s) {
   g.tiles_m = g.max_tiles;
   g.tiles_n = ACT ? cdiv(g.act_half, 32) : cdiv(g.N, 64);
   constexpr size_t smem = STREAM_WAVES * 3 * PIECE;          // (the partial tiles take two thirds of it)
-  hipLaunchKernelGGL((expert_stream_k<BT, ACT>), dim3(g.tiles_n * g.tiles_m), dim3(STREAM_WAVES * 64), smem, s, g);
+  GemmDense d;
+  if (g.co) { d = *g.co; place_dense_grid(d, ACT ? 32 : 64); }
+  hipLaunchKernelGGL((expert_stream_k<BT, ACT>), dim3(d.blocks + g.tiles_n * g.tiles_m), dim3(STREAM_WAVES * 64), smem, s, g, d);
 }
 void launch_gemm_experts(const GemmArgs& g, hipStream_t s) {
   if (g.act_half) go<false, true>(g, s);

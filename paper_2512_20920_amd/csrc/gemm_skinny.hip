@@ -15,6 +15,7 @@
 //    least that 512 bytes can take).
 // Workgroups of one XCD take a run of column tiles with the row tile fastest, so a weight line enters one L2 only.
 #include "lds_load.h"
+#include <type_traits>
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
@@ -24,7 +25,7 @@ typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 // EPI: what goes with the product (EPI_ACT, EPI_ROPE, EPI_NORM, see GemmArgs); NW = waves; NS = pieces of a wave in flight; PAIR: problem 0 has a second pair of operands, its pieces follow the first's
 template <bool BT, class TC, int EPI, int NW, int NS, bool PAIR, bool GRP>
-__global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
+__global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g, std::conditional_t<GRP, GemmDense, char> d) {
   constexpr bool ACT = EPI & EPI_ACT, ROPE = EPI & EPI_ROPE, NORM = EPI & EPI_NORM;
   constexpr int RS = 32 + 8;                         // row stride of a partial tile (floats): rows 4 apart are 32 banks apart
   constexpr unsigned OPD = 64 * 32 * 2, STAGE = 2 * OPD + (NORM ? 256 : 0);     // LDS bytes of a piece: A, B, gains
@@ -33,15 +34,28 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
   const bf16* B = (const bf16*)g.B;
   TC* C = (TC*)g.C;
   const bf16* bias = (const bf16*)g.bias;
-  int bx, by, m0, m_end;
-  if constexpr (GRP) {                               // routed experts: row tiles from the list, 32 high
-    int bz = 0;
-    if (!place_tile(1, 1, 0, g.tiles_n, 1, g.tile_count[0], g.tile_first, (int)blockIdx.x, &bx, &by, &bz)) return;
-    const int grp = g.tile_group[by];
-    if (grp < 0) return;
-    m0 = g.tile_m0[by];
-    m_end = min(g.offsets[grp + 1], m0 + 32);
-    B += (i64)grp * g.b_group_stride;
+  int bx, by, m0, m_end, K = g.K, N = g.N, act_half = g.act_half;
+  i64 lda = g.lda, ldb = g.ldb, ldc = g.ldc, ldact = g.ldact;
+  const int* gather = g.a_gather;
+  void *act_out = g.act_out, *dact_out = g.dact_out;
+  const void* dact_gu = g.dact_gu;
+  bool once = GRP && g.once;
+  if constexpr (GRP) {
+    if ((int)blockIdx.x < d.blocks) {                // the dense problem that came along
+      if (!place_dense(d, (int)blockIdx.x, &bx, &by)) return;
+      A = (const bf16*)d.A; B = (const bf16*)d.B; C = (TC*)d.C;
+      K = d.K; N = d.N; act_half = d.act_half; lda = d.lda; ldb = d.ldb; ldc = d.ldc; ldact = d.act_half;
+      gather = nullptr; act_out = d.act_out; dact_out = d.dact_out; dact_gu = d.dact_gu; once = false;
+      m0 = by * 32; m_end = d.M;
+    } else {                                         // routed experts: row tiles from the list, 32 high
+      int bz = 0;
+      if (!place_tile(1, 1, 0, g.tiles_n, 1, g.tile_count[0], g.tile_first, (int)blockIdx.x - d.blocks, &bx, &by, &bz)) return;
+      const int grp = g.tile_group[by];
+      if (grp < 0) return;
+      m0 = g.tile_m0[by];
+      m_end = min(g.offsets[grp + 1], m0 + 32);
+      B += (i64)grp * g.b_group_stride;
+    }
   } else {
     if (blockIdx.z == 1) { A = (const bf16*)g.subA[0]; B = (const bf16*)g.subB[0]; C = (TC*)g.subC[0]; bias = (const bf16*)g.subBias[0]; }
     if (blockIdx.z == 2) { A = (const bf16*)g.subA[1]; B = (const bf16*)g.subB[1]; C = (TC*)g.subC[1]; bias = (const bf16*)g.subBias[1]; }
@@ -50,7 +64,7 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
     if (bx >= g.tiles_n) return;
     m0 = by * 32; m_end = g.M;
   }
-  const int n0 = bx * (ACT ? 16 : 32), ncols = ACT ? g.act_half : g.N;
+  const int n0 = bx * (ACT ? 16 : 32), ncols = ACT ? act_half : N;
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5;
   if (!GRP && g.row_skip) {                          // every wave looks at all rows of the tile: same answer, no barrier
     const int r = m0 + (lane & 31);
@@ -58,8 +72,8 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
   }
   const bool pair = PAIR && blockIdx.z == 0;
   const u32x4 da = make_desc(A), db = make_desc(B), da2 = make_desc(PAIR ? g.A2 : A), db2 = make_desc(PAIR ? g.B2 : B);
-  const int np1 = (g.K + 63) >> 6, np = pair ? 2 * np1 : np1;
-  const unsigned lda_b = (unsigned)g.lda * 2u, ldb_b = (unsigned)g.ldb * 2u;
+  const int np1 = (K + 63) >> 6, np = pair ? 2 * np1 : np1;
+  const unsigned lda_b = (unsigned)lda * 2u, ldb_b = (unsigned)ldb * 2u;
   // where this lane's share of the four wave-loads of each operand comes from at k = 0, and which k it is (relative to
   // the piece): a load at or past K is out of range, rows and columns past the end repeat the last one or are zeros
   unsigned aoff[4], boff[4];
@@ -69,13 +83,13 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
     const int r = i * 8 + (lane >> 3), ch = (lane & 7) ^ ((r >> 1) & 7);
     akc[i] = ch * 8;
     const int row = min(m0 + r, m_end - 1);
-    aoff[i] = (unsigned)(GRP && g.a_gather ? g.a_gather[row] / g.gather_div : row) * lda_b + (unsigned)ch * 16u;
+    aoff[i] = (unsigned)(GRP && gather ? gather[row] / g.gather_div : row) * lda_b + (unsigned)ch * 16u;
     if constexpr (!BT) {
       const int col = ACT ? (r >> 4) * ncols + min(n0 + (r & 15), ncols - 1) : ROPE ? rope_tile_col(bx, r, g.rope_dh) : min(n0 + r, ncols - 1);
       boff[i] = (unsigned)col * ldb_b + (unsigned)ch * 16u;
     } else {                                         // 16 k's: lane l brings columns (l & 3) * 8 .. + 7 of row l >> 2
       const int col = n0 + (lane & 3) * 8;
-      boff[i] = col < g.N ? (unsigned)(i * 16 + (lane >> 2)) * ldb_b + (unsigned)col * 2u : OOB;
+      boff[i] = col < N ? (unsigned)(i * 16 + (lane >> 2)) * ldb_b + (unsigned)col * 2u : OOB;
     }
   }
   const bf16* gain = NORM ? (const bf16*)(blockIdx.z == 0 ? g.norm_g[0] : blockIdx.z == 1 ? g.norm_g[1] : g.norm_g[2]) : nullptr;
@@ -84,7 +98,7 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
   const unsigned my = (unsigned)wv * NS * STAGE;     // this wave's part of LDS
   const unsigned lds0 = lds_address(smem) + my;
   auto load_b = [&](u32x4 rb, unsigned lds, unsigned off) {
-    if (GRP && g.once) load_lds_b128_once(rb, lds, off);
+    if (once) load_lds_b128_once(rb, lds, off);
     else load_lds_b128(rb, lds, off);
   };
   auto issue = [&](int p, int stage) {
@@ -92,15 +106,15 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
     const int k0 = (second ? p - np1 : p) * 64;
     const u32x4 ra = second ? da2 : da, rb = second ? db2 : db;
     const unsigned dst = lds0 + (unsigned)stage * STAGE;
-    if constexpr (NORM) load_lds_b32(dg, __builtin_amdgcn_readfirstlane(dst + 2 * OPD), k0 + 2 * lane < g.K ? (unsigned)(k0 + 2 * lane) * 2u : OOB);
+    if constexpr (NORM) load_lds_b32(dg, __builtin_amdgcn_readfirstlane(dst + 2 * OPD), k0 + 2 * lane < K ? (unsigned)(k0 + 2 * lane) * 2u : OOB);
 #pragma unroll
     for (int i = 0; i < 4; i++) {
-      const bool in = k0 + akc[i] < g.K;
+      const bool in = k0 + akc[i] < K;
       load_lds_b128(ra, __builtin_amdgcn_readfirstlane(dst + i * 1024u), in ? aoff[i] + (unsigned)k0 * 2u : OOB);
       if constexpr (!BT) {
         load_b(rb, __builtin_amdgcn_readfirstlane(dst + OPD + i * 1024u), in ? boff[i] + (unsigned)k0 * 2u : OOB);
       } else {
-        const bool kin = k0 + i * 16 + (lane >> 2) < g.K && boff[i] != OOB;
+        const bool kin = k0 + i * 16 + (lane >> 2) < K && boff[i] != OOB;
         load_b(rb, __builtin_amdgcn_readfirstlane(dst + OPD + i * 1024u), kin ? boff[i] + (unsigned)k0 * ldb_b : OOB);
       }
     }
@@ -132,7 +146,7 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
     float sum = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; w++) sum += sq[w * 32 + fr];
-    const float rinv = 1.0f / sqrtf(sum / (float)g.K + g.norm_eps);
+    const float rinv = 1.0f / sqrtf(sum / (float)K + g.norm_eps);
 #pragma unroll
     for (int u = 0; u < NS; u++) {
       const unsigned char* t = smem + my + u * STAGE;
@@ -146,7 +160,7 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
 #pragma unroll
         for (int i = 0; i < 8; i++) x[i] = (__bf16)((float)fa[u][s][i] * rinv * (float)gv[i]);
         const int k = p * 64 + s * 16 + half * 8;
-        if (keep && k < g.K) *(bf16x8*)(nout + (i64)(m0 + fr) * g.K + k) = x;
+        if (keep && k < K) *(bf16x8*)(nout + (i64)(m0 + fr) * K + k) = x;
         acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, fb, acc, 0, 0, 0);
       }
     }
@@ -195,22 +209,22 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
     if constexpr (ACT) {                             // silu(gate) * up from the rounded values, as the tile kernel
       const TC x = (TC)v;
       const float own = (float)x, up = __shfl(own, lane | 16, WAVE);
-      C[(i64)m * g.ldc + (col >> 4) * ncols + n] = x;
-      if (col < 16) ((TC*)g.act_out)[(i64)m * g.ldact + n] = (TC)(own * sigmoid_f(own) * up);
+      C[(i64)m * ldc + (col >> 4) * ncols + n] = x;
+      if (col < 16) ((TC*)act_out)[(i64)m * ldact + n] = (TC)(own * sigmoid_f(own) * up);
     } else if constexpr (ROPE) {
       const float own = (float)(TC)(v + (bias ? (float)bias[n] : 0.f));
       const int step = g.rope_dh == 16 ? 8 : 16, i = n & (g.rope_dh / 2 - 1);
       const float other = __shfl_xor(own, step, WAVE);
       const bool turn = (g.rope_mask >> blockIdx.z) & 1;
       const float2 cs = turn ? ((const float2*)g.rope_cs)[(i64)(m % g.rope_S) * (g.rope_dh / 2) + i] : make_float2(1.f, 0.f);
-      C[(i64)m * g.ldc + n] = (TC)(turn ? rope_value(own, other, col & step, cs) : own);
-    } else if (g.dact_out) {                         // SwiGLU's backward, from what C would have held
-      const bf16* gu = (const bf16*)g.dact_gu + (i64)m * 2 * g.N + n;
+      C[(i64)m * ldc + n] = (TC)(turn ? rope_value(own, other, col & step, cs) : own);
+    } else if (dact_out) {                         // SwiGLU's backward, from what C would have held
+      const bf16* gu = (const bf16*)dact_gu + (i64)m * 2 * N + n;
       float dg, du;
-      swiglu_grad((float)(TC)v, (float)gu[0], (float)gu[g.N], &dg, &du);
-      TC* out = (TC*)g.dact_out + (i64)m * 2 * g.N + n;
+      swiglu_grad((float)(TC)v, (float)gu[0], (float)gu[N], &dg, &du);
+      TC* out = (TC*)dact_out + (i64)m * 2 * N + n;
       out[0] = (TC)dg;
-      out[g.N] = (TC)du;
+      out[N] = (TC)du;
     } else {
       float o = v + (bias ? (float)bias[n] : 0.f);
       if (g.tap) g.tap[(i64)m * g.ldtap + n] = o;
@@ -218,7 +232,7 @@ __global__ void __launch_bounds__(NW * 64) gemm_skinny_k(GemmArgs g) {
         const i64 at = (i64)m * g.ldr + n;
         o = (g.resid_f32 ? ((const float*)g.resid)[at] : (float)((const bf16*)g.resid)[at]) + g.resid_sign * o;
       }
-      C[(i64)m * g.ldc + n] = (TC)o;
+      C[(i64)m * ldc + n] = (TC)o;
     }
   }
 }
@@ -235,7 +249,13 @@ static void go(GemmArgs g, hipStream_t s) {
     (void)hipFuncSetAttribute((const void*)gemm_skinny_k<BT, TC, EPI, NW, NS, PAIR, GRP>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     attr_done(attr_mask);
   }
-  hipLaunchKernelGGL((gemm_skinny_k<BT, TC, EPI, NW, NS, PAIR, GRP>), dim3(GRP ? g.tiles_n * g.tiles_m : 8 * cdiv(g.tiles_n, 8) * g.tiles_m, 1, g.n_sub), dim3(NW * 64), smem, s, g);
+  if constexpr (GRP) {
+    GemmDense d;
+    if (g.co) { d = *g.co; place_dense_grid(d, EPI & EPI_ACT ? 16 : 32); }
+    hipLaunchKernelGGL((gemm_skinny_k<BT, TC, EPI, NW, NS, PAIR, true>), dim3(d.blocks + g.tiles_n * g.tiles_m), dim3(NW * 64), smem, s, g, d);
+  } else {
+    hipLaunchKernelGGL((gemm_skinny_k<BT, TC, EPI, NW, NS, PAIR, false>), dim3(8 * cdiv(g.tiles_n, 8) * g.tiles_m, 1, g.n_sub), dim3(NW * 64), smem, s, g, '\0');
+  }
 }
 
 // Pieces in flight are LDS, and LDS decides how many workgroups share a CU.  Up to 4 pieces there are 4 waves with one each

@@ -18,6 +18,15 @@
 //                 RB + g*b_group_stride.  M is ignored (rows are absolute permuted rows).
 //   group_mode 2: the k range of group g is [offsets[g], offsets[g+1]); C of group g is
 //                 C + g*c_group_stride (written with zeros when the range is empty).
+// A dense problem in a launch of the routed experts' kernels for few rows, of the same layout and epilogue (the shared expert's); its
+// tiles come first in the grid.  M = 0: none
+struct GemmDense {
+  const void *A = nullptr, *B = nullptr; void* C = nullptr;
+  int M = 0, N = 0, K = 0, lda = 0, ldb = 0, ldc = 0;
+  void* act_out = nullptr; int act_half = 0;          // (ldact = act_half)
+  const void* dact_gu = nullptr; void* dact_out = nullptr;
+  int tiles_m = 0, tiles_n = 0, blocks = 0;           // set by the launcher
+};
 struct GemmArgs {
   const void* A = nullptr; const void* B = nullptr; void* C = nullptr;
   int M = 0, N = 0, K = 0;
@@ -82,6 +91,7 @@ struct GemmArgs {
   const unsigned char* row_skip = nullptr;
   int few_rows = 0;                       // MFMA kernel, a_trans = 0: the kernel for few rows (gemm_skinny.hip)
   int stream = 0;                         // few_rows, group_mode 1: the one for weights that come from memory (gemm_experts.hip)
+  const struct GemmDense* co = nullptr;   // group_mode 1, the kernels for few rows: a problem that comes along (host memory)
   // set by the MFMA launcher: XCD-aware placement of the tiles (0 = plain 2-D grid), tile counts of the problem
   int xcd_m = 0, tiles_m = 0, tiles_n = 0;
 };
@@ -161,6 +171,19 @@ inline long long wgrad_grid_x(int xcd_m, int tiles_m, int tiles_n, int n_groups)
 }
 inline int dense_grid_x(int xcd_m, int tiles_m, int tiles_n) {
   return 8 * ((tiles_m + xcd_m - 1) / xcd_m) * ((tiles_n + 8 / xcd_m - 1) / (8 / xcd_m));
+}
+
+// tiles of 32 rows of the dense problem that comes along with the routed experts' (GemmDense): XCDs take runs of column tiles with
+// the row tile fastest; bn: columns per tile (gate columns with the SwiGLU epilogue)
+inline void place_dense_grid(GemmDense& d, int bn) {
+  d.tiles_m = (d.M + 31) / 32;
+  d.tiles_n = ((d.act_half ? d.act_half : d.N) + bn - 1) / bn;
+  d.blocks = 8 * ((d.tiles_n + 7) / 8) * d.tiles_m;
+}
+__host__ __device__ inline bool place_dense(const GemmDense& d, int bid, int* bx, int* by) {
+  const int run = (d.tiles_n + 7) >> 3, loc = bid >> 3, col = loc / d.tiles_m;
+  *bx = (bid & 7) * run + col; *by = loc - col * d.tiles_m;
+  return *bx < d.tiles_n;
 }
 
 // Tiles of the epilogues that pair columns: a 32-column tile holds two blocks of 16 that belong together, `first` and the columns

@@ -160,6 +160,18 @@ def test_block_parity_small_problems(dtype, d, H, E, k, I, Is, B, S):
     _backward_checks(case, x1d, x2d, y1d, tol)
 
 
+# The shared expert's GEMMs in the launches of the routed ones, of other widths and contractions: one of the two only (gate/up too many
+# tiles for the kernel for few rows; down too many), both in calls of one tile and with weights that come from memory
+@pytest.mark.parametrize("d,H,E,k,I,Is,B,S", [(256, 4, 15, 4, 360, 448, 3, 251), (640, 5, 48, 4, 24, 40, 1, 300), (256, 2, 4, 2, 72, 200, 1, 31),
+                                              (256, 2, 128, 1, 264, 104, 1, 300)])
+def test_block_parity_shared_expert_comes_along(d, H, E, k, I, Is, B, S):
+    wl = synth.Workload(f"along_d{d}_E{E}", d, H, d // H, E, k, I, Is, B, S, "bf16", gain_jitter=0.02, seed=d + E)
+    case = Case(wl)
+    y1d, y2d, _ = _forward_checks(case, TOL["bf16"], min_same=0.85)
+    x1d, x2d = _inverse_checks(case, y1d, y2d, TOL["bf16"], 1)
+    _backward_checks(case, x1d, x2d, y1d, TOL["bf16"])
+
+
 # More routed work than the kernel for few rows takes: the tiles of the expert GEMMs with widths and row counts that end inside
 # them, at 50 rows per expert (128x256), 137 (160x256, 256x256, 256x128) and 391 (256x256 throughout); and 4100 tokens
 @pytest.mark.parametrize("E,k,I,B,S", [(24, 2, 600, 2, 300), (12, 3, 600, 2, 274), (6, 3, 440, 3, 261), (4, 2, 200, 20, 205)])
