@@ -337,21 +337,24 @@ __global__ void __launch_bounds__(R == 16 ? 1024 : 512) gemm_f32_k(GemmArgs g) {
 // The weight gradients of several dense layers as one launch, tiles numbered over the problems: alone each is a launch of one
 // to a few hundred workgroups that mostly wait for their loads (ten of them at 400 tokens, d = 512: 95 us, together 48).  The sum is
 // cut as in a launch of its own, so the bits are the same.
+__host__ __device__ inline int batch_waves(int K, int groups) { return f32_k_waves(groups ? (K + groups - 1) / groups : K, 32, 8); }      // (as go())
 template <bool STG>
 __global__ void __launch_bounds__(512) gemm_f32_batch_tn_k(GemmBatch b) {
   typedef const __attribute__((address_space(4))) GemmBatch* KernArg;     // (indexed in the kernel-argument segment)
   const KernArg ka = (KernArg)__builtin_amdgcn_kernarg_segment_ptr();
   int i = 0;
   while (i + 1 < ka->n && (int)blockIdx.x >= ka->p[i + 1].tile0) i++;
-  const int local = (int)blockIdx.x - ka->p[i].tile0, by = local / ka->p[i].tiles_n, bx = local - by * ka->p[i].tiles_n;
+  const int per = ka->p[i].tiles_m * ka->p[i].tiles_n, grp = ((int)blockIdx.x - ka->p[i].tile0) / per;
+  const int local = (int)blockIdx.x - ka->p[i].tile0 - grp * per, by = local / ka->p[i].tiles_n, bx = local - by * ka->p[i].tiles_n;
   GemmArgs g;
   g.M = ka->p[i].M; g.N = ka->p[i].N; g.K = ka->p[i].K;
   g.lda = ka->p[i].lda; g.ldb = ka->p[i].ldb; g.ldc = ka->p[i].ldc;
   const float *A = (const float*)ka->p[i].A, *B = (const float*)ka->p[i].B;
-  float* C = (float*)ka->p[i].C;
-  const int nw = f32_k_waves(g.K, 32, 8);
-  if constexpr (STG) f32_tile_staged<true, true, 0>(g, A, B, C, nullptr, by * 32, g.M, bx * 32, 0, g.K, nw, nullptr, nullptr);
-  else f32_tile<float, float, float, float, true, true, 32, 1, 1, false>(g, A, B, C, nullptr, by * 32, g.M, bx * 32, 0, g.K, nw, nullptr, nullptr);
+  float* C = (float*)ka->p[i].C + (i64)grp * ka->p[i].c_stride;
+  const int groups = ka->p[i].groups, nw = batch_waves(g.K, groups);
+  const int k0 = groups ? ka->offsets[grp] : 0, k_end = groups ? ka->offsets[grp + 1] : g.K;
+  if constexpr (STG) f32_tile_staged<true, true, 0>(g, A, B, C, nullptr, by * 32, g.M, bx * 32, k0, k_end, nw, nullptr, nullptr);
+  else f32_tile<float, float, float, float, true, true, 32, 1, 1, false>(g, A, B, C, nullptr, by * 32, g.M, bx * 32, k0, k_end, nw, nullptr, nullptr);
 }
 
 template <class TA, class TB, class TC, class TS, bool AT, bool BT, int R, int TM, int TN, int EPI = 0, bool STG = false>
@@ -456,8 +459,8 @@ int launch_gemm_f32_batch_tn(GemmBatch& b, hipStream_t s) {
   for (int i = 0; i < b.n; i++) {
     GemmProb& p = b.p[i];
     p.tile0 = b.total; p.tiles_m = cdiv(p.M, 32); p.tiles_n = cdiv(p.N, 32);
-    b.total += p.tiles_m * p.tiles_n;
-    const int w = f32_k_waves(p.K, 32, 8);
+    b.total += p.tiles_m * p.tiles_n * (p.groups ? p.groups : 1);
+    const int w = batch_waves(p.K, p.groups);
     if (w > nw) nw = w;
   }
   if (b.total <= 0) return 0;

@@ -846,20 +846,25 @@ __global__ void __launch_bounds__(NW * 64) gemm_batch_tn_k(GemmBatch b) {
   const int total = ka->total, n = ka->n;
   const int c = (int)blockIdx.x & 7, loc = (int)blockIdx.x >> 3, q = total >> 3, r = total & 7;
   if (loc >= q + (c < r ? 1 : 0)) return;
-  const int id = c * q + (c < r ? c : r) + loc;
+  // (with experts among the problems, whose contractions are a fraction as long, a run each would leave XCDs idle: round-robin)
+  const int id = ka->spread ? (int)blockIdx.x : c * q + (c < r ? c : r) + loc;
+  if (id >= total) return;
   int i = 0;
   while (i + 1 < n && id >= ka->p[i + 1].tile0) i++;
   const int tm = ka->p[i].tiles_m, tn = ka->p[i].tiles_n;
-  const int local = id - ka->p[i].tile0, band = local / (4 * tn), rem = local - band * 4 * tn;
+  const int per = tm * tn, grp = (id - ka->p[i].tile0) / per;
+  const int local = id - ka->p[i].tile0 - grp * per, band = local / (4 * tn), rem = local - band * 4 * tn;
   const int bh = tm - band * 4 < 4 ? tm - band * 4 : 4;
   const int bx = rem / bh, by = band * 4 + rem - bx * bh;
   GemmArgs g;
   g.M = ka->p[i].M; g.N = ka->p[i].N; g.K = ka->p[i].K;
   g.lda = ka->p[i].lda; g.ldb = ka->p[i].ldb; g.ldc = ka->p[i].ldc;
   const bf16 *A = (const bf16*)ka->p[i].A, *B = (const bf16*)ka->p[i].B;
-  TC* C = (TC*)ka->p[i].C;
-  if constexpr (NS == PHASED) gemm_tile_phased<true, true, TC>(g, A, B, C, nullptr, bx, by * BM, g.M, 0, g.K);
-  else gemm_tile<BM, BN, WGM, true, true, TC, NW, NS, BM / WGM / 32, KB>(g, A, B, C, nullptr, bx, 0, by * BM, g.M, 0, g.K, 0);
+  TC* C = (TC*)ka->p[i].C + (i64)grp * ka->p[i].c_stride;
+  const bool grouped = ka->p[i].groups > 0;
+  const int k0 = grouped ? ka->offsets[grp] : 0, k_end = grouped ? ka->offsets[grp + 1] : g.K;
+  if constexpr (NS == PHASED) gemm_tile_phased<true, true, TC>(g, A, B, C, nullptr, bx, by * BM, g.M, k0, k_end);
+  else gemm_tile<BM, BN, WGM, true, true, TC, NW, NS, BM / WGM / 32, KB>(g, A, B, C, nullptr, bx, 0, by * BM, g.M, k0, k_end, 0);
 }
 template <int BM, int BN, int WGM, class TC, int NW, int NS, int KB = BK>
 static void go_batch(GemmBatch& b, hipStream_t s) {
@@ -867,7 +872,7 @@ static void go_batch(GemmBatch& b, hipStream_t s) {
   for (int i = 0; i < b.n; i++) {
     GemmProb& p = b.p[i];
     p.tile0 = b.total; p.tiles_m = cdiv(p.M, BM); p.tiles_n = cdiv(p.N, BN);
-    b.total += p.tiles_m * p.tiles_n;
+    b.total += p.tiles_m * p.tiles_n * (p.groups ? p.groups : 1);
   }
   constexpr size_t smem = (size_t)(NS == PHASED ? 2 : NS) * (BM + BN) * KB * 2;
   static std::atomic<unsigned long long> attr_mask{0};
@@ -882,15 +887,20 @@ static void go_batch(GemmBatch& b, hipStream_t s) {
 template <class TC> static void pick_batch_tile(GemmBatch& b, bool bulk, hipStream_t s) {
   // the same costs per tile as for a single problem (pick_tile), over the tiles of all problems
   double t64 = 0, t128 = 0, t256x128 = 0, t256 = 0;
+  bool experts = false;
   for (int i = 0; i < b.n; i++) {
-    t64 += (double)cdiv(b.p[i].M, 128) * cdiv(b.p[i].N, 64);
-    t128 += (double)cdiv(b.p[i].M, 128) * cdiv(b.p[i].N, 128);
-    t256x128 += (double)cdiv(b.p[i].M, 256) * cdiv(b.p[i].N, 128);
-    t256 += (double)cdiv(b.p[i].M, 256) * cdiv(b.p[i].N, 256);
+    experts = experts || b.p[i].groups;
+    const double n = b.p[i].groups ? b.p[i].groups : 1;
+    t64 += n * cdiv(b.p[i].M, 128) * cdiv(b.p[i].N, 64);
+    t128 += n * cdiv(b.p[i].M, 128) * cdiv(b.p[i].N, 128);
+    t256x128 += n * cdiv(b.p[i].M, 256) * cdiv(b.p[i].N, 128);
+    t256 += n * cdiv(b.p[i].M, 256) * cdiv(b.p[i].N, 256);
   }
   auto rounds = [&](double t) { return bulk && t256 >= 128 ? t / 256.0 : ceil(t / 256.0); };
   const double c2 = rounds(t128), c3 = 1.85 * rounds(t256x128), c4 = 2.6 * rounds(t256);
-  if (c4 < c2 && c4 < c3) go_batch<256, 256, 2, TC, 8, PHASED>(b, s);
+  b.spread = experts;
+  if (experts) go_batch<128, 64, 4, TC, 8, 3>(b, s);                   // (what they take alone at these sizes, see pick_tile)
+  else if (c4 < c2 && c4 < c3) go_batch<256, 256, 2, TC, 8, PHASED>(b, s);
   else if (c3 < c2) go_batch<256, 128, 4, TC, 8, 3>(b, s);
   else if (t128 >= 200) go_batch<128, 128, 4, TC, 8, 4>(b, s);
   else go_batch<128, 64, 4, TC, 8, 3>(b, s);
@@ -961,7 +971,7 @@ int launch_gemm_mfma(const GemmArgs& g, GemmTypes t, hipStream_t s) {
 int launch_gemm_batch_tn(GemmBatch& b, int out_f32, int bulk, hipStream_t s) {
   for (int i = 0; i < b.n; i++) {
     const GemmProb& p = b.p[i];
-    if (!aligned16(p.A) || !aligned16(p.B) || (p.lda & 7) || (p.ldb & 7) || (p.M & 7) || (p.N & 7) || p.M <= 0) return 1;
+    if (!aligned16(p.A) || !aligned16(p.B) || (p.lda & 7) || (p.ldb & 7) || (p.M & 7) || (p.N & 7) || (p.c_stride & 7) || p.M <= 0) return 1;
     if ((i64)p.K * p.lda >= (i64)1 << 30 || (i64)p.K * p.ldb >= (i64)1 << 30) return 1;
   }
   if (b.n == 0) return 0;

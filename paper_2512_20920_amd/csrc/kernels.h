@@ -218,12 +218,12 @@ inline bool gemm_few_rows(i64 T, i64 N) { return ((T + 31) / 32) * ((N + 31) / 3
 void launch_gemm_skinny(const GemmArgs& g, int out_f32, hipStream_t s);
 void launch_gemm_experts(const GemmArgs& g, hipStream_t s);      // (bf16 results, rows from list a)
 
-// Weight gradients of several dense layers, C_i[M_i,N_i] = A_i^T . B_i with A_i [K_i, M_i], B_i [K_i, N_i] row-major
-// (bf16 operands, bf16 or float32 results), as one launch.  Returns 1 (nothing launched) if a problem does not meet
-// the matrix-core kernel's alignment rules.
+// Weight gradients of several layers, C_i[M_i,N_i] = A_i^T . B_i with A_i [K_i, M_i], B_i [K_i, N_i] row-major
+// (bf16 operands, bf16 or float32 results), as one launch.  groups > 0: a grouped layer (group_mode 2, GemmBatch::offsets), result
+// of expert e at C + e c_stride.  Returns 1 (nothing launched) if a problem does not meet the matrix-core kernel's alignment rules.
 #define GEMM_BATCH 12
-struct GemmProb { const void *A, *B; void* C; int M, N, K, lda, ldb, ldc; int tile0, tiles_m, tiles_n; };
-struct GemmBatch { int n = 0, total = 0; GemmProb p[GEMM_BATCH]; };
+struct GemmProb { const void *A, *B; void* C; int M, N, K, lda, ldb, ldc; int tile0, tiles_m, tiles_n; int groups = 0; i64 c_stride = 0; };
+struct GemmBatch { int n = 0, total = 0, spread = 0; const int* offsets = nullptr; GemmProb p[GEMM_BATCH]; };
 int launch_gemm_batch_tn(GemmBatch& b, int out_f32, int bulk, hipStream_t s);
 
 // the same for float32 operands and results

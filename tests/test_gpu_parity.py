@@ -161,9 +161,10 @@ def test_block_parity_small_problems(dtype, d, H, E, k, I, Is, B, S):
 
 
 # The shared expert's GEMMs in the launches of the routed ones, of other widths and contractions: one of the two only (gate/up too many
-# tiles for the kernel for few rows; down too many), both in calls of one tile and with weights that come from memory
+# tiles for the kernel for few rows; down too many), both in calls of one tile and with weights that come from memory.  And the experts'
+# weight gradients in the launch of the dense layers', with experts that have no rows.
 @pytest.mark.parametrize("d,H,E,k,I,Is,B,S", [(256, 4, 15, 4, 360, 448, 3, 251), (640, 5, 48, 4, 24, 40, 1, 300), (256, 2, 4, 2, 72, 200, 1, 31),
-                                              (256, 2, 128, 1, 264, 104, 1, 300)])
+                                              (256, 2, 128, 1, 264, 104, 1, 300), (256, 2, 16, 1, 264, 104, 1, 9)])
 def test_block_parity_shared_expert_comes_along(d, H, E, k, I, Is, B, S):
     wl = synth.Workload(f"along_d{d}_E{E}", d, H, d // H, E, k, I, Is, B, S, "bf16", gain_jitter=0.02, seed=d + E)
     case = Case(wl)
