@@ -29,8 +29,8 @@ struct Carver {            // hands out 256-byte aligned slices of one allocatio
 // HBM) are kept apart from the dense GEMMs of the same operand layout (bound by the matrix cores).
 enum { KID_GEMM_NT = 0, KID_GEMM_NN, KID_GEMM_TN, KID_GEMM_GENERIC, KID_ATTN_FWD_FLASH, KID_ATTN_BWD_FLASH,
        KID_ATTN_FWD_GENERIC, KID_ATTN_BWD_GENERIC, KID_GEMM_NT_EXPERTS, KID_GEMM_NN_EXPERTS, KID_GEMM_TN_EXPERTS,
-       // the memory-bound kernels: algorithmic bytes only (every input read once, every output written once; the family
-       // router_bwd is part of moe_bwd_rows now and keeps its place in the list)
+       // the memory-bound kernels: algorithmic bytes only (every input read once, every output written once; the families
+       // router_bwd and gather_rows are part of moe_bwd_rows now and keep their places in the list)
        KID_RMSNORM_FWD, KID_RMSNORM_BWD, KID_ROPE, KID_ROUTER, KID_PERMUTE, KID_COMBINE, KID_MOE_BWD_ROWS,
        KID_ROUTER_BWD, KID_DUM_FINALIZE, KID_SWIGLU_BWD, KID_COLSUM, KID_GATHER_ROWS, KID_COPY_ROWS,
        KID_COUNT };
@@ -526,10 +526,10 @@ void p_combine(revffn_ctx* c, int dt, const void* yp, const int* inv_map, const 
 }
 void p_moe_bwd_rows(revffn_ctx* c, int dt, const void* drs, const void* yp, const void* ys, const int* inv_map,
                     const float* wts, const float* gamma, void* dyp, void* dys, float* dzext, int T, int d,
-                    int k, int E1, int has_gate, const RouterBwd& r, const RowCopy& copy, hipStream_t s) {
-  ProfScope ps(c, s, 0, (double)T * d * esz(dt) * (1 + 2 * k + (has_gate ? 2 : 0)) + 2.0 * (copy.rows_a + copy.rows_b) * d * esz(dt) +
+                    int k, int E1, int has_gate, const RouterBwd& r, const RowCopy& copy, const RowGather& gather, hipStream_t s) {
+  ProfScope ps(c, s, 0, (double)T * d * esz(dt) * (1 + 2 * k + (has_gate ? 2 : 0)) + 2.0 * (copy.rows_a + copy.rows_b) * d * esz(dt) + (gather.um ? (double)T * d * esz(dt) * (1 + k) : 0.0) +
                         (double)T * (r.E * 8.0 + k * 12.0 + (r.dzb ? r.E1p * 2.0 : 0.0)));
-  launch_moe_bwd_rows(dt, drs, yp, ys, inv_map, wts, gamma, dyp, dys, dzext, T, d, k, E1, has_gate, r, copy, s);
+  launch_moe_bwd_rows(dt, drs, yp, ys, inv_map, wts, gamma, dyp, dys, dzext, T, d, k, E1, has_gate, r, copy, gather, s);
   ps.done(KID_MOE_BWD_ROWS);
 }
 void p_dum_finalize(revffn_ctx* c, int dt, const void* dxg, const int* inv_map, const void* dum_sh, const void* dum_r,
@@ -552,12 +552,6 @@ void p_colsum_batch(revffn_ctx* c, ColsumBatch& q, hipStream_t s) {
   ProfScope ps(c, s, 0, by);
   launch_colsum_batch(q, c->partial, c->ticket, s);
   ps.done(KID_COLSUM);
-}
-void p_gather_rows(revffn_ctx* c, int dt, const void* src, const int* row_map, int div, void* dst, int rows, int cols,
-                   hipStream_t s) {
-  ProfScope ps(c, s, 0, 2.0 * rows * cols * esz(dt) + rows * 4.0);
-  launch_gather_rows(dt, src, row_map, div, dst, rows, cols, s);
-  ps.done(KID_GATHER_ROWS);
 }
 void p_copy_rows(revffn_ctx* c, int dt, const void* src, i64 lds_, void* dst, i64 ldd, int rows, int cols, hipStream_t s) {
   ProfScope ps(c, s, 0, 2.0 * rows * cols * esz(dt));
@@ -1204,8 +1198,10 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
   const bool dz_bf16 = dt == 1 && c->mode == 0;
   const int E1p = (E1 + 7) / 8 * 8;
   const RouterBwd rb{c->probs, c->idx, E, f.norm_topk_prob, dz_bf16 ? c->dzb : nullptr, E1p};
+  // Xg, the permuted rows of Um: for the gate/up weight gradient
+  const RowGather rg{GF(w_gate_up) ? c->Um : nullptr, c->Xg};
   const RowCopy rc{w->w_router, Is ? w->ws_gate : w->w_router, c->wr_ext, dz_bf16 ? E : 0, dz_bf16 && Is ? 1 : 0};
-  p_moe_bwd_rows(c, dt, c->dRS, c->Yp, c->Ys, c->inv_map, c->wts, c->gamma, c->dYp, c->dYs, c->dzext, T, d, k, E1, Is ? 1 : 0, rb, rc, s);
+  p_moe_bwd_rows(c, dt, c->dRS, c->Yp, c->Ys, c->inv_map, c->wts, c->gamma, c->dYp, c->dYs, c->dzext, T, d, k, E1, Is ? 1 : 0, rb, rc, rg, s);
   // The shared expert's data gradients go in front of the weight gradients on sw: a stream of their own is one more edge in
   // the chain, and one more hardware queue (see the streams' creation).  Own stream / sw: 128 tokens 1386 / 1370 us,
   // 3 x 333, adapters only, 1633 / 1626, skewed 2 x 2048 4553 / 4580, four blocks of 1024 8302 / 8255, others within 1 %.
@@ -1245,9 +1241,8 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
     TRY(run_gemm(c, a1, s));
     if (a1.co && !a2.co) TRY(run_gemm(c, nn(c->dGUs, 2 * Is, w->ws_gate_up, d, c->dUm_sh, d, T, d, 2 * Is), s));
     if (GF(w_gate_up)) {
-      // dWgu_e = dGU_e^T . Xg_e, with the permuted input rows Xg materialised once
+      // dWgu_e = dGU_e^T . Xg_e
       to_sw();
-      p_gather_rows(c, dt, c->Um, c->row_map, k, c->Xg, N, d, sw);
       GemmArgs b = tn(c->dGU, 2 * I, c->Xg, d, GF(w_gate_up), d, 2 * I, d, N);
       b.group_mode = 2; b.n_groups = E; b.offsets = c->offsets; b.tile_count = c->tile_cnt + 3; b.c_group_stride = (i64)2 * I * d;
       if (batched) wg[nwg++] = b;

@@ -443,23 +443,8 @@ void launch_swiglu_bwd(int dt, const void* dhh, const void* gu, void* dgu, i64 r
 }
 
 // ---------------------------------------------------------------------------------
-// Row gather (dst[r] = src[row_map[r] / div]) and strided row copy.
+// Strided row copy.
 // ---------------------------------------------------------------------------------
-template <class T>
-__global__ void __launch_bounds__(256) gather_rows_k(const T* __restrict__ src, const int* __restrict__ row_map,
-                                                     int div, T* __restrict__ dst, int rows, int cols) {
-  int r = blockIdx.x;
-  if (r >= rows) return;
-  const T* sp = src + (i64)(row_map[r] / div) * cols;
-  T* dp = dst + (i64)r * cols;
-  for (int c = threadIdx.x; c < cols; c += 256) dp[c] = sp[c];
-}
-void launch_gather_rows(int dt, const void* src, const int* row_map, int div, void* dst, int rows, int cols,
-                        hipStream_t s) {
-  if (rows <= 0) return;
-  DISPATCH_DT(dt, hipLaunchKernelGGL(gather_rows_k<T>, dim3(rows), dim3(256), 0, s, (const T*)src, row_map, div,
-                                     (T*)dst, rows, cols));
-}
 template <class T>
 __global__ void __launch_bounds__(256) copy_rows_k(const T* __restrict__ src, i64 lds_, T* __restrict__ dst, i64 ldd,
                                                    int rows, int cols) {

@@ -255,8 +255,6 @@ void launch_rope(int dt, void* buf, const float* cs_table, int T, int S, int H, 
                  hipStream_t s, void* buf2 = nullptr, const unsigned char* row_skip = nullptr);
 void launch_swiglu_fwd(int dt, const void* gu, void* hh, i64 rows, int I, hipStream_t s);
 void launch_swiglu_bwd(int dt, const void* dhh, const void* gu, void* dgu, i64 rows, int I, hipStream_t s);
-void launch_gather_rows(int dt, const void* src, const int* row_map, int div, void* dst, int rows, int cols,
-                        hipStream_t s);
 void launch_copy_rows(int dt, const void* src, i64 lds_, void* dst, i64 ldd, int rows, int cols, hipStream_t s);
 void launch_zero(int dt, void* p, int n, hipStream_t s);           // n elements of type dt set to zero
 // res[0] = max |a - b| (bitwise max of non-negative floats; res must be zeroed first) ; dst = a
@@ -307,11 +305,13 @@ void launch_combine_couple(int dt, int ts, const void* yp, const int* inv_map, c
 // Backward of the combine and of the routing weights.  copy: rows of width d that the same launch copies to dst, src_a's and
 // then src_b's (the stacked router matrix; rows_a = rows_b = 0: none)
 struct RowCopy { const void *src_a, *src_b; void* dst; int rows_a, rows_b; };
+// gather (um != null): row t of um goes to the k rows of xg that inv_map names
+struct RowGather { const void* um; void* xg; };
 struct RouterBwd { const float* probs; const int* idx; int E, norm_topk; void* dzb; int E1p; };
 // dzext[T, E1]: logit gradients; r.dzb != null: also as bf16 rows of width E1p (zero padded) for the matrix-core GEMMs
 void launch_moe_bwd_rows(int dt, const void* drs, const void* yp, const void* ys, const int* inv_map,
                          const float* wts, const float* gamma, void* dyp, void* dys, float* dzext, int T, int d,
-                         int k, int E1, int has_gate, const RouterBwd& r, const RowCopy& copy, hipStream_t s);
+                         int k, int E1, int has_gate, const RouterBwd& r, const RowCopy& copy, const RowGather& gather, hipStream_t s);
 void launch_dum_finalize(int dt, const void* dxg, const int* inv_map, const void* dum_sh, const void* dum_r,
                          const float* dzext, const void* w_router, const void* ws_gate, void* dum, int T, int d,
                          int k, int E, int E1, hipStream_t s);

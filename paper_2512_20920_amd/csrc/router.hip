@@ -492,6 +492,9 @@ void launch_combine_couple(int dt, int ts, const void* yp, const int* inv_map, c
 //   dz_j   = p_j * ([j selected] dp_j - sum_sel dp_e p_e)        for every expert j
 // (a kernel of its own for the second part, and one that stacks the router rows for the GEMM that follows, were 5 us each of
 // every step at any size: both are latency)
+// gather.um != null: the token's row of Um goes to its experts' rows of gather.xg on the way (the operand of the gate/up weight
+// gradient; as a kernel of its own, which read the row once per slot, 3 us of the chain in small calls, 44 us on a
+// helper stream at 8192 tokens)
 // ---------------------------------------------------------------------------------
 // dz of one token by one wave, lanes over the experts; my_dw: dw of slot `lane`, sgate: dz of the gate logit
 __device__ __forceinline__ void router_bwd_token(const RouterBwd& r, const float* wts, float my_dw, float sgate, float* dzext,
@@ -528,7 +531,7 @@ __global__ void __launch_bounds__(256) moe_bwd_rows_k(const T* __restrict__ drs,
                                                       const float* __restrict__ wts, const float* __restrict__ gamma,
                                                       T* __restrict__ dyp, T* __restrict__ dys,
                                                       float* __restrict__ dzext, int Tn, int d, int k, int E1, int has_gate,
-                                                      RouterBwd r, RowCopy copy) {
+                                                      RouterBwd r, RowCopy copy, RowGather gather) {
   __shared__ float red[4];
   const int t = blockIdx.x;
   if (t >= Tn) {
@@ -559,6 +562,7 @@ __global__ void __launch_bounds__(256) moe_bwd_rows_k(const T* __restrict__ drs,
       float v = to_f(dr[c]);
       acc += v * to_f(yp[(i64)pos * d + c]);
       dyp[(i64)pos * d + c] = from_f<T>(w * v);
+      if (gather.um) ((T*)gather.xg)[(i64)pos * d + c] = ((const T*)gather.um)[(i64)t * d + c];
     }
     acc = block_sum_256(acc, red);
     if ((int)threadIdx.x == s) my_dw = acc;
@@ -570,7 +574,7 @@ __global__ void __launch_bounds__(256) moe_bwd_rows_v8_k(const bf16* __restrict_
                                                          const float* __restrict__ wts, const float* __restrict__ gamma,
                                                          bf16* __restrict__ dyp, bf16* __restrict__ dys,
                                                          float* __restrict__ dzext, int Tn, int d, int k,
-                                                         int E1, int has_gate, RouterBwd r, RowCopy copy, int copy8) {
+                                                         int E1, int has_gate, RouterBwd r, RowCopy copy, int copy8, RowGather gather) {
   __shared__ float red[4];
   const int t = blockIdx.x;
   if (t >= Tn) {
@@ -607,6 +611,7 @@ __global__ void __launch_bounds__(256) moe_bwd_rows_v8_k(const bf16* __restrict_
 #pragma unroll
       for (int q = 0; q < 8; q++) { acc += (float)v[q] * (float)y[q]; o[q] = (__bf16)(w * (float)v[q]); }
       *(bf16x8_t*)(dyp + (i64)pos * d + c) = o;
+      if (gather.um) *(bf16x8_t*)((bf16*)gather.xg + (i64)pos * d + c) = *(const bf16x8_t*)((const bf16*)gather.um + (i64)t * d + c);
     }
     acc = block_sum_256(acc, red);
     if ((int)threadIdx.x == s) my_dw = acc;
@@ -615,18 +620,18 @@ __global__ void __launch_bounds__(256) moe_bwd_rows_v8_k(const bf16* __restrict_
 }
 void launch_moe_bwd_rows(int dt, const void* drs, const void* yp, const void* ys, const int* inv_map,
                          const float* wts, const float* gamma, void* dyp, void* dys, float* dzext, int Tn, int d,
-                         int k, int E1, int has_gate, const RouterBwd& r, const RowCopy& copy, hipStream_t s) {
+                         int k, int E1, int has_gate, const RouterBwd& r, const RowCopy& copy, const RowGather& gather, hipStream_t s) {
   if (Tn <= 0) return;
   const dim3 grid(Tn + copy.rows_a + copy.rows_b);
-  if (vec8_ok(dt, d, {drs, yp, ys, dyp, dys})) {          // (buffers of the workspace; the copied rows are the caller's weights)
+  if (vec8_ok(dt, d, {drs, yp, ys, dyp, dys, gather.um, gather.xg})) {          // (buffers of the workspace; the copied rows are the caller's weights)
     hipLaunchKernelGGL(moe_bwd_rows_v8_k, grid, dim3(256), 0, s, (const bf16*)drs, (const bf16*)yp, (const bf16*)ys,
                        inv_map, wts, gamma, (bf16*)dyp, (bf16*)dys, dzext, Tn, d, k, E1, has_gate, r, copy,
-                       (int)vec8_ok(dt, d, {copy.src_a, copy.src_b, copy.dst}));
+                       (int)vec8_ok(dt, d, {copy.src_a, copy.src_b, copy.dst}), gather);
     return;
   }
   DISPATCH_DT(dt, hipLaunchKernelGGL(moe_bwd_rows_k<T>, grid, dim3(256), 0, s, (const T*)drs, (const T*)yp,
                                      (const T*)ys, inv_map, wts, gamma, (T*)dyp, (T*)dys, dzext, Tn, d, k, E1,
-                                     has_gate, r, copy));
+                                     has_gate, r, copy, gather));
 }
 
 // ---------------------------------------------------------------------------------
