@@ -2,7 +2,7 @@
 // for the cross-branch attention of Eq. 1: queries from stream 1, keys/values from stream 2.
 //
 // Layout: q,k,v,o,do,dq,dk,dv are [T, H*128] token-major, head hh in columns hh*128...
-// All three kernels work on TRANSPOSED score tiles S^T[key, query] = K Q^T, so that in the
+// All kernels work on TRANSPOSED score tiles S^T[key, query] = K Q^T, so that in the
 // MFMA result layout a lane owns one query (forward, dQ) or one key (dK/dV) column: softmax
 // statistics and accumulator rescaling stay inside a lane, and the probability tile is
 // already in the operand layout of the second product.  The operand that has to be read
@@ -13,36 +13,16 @@
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
-typedef __attribute__((ext_vector_type(8))) short s16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 #define DH 128
 #define BKV 64            // rows of the tile that is streamed through LDS
-#define KST (DH + 8)      // LDS row stride (elements) of a tile read with 16-byte fragment reads
-#define VST (DH + 32)     // LDS row stride of a tile read with transposing reads
-#define BST (DH + 24)     // LDS row stride of a tile read both ways (backward: K; Q and dO): 76 dwords, i.e. rows 12
-                          // banks apart, so that 16 rows x 16 bytes and 4 rows x 32 bytes both fall on distinct banks
 #define LOG2E 1.4426950408889634f
 #define LN2 0.6931471805599453f
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// 16-byte fragment of a row-major LDS tile: rows r0 + (lane&31), columns kk*16 + (lane>>5)*8 ..
-__device__ __forceinline__ bf16x8 frag_rows(const bf16* lds, int stride, int r0, int kk, int lane) {
-  return *(const bf16x8*)(lds + (r0 + (lane & 31)) * stride + kk * 16 + (lane >> 5) * 8);
-}
-// Transposed fragment for a product whose contraction runs over the tile ROWS: operand row
-// (MFMA row index) = tile column c0 + (lane&31); the 8 contraction slots u = 4*jp + i of half
-// g = lane>>5 are tile rows rb + 8*jp + 4*g + i.  This matches a probability/score tile taken
-// straight from the accumulator layout of a 32x32 MFMA (elements 8c..8c+7 of block c).
-__device__ __forceinline__ bf16x8 frag_cols_tr(const bf16* lds, int stride, int rb, int c0, int lane) {
-  int blk = lane >> 4, i16 = lane & 15;
-  const bf16* p = lds + (rb + 4 * (blk >> 1) + (i16 >> 2)) * stride + c0 + 16 * (blk & 1) + 4 * (i16 & 3);
-  s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
-  s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 8 * stride));
-  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-}
 // elements 8c..8c+7 of an accumulator tile as a bf16 operand fragment
 __device__ __forceinline__ bf16x8 acc_to_frag(const f32x16& a, int c) {
   bf16x8 r;
@@ -51,11 +31,9 @@ __device__ __forceinline__ bf16x8 acc_to_frag(const f32x16& a, int c) {
   return r;
 }
 
-// global [rows, DH] slice (row stride ld) -> registers: 64 rows x 16 chunks of 16 bytes, 4 per thread; rows at or
-// past the sequence end are zero.  The loads are range-checked buffer loads: the descriptor covers the slice of one
-// (batch, head) up to the last byte of row S - 1, so a row past the end is out of range and reads as zeros with no
-// branch and no traffic, the address is one 32-bit offset per lane, and the loads of a tile issue back to back.
-// (Predicated pointer loads put a branch and a full wait after every load and spilled their 64-bit addresses.)
+// Rows of one (batch, head) slice [S, DH], row stride ld.  Tiles of them are brought by range-checked buffer loads: the
+// descriptor ends at the last byte of row S - 1, so a row past the end is out of range and reads as zeros with no branch and
+// no traffic, and the address is one 32-bit offset per lane.
 struct RowSlice { __amdgpu_buffer_rsrc_t rs; unsigned ldb; };    // ldb = row stride in bytes
 __device__ __forceinline__ RowSlice row_slice(const bf16* base, i64 ld, int S) {
   RowSlice r;
@@ -63,307 +41,19 @@ __device__ __forceinline__ RowSlice row_slice(const bf16* base, i64 ld, int S) {
   r.ldb = (unsigned)(ld * 2);
   return r;
 }
-__device__ __forceinline__ void load_rows64(const RowSlice& sl, int row0, uint4 (&r)[4]) {
-#pragma unroll
-  for (int i = 0; i < 4; i++) {
-    const int c = threadIdx.x + 256 * i;
-    const unsigned voff = (unsigned)(row0 + (c >> 4)) * sl.ldb + (unsigned)(c & 15) * 16u;
-    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(sl.rs, (int)voff, 0, 0);
-    r[i] = make_uint4(v[0], v[1], v[2], v[3]);
-  }
-}
-__device__ __forceinline__ void store_rows64(bf16* lds, int stride, const uint4 (&r)[4]) {
-#pragma unroll
-  for (int i = 0; i < 4; i++) {
-    int c = threadIdx.x + 256 * i;
-    *(uint4*)(lds + (c >> 4) * stride + (c & 15) * 8) = r[i];
-  }
-}
 
 // Which tile a workgroup takes (1-D grid of tiles x B x H workgroups; tile 0 has the most work when causal).  Heads are the
 // fastest index, so that an XCD (id & 7) keeps to H / 8 heads, then batches, so that long tiles of all batches come first
 // (a 3-D grid with the batch slowest: 2 x 2048 tokens, 16 heads, forward and dQ 78 and 111 us, 65 and 98 like this).  Two
 // workgroups fit on a CU: where the whole grid is resident at once, workgroups i and i + 256 share one, so the second 256
 // run from short to long (forward, dQ, dK/dV: 65, 98, 137 -> 63, 95, 134).
-__device__ __forceinline__ void place(int H, int B, int tiles, int* t, int* hh, int* b) {
+__device__ __forceinline__ void place(int H, int B, int tiles, int per_cu, int* t, int* hh, int* b) {
   const int rows = tiles * B, first = 256 / H;
   int row = (int)blockIdx.x / H;
   *hh = (int)blockIdx.x - row * H;
-  if ((int)gridDim.x <= 512 && row >= first) row = rows - 1 - (row - first);
+  if (per_cu == 2 && (int)gridDim.x <= 512 && row >= first) row = rows - 1 - (row - first);
   *t = row / B;
   *b = row - *t * B;
-}
-
-// ------------------------------------------------------------------------------------
-// Forward.  Workgroup = 128 queries of one (batch, head); wave = 32 queries; keys/values
-// streamed in tiles of 64.
-// ------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256, 2) flash_fwd_k(const bf16* __restrict__ q, const bf16* __restrict__ k,
-                                                   const bf16* __restrict__ v, bf16* __restrict__ o,
-                                                   float* __restrict__ lse, int B, int S, int H, int causal, float scale,
-                                                   const unsigned char* __restrict__ row_skip) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  bf16* sK = (bf16*)smem_raw;               // 2 stages [64][KST]
-  bf16* sV = sK + 2 * BKV * KST;            // 2 stages [64][VST]
-  int qt, hh, b;
-  place(H, B, (S + 127) / 128, &qt, &hh, &b);
-  qt = (S + 127) / 128 - 1 - qt;            // late query tiles are the long ones
-  if (row_skip) {                           // every query of the tile is a finished row of the inverse's iteration
-    int live = 0;                           // every wave checks all 128 rows of the tile: same answer, no LDS
-    for (int r = qt * 128 + (int)(threadIdx.x & 63); r < min(S, qt * 128 + 128); r += 64) live |= row_skip[(i64)b * S + r] == 0;
-    if (!__any(live)) return;
-  }
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, g = lane >> 5;
-  const i64 ld = (i64)H * DH;
-  const bf16* qb = q + (i64)b * S * ld + hh * DH;
-  const bf16* kb = k + (i64)b * S * ld + hh * DH;
-  const bf16* vb = v + (i64)b * S * ld + hh * DH;
-  const int q0 = qt * 128, qw = q0 + wv * 32;
-  const int myq = qw + (lane & 31);
-  const float sl2 = scale * LOG2E;
-
-  bf16x8 qf[8];
-#pragma unroll
-  for (int kk = 0; kk < 8; kk++) {
-    uint4 t = make_uint4(0, 0, 0, 0);
-    if (myq < S) t = *(const uint4*)(qb + (i64)myq * ld + kk * 16 + g * 8);
-    qf[kk] = __builtin_bit_cast(bf16x8, t);
-  }
-  const int kv_lim = causal ? min(S, q0 + 128) : S;
-  const int nt = (kv_lim + BKV - 1) / BKV;
-
-  f32x16 oacc[4];
-#pragma unroll
-  for (int i = 0; i < 4; i++)
-#pragma unroll
-    for (int e = 0; e < 16; e++) oacc[i][e] = 0.f;
-  float m = -INFINITY, l = 0.f;
-
-  uint4 rk[4], rv[4];
-  const RowSlice slK = row_slice(kb, ld, S), slV = row_slice(vb, ld, S);
-  load_rows64(slK, 0, rk);
-  load_rows64(slV, 0, rv);
-  store_rows64(sK, KST, rk);
-  store_rows64(sV, VST, rv);
-  __syncthreads();
-  for (int t = 0; t < nt; t++) {
-    const int cur = t & 1, kv0 = t * BKV;
-    if (t + 1 < nt) {
-      load_rows64(slK, kv0 + BKV, rk);
-      load_rows64(slV, kv0 + BKV, rv);
-    }
-    const bf16* cK = sK + cur * BKV * KST;
-    const bf16* cV = sV + cur * BKV * VST;
-    if (!causal || kv0 <= qw + 31) {        // this wave has at least one unmasked key in the tile
-      f32x16 sacc[2];
-#pragma unroll
-      for (int j = 0; j < 2; j++)
-#pragma unroll
-        for (int e = 0; e < 16; e++) sacc[j][e] = 0.f;
-#pragma unroll
-      for (int kk = 0; kk < 8; kk++)
-#pragma unroll
-        for (int j = 0; j < 2; j++)
-          sacc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows(cK, KST, j * 32, kk, lane), qf[kk], sacc[j], 0, 0, 0);
-      // scores in the log2 domain; keys past the sequence end or after the query are masked, which
-      // only tiles on the diagonal or at the end of the sequence need
-      const bool need_mask = (kv0 + BKV > S) || (causal && kv0 + BKV - 1 > qw);
-      float mx = -INFINITY;
-      if (need_mask) {
-#pragma unroll
-        for (int j = 0; j < 2; j++)
-#pragma unroll
-          for (int e = 0; e < 16; e++) {
-            int kv = kv0 + j * 32 + (e >> 2) * 8 + g * 4 + (e & 3);
-            float sv = sacc[j][e] * sl2;
-            if (kv >= S || (causal && kv > myq)) sv = -INFINITY;
-            sacc[j][e] = sv;
-            mx = fmaxf(mx, sv);
-          }
-      } else {
-#pragma unroll
-        for (int j = 0; j < 2; j++)
-#pragma unroll
-          for (int e = 0; e < 16; e++) {
-            float sv = sacc[j][e] * sl2;
-            sacc[j][e] = sv;
-            mx = fmaxf(mx, sv);
-          }
-      }
-      mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE));
-      const float mn = fmaxf(m, mx);
-      const float msafe = (mn == -INFINITY) ? 0.f : mn;
-      float rs = 0.f;
-#pragma unroll
-      for (int j = 0; j < 2; j++)
-#pragma unroll
-        for (int e = 0; e < 16; e++) {
-          float p = fast_exp2(sacc[j][e] - msafe);
-          sacc[j][e] = p;
-          rs += p;
-        }
-      rs += __shfl_xor(rs, 32, WAVE);
-      // the running maximum settles after the first tiles: rescale the accumulator only when some
-      // query of this wave actually raised it
-      if (__any(mn > m)) {
-        const float alpha = fast_exp2(m - msafe);
-        l = l * alpha + rs;
-#pragma unroll
-        for (int i = 0; i < 4; i++)
-#pragma unroll
-          for (int e = 0; e < 16; e++) oacc[i][e] *= alpha;
-      } else {
-        l += rs;
-      }
-      m = mn;
-      // O^T[dh, q] += V^T[dh, kv] P^T[kv, q]
-#pragma unroll
-      for (int j = 0; j < 2; j++)
-#pragma unroll
-        for (int c = 0; c < 2; c++) {
-          bf16x8 pf = acc_to_frag(sacc[j], c);
-#pragma unroll
-          for (int dtile = 0; dtile < 4; dtile++)
-            oacc[dtile] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_tr(cV, VST, j * 32 + c * 16, dtile * 32, lane),
-                                                                  pf, oacc[dtile], 0, 0, 0);
-        }
-    }
-    if (t + 1 < nt) {
-      store_rows64(sK + (cur ^ 1) * BKV * KST, KST, rk);
-      store_rows64(sV + (cur ^ 1) * BKV * VST, VST, rv);
-    }
-    __syncthreads();
-  }
-  if (myq < S) {
-    const float inv = 1.0f / l;
-    bf16* op = o + ((i64)b * S + myq) * ld + hh * DH;
-#pragma unroll
-    for (int dtile = 0; dtile < 4; dtile++)
-#pragma unroll
-      for (int jj = 0; jj < 4; jj++) {
-        bf16x4 w;
-#pragma unroll
-        for (int i = 0; i < 4; i++) w[i] = (__bf16)(oacc[dtile][jj * 4 + i] * inv);
-        *(bf16x4*)(op + dtile * 32 + jj * 8 + g * 4) = w;
-      }
-    if (g == 0) lse[((i64)b * H + hh) * S + myq] = (m + __log2f(l)) * LN2;
-  }
-}
-
-// ------------------------------------------------------------------------------------
-// Backward, part 1: dQ.  Workgroup = 128 queries, wave = 32 queries (one per lane column);
-// keys/values streamed in tiles of 64.  Per tile:
-//   S^T = K Q^T,  P^T = exp(S^T*scale - lse),  dP^T = V dO^T,  dS^T = P^T (dP^T - D) scale,
-//   dQ^T += K^T dS^T.
-// ------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256, 2) flash_bwd_dq_k(const bf16* __restrict__ q, const bf16* __restrict__ k,
-                                                      const bf16* __restrict__ v, const bf16* __restrict__ d_o,
-                                                      const float* __restrict__ lse, const float* __restrict__ dvec,
-                                                      bf16* __restrict__ dq, int B, int S, int H, int causal, float scale) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  bf16* sK = (bf16*)smem_raw;               // 2 stages [64][BST]
-  bf16* sV = sK + 2 * BKV * BST;            // 2 stages [64][BST]
-  int qt, hh, b;
-  place(H, B, (S + 127) / 128, &qt, &hh, &b);
-  qt = (S + 127) / 128 - 1 - qt;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, g = lane >> 5;
-  const i64 ld = (i64)H * DH;
-  const i64 boff = (i64)b * S * ld + hh * DH;
-  const int q0 = qt * 128, qw = q0 + wv * 32;
-  const int myq = qw + (lane & 31);
-  const float sl2 = scale * LOG2E;
-
-  bf16x8 qf[8], dof[8];
-#pragma unroll
-  for (int kk = 0; kk < 8; kk++) {
-    uint4 t = make_uint4(0, 0, 0, 0), u = make_uint4(0, 0, 0, 0);
-    if (myq < S) {
-      t = *(const uint4*)(q + boff + (i64)myq * ld + kk * 16 + g * 8);
-      u = *(const uint4*)(d_o + boff + (i64)myq * ld + kk * 16 + g * 8);
-    }
-    qf[kk] = __builtin_bit_cast(bf16x8, t);
-    dof[kk] = __builtin_bit_cast(bf16x8, u);
-  }
-  const float mylse = (myq < S) ? lse[((i64)b * H + hh) * S + myq] * LOG2E : 0.f;
-  const float myD = (myq < S) ? dvec[((i64)b * H + hh) * S + myq] : 0.f;
-  const int kv_lim = causal ? min(S, q0 + 128) : S;
-  const int nt = (kv_lim + BKV - 1) / BKV;
-
-  f32x16 acc[4];
-#pragma unroll
-  for (int i = 0; i < 4; i++)
-#pragma unroll
-    for (int e = 0; e < 16; e++) acc[i][e] = 0.f;
-
-  uint4 rk[4], rv[4];
-  const RowSlice slK = row_slice(k + boff, ld, S), slV = row_slice(v + boff, ld, S);
-  load_rows64(slK, 0, rk);
-  load_rows64(slV, 0, rv);
-  store_rows64(sK, BST, rk);
-  store_rows64(sV, BST, rv);
-  __syncthreads();
-  for (int t = 0; t < nt; t++) {
-    const int cur = t & 1, kv0 = t * BKV;
-    if (t + 1 < nt) {
-      load_rows64(slK, kv0 + BKV, rk);
-      load_rows64(slV, kv0 + BKV, rv);
-    }
-    const bf16* cK = sK + cur * BKV * BST;
-    const bf16* cV = sV + cur * BKV * BST;
-    if (!causal || kv0 <= qw + 31) {
-      f32x16 sacc[2], dpacc[2];
-#pragma unroll
-      for (int j = 0; j < 2; j++)
-#pragma unroll
-        for (int e = 0; e < 16; e++) { sacc[j][e] = 0.f; dpacc[j][e] = 0.f; }
-#pragma unroll
-      for (int kk = 0; kk < 8; kk++)
-#pragma unroll
-        for (int j = 0; j < 2; j++) {
-          sacc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows(cK, BST, j * 32, kk, lane), qf[kk], sacc[j], 0, 0, 0);
-          dpacc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows(cV, BST, j * 32, kk, lane), dof[kk], dpacc[j], 0, 0, 0);
-        }
-      const bool need_mask = (kv0 + BKV > S) || (causal && kv0 + BKV - 1 > qw);
-#pragma unroll
-      for (int j = 0; j < 2; j++)
-#pragma unroll
-        for (int e = 0; e < 16; e++) {
-          float p = fast_exp2(sacc[j][e] * sl2 - mylse);
-          if (need_mask) {
-            int kv = kv0 + j * 32 + (e >> 2) * 8 + g * 4 + (e & 3);
-            if (kv >= S || (causal && kv > myq)) p = 0.f;
-          }
-          sacc[j][e] = p * (dpacc[j][e] - myD) * scale;      // dS^T
-        }
-#pragma unroll
-      for (int j = 0; j < 2; j++)
-#pragma unroll
-        for (int c = 0; c < 2; c++) {
-          bf16x8 dsf = acc_to_frag(sacc[j], c);
-#pragma unroll
-          for (int dtile = 0; dtile < 4; dtile++)
-            acc[dtile] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_tr(cK, BST, j * 32 + c * 16, dtile * 32, lane),
-                                                                 dsf, acc[dtile], 0, 0, 0);
-        }
-    }
-    if (t + 1 < nt) {
-      store_rows64(sK + (cur ^ 1) * BKV * BST, BST, rk);
-      store_rows64(sV + (cur ^ 1) * BKV * BST, BST, rv);
-    }
-    __syncthreads();
-  }
-  if (myq < S) {
-    bf16* op = dq + boff + (i64)myq * ld;
-#pragma unroll
-    for (int dtile = 0; dtile < 4; dtile++)
-#pragma unroll
-      for (int jj = 0; jj < 4; jj++) {
-        bf16x4 w;
-#pragma unroll
-        for (int i = 0; i < 4; i++) w[i] = (__bf16)acc[dtile][jj * 4 + i];
-        *(bf16x4*)(op + dtile * 32 + jj * 8 + g * 4) = w;
-      }
-  }
 }
 
 // ------------------------------------------------------------------------------------
@@ -382,21 +72,466 @@ __device__ __forceinline__ void load_rows16_lds(const RowSlice& sl, int row0, un
     load_lds_b128(sl.rs, __builtin_amdgcn_readfirstlane(dst + i * 1024u), voff);
   }
 }
+// the same with what does not change from tile to tile worked out once
+__device__ __forceinline__ void row_offsets(const RowSlice& sl, int row0, int lane, unsigned (&off)[4]) {
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    const int r = i * 4 + (lane >> 4);
+    off[i] = (unsigned)(row0 + r) * sl.ldb + (unsigned)((lane & 15) ^ swz(r)) * 16u;
+  }
+}
+__device__ __forceinline__ void load_rows16_lds(const RowSlice& sl, const unsigned (&off)[4], int row0, unsigned dst) {
+  const unsigned add = __builtin_amdgcn_readfirstlane((unsigned)row0 * sl.ldb);
+#pragma unroll
+  for (int i = 0; i < 4; i++) load_lds_b128(sl.rs, __builtin_amdgcn_readfirstlane(dst + i * 1024u), off[i] + add);
+}
 // 64 floats
 __device__ __forceinline__ void load_stats64_lds(__amdgpu_buffer_rsrc_t rs, int row0, unsigned dst, int lane) {
   load_lds_b32(rs, __builtin_amdgcn_readfirstlane(dst), (unsigned)(row0 + lane) * 4u);
 }
-// per-lane byte offsets: frag_rows (k-step kk: ^ kk * 32), frag_cols_tr (column block: ^ dtile * 64)
+// per-lane byte offsets: 16-byte fragments of rows lane & 31 (k-step kk: ^ kk * 32), transposed ones (column block: ^ dtile * 64)
 __device__ __forceinline__ unsigned swz_row_base(int lane) { return (unsigned)(lane & 31) * 256u + (unsigned)((lane >> 5) ^ swz(lane & 15)) * 16u; }
 __device__ __forceinline__ unsigned swz_col_base(int lane) {
   const int blk = lane >> 4, i16 = lane & 15, row = 4 * (blk >> 1) + (i16 >> 2), c = 2 * (blk & 1) + ((i16 & 3) >> 1);
   return (unsigned)row * 256u + (unsigned)(c ^ swz(row)) * 16u + (unsigned)(i16 & 1) * 8u;
 }
+// Transposed fragment for a product whose contraction runs over the tile's rows: operand row (MFMA row index) = tile column
+// dtile * 32 + (lane & 31); the 8 contraction slots u = 4 * jp + i of half g = lane >> 5 are tile rows rb + 8 * jp + 4 * g + i.
+// This matches a probability or score tile taken straight from the accumulator layout of a 32x32 MFMA (elements 8c..8c+7).
 __device__ __forceinline__ bf16x8 swz_cols(const unsigned char* tile, unsigned base, int rb, int dtile) {
   const unsigned at = base ^ (unsigned)(dtile * 64);
   s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tile + rb * 256 + at));
   s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tile + rb * 256 + 2048 + (at ^ 32u)));     // rows + 8
   return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// one row of 128 as operand fragments of a product over the head width; rows past the end are zeros
+__device__ __forceinline__ void load_frags(const bf16* base, i64 ld, int row, int S, int g, bf16x8 (&f)[8]) {
+#pragma unroll
+  for (int kk = 0; kk < 8; kk++) {
+    uint4 t = make_uint4(0, 0, 0, 0);
+    if (row < S) t = *(const uint4*)(base + (i64)row * ld + kk * 16 + g * 8);
+    f[kk] = __builtin_bit_cast(bf16x8, t);
+  }
+}
+// the compiler's own wait for fragments just loaded belongs here: inside the loop it would wait for every tile on its way too
+__device__ __forceinline__ void arrived(bf16x8 (&f)[8]) {
+#pragma unroll
+  for (int kk = 0; kk < 8; kk++) asm volatile("" : "+v"(f[kk]));
+}
+
+// ------------------------------------------------------------------------------------
+// Forward.  Workgroup = 128 queries of one (batch, head), wave = 32 queries; keys/values streamed in tiles of 64, straight into
+// LDS, K two tiles ahead and V one.  An iteration is two phases with a barrier behind each.  In the first a wave multiplies:
+// scores of the next tile from key fragments that are in registers already, then P V of this one, the value fragments read 16
+// rows ahead; half of the tile's exponentials go between the former.  In the second it takes the maximum and the other half of
+// the exponentials, and reads the next key fragments meanwhile, so that LDS is busy in both phases.
+// GROUPS = 1: 4 waves, two workgroups on a CU.  GROUPS = 2: two groups of 4 waves with the same queries, group 0 on the even
+// tiles and group 1 on the odd ones, half an iteration apart (one wave of each on a SIMD: one multiplies while the other
+// doesn't); their partial results meet in LDS at the end.  two_groups() has the rule.
+// Bound by the power limit where the grid is large: 8192 tokens, 16 heads, 1.08 PFLOP/s on random values, 1.3 on zeros.
+// Against tiles staged through registers and fragments read just before use, us: 1 x 8192 319 -> 254, 2 x 2048 59 -> 46,
+// 4 x 512 20 -> 16.5, 1 x 4096 105 -> 77, 64 x 128 31.7 -> 31.1.
+// ------------------------------------------------------------------------------------
+#define KV_TILE 16384u                            // 64 rows x 256 bytes, swizzled
+#define FWD_SMEM(GROUPS) ((GROUPS) * 4 * KV_TILE) // two stages of K and V per group; the partial results at the end
+__device__ __forceinline__ void phase_end() {     // reads of this phase have returned, then everybody's
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ float both_halves_max(float x) {       // of lane l and lane l ^ 32
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, x), false, false);
+  return fmaxf(__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1]));
+}
+__device__ __forceinline__ float both_halves_sum(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, x), false, false);
+  return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+}
+// one row of 128, times f
+__device__ __forceinline__ void store_cols(bf16* row, const f32x16 (&acc)[4], float f, int g) {
+#pragma unroll
+  for (int d = 0; d < 4; d++)
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      bf16x4 r;
+#pragma unroll
+      for (int i = 0; i < 4; i++) r[i] = (__bf16)(acc[d][e * 4 + i] * f);
+      *(bf16x4*)(row + d * 32 + e * 8 + g * 4) = r;
+    }
+}
+// acc^T[column, lane] += tile^T p for a tile of 64 rows, the next 16 rows' fragments read while this one's are multiplied; first:
+// the fragments of the first 16 rows
+__device__ __forceinline__ void read_cols(bf16x8 (&f)[4], const unsigned char* tile, unsigned cbase, int c) {
+#pragma unroll
+  for (int dtile = 0; dtile < 4; dtile++) f[dtile] = swz_cols(tile, cbase, c * 16, dtile);
+}
+__device__ __forceinline__ void cols_times64(f32x16 (&acc)[4], const unsigned char* tile, unsigned cbase, const bf16x8 (&p)[4], bf16x8 (&first)[4]) {
+  bf16x8 f[2][4];
+#pragma unroll
+  for (int dtile = 0; dtile < 4; dtile++) f[0][dtile] = first[dtile];
+#pragma unroll
+  for (int c = 0; c < 4; c++) {
+    if (c < 3) read_cols(f[(c + 1) & 1], tile, cbase, c + 1);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int dtile = 0; dtile < 4; dtile++) acc[dtile] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[c & 1][dtile], p[c], acc[dtile], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+template <int GROUPS>
+__global__ void __launch_bounds__(256 * GROUPS, 2) flash_fwd_k(const bf16* __restrict__ q, const bf16* __restrict__ k,
+                                                   const bf16* __restrict__ v, bf16* __restrict__ o,
+                                                   float* __restrict__ lse, int B, int S, int H, int causal, float scale,
+                                                   const unsigned char* __restrict__ row_skip) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
+  int qt, hh, b;
+  place(H, B, (S + 127) / 128, 3 - GROUPS, &qt, &hh, &b);
+  qt = (S + 127) / 128 - 1 - qt;            // late query tiles are the long ones
+  if (row_skip) {                           // every query of the tile is a finished row of the inverse's iteration
+    int live = 0;                           // every wave checks all 128 rows of the tile: same answer, no LDS
+    for (int r = qt * 128 + (int)(threadIdx.x & 63); r < min(S, qt * 128 + 128); r += 64) live |= row_skip[(i64)b * S + r] == 0;
+    if (!__any(live)) return;
+  }
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 5;
+  const int grp = GROUPS == 2 ? wave >> 2 : 0, wv = wave & 3;
+  const i64 ld = (i64)H * DH, boff = (i64)b * S * ld + hh * DH;
+  const int q0 = qt * 128, qw = q0 + wv * 32;
+  const int myq = qw + (lane & 31);
+  const float sl2 = scale * LOG2E;
+  const int nt = ((causal ? min(S, q0 + 128) : S) + BKV - 1) / BKV, ni = (nt + GROUPS - 1) / GROUPS;
+  const int none = S;                               // (a tile that is not there: rows past the end, zeros without traffic)
+
+  bf16x8 qf[8];
+  load_frags(q + boff, ld, myq, S, g, qf);
+  const RowSlice slK = row_slice(k + boff, ld, S), slV = row_slice(v + boff, ld, S);
+  const unsigned char* tiles = smem_raw + (unsigned)grp * 4 * KV_TILE;      // K, V, K, V
+  const unsigned lds0 = lds_address(smem_raw) + (unsigned)grp * 4 * KV_TILE + (unsigned)wv * 4096u;
+  unsigned off[4];
+  row_offsets(slK, wv * 16, lane, off);
+  auto issue = [&](const RowSlice& sl, int i, unsigned which) {           // 16 of tile i's rows
+    const int t = GROUPS * i + grp;
+    load_rows16_lds(sl, off, t < nt ? t * BKV : none, lds0 + ((unsigned)(i & 1) * 2 + which) * KV_TILE);
+  };
+  auto live = [&](int i) { const int t = GROUPS * i + grp; return t < nt && (!causal || t * BKV <= qw + 31); };   // some key to see
+  const unsigned rbase = swz_row_base(lane), cbase = swz_col_base(lane);
+  f32x16 oacc[4] = {}, s[2];
+  bf16x8 kf[16], pf[4];
+  float m = -INFINITY, l = 0.f;
+  auto read_k = [&](int i, int from) {              // half of K of tile i
+    const unsigned char* cK = tiles + (unsigned)(i & 1) * 2 * KV_TILE;
+#pragma unroll
+    for (int kk = from; kk < from + 4; kk++)
+#pragma unroll
+      for (int j = 0; j < 2; j++) kf[kk * 2 + j] = *(const bf16x8*)(cK + j * 8192 + (rbase ^ (unsigned)(kk * 32)));
+  };
+  auto times_q = [&]() {
+    s[0] = f32x16{};
+    s[1] = f32x16{};
+#pragma unroll
+    for (int kk = 0; kk < 8; kk++)
+#pragma unroll
+      for (int j = 0; j < 2; j++) s[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk * 2 + j], qf[kk], s[j], 0, 0, 0);
+  };
+  issue(slK, 0, 0); issue(slV, 0, 1); issue(slK, 1, 0);
+  arrived(qf);
+  wait_vmcnt<8>();                                  // the first keys
+  phase_end();
+  if (GROUPS == 2 && grp == 1) phase_end();                        // half an iteration behind
+  read_k(0, 0);
+  read_k(0, 4);
+  times_q();
+  wait_vmcnt<4>();                                  // K of tile 1 is there
+  phase_end();
+  // keys past the sequence end or after the query
+  auto mask = [&](int i) {
+    const int seen = (causal ? min(myq, S - 1) : S - 1) - (GROUPS * i + grp) * BKV - g * 4;
+#pragma unroll
+    for (int j = 0; j < 2; j++)
+#pragma unroll
+      for (int e = 0; e < 16; e++)
+        if (j * 32 + (e >> 2) * 8 + (e & 3) > seen) s[j][e] = -INFINITY;
+  };
+  // half of a tile's probabilities, and their part of the sum (of this half's keys; the halves meet at the end)
+  float ms = 0.f;
+  auto exponentials = [&](f32x16 x, int h) {
+    float rs[2] = {};
+#pragma unroll
+    for (int e = 0; e < 16; e++) {
+      x[e] = fast_exp2(fmaf(x[e], sl2, -ms));
+      rs[e & 1] += x[e];
+    }
+    l += rs[0] + rs[1];
+    pf[h * 2] = acc_to_frag(x, 0);
+    pf[h * 2 + 1] = acc_to_frag(x, 1);
+  };
+  // the keys read in the phase before and the values just read make room
+  auto softmax = [&](int i) {
+    issue(slK, i + 2, 0);
+    issue(slV, i + 1, 1);
+    read_k(i + 1, 0);
+    float mx[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+#pragma unroll
+    for (int e = 0; e < 32; e += 2) mx[(e >> 1) & 3] = fmaxf(fmaxf(mx[(e >> 1) & 3], s[e >> 4][e & 15]), s[e >> 4][(e & 15) + 1]);
+    const float mn = fmaxf(m, both_halves_max(fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3]))) * sl2);
+    // the accumulator is rescaled only when some query of the wave has raised its maximum by more than 2^8: until then
+    // probabilities are up to 256, of the same relative precision
+    if (__any(mn > m + 8.f)) {
+      const float alpha = fast_exp2(m - (mn == -INFINITY ? 0.f : mn));
+      l *= alpha;
+#pragma unroll
+      for (int d = 0; d < 4; d++) oacc[d] *= alpha;
+      m = mn;
+    }
+    read_k(i + 1, 4);
+    ms = m == -INFINITY ? 0.f : m;
+    exponentials(s[0], 0);
+    wait_vmcnt<8>();                                // V of i is there
+    phase_end();
+  };
+  for (int i = 0; i + 1 < ni; i++) {
+    if (GROUPS == 1 && i + 2 == ni) mask(i);
+    softmax(i);
+    __builtin_amdgcn_s_setprio(1);
+    const f32x16 rest = s[1];
+    const unsigned char* cV = tiles + ((unsigned)(i & 1) * 2 + 1) * KV_TILE;
+    bf16x8 vf[4];
+    times_q();
+    exponentials(rest, 1);
+    read_cols(vf, cV, cbase, 0);
+    __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+#pragma unroll
+    for (int j = 0; j < 14; j++) {
+      __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);
+      if (j >= 6) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    cols_times64(oacc, cV, cbase, pf, vf);          // O^T[dh, q] += V^T[dh, kv] P^T[kv, q]
+    __builtin_amdgcn_s_setprio(0);
+    wait_vmcnt<4>();                                // K of i + 2 is there
+    phase_end();
+  }
+  mask(ni - 1);                                     // only the last 128 keys can hold some that are not to be seen
+  softmax(ni - 1);
+  exponentials(s[1], 1);
+  if (live(ni - 1)) {
+    const unsigned char* cV = tiles + ((unsigned)((ni - 1) & 1) * 2 + 1) * KV_TILE;
+    bf16x8 vf[4];
+    read_cols(vf, cV, cbase, 0);
+    cols_times64(oacc, cV, cbase, pf, vf);
+  }
+  if (GROUPS == 2 && grp == 0) phase_end();
+  wait_vmcnt<0>();                                  // the zero-filled loads past the last tile
+  phase_end();
+  l = both_halves_sum(l);
+  if constexpr (GROUPS == 1) {
+    if (myq < S) {
+      const float inv = 1.0f / l;
+      store_cols(o + boff + (i64)myq * ld, oacc, inv, g);
+      if (g == 0) lse[((i64)b * H + hh) * S + myq] = (m + __log2f(l)) * LN2;
+    }
+    return;
+  }
+  // each group takes half of the columns of both
+  float4* part = (float4*)smem_raw;                 // [wave][8][lane], then statistics
+  float2* stats = (float2*)(smem_raw + 8 * 8192);
+  // element e of accumulator d of this group's half, of the other one's
+  auto half = [&](int theirs, int d, int e) { return grp == theirs ? oacc[d][e] : oacc[2 + d][e]; };
+#pragma unroll
+  for (int d = 0; d < 2; d++)
+#pragma unroll
+    for (int e = 0; e < 4; e++) part[(wave * 8 + d * 4 + e) * 64 + lane] = make_float4(half(1, d, e * 4), half(1, d, e * 4 + 1), half(1, d, e * 4 + 2), half(1, d, e * 4 + 3));
+  if (g == 0) stats[wave * 32 + lane] = make_float2(m, l);
+  __syncthreads();
+  const float2 other = stats[(wave ^ 4) * 32 + (lane & 31)];
+  const float M = fmaxf(m, other.x), Ms = M == -INFINITY ? 0.f : M;
+  float w = fast_exp2(m - Ms), w2 = fast_exp2(other.x - Ms);
+  const float tot = grp == 0 ? w * l + w2 * other.y : w2 * other.y + w * l;
+  const float inv = 1.0f / tot;
+  w *= inv;
+  w2 *= inv;
+  if (myq < S) {
+    bf16* op = o + boff + (i64)myq * ld + grp * 64;
+#pragma unroll
+    for (int d = 0; d < 2; d++)
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        const float4 p = part[((wave ^ 4) * 8 + d * 4 + e) * 64 + lane];
+        bf16x4 r;
+        r[0] = (__bf16)(half(0, d, e * 4) * w + p.x * w2);
+        r[1] = (__bf16)(half(0, d, e * 4 + 1) * w + p.y * w2);
+        r[2] = (__bf16)(half(0, d, e * 4 + 2) * w + p.z * w2);
+        r[3] = (__bf16)(half(0, d, e * 4 + 3) * w + p.w * w2);
+        *(bf16x4*)(op + d * 32 + e * 8 + g * 4) = r;
+      }
+    if (wave < 4 && g == 0) lse[((i64)b * H + hh) * S + myq] = (M + __log2f(tot)) * LN2;
+  }
+}
+
+// ------------------------------------------------------------------------------------
+// Backward, part 1: dQ, and D = <o, dO> of the rows.  The forward kernel's scheme and groups.  Per tile:
+//   S^T = K Q^T,  P^T = exp(S^T*scale - lse),  dP^T = V dO^T,  dS^T = P^T (dP^T - D),
+//   dQ^T += K^T dS^T,  times scale at the end.
+// Three products against one exponential: bound by the matrix cores, fragments are read one step ahead of theirs.  The keys of
+// a tile are read once more in the phase after, so they have three stages.  Against tiles staged through registers and a
+// kernel of its own for D, us: 1 x 8192, 16 heads, 475 -> 355, 2 x 2048 108 -> 72, 4 x 512 32 -> 21.
+// ------------------------------------------------------------------------------------
+#define DQ_SMEM(GROUPS) ((GROUPS) * 5 * KV_TILE)  // three stages of K and two of V per group; the partial results at the end
+template <int GROUPS>
+__global__ void __launch_bounds__(256 * GROUPS, 2) flash_bwd_dq_k(const bf16* __restrict__ q, const bf16* __restrict__ k,
+                                                      const bf16* __restrict__ v, const bf16* __restrict__ o, const bf16* __restrict__ d_o,
+                                                      const float* __restrict__ lse, float* __restrict__ dvec,
+                                                      bf16* __restrict__ dq, int B, int S, int H, int causal, float scale) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
+  int qt, hh, b;
+  place(H, B, (S + 127) / 128, 3 - GROUPS, &qt, &hh, &b);
+  qt = (S + 127) / 128 - 1 - qt;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 5;
+  const int grp = GROUPS == 2 ? wave >> 2 : 0, wv = wave & 3;
+  const i64 ld = (i64)H * DH, boff = (i64)b * S * ld + hh * DH;
+  const int q0 = qt * 128, qw = q0 + wv * 32;
+  const int myq = qw + (lane & 31);
+  const float sl2 = scale * LOG2E;
+  const int nt = ((causal ? min(S, q0 + 128) : S) + BKV - 1) / BKV, ni = (nt + GROUPS - 1) / GROUPS;
+  const int none = S;
+
+  bf16x8 qf[8], dof[8];
+  load_frags(q + boff, ld, myq, S, g, qf);
+  load_frags(d_o + boff, ld, myq, S, g, dof);
+  float mylse = (myq < S) ? lse[((i64)b * H + hh) * S + myq] * LOG2E : 0.f;
+  // D = <o, dO> of the row, for the kernel behind this one too
+  float myD = 0.f;
+  {
+    bf16x8 of[8];
+    load_frags(o + boff, ld, myq, S, g, of);
+#pragma unroll
+    for (int kk = 0; kk < 8; kk++)
+#pragma unroll
+      for (int u = 0; u < 8; u++) myD = fmaf((float)of[kk][u], (float)dof[kk][u], myD);
+    myD = both_halves_sum(myD);
+    if (grp == 0 && g == 0 && myq < S) dvec[((i64)b * H + hh) * S + myq] = myD;
+  }
+  const RowSlice slK = row_slice(k + boff, ld, S), slV = row_slice(v + boff, ld, S);
+  const unsigned char* tiles = smem_raw + (unsigned)grp * 5 * KV_TILE;      // K, K, K, V, V
+  const unsigned lds0 = lds_address(smem_raw) + (unsigned)grp * 5 * KV_TILE + (unsigned)wv * 4096u;
+  unsigned off[4];
+  row_offsets(slK, wv * 16, lane, off);
+  auto issue = [&](const RowSlice& sl, int i, unsigned place_) {          // 16 of tile i's rows
+    const int t = GROUPS * i + grp;
+    load_rows16_lds(sl, off, t < nt ? t * BKV : none, lds0 + place_ * KV_TILE);
+  };
+  auto live = [&](int i) { const int t = GROUPS * i + grp; return t < nt && (!causal || t * BKV <= qw + 31); };
+  const unsigned rbase = swz_row_base(lane), cbase = swz_col_base(lane);
+  f32x16 acc[4] = {}, s[2], dp[2];
+  bf16x8 dsf[4], first[4];
+  bf16x8 fr[2][4];
+  auto read_kv = [&](bf16x8 (&f)[4], int i, unsigned stage, int kk) {
+    const unsigned char* cK = tiles + stage * KV_TILE;
+    const unsigned char* cV = tiles + (3u + (unsigned)(i & 1)) * KV_TILE;
+    const unsigned at = rbase ^ (unsigned)(kk * 32);
+    f[0] = *(const bf16x8*)(cK + at);
+    f[1] = *(const bf16x8*)(cV + at);
+    f[2] = *(const bf16x8*)(cK + 8192 + at);
+    f[3] = *(const bf16x8*)(cV + 8192 + at);
+  };
+  auto times_q = [&](int i, unsigned stage) {       // (after read_kv(fr[0], i, stage, 0))
+#pragma unroll
+    for (int j = 0; j < 2; j++) { s[j] = f32x16{}; dp[j] = f32x16{}; }
+#pragma unroll
+    for (int kk = 0; kk < 8; kk++) {
+      if (kk < 7) read_kv(fr[(kk + 1) & 1], i, stage, kk + 1);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < 2; j++) {
+        s[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[kk & 1][j * 2], qf[kk], s[j], 0, 0, 0);
+        dp[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[kk & 1][j * 2 + 1], dof[kk], dp[j], 0, 0, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+
+  issue(slK, 0, 0); issue(slV, 0, 3); issue(slK, 1, 1); issue(slV, 1, 4);
+  arrived(qf);
+  arrived(dof);
+  asm volatile("" : "+v"(mylse), "+v"(myD));
+  wait_vmcnt<8>();
+  phase_end();
+  if (GROUPS == 2 && grp == 1) phase_end();                        // half an iteration behind
+  unsigned before = 2, now = 0;                     // places of K of the last iteration and this one
+  read_kv(fr[0], 0, 0, 0);
+  times_q(0, 0);
+  phase_end();
+  // keys past the sequence end or after the query
+  auto mask = [&](int i) {
+    const int seen = (causal ? min(myq, S - 1) : S - 1) - (GROUPS * i + grp) * BKV - g * 4;
+#pragma unroll
+    for (int j = 0; j < 2; j++)
+#pragma unroll
+      for (int e = 0; e < 16; e++)
+        if (j * 32 + (e >> 2) * 8 + (e & 3) > seen) s[j][e] = -INFINITY;
+  };
+  // the values just read and the keys read for the second time make room
+  auto probabilities = [&](int i) {
+    issue(slK, i + 2, before);
+    issue(slV, i + 2, 3u + (unsigned)(i & 1));
+#pragma unroll
+    for (int j = 0; j < 2; j++)
+#pragma unroll
+      for (int e = 0; e < 16; e++) s[j][e] = fast_exp2(fmaf(s[j][e], sl2, -mylse)) * (dp[j][e] - myD);
+#pragma unroll
+    for (int c = 0; c < 4; c++) dsf[c] = acc_to_frag(s[c >> 1], c & 1);
+    read_cols(first, tiles + now * KV_TILE, cbase, 0);
+    const unsigned next = 3u - before - now;
+    before = now;
+    now = next;
+    wait_vmcnt<8>();                                // K and V of i + 1 are there
+    phase_end();
+  };
+  for (int i = 0; i + 1 < ni; i++) {
+    if (GROUPS == 1 && i + 2 == ni) mask(i);
+    probabilities(i);
+    __builtin_amdgcn_s_setprio(1);
+    read_kv(fr[0], i + 1, now, 0);
+    cols_times64(acc, tiles + before * KV_TILE, cbase, dsf, first);
+    times_q(i + 1, now);
+    __builtin_amdgcn_s_setprio(0);
+    phase_end();
+  }
+  mask(ni - 1);                                     // only the last 128 keys can hold some that are not to be seen
+  probabilities(ni - 1);
+  if (live(ni - 1)) cols_times64(acc, tiles + before * KV_TILE, cbase, dsf, first);
+  if (GROUPS == 2 && grp == 0) phase_end();
+  wait_vmcnt<0>();                                  // the zero-filled loads past the last tile
+  phase_end();
+  if constexpr (GROUPS == 1) {
+    if (myq < S) store_cols(dq + boff + (i64)myq * ld, acc, scale, g);
+    return;
+  }
+  // each group takes half of the columns of both
+  float4* part = (float4*)smem_raw;                 // [wave][8][lane]
+  auto half = [&](int theirs, int d, int e) { return grp == theirs ? acc[d][e] : acc[2 + d][e]; };
+#pragma unroll
+  for (int d = 0; d < 2; d++)
+#pragma unroll
+    for (int e = 0; e < 4; e++) part[(wave * 8 + d * 4 + e) * 64 + lane] = make_float4(half(1, d, e * 4), half(1, d, e * 4 + 1), half(1, d, e * 4 + 2), half(1, d, e * 4 + 3));
+  __syncthreads();
+  if (myq < S) {
+    bf16* op = dq + boff + (i64)myq * ld + grp * 64;
+#pragma unroll
+    for (int d = 0; d < 2; d++)
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        const float4 p = part[((wave ^ 4) * 8 + d * 4 + e) * 64 + lane];
+        bf16x4 r;
+        r[0] = (__bf16)((half(0, d, e * 4) + p.x) * scale);
+        r[1] = (__bf16)((half(0, d, e * 4 + 1) + p.y) * scale);
+        r[2] = (__bf16)((half(0, d, e * 4 + 2) + p.z) * scale);
+        r[3] = (__bf16)((half(0, d, e * 4 + 3) + p.w) * scale);
+        *(bf16x4*)(op + d * 32 + e * 8 + g * 4) = r;
+      }
+  }
 }
 
 // ------------------------------------------------------------------------------------
@@ -420,7 +555,7 @@ __global__ void __launch_bounds__(256, QB == 1 ? 2 : 1) flash_bwd_dkv_k(const bf
                                                        int causal, float scale) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];      // 2 stages
   int kt, hh, b;
-  place(H, B, (S + 127) / 128, &kt, &hh, &b);       // early key tiles see the most queries
+  place(H, B, (S + 127) / 128, 2, &kt, &hh, &b);       // early key tiles see the most queries
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 5;
   const i64 ld = (i64)H * DH;
   const i64 boff = (i64)b * S * ld + hh * DH;
@@ -553,15 +688,6 @@ __global__ void __launch_bounds__(256, QB == 1 ? 2 : 1) flash_bwd_dkv_k(const bf
 __device__ __forceinline__ void load_rows32_lds(const RowSlice& sl, int row0, unsigned dst, int lane) {
   load_rows16_lds(sl, row0, dst, lane);
   load_rows16_lds(sl, row0 + 16, dst + 4096u, lane);
-}
-// one row of 128 as operand fragments of a product over the head width; rows past the end are zeros
-__device__ __forceinline__ void load_frags(const bf16* base, i64 ld, int row, int S, int g, bf16x8 (&f)[8]) {
-#pragma unroll
-  for (int kk = 0; kk < 8; kk++) {
-    uint4 t = make_uint4(0, 0, 0, 0);
-    if (row < S) t = *(const uint4*)(base + (i64)row * ld + kk * 16 + g * 8);
-    f[kk] = __builtin_bit_cast(bf16x8, t);
-  }
 }
 // tile rows x fragments: element e of lane l is tile row (e >> 2) * 8 + (l >> 5) * 4 + (e & 3), column l & 31
 __device__ __forceinline__ f32x16 rows_times(const unsigned char* tile, unsigned rbase, const bf16x8 (&f)[8]) {
@@ -800,6 +926,23 @@ __device__ __forceinline__ void short_dkv(unsigned char* smem_raw, int tile, int
   __syncthreads();
   store_partials((const float*)smem_raw, w, dv + at, k0 + r < S);
 }
+// D = <o, dO> of each row, 16 bytes per lane and 16 lanes per row
+__global__ void __launch_bounds__(256) flash_dvec_k(const bf16* __restrict__ o, const bf16* __restrict__ d_o, float* __restrict__ dvec, int S, int H,
+                                                    i64 rows) {
+  const i64 r = (i64)blockIdx.x * 16 + (threadIdx.x >> 4);
+  if (r >= rows) return;
+  const int c = (threadIdx.x & 15) * 8;
+  const bf16x8 a = *(const bf16x8*)(o + r * DH + c), d = *(const bf16x8*)(d_o + r * DH + c);
+  float acc = 0.f;
+#pragma unroll
+  for (int u = 0; u < 8; u++) acc = fmaf((float)a[u], (float)d[u], acc);
+#pragma unroll
+  for (int x = 8; x; x >>= 1) acc += __shfl_xor(acc, x, WAVE);
+  if (c == 0) {
+    const i64 t = r / H, b = t / S;
+    dvec[(b * H + (r - t * H)) * S + (t - b * S)] = acc;
+  }
+}
 // rows of H workgroups, by turns dK/dV and dQ, long tiles first in both
 __global__ void __launch_bounds__(256, 2) flash_bwd_short_k(const bf16* __restrict__ q, const bf16* __restrict__ k, const bf16* __restrict__ v,
                                                             const bf16* __restrict__ d_o, const float* __restrict__ lse,
@@ -834,6 +977,19 @@ static bool short_sequence(int B, int S, int H) {
   return H <= 16 || tokens * H <= 16 * (S >= 1024 ? 3072 : S >= 448 ? 2752 : S >= 256 ? 1856 : S >= 128 ? 1344 : 768);
 }
 
+// One or two groups of waves per workgroup (forward and dQ).  One lets two workgroups share a CU, which keeps both busy where
+// there are enough of them; two halve the chain of tiles, which is what counts where the workgroups are few or the longest ones
+// run on alone.  Measured, us, forward / all of the backward pass, 16 heads, causal, one group -> two (workgroups):
+//   4 x 512 (256) 16.8 / 57.9 -> 16.4 / 58.0    8 x 256 (256) 11.7 / 39.5 -> 12.3 / 41.0    5 x 400 (320) 14.1 / 54 -> 20.5 / 62
+//   2 x 1100 (288) 26.8 / 108 -> 22.5 / 103     3 x 1024 (384) 27.0 / 105 -> 29.1 / 107     2 x 1300 (352) 31.0 / 122 -> 29.2 / 120
+//   2 x 1700 (448) 39.3 / 154.5 -> 39.1 / 153.8   2 x 2048 (512) 47.3 / 194 -> 46.3 / 189   2 x 2300 (576) 58.8 / 228 -> 62.7 / 234
+//   1 x 2500 (320) 49.5 / 211 -> 39.2 / 193     1 x 4600 (576) 108 / 421 -> 104 / 415       1 x 5600 (704) 142 / 544 -> 143 / 539
+//   8 heads: 1 x 8192 (512) 164 / 681 -> 141 / 634    32 heads: 1 x 2500 (640) 66.5 / 255 -> 71.2 / 263
+static bool two_groups(int B, int S, int H) {
+  const i64 tiles = cdiv(S, 128), workgroups = tiles * B * H;
+  return tiles >= 4 && (workgroups <= 256 + 10 * tiles || (tiles >= 14 && workgroups <= 512));
+}
+
 int launch_attn_fwd_flash(const void* q, const void* k, const void* v, void* o, float* lse, int B, int S, int H,
                           int dh, int causal, hipStream_t s, const unsigned char* row_skip) {
   if (dh != DH || B <= 0 || S <= 0) return 1;
@@ -849,14 +1005,15 @@ int launch_attn_fwd_flash(const void* q, const void* k, const void* v, void* o, 
                        (const bf16*)v, (bf16*)o, lse, B, S, H, causal, 1.0f / sqrtf((float)dh), row_skip);
     return 0;
   }
-  size_t smem = (size_t)2 * BKV * (KST + VST) * sizeof(bf16);
   static std::atomic<unsigned long long> attr_mask{0};
   if (attr_needed(attr_mask)) {
-    (void)hipFuncSetAttribute((const void*)flash_fwd_k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    (void)hipFuncSetAttribute((const void*)flash_fwd_k<1>, hipFuncAttributeMaxDynamicSharedMemorySize, FWD_SMEM(1));
+    (void)hipFuncSetAttribute((const void*)flash_fwd_k<2>, hipFuncAttributeMaxDynamicSharedMemorySize, FWD_SMEM(2));
     attr_done(attr_mask);
   }
-  hipLaunchKernelGGL(flash_fwd_k, dim3((unsigned)((i64)H * cdiv(S, 128) * B)), dim3(256), smem, s, (const bf16*)q, (const bf16*)k,
-                     (const bf16*)v, (bf16*)o, lse, B, S, H, causal, 1.0f / sqrtf((float)dh), row_skip);
+  const int groups = two_groups(B, S, H) ? 2 : 1;
+  hipLaunchKernelGGL(groups == 2 ? flash_fwd_k<2> : flash_fwd_k<1>, dim3((unsigned)((i64)H * cdiv(S, 128) * B)), dim3(256 * groups), FWD_SMEM(groups), s,
+                     (const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)o, lse, B, S, H, causal, 1.0f / sqrtf((float)dh), row_skip);
   return 0;
 }
 
@@ -868,9 +1025,10 @@ int launch_attn_bwd_flash(const void* q, const void* k, const void* v, const voi
   if (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o | (uintptr_t)d_o | (uintptr_t)dq | (uintptr_t)dk |
        (uintptr_t)dv) & 15)
     return 1;
-  launch_attn_dvec(1, o, d_o, dvec, B, S, H, dh, s);
   const float scale = 1.0f / sqrtf((float)dh);
   if (short_sequence(B, S, H)) {
+    const i64 rows = (i64)B * S * H;
+    hipLaunchKernelGGL(flash_dvec_k, dim3((unsigned)cdiv(rows, 16)), dim3(256), 0, s, (const bf16*)o, (const bf16*)d_o, dvec, S, H, rows);
     static std::atomic<unsigned long long> attr_mask{0};
     if (attr_needed(attr_mask)) {
       (void)hipFuncSetAttribute((const void*)flash_bwd_short_k, hipFuncAttributeMaxDynamicSharedMemorySize, SHORT_SMEM);
@@ -880,18 +1038,19 @@ int launch_attn_bwd_flash(const void* q, const void* k, const void* v, const voi
                        (const bf16*)v, (const bf16*)d_o, lse, dvec, (bf16*)dq, (bf16*)dk, (bf16*)dv, B, S, H, causal, scale);
     return 0;
   }
-  size_t sm1 = (size_t)4 * BKV * BST * sizeof(bf16);
   size_t sm2 = 2 * DKV_STAGE;
   static std::atomic<unsigned long long> attr_mask{0};
   if (attr_needed(attr_mask)) {
-    (void)hipFuncSetAttribute((const void*)flash_bwd_dq_k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm1);
+    (void)hipFuncSetAttribute((const void*)flash_bwd_dq_k<1>, hipFuncAttributeMaxDynamicSharedMemorySize, DQ_SMEM(1));
+    (void)hipFuncSetAttribute((const void*)flash_bwd_dq_k<2>, hipFuncAttributeMaxDynamicSharedMemorySize, DQ_SMEM(2));
     (void)hipFuncSetAttribute((const void*)flash_bwd_dkv_k<1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm2);
     (void)hipFuncSetAttribute((const void*)flash_bwd_dkv_k<2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm2);
     attr_done(attr_mask);
   }
   dim3 grid((unsigned)((i64)H * cdiv(S, 128) * B));
-  hipLaunchKernelGGL(flash_bwd_dq_k, grid, dim3(256), sm1, s, (const bf16*)q, (const bf16*)k, (const bf16*)v,
-                     (const bf16*)d_o, lse, dvec, (bf16*)dq, B, S, H, causal, scale);
+  const int groups = two_groups(B, S, H) ? 2 : 1;
+  hipLaunchKernelGGL(groups == 2 ? flash_bwd_dq_k<2> : flash_bwd_dq_k<1>, grid, dim3(256 * groups), DQ_SMEM(groups), s, (const bf16*)q, (const bf16*)k,
+                     (const bf16*)v, (const bf16*)o, (const bf16*)d_o, lse, dvec, (bf16*)dq, B, S, H, causal, scale);
   if (grid.x <= 256)         // one workgroup on a CU at most (512 of them, 2 x 2048 tokens: QB = 1 135 us, QB = 2 157)
     hipLaunchKernelGGL(flash_bwd_dkv_k<2>, grid, dim3(256), sm2, s, (const bf16*)q, (const bf16*)k, (const bf16*)v,
                        (const bf16*)d_o, lse, dvec, (bf16*)dk, (bf16*)dv, B, S, H, causal, scale);
