@@ -371,30 +371,28 @@ __global__ void __launch_bounds__(256 * GROUPS, 2) flash_fwd_k(const bf16* __res
 }
 
 // ------------------------------------------------------------------------------------
-// Backward, part 1: dQ, and D = <o, dO> of the rows.  The forward kernel's scheme and groups.  Per tile:
+// Backward, part 1: dQ, and D = <o, dO> of the rows.  The forward kernel's scheme with 4 waves.  Per tile:
 //   S^T = K Q^T,  P^T = exp(S^T*scale - lse),  dP^T = V dO^T,  dS^T = P^T (dP^T - D),
 //   dQ^T += K^T dS^T,  times scale at the end.
 // Three products against one exponential: bound by the matrix cores, fragments are read one step ahead of theirs.  The keys of
 // a tile are read once more in the phase after, so they have three stages.  Against tiles staged through registers and a
 // kernel of its own for D, us: 1 x 8192, 16 heads, 475 -> 355, 2 x 2048 108 -> 72, 4 x 512 32 -> 21.
 // ------------------------------------------------------------------------------------
-#define DQ_SMEM(GROUPS) ((GROUPS) * 5 * KV_TILE)  // three stages of K and two of V per group; the partial results at the end
-template <int GROUPS>
-__global__ void __launch_bounds__(256 * GROUPS, 2) flash_bwd_dq_k(const bf16* __restrict__ q, const bf16* __restrict__ k,
+#define DQ_SMEM (5 * KV_TILE)                     // three stages of K, two of V
+__global__ void __launch_bounds__(256, 2) flash_bwd_dq_k(const bf16* __restrict__ q, const bf16* __restrict__ k,
                                                       const bf16* __restrict__ v, const bf16* __restrict__ o, const bf16* __restrict__ d_o,
                                                       const float* __restrict__ lse, float* __restrict__ dvec,
                                                       bf16* __restrict__ dq, int B, int S, int H, int causal, float scale) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
   int qt, hh, b;
-  place(H, B, (S + 127) / 128, 3 - GROUPS, &qt, &hh, &b);
+  place(H, B, (S + 127) / 128, 2, &qt, &hh, &b);
   qt = (S + 127) / 128 - 1 - qt;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 5;
-  const int grp = GROUPS == 2 ? wave >> 2 : 0, wv = wave & 3;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 5;
   const i64 ld = (i64)H * DH, boff = (i64)b * S * ld + hh * DH;
   const int q0 = qt * 128, qw = q0 + wv * 32;
   const int myq = qw + (lane & 31);
   const float sl2 = scale * LOG2E;
-  const int nt = ((causal ? min(S, q0 + 128) : S) + BKV - 1) / BKV, ni = (nt + GROUPS - 1) / GROUPS;
+  const int nt = ((causal ? min(S, q0 + 128) : S) + BKV - 1) / BKV;
   const int none = S;
 
   bf16x8 qf[8], dof[8];
@@ -411,25 +409,22 @@ __global__ void __launch_bounds__(256 * GROUPS, 2) flash_bwd_dq_k(const bf16* __
 #pragma unroll
       for (int u = 0; u < 8; u++) myD = fmaf((float)of[kk][u], (float)dof[kk][u], myD);
     myD = both_halves_sum(myD);
-    if (grp == 0 && g == 0 && myq < S) dvec[((i64)b * H + hh) * S + myq] = myD;
+    if (g == 0 && myq < S) dvec[((i64)b * H + hh) * S + myq] = myD;
   }
   const RowSlice slK = row_slice(k + boff, ld, S), slV = row_slice(v + boff, ld, S);
-  const unsigned char* tiles = smem_raw + (unsigned)grp * 5 * KV_TILE;      // K, K, K, V, V
-  const unsigned lds0 = lds_address(smem_raw) + (unsigned)grp * 5 * KV_TILE + (unsigned)wv * 4096u;
+  const unsigned lds0 = lds_address(smem_raw) + (unsigned)wv * 4096u;
   unsigned off[4];
   row_offsets(slK, wv * 16, lane, off);
-  auto issue = [&](const RowSlice& sl, int i, unsigned place_) {          // 16 of tile i's rows
-    const int t = GROUPS * i + grp;
-    load_rows16_lds(sl, off, t < nt ? t * BKV : none, lds0 + place_ * KV_TILE);
+  auto issue = [&](const RowSlice& sl, int i, unsigned stage) {           // 16 of tile i's rows; stages K, K, K, V, V
+    load_rows16_lds(sl, off, i < nt ? i * BKV : none, lds0 + stage * KV_TILE);
   };
-  auto live = [&](int i) { const int t = GROUPS * i + grp; return t < nt && (!causal || t * BKV <= qw + 31); };
   const unsigned rbase = swz_row_base(lane), cbase = swz_col_base(lane);
   f32x16 acc[4] = {}, s[2], dp[2];
   bf16x8 dsf[4], first[4];
   bf16x8 fr[2][4];
   auto read_kv = [&](bf16x8 (&f)[4], int i, unsigned stage, int kk) {
-    const unsigned char* cK = tiles + stage * KV_TILE;
-    const unsigned char* cV = tiles + (3u + (unsigned)(i & 1)) * KV_TILE;
+    const unsigned char* cK = smem_raw + stage * KV_TILE;
+    const unsigned char* cV = smem_raw + (3u + (unsigned)(i & 1)) * KV_TILE;
     const unsigned at = rbase ^ (unsigned)(kk * 32);
     f[0] = *(const bf16x8*)(cK + at);
     f[1] = *(const bf16x8*)(cV + at);
@@ -458,14 +453,13 @@ __global__ void __launch_bounds__(256 * GROUPS, 2) flash_bwd_dq_k(const bf16* __
   asm volatile("" : "+v"(mylse), "+v"(myD));
   wait_vmcnt<8>();
   phase_end();
-  if (GROUPS == 2 && grp == 1) phase_end();                        // half an iteration behind
   unsigned before = 2, now = 0;                     // places of K of the last iteration and this one
   read_kv(fr[0], 0, 0, 0);
   times_q(0, 0);
   phase_end();
   // keys past the sequence end or after the query
   auto mask = [&](int i) {
-    const int seen = (causal ? min(myq, S - 1) : S - 1) - (GROUPS * i + grp) * BKV - g * 4;
+    const int seen = (causal ? min(myq, S - 1) : S - 1) - i * BKV - g * 4;
 #pragma unroll
     for (int j = 0; j < 2; j++)
 #pragma unroll
@@ -482,56 +476,28 @@ __global__ void __launch_bounds__(256 * GROUPS, 2) flash_bwd_dq_k(const bf16* __
       for (int e = 0; e < 16; e++) s[j][e] = fast_exp2(fmaf(s[j][e], sl2, -mylse)) * (dp[j][e] - myD);
 #pragma unroll
     for (int c = 0; c < 4; c++) dsf[c] = acc_to_frag(s[c >> 1], c & 1);
-    read_cols(first, tiles + now * KV_TILE, cbase, 0);
+    read_cols(first, smem_raw + now * KV_TILE, cbase, 0);
     const unsigned next = 3u - before - now;
     before = now;
     now = next;
     wait_vmcnt<8>();                                // K and V of i + 1 are there
     phase_end();
   };
-  for (int i = 0; i + 1 < ni; i++) {
-    if (GROUPS == 1 && i + 2 == ni) mask(i);
+  for (int i = 0; i + 1 < nt; i++) {
+    if (i + 2 == nt) mask(i);
     probabilities(i);
     __builtin_amdgcn_s_setprio(1);
     read_kv(fr[0], i + 1, now, 0);
-    cols_times64(acc, tiles + before * KV_TILE, cbase, dsf, first);
+    cols_times64(acc, smem_raw + before * KV_TILE, cbase, dsf, first);
     times_q(i + 1, now);
     __builtin_amdgcn_s_setprio(0);
     phase_end();
   }
-  mask(ni - 1);                                     // only the last 128 keys can hold some that are not to be seen
-  probabilities(ni - 1);
-  if (live(ni - 1)) cols_times64(acc, tiles + before * KV_TILE, cbase, dsf, first);
-  if (GROUPS == 2 && grp == 0) phase_end();
+  mask(nt - 1);                                     // only the last 128 keys can hold some that are not to be seen
+  probabilities(nt - 1);
+  if (!causal || (nt - 1) * BKV <= qw + 31) cols_times64(acc, smem_raw + before * KV_TILE, cbase, dsf, first);
   wait_vmcnt<0>();                                  // the zero-filled loads past the last tile
-  phase_end();
-  if constexpr (GROUPS == 1) {
-    if (myq < S) store_cols(dq + boff + (i64)myq * ld, acc, scale, g);
-    return;
-  }
-  // each group takes half of the columns of both
-  float4* part = (float4*)smem_raw;                 // [wave][8][lane]
-  auto half = [&](int theirs, int d, int e) { return grp == theirs ? acc[d][e] : acc[2 + d][e]; };
-#pragma unroll
-  for (int d = 0; d < 2; d++)
-#pragma unroll
-    for (int e = 0; e < 4; e++) part[(wave * 8 + d * 4 + e) * 64 + lane] = make_float4(half(1, d, e * 4), half(1, d, e * 4 + 1), half(1, d, e * 4 + 2), half(1, d, e * 4 + 3));
-  __syncthreads();
-  if (myq < S) {
-    bf16* op = dq + boff + (i64)myq * ld + grp * 64;
-#pragma unroll
-    for (int d = 0; d < 2; d++)
-#pragma unroll
-      for (int e = 0; e < 4; e++) {
-        const float4 p = part[((wave ^ 4) * 8 + d * 4 + e) * 64 + lane];
-        bf16x4 r;
-        r[0] = (__bf16)((half(0, d, e * 4) + p.x) * scale);
-        r[1] = (__bf16)((half(0, d, e * 4 + 1) + p.y) * scale);
-        r[2] = (__bf16)((half(0, d, e * 4 + 2) + p.z) * scale);
-        r[3] = (__bf16)((half(0, d, e * 4 + 3) + p.w) * scale);
-        *(bf16x4*)(op + d * 32 + e * 8 + g * 4) = r;
-      }
-  }
+  if (myq < S) store_cols(dq + boff + (i64)myq * ld, acc, scale, g);
 }
 
 // ------------------------------------------------------------------------------------
@@ -977,17 +943,19 @@ static bool short_sequence(int B, int S, int H) {
   return H <= 16 || tokens * H <= 16 * (S >= 1024 ? 3072 : S >= 448 ? 2752 : S >= 256 ? 1856 : S >= 128 ? 1344 : 768);
 }
 
-// One or two groups of waves per workgroup (forward and dQ).  One lets two workgroups share a CU, which keeps both busy where
-// there are enough of them; two halve the chain of tiles, which is what counts where the workgroups are few or the longest ones
-// run on alone.  Measured, us, forward / all of the backward pass, 16 heads, causal, one group -> two (workgroups):
-//   4 x 512 (256) 16.8 / 57.9 -> 16.4 / 58.0    8 x 256 (256) 11.7 / 39.5 -> 12.3 / 41.0    5 x 400 (320) 14.1 / 54 -> 20.5 / 62
-//   2 x 1100 (288) 26.8 / 108 -> 22.5 / 103     3 x 1024 (384) 27.0 / 105 -> 29.1 / 107     2 x 1300 (352) 31.0 / 122 -> 29.2 / 120
-//   2 x 1700 (448) 39.3 / 154.5 -> 39.1 / 153.8   2 x 2048 (512) 47.3 / 194 -> 46.3 / 189   2 x 2300 (576) 58.8 / 228 -> 62.7 / 234
-//   1 x 2500 (320) 49.5 / 211 -> 39.2 / 193     1 x 4600 (576) 108 / 421 -> 104 / 415       1 x 5600 (704) 142 / 544 -> 143 / 539
-//   8 heads: 1 x 8192 (512) 164 / 681 -> 141 / 634    32 heads: 1 x 2500 (640) 66.5 / 255 -> 71.2 / 263
+// One or two groups of waves per workgroup of the forward kernel.  One lets two workgroups share a CU, which keeps both busy
+// where there are enough of them; two halve the chain of tiles, which is what counts where the workgroups are few or the longest
+// ones run on alone.  Measured, us, 16 heads, causal, one group -> two (workgroups):
+//   4 x 512 (256) 16.8 -> 16.4    8 x 256 (256) 11.7 -> 12.3    5 x 400 (320) 14.1 -> 20.5    2 x 1100 (288) 26.8 -> 22.5
+//   3 x 1024 (384) 27.0 -> 29.1   2 x 1300 (352) 31.0 -> 29.2   2 x 1700 (448) 39.3 -> 39.1   2 x 2048 (512) 47.3 -> 46.3
+//   2 x 2300 (576) 58.8 -> 62.7   1 x 2500 (320) 49.5 -> 39.2   1 x 4096 (512) 85.8 -> 80.1   1 x 5600 (704) 142 -> 143
+//   8 heads: 1 x 8192 (512) 164 -> 141    32 heads: 1 x 2500 (640) 66.5 -> 71.2
+// Workgroups of two leave no room beside them, so where both take about the same time other streams' kernels decide for one
+// (2 x 2048: a step 0.7 % faster with one); dQ, which runs beside the experts' gradients, gains only alone (1 x 4096 355 -> 338
+// us, a step 0.5 % slower) and has one.
 static bool two_groups(int B, int S, int H) {
   const i64 tiles = cdiv(S, 128), workgroups = tiles * B * H;
-  return tiles >= 4 && (workgroups <= 256 + 10 * tiles || (tiles >= 14 && workgroups <= 512));
+  return tiles >= 8 && workgroups <= 256 + 10 * tiles;
 }
 
 int launch_attn_fwd_flash(const void* q, const void* k, const void* v, void* o, float* lse, int B, int S, int H,
@@ -1041,15 +1009,13 @@ int launch_attn_bwd_flash(const void* q, const void* k, const void* v, const voi
   size_t sm2 = 2 * DKV_STAGE;
   static std::atomic<unsigned long long> attr_mask{0};
   if (attr_needed(attr_mask)) {
-    (void)hipFuncSetAttribute((const void*)flash_bwd_dq_k<1>, hipFuncAttributeMaxDynamicSharedMemorySize, DQ_SMEM(1));
-    (void)hipFuncSetAttribute((const void*)flash_bwd_dq_k<2>, hipFuncAttributeMaxDynamicSharedMemorySize, DQ_SMEM(2));
+    (void)hipFuncSetAttribute((const void*)flash_bwd_dq_k, hipFuncAttributeMaxDynamicSharedMemorySize, DQ_SMEM);
     (void)hipFuncSetAttribute((const void*)flash_bwd_dkv_k<1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm2);
     (void)hipFuncSetAttribute((const void*)flash_bwd_dkv_k<2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm2);
     attr_done(attr_mask);
   }
   dim3 grid((unsigned)((i64)H * cdiv(S, 128) * B));
-  const int groups = two_groups(B, S, H) ? 2 : 1;
-  hipLaunchKernelGGL(groups == 2 ? flash_bwd_dq_k<2> : flash_bwd_dq_k<1>, grid, dim3(256 * groups), DQ_SMEM(groups), s, (const bf16*)q, (const bf16*)k,
+  hipLaunchKernelGGL(flash_bwd_dq_k, grid, dim3(256), DQ_SMEM, s, (const bf16*)q, (const bf16*)k,
                      (const bf16*)v, (const bf16*)o, (const bf16*)d_o, lse, dvec, (bf16*)dq, B, S, H, causal, scale);
   if (grid.x <= 256)         // one workgroup on a CU at most (512 of them, 2 x 2048 tokens: QB = 1 135 us, QB = 2 157)
     hipLaunchKernelGGL(flash_bwd_dkv_k<2>, grid, dim3(256), sm2, s, (const bf16*)q, (const bf16*)k, (const bf16*)v,
