@@ -63,30 +63,24 @@ __device__ __forceinline__ void place(int H, int B, int tiles, int per_cu, int* 
 // rows of a transposing read differ in the upper two bits, i.e. in which quarter of the banks their 64 bytes fall.
 // ------------------------------------------------------------------------------------
 __device__ __forceinline__ int swz(int r) { return ((r & 3) << 2) | ((r >> 2) & 3); }
-// 16 rows (4 wave-loads) of the slice, from row0 on, to LDS at dst
-__device__ __forceinline__ void load_rows16_lds(const RowSlice& sl, int row0, unsigned dst, int lane) {
-#pragma unroll
-  for (int i = 0; i < 4; i++) {
-    const int r = i * 4 + (lane >> 4);
-    const unsigned voff = (unsigned)(row0 + r) * sl.ldb + (unsigned)((lane & 15) ^ swz(r)) * 16u;
-    load_lds_b128(sl.rs, __builtin_amdgcn_readfirstlane(dst + i * 1024u), voff);
-  }
+// 16 rows (4 wave-loads) of the slice, from row0 on, to LDS at dst.  What does not change from tile to tile is worked out once and
+// takes two registers: swz(4 i + (lane >> 4)) = swz(lane >> 4) ^ i.
+struct RowOffset { unsigned row, chunk; };
+__device__ __forceinline__ RowOffset row_offset(const RowSlice& sl, int row0, int lane) {
+  return {(unsigned)(row0 + (lane >> 4)) * sl.ldb, (unsigned)((lane & 15) ^ swz(lane >> 4)) * 16u};
 }
-// the same with what does not change from tile to tile worked out once
-__device__ __forceinline__ void row_offsets(const RowSlice& sl, int row0, int lane, unsigned (&off)[4]) {
+__device__ __forceinline__ void load_rows16_lds(const RowSlice& sl, RowOffset at, int row0, unsigned dst) {
+  asm volatile("" : "+v"(at.row), "+v"(at.chunk));  // (the sums below are not worth a register each from tile to tile)
 #pragma unroll
-  for (int i = 0; i < 4; i++) {
-    const int r = i * 4 + (lane >> 4);
-    off[i] = (unsigned)(row0 + r) * sl.ldb + (unsigned)((lane & 15) ^ swz(r)) * 16u;
-  }
+  for (int i = 0; i < 4; i++)
+    load_lds_b128(sl.rs, __builtin_amdgcn_readfirstlane(dst + i * 1024u),
+                  at.row + (at.chunk ^ (i * 16u)) + __builtin_amdgcn_readfirstlane((unsigned)(row0 + i * 4) * sl.ldb));
 }
-__device__ __forceinline__ void load_rows16_lds(const RowSlice& sl, const unsigned (&off)[4], int row0, unsigned dst) {
-  const unsigned add = __builtin_amdgcn_readfirstlane((unsigned)row0 * sl.ldb);
-#pragma unroll
-  for (int i = 0; i < 4; i++) load_lds_b128(sl.rs, __builtin_amdgcn_readfirstlane(dst + i * 1024u), off[i] + add);
-}
-// 64 floats
-__device__ __forceinline__ void load_stats64_lds(__amdgpu_buffer_rsrc_t rs, int row0, unsigned dst, int lane) {
+// 64 floats (the lane number is asked for here: spilled, it would come back through a wait for all loads on their way)
+__device__ __forceinline__ void load_stats64_lds(__amdgpu_buffer_rsrc_t rs, int row0, unsigned dst) {
+  unsigned none = 0;
+  asm volatile("" : "+v"(none));
+  const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, none));
   load_lds_b32(rs, __builtin_amdgcn_readfirstlane(dst), (unsigned)(row0 + lane) * 4u);
 }
 // per-lane byte offsets: 16-byte fragments of rows lane & 31 (k-step kk: ^ kk * 32), transposed ones (column block: ^ dtile * 64)
@@ -208,8 +202,7 @@ __global__ void __launch_bounds__(256 * GROUPS, 2) flash_fwd_k(const bf16* __res
   const RowSlice slK = row_slice(k + boff, ld, S), slV = row_slice(v + boff, ld, S);
   const unsigned char* tiles = smem_raw + (unsigned)grp * 4 * KV_TILE;      // K, V, K, V
   const unsigned lds0 = lds_address(smem_raw) + (unsigned)grp * 4 * KV_TILE + (unsigned)wv * 4096u;
-  unsigned off[4];
-  row_offsets(slK, wv * 16, lane, off);
+  const RowOffset off = row_offset(slK, wv * 16, lane);
   auto issue = [&](const RowSlice& sl, int i, unsigned which) {           // 16 of tile i's rows
     const int t = GROUPS * i + grp;
     load_rows16_lds(sl, off, t < nt ? t * BKV : none, lds0 + ((unsigned)(i & 1) * 2 + which) * KV_TILE);
@@ -413,8 +406,7 @@ __global__ void __launch_bounds__(256, 2) flash_bwd_dq_k(const bf16* __restrict_
   }
   const RowSlice slK = row_slice(k + boff, ld, S), slV = row_slice(v + boff, ld, S);
   const unsigned lds0 = lds_address(smem_raw) + (unsigned)wv * 4096u;
-  unsigned off[4];
-  row_offsets(slK, wv * 16, lane, off);
+  const RowOffset off = row_offset(slK, wv * 16, lane);
   auto issue = [&](const RowSlice& sl, int i, unsigned stage) {           // 16 of tile i's rows; stages K, K, K, V, V
     load_rows16_lds(sl, off, i < nt ? i * BKV : none, lds0 + stage * KV_TILE);
   };
@@ -555,15 +547,18 @@ __global__ void __launch_bounds__(256, QB == 1 ? 2 : 1) flash_bwd_dkv_k(const bf
   const __amdgpu_buffer_rsrc_t rsD = __builtin_amdgcn_make_buffer_rsrc((void*)(dvec + soff), (short)0, S * 4, 0x00020000);
   const unsigned lds0 = lds_address(smem_raw);
   // rows past the end are zeros throughout: whatever their probabilities, they add Q = dO = 0
+  const RowOffset off = row_offset(slQ, wv * 16, lane);
   auto issue = [&](int t, int stage) {
     const unsigned dst = lds0 + (unsigned)stage * DKV_STAGE;
-    load_rows16_lds(slQ, t * BKV + wv * 16, dst + wv * 4096u, lane);
-    load_rows16_lds(slO, t * BKV + wv * 16, dst + 16384u + wv * 4096u, lane);
-    if (wv == 0) load_stats64_lds(rsL, t * BKV, dst + 32768u, lane);
-    if (wv == 1) load_stats64_lds(rsD, t * BKV, dst + 32768u + 256u, lane);
+    load_rows16_lds(slQ, off, t * BKV, dst + wv * 4096u);
+    load_rows16_lds(slO, off, t * BKV, dst + 16384u + wv * 4096u);
+    if (wv == 0) load_stats64_lds(rsL, t * BKV, dst + 32768u);
+    if (wv == 1) load_stats64_lds(rsD, t * BKV, dst + 32768u + 256u);
   };
   const unsigned rbase = swz_row_base(lane), cbase = swz_col_base(lane);
   issue(t_lo, 0);
+  arrived(kf);
+  arrived(vf);
   wait_vmcnt<0>();
   __syncthreads();
   for (int t = t_lo; t < nt; t++) {
@@ -576,68 +571,81 @@ __global__ void __launch_bounds__(256, QB == 1 ? 2 : 1) flash_bwd_dkv_k(const bf
 #pragma unroll 1
     for (int j0 = 0; j0 < 2; j0 += QB) {
       if (causal && q0 + (j0 + QB) * 32 - 1 < kw) continue;    // no query of the block can see a key of this wave
+      // (addresses are worked out where they are used: kept for all k-steps they cost the registers that are short here)
+      unsigned rb = rbase + (unsigned)(j0 * 8192), cb = cbase;
+      asm volatile("" : "+v"(rb), "+v"(cb));
       f32x16 s[QB], dp[QB];
-#pragma unroll
-      for (int j = 0; j < QB; j++)
-#pragma unroll
-        for (int e = 0; e < 16; e++) { s[j][e] = 0.f; dp[j][e] = 0.f; }
-#pragma unroll
-      for (int kk = 0; kk < 8; kk++)
+      bf16x8 f[2][QB * 2];
+      auto read_rows = [&](bf16x8 (&x)[QB * 2], int kk) {
 #pragma unroll
         for (int j = 0; j < QB; j++) {
-          const unsigned at = (unsigned)((j0 + j) * 32 * 256) + (rbase ^ (unsigned)(kk * 32));
-          s[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(cQ + at), kf[kk], s[j], 0, 0, 0);
-          dp[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(cO + at), vf[kk], dp[j], 0, 0, 0);
+          const unsigned at = (unsigned)(j * 8192) + (rb ^ (unsigned)(kk * 32));
+          x[j * 2] = *(const bf16x8*)(cQ + at);
+          x[j * 2 + 1] = *(const bf16x8*)(cO + at);
         }
-      if (QB == 1) __builtin_amdgcn_sched_barrier(0);
-      const bool need_mask = causal && (q0 + j0 * 32 < kw + 31);     // some query of the block precedes some key of the wave
+      };
 #pragma unroll
-      for (int j = 0; j < QB; j++)
+      for (int j = 0; j < QB; j++) { s[j] = f32x16{}; dp[j] = f32x16{}; }
+      read_rows(f[0], 0);
+#pragma unroll
+      for (int kk = 0; kk < 8; kk++) {
+        if (kk < 7) read_rows(f[(kk + 1) & 1], kk + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < QB; j++) {
+          s[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[kk & 1][j * 2], kf[kk], s[j], 0, 0, 0);
+          dp[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[kk & 1][j * 2 + 1], vf[kk], dp[j], 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      bf16x8 pf[QB * 2], dsf[QB * 2];
+#pragma unroll
+      for (int j = 0; j < QB; j++) {
 #pragma unroll
         for (int eb = 0; eb < 4; eb++) {
-          const int r0 = (j0 + j) * 32 + eb * 8 + g * 4;        // 4 consecutive query rows inside the tile
-          const float4 l4 = *(const float4*)(cL + r0), d4 = *(const float4*)(cD + r0);
-          const float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dv4[4] = {d4.x, d4.y, d4.z, d4.w};
+          const float4 l4 = *(const float4*)(cL + (j0 + j) * 32 + eb * 8 + g * 4);   // 4 consecutive query rows inside the tile
+          const float lv[4] = {l4.x, l4.y, l4.z, l4.w};
 #pragma unroll
-          for (int i = 0; i < 4; i++) {
-            const int e = eb * 4 + i;
-            float p = fast_exp2(s[j][e] * sl2 - lv[i] * LOG2E);
-            if (need_mask && mykv > q0 + r0 + i) p = 0.f;
-            dp[j][e] = p * (dp[j][e] - dv4[i]) * scale;         // dS
-            s[j][e] = p;                                        // P
-          }
+          for (int i = 0; i < 4; i++) s[j][eb * 4 + i] = fast_exp2(s[j][eb * 4 + i] * sl2 - lv[i] * LOG2E);      // P
         }
-      if (QB == 1) __builtin_amdgcn_sched_barrier(0);
+        const int before = mykv - q0 - (j0 + j) * 32 - g * 4;         // queries that precede this lane's key
+        if (causal && q0 + (j0 + j) * 32 < kw + 31) {
 #pragma unroll
-      for (int j = 0; j < QB; j++)
-#pragma unroll
-        for (int c = 0; c < 2; c++) {
-          bf16x8 pf = acc_to_frag(s[j], c);
-          bf16x8 dsf = acc_to_frag(dp[j], c);
-#pragma unroll
-          for (int dtile = 0; dtile < 4; dtile++) {
-            dvacc[dtile] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(swz_cols(cO, cbase, (j0 + j) * 32 + c * 16, dtile), pf, dvacc[dtile], 0, 0, 0);
-            dkacc[dtile] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(swz_cols(cQ, cbase, (j0 + j) * 32 + c * 16, dtile), dsf, dkacc[dtile], 0, 0, 0);
-          }
+          for (int e = 0; e < 16; e++)
+            if ((e >> 2) * 8 + (e & 3) < before) s[j][e] = 0.f;
         }
+#pragma unroll
+        for (int eb = 0; eb < 4; eb++) {
+          const float4 d4 = *(const float4*)(cD + (j0 + j) * 32 + eb * 8 + g * 4);
+          const float dv4[4] = {d4.x, d4.y, d4.z, d4.w};
+#pragma unroll
+          for (int i = 0; i < 4; i++) dp[j][eb * 4 + i] = s[j][eb * 4 + i] * (dp[j][eb * 4 + i] - dv4[i]);     // dS, without scale
+        }
+#pragma unroll
+        for (int c = 0; c < 2; c++) { pf[j * 2 + c] = acc_to_frag(s[j], c); dsf[j * 2 + c] = acc_to_frag(dp[j], c); }
+      }
+      // dO^T P and Q^T dS by turns, 16 queries each, the next fragments read while these are multiplied
+      bf16x8 x[2][4];
+      read_cols(x[0], cO + j0 * 8192, cb, 0);
+#pragma unroll
+      for (int c = 0; c < QB * 4; c++) {
+        if (c + 1 < QB * 4) read_cols(x[(c + 1) & 1], (c & 1 ? cO : cQ) + j0 * 8192, cb, (c + 1) >> 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int d = 0; d < 4; d++) {
+          if (c & 1) dkacc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[c & 1][d], dsf[c >> 1], dkacc[d], 0, 0, 0);
+          else dvacc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[c & 1][d], pf[c >> 1], dvacc[d], 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
     // this wave's part of the next tile has landed, and its reads of this one have returned
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __syncthreads();
   }
   if (mykv < S) {
-    bf16* pk = dk + boff + (i64)mykv * ld;
-    bf16* pv = dv + boff + (i64)mykv * ld;
-#pragma unroll
-    for (int dtile = 0; dtile < 4; dtile++)
-#pragma unroll
-      for (int jj = 0; jj < 4; jj++) {
-        bf16x4 a, c2;
-#pragma unroll
-        for (int i = 0; i < 4; i++) { a[i] = (__bf16)dkacc[dtile][jj * 4 + i]; c2[i] = (__bf16)dvacc[dtile][jj * 4 + i]; }
-        *(bf16x4*)(pk + dtile * 32 + jj * 8 + g * 4) = a;
-        *(bf16x4*)(pv + dtile * 32 + jj * 8 + g * 4) = c2;
-      }
+    store_cols(dk + boff + (i64)mykv * ld, dkacc, scale, g);
+    store_cols(dv + boff + (i64)mykv * ld, dvacc, 1.0f, g);
   }
 }
 
@@ -651,24 +659,71 @@ __global__ void __launch_bounds__(256, QB == 1 ? 2 : 1) flash_bwd_dkv_k(const bf
 // ------------------------------------------------------------------------------------
 #define SHORT_TILE 8192u                          // 32 rows x 256 bytes, swizzled
 #define SHORT_SMEM (4 * 2 * SHORT_TILE + 2048)    // the waves' tiles (then their partial results), then statistics
-__device__ __forceinline__ void load_rows32_lds(const RowSlice& sl, int row0, unsigned dst, int lane) {
-  load_rows16_lds(sl, row0, dst, lane);
-  load_rows16_lds(sl, row0 + 16, dst + 4096u, lane);
+__device__ __forceinline__ void load_rows32_lds(const RowSlice& sl, RowOffset at, int row0, unsigned dst) {
+  load_rows16_lds(sl, at, row0, dst);
+  load_rows16_lds(sl, at, row0 + 16, dst + 4096u);
 }
 // tile rows x fragments: element e of lane l is tile row (e >> 2) * 8 + (l >> 5) * 4 + (e & 3), column l & 31
 __device__ __forceinline__ f32x16 rows_times(const unsigned char* tile, unsigned rbase, const bf16x8 (&f)[8]) {
   f32x16 a = {};
+  bf16x8 x[8];
 #pragma unroll
-  for (int kk = 0; kk < 8; kk++) a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(tile + (rbase ^ (unsigned)(kk * 32))), f[kk], a, 0, 0, 0);
+  for (int kk = 0; kk < 8; kk++) x[kk] = *(const bf16x8*)(tile + (rbase ^ (unsigned)(kk * 32)));
+  __builtin_amdgcn_sched_barrier(0);                // (or each product would wait for a read of its own)
+#pragma unroll
+  for (int kk = 0; kk < 8; kk++) a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[kk], f[kk], a, 0, 0, 0);
   return a;
 }
-// acc^T[column, lane] += tile^T p
+// two of them, the next fragments read while these are multiplied
+__device__ __forceinline__ void rows_times2(f32x16& a, f32x16& b, const unsigned char* ta, const unsigned char* tb, unsigned rbase,
+                                            const bf16x8 (&fa)[8], const bf16x8 (&fb)[8]) {
+  asm volatile("" : "+v"(rbase));                   // (eight addresses kept from tile to tile cost the registers that are short)
+  bf16x8 x[2][2];
+  auto read = [&](bf16x8 (&y)[2], int kk) {
+    y[0] = *(const bf16x8*)(ta + (rbase ^ (unsigned)(kk * 32)));
+    y[1] = *(const bf16x8*)(tb + (rbase ^ (unsigned)(kk * 32)));
+  };
+  a = f32x16{};
+  b = f32x16{};
+  read(x[0], 0);
+#pragma unroll
+  for (int kk = 0; kk < 8; kk++) {
+    if (kk < 7) read(x[(kk + 1) & 1], kk + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[kk & 1][0], fa[kk], a, 0, 0, 0);
+    b = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[kk & 1][1], fb[kk], b, 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+// acc^T[column, lane] += tile^T p for a tile of 32 rows
 __device__ __forceinline__ void cols_times(f32x16 (&acc)[4], const unsigned char* tile, unsigned cbase, const f32x16& p) {
+  bf16x8 x[2][4];
+#pragma unroll
+  for (int c = 0; c < 2; c++) read_cols(x[c], tile, cbase, c);
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int c = 0; c < 2; c++) {
     const bf16x8 f = acc_to_frag(p, c);
 #pragma unroll
-    for (int dtile = 0; dtile < 4; dtile++) acc[dtile] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(swz_cols(tile, cbase, c * 16, dtile), f, acc[dtile], 0, 0, 0);
+    for (int dtile = 0; dtile < 4; dtile++) acc[dtile] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[c][dtile], f, acc[dtile], 0, 0, 0);
+  }
+}
+// a += ta^T pa and b += tb^T pb by turns, 16 rows each, the next fragments read while these are multiplied
+__device__ __forceinline__ void cols_times2(f32x16 (&a)[4], f32x16 (&b)[4], const unsigned char* ta, const unsigned char* tb, unsigned cbase,
+                                            const bf16x8 (&pa)[2], const bf16x8 (&pb)[2]) {
+  asm volatile("" : "+v"(cbase));
+  bf16x8 x[2][4];
+  read_cols(x[0], ta, cbase, 0);
+#pragma unroll
+  for (int c = 0; c < 4; c++) {
+    if (c < 3) read_cols(x[(c + 1) & 1], c & 1 ? ta : tb, cbase, (c + 1) >> 1);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int d = 0; d < 4; d++) {
+      if (c & 1) b[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[c & 1][d], pb[c >> 1], b[d], 0, 0, 0);
+      else a[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[c & 1][d], pa[c >> 1], a[d], 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
   }
 }
 // a wave's partial result to its 16 KiB: [column 128][row 32]
@@ -703,14 +758,16 @@ __global__ void __launch_bounds__(256, 2) flash_fwd_short_k(const bf16* __restri
   if (row_skip && !__any(myq < S && row_skip[(i64)b * S + myq] == 0)) return;      // (the same answer in every wave)
   const i64 ld = (i64)H * DH, boff = (i64)b * S * ld + hh * DH;
   const RowSlice slK = row_slice(k + boff, ld, S), slV = row_slice(v + boff, ld, S);
+  const RowOffset off = row_offset(slK, 0, lane);
   unsigned char* tK = smem_raw + wv * 2 * SHORT_TILE;
   const unsigned aK = lds_address(smem_raw) + (unsigned)wv * 2 * SHORT_TILE, aV = aK + SHORT_TILE;
   const int nt = ((causal ? min(S, q0 + 32) : S) + 31) / 32;
   const int none = tiles * 32;                      // (a tile that is not there: rows past the end, zeros without traffic)
-  load_rows32_lds(slK, wv < nt ? wv * 32 : none, aK, lane);
-  load_rows32_lds(slV, wv < nt ? wv * 32 : none, aV, lane);
+  load_rows32_lds(slK, off, wv < nt ? wv * 32 : none, aK);
+  load_rows32_lds(slV, off, wv < nt ? wv * 32 : none, aV);
   bf16x8 qf[8];
   load_frags(q + boff, ld, myq, S, g, qf);
+  arrived(qf);
   const unsigned rbase = swz_row_base(lane), cbase = swz_col_base(lane);
   const float sl2 = scale * LOG2E;
   f32x16 acc[4] = {};
@@ -722,7 +779,7 @@ __global__ void __launch_bounds__(256, 2) flash_fwd_short_k(const bf16* __restri
     f32x16 s = rows_times(tK, rbase, qf);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
-    load_rows32_lds(slK, next, aK, lane);
+    load_rows32_lds(slK, off, next, aK);
     float mx = -INFINITY;
     const bool need_mask = kv0 + 32 > S || (causal && kv0 + 31 > q0);
 #pragma unroll
@@ -751,7 +808,7 @@ __global__ void __launch_bounds__(256, 2) flash_fwd_short_k(const bf16* __restri
     cols_times(acc, tK + SHORT_TILE, cbase, s);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
-    load_rows32_lds(slV, next, aV, lane);
+    load_rows32_lds(slV, off, next, aV);
   }
   wait_vmcnt<0>();
   float* stats = (float*)(smem_raw + 8 * SHORT_TILE);
@@ -779,28 +836,32 @@ __device__ __forceinline__ void short_dq(unsigned char* smem_raw, int tile, int 
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 5, myq = q0 + (lane & 31);
   const i64 ld = (i64)H * DH, boff = (i64)b * S * ld + hh * DH, soff = ((i64)b * H + hh) * S;
   const RowSlice slK = row_slice(k + boff, ld, S), slV = row_slice(v + boff, ld, S);
+  const RowOffset off = row_offset(slK, 0, lane);
   unsigned char* tK = smem_raw + wv * 2 * SHORT_TILE;
   const unsigned aK = lds_address(smem_raw) + (unsigned)wv * 2 * SHORT_TILE, aV = aK + SHORT_TILE;
   const int nt = ((causal ? min(S, q0 + 32) : S) + 31) / 32;
   if (wv < nt) {
-    load_rows32_lds(slV, wv * 32, aV, lane);
-    load_rows32_lds(slK, wv * 32, aK, lane);
+    load_rows32_lds(slV, off, wv * 32, aV);
+    load_rows32_lds(slK, off, wv * 32, aK);
   }
   bf16x8 qf[8], dof[8];
   load_frags(q + boff, ld, myq, S, g, qf);
   load_frags(d_o + boff, ld, myq, S, g, dof);
-  const float L = myq < S ? lse[soff + myq] * LOG2E : 0.f, D = myq < S ? dvec[soff + myq] : 0.f;
+  float L = myq < S ? lse[soff + myq] * LOG2E : 0.f, D = myq < S ? dvec[soff + myq] : 0.f;
+  arrived(qf);
+  arrived(dof);
+  asm volatile("" : "+v"(L), "+v"(D));
   const unsigned rbase = swz_row_base(lane), cbase = swz_col_base(lane);
   const float sl2 = scale * LOG2E;
   f32x16 acc[4] = {};
   for (int t = wv; t < nt; t += 4) {
     const int kv0 = t * 32;
     wait_vmcnt<0>();
-    f32x16 dp = rows_times(tK + SHORT_TILE, rbase, dof);
-    f32x16 s = rows_times(tK, rbase, qf);
+    f32x16 dp, s;
+    rows_times2(dp, s, tK + SHORT_TILE, tK, rbase, dof, qf);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
-    if (t + 4 < nt) load_rows32_lds(slV, kv0 + 128, aV, lane);
+    if (t + 4 < nt) load_rows32_lds(slV, off, kv0 + 128, aV);
     const bool need_mask = kv0 + 32 > S || (causal && kv0 + 31 > q0);
 #pragma unroll
     for (int e = 0; e < 16; e++) {
@@ -812,7 +873,7 @@ __device__ __forceinline__ void short_dq(unsigned char* smem_raw, int tile, int 
     cols_times(acc, tK, cbase, s);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
-    if (t + 4 < nt) load_rows32_lds(slK, kv0 + 128, aK, lane);
+    if (t + 4 < nt) load_rows32_lds(slK, off, kv0 + 128, aK);
   }
   put_partial((float*)tK, acc, lane);
   __syncthreads();
@@ -828,6 +889,7 @@ __device__ __forceinline__ void short_dkv(unsigned char* smem_raw, int tile, int
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 5, mykv = k0 + (lane & 31);
   const i64 ld = (i64)H * DH, boff = (i64)b * S * ld + hh * DH, soff = ((i64)b * H + hh) * S;
   const RowSlice slQ = row_slice(q + boff, ld, S), slO = row_slice(d_o + boff, ld, S);
+  const RowOffset off = row_offset(slQ, 0, lane);
   const __amdgpu_buffer_rsrc_t rsL = __builtin_amdgcn_make_buffer_rsrc((void*)(lse + soff), (short)0, S * 4, 0x00020000);
   const __amdgpu_buffer_rsrc_t rsD = __builtin_amdgcn_make_buffer_rsrc((void*)(dvec + soff), (short)0, S * 4, 0x00020000);
   unsigned char* tQ = smem_raw + wv * 2 * SHORT_TILE;
@@ -836,26 +898,28 @@ __device__ __forceinline__ void short_dkv(unsigned char* smem_raw, int tile, int
   float* st = (float*)(smem_raw + 8 * SHORT_TILE) + wv * 128;
   const unsigned aS = lds_address(smem_raw) + 8 * SHORT_TILE + (unsigned)wv * 512u;
   auto stats = [&](int row0) {
-    load_stats64_lds(rsL, row0, aS, lane);
-    load_stats64_lds(rsD, row0, aS + 256u, lane);
+    load_stats64_lds(rsL, row0, aS);
+    load_stats64_lds(rsD, row0, aS + 256u);
   };
   const int t0 = (causal ? tile : 0) + wv;
   if (t0 < nt) {
-    load_rows32_lds(slQ, t0 * 32, aQ, lane);
-    load_rows32_lds(slO, t0 * 32, aO, lane);
+    load_rows32_lds(slQ, off, t0 * 32, aQ);
+    load_rows32_lds(slO, off, t0 * 32, aO);
     stats(t0 * 32);
   }
   bf16x8 kf[8], vf[8];
   load_frags(k + boff, ld, mykv, S, g, kf);
   load_frags(v + boff, ld, mykv, S, g, vf);
+  arrived(kf);
+  arrived(vf);
   const unsigned rbase = swz_row_base(lane), cbase = swz_col_base(lane);
   const float sl2 = scale * LOG2E;
   f32x16 dka[4] = {}, dva[4] = {};
   for (int t = t0; t < nt; t += 4) {
     const int q0 = t * 32;
     wait_vmcnt<0>();
-    f32x16 s = rows_times(tQ, rbase, kf);
-    f32x16 dp = rows_times(tQ + SHORT_TILE, rbase, vf);
+    f32x16 s, dp;
+    rows_times2(s, dp, tQ, tQ + SHORT_TILE, rbase, kf, vf);
     const bool need_mask = causal && q0 < k0 + 31;
 #pragma unroll
     for (int eb = 0; eb < 4; eb++) {
@@ -871,13 +935,15 @@ __device__ __forceinline__ void short_dkv(unsigned char* smem_raw, int tile, int
         s[e] = p;
       }
     }
-    cols_times(dva, tQ + SHORT_TILE, cbase, s);
-    cols_times(dka, tQ, cbase, dp);
+    bf16x8 pf[2], dsf[2];
+#pragma unroll
+    for (int c = 0; c < 2; c++) { pf[c] = acc_to_frag(s, c); dsf[c] = acc_to_frag(dp, c); }
+    cols_times2(dva, dka, tQ + SHORT_TILE, tQ, cbase, pf, dsf);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
     if (t + 4 < nt) {
-      load_rows32_lds(slQ, q0 + 128, aQ, lane);
-      load_rows32_lds(slO, q0 + 128, aO, lane);
+      load_rows32_lds(slQ, off, q0 + 128, aQ);
+      load_rows32_lds(slO, off, q0 + 128, aO);
       stats(q0 + 128);
     }
   }
