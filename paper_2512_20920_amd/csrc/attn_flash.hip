@@ -495,14 +495,16 @@ __global__ void __launch_bounds__(256, 2) flash_bwd_dq_k(const bf16* __restrict_
 // ------------------------------------------------------------------------------------
 // Backward, part 2: dK and dV.  Workgroup = 128 keys, wave = 32 keys (one per lane column);
 // queries (with dO, lse, D) streamed in tiles of 64, starting at the diagonal when causal.
-//   S = Q K^T,  P = exp(S*scale - lse),  dP = dO V^T,  dS = P (dP - D) scale,
-//   dV^T += dO^T P,   dK^T += Q^T dS.
-// Tiles go straight to LDS.  Accumulators and the wave's K and V take 192 registers, so with the queries of a tile worked on
-// QB = 1 block of 32 at a time two workgroups fit on a CU, and one wave's exponentials run beside the other's products:
-// 8192 tokens, 16 heads: 885 -> 620 us (against one wave per SIMD, 64 queries at a time, tiles staged through registers).
-// A grid that has one workgroup per CU at most gains nothing from that; there QB = 2, 64 queries at a time, leaves the
-// compiler more to overlap inside the wave: 4 x 512 tokens, 16 heads: 39.1 -> 35.8 us, 2048: 115 -> 102, 3 x 333: 29.1 -> 27.0.
-// Both add the queries in the same order, so the results have the same bits.
+//   S = Q K^T,  P = exp(S*scale - lse),  dP = dO V^T,  dS = P (dP - D),
+//   dV^T += dO^T P,   dK^T += Q^T dS,  times scale at the end.
+// Four products against one exponential: bound by the matrix cores.  Accumulators and the wave's K and V take 192 registers, so with
+// the queries of a tile worked on QB = 1 block of 32 at a time two workgroups fit on a CU, and one wave's exponentials run beside
+// the other's products.  A grid that has one workgroup per CU at most gains nothing from that; there QB = 2, 64 queries at a time,
+// leaves more to overlap inside the wave.  All of the backward pass, us, 16 heads, QB = 1 -> 2: 4 x 512 50.1 -> 49.1, 1 x 2048 128.9
+// -> 126.2, 2 x 2048 158 -> 172, 1 x 8192 918 -> 962.  Both add the queries in the same order, so the results have the same bits.
+// Fragments are read one step ahead of their products, addresses are worked out where they are used, and nothing is spilled inside
+// the loop (a register that is comes back through a wait for every tile on its way): all of the backward pass 8192 tokens 942 ->
+// 880 us, 2 x 2048 192 -> 153, 4 x 512 58 -> 46.
 // ------------------------------------------------------------------------------------
 #define DKV_STAGE (2 * 64 * 256 + 2 * 256)      // Q, dO, lse, D
 template <int QB>
@@ -653,7 +655,8 @@ __global__ void __launch_bounds__(256, QB == 1 ? 2 : 1) flash_bwd_dkv_k(const bf
 // Short sequences.  With 128 queries (keys) per workgroup a short sequence leaves most CUs idle or gives each one chain over
 // all its key tiles: one wave per SIMD whose products, exponentials and loads follow each other.  Here a workgroup is 32
 // queries (keys) and its 4 waves share the keys (queries) out, tile w, w + 4, .. of 32, each in LDS of its own that no other
-// wave touches, so nothing waits at a barrier until the waves' partial results meet in LDS in wave order.  A wave's two
+// wave touches, so nothing waits at a barrier until the waves' partial results meet in LDS in wave order; fragments are read ahead
+// of their products as above (2 x 1024 tokens, 16 heads, backward 80 -> 72 us, 1 x 1024 forward 18.2 -> 16.8).  A wave's two
 // tiles (K and V, or Q and dO) are 16 KiB, two workgroups share a CU.  Every wave loads its tiles itself, four times the
 // traffic of the kernels above, which is what bounds this form once it fills the chip.  dQ and dK/dV are one launch.
 // ------------------------------------------------------------------------------------
@@ -987,26 +990,28 @@ __global__ void __launch_bounds__(256, 2) flash_bwd_short_k(const bf16* __restri
 }
 
 // Which form a problem takes.  Measured, us, forward / all of the backward pass, 128 queries per workgroup -> 32:
-//   16 heads: 1 x 128 9.5 / 27 -> 8.0 / 12    3 x 333 15 / 52 -> 13 / 33    1 x 1024 30 / 104 -> 18 / 42    1 x 2048 56 / 195 -> 39 / 120
-//             4 x 512 19.7 / 69 -> 19.6 / 60    8 x 256 14 / 50 -> 17 / 55    16 x 128 11 / 40 -> 15 / 47    8 x 512 24 / 95 -> 38 / 131
-//   4 heads: 2 x 200 11 / 36 -> 8.4 / 13    1 x 2048 52 / 186 -> 24 / 43    32 heads: 1 x 1024 33 / 115 -> 26 / 74    4 x 256 14 / 49 -> 16 / 49
-// Alone it pays up to two workgroups per CU and up to four for long chains.  Inside a step, where the attention shares the chip
-// with the routed experts, CU time counts too: 4 x 512 tokens 2793 -> 2820 us per step, 1 x 1024 2190 -> 2158, 1 x 1300 2460 ->
-// 2438, so the line is at 1024 tokens of 16 heads, 2048 from 1024 positions on, with the heads counted coarsely and more than
-// 16 as 18.
+//   16 heads: 1 x 256 10.8 / 29 -> 7.9 / 13    1 x 512 15.0 / 42 -> 10.1 / 19    2 x 400 13.0 / 38 -> 11.5 / 27    3 x 333 12.3 / 36 -> 13.0 / 30
+//             2 x 512 15.5 / 43 -> 12.0 / 30   1 x 1024 20.4 / 70 -> 16.4 / 41   1 x 1536 26.7 / 97 -> 26.5 / 69   2 x 1024 21.4 / 72 -> 27.0 / 72
+//             1 x 2048 33.7 / 125 -> 39.5 / 105
+//   8 heads: 1 x 2048 31.5 / 122 -> 26.4 / 56    4 heads: 4 x 1024 19.9 / 68 -> 16.3 / 42    32 heads: 1 x 1024 21.7 / 72 -> 26.2 / 67
+// Alone 32 queries pay further up than inside a step, where the attention shares the chip with the experts' weight gradients and
+// the CU time counts, of which they take more.  16 heads, us per step, 128 queries always -> 32 at both: 1 x 512 1486.6 -> 1487.4,
+// 1 x 1024 1872 -> 1886, 1 x 1600 2280 -> 2324, 1 x 2048 2813 -> 2891; adapters only, with little beside the attention, 3 x 333
+// 1578 -> 1573; merged passes, forward only, 1 x 512 472 -> 465, 1 x 1024 535.5 -> 529.8, 1 x 2048 792 -> 807; 4 heads, 2 x 1024
+// 566 -> 518.  So the line is at 1024 tokens of 16 heads, backward 1280 from 1024 positions on, with the heads counted coarsely and
+// more than 16 as 18.
 // Many heads fill the chip with few tokens, so from there on a second line bounds tokens x heads, in tokens of 16 heads (work).
-// Measured, us, two forward passes and a backward one, 128 queries -> 32 (heads, tokens: work):
-//   20, 1 x 1024: 1280 168 -> 93    48, 1 x 1024: 3072 197 -> 191    64, 1 x 1024: 4096 204 -> 244    128, 1 x 1024: 8192 330 -> 536
+// Measured, us, two forward passes and a backward one, 128 queries (an earlier kernel, a fifth slower) -> 32 (heads, tokens: work):
 //   64, 1 x 512: 2048 105 -> 96    48, 2 x 512: 3072 128 -> 143    128, 1 x 512: 4096 137 -> 188
 //   32, 3 x 256: 1536 70 -> 69    32, 4 x 256: 2048 73 -> 80    64, 4 x 256: 4096 109 -> 156
 //   64, 2 x 128: 1024 49 -> 41    48, 4 x 128: 1536 54 -> 59    64, 4 x 128: 2048 59 -> 70
 //   40, 4 x 64: 640 35 -> 34    48, 4 x 64: 768 35 -> 38    64, 8 x 64: 2048 51 -> 67
 // The two forms add in different orders.  A call on some of the heads takes the short form wherever the call on all of them does,
-// and gives the same bits then; where all of them take the long form, some alone need not.
-static bool short_sequence(int B, int S, int H) {
+// and gives the same bits then; where all of them take the long form, some alone need not.  Two groups of waves add in yet another.
+static bool short_sequence(int B, int S, int H, int most) {
   const i64 tokens = (i64)B * S, load = tokens * (H <= 4 ? 4 : H <= 8 ? 8 : H <= 16 ? 16 : 18) / 16;
-  if (S > 2048 || load > (S >= 1024 ? 2048 : 1024)) return false;
-  return H <= 16 || tokens * H <= 16 * (S >= 1024 ? 3072 : S >= 448 ? 2752 : S >= 256 ? 1856 : S >= 128 ? 1344 : 768);
+  if (S > 2048 || load > most) return false;
+  return H <= 16 || tokens * H <= 16 * (S >= 448 ? 2752 : S >= 256 ? 1856 : S >= 128 ? 1344 : 768);
 }
 
 // One or two groups of waves per workgroup of the forward kernel.  One lets two workgroups share a CU, which keeps both busy
@@ -1029,7 +1034,7 @@ int launch_attn_fwd_flash(const void* q, const void* k, const void* v, void* o, 
   if (dh != DH || B <= 0 || S <= 0) return 1;
   if ((i64)S * H * DH * 2 >= ((i64)1 << 31)) return 1;      // one sequence of one tensor is addressed with 32-bit offsets
   if (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o) & 15) return 1;
-  if (short_sequence(B, S, H)) {
+  if (short_sequence(B, S, H, 1024)) {
     static std::atomic<unsigned long long> attr_mask{0};
     if (attr_needed(attr_mask)) {
       (void)hipFuncSetAttribute((const void*)flash_fwd_short_k, hipFuncAttributeMaxDynamicSharedMemorySize, SHORT_SMEM);
@@ -1060,7 +1065,7 @@ int launch_attn_bwd_flash(const void* q, const void* k, const void* v, const voi
        (uintptr_t)dv) & 15)
     return 1;
   const float scale = 1.0f / sqrtf((float)dh);
-  if (short_sequence(B, S, H)) {
+  if (short_sequence(B, S, H, S >= 1024 ? 1280 : 1024)) {
     const i64 rows = (i64)B * S * H;
     hipLaunchKernelGGL(flash_dvec_k, dim3((unsigned)cdiv(rows, 16)), dim3(256), 0, s, (const bf16*)o, (const bf16*)d_o, dvec, S, H, rows);
     static std::atomic<unsigned long long> attr_mask{0};
@@ -1083,7 +1088,7 @@ int launch_attn_bwd_flash(const void* q, const void* k, const void* v, const voi
   dim3 grid((unsigned)((i64)H * cdiv(S, 128) * B));
   hipLaunchKernelGGL(flash_bwd_dq_k, grid, dim3(256), DQ_SMEM, s, (const bf16*)q, (const bf16*)k,
                      (const bf16*)v, (const bf16*)o, (const bf16*)d_o, lse, dvec, (bf16*)dq, B, S, H, causal, scale);
-  if (grid.x <= 256)         // one workgroup on a CU at most (512 of them, 2 x 2048 tokens: QB = 1 135 us, QB = 2 157)
+  if (grid.x <= 256)         // one workgroup on a CU at most
     hipLaunchKernelGGL(flash_bwd_dkv_k<2>, grid, dim3(256), sm2, s, (const bf16*)q, (const bf16*)k, (const bf16*)v,
                        (const bf16*)d_o, lse, dvec, (bf16*)dk, (bf16*)dv, B, S, H, causal, scale);
   else

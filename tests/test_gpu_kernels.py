@@ -90,12 +90,16 @@ def test_few_rows_gemm(layout, M, N, K):
         assert torch.isnan(cd[M]).all()                       # nothing past the last row
 
 
-def _attention_case(B, S, H, dh, causal, mode, dtype, offset=0):
+def _attention_case(B, S, H, dh, causal, mode, dtype, offset=0, rise=0.0):
     rng = np.random.default_rng(S * 31 + H + (7 if causal else 0))
     rnd = (lambda s, sc=1.0: _bf(rng, s, sc)) if dtype == 1 else \
           (lambda s, sc=1.0: (sc * rng.standard_normal(s)).astype(np.float32).astype(np.float64))
     d = H * dh
     q, k, v, do = rnd((B * S, d), 1.5), rnd((B * S, d), 1.5), rnd((B * S, d)), rnd((B * S, d))
+    if rise:              # scores that rise by `rise` powers of two from one tile of 64 keys to the next, half way, then fall
+        u = rng.choice((-1.0, 1.0), d)
+        ramp = rise / 64 * np.log(2.0) / np.sqrt(dh) * np.minimum(np.arange(S), S - np.arange(S))
+        q, k = (synth.round_bf16(a.astype(np.float32)) for a in (q + u, k + np.tile(ramp, B)[:, None] * u))
     r4 = lambda a: a.reshape(B, S, H, dh)
     if S > 2048:          # long sequences: one S x S matrix in flight instead of a stored probability tensor
         o_ref, _ = O.attention_core(r4(q), r4(k), r4(v), causal, keep_probs=False)
@@ -151,6 +155,14 @@ def test_flash_attention_ragged_long_sequence():
     _attention_case(1, 2500, 2, 128, True, 2, 1)
 
 
+# 128 queries per workgroup: one and two groups of waves (eight and more tiles), an odd and an even number of key tiles, the last of
+# one key, 63 and 64; the running maximum is raised by less and by more than the step that the kernel lets pass, and not at all
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("B,S,H,rise", [(1, 2049, 2, 3.0), (1, 2111, 1, 11.0), (1, 1216, 17, 0.0), (3, 705, 16, 3.0), (3, 448, 16, 11.0)])
+def test_flash_attention_key_tiles(B, S, H, rise, causal):
+    _attention_case(B, S, H, 128, causal, 2, 1, rise=rise)
+
+
 @pytest.mark.parametrize("dtype,dh", [(0, 16), (1, 32), (0, 80)])
 def test_generic_attention(dtype, dh):
     _attention_case(2, 70, 3, dh, True, 1, dtype)
@@ -167,7 +179,7 @@ def test_vector_attention(dtype, dh, offset):
 
 # 128 queries per workgroup, more workgroups than CUs and no more than two for each: the second part of the grid runs in
 # reverse (16 and 24 heads: a whole and a broken row of heads where it starts; 100 heads: three tiles each); 48 heads of 2 x 451
-# tokens: 32 queries per workgroup
+# tokens: 32 queries per workgroup forward; 16 and 24 heads: two groups of waves forward
 @pytest.mark.parametrize("B,S,H", [(2, 451, 48), (1, 300, 100), (1, 2200, 16), (1, 2100, 24)])
 def test_flash_attention_paired_tiles(B, S, H):
     _attention_case(B, S, H, 128, True, 2, 1)
