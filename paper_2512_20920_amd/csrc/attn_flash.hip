@@ -123,9 +123,9 @@ __device__ __forceinline__ void arrived(bf16x8 (&f)[8]) {
 // GROUPS = 1: 4 waves, two workgroups on a CU.  GROUPS = 2: two groups of 4 waves with the same queries, group 0 on the even
 // tiles and group 1 on the odd ones, half an iteration apart (one wave of each on a SIMD: one multiplies while the other
 // doesn't); their partial results meet in LDS at the end.  two_groups() has the rule.
-// Bound by the power limit where the grid is large: 8192 tokens, 16 heads, 1.08 PFLOP/s on random values, 1.3 on zeros.
-// Against tiles staged through registers and fragments read just before use, us: 1 x 8192 319 -> 254, 2 x 2048 59 -> 46,
-// 4 x 512 20 -> 16.5, 1 x 4096 105 -> 77, 64 x 128 31.7 -> 31.1.
+// Bound by the power limit where the grid is large: 8192 tokens, 16 heads, 0.97 PFLOP/s on random values, a third more on zeros.
+// Against tiles staged through registers and fragments read just before use, us: 1 x 8192 332 -> 284, 1 x 4096 109 -> 84, 2 x 2048
+// 59 -> 51, 4 x 512 20.1 -> 17.8, 64 x 128 32.1 -> 31.5.
 // ------------------------------------------------------------------------------------
 #define KV_TILE 16384u                            // 64 rows x 256 bytes, swizzled
 #define FWD_SMEM(GROUPS) ((GROUPS) * 4 * KV_TILE) // two stages of K and V per group; the partial results at the end
@@ -268,9 +268,9 @@ __global__ void __launch_bounds__(256 * GROUPS, 2) flash_fwd_k(const bf16* __res
 #pragma unroll
     for (int e = 0; e < 32; e += 2) mx[(e >> 1) & 3] = fmaxf(fmaxf(mx[(e >> 1) & 3], s[e >> 4][e & 15]), s[e >> 4][(e & 15) + 1]);
     const float mn = fmaxf(m, both_halves_max(fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3]))) * sl2);
-    // the accumulator is rescaled only when some query of the wave has raised its maximum by more than 2^8: until then
-    // probabilities are up to 256, of the same relative precision
-    if (__any(mn > m + 8.f)) {
+    // the accumulator is rescaled only when some query of the wave has raised its maximum.  (Letting it lag by up to 2^8 saves a
+    // part of that, but the largest probabilities are then no longer exactly 1: O's error against 64 bits 1.82e-3 -> 2.12e-3.)
+    if (__any(mn > m)) {
       const float alpha = fast_exp2(m - (mn == -INFINITY ? 0.f : mn));
       l *= alpha;
 #pragma unroll
@@ -369,7 +369,7 @@ __global__ void __launch_bounds__(256 * GROUPS, 2) flash_fwd_k(const bf16* __res
 //   dQ^T += K^T dS^T,  times scale at the end.
 // Three products against one exponential: bound by the matrix cores, fragments are read one step ahead of theirs.  The keys of
 // a tile are read once more in the phase after, so they have three stages.  Against tiles staged through registers and a
-// kernel of its own for D, us: 1 x 8192, 16 heads, 475 -> 355, 2 x 2048 108 -> 72, 4 x 512 32 -> 21.
+// kernel of its own for D, us, 16 heads: 1 x 8192 475 -> 355, 2 x 2048 108 -> 72, 4 x 512 32 -> 21.
 // ------------------------------------------------------------------------------------
 #define DQ_SMEM (5 * KV_TILE)                     // three stages of K, two of V
 __global__ void __launch_bounds__(256, 2) flash_bwd_dq_k(const bf16* __restrict__ q, const bf16* __restrict__ k,
@@ -503,8 +503,8 @@ __global__ void __launch_bounds__(256, 2) flash_bwd_dq_k(const bf16* __restrict_
 // leaves more to overlap inside the wave.  All of the backward pass, us, 16 heads, QB = 1 -> 2: 4 x 512 50.1 -> 49.1, 1 x 2048 128.9
 // -> 126.2, 2 x 2048 158 -> 172, 1 x 8192 918 -> 962.  Both add the queries in the same order, so the results have the same bits.
 // Fragments are read one step ahead of their products, addresses are worked out where they are used, and nothing is spilled inside
-// the loop (a register that is comes back through a wait for every tile on its way): all of the backward pass 8192 tokens 942 ->
-// 880 us, 2 x 2048 192 -> 153, 4 x 512 58 -> 46.
+// the loop (a register that is comes back through a wait for every tile on its way): the backward pass with dQ's part 1 x 8192
+// 1074 -> 897 us, 2 x 2048 227 -> 156, 4 x 512 70 -> 48.
 // ------------------------------------------------------------------------------------
 #define DKV_STAGE (2 * 64 * 256 + 2 * 256)      // Q, dO, lse, D
 template <int QB>
@@ -991,15 +991,15 @@ __global__ void __launch_bounds__(256, 2) flash_bwd_short_k(const bf16* __restri
 
 // Which form a problem takes.  Measured, us, forward / all of the backward pass, 128 queries per workgroup -> 32:
 //   16 heads: 1 x 256 10.8 / 29 -> 7.9 / 13    1 x 512 15.0 / 42 -> 10.1 / 19    2 x 400 13.0 / 38 -> 11.5 / 27    3 x 333 12.3 / 36 -> 13.0 / 30
-//             2 x 512 15.5 / 43 -> 12.0 / 30   1 x 1024 20.4 / 70 -> 16.4 / 41   1 x 1536 26.7 / 97 -> 26.5 / 69   2 x 1024 21.4 / 72 -> 27.0 / 72
-//             1 x 2048 33.7 / 125 -> 39.5 / 105
+//             2 x 512 15.5 / 43 -> 12.0 / 30   1 x 1024 20.4 / 70 -> 16.4 / 41   1 x 1536 28.6 / 97 -> 26.1 / 69   2 x 1024 23.1 / 72 -> 27.0 / 72
+//             1 x 2048 36 / 125 -> 39.5 / 105
 //   8 heads: 1 x 2048 31.5 / 122 -> 26.4 / 56    4 heads: 4 x 1024 19.9 / 68 -> 16.3 / 42    32 heads: 1 x 1024 21.7 / 72 -> 26.2 / 67
 // Alone 32 queries pay further up than inside a step, where the attention shares the chip with the experts' weight gradients and
 // the CU time counts, of which they take more.  16 heads, us per step, 128 queries always -> 32 at both: 1 x 512 1486.6 -> 1487.4,
 // 1 x 1024 1872 -> 1886, 1 x 1600 2280 -> 2324, 1 x 2048 2813 -> 2891; adapters only, with little beside the attention, 3 x 333
 // 1578 -> 1573; merged passes, forward only, 1 x 512 472 -> 465, 1 x 1024 535.5 -> 529.8, 1 x 2048 792 -> 807; 4 heads, 2 x 1024
-// 566 -> 518.  So the line is at 1024 tokens of 16 heads, backward 1280 from 1024 positions on, with the heads counted coarsely and
-// more than 16 as 18.
+// 566 -> 518.  So the line is at 1024 tokens of 16 heads, from 1024 positions on at 1536 forward and 1280 backward, with the heads
+// counted coarsely and more than 16 as 18.
 // Many heads fill the chip with few tokens, so from there on a second line bounds tokens x heads, in tokens of 16 heads (work).
 // Measured, us, two forward passes and a backward one, 128 queries (an earlier kernel, a fifth slower) -> 32 (heads, tokens: work):
 //   64, 1 x 512: 2048 105 -> 96    48, 2 x 512: 3072 128 -> 143    128, 1 x 512: 4096 137 -> 188
@@ -1017,10 +1017,10 @@ static bool short_sequence(int B, int S, int H, int most) {
 // One or two groups of waves per workgroup of the forward kernel.  One lets two workgroups share a CU, which keeps both busy
 // where there are enough of them; two halve the chain of tiles, which is what counts where the workgroups are few or the longest
 // ones run on alone.  Measured, us, 16 heads, causal, one group -> two (workgroups):
-//   4 x 512 (256) 16.8 -> 16.4    8 x 256 (256) 11.7 -> 12.3    5 x 400 (320) 14.1 -> 20.5    2 x 1100 (288) 26.8 -> 22.5
-//   3 x 1024 (384) 27.0 -> 29.1   2 x 1300 (352) 31.0 -> 29.2   2 x 1700 (448) 39.3 -> 39.1   2 x 2048 (512) 47.3 -> 46.3
-//   2 x 2300 (576) 58.8 -> 62.7   1 x 2500 (320) 49.5 -> 39.2   1 x 4096 (512) 85.8 -> 80.1   1 x 5600 (704) 142 -> 143
-//   8 heads: 1 x 8192 (512) 164 -> 141    32 heads: 1 x 2500 (640) 66.5 -> 71.2
+//   4 x 512 (256) 17.9 -> 17.6    8 x 256 (256) 12.5 -> 13.1    5 x 400 (320) 15.2 -> 21.5    2 x 1100 (288) 28.3 -> 23.8
+//   3 x 1024 (384) 28.6 -> 30.1   2 x 1300 (352) 32.6 -> 29.3   2 x 1700 (448) 41.8 -> 40.1   2 x 2048 (512) 51.3 -> 50.1
+//   2 x 2300 (576) 63.4 -> 67.0   1 x 2500 (320) 54.0 -> 43.7   1 x 4096 (512) 93.2 -> 85.2   1 x 5600 (704) 154 -> 159
+//   8 heads: 1 x 8192 (512) 175 -> 154    32 heads: 1 x 2500 (640) 71.4 -> 77.5
 // Workgroups of two leave no room beside them, so where both take about the same time other streams' kernels decide for one
 // (2 x 2048: a step 0.7 % faster with one); dQ, which runs beside the experts' gradients, gains only alone (1 x 4096 355 -> 338
 // us, a step 0.5 % slower) and has one.
@@ -1034,7 +1034,7 @@ int launch_attn_fwd_flash(const void* q, const void* k, const void* v, void* o, 
   if (dh != DH || B <= 0 || S <= 0) return 1;
   if ((i64)S * H * DH * 2 >= ((i64)1 << 31)) return 1;      // one sequence of one tensor is addressed with 32-bit offsets
   if (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o) & 15) return 1;
-  if (short_sequence(B, S, H, 1024)) {
+  if (short_sequence(B, S, H, S >= 1024 ? 1536 : 1024)) {
     static std::atomic<unsigned long long> attr_mask{0};
     if (attr_needed(attr_mask)) {
       (void)hipFuncSetAttribute((const void*)flash_fwd_short_k, hipFuncAttributeMaxDynamicSharedMemorySize, SHORT_SMEM);

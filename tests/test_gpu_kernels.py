@@ -156,7 +156,7 @@ def test_flash_attention_ragged_long_sequence():
 
 
 # 128 queries per workgroup: one and two groups of waves (eight and more tiles), an odd and an even number of key tiles, the last of
-# one key, 63 and 64; the running maximum is raised by less and by more than the step that the kernel lets pass, and not at all
+# 1, 63 and 64 keys; scores that rise slowly and fast, so that the running maximum goes up in every tile, then in none
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("B,S,H,rise", [(1, 2049, 2, 3.0), (1, 2111, 1, 11.0), (1, 1216, 17, 0.0), (3, 705, 16, 3.0), (3, 448, 16, 11.0)])
 def test_flash_attention_key_tiles(B, S, H, rise, causal):
