@@ -296,9 +296,10 @@ void gemm_work(const revffn_ctx* c, const GemmArgs& g, int ta, int tb, int tc, d
   if (g.act_half) *bytes += M * (double)g.act_half * ec;
 }
 
-// a layer's GEMM over the rows of the call (one or both streams), few enough for the kernel of that name
+// a layer's GEMM over the rows of the call (one or both streams), few enough for the kernel of that name, or with a second pair of
+// operands, which no other takes
 bool few_rows(const revffn_ctx* c, const GemmArgs& g) {
-  return g.group_mode == 0 && !g.a_trans && g.M <= 2 * c->call_T && gemm_few_rows(c->call_T, g.N);
+  return g.group_mode == 0 && !g.a_trans && (g.A2 || (g.M <= 2 * c->call_T && gemm_few_rows(c->call_T, g.N)));
 }
 
 // Up to this mean of rows per expert nearly all experts fit in one tile of 128 rows
@@ -1315,8 +1316,8 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
   if (w->bk) add_colsum(cs, dt, c->dK, d, dt, nullptr, 0, nullptr, c->gdt, GF(bk), T, d);
   if (w->bv) add_colsum(cs, dt, c->dV, d, dt, nullptr, 0, nullptr, c->gdt, GF(bv), T, d);
   // dU2 = dK . Wk + dV . Wv: one contraction over both where the kernel takes two pairs of operands (then in one launch with
-  // dU1 = dQ . Wq), else one after the other
-  const bool pairs = dt == 0 || c->mode == 1 || gemm_few_rows(T, d);
+  // dU1 = dQ . Wq), else one after the other, with the first product rounded in between
+  const bool pairs = dt == 0 || c->mode == 1 || gemm_pairs(T, d);
   GemmArgs du[2] = {nn(c->dK, d, w->wk, d, dU2, d, T, d, d), nn(c->dQ, d, w->wq, d, dU1, d, T, d, d)};
   if (pairs) {
     du[0].A2 = c->dV; du[0].B2 = w->wv;

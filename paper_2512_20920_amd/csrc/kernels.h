@@ -215,6 +215,9 @@ int launch_gemm_mfma(const GemmArgs& g, GemmTypes t, hipStream_t s);
 // for less of what it holds up.  Line at 256, 384, 512: 160 tokens (320 tiles) 1113, 1119, 1120   200 (448) 1151, 1146, 1182
 //   240 (512) 1165, 1163, 1242   4096 wide, 100 tokens (512) 2557, 2558, 2590
 inline bool gemm_few_rows(i64 T, i64 N) { return ((T + 31) / 32) * ((N + 31) / 32) <= (N >= 2048 ? 384 : 512); }
+// When two products are summed there as one contraction (GemmArgs::A2).  A line of its own, above the other: with one launch per product
+// the first is rounded to bf16 in between, so this line is about precision and doesn't follow the faster kernel.
+inline bool gemm_pairs(i64 T, i64 N) { return ((T + 31) / 32) * ((N + 31) / 32) <= 512; }
 void launch_gemm_skinny(const GemmArgs& g, int out_f32, hipStream_t s);
 void launch_gemm_experts(const GemmArgs& g, hipStream_t s);      // (bf16 results, rows from list a)
 

@@ -184,6 +184,38 @@ def test_block_parity_expert_tiles(E, k, I, B, S):
     _backward_checks(case, x1d, x2d, y1d, TOL["bf16"])
 
 
+# dU2 = dK . Wk + dV . Wv is one contraction, rounded once, as long as it has at most 512 tiles of 32x32: the last size below 384 of them,
+# sizes above, and the last of all.  Tokens with one non-zero each make every element of dU2 readable from the up-projection's
+# gradient; columns of Wk and Wv with one 1 give dK and dV themselves, so the sum of two of dK's and one of dV's is known exactly.
+# (float32 sums of three such terms may round a second time: about one in 2 ** 16.  With dK . Wk rounded in between 14 to 18 % differ.)
+@pytest.mark.parametrize("d,B,S", [(2048, 1, 192), (2048, 1, 200), (2048, 4, 64), (4096, 1, 128)])
+def test_key_value_gradient_rounds_once(d, B, S):
+    wl = synth.Workload(f"pairs_{d}_{B}x{S}", d, d // 128, 128, 4, 1, 64, 0, B, S, "bf16", seed=S)
+    W, h, T, n = synth.make_weights(wl), d // 2, B * S, 64
+    for name in ("norm_a1", "norm_a2"):
+        W[name] = np.ones_like(W[name])
+    W["wk"][:, :5 * n] = W["wv"][:, :5 * n] = 0.0
+    for i in range(2 * n):
+        W["wk"][i, i] = W["wv"][i, 2 * n + i] = 1.0                       # dU2 = dK, dV
+    for i in range(n):
+        W["wk"][2 * i:2 * i + 2, 4 * n + i] = 1.0                        # dU2 = dK_2i + dK_2i+1 + 2^-p dV_i
+        W["wv"][i, 4 * n + i] = 2.0 ** -(i % 16)
+    one_hot = np.zeros((2, T, h))
+    one_hot[0, np.arange(T), np.arange(T)] = one_hot[1, np.arange(T), T + np.arange(T)] = 64.0
+    _, _, dy1, dy2 = synth.make_inputs(wl)
+    case = Case(wl, weights=W, inputs=(one_hot[0], one_hot[1], dy1, dy2), fp32_grads=True)
+    y1d, _ = case.forward()
+    _, _, G = case.backward(case.up(case.x1), case.up(case.x2), y1d)
+    normed = synth.round_bf16(np.float32(64.0 / np.sqrt(64.0 ** 2 / h + 1e-6)))
+    dU2 = Hn.download(G["pup_a"])[:5 * n, T:2 * T] / normed              # [column, token]
+    dK, dV, got = dU2[:2 * n], dU2[2 * n:4 * n], dU2[4 * n:]
+    assert min(np.count_nonzero(dK), np.count_nonzero(dV)) > 0.9 * dK.size
+    exact = dK[0::2] + dK[1::2] + dV[:n] * 2.0 ** -(np.arange(n) % 16)[:, None]
+    off = np.mean(got != synth.round_bf16(exact.astype(np.float32)))
+    print(f"PAIRS d {d} T {T}: {off:.1e} of dU2 not rounded once")
+    assert off < 1e-3
+
+
 # An expert's last tile of 256 rows takes up to 64 rows more.  Every expert has all T rows (top-k of all): a whole tile, one row more,
 # the most one tile takes, one more than that, two tiles of which the last is a tall one; gate/up widths that give the forward
 # kernel enough tiles, ending inside one, and k that ends inside a k-tile.
