@@ -227,7 +227,9 @@ __global__ void __launch_bounds__(256 * GROUPS, 2) flash_fwd_k(const bf16* __res
 #pragma unroll
       for (int j = 0; j < 2; j++) s[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk * 2 + j], qf[kk], s[j], 0, 0, 0);
   };
-  issue(slK, 0, 0); issue(slV, 0, 1); issue(slK, 1, 0);
+  // In the order of the loop below (keys of a tile before the values of the one before it), so that each wait counts what is younger
+  // than the tile it is for.  (The compiler's wait for Q, which doesn't count these loads, lets them all arrive today; nothing relies on it.)
+  issue(slK, 0, 0); issue(slK, 1, 0); issue(slV, 0, 1);
   arrived(qf);
   wait_vmcnt<8>();                                  // the first keys
   phase_end();
@@ -235,7 +237,7 @@ __global__ void __launch_bounds__(256 * GROUPS, 2) flash_fwd_k(const bf16* __res
   read_k(0, 0);
   read_k(0, 4);
   times_q();
-  wait_vmcnt<4>();                                  // K of tile 1 is there
+  wait_vmcnt<4>();                                  // K of tile 1 is there, V of tile 0 may be on its way
   phase_end();
   // keys past the sequence end or after the query
   auto mask = [&](int i) {

@@ -163,6 +163,14 @@ def test_flash_attention_key_tiles(B, S, H, rise, causal):
     _attention_case(B, S, H, 128, causal, 2, 1, rise=rise)
 
 
+# 128 queries per workgroup and no more key tiles than are on their way before the loop: one, two of which the second has 1, 36 and
+# 64 keys, and three
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("S", [64, 65, 100, 128, 129])
+def test_flash_attention_first_key_tiles(S, causal):
+    _attention_case(17, S, 16, 128, causal, 2, 1, rise=3.0)
+
+
 @pytest.mark.parametrize("dtype,dh", [(0, 16), (1, 32), (0, 80)])
 def test_generic_attention(dtype, dh):
     _attention_case(2, 70, 3, dh, True, 1, dtype)
