@@ -1192,7 +1192,9 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
   // In calls too small for helper streams the experts' weight gradients wait for the dense layers' launch, where they are fewer than the tiles
   // that suit larger ones (see pick_tile).  512 wide, 12 experts, 400 tokens 297 -> 286 us per step, 256 wide, 753 tokens 375 -> 361, float32,
   // 64 tokens 253 -> 245.
-  const bool batched = c->small && (i64)cdiv(d, 256) * cdiv(2 * I, 256) * E <= 256;
+  // (Only widths of whole 16-byte pieces: for one problem of another that launch refuses all of them, or in float32 takes them through
+  // slower loads.  512 wide, 12 experts of 196, 400 tokens 379 us with the experts among them, 336 without.)
+  const bool batched = c->small && (i64)cdiv(d, 256) * cdiv(2 * I, 256) * E <= 256 && I % (16 / c->es) == 0;
   ColsumBatch cs;
   TRY(run_gemm(c, nn(dy2, ld, w->pdn_m, d, c->dRS, d, T, d, h), s));
   // (for the matrix-core router GEMM below: the logit gradients also in bf16, and the router rows stacked, dz . [W_r ; w_gate ; 0])

@@ -173,6 +173,20 @@ def test_block_parity_shared_expert_comes_along(d, H, E, k, I, Is, B, S):
     _backward_checks(case, x1d, x2d, y1d, TOL["bf16"])
 
 
+# In small calls the experts' weight gradients share the dense layers' launch where it takes their width.  Where it doesn't the dense
+# layers still are one launch, and the experts' down gradient the one that the matrix-core kernel leaves to the generic one.
+@pytest.mark.parametrize("I,experts", [(200, 0), (196, 1)])
+def test_expert_gradients_of_odd_width_leave_the_dense_layers_launch(I, experts):
+    wl = synth.Workload(f"odd_{I}", 512, 4, 128, 12, 3, I, 320, 2, 100, "bf16", seed=I)
+    case = Case(wl)
+    y1d, _ = case.forward()
+    case.ctx.profile_enable()
+    case.backward(case.up(case.x1), case.up(case.x2), y1d)
+    count = {n: v["launches"] for n, v in case.ctx.profile_read().items()}
+    assert (count["gemm_mfma_tn"], count.get("gemm_mfma_tn_experts", 0)) == (1, experts)
+    _backward_checks(case, case.up(case.x1), case.up(case.x2), y1d, TOL["bf16"])
+
+
 # More routed work than the kernel for few rows takes: the tiles of the expert GEMMs with widths and row counts that end inside
 # them, at 50 rows per expert (128x256), 137 (160x256, 256x256, 256x128) and 391 (256x256 throughout); and 4100 tokens
 @pytest.mark.parametrize("E,k,I,B,S", [(24, 2, 600, 2, 300), (12, 3, 600, 2, 274), (6, 3, 440, 3, 261), (4, 2, 200, 20, 205)])
