@@ -387,8 +387,15 @@ int run_gemm(revffn_ctx* c, GemmArgs g, int ta, int tb, int tc, hipStream_t s) {
   if (g.co) co = *g.co;
   const GemmDense co_asked = co;
   if (c->no_fused_swiglu) { g.act_out = co.act_out = nullptr; g.act_half = co.act_half = 0; g.dact_out = co.dact_out = nullptr; }
-  if (g.co) g.co = &co;
-  auto swiglu_after = [&]() {
+  const bool has_co = g.co != nullptr;
+  if (has_co) g.co = &co;
+  // co_in: the problem that comes along was in the launch; otherwise it gets one of its own, whichever kernel that was
+  auto finish = [&](bool co_in) -> int {
+    if (has_co && !co_in) {
+      const int e = run_gemm(c, alone(co_asked, g.b_trans), ta, tb, tc, s);
+      if (e) return e;
+      co = co_asked;
+    }
     if (co_asked.act_half && !co.act_half) launch_swiglu_fwd(c->dt, co.C, co_asked.act_out, co.M, co_asked.act_half, s);
     if (co_asked.dact_out && !co.dact_out) launch_swiglu_bwd(c->dt, co.C, co.dact_gu, co_asked.dact_out, co.M, co.N, s);
     if (act_half && !g.act_half) launch_swiglu_fwd(c->dt, g.C, act_out, out_rows, act_half, s);
@@ -397,6 +404,7 @@ int run_gemm(revffn_ctx* c, GemmArgs g, int ta, int tb, int tc, hipStream_t s) {
       launch_swiglu_bwd(c->dt, g.C, g.dact_gu, dact_out, out_rows, g.N, s);
       q.done(KID_SWIGLU_BWD);
     }
+    return 0;
   };
   if (c->dt == 1 && c->mode == 0 && ta == 1 && tb == 1) {
     if (g.group_mode == 1) {
@@ -457,19 +465,17 @@ int run_gemm(revffn_ctx* c, GemmArgs g, int ta, int tb, int tc, hipStream_t s) {
       }
     }
     if (!g.few_rows) g.dact_out = nullptr;
-    if (launch_gemm_mfma(g, t, s) == 0) {                        // (its caller has asked rides() about a problem that comes along)
+    if (launch_gemm_mfma(g, t, s) == 0) {
       if (g.group_mode) ps.done(g.a_trans ? KID_GEMM_TN_EXPERTS : (g.b_trans ? KID_GEMM_NN_EXPERTS : KID_GEMM_NT_EXPERTS));
       else ps.done(g.a_trans ? KID_GEMM_TN : (g.b_trans ? KID_GEMM_NN : KID_GEMM_NT));
-      swiglu_after();
-      return 0;
+      return finish(g.group_mode == 1 && g.few_rows);            // (the kernels that take a second problem)
     }
   }
   if (g.group_mode == 1) { g.tile_group = c->tg_a; g.tile_m0 = c->tm_a; g.max_tiles = c->max_tiles_a; g.tile_bm = BM_A; g.tile_count = c->tile_cnt; }
   if (!c->no_fused_swiglu) g.dact_out = dact_out;
   int e = launch_gemm_generic(g, t, s) == 0 ? 0 : REVFFN_EUNSUPPORTED;
   ps.done(KID_GEMM_GENERIC);
-  if (!e) swiglu_after();
-  return e;
+  return e ? e : finish(false);
 }
 int run_gemm(revffn_ctx* c, const GemmArgs& g, hipStream_t s) { return run_gemm(c, g, c->dt, c->dt, c->dt, s); }
 // a GEMM whose result is a weight gradient: written in the gradient dtype (float32 with fp32_grads)
