@@ -872,6 +872,15 @@ void moe_gemms(revffn_ctx* c, const void* w_gu, const void* w_dn, const void* ws
 // either.  Not in training steps that have helper streams, where the first query side shares the fork and larger tiles run beside the
 // routing chain: with them along, 64 tokens at the Qwen shape 992 -> 1007 us, 128 1067 -> 1105, 160 1118 -> 1156.
 // A 512-wide block, 400 tokens, 323 -> 298 us (the backward's two as well); merged Qwen weights, 1 token 145 -> 125, 37 295 -> 274, 240 353 -> 351.
+// Up to a size: these kernels' tiles load twice and more of what larger ones do per product, which a wide shared expert beside narrow
+// routed ones makes the larger part of the launch.  Alone -> along, us:
+//   one stream, tiles of 32x32 of its gate/up GEMM: 128 wide, a step of 2048 tokens, 1920 469.6 -> 465.2,
+//   2880 476.8 -> 475.4, 3840 481 -> 487, 5760 500 -> 510; merged, 1920 182.5 -> 178.7, 2880 185.3 -> 186.2, 5760 196.6 -> 206.1; 256 wide,
+//   2250 147.7 -> 143.0, 3125 147.1 -> 148.1; 512 wide, 2000 123.5 -> 121.0, 2880 167.4 -> 169.1, 5760 177 -> 189
+//   one stream, merged, down, row tiles of 32 x outputs x k: 128 wide, 11e6 234 -> 222, 512 wide, 24e6 183 -> 177, 768 wide, 35e6 206 -> 210
+//   helper streams, merged, the same of gate/up: up to 8 row tiles 46e6 (60 experts) 325 -> 312, 92e6 357 -> 352, (128 experts)
+//   46e6 427 -> 412, 58e6 484 -> 486; more of them: 24e6 203 -> 204, 35e6 190 -> 205, 46e6 617 -> 628, 47e6 209 -> 225, 92e6 622 -> 648,
+//   94e6 226 -> 273, 173e6 564 -> 607
 struct Riders { bool gate_up = false, down = false; GemmDense d1, d2; bool both() const { return gate_up && down; } };
 Riders riders(const revffn_ctx* c, const GemmArgs& g1, const GemmArgs& g2, const GemmArgs& gs, const GemmArgs& gd) {
   Riders r;
@@ -879,7 +888,12 @@ Riders riders(const revffn_ctx* c, const GemmArgs& g1, const GemmArgs& g2, const
   if (!c->cfg.d_shared || (!c->small && !merged)) return r;
   r.gate_up = rides(c, g1, gs);
   r.down = rides(c, g2, gd);
-  if (!c->small && !r.both()) r.gate_up = r.down = false;
+  const i64 row_tiles = cdiv(gs.M, 32);
+  const double most = 28e6;                          // (row tiles x outputs x k)
+  if (c->small) {
+    r.gate_up = r.gate_up && row_tiles * cdiv(gs.N, 32) <= 2560;
+    r.down = r.down && (double)row_tiles * gd.N * gd.K <= most;
+  } else if (!r.both() || (row_tiles > 8 && (double)row_tiles * gs.N * gs.K > most)) r.gate_up = r.down = false;
   r.d1 = along(gs);
   r.d2 = along(gd);
   return r;

@@ -164,7 +164,8 @@ def test_block_parity_small_problems(dtype, d, H, E, k, I, Is, B, S):
 # tiles for the kernel for few rows; down too many), both in calls of one tile and with weights that come from memory.  And the experts'
 # weight gradients in the launch of the dense layers', with experts that have no rows.
 @pytest.mark.parametrize("d,H,E,k,I,Is,B,S", [(256, 4, 15, 4, 360, 448, 3, 251), (640, 5, 48, 4, 24, 40, 1, 300), (256, 2, 4, 2, 72, 200, 1, 31),
-                                              (256, 2, 128, 1, 264, 104, 1, 300), (256, 2, 16, 1, 264, 104, 1, 9)])
+                                              (256, 2, 128, 1, 264, 104, 1, 300), (256, 2, 16, 1, 264, 104, 1, 9),
+                                              (128, 2, 4, 1, 64, 1440, 1, 1000)])         # (its gate/up on its own, the others along)
 def test_block_parity_shared_expert_comes_along(d, H, E, k, I, Is, B, S):
     wl = synth.Workload(f"along_d{d}_E{E}", d, H, d // H, E, k, I, Is, B, S, "bf16", gain_jitter=0.02, seed=d + E)
     case = Case(wl)
@@ -1169,6 +1170,24 @@ def test_merged_adapters_parity(name):
                                     (1280, 64, 17), (1280, 128, 40), (2048, 128, 1), (2048, 64, 17), (2048, 128, 32)])
 def test_merged_adapters_parity_few_tokens(d, dh, T):
     _merged_checks(synth.Workload(f"merged_d{d}_dh{dh}", d, d // dh, dh, 4, 2, 64, 96, 1, T, "bf16", gain_jitter=0.02, seed=d + T))
+
+
+# The shared expert's GEMMs go along with the routed ones' up to a size.  One stream: gate/up up to 2560 tiles (2400 and 2880 here),
+# down up to 28e6 row tiles x outputs x k (6e6; 35e6 of 768 wide); helper streams: both or, over 8 row tiles and 28e6 of gate/up
+# (27.2e6 and 34.8e6 here), neither.  `own`: the launches that the shared expert adds to the call.
+@pytest.mark.parametrize("d,dh,Is,B,S,own", [(128, 64, 1200, 1, 1000, 0), (128, 64, 1440, 1, 1000, 1), (768, 128, 1440, 2, 1000, 2),
+                                             (1024, 128, 312, 3, 900, 0), (1024, 128, 400, 3, 900, 2)])
+def test_merged_shared_expert_comes_along_up_to_a_size(d, dh, Is, B, S, own):
+    count = []
+    for width in (Is, 0):
+        wl = synth.Workload(f"wide_shared_{d}_{width}", d, d // dh, dh, 4, 1, 64, width, B, S, "bf16", gain_jitter=0.02, seed=Is)
+        case, Md = Case(wl), Hn.alloc_merged(wl)
+        R.revffn_merge_adapters(case.ctx, case.Wd, Md)
+        case.ctx.profile_enable()
+        R.revffn_forward_merged(case.ctx, case.Wd, Md, case.up(case.x1), case.up(case.x2), case.empty(), case.empty(), B, S, wl.h)
+        count.append(sum(v["launches"] for n, v in case.ctx.profile_read().items() if n.startswith("gemm_mfma_nt")))
+    assert count[0] - count[1] == own
+    _merged_checks(synth.Workload(f"wide_shared_{d}_{Is}", d, d // dh, dh, 4, 1, 64, Is, B, S, "bf16", gain_jitter=0.02, seed=Is))
 
 
 def _merged_checks(wl):
