@@ -493,8 +493,9 @@ void launch_combine_couple(int dt, int ts, const void* yp, const int* inv_map, c
 // (a kernel of its own for the second part, and one that stacks the router rows for the GEMM that follows, were 5 us each of
 // every step at any size: both are latency)
 // gather.um != null: the token's row of Um goes to its experts' rows of gather.xg on the way (the operand of the gate/up weight
-// gradient; as a kernel of its own, which read the row once per slot, 3 us of the chain in small calls, 44 us on a
-// helper stream at 8192 tokens)
+// gradient).  As a kernel of its own that was 3 us of the chain in small calls; from 2048 tokens on, where it ran on a helper stream, a
+// step takes the same either way (this kernel 20.6 -> 28 us at 2048 tokens, 66 -> 94 at 8192, the other 16 and 50).  Bound by the rows of
+// k slots, read once and written twice.  With the token's own rows read anew for every slot: 32 and 101 us.
 // ---------------------------------------------------------------------------------
 // dz of one token by one wave, lanes over the experts; my_dw: dw of slot `lane`, sgate: dz of the gate logit
 __device__ __forceinline__ void router_bwd_token(const RouterBwd& r, const float* wts, float my_dw, float sgate, float* dzext,
@@ -585,13 +586,20 @@ __global__ void __launch_bounds__(256) moe_bwd_rows_v8_k(const bf16* __restrict_
     else for (int c = threadIdx.x; c < d; c += 256) dp[c] = sp[c];
     return;
   }
-  const bf16* dr = drs + (i64)t * d;
+  // this thread's first piece of the token's two rows, which up to 2048 wide is all of them, is read once for all slots
+  const bf16 *dr = drs + (i64)t * d, *um = (const bf16*)gather.um + (i64)t * d;
+  const int c0 = threadIdx.x * 8;
+  bf16x8_t dr0 = {}, um0 = {};
+  if (c0 < d) {
+    dr0 = *(const bf16x8_t*)(dr + c0);
+    if (gather.um) um0 = *(const bf16x8_t*)(um + c0);
+  }
   float gate = 0.f;
   if (has_gate) {
     const float g = gamma[t];
     float acc = 0.f;
-    for (int c = threadIdx.x * 8; c < d; c += 256 * 8) {
-      const bf16x8_t v = *(const bf16x8_t*)(dr + c), y = *(const bf16x8_t*)(ys + (i64)t * d + c);
+    for (int c = c0; c < d; c += 256 * 8) {
+      const bf16x8_t v = c == c0 ? dr0 : *(const bf16x8_t*)(dr + c), y = *(const bf16x8_t*)(ys + (i64)t * d + c);
       bf16x8_t o;
 #pragma unroll
       for (int q = 0; q < 8; q++) { acc += (float)v[q] * (float)y[q]; o[q] = (__bf16)(g * (float)v[q]); }
@@ -605,13 +613,13 @@ __global__ void __launch_bounds__(256) moe_bwd_rows_v8_k(const bf16* __restrict_
     const int pos = inv_map[(i64)t * k + s];
     const float w = wts[(i64)t * k + s];
     float acc = 0.f;
-    for (int c = threadIdx.x * 8; c < d; c += 256 * 8) {
-      const bf16x8_t v = *(const bf16x8_t*)(dr + c), y = *(const bf16x8_t*)(yp + (i64)pos * d + c);
+    for (int c = c0; c < d; c += 256 * 8) {
+      const bf16x8_t v = c == c0 ? dr0 : *(const bf16x8_t*)(dr + c), y = *(const bf16x8_t*)(yp + (i64)pos * d + c);
       bf16x8_t o;
 #pragma unroll
       for (int q = 0; q < 8; q++) { acc += (float)v[q] * (float)y[q]; o[q] = (__bf16)(w * (float)v[q]); }
       *(bf16x8_t*)(dyp + (i64)pos * d + c) = o;
-      if (gather.um) *(bf16x8_t*)((bf16*)gather.xg + (i64)pos * d + c) = *(const bf16x8_t*)((const bf16*)gather.um + (i64)t * d + c);
+      if (gather.um) *(bf16x8_t*)((bf16*)gather.xg + (i64)pos * d + c) = c == c0 ? um0 : *(const bf16x8_t*)(um + c);
     }
     acc = block_sum_256(acc, red);
     if ((int)threadIdx.x == s) my_dw = acc;

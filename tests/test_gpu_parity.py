@@ -174,6 +174,16 @@ def test_block_parity_shared_expert_comes_along(d, H, E, k, I, Is, B, S):
     _backward_checks(case, x1d, x2d, y1d, TOL["bf16"])
 
 
+# The backward of the combine keeps a thread's first piece of the token's rows over the slots: rows a piece shorter than the
+# workgroup, of it exactly, and with pieces left over for one thread
+@pytest.mark.parametrize("d", [2040, 2048, 2056])
+def test_block_parity_rows_about_a_workgroup_wide(d):
+    wl = synth.Workload(f"rows_{d}", d, 4, d // 4, 4, 3, 64, 40, 1, 19, "bf16", gain_jitter=0.02, seed=d)
+    case = Case(wl)
+    y1d, _, _ = _forward_checks(case, TOL["bf16"], min_same=0.9)
+    _backward_checks(case, case.up(case.x1), case.up(case.x2), y1d, TOL["bf16"])
+
+
 # In small calls the experts' weight gradients share the dense layers' launch where it takes their width.  Where it doesn't the dense
 # layers still are one launch, and the experts' down gradient the one that the matrix-core kernel leaves to the generic one.
 @pytest.mark.parametrize("I,experts", [(200, 0), (196, 1)])
