@@ -332,7 +332,8 @@ int experts_kernel(const revffn_ctx* c, i64 rows, i64 N, i64 K, bool b_trans) {
   // 8 experts of 14336, 64 tokens 2416 / 2317, 80 (20 rows) 2505 / 2575 (experts of two tiles are read twice); 260 tokens
   // 1240 / 1337 (its workgroups leave no room for the shared expert's larger tiles beside them).  Data gradients with k long (dXg)
   // are faster on 128x256 tiles, whose lines are 512 bytes: 64 tokens 108 / 116 us, unless an expert has a row or two:
-  // 20 tokens 101 / 93.
+  // 20 tokens 101 / 93.  The rule looks at the mean.  Skewed, the hottest expert 8 times the mean, a step of 64, 128, 200, 240 tokens
+  // 986, 1090, 1171, 1194 / 929, 1053, 1166, 1202, merged 37, 128, 240 285, 339, 386 / 251, 311, 364.
   if (rows <= 16 * E && (!b_trans || K <= 2048 || (rows <= 2 * E && K <= 4096))) return 2;
   return 0;
 }
@@ -453,7 +454,9 @@ int run_gemm(revffn_ctx* c, GemmArgs g, int ta, int tb, int tc, hipStream_t s) {
         g.tile_group = c->tg_a; g.tile_m0 = c->tm_a; g.max_tiles = (int)row_tiles32(rows, E); g.tile_bm = BM_A; g.tile_count = c->tile_cnt; g.tile_first = c->tf_a;
         // (Weights past the caches, see GemmArgs::once; with k as the slow index a line belongs to two tiles, which does not pay
         // where k is long.  Through / past, us: 8, 16, 25 tokens at the Qwen shape 862, 1005, 1107 / 816, 972, 1043;
-        // merged 16, 29 tokens 300, 344 / 280, 318; 8 experts of 14336, 8 tokens, the forward layout only / both 2589 / 2629.)
+        // merged 16, 29 tokens 300, 344 / 280, 318; 8 experts of 14336, 8 tokens, the forward layout only / both 2589 / 2629.  An expert of
+        // several row tiles is then fetched once for each, which still pays skewed as above: 64, 128, 240 tokens 1038, 1178, 1308 / 929,
+        // 1053, 1202.)
         g.once = rows <= 16 * E && (!g.b_trans || g.K <= 2048) && past;
       } else if (tall) {
         g.tile_group = c->tg_c; g.tile_m0 = c->tm_c; g.max_tiles = c->max_tiles_c; g.tile_bm = c->bm_c; g.tile_count = c->tile_cnt + 2;

@@ -123,7 +123,9 @@ __device__ __forceinline__ void arrived(bf16x8 (&f)[8]) {
 // GROUPS = 1: 4 waves, two workgroups on a CU.  GROUPS = 2: two groups of 4 waves with the same queries, group 0 on the even
 // tiles and group 1 on the odd ones, half an iteration apart (one wave of each on a SIMD: one multiplies while the other
 // doesn't); their partial results meet in LDS at the end.  two_groups() has the rule.
-// Bound by the power limit where the grid is large: 8192 tokens, 16 heads, 0.97 PFLOP/s on random values, a third more on zeros.
+// Where the grid is large (8192 tokens, 16 heads): 0.97 PFLOP/s on random values, the matrix pipe busy half of the time at 80 % of its
+// nominal rate.  Power has a part in the rate (a third more on zeros), the idle half is the maximum, half of the exponentials and
+// the barriers, which the other workgroup's products only partly cover.
 // Against tiles staged through registers and fragments read just before use, us: 1 x 8192 332 -> 284, 1 x 4096 109 -> 84, 2 x 2048
 // 59 -> 51, 4 x 512 20.1 -> 17.8, 64 x 128 32.1 -> 31.5.
 // ------------------------------------------------------------------------------------
@@ -1003,13 +1005,17 @@ __global__ void __launch_bounds__(256, 2) flash_bwd_short_k(const bf16* __restri
 // 566 -> 518.  So the line is at 1024 tokens of 16 heads, from 1024 positions on at 1536 forward and 1280 backward, with the heads
 // counted coarsely and more than 16 as 18.
 // Many heads fill the chip with few tokens, so from there on a second line bounds tokens x heads, in tokens of 16 heads (work).
-// Measured, us, two forward passes and a backward one, 128 queries (an earlier kernel, a fifth slower) -> 32 (heads, tokens: work):
-//   64, 1 x 512: 2048 105 -> 96    48, 2 x 512: 3072 128 -> 143    128, 1 x 512: 4096 137 -> 188
-//   32, 3 x 256: 1536 70 -> 69    32, 4 x 256: 2048 73 -> 80    64, 4 x 256: 4096 109 -> 156
-//   64, 2 x 128: 1024 49 -> 41    48, 4 x 128: 1536 54 -> 59    64, 4 x 128: 2048 59 -> 70
-//   40, 4 x 64: 640 35 -> 34    48, 4 x 64: 768 35 -> 38    64, 8 x 64: 2048 51 -> 67
+// Measured, us, two forward passes and a backward one, 128 queries -> 32 (heads, tokens: work):
+//   24, 1 x 1024: 1536 115 -> 96    32, 1 x 1024: 2048 117 -> 116    40, 1 x 1024: 2560 131 -> 147    48, 1 x 1024: 3072 139 -> 169
+//   32, 1 x 512: 1024 74 -> 52    48, 1 x 512: 1536 77 -> 76    64, 1 x 512: 2048 78 -> 88    48, 2 x 451: 2706 88 -> 123    128, 1 x 512: 4096 101 -> 172
+//   32, 2 x 256: 1024 52 -> 43    32, 3 x 256: 1536 54 -> 64    64, 4 x 256: 4096 91 -> 151
+//   64, 2 x 128: 1024 41 -> 40    40, 4 x 128: 1280 43 -> 54    64, 4 x 128: 2048 49 -> 70
+//   32, 4 x 64: 512 31 -> 29    40, 4 x 64: 640 31 -> 35    64, 8 x 64: 2048 42 -> 67
+// By time alone it would lie at 2048 from 1024 positions on, 1536 from 448, 1024 from 128 and 512 below.  It lies where the kernels
+// before these had it, because of what it decides besides:
 // The two forms add in different orders.  A call on some of the heads takes the short form wherever the call on all of them does,
-// and gives the same bits then; where all of them take the long form, some alone need not.  Two groups of waves add in yet another.
+// and gives the same bits then; where all of them take the long form, some alone need not.  A lower line would take that from calls
+// that have it.  Two groups of waves add in yet another order.
 static bool short_sequence(int B, int S, int H, int most) {
   const i64 tokens = (i64)B * S, load = tokens * (H <= 4 ? 4 : H <= 8 ? 8 : H <= 16 ? 16 : 18) / 16;
   if (S > 2048 || load > most) return false;

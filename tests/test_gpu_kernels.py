@@ -156,11 +156,20 @@ def test_flash_attention_ragged_long_sequence():
 
 
 # 128 queries per workgroup: one and two groups of waves (eight and more tiles), an odd and an even number of key tiles, the last of
-# 1, 63 and 64 keys; scores that rise slowly and fast, so that the running maximum goes up in every tile, then in none
+# 1, 63 and 64 keys; scores that rise slowly and fast, so that the running maximum goes up in every tile, then in none.  (1 x 1216, 17
+# heads: backward only, the forward pass takes 32 queries per workgroup.)
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("B,S,H,rise", [(1, 2049, 2, 3.0), (1, 2111, 1, 11.0), (1, 1216, 17, 0.0), (3, 705, 16, 3.0), (3, 448, 16, 11.0)])
 def test_flash_attention_key_tiles(B, S, H, rise, causal):
     _attention_case(B, S, H, 128, causal, 2, 1, rise=rise)
+
+
+# Two groups of waves, group 1 on the odd tiles: 33 key tiles (it ends first) of which the last has 64 keys, 34 with a last one of 1 and
+# of 64 keys; maxima that differ between the groups where their results meet
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("S,rise", [(2112, 3.0), (2113, 11.0), (2176, 3.0)])
+def test_flash_attention_two_groups_key_tiles(S, rise, causal):
+    _attention_case(1, S, 2, 128, causal, 2, 1, rise=rise)
 
 
 # 128 queries per workgroup and no more key tiles than are on their way before the loop: one, two of which the second has 1, 36 and
@@ -187,7 +196,7 @@ def test_vector_attention(dtype, dh, offset):
 
 # 128 queries per workgroup, more workgroups than CUs and no more than two for each: the second part of the grid runs in
 # reverse (16 and 24 heads: a whole and a broken row of heads where it starts; 100 heads: three tiles each); 48 heads of 2 x 451
-# tokens: 32 queries per workgroup forward; 16 and 24 heads: two groups of waves forward
+# tokens: 32 queries per workgroup both ways; 16 and 24 heads: two groups of waves forward
 @pytest.mark.parametrize("B,S,H", [(2, 451, 48), (1, 300, 100), (1, 2200, 16), (1, 2100, 24)])
 def test_flash_attention_paired_tiles(B, S, H):
     _attention_case(B, S, H, 128, True, 2, 1)
