@@ -1002,8 +1002,14 @@ __global__ void __launch_bounds__(256, 2) flash_bwd_short_k(const bf16* __restri
 // the CU time counts, of which they take more.  16 heads, us per step, 128 queries always -> 32 at both: 1 x 512 1486.6 -> 1487.4,
 // 1 x 1024 1872 -> 1886, 1 x 1600 2280 -> 2324, 1 x 2048 2813 -> 2891; adapters only, with little beside the attention, 3 x 333
 // 1578 -> 1573; merged passes, forward only, 1 x 512 472 -> 465, 1 x 1024 535.5 -> 529.8, 1 x 2048 792 -> 807; 4 heads, 2 x 1024
-// 566 -> 518.  So the line is at 1024 tokens of 16 heads, from 1024 positions on at 1536 forward and 1280 backward, with the heads
-// counted coarsely and more than 16 as 18.
+// 566 -> 518.  So the line is at 1024 tokens of 16 heads, from 1024 positions on at 1536, with more than 16 heads counted as 18.
+// Backward at 1280 instead: all gradients 1 x 1300 2220 -> 2205, 1 x 1536 2354 -> 2336, but adapters only 1853 -> 1872, 1934 -> 1953, and a
+// block of 8 experts of 704, 16 heads, 1 x 1400 1079 -> 1087, its adapters only 950 -> 976.
+// From 1024 positions on fewer heads than 16 count as they are: alone, forward / backward, 9 heads, 1 x 1400 26.2 / 89 -> 21.0 / 39, 12,
+// 1 x 1700 29.7 / 105 -> 25.5 / 63, 5, 2 x 2048 34.7 / 122 -> 28.1 / 68; a step of the block of 8 experts, counted as 16 -> as they are, 9
+// heads, 1 x 1400 745 -> 698, 12, 1 x 1700 974 -> 940, of 32 experts of 1024, 12, 1 x 1700 1356 -> 1342.  Below that they count coarsely
+// (5 heads as 8, 9 as 16): a call on 40 heads of 5 x 300 tokens, which takes 128 queries, and one on a quarter of them give the
+// same bits that way.
 // Many heads fill the chip with few tokens, so from there on a second line bounds tokens x heads, in tokens of 16 heads (work).
 // Measured, us, two forward passes and a backward one, 128 queries -> 32 (heads, tokens: work):
 //   24, 1 x 1024: 1536 115 -> 96    32, 1 x 1024: 2048 117 -> 116    40, 1 x 1024: 2560 131 -> 147    48, 1 x 1024: 3072 139 -> 169
@@ -1016,9 +1022,9 @@ __global__ void __launch_bounds__(256, 2) flash_bwd_short_k(const bf16* __restri
 // The two forms add in different orders.  A call on some of the heads takes the short form wherever the call on all of them does,
 // and gives the same bits then; where all of them take the long form, some alone need not.  A lower line would take that from calls
 // that have it.  Two groups of waves add in yet another order.
-static bool short_sequence(int B, int S, int H, int most) {
-  const i64 tokens = (i64)B * S, load = tokens * (H <= 4 ? 4 : H <= 8 ? 8 : H <= 16 ? 16 : 18) / 16;
-  if (S > 2048 || load > most) return false;
+static bool short_sequence(int B, int S, int H) {
+  const i64 tokens = (i64)B * S, heads = H > 16 ? 18 : S >= 1024 ? H : H > 8 ? 16 : H > 4 ? 8 : 4, load = tokens * heads / 16;
+  if (S > 2048 || load > (S >= 1024 ? 1536 : 1024)) return false;
   return H <= 16 || tokens * H <= 16 * (S >= 448 ? 2752 : S >= 256 ? 1856 : S >= 128 ? 1344 : 768);
 }
 
@@ -1042,7 +1048,7 @@ int launch_attn_fwd_flash(const void* q, const void* k, const void* v, void* o, 
   if (dh != DH || B <= 0 || S <= 0) return 1;
   if ((i64)S * H * DH * 2 >= ((i64)1 << 31)) return 1;      // one sequence of one tensor is addressed with 32-bit offsets
   if (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o) & 15) return 1;
-  if (short_sequence(B, S, H, S >= 1024 ? 1536 : 1024)) {
+  if (short_sequence(B, S, H)) {
     static std::atomic<unsigned long long> attr_mask{0};
     if (attr_needed(attr_mask)) {
       (void)hipFuncSetAttribute((const void*)flash_fwd_short_k, hipFuncAttributeMaxDynamicSharedMemorySize, SHORT_SMEM);
@@ -1073,7 +1079,7 @@ int launch_attn_bwd_flash(const void* q, const void* k, const void* v, const voi
        (uintptr_t)dv) & 15)
     return 1;
   const float scale = 1.0f / sqrtf((float)dh);
-  if (short_sequence(B, S, H, S >= 1024 ? 1280 : 1024)) {
+  if (short_sequence(B, S, H)) {
     const i64 rows = (i64)B * S * H;
     hipLaunchKernelGGL(flash_dvec_k, dim3((unsigned)cdiv(rows, 16)), dim3(256), 0, s, (const bf16*)o, (const bf16*)d_o, dvec, S, H, rows);
     static std::atomic<unsigned long long> attr_mask{0};

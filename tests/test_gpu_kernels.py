@@ -157,7 +157,7 @@ def test_flash_attention_ragged_long_sequence():
 
 # 128 queries per workgroup: one and two groups of waves (eight and more tiles), an odd and an even number of key tiles, the last of
 # 1, 63 and 64 keys; scores that rise slowly and fast, so that the running maximum goes up in every tile, then in none.  (1 x 1216, 17
-# heads: backward only, the forward pass takes 32 queries per workgroup.)
+# heads, takes 32 queries per workgroup; three such sequences, below, 128.)
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("B,S,H,rise", [(1, 2049, 2, 3.0), (1, 2111, 1, 11.0), (1, 1216, 17, 0.0), (3, 705, 16, 3.0), (3, 448, 16, 11.0)])
 def test_flash_attention_key_tiles(B, S, H, rise, causal):
@@ -165,11 +165,11 @@ def test_flash_attention_key_tiles(B, S, H, rise, causal):
 
 
 # Two groups of waves, group 1 on the odd tiles: 33 key tiles (it ends first) of which the last has 64 keys, 34 with a last one of 1 and
-# of 64 keys; maxima that differ between the groups where their results meet
+# of 64 keys; maxima that differ between the groups where their results meet.  And one group, 19 tiles, the last full.
 @pytest.mark.parametrize("causal", [True, False])
-@pytest.mark.parametrize("S,rise", [(2112, 3.0), (2113, 11.0), (2176, 3.0)])
-def test_flash_attention_two_groups_key_tiles(S, rise, causal):
-    _attention_case(1, S, 2, 128, causal, 2, 1, rise=rise)
+@pytest.mark.parametrize("B,S,H,rise", [(1, 2112, 2, 3.0), (1, 2113, 2, 11.0), (1, 2176, 2, 3.0), (3, 1216, 17, 0.0)])
+def test_flash_attention_two_groups_key_tiles(B, S, H, rise, causal):
+    _attention_case(B, S, H, 128, causal, 2, 1, rise=rise)
 
 
 # 128 queries per workgroup and no more key tiles than are on their way before the loop: one, two of which the second has 1, 36 and
@@ -225,6 +225,18 @@ def test_flash_attention_gradients_do_not_depend_on_the_grid(B, S, H, causal):
     for i in range(4):
         for a, b in zip(whole, run(i * n, i * n + n)):
             assert torch.isfinite(b).all() and torch.equal(a[:, i * n * 128:(i + 1) * n * 128], b)
+
+
+# The same where fewer heads than 16 decide for 32 queries per workgroup: what a quarter of the heads takes all of them take too
+@pytest.mark.parametrize("B,S,H", [(1, 1400, 12), (1, 1600, 12), (2, 1024, 8)])
+def test_flash_attention_some_heads_have_the_bits_of_all(B, S, H):
+    test_flash_attention_gradients_do_not_depend_on_the_grid(B, S, H, True)
+
+
+# 32 queries per workgroup for heads between 8 and 16, and for few heads of many sequences
+@pytest.mark.parametrize("B,S,H", [(1, 1400, 9), (1, 1800, 11), (2, 1100, 7), (5, 1024, 3)])
+def test_flash_attention_few_heads(B, S, H):
+    _attention_case(B, S, H, 128, True, 2, 1)
 
 
 @pytest.mark.parametrize("dtype", [0, 1])
