@@ -838,10 +838,17 @@ static int expert_rows_b(const revffn_ctx* c, i64 N, i64 E) {
 // results' bits are the same either way).  Us per launch, gate/up, down, dHh, dXg: 8 experts of 14336, 512 rows 1075, 635,
 // 513, 1250 / 910, 418, 517, 834 (320 tiles are two rounds of 256 CUs, 256 one); Qwen shape, 546 rows 464, 227, 245, 415 / 436, 206, 208, 367.
 // A step: 2 x 1024 tokens of the former 9030 -> 8340, 1200 6330 -> 5720, Qwen shape 4096 4860 -> 4645, 4600 5410 -> 5230, 8192 9390 -> 9210.
+// Not where a tile more per expert still is one round of CUs that takes most of them: then the taller tile only makes that round
+// longer.  By dXg's grid with that tile, as long as gate/up's is one round too; a step, us, 256 rows / up to 320, 275 rows unless said:
+// 192 (8 experts, 3072 wide) 1409 / 1449, 192 (8, 2048 wide, 520 rows) 1479 / 1491, 256 (8, 4096 wide) 2072 / 2121, 256 (16, 2048 wide)
+// 1519 / 1554; but 128 (8, 2048 wide) 976 / 962, 144 (12, 1536 wide) 762 / 756, 384 (16, 3072 wide) 2449 / 2431, 256 with a gate/up
+// of 352 (8, 4096 wide, experts of 2816) 2854 / 2734.
 static int expert_rows_c(const revffn_ctx* c, i64 N, i64 E) {
   if (c->expert_tile || c->expert_nt || c->expert_nn) return BM_C;
   const i64 mean = (N + E - 1) / E, over = mean % BM_C;
-  return mean >= 240 && (over <= 72 || over >= 240) ? BM_C_TALL : BM_C;
+  if (mean < 240 || (over > 72 && over < 240)) return BM_C;
+  const i64 tiles = ((mean + 16) / BM_C + 1) * E, dxg = tiles * cdiv(c->expert_width, 256), gate_up = tiles * cdiv(c->cfg.d_expert, 128);
+  return dxg > 160 && dxg <= 256 && gate_up <= 256 ? BM_C : BM_C_TALL;
 }
 
 // the geometry of the routing that an evaluation of the MoE half is about to make; width: of the routed experts' inputs and outputs

@@ -256,6 +256,18 @@ def test_block_parity_tall_expert_tiles(T):
     _backward_checks(case, case.up(case.x1), case.up(case.x2), y1d, TOL["bf16"])
 
 
+# As many rows, but 256 tiles of the data gradients with a tile more per expert, one round of the chip: tiles of 256 rows throughout
+def test_block_parity_expert_tiles_of_one_round():
+    wl = synth.Workload("one_round", 512, 4, 128, 64, 16, 72, 0, 1, 1040, "bf16", gain_jitter=0.02, seed=64)
+    case = Case(wl)
+    y1d, _ = case.forward()
+    _, mo = case.branches()
+    _, _, idx = check_routing(case, Hn.download(y1d))
+    ref, _ = O.moe_half_forward(Hn.download(y1d), case.W, case.ocfg, forced_idx=idx)
+    assert relerr(mo, ref) < TOL["bf16"]
+    _backward_checks(case, case.up(case.x1), case.up(case.x2), y1d, TOL["bf16"])
+
+
 # More expert weights than the memory-side cache holds: weights and gradients go past the caches, in the kernel for few rows (40
 # tokens, 2 rows per expert) and on 128x256 tiles (300 tokens; 2140: 107 rows per expert), with widths that end inside the tiles
 @pytest.mark.parametrize("S", [40, 300, 2140])
