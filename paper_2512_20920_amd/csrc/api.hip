@@ -331,10 +331,11 @@ int experts_kernel(const revffn_ctx* c, i64 rows, i64 N, i64 K, bool b_trans) {
   // shape: 16 tokens 925 / 895, 64 1050 / 993, 128 1105 / 1067, 240 (16 rows) 1284 / 1240, merged 37 tokens 323 / 294, 200 378 / 350;
   // 8 experts of 14336, 64 tokens 2416 / 2317, 80 (20 rows) 2505 / 2575 (experts of two tiles are read twice); 260 tokens
   // 1240 / 1337 (its workgroups leave no room for the shared expert's larger tiles beside them).  Data gradients with k long (dXg)
-  // are faster on 128x256 tiles, whose lines are 512 bytes: 64 tokens 108 / 116 us, unless an expert has a row or two:
-  // 20 tokens 101 / 93.  The rule looks at the mean.  Skewed, the hottest expert 8 times the mean, a step of 64, 128, 200, 240 tokens
+  // are faster on 128x256 tiles, whose lines are 512 bytes: 64 tokens 108 / 116 us alone; with a row or two per expert 20 tokens
+  // 101 / 93 alone, but a step of 16, 25, 30 tokens 912, 894, 980 / 997, 972, 1085 (with a k as long its weights do not go past the
+  // caches, see below, and it runs beside the weight gradients).  The rule looks at the mean.  Skewed, the hottest expert 8 times the mean, a step of 64, 128, 200, 240 tokens
   // 986, 1090, 1171, 1194 / 929, 1053, 1166, 1202, merged 37, 128, 240 285, 339, 386 / 251, 311, 364.
-  if (rows <= 16 * E && (!b_trans || K <= 2048 || (rows <= 2 * E && K <= 4096))) return 2;
+  if (rows <= 16 * E && (!b_trans || K <= 2048)) return 2;
   return 0;
 }
 

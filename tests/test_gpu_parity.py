@@ -282,7 +282,8 @@ def test_block_parity_weights_past_the_caches(S):
 
 
 # The kernel for expert weights that come from memory: 3 rows per expert and weights that stay in the caches; the most rows it is
-# given (16 on average: some experts end inside their row tile, some take two); a row or two and k past 2048 in every layout.
+# given (16 on average: some experts end inside their row tile, some take two); a row or two, with data gradients of a k past 2048
+# on 128x256 tiles and of one below it here.
 # Widths and contractions end inside a tile of 64 columns, of 32 gate columns and a piece of 64 k's.
 @pytest.mark.parametrize("E,k,I,S", [(64, 2, 600, 100), (64, 2, 600, 512), (60, 3, 1400, 40)])
 def test_block_parity_streamed_experts(E, k, I, S):
