@@ -256,6 +256,19 @@ def test_block_parity_tall_expert_tiles(T):
     _backward_checks(case, case.up(case.x1), case.up(case.x2), y1d, TOL["bf16"])
 
 
+# Experts of different rows in one call of that list: 241 to 324, 232 to 303, and skewed from none to all 1160
+@pytest.mark.parametrize("T,zipf", [(1160, False), (1028, False), (1160, True)])
+def test_block_parity_tall_tiles_of_uneven_experts(T, zipf):
+    wl = synth.Workload(f"uneven_{T}", 256, 2, 128, 16, 4, 520, 0, 1, T, "bf16", zipf=zipf, gain_jitter=0.02, seed=T)
+    case = Case(wl)
+    y1d, _ = case.forward()
+    _, mo = case.branches()
+    _, _, idx = check_routing(case, Hn.download(y1d))
+    ref, _ = O.moe_half_forward(Hn.download(y1d), case.W, case.ocfg, forced_idx=idx)
+    assert relerr(mo, ref) < TOL["bf16"]
+    _backward_checks(case, case.up(case.x1), case.up(case.x2), y1d, TOL["bf16"])
+
+
 # As many rows, but 256 tiles of the data gradients with a tile more per expert, one round of the chip: tiles of 256 rows throughout
 def test_block_parity_expert_tiles_of_one_round():
     wl = synth.Workload("one_round", 512, 4, 128, 64, 16, 72, 0, 1, 1040, "bf16", gain_jitter=0.02, seed=64)
