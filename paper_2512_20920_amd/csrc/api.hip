@@ -843,22 +843,27 @@ static int expert_rows_b(const revffn_ctx* c, i64 N, i64 E) {
 // longer.  By dXg's grid with that tile, as long as gate/up's is one round too; a step, us, 256 rows / up to 320, 275 rows unless said:
 // 192 (8 experts, 3072 wide) 1409 / 1449, 192 (8, 2048 wide, 520 rows) 1479 / 1491, 256 (8, 4096 wide) 2072 / 2121, 256 (16, 2048 wide)
 // 1519 / 1554; but 128 (8, 2048 wide) 976 / 962, 144 (12, 1536 wide) 762 / 756, 384 (16, 3072 wide) 2449 / 2431, 256 with a gate/up
-// of 352 (8, 4096 wide, experts of 2816) 2854 / 2734.
-static int expert_rows_c(const revffn_ctx* c, i64 N, i64 E) {
+// of 352 (8, 4096 wide, experts of 2816) 2854 / 2734.  That is a fused step with helper streams.  On one stream,
+// in a forward call (whose lists the backward of stored activations uses) and where a backward call evaluates the half itself
+// (`plain`), any one round is better without: forward and stored backward, 8 experts, 264 and 326 rows, 512 wide 342 / 352, 352 / 364,
+// 2048 wide 684 / 710, 758 / 787; three separate calls, 2048 wide, 296 and 312 rows, 1135 / 1149, 1325 / 1370.
+static int expert_rows_c(const revffn_ctx* c, i64 N, i64 E, bool plain) {
   if (c->expert_tile || c->expert_nt || c->expert_nn) return BM_C;
   const i64 mean = (N + E - 1) / E, over = mean % BM_C;
   if (mean < 240 || (over > 72 && over < 240)) return BM_C;
   const i64 tiles = ((mean + 16) / BM_C + 1) * E, dxg = tiles * cdiv(c->expert_width, 256), gate_up = tiles * cdiv(c->cfg.d_expert, 128);
-  return dxg > 160 && dxg <= 256 && gate_up <= 256 ? BM_C : BM_C_TALL;
+  const bool one_round = dxg <= 256 && gate_up <= 256;
+  return one_round && (plain || dxg > 160) ? BM_C : BM_C_TALL;
 }
 
-// the geometry of the routing that an evaluation of the MoE half is about to make; width: of the routed experts' inputs and outputs
-void moe_begin(revffn_ctx* c, int T, int width) {
+// the geometry of the routing that an evaluation of the MoE half is about to make; width: of the routed experts' inputs and outputs;
+// plain: not in an inversion
+void moe_begin(revffn_ctx* c, int T, int width, bool plain) {
   c->lastT = T;
   c->lastT_rows = T * c->cfg.top_k;
   c->expert_width = width;
   c->bm_b = expert_rows_b(c, c->lastT_rows, c->cfg.n_experts);
-  c->bm_c = expert_rows_c(c, c->lastT_rows, c->cfg.n_experts);
+  c->bm_c = expert_rows_c(c, c->lastT_rows, c->cfg.n_experts, plain || !c->par);
 }
 
 // The four GEMMs of the MoE half on inputs and outputs `width` wide (d_model; half of it with merged weights)
@@ -913,10 +918,10 @@ Riders riders(const revffn_ctx* c, const GemmArgs& g1, const GemmArgs& g2, const
 // Recomputes n3, Um, routing, GU, Hh, Yp, shared expert and RS at y1.  q_x1 != null: the query side of the attention
 // half at q_x1 (which must not depend on this MoE evaluation) is enqueued beside it and done when s goes on.
 int moe_acts(revffn_ctx* c, const revffn_weights* w, const void* y1, i64 ld, int T, hipStream_t s,
-             const void* q_x1 = nullptr, i64 q_ld = 0, int qB = 0, int qS = 0, const unsigned char* q_skip = nullptr) {
+             const void* q_x1 = nullptr, i64 q_ld = 0, int qB = 0, int qS = 0, const unsigned char* q_skip = nullptr, bool plain = false) {
   const revffn_config& f = c->cfg;
   const int d = f.d_model, k = f.top_k, Is = f.d_shared, dt = c->dt;
-  moe_begin(c, T, d);
+  moe_begin(c, T, d, plain);
   // The norm and the up-projection come first, then one fork (if there is work for it): the first query side and the shared expert
   // (which needs Um only) run beside the routing chain and the routed experts, and join where the results are combined.  An edge costs
   // the chain of launches more than the 6 us of the up-projection in front of the routing chain: with the routing chain
@@ -1052,7 +1057,7 @@ int moe_merged(revffn_ctx* c, const revffn_weights* w, const revffn_merged* m, c
                i64 ldr, float sign, void* dst, i64 ldd, int T, hipStream_t s) {
   const revffn_config& f = c->cfg;
   const int h = f.d_model / 2, k = f.top_k, Is = f.d_shared, dt = c->dt;
-  moe_begin(c, T, h);
+  moe_begin(c, T, h, true);
   hipStream_t s0 = side(c, s, 0);
   p_rmsnorm_fwd(c, dt, c->sdt, y1, ld, w->norm_m, c->n3, h, T, h, f.rms_eps, s);
   GemmArgs g1, g2, gs, gd;
@@ -1106,7 +1111,7 @@ int forward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const v
   const int T = B * S;
   TRY(attn_acts(c, w, x1, ld, x2, ld, B, S, true, s));
   TRY(attn_out(c, w, x1, ld, 1.f, y1, ld, T, s));                 // Eq. 1
-  TRY(moe_acts(c, w, y1, ld, T, s));
+  TRY(moe_acts(c, w, y1, ld, T, s, nullptr, 0, 0, 0, nullptr, true));
   TRY(moe_out(c, w, x2, ld, 1.f, y2, ld, T, s));                  // Eq. 2
   return 0;
 }
@@ -1208,7 +1213,7 @@ int backward_impl(revffn_ctx* c, const revffn_weights* w, const void* x1, const 
     reuse_moe = false;
   }
   // ---- recompute the MoE half at the exact y1
-  if (!reuse_moe) TRY(moe_acts(c, w, y1, ldy, T, s));
+  if (!reuse_moe) TRY(moe_acts(c, w, y1, ldy, T, s, nullptr, 0, 0, 0, nullptr, true));
   // ---- MoE half backward: Y2 = X2 + P_dn_m(RS)
   // Weight gradients are leaves of the computation.  With helper streams they run on sw, the experts' next to the data
   // gradients of the experts, the dense layers' known before the attention core's backward pass as one launch next to

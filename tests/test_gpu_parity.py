@@ -259,7 +259,7 @@ def test_block_parity_tall_expert_tiles(T):
 # Experts of different rows in one call of that list: 241 to 324, 232 to 303, and skewed from none to all 1160
 @pytest.mark.parametrize("T,zipf", [(1160, False), (1028, False), (1160, True)])
 def test_block_parity_tall_tiles_of_uneven_experts(T, zipf):
-    wl = synth.Workload(f"uneven_{T}", 256, 2, 128, 16, 4, 520, 0, 1, T, "bf16", zipf=zipf, gain_jitter=0.02, seed=T)
+    wl = synth.Workload(f"uneven_{T}", 256, 2, 128, 16, 4, 1032, 0, 1, T, "bf16", zipf=zipf, gain_jitter=0.02, seed=T)
     case = Case(wl)
     y1d, _ = case.forward()
     _, mo = case.branches()
