@@ -80,6 +80,7 @@ struct revffn_ctx {
   int expert_width = 0;       // width of the routed experts' inputs and outputs: d_model, half of it with merged weights
   int bm_b = 128;             // height of the tiles in list b for the routing in the workspace: 128, or 160 (see expert_rows_b)
   int bm_c = 256;             // height of the tiles in list c: 256, or 320 (see expert_rows_c)
+  int bm_c_kernel = 256;      // the height that experts_in_phases goes by: no call's, so that all calls get the same kernels
   int expert_nt = 0, expert_nn = 0;
   bool no_fused_swiglu = false; // REVFFN_NO_FUSED_SWIGLU (tuning aid): SwiGLU as a kernel of its own after the gate/up GEMM
   int expert_tile = 0;        // m-tile height of the MFMA expert GEMMs forced to 128 or 256 (REVFFN_EXPERT_TILE), 0 = by rows per expert
@@ -339,6 +340,20 @@ int experts_kernel(const revffn_ctx* c, i64 rows, i64 N, i64 K, bool b_trans) {
   return 0;
 }
 
+// Which tile a forward GEMM of the routed experts takes beyond few rows, for `rows` permuted rows, N outputs and last tiles of up to
+// bm_c rows: 256 (320) rows in phases where their rounds over the 256 CUs cost less than those of 128x256, a tile of 256
+// rows (with both phases at work) 1.8 times as much.  The two add in different orders, and the calls on one block promise each other's
+// bits, so the answer must not depend on the call (bm_c_kernel).  128x256 / this, us per launch, gate/up and down: 173 rows 241, 115 /
+// 220, 102   200: a step 3750 / 3680   273: 285, 151 / 248, 120   347: 306, 160 / 321, 175 (two tiles of which one is
+// mostly empty; the rule stays)   546: 495, 245 / 436, 206   8 experts of 14336, 175: down 221 / 316 (half the CUs; stays)
+bool experts_in_phases(i64 rows, i64 E, i64 N, int bm_c) {
+  const i64 mean = (rows + E - 1) / E, cols = (N + 255) / 256;
+  auto rounds = [&](i64 tiles) { return (double)((E * tiles * cols + 255) / 256); };
+  const i64 nt = mean <= bm_c ? 1 : (mean - (bm_c - BM_C) + BM_C - 1) / BM_C, last = mean - (nt - 1) * BM_C;
+  const double tile = 1.8 * ((nt - 1) + (last > 256 ? 1.25 : last > 128 ? 1.0 : 0.55)) / nt;
+  return rows > 152 * E && tile * rounds(nt) < rounds((mean + 127) / 128);
+}
+
 // Whether the shared expert's GEMM `d` goes into the launch of the routed experts' one `g`.  In calls that the kernels for few rows take,
 // a launch of its own is its place in the chain or, on a helper stream, a fork and a join of it, 13 us.
 bool rides(const revffn_ctx* c, const GemmArgs& g, const GemmArgs& d) {
@@ -430,15 +445,7 @@ int run_gemm(revffn_ctx* c, GemmArgs g, int ta, int tb, int tc, hipStream_t s) {
       const bool forced = shape != 0;
       if (!forced) {
         if (!g.b_trans) {
-          // Forward: 256 (320) rows in phases where their rounds over the 256 CUs cost less than those of 128x256, a tile of 256
-          // rows (with both phases at work) 1.8 times as much.  128x256 / this, us per launch, gate/up and down: 173 rows 241, 115 /
-          // 220, 102   200: a step 3750 / 3680   273: 285, 151 / 248, 120   347: 306, 160 / 321, 175 (two tiles of which one is
-          // mostly empty; the rule stays)   546: 495, 245 / 436, 206   8 experts of 14336, 175: down 221 / 316 (half the CUs; stays)
-          const i64 mean = (rows + E - 1) / E, cols = ((g.act_half ? 2 * g.act_half : g.N) + 255) / 256;
-          auto rounds = [&](i64 tiles) { return (double)((E * tiles * cols + 255) / 256); };
-          const i64 nt = mean <= c->bm_c ? 1 : (mean - (c->bm_c - BM_C) + BM_C - 1) / BM_C, last = mean - (nt - 1) * BM_C;
-          const double tile = 1.8 * ((nt - 1) + (last > 256 ? 1.25 : last > 128 ? 1.0 : 0.55)) / nt;
-          shape = rows > 152 * E && tile * rounds(nt) < rounds((mean + 127) / 128) ? 4 : 3;
+          shape = experts_in_phases(rows, E, g.act_half ? 2 * g.act_half : g.N, c->bm_c_kernel) ? 4 : 3;
         }
         else if (rows > 192 * E || (rows > one_tile && g.N % 256 == 0)) shape = 4;
         else shape = rows > one_tile ? 2 : 3;
@@ -845,8 +852,9 @@ static int expert_rows_b(const revffn_ctx* c, i64 N, i64 E) {
 // 1519 / 1554; but 128 (8, 2048 wide) 976 / 962, 144 (12, 1536 wide) 762 / 756, 384 (16, 3072 wide) 2449 / 2431, 256 with a gate/up
 // of 352 (8, 4096 wide, experts of 2816) 2854 / 2734.  That is a fused step with helper streams.  On one stream,
 // in a forward call (whose lists the backward of stored activations uses) and where a backward call evaluates the half itself
-// (`plain`), any one round is better without: forward and stored backward, 8 experts, 264 and 326 rows, 512 wide 342 / 352, 352 / 364,
-// 2048 wide 684 / 710, 758 / 787; three separate calls, 2048 wide, 296 and 312 rows, 1135 / 1149, 1325 / 1370.
+// (`plain`), any one round is better without: forward and stored backward, 8 experts of 1408, 512 wide, 264 and 326 rows 383 / 398,
+// 401 / 423, 2048 wide, 296 and 326 rows 796 / 838, 825 / 878, of 704, 264 and 326 rows 680 / 702, 754 / 782; three separate calls, of 1408,
+// 2048 wide 1285 / 1327, 1318 / 1372.
 static int expert_rows_c(const revffn_ctx* c, i64 N, i64 E, bool plain) {
   if (c->expert_tile || c->expert_nt || c->expert_nn) return BM_C;
   const i64 mean = (N + E - 1) / E, over = mean % BM_C;
@@ -864,6 +872,7 @@ void moe_begin(revffn_ctx* c, int T, int width, bool plain) {
   c->expert_width = width;
   c->bm_b = expert_rows_b(c, c->lastT_rows, c->cfg.n_experts);
   c->bm_c = expert_rows_c(c, c->lastT_rows, c->cfg.n_experts, plain || !c->par);
+  c->bm_c_kernel = expert_rows_c(c, c->lastT_rows, c->cfg.n_experts, false);
 }
 
 // The four GEMMs of the MoE half on inputs and outputs `width` wide (d_model; half of it with merged weights)

@@ -415,6 +415,29 @@ def test_inverse_backward_equals_the_two_calls(name):
             assert torch.equal(G[k], G3[k]), k
 
 
+# The height of the experts' last tiles depends on the call (an inversion or not, one stream or several); which kernel computes a
+# product must not, since they add in different orders: 264 and 520 rows per expert, whose gate/up grid is one round of the CUs with a tile
+# more per expert and two of 128x256 tiles, and 264 where it is one of both.
+@pytest.mark.parametrize("E,k,I,T", [(16, 4, 1024, 1056), (16, 8, 640, 1040), (16, 4, 640, 1056)])
+def test_expert_kernels_do_not_depend_on_the_call(E, k, I, T):
+    wl = synth.Workload(f"calls_{I}_{T}", 256, 2, 128, E, k, I, 0, 1, T, "bf16", gain_jitter=0.02, seed=T)
+    case = Case(wl)
+    case.ctx.set_inv_iters(1)
+    y1d, y2d = case.forward()
+    x1d, x2d = case.inverse(y1d, y2d)
+    dx1, dx2, G = case.backward(x1d, x2d, y1d)
+    for streams in (True, False):
+        case.ctx.set_helper_streams(streams)
+        a, b, ga, gb = y1d.clone(), y2d.clone(), case.up(case.dy1), case.up(case.dy2)
+        G2 = Hn.alloc_grads(case.Wd)
+        R.revffn_inverse_backward(case.ctx, case.Wd, a, b, a, b, ga, gb, ga, gb, G2, wl.B, wl.S, wl.h, None)
+        torch.cuda.synchronize()
+        assert torch.equal(a, x1d) and torch.equal(b, x2d) and torch.equal(ga, dx1) and torch.equal(gb, dx2), streams
+        for n in G:
+            if G[n] is not None:
+                assert torch.equal(G[n], G2[n]), (streams, n)
+
+
 @pytest.mark.parametrize("mode", [0, 1])
 def test_fp32_residual_streams(mode):
     """bf16 block with float32 residual streams (config.fp32_streams): same parity bar for every branch term and
